@@ -245,7 +245,6 @@ int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       (rc = check_ptrs((const void* const*)y_dev, p->P_fo, esz, "y")))
     return rc;
   if (b_dev && (rc = check_ptrs(b_dev, p->P_fo, esz, "b", true))) return rc;
-  if ((rc = prepare(p))) return rc;
   const bool bf16 = p->dtype == DISTDL_BF16;
   {  // matrix-core path: y_i = sum_j x_j W_ij^T + b_i, the sum over j inside the K loop
     std::vector<GemmBlock> blocks(p->P_fo);
@@ -261,6 +260,13 @@ int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const vo
         g.seg[j] = GemmSeg{x_dev[j], W_dev[i * p->P_fi + j], (int32_t)p->fi_size[j], (int32_t)p->fi_size[j],
                            (int32_t)p->fi_size[j], 0};
     }
+    if ((!bf16 || !gemm_mfma_usable(blocks, bf16, true, true)) && gemm_split_usable(blocks, bf16, true, true)) {
+      const GemmSplitPlan sp = gemm_split_plan(blocks, gemm_split_vec(blocks, bf16, true, true));
+      if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = ensure_partial(p, sp.partial_floats))) return rc;
+      if ((rc = launch_gemm_split_fwd(p->g_fwd.dev, blocks, bf16, sp, p->d_partial, st_))) return rc;
+      DISTDL_HIP_TRY(hipGetLastError());
+      return DISTDL_OK;
+    }
     if (gemm_mfma_usable(blocks, bf16, true, true)) {
       const int ns = gemm_mfma_splits(blocks, bf16, true);
       if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = ensure_partial(p, gemm_mfma_partial_floats(blocks, ns)))) return rc;
@@ -269,7 +275,7 @@ int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       return DISTDL_OK;
     }
   }
-  if ((rc = p->tab_x.upload(x_dev, p->P_fi, st_)) || (rc = p->tab_W.upload(W_dev, p->P_fo * p->P_fi, st_)) ||
+  if ((rc = prepare(p)) || (rc = p->tab_x.upload(x_dev, p->P_fi, st_)) || (rc = p->tab_W.upload(W_dev, p->P_fo * p->P_fi, st_)) ||
       (rc = p->tab_y.upload((const void* const*)y_dev, p->P_fo, st_)))
     return rc;
   if (b_dev && (rc = p->tab_b.upload(b_dev, p->P_fo, st_))) return rc;
@@ -291,7 +297,6 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       (rc = check_ptrs((const void* const*)dW_dev, p->P_fo * p->P_fi, esz, "dW")))
     return rc;
   if (db_dev && (rc = check_ptrs((const void* const*)db_dev, p->P_fo, esz, "db", true))) return rc;
-  if ((rc = prepare(p))) return rc;
   const bool bf16 = p->dtype == DISTDL_BF16;
   {  // matrix-core path
     std::vector<GemmBlock> bx(p->P_fi), bw((size_t)p->P_fo * p->P_fi);
@@ -319,6 +324,30 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       }
       bb[i] = ColsumBlock{dy_dev[i], db_dev ? db_dev[i] : nullptr, (int32_t)p->n_b, (int32_t)p->fo_size[i]};
     }
+    if ((!bf16 || !(gemm_mfma_usable(bx, bf16, true, false) && gemm_mfma_usable(bw, bf16, false, false))) &&
+        gemm_split_usable(bx, bf16, true, false) && gemm_split_usable(bw, bf16, false, false)) {
+      const bool vec = gemm_split_vec(bx, bf16, true, false) && gemm_split_vec(bw, bf16, false, false);
+      const GemmSplitPlan px = gemm_split_plan(bx, vec);
+      GemmSplitPlan pw = gemm_split_plan(bw, vec);
+      // At most 32 samples: dW is bound by writing it, and the fp32 kernel that holds four 32 KB workgroups per compute
+      // unit writes faster than the split one with three of 49 KB (4096 x 4096 per worker, 16 samples: 57 against 92 us;
+      // 2048 x 2048: 16 samples 20 against 23 us, 32 equal, 64 samples 31 against 28 us).
+      const bool dw_stream = !bf16 && vec && pw.T == 2 && p->n_b <= 32 && gemm_stream_usable(bw, false, false, false);
+      if (dw_stream) pw.wgs = 0, pw.nsplit = 1, pw.partial_floats = 0;
+      if ((rc = p->g_dx.upload(bx, st_)) || (rc = p->g_dw.upload(bw, st_)) || (db_dev && (rc = p->g_db.upload(bb, st_))) ||
+          (rc = ensure_partial(p, px.partial_floats + pw.partial_floats)))
+        return rc;
+      const ColsumBlock* cs = db_dev ? p->g_db.dev : nullptr;
+      if ((rc = launch_gemm_split_bwd(p->g_dx.dev, bx, px, p->g_dw.dev, bw, pw, cs, p->P_fo, (int)p->max_fo, bf16,
+                                      p->d_partial, st_)))
+        return rc;
+      if (dw_stream) {
+        ProfScope prof("affine_bwd_w_mfma", st_);
+        if ((rc = launch_gemm_stream_tt(p->g_dw.dev, bw, false, nullptr, 0, 0, st_))) return rc;
+      }
+      DISTDL_HIP_TRY(hipGetLastError());
+      return DISTDL_OK;
+    }
     if (gemm_mfma_usable(bx, bf16, true, false) && gemm_mfma_usable(bw, bf16, false, false)) {
       const int nsx = gemm_mfma_splits(bx, bf16, true), nsw = gemm_mfma_splits(bw, bf16, false);
       if ((rc = p->g_dx.upload(bx, st_)) || (rc = p->g_dw.upload(bw, st_)) ||
@@ -343,7 +372,7 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       return DISTDL_OK;
     }
   }
-  if ((rc = p->tab_x.upload(x_dev, p->P_fi, st_)) || (rc = p->tab_W.upload(W_dev, p->P_fo * p->P_fi, st_)) ||
+  if ((rc = prepare(p)) || (rc = p->tab_x.upload(x_dev, p->P_fi, st_)) || (rc = p->tab_W.upload(W_dev, p->P_fo * p->P_fi, st_)) ||
       (rc = p->tab_dy.upload(dy_dev, p->P_fo, st_)) ||
       (rc = p->tab_dx.upload((const void* const*)dx_dev, p->P_fi, st_)) ||
       (rc = p->tab_dW.upload((const void* const*)dW_dev, p->P_fo * p->P_fi, st_)))

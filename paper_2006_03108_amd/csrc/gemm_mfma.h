@@ -55,6 +55,23 @@ int launch_gemm_stream(const GemmBlock* d_blocks, const std::vector<GemmBlock>& 
 // d_colsum (or null): column sums (the bias gradient) computed by extra workgroups of the same launch
 int launch_gemm_stream_tt(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool bf16,
                           const ColsumBlock* d_colsum, int n_colsum, int max_f, hipStream_t st);
+// Any shape and alignment (gemm_split.hip): fp32 operands on the bf16 matrix cores, bf16 ones as they are.
+struct GemmSplitPlan {
+  int T = 1;         // workgroup tile / 64
+  bool vec = false;  // operands move in 16-byte pieces and 8-byte pairs
+  int tiles = 0, nsplit = 1, wgs = 0;
+  int64_t max_mn = 0;
+  size_t partial_floats = 0;  // of the fp32 partial tiles
+};
+bool gemm_split_usable(const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc);
+bool gemm_split_vec(const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc);
+GemmSplitPlan gemm_split_plan(const std::vector<GemmBlock>& blocks, bool vec);
+int launch_gemm_split_fwd(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool bf16,
+                          const GemmSplitPlan& p, float* partial, hipStream_t st);
+// dx, dW and (d_cs not null) db in one launch; both plans with the same `vec`; `partial` holds px's floats, then pw's
+int launch_gemm_split_bwd(const GemmBlock* d_bx, const std::vector<GemmBlock>& bx, const GemmSplitPlan& px,
+                          const GemmBlock* d_bw, const std::vector<GemmBlock>& bw, const GemmSplitPlan& pw,
+                          const ColsumBlock* d_cs, int n_cs, int max_f, bool bf16, float* partial, hipStream_t st);
 int launch_colsum(const ColsumBlock* d_blocks, int nblocks, int max_f, bool bf16, hipStream_t st);
 
 }  // namespace distdl

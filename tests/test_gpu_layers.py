@@ -768,3 +768,63 @@ def test_conv_step_replayed_from_a_graph_matches_eager(dtype):
         torch.cuda.synchronize()
         for got, ref in zip(snapshot(), want):
             assert torch.equal(got, ref)
+
+
+# K tails of 1 .. 15, tiles of 64 and 128 with remainders, K split over workgroups, two and more segments, operands
+# whose rows are no whole 16-byte pieces; the last ones: dW in a launch of its own, and at most 32 samples
+AFFINE_SPLIT_CASES = [(1, 1, 1, 1, 1), (2, 17, 3, 1, 1), (65, 129, 67, 2, 3), (64, 64, 64, 1, 1), (63, 1025, 130, 1, 2),
+                      (129, 260, 388, 2, 2), (128, 2052, 256, 1, 1), (40, 4100, 68, 1, 4), (260, 3600, 3584, 1, 1),
+                      (32, 1028, 1028, 2, 2), (33, 1028, 1028, 2, 2)]
+
+
+@pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "odd"])
+@pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi", AFFINE_SPLIT_CASES)
+def test_affine_split_against_fp64(n_b, n_fi, n_fo, P_fo, P_fi, offset):
+    """fp32 layers on the split bf16 products, against fp64 sums on the device; the arrays start `offset` elements into
+    an allocation.  A sum of K products of the split is off by at most K / 16 + 2 roundings of 2^-24 of its running
+    sum (random walk: about sqrt(K / 16) of them): 1e-6 in the 2-norm is more than twice what that gives at K = 4100."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(n_b * 7919 + n_fi)
+    new = lambda *shape: torch.randn(int(np.prod(shape)) + offset, generator=g, device="cuda")[offset:].view(shape)
+    rows, cols = layers.feature_blocks(n_fo, P_fo), layers.feature_blocks(n_fi, P_fi)
+    size = lambda s: s.stop - s.start
+    x, dy = [new(n_b, size(c)) for c in cols], [new(n_b, size(r)) for r in rows]
+    W, b = [new(size(r), size(c)) for r in rows for c in cols], [new(size(r)) for r in rows]
+    y, dx, dW, db = ([new(*t.shape) for t in ts] for ts in (dy, x, W, b))
+    plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi)
+    dd.distdl_affine_fwd(plan, x, W, b, y)
+    dd.distdl_affine_bwd(plan, x, W, dy, dx, dW, db)
+    err = lambda got, want: float((got.double() - want).norm() / want.norm().clamp_min(1e-300))
+    d = lambda ts: [t.double() for t in ts]
+    x, dy, W, b = d(x), d(dy), d(W), d(b)
+    for i in range(P_fo):
+        assert err(y[i], sum(x[j] @ W[i * P_fi + j].t() for j in range(P_fi)) + b[i]) < 1e-6
+        assert err(db[i], dy[i].sum(0)) < 1e-6
+        for j in range(P_fi):
+            assert err(dW[i * P_fi + j], dy[i].t() @ x[j]) < 1e-6
+    for j in range(P_fi):
+        assert err(dx[j], sum(dy[i] @ W[i * P_fi + j] for i in range(P_fo))) < 1e-6
+
+
+@pytest.mark.parametrize("n_b,n_fi,n_fo", [(70, 100, 130), (256, 1024, 1024), (37, 333, 77)])
+def test_affine_infinities_and_nans_stay_what_fp32_makes_of_them(n_b, n_fi, n_fo):
+    """The split of an infinity, a NaN or a number next to the largest is no number; the sums they enter have to be
+    what fp32 products give: an infinity where one term is infinite, NaN where terms cancel, finite otherwise."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(5)
+    new = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    x, W, dy = new(n_b, n_fi), new(n_fo, n_fi), new(n_b, n_fo)
+    x[0, 3], x[1, 5], x[2, 7], x[2, 8] = float("inf"), float("-inf"), float("nan"), 1.0
+    x[3, 0], W[:, 0] = 3.4e38, 0.25             # rounds to an infinite bf16, its products are finite
+    dy[3, :] = 0.5                               # (so are those of dW)
+    W[4, :] = 0.0                                # 0 * inf
+    plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, 1, 1)
+    y, dx, dW = torch.empty(n_b, n_fo, device="cuda"), torch.empty_like(x), torch.empty_like(W)
+    dd.distdl_affine_fwd(plan, [x], [W], None, [y])
+    dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], None)
+    for got, want in ((y, x.double() @ W.double().t()), (dx, dy.double() @ W.double()), (dW, dy.double().t() @ x.double())):
+        finite = want.abs() < 3e38
+        assert torch.equal(torch.isnan(got), torch.isnan(want))
+        assert torch.equal(got == float("inf"), want > 3.5e38) and torch.equal(got == float("-inf"), want < -3.5e38)
+        scale = want[finite].abs().clamp_min(1.0)
+        assert float(((got[finite].double() - want[finite]).abs() / scale).max()) < 1e-4
