@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "conv_any.h"
 #include "conv_core.h"
 #include "conv_mfma.h"
 #include "profile.h"
@@ -259,6 +260,7 @@ size_t distdl_conv_bwd_workspace(const distdl_plan* plan) {
   size_t nw = (size_t)c.taps * c.ci * c.co + c.co;
   int chunks = direct_chunks(plan);
   if (wgrad_mfma_supported(plan)) chunks = std::max(chunks, wgrad_chunks(plan));
+  if (conv_any_supported(plan)) chunks = std::max(chunks, wgrad_any_chunks(plan));
   chunks = std::max(chunks, std::max(wgrad16_chunks(plan, true), wgrad16_chunks(plan, false)));
   return nw * sizeof(float) * plan->n_workers * chunks;
 }
@@ -337,6 +339,11 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
     DISTDL_HIP_TRY(hipGetLastError());
     return DISTDL_OK;
   }
+  if (conv_any_supported(plan)) {
+    if ((rc = conv_fwd_any(plan, w_dev, bias_dev, xvec, st))) return rc;
+    DISTDL_HIP_TRY(hipGetLastError());
+    return DISTDL_OK;
+  }
   if ((rc = prepare_weights(plan, w_dev, st))) return rc;
   ConvDev c = conv_params(plan);
   int64_t total = plan->n_b * plan->max_out_cells * c.co;
@@ -380,14 +387,19 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   bool vec16 = aligned && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
   for (int w = 0; w < plan->n_workers; ++w) vec16 &= (uintptr_t)x_bufs_dev[w] % 16 == 0;
   const bool wgrad16 = wgrad16_supported(plan, vec16);
-  const bool wgrad_mfma = !wgrad16 && wgrad_mfma_supported(plan) && plan->n_workers * wgrad_chunks(plan) <= 65535 &&
-                          (!bf16 || vec16);
+  // 32-wide: the plane-per-workgroup kernel where its shape fits; else the gather kernel, which takes any shape of
+  // tensors under 2 GiB; the kernels that read their operands from memory for what is larger
+  const bool wgrad_fits = !wgrad16 && wgrad_mfma_supported(plan) && plan->n_workers * wgrad_chunks(plan) <= 65535;
+  const bool wgrad_any = !wgrad16 && !(wgrad_fits && vec16 && wgrad_taps_supported(plan)) && conv_any_supported(plan);
+  const bool wgrad_mfma = wgrad_fits && !wgrad_any && (!bf16 || vec16);
   // [dConv]* with respect to x, into the whole padded buffers
   int64_t total = plan->n_b * plan->max_buf_cells * c.ci;
   if (corr16_bwd_supported(plan, aligned)) {
     if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
   } else if (data_mfma) {
     if ((rc = conv_bwd_data_mfma(plan, w_dev, st))) return rc;
+  } else if (conv_any_supported(plan)) {
+    if ((rc = conv_bwd_data_any(plan, w_dev, aligned, st))) return rc;
   } else {
     if ((rc = prepare_weights(plan, w_dev, st))) return rc;
     ProfScope prof("conv_bwd_data_direct", st);
@@ -400,10 +412,12 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
                          plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
   }
   // [dConv]* with respect to w and b, then R over the workers
-  int nchunks = wgrad16 ? wgrad16_chunks(plan, vec16) : wgrad_mfma ? wgrad_chunks(plan) : direct_chunks(plan);
+  int nchunks = wgrad16 ? wgrad16_chunks(plan, vec16) : wgrad_any ? wgrad_any_chunks(plan) : wgrad_mfma ? wgrad_chunks(plan) : direct_chunks(plan);
   int nw = c.taps * c.ci * c.co + c.co;
   if (wgrad16) {
     if ((rc = conv_wgrad16(plan, (float*)workspace_dev, vec16, st))) return rc;
+  } else if (wgrad_any) {
+    if ((rc = conv_wgrad_any(plan, (float*)workspace_dev, st))) return rc;
   } else if (wgrad_mfma) {
     if ((rc = conv_wgrad_mfma(plan, (float*)workspace_dev, st))) return rc;
   } else {

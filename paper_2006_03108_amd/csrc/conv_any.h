@@ -1,0 +1,14 @@
+// Convolution kernels for any shape whose tensors are addressed by 31-bit byte offsets (conv_any.hip).  The entry
+// points expect the plan's pointer tables to be uploaded; `aligned`: the arrays that are read are 16-byte aligned.
+#pragma once
+#include "common.h"
+
+namespace distdl {
+
+bool conv_any_supported(const distdl_plan* p);
+int conv_fwd_any(distdl_plan* p, const void* w, const void* bias, bool aligned, hipStream_t st);
+int conv_bwd_data_any(distdl_plan* p, const void* w, bool aligned, hipStream_t st);
+int wgrad_any_chunks(const distdl_plan* p);
+int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st);
+
+}  // namespace distdl

@@ -1,0 +1,851 @@
+// Local convolution (Sec. 4, "Conv" and "[dConv]*" steps) of any channel count, kernel width, stride and dilation on
+// the matrix cores: the layers whose shapes the patch kernels (conv_mfma.hip, conv_small.hip) do not take, for
+// instance three input channels, or 7 x 7 kernels.  fp32 tensors are multiplied as three bf16 planes (split_bf16.h),
+// bf16 tensors as they are; accumulation in fp32.
+//
+// Both kernels are one product C[row][col] = sum_k A[row][k] B[k][col] with 256 (or 64) rows and 32 NT columns per
+// workgroup.  The values of a stage are gathered straight from the tensor, split and written to LDS as MFMA operand
+// pieces (8 k of one row).
+//   corr_any_kernel: rows are output positions, columns output channels, k = (tap, channel) with the channel fastest and
+//     without padding (three channels of 49 taps are 147 k, not 49 x 8).  Data gradient: one class of the cells of dx^
+//     per residue modulo the stride, all classes in one launch; a tap whose output does not exist reads as zero.
+//     256 rows, 32 k per stage: wave w multiplies rows 64 w ... + 63 (2 x NT MFMA tiles).  64 rows, 128 k per stage, for
+//     layers with too few positions to fill the chip: every wave multiplies all rows for its 32 k, and the four partial
+//     tiles are added through LDS, in wave order.
+//     Channel counts that are multiples of 4: neighbouring lanes load neighbouring pieces of 4 channels (with a lane per
+//     row the 64 lanes of a load touch 64 lines, and the chip then loads 15 bytes per clock and compute unit: data
+//     gradient of 8 x 224 x 224, 3 -> 32 channels, 7 x 7: 156 us).  Other counts: a lane per row, and the offset of a
+//     k, the same for all lanes, goes into the scalar offset of the load.
+//   wgrad_any_kernel: rows are k, columns output channels, the sum runs over output positions; the offset that all
+//     lanes share is that of the position.  Every (worker, chunk of positions) writes a partial, which also holds the
+//     chunk's part of db^.
+// Offsets that the lanes share are computed by the lanes, one each, and read out with v_readlane.
+// fp32: the hi * hi products have an accumulator of their own, see gemm_split.hip.
+#include <algorithm>
+
+#include "common.h"
+#include "conv_any.h"
+#include "conv_mfma.h"
+#include "profile.h"
+#include "split_bf16.h"
+
+namespace distdl {
+
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GiB)
+constexpr int kMaxCls = 64;
+
+struct AnyArgs {
+  int32_t mode;          // 0: forward, 1: data gradient
+  int32_t n_b, kc, nc;   // batch, contraction channels, output channels
+  int32_t k[3], s[3], dil[3];
+  int32_t n_workers, ntn, ncls, tiles_max;
+  int32_t ci, co, taps;
+  const u32x4* wt;         // weights as operand pieces
+  const void* w;           // the caller's weights
+  const void* bias;        // may be null
+  int32_t woff[kMaxCls];   // first octet of a class's weights
+};
+
+struct WgradAnyArgs {
+  int32_t n_b, ci, co;
+  int32_t k[3], s[3], dil[3];
+  int32_t nchunks, ntm, ntn;  // position chunks per worker, row tiles, column tiles
+  int32_t rows;               // taps * ci
+  int64_t slot;
+};
+
+template <bool BF16>
+struct Elem {
+  typedef float T;
+};
+template <>
+struct Elem<true> {
+  typedef uint16_t T;
+};
+
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+template <bool BF16>
+__device__ inline float load1(__amdgpu_buffer_rsrc_t rs, uint32_t vo, uint32_t so) {
+  if constexpr (BF16) return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, vo, so, 0) << 16);
+  else return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, vo, so, 0));
+}
+template <bool BF16>
+__device__ inline void load4(float* v, __amdgpu_buffer_rsrc_t rs, uint32_t vo, uint32_t so) {
+  if constexpr (BF16) {
+    const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, vo, so, 0);
+    v[0] = __uint_as_float(t[0] << 16), v[1] = __uint_as_float(t[0] & 0xffff0000u);
+    v[2] = __uint_as_float(t[1] << 16), v[3] = __uint_as_float(t[1] & 0xffff0000u);
+  } else {
+    const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, so, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(t[e]);
+  }
+}
+
+// One dimension of a launch: the taps that take part and the input coordinate of the first one for output position q,
+// in0 + q * step, and from one to the next, + dt.
+struct DimAny {
+  int32_t nt, tf, ts;      // taps tf, tf + ts, ...
+  int32_t step, in0, dt;   // input coordinate of tap i at position q: in0 + q * step + i * dt
+  int32_t nq, in_ext, out_ext, out0, ostep;
+};
+__host__ __device__ inline int gcd_of(int a, int b) {
+  while (b) {
+    const int t = a % b;
+    a = b, b = t;
+  }
+  return a;
+}
+// taps along one dimension of parity class `par`: t * dil == par modulo s
+__host__ __device__ inline void class_taps(int k, int s, int dil, int par, int& nt, int& tf, int& ts) {
+  ts = s / gcd_of(dil, s);
+  tf = 0;
+  while (tf < ts && (tf * dil) % s != par) ++tf;
+  nt = tf < ts && tf < k ? (k - 1 - tf) / ts + 1 : 0;
+}
+__device__ inline DimAny dim_any(const WorkerDev& wd, const AnyArgs& a, int d, int par) {
+  DimAny g;
+  if (a.mode == 0) {
+    g.nt = a.k[d], g.tf = 0, g.ts = 1;
+    g.step = a.s[d], g.in0 = wd.origin[d], g.dt = a.dil[d];
+    g.nq = g.out_ext = wd.out[d], g.in_ext = wd.buf[d], g.out0 = 0, g.ostep = 1;
+  } else {
+    const int s = a.s[d], op = wd.origin[d] + par, first = op % s;  // first buffer cell of the class
+    class_taps(a.k[d], s, a.dil[d], par, g.nt, g.tf, g.ts);
+    // cell first + s q is origin + par + s (q - op / s): tap t reads dy[(q - op / s) - (t dil - par) / s]
+    g.step = 1, g.in0 = -(op / s) - (g.tf * a.dil[d] - par) / s, g.dt = -(g.ts * a.dil[d] / s);
+    g.nq = first < wd.buf[d] ? (wd.buf[d] - 1 - first) / s + 1 : 0;
+    g.in_ext = wd.out[d], g.out_ext = wd.buf[d], g.out0 = first, g.ostep = s;
+  }
+  return g;
+}
+
+constexpr int planes_of(bool bf16) { return bf16 ? 1 : 3; }
+// ROWS rows x KS octets of k per stage: 1024 pieces of A
+constexpr int octets_of(int ROWS) { return 1024 / ROWS; }
+// a little more than the planes, so that the pieces that eight neighbouring lanes write fall into different banks
+constexpr uint32_t a_pitch(int ROWS, bool bf16) { return planes_of(bf16) * ROWS * 16 + (ROWS == 256 ? 32 : 16); }
+constexpr uint32_t b_pitch(int NT, bool bf16) { return planes_of(bf16) * 32 * NT * 16 + 16; }
+constexpr int any_lds(int ROWS, int NT, bool bf16) {
+  const int stage = octets_of(ROWS) * (int)(a_pitch(ROWS, bf16) + b_pitch(NT, bf16));
+  return std::max(stage, ROWS == 64 ? 4 * 64 * 32 * NT * 4 : 0) + ROWS * 4;  // (64 rows: four partial tiles at the end)
+}
+constexpr int kOctPad = 16;  // a class's weights are padded to whole stages of either kind
+
+// n / d for n, d < 2^22 through the reciprocal
+__device__ inline int div_by(int n, int d, float rcp) {
+  int q = (int)((float)n * rcp);
+  q -= q * d > n;
+  q += (q + 1) * d <= n;
+  return q;
+}
+
+// eight values -> the operand pieces of one (octet, row)
+template <bool BF16>
+__device__ inline void put_octet(char* at, uint32_t plane, const float (&v)[8]) {
+  if constexpr (BF16) {
+    u32x4 h;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) h[j] = pack_bf16(v[2 * j], v[2 * j + 1]);  // exact
+    *(u32x4*)at = h;
+  } else {
+    u32x4 h, m, l;
+    split_eight(v, h, m, l);
+    *(u32x4*)at = h;
+    *(u32x4*)(at + plane) = m;
+    *(u32x4*)(at + 2 * plane) = l;
+  }
+}
+
+// the products of two 16-k slices, smallest first; la, lb: this wave's first row and octet
+template <int ROWS, int NT, bool BF16>
+__device__ inline void multiply_stage(floatx16 (&acc)[2][NT], floatx16 (&low)[2][NT], const char* la, const char* lb, int lane) {
+  union Frag {
+    u32x4 u;
+    bf16x8 v;
+  };
+  constexpr int PL = planes_of(BF16);
+  const int h = lane >> 5, ml = lane & 31;
+#pragma unroll
+  for (int sl = 0; sl < 2; ++sl) {
+    Frag fa[PL][2], fb[PL][NT];
+#pragma unroll
+    for (int p = 0; p < PL; ++p) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        fa[p][t].u = *(const u32x4*)(la + (2 * sl + h) * a_pitch(ROWS, BF16) + (p * ROWS + 32 * t + ml) * 16);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        fb[p][t].u = *(const u32x4*)(lb + (2 * sl + h) * b_pitch(NT, BF16) + (p * 32 * NT + 32 * t + ml) * 16);
+    }
+    auto mm = [&](floatx16 (&c)[2][NT], int pa, int pb) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa][i].v, fb[pb][j].v, c[i][j], 0, 0, 0);
+    };
+    if constexpr (!BF16) {
+      mm(low, 2, 0);
+      mm(low, 0, 2);
+      mm(low, 1, 1);
+      mm(low, 1, 0);
+      mm(low, 0, 1);
+    }
+    mm(acc, 0, 0);
+  }
+}
+template <int NT, bool BF16>
+struct Sums {
+  floatx16 acc[2][NT], low[2][NT];
+  __device__ inline Sums() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = low[i][j][e] = 0.f;
+  }
+  __device__ inline void finish() {
+    if constexpr (!BF16) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] += low[i][j];
+    }
+  }
+};
+
+// output element (position, channel) once more, term by term in fp32
+__device__ inline float corr_direct(const AnyArgs& a, const DimAny& g0, const DimAny& g1, const DimAny& g2, const float* in, int q0,
+                                   int q1, int q2, int n, int ch) {
+  float sum = 0.f;
+  for (int i0 = 0; i0 < g0.nt; ++i0)
+    for (int i1 = 0; i1 < g1.nt; ++i1)
+      for (int i2 = 0; i2 < g2.nt; ++i2) {
+        const int c0 = g0.in0 + q0 * g0.step + i0 * g0.dt, c1 = g1.in0 + q1 * g1.step + i1 * g1.dt,
+                  c2 = g2.in0 + q2 * g2.step + i2 * g2.dt;
+        if (c0 < 0 || c0 >= g0.in_ext || c1 < 0 || c1 >= g1.in_ext || c2 < 0 || c2 >= g2.in_ext) continue;
+        const int tap = ((g0.tf + i0 * g0.ts) * a.k[1] + g1.tf + i1 * g1.ts) * a.k[2] + g2.tf + i2 * g2.ts;
+        const float* x = in + ((((size_t)n * g0.in_ext + c0) * g1.in_ext + c1) * g2.in_ext + c2) * a.kc;
+        for (int c = 0; c < a.kc; ++c) {
+          const int o = a.mode == 0 ? ch : c, i = a.mode == 0 ? c : ch;
+          sum = fmaf(x[c], ((const float*)a.w)[((size_t)o * a.ci + i) * a.taps + tap], sum);
+        }
+      }
+  return sum;
+}
+
+template <int ROWS, int NT, bool BF16, int MODE, bool VEC>
+__global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __restrict__ workers, void* const* in_bufs,
+                                                          void* const* out_bufs, AnyArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr uint32_t ES = BF16 ? 2 : 4;
+  constexpr int PL = planes_of(BF16), KS = octets_of(ROWS);
+  constexpr bool FLAT = MODE == 0 || VEC;  // k without padding; else the octets of a tap are its own
+  // consecutive tiles share input rows and stay on one XCD (one L2)
+  const uint32_t nblk = gridDim.x, r = (blockIdx.x & 7u) * (nblk >> 3) + (blockIdx.x >> 3);
+  const uint32_t worker = r / a.tiles_max;
+  int tile = (int)(r - worker * a.tiles_max);
+  if (worker >= (uint32_t)a.n_workers) return;
+  const WorkerDev wd = workers[worker];
+  const int cls = (int)blockIdx.y;
+  const int c12 = a.s[1] * a.s[2];
+  const DimAny g0 = dim_any(wd, a, 0, MODE == 0 ? 0 : cls / c12), g1 = dim_any(wd, a, 1, MODE == 0 ? 0 : cls / a.s[2] % a.s[1]),
+               g2 = dim_any(wd, a, 2, MODE == 0 ? 0 : cls % a.s[2]);
+  const int ntile = tile % a.ntn;
+  tile /= a.ntn;
+  const int64_t total = (int64_t)a.n_b * g0.nq * g1.nq * g2.nq;
+  if ((int64_t)tile * ROWS >= total) return;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ml = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t sc1 = (uint32_t)g2.in_ext * a.kc, sc0 = (uint32_t)g1.in_ext * sc1, scn = (uint32_t)g0.in_ext * sc0;
+  const uint32_t so1 = (uint32_t)g2.out_ext * a.nc, so0 = (uint32_t)g1.out_ext * so1, son = (uint32_t)g0.out_ext * so0;
+  const __amdgpu_buffer_rsrc_t rin = rsrc_of(in_bufs[worker], (uint32_t)a.n_b * scn * ES);
+  const __amdgpu_buffer_rsrc_t rout = rsrc_of(out_bufs[worker], (uint32_t)a.n_b * son * ES);
+
+  // a row's sample and position; false: beyond the last
+  auto position = [&](int row, int& n, int& q0, int& q1, int& q2) {
+    const int64_t pos = (int64_t)tile * ROWS + row;
+    if (pos >= total) return false;
+    uint32_t t = (uint32_t)pos;  // (fewer than 2^31 positions: the tensors are < 2 GiB)
+    q2 = (int)(t % (uint32_t)g2.nq); t /= (uint32_t)g2.nq;
+    q1 = (int)(t % (uint32_t)g1.nq); t /= (uint32_t)g1.nq;
+    q0 = (int)(t % (uint32_t)g0.nq);
+    n = (int)(t / (uint32_t)g0.nq);
+    return true;
+  };
+  // The rows this thread gathers: VEC: octet tid % KS of row tid / KS + i * (256 / KS); else row tid % ROWS, whose octets
+  // (wave of the row) + (256 / ROWS) * o it takes.
+  constexpr int NR = VEC ? 4 : 1;
+  uint32_t base[NR];
+  int p0[NR], p1[NR], p2[NR];  // input coordinates of tap 0 (data gradient: they may lie outside)
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int row = VEC ? tid / KS + i * (256 / KS) : tid % ROWS;
+    int n, q0, q1, q2;
+    base[i] = kOob;
+    p0[i] = -0x40000000, p1[i] = p2[i] = 0;  // no tap of such a row is in range
+    if (position(row, n, q0, q1, q2)) {
+      p0[i] = g0.in0 + q0 * g0.step, p1[i] = g1.in0 + q1 * g1.step, p2[i] = g2.in0 + q2 * g2.step;
+      base[i] = ((uint32_t)n * scn + (uint32_t)p0[i] * sc0 + (uint32_t)p1[i] * sc1 + (uint32_t)p2[i] * a.kc) * ES;
+    }
+  }
+  char* const la = smem;
+  char* const lb = smem + KS * a_pitch(ROWS, BF16);
+  uint32_t* const row_out = (uint32_t*)(smem + any_lds(ROWS, NT, BF16) - ROWS * 4);  // byte offset of a row's outputs
+  if (tid < ROWS) {
+    int n, q0, q1, q2;
+    row_out[tid] = position(tid, n, q0, q1, q2)
+                       ? ((uint32_t)n * son + (uint32_t)(g0.out0 + q0 * g0.ostep) * so0 + (uint32_t)(g1.out0 + q1 * g1.ostep) * so1 +
+                          (uint32_t)(g2.out0 + q2 * g2.ostep) * a.nc) * ES
+                       : kOob;
+  }
+
+  const int ntaps = g0.nt * g1.nt * g2.nt, noct = (a.kc + 7) / 8;
+  const int K = FLAT ? ntaps * a.kc : ntaps * noct * 8;
+  const int stages = (K + 8 * KS - 1) / (8 * KS);
+  const int octs = (K + 8 * kOctPad - 1) / (8 * kOctPad) * kOctPad;
+  const float rc = 1.0f / (float)(FLAT ? a.kc : noct), r2 = 1.0f / (float)max(g2.nt, 1), r1 = 1.0f / (float)max(g1.nt, 1);
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wt + ((size_t)a.woff[cls] * a.ntn + (size_t)ntile * octs) * (PL * 32 * NT),
+                                            (uint32_t)octs * (PL * 32 * NT) * 16u);
+  // index of a tap -> what its input coordinates add to those of tap 0
+  auto steps_of = [&](int tap, int& d0, int& d1, int& d2) {
+    const int t01 = div_by(tap, max(g2.nt, 1), r2), t0 = div_by(t01, max(g1.nt, 1), r1);
+    d2 = (tap - t01 * g2.nt) * g2.dt, d1 = (t01 - t0 * g1.nt) * g1.dt, d0 = t0 * g0.dt;
+  };
+
+  float v[4][8];
+  constexpr int BP = KS * PL * 32 * NT, BPT = (BP + 255) / 256;  // weight pieces of a stage
+  u32x4 wp[BPT];
+  auto load_stage = [&](int st) {
+    if constexpr (VEC) {
+      // two groups of four channels, each within one tap
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int k = (st * KS + tid % KS) * 8 + 4 * j, tap = div_by(k, a.kc, rc), c = k - tap * a.kc;
+        int d0, d1, d2;
+        steps_of(tap, d0, d1, d2);
+        const uint32_t add = ((uint32_t)d0 * sc0 + (uint32_t)d1 * sc1 + (uint32_t)d2 * (uint32_t)a.kc + (uint32_t)c) * ES;
+        if (k >= K) d0 = -0x20000000;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          bool ok;
+          if constexpr (MODE == 0) ok = k < K && base[i] != kOob;
+          else ok = (uint32_t)(p0[i] + d0) < (uint32_t)g0.in_ext && (uint32_t)(p1[i] + d1) < (uint32_t)g1.in_ext &&
+                    (uint32_t)(p2[i] + d2) < (uint32_t)g2.in_ext;
+          load4<BF16>(&v[i][4 * j], rin, ok ? base[i] + add : kOob, 0);
+        }
+      }
+    } else if constexpr (MODE == 0) {
+      // lane l works out where element l % 8 of this wave's octet l / 8 lies
+      const int k = (st * KS + (ROWS == 256 ? 0 : wave) + (256 / ROWS) * ((lane & 31) >> 3)) * 8 + (lane & 7);
+      const int tap = div_by(k, a.kc, rc);
+      int d0, d1, d2;
+      steps_of(tap, d0, d1, d2);
+      const uint32_t ko = k < K ? ((uint32_t)d0 * sc0 + (uint32_t)d1 * sc1 + (uint32_t)d2 * (uint32_t)a.kc + (uint32_t)(k - tap * a.kc)) * ES : kOob;
+#pragma unroll
+      for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[o][e] = load1<BF16>(rin, base[0], __builtin_amdgcn_readlane(ko, 8 * o + e));
+    } else {
+      // lane l works out octet l % 4 of this wave's: its tap's steps and first channel
+      const int oct = st * KS + (ROWS == 256 ? 0 : wave) + (256 / ROWS) * (lane & 3);
+      const int tap = div_by(oct, noct, rc), c8 = (oct - tap * noct) * 8;
+      int d0, d1, d2;
+      steps_of(tap, d0, d1, d2);
+      if (tap >= ntaps) d0 = -0x20000000;
+#pragma unroll
+      for (int o = 0; o < 4; ++o) {
+        const int e0 = __builtin_amdgcn_readlane(d0, o), e1 = __builtin_amdgcn_readlane(d1, o),
+                  e2 = __builtin_amdgcn_readlane(d2, o), c0 = __builtin_amdgcn_readlane(c8, o);
+        const bool ok = (uint32_t)(p0[0] + e0) < (uint32_t)g0.in_ext && (uint32_t)(p1[0] + e1) < (uint32_t)g1.in_ext &&
+                        (uint32_t)(p2[0] + e2) < (uint32_t)g2.in_ext;
+        const uint32_t vo = base[0] + ((uint32_t)e0 * sc0 + (uint32_t)e1 * sc1 + (uint32_t)e2 * (uint32_t)a.kc + (uint32_t)c0) * ES;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)  // channels beyond kc (the same for all lanes) read as zero
+          v[o][e] = load1<BF16>(rin, ok ? vo + e * ES : kOob, c0 + e < a.kc ? 0u : kOob);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      const int piece = tid + i * 256;
+      wp[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, piece < BP ? piece * 16u : kOob, (uint32_t)st * (BP * 16u), 0);
+    }
+  };
+  auto write_stage = [&]() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int oct = VEC ? tid % KS : tid / ROWS + (256 / ROWS) * i, row = VEC ? tid / KS + i * (256 / KS) : tid % ROWS;
+      put_octet<BF16>(la + oct * a_pitch(ROWS, BF16) + row * 16, ROWS * 16, v[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      const int piece = tid + i * 256;  // [octet][plane][column]
+      if (piece < BP) *(u32x4*)(lb + (piece / (PL * 32 * NT)) * b_pitch(NT, BF16) + piece % (PL * 32 * NT) * 16) = wp[i];
+    }
+  };
+
+  Sums<NT, BF16> sums;
+  const char* const wa = la + (ROWS == 256 ? wave * 64 * 16 : wave * 4 * a_pitch(ROWS, BF16));
+  const char* const wb = lb + (ROWS == 256 ? 0 : wave * 4 * b_pitch(NT, BF16));
+  if (stages > 0) load_stage(0);
+  for (int st = 0; st < stages; ++st) {
+    write_stage();
+    __syncthreads();
+    if (st + 1 < stages) load_stage(st + 1);  // in flight while this stage multiplies
+    multiply_stage<ROWS, NT, BF16>(sums.acc, sums.low, wa, wb, lane);
+    __syncthreads();
+  }
+  if (stages == 0) __syncthreads();  // row_out
+  sums.finish();
+
+  bool bad = false;
+  auto store = [&](int row, int ch, float bias, float s) {
+    const uint32_t ro = row_out[row];
+    bad |= not_finite(s) && ro != kOob && ch < a.nc;
+    const uint32_t off = ch < a.nc ? ro + (uint32_t)ch * ES : kOob;
+    if constexpr (BF16) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)pack_bf16(s + bias, 0.f), rout, off, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s + bias), rout, off, 0, 0);
+  };
+  // the sum term by term in fp32, where the split's is not finite (rare)
+  auto again = [&](int row, int ch) {
+    int n, q0, q1, q2;
+    if (ch >= a.nc || !position(row, n, q0, q1, q2)) return;
+    const float s = corr_direct(a, g0, g1, g2, (const float*)in_bufs[worker], q0, q1, q2, n, ch) + (a.bias ? ((const float*)a.bias)[ch] : 0.f);
+    ((float*)out_bufs[worker])[row_out[row] / 4 + ch] = s;
+  };
+  auto bias_of = [&](int ch) { return a.bias && ch < a.nc ? ld((const typename Elem<BF16>::T*)a.bias, ch) : 0.f; };
+  const int ch0 = ntile * 32 * NT;
+  // register e of lane (h, ml) of MFMA tile (i, j): row 32 i + 8 (e / 4) + 4 h + e % 4, column 32 j + ml
+  if constexpr (ROWS == 256) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const float bias = bias_of(ch0 + 32 * j + ml);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          store(wave * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4), ch0 + 32 * j + ml, bias, sums.acc[i][j][e]);
+    }
+    if constexpr (!BF16) {
+      if (bad)
+        for (int t = 0; t < 32 * NT; ++t) {
+          const int e = (t >> 1) & 15;
+          again(wave * 64 + 32 * (t & 1) + 8 * (e >> 2) + 4 * h + (e & 3), ch0 + 32 * (t >> 5) + ml);
+        }
+    }
+  } else {
+    float* const red = (float*)smem;  // [wave][row][column]; the last barrier above came after the last read of a stage
+    constexpr int NB = 32 * NT;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          red[(wave * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4)) * NB + 32 * j + ml] = sums.acc[i][j][e];
+    __syncthreads();
+    const int col = tid % NB;
+    const float bias = bias_of(ch0 + col);
+#pragma unroll
+    for (int t = 0; t < 64 * NB / 256; ++t) {
+      const int row = tid / NB + t * (256 / NB);
+      const float* p = red + row * NB + col;
+      store(row, ch0 + col, bias, ((p[0] + p[64 * NB]) + p[2 * 64 * NB]) + p[3 * 64 * NB]);
+    }
+    if constexpr (!BF16) {
+      if (bad)
+        for (int t = 0; t < 64 * NB / 256; ++t) again(tid / NB + t * (256 / NB), ch0 + col);
+    }
+  }
+}
+
+// Weights as the correlation stages them: pieces [class][column tile][octet][plane][column], 8 k each; zero beyond the
+// channels and taps.  One thread per (column tile, octet, column), all planes; grid.y = class.
+template <int NT, bool BF16, bool FLAT>
+__global__ __launch_bounds__(256) void corr_any_weights_kernel(AnyArgs a, u32x4* __restrict__ dst) {
+  constexpr int PL = planes_of(BF16);
+  const int cls = (int)blockIdx.y;
+  const int par[3] = {cls / (a.s[1] * a.s[2]), cls / a.s[2] % a.s[1], cls % a.s[2]};
+  int nt[3], tf[3], ts[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    if (a.mode == 0) nt[d] = a.k[d], tf[d] = 0, ts[d] = 1;
+    else class_taps(a.k[d], a.s[d], a.dil[d], par[d], nt[d], tf[d], ts[d]);
+  }
+  const int ntaps = nt[0] * nt[1] * nt[2], noct = (a.kc + 7) / 8;
+  const int K = FLAT ? ntaps * a.kc : ntaps * noct * 8, octs = (K + 8 * kOctPad - 1) / (8 * kOctPad) * kOctPad;
+  const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (idx >= a.ntn * octs * 32 * NT) return;
+  const int col = idx % (32 * NT), r = idx / (32 * NT), oct = r % octs, ntile = r / octs;
+  const int ch = ntile * 32 * NT + col;
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    int tap, c;
+    if (FLAT) {
+      const int k = oct * 8 + e;
+      tap = k / a.kc, c = k - tap * a.kc;
+    } else {
+      tap = oct / noct, c = (oct - tap * noct) * 8 + e;
+    }
+    v[e] = 0.f;
+    if (tap < ntaps && c < a.kc && ch < a.nc) {
+      const int i2 = tap % nt[2], i01 = tap / nt[2], i1 = i01 % nt[1], i0 = i01 / nt[1];
+      const int t = ((tf[0] + i0 * ts[0]) * a.k[1] + tf[1] + i1 * ts[1]) * a.k[2] + tf[2] + i2 * ts[2];
+      const int oc = a.mode == 0 ? ch : c, ic = a.mode == 0 ? c : ch;
+      v[e] = ld((const typename Elem<BF16>::T*)a.w, ((size_t)oc * a.ci + ic) * a.taps + t);
+    }
+  }
+  u32x4* const at = dst + ((size_t)a.woff[cls] * a.ntn + (size_t)ntile * octs + oct) * (PL * 32 * NT) + col;
+  put_octet<BF16>((char*)at, 32 * NT * 16, v);
+}
+
+// grid: (row tiles * column tiles, chunks, workers)
+template <int NT, bool BF16>
+__global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __restrict__ workers, void* const* x_bufs,
+                                                           void* const* dy_bufs, float* __restrict__ partial, WgradAnyArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr uint32_t ES = BF16 ? 2 : 4;
+  constexpr int kRows = 256, kKp = 4;
+  const int mt = (int)blockIdx.x % a.ntm, ntile = (int)blockIdx.x / a.ntm, chunk = (int)blockIdx.y, worker = (int)blockIdx.z;
+  const WorkerDev wd = workers[worker];
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ml = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t sx1 = (uint32_t)wd.buf[2] * a.ci, sx0 = (uint32_t)wd.buf[1] * sx1, sxn = (uint32_t)wd.buf[0] * sx0;
+  const int npos = a.n_b * wd.out[0] * wd.out[1] * wd.out[2];
+  const int all = (npos + 8 * kKp - 1) / (8 * kKp);  // stages of the worker, dealt to the chunks
+  const int s_begin = (int)((int64_t)all * chunk / a.nchunks), s_end = (int)((int64_t)all * (chunk + 1) / a.nchunks);
+  const __amdgpu_buffer_rsrc_t rx = rsrc_of(x_bufs[worker], (uint32_t)a.n_b * sxn * ES);
+  const __amdgpu_buffer_rsrc_t ry = rsrc_of(dy_bufs[worker], (uint32_t)npos * a.co * ES);
+
+  // this thread's row: tap and input channel
+  uint32_t base = kOob;
+  {
+    const int k = mt * kRows + tid;
+    if (k < a.rows) {
+      const int tap = k / a.ci, c = k - tap * a.ci;
+      const int t2 = tap % a.k[2], t01 = tap / a.k[2], t1 = t01 % a.k[1], t0 = t01 / a.k[1];
+      base = ((uint32_t)(wd.origin[0] + t0 * a.dil[0]) * sx0 + (uint32_t)(wd.origin[1] + t1 * a.dil[1]) * sx1 +
+              (uint32_t)(wd.origin[2] + t2 * a.dil[2]) * a.ci + c) * ES;
+    }
+  }
+  // and its column of dy, an octet of positions
+  constexpr int NB = 32 * NT, YO = (kKp * NB + 255) / 256;  // octets of dy per thread
+  char* const la = smem;
+  char* const lb = smem + kKp * a_pitch(kRows, BF16);
+  float v[kKp][8], y[YO][8];
+  uint32_t yoff[YO];
+#pragma unroll
+  for (int i = 0; i < YO; ++i) {
+    const int u = tid + i * 256, col = u % NB, o = u / NB, ch = ntile * NB + col;
+    yoff[i] = o < kKp && ch < a.co ? ((uint32_t)(o * 8) * a.co + ch) * ES : kOob;
+  }
+  auto load_stage = [&](int st) {
+    // lane l works out where position 32 st + l lies
+    uint32_t t = (uint32_t)(st * 32 + (lane & 31));
+    uint32_t po = kOob;
+    if ((int)t < npos) {
+      const uint32_t o2 = t % (uint32_t)wd.out[2]; t /= (uint32_t)wd.out[2];
+      const uint32_t o1 = t % (uint32_t)wd.out[1]; t /= (uint32_t)wd.out[1];
+      const uint32_t o0 = t % (uint32_t)wd.out[0], n = t / (uint32_t)wd.out[0];
+      po = (n * sxn + o0 * a.s[0] * sx0 + o1 * a.s[1] * sx1 + o2 * a.s[2] * (uint32_t)a.ci) * ES;
+    }
+#pragma unroll
+    for (int o = 0; o < kKp; ++o)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[o][e] = load1<BF16>(rx, base, __builtin_amdgcn_readlane(po, 8 * o + e));
+    // positions beyond the last lie beyond the resource and read as zero
+#pragma unroll
+    for (int i = 0; i < YO; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[i][e] = load1<BF16>(ry, yoff[i], (uint32_t)(st * 32 + e) * a.co * ES);
+  };
+  const bool bias_wg = mt == 0;  // these workgroups see every dy element of their columns and chunk once
+  float bsum[YO];
+#pragma unroll
+  for (int i = 0; i < YO; ++i) bsum[i] = 0.f;
+  auto write_stage = [&]() {
+#pragma unroll
+    for (int o = 0; o < kKp; ++o) put_octet<BF16>(la + o * a_pitch(kRows, BF16) + tid * 16, kRows * 16, v[o]);
+#pragma unroll
+    for (int i = 0; i < YO; ++i) {
+      const int u = tid + i * 256;
+      if (u < kKp * NB) put_octet<BF16>(lb + (u / NB) * b_pitch(NT, BF16) + u % NB * 16, NB * 16, y[i]);
+      if (bias_wg)
+        bsum[i] += ((y[i][0] + y[i][1]) + (y[i][2] + y[i][3])) + ((y[i][4] + y[i][5]) + (y[i][6] + y[i][7]));
+    }
+  };
+  Sums<NT, BF16> sums;
+  if (s_begin < s_end) load_stage(s_begin);
+  for (int st = s_begin; st < s_end; ++st) {
+    write_stage();
+    __syncthreads();
+    if (st + 1 < s_end) load_stage(st + 1);
+    multiply_stage<kRows, NT, BF16>(sums.acc, sums.low, la + wave * 64 * 16, lb, lane);
+    __syncthreads();
+  }
+  sums.finish();
+  float* const slot = partial + ((size_t)worker * a.nchunks + chunk) * a.slot;
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int ch = ntile * NB + 32 * j + ml;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int k = mt * kRows + wave * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4);
+        if (k < a.rows && ch < a.co) {
+          bad |= not_finite(sums.acc[i][j][e]);
+          slot[(size_t)k * a.co + ch] = sums.acc[i][j][e];
+        }
+      }
+  }
+  if constexpr (!BF16) {
+    if (bad)  // rare: this lane's sums term by term
+      for (int t = 0; t < 32 * NT; ++t) {
+        const int k = mt * kRows + wave * 64 + 32 * (t & 1) + 8 * ((t >> 1) >> 2 & 3) + 4 * h + (t >> 1 & 3);
+        const int ch = ntile * NB + 32 * (t >> 5) + ml;
+        if (k >= a.rows || ch >= a.co) continue;
+        const int tap = k / a.ci, c = k - tap * a.ci;
+        const int t2 = tap % a.k[2], t01 = tap / a.k[2], t1 = t01 % a.k[1], t0 = t01 / a.k[1];
+        float sum = 0.f;
+        for (int p = s_begin * 32; p < min(npos, s_end * 32); ++p) {
+          int u = p;
+          const int o2 = u % wd.out[2]; u /= wd.out[2];
+          const int o1 = u % wd.out[1]; u /= wd.out[1];
+          const int o0 = u % wd.out[0], n = u / wd.out[0];
+          const size_t at = (size_t)n * sxn + (size_t)(wd.origin[0] + o0 * a.s[0] + t0 * a.dil[0]) * sx0 +
+                            (size_t)(wd.origin[1] + o1 * a.s[1] + t1 * a.dil[1]) * sx1 +
+                            (size_t)(wd.origin[2] + o2 * a.s[2] + t2 * a.dil[2]) * a.ci + c;
+          sum = fmaf(((const float*)dy_bufs[worker])[(size_t)p * a.co + ch], ((const float*)x_bufs[worker])[at], sum);
+        }
+        slot[(size_t)k * a.co + ch] = sum;
+      }
+  }
+  if (bias_wg) {  // the octets of a column, in order
+    float* const red = (float*)smem;  // (the last barrier above came after the last read of the stage)
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < YO; ++i)
+      if (tid + i * 256 < kKp * NB) red[tid + i * 256] = bsum[i];
+    __syncthreads();
+    if (tid < NB && ntile * NB + tid < a.co) {
+      float sum = red[tid];
+#pragma unroll
+      for (int o = 1; o < kKp; ++o) sum += red[o * NB + tid];
+      slot[(size_t)a.rows * a.co + ntile * NB + tid] = sum;
+    }
+  }
+}
+
+// ---- host side ------------------------------------------------------------------
+
+int nt_of(int64_t channels) { return channels > 32 ? 2 : 1; }
+
+AnyArgs any_args(const distdl_plan* p, int mode, int NT) {
+  AnyArgs a{};
+  a.mode = mode;
+  a.n_b = (int32_t)p->n_b;
+  a.ci = (int32_t)p->n_ci;
+  a.co = (int32_t)p->n_co;
+  a.kc = mode == 0 ? a.ci : a.co;
+  a.nc = mode == 0 ? a.co : a.ci;
+  a.taps = 1;
+  a.ncls = 1;
+  for (int d = 0; d < 3; ++d) {
+    a.k[d] = p->ksize[d];
+    a.s[d] = p->stride[d];
+    a.dil[d] = p->dilation[d];
+    a.taps *= a.k[d];
+    if (mode == 1) a.ncls *= a.s[d];
+  }
+  a.n_workers = p->n_workers;
+  a.ntn = (a.nc + 32 * NT - 1) / (32 * NT);
+  return a;
+}
+
+// k without padding, or the octets of a tap on their own (see the kernel)
+bool flat_k(const AnyArgs& a, bool vec) { return a.mode == 0 || vec; }
+
+// octets of weights of every class; returns their sum
+int64_t class_octets(const AnyArgs& a, bool flat, int32_t* first, int& most) {
+  int64_t sum = 0;
+  most = 0;
+  for (int cls = 0; cls < a.ncls; ++cls) {
+    int ntaps = 1;
+    const int par[3] = {cls / (a.s[1] * a.s[2]), cls / a.s[2] % a.s[1], cls % a.s[2]};
+    for (int d = 0; d < 3; ++d) {
+      int nt = a.k[d], tf, ts;
+      if (a.mode == 1) class_taps(a.k[d], a.s[d], a.dil[d], par[d], nt, tf, ts);
+      ntaps *= nt;
+    }
+    const int K = flat ? ntaps * a.kc : ntaps * ((a.kc + 7) / 8) * 8;
+    const int octs = (K + 8 * kOctPad - 1) / (8 * kOctPad) * kOctPad;
+    if (first) first[cls] = (int32_t)sum;
+    sum += octs;
+    most = std::max(most, octs);
+  }
+  return sum;
+}
+
+int64_t positions_max(const distdl_plan* p, const AnyArgs& a) {
+  int64_t mx = 0;
+  for (const WorkerDev& wd : p->workers) {
+    int64_t v = p->n_b;
+    for (int d = 0; d < 3; ++d) v *= a.mode == 0 ? wd.out[d] : (wd.buf[d] + a.s[d] - 1) / a.s[d];
+    mx = std::max(mx, v);
+  }
+  return mx;
+}
+
+size_t weight_floats(const distdl_plan* p, int mode) {
+  const AnyArgs a = any_args(p, mode, 2);
+  int most;
+  const int64_t octs = std::max(class_octets(a, true, nullptr, most), class_octets(a, false, nullptr, most));
+  return (size_t)octs * a.ntn * planes_of(p->dtype == DISTDL_BF16) * 32 * 2 * 4;
+}
+
+template <int ROWS, int NT, bool BF16, int MODE, bool VEC>
+int launch_corr_any(distdl_plan* p, const AnyArgs& a, void** in_tab, void** out_tab, int most, const char* name, hipStream_t st) {
+  constexpr bool FLAT = MODE == 0 || VEC;
+  {
+    ProfScope prof("conv_relayout_w", st);
+    const int64_t n = (int64_t)a.ntn * most * 32 * NT;
+    if (n > 0)
+      hipLaunchKernelGGL((corr_any_weights_kernel<NT, BF16, FLAT>), dim3((unsigned)((n + 255) / 256), (unsigned)a.ncls),
+                         dim3(256), 0, st, a, (u32x4*)p->d_wt);
+  }
+  constexpr int lds = any_lds(ROWS, NT, BF16);
+  const int64_t blocks = ((int64_t)a.tiles_max * p->n_workers + 7) / 8 * 8;
+  if (lds > 64 * 1024)
+    if (int rc = allow_large_lds<corr_any_kernel<ROWS, NT, BF16, MODE, VEC>>()) return rc;
+  ProfScope prof(name, st);
+  hipLaunchKernelGGL((corr_any_kernel<ROWS, NT, BF16, MODE, VEC>), dim3((unsigned)blocks, (unsigned)a.ncls), dim3(256), lds,
+                     st, p->d_workers, in_tab, out_tab, a);
+  return DISTDL_OK;
+}
+
+template <int ROWS, int NT, bool BF16>
+int pick_corr_any(distdl_plan* p, const AnyArgs& a, bool vec, void** in_tab, void** out_tab, int most, const char* name, hipStream_t st) {
+  if (a.mode == 0)
+    return vec ? launch_corr_any<ROWS, NT, BF16, 0, true>(p, a, in_tab, out_tab, most, name, st)
+               : launch_corr_any<ROWS, NT, BF16, 0, false>(p, a, in_tab, out_tab, most, name, st);
+  return vec ? launch_corr_any<ROWS, NT, BF16, 1, true>(p, a, in_tab, out_tab, most, name, st)
+             : launch_corr_any<ROWS, NT, BF16, 1, false>(p, a, in_tab, out_tab, most, name, st);
+}
+
+int run_corr_any(distdl_plan* p, int mode, const void* w, const void* bias, bool aligned, void** in_tab, void** out_tab,
+                 const char* name, hipStream_t st) {
+  int NT = nt_of(mode == 0 ? p->n_co : p->n_ci);
+  AnyArgs a = any_args(p, mode, NT);
+  const bool vec = aligned && a.kc % 4 == 0, bf16 = p->dtype == DISTDL_BF16;
+  int most;
+  class_octets(a, flat_k(a, vec), a.woff, most);
+  // 64 rows where 256 would leave compute units idle and there is enough k for four waves (32 columns: with 64 their
+  // accumulators and the larger stages of weights do not fit the registers)
+  const int64_t pos = positions_max(p, a);
+  const bool few = (pos + 255) / 256 * a.ntn * p->n_workers * a.ncls < 384 && most > kOctPad;
+  const int rows = few ? 64 : 256;
+  if (few) NT = 1, a.ntn = (a.nc + 31) / 32;
+  if (int rc = ensure_wscratch(p, std::max(weight_floats(p, 0), weight_floats(p, 1)))) return rc;
+  a.w = w;
+  a.bias = bias;
+  a.wt = (const u32x4*)p->d_wt;
+  a.tiles_max = (int32_t)((pos + rows - 1) / rows * a.ntn);
+#define DISTDL_ANY(ROWS_, NT_)                                                               \
+  (bf16 ? pick_corr_any<ROWS_, NT_, true>(p, a, vec, in_tab, out_tab, most, name, st)        \
+        : pick_corr_any<ROWS_, NT_, false>(p, a, vec, in_tab, out_tab, most, name, st))
+  return few ? DISTDL_ANY(64, 1) : NT == 1 ? DISTDL_ANY(256, 1) : DISTDL_ANY(256, 2);
+#undef DISTDL_ANY
+}
+
+}  // namespace
+
+// 31-bit byte offsets into one worker's tensors, all classes in one launch
+bool conv_any_supported(const distdl_plan* p) {
+  if (p->explicit_halo) return false;
+  if ((double)p->n_b * p->max_buf_cells * std::max(p->n_ci, p->n_co) * 4.0 >= 2147480000.0) return false;
+  if ((double)p->n_b * p->max_out_cells * std::max(p->n_ci, p->n_co) * 4.0 >= 2147480000.0) return false;
+  int64_t cls = 1, taps = 1;
+  for (int d = 0; d < 3; ++d) {
+    cls *= p->stride[d];
+    taps *= p->ksize[d];
+    if (p->stride[d] > 64) return false;
+  }
+  // (k is divided through a float reciprocal: fewer than 2^22)
+  if (cls > kMaxCls || taps * (std::max(p->n_ci, p->n_co) + 8) >= (int64_t(1) << 22)) return false;
+  if (taps * (p->n_ci + 64) * (p->n_co + 64) >= (int64_t(1) << 28)) return false;
+  for (int mode = 0; mode < 2; ++mode) {  // 32-bit block numbers
+    const AnyArgs a = any_args(p, mode, 1);
+    if ((double)(positions_max(p, a) / 64 + 1) * a.ntn * p->n_workers >= 2147480000.0) return false;
+  }
+  return p->n_workers <= 65535;
+}
+
+int conv_fwd_any(distdl_plan* p, const void* w, const void* bias, bool aligned, hipStream_t st) {
+  return run_corr_any(p, 0, w, bias, aligned, p->tab_x.dev, p->tab_y.dev, "conv_fwd_any", st);
+}
+
+int conv_bwd_data_any(distdl_plan* p, const void* w, bool aligned, hipStream_t st) {
+  return run_corr_any(p, 1, w, nullptr, aligned, p->tab_dy.dev, p->tab_dx.dev, "conv_bwd_data_any", st);
+}
+
+// position chunks per worker: about two workgroups per compute unit, at least four stages each
+int wgrad_any_chunks(const distdl_plan* p) {
+  const int64_t rows = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci;
+  const int NT = nt_of(p->n_co);
+  const int64_t tiles = (rows + 255) / 256 * ((p->n_co + 32 * NT - 1) / (32 * NT)) * p->n_workers;
+  const int64_t stages = (p->n_b * p->max_out_cells + 31) / 32;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((512 + tiles - 1) / tiles, stages / 4), 512));
+}
+
+int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st) {
+  WgradAnyArgs a{};
+  a.n_b = (int32_t)p->n_b;
+  a.ci = (int32_t)p->n_ci;
+  a.co = (int32_t)p->n_co;
+  a.rows = a.ci;
+  for (int d = 0; d < 3; ++d) {
+    a.k[d] = p->ksize[d];
+    a.s[d] = p->stride[d];
+    a.dil[d] = p->dilation[d];
+    a.rows *= a.k[d];
+  }
+  a.nchunks = wgrad_any_chunks(p);
+  const int NT = nt_of(a.co);
+  a.ntm = (a.rows + 255) / 256;
+  a.ntn = (a.co + 32 * NT - 1) / (32 * NT);
+  a.slot = (int64_t)a.rows * a.co + a.co;
+  const dim3 grid((unsigned)(a.ntm * a.ntn), (unsigned)a.nchunks, (unsigned)p->n_workers);
+  ProfScope prof("conv_bwd_weight_any", st);
+#define DISTDL_WANY(NT_, BF_)                                                                                          \
+  do {                                                                                                                 \
+    constexpr int lds = any_lds(256, NT_, BF_);                                                                            \
+    if (lds > 64 * 1024)                                                                                               \
+      if (int rc_ = allow_large_lds<wgrad_any_kernel<NT_, BF_>>()) return rc_;                                         \
+    hipLaunchKernelGGL((wgrad_any_kernel<NT_, BF_>), grid, dim3(256), lds, st, p->d_workers, p->tab_x.dev,             \
+                       p->tab_dy.dev, partial, a);                                                                     \
+  } while (0)
+  if (p->dtype == DISTDL_BF16) {
+    if (NT == 1) DISTDL_WANY(1, true);
+    else DISTDL_WANY(2, true);
+  } else {
+    if (NT == 1) DISTDL_WANY(1, false);
+    else DISTDL_WANY(2, false);
+  }
+#undef DISTDL_WANY
+  return DISTDL_OK;
+}
+
+}  // namespace distdl

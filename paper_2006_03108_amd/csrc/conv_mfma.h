@@ -81,6 +81,7 @@ int ensure_wscratch(distdl_plan* p, size_t elems);
 
 bool corr_mfma_supported(const distdl_plan* p);
 bool wgrad_mfma_supported(const distdl_plan* p);
+bool wgrad_taps_supported(const distdl_plan* p);  // the plane-per-workgroup kernel's shapes
 size_t bwd_scratch_elems(const distdl_plan* p);
 int wgrad_chunks(const distdl_plan* p);
 // All three expect the plan's pointer tables (tab_x, tab_y, tab_dy, tab_dx) to be uploaded.

@@ -1562,6 +1562,8 @@ static bool wgrad_rows_shape_ok(const distdl_plan* p) {
   return true;
 }
 
+bool wgrad_taps_supported(const distdl_plan* p) { return !p->explicit_halo && wgrad_rows_shape_ok(p); }
+
 // Output rows per work unit of the plane-per-workgroup kernel: whole planes when there are enough of them to
 // fill the chip, else blocks of rows (each block re-reads span - s1 rows to prime its ring).
 static int wgrad_row_block(const distdl_plan* p) {

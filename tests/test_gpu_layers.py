@@ -828,3 +828,78 @@ def test_affine_infinities_and_nans_stay_what_fp32_makes_of_them(n_b, n_fi, n_fo
         assert torch.equal(got == float("inf"), want > 3.5e38) and torch.equal(got == float("-inf"), want < -3.5e38)
         scale = want[finite].abs().clamp_min(1.0)
         assert float(((got[finite].double() - want[finite]).abs() / scale).max()) < 1e-4
+
+
+# layers for the gather kernels: remainders of 64 and 256 rows and of 32 and 64 columns, one and several stages of k,
+# channel counts that are no multiples of 4, kernels wider than the patch kernels take, strides 2 - 4 with classes that
+# no tap reaches, dilation that shares a factor with the stride
+CONV_ANY = [
+    dict(D=1, n_b=1, c_in=17, c_out=1, in_shape=(9,), P=(2,), ksize=(2,), stride=(1,), padding=(0,), dilation=(1,)),
+    dict(D=2, n_b=3, c_in=3, c_out=33, in_shape=(29, 31), P=(2, 2), ksize=(7, 7), stride=(2, 2), padding=(3, 3), dilation=(1, 1)),
+    dict(D=2, n_b=2, c_in=20, c_out=65, in_shape=(19, 22), P=(2, 1), ksize=(3, 5), stride=(4, 3), padding=(1, 2), dilation=(1, 1)),
+    dict(D=3, n_b=1, c_in=18, c_out=22, in_shape=(9, 10, 11), P=(1, 2, 2), ksize=(3, 1, 2), stride=(2, 2, 2), padding=(1, 0, 1), dilation=(2, 1, 2)),
+    dict(D=2, n_b=2, c_in=32, c_out=36, in_shape=(20, 24), P=(2, 2), ksize=(9, 1), stride=(1, 2), padding=(4, 0), dilation=(1, 1)),
+    dict(D=2, n_b=5, c_in=40, c_out=70, in_shape=(33, 30), P=(1, 1), ksize=(1, 1), stride=(1, 1), padding=(0, 0), dilation=(1, 1)),
+    dict(D=2, n_b=40, c_in=19, c_out=24, in_shape=(40, 41), P=(2, 2), ksize=(3, 3), stride=(1, 1), padding=(1, 1), dilation=(1, 1)),
+]
+
+
+@pytest.mark.parametrize("cfg", CONV_ANY, ids=lambda c: f"c{c['c_in']}-{c['c_out']}k{'x'.join(map(str, c['ksize']))}s{c['stride'][-1]}")
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("misaligned", [False, True], ids=["aligned", "odd"])
+def test_conv_gather_kernels(cfg, dtype, misaligned):
+    require_gpu()
+    cfg = dict(cfg, seed=77)
+    part = oracle_partition(cfg)
+    case = syn.conv_case(cfg, part.global_out_shape())
+    if dtype == torch.bfloat16:
+        case = {k: (syn.to_bf16_values(v) if isinstance(v, np.ndarray) else v) for k, v in case.items()}
+    x_bufs, y, dx_bufs, dw, db = _run_conv(cfg, part, case, True, dtype, misaligned_outputs=misaligned)
+    tol = TOL32 if dtype == torch.float32 else TOL16
+    o_bufs = prim.scatter_bulk(case["x"].astype(np.float64), part, fill=np.nan)
+    y_want = layers.dist_conv_forward(o_bufs, case["w"], case["bias"], part, cfg["stride"], cfg["dilation"])
+    dx_want, dw_want, db_want = layers.dist_conv_adjoint(o_bufs, case["w"], prim.scatter_out(case["dy"], part), part,
+                                                         cfg["stride"], cfg["dilation"], True)
+    for wk in range(part.n_workers):
+        assert_close(from_cl(y[wk]), y_want[wk], tol, f"y worker {wk}")
+        if np.abs(dx_want[wk]).max() > 0:
+            assert_close(from_cl(dx_bufs[wk]), dx_want[wk], tol, f"dx worker {wk}")
+    assert_close(dw.float().cpu().numpy(), dw_want, tol, "dw")
+    assert_close(db.float().cpu().numpy(), db_want, tol, "db")
+
+
+# (channels in, out, kernel): gather kernels with 64 and 256 rows, and the patch kernels
+@pytest.mark.parametrize("c_in,c_out,k,n", [(5, 40, 7, 24), (18, 33, 3, 40), (3, 17, 3, 150), (32, 32, 3, 33), (16, 40, 5, 20)])
+def test_conv_infinities_and_nans_stay_what_fp32_makes_of_them(c_in, c_out, k, n):
+    """As for the affine layer: a sum with an infinite, a NaN or a nearly infinite term is what fp32 products give."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(9)
+    new = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    p = k // 2
+    plan = dd.distdl_plan_create(2, 1, c_in, c_out, (n, n), (1, 1), (k, k), (1, 1), (p, p), (1, 1))
+    x, w, dy = torch.zeros(1, n + 2 * p, n + 2 * p, c_in, device="cuda"), new(c_out, c_in, k, k), new(1, n, n, c_out)
+    inner = x[:, p:p + n, p:p + n]
+    inner.copy_(new(1, n, n, c_in))
+    inner[0, 2, 3, 0], inner[0, 9, 9, 1], inner[0, 15, 4, 2] = float("inf"), float("nan"), 3.4e38
+    w[:, 2] *= 0.01                              # keeps the products with the nearly infinite value finite
+    dy[0, n - 1, n - 1, 0], dy[0, n - 8, 2, 1] = float("-inf"), 3.4e38
+    w[1] *= 0.01
+    y, dx, dw = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w)
+    ws = torch.empty(max(dd.distdl_conv_bwd_workspace(plan), 16), dtype=torch.uint8, device="cuda")
+    want_x = x.permute(0, 3, 1, 2).double().cpu().requires_grad_()
+    want_w = w.double().cpu().requires_grad_()
+    dd.distdl_conv_fwd(plan, [x], w, None, [y])
+    dd.distdl_conv_bwd(plan, [x], w, [dy], [dx], dw, None, ws)
+    want_y = torch.nn.functional.conv2d(want_x, want_w)
+    want_y.backward(dy.permute(0, 3, 1, 2).double().cpu())
+    for name, got, want in (("y", y.permute(0, 3, 1, 2), want_y.detach()), ("dx", dx.permute(0, 3, 1, 2)[:, :, p:p + n, p:p + n], want_x.grad[:, :, p:p + n, p:p + n])):
+        got = got.cpu()
+        sure = (want.abs() < 3.3e38) | ~torch.isfinite(want)
+        assert torch.equal(torch.isnan(got)[sure], torch.isnan(want)[sure]), name
+        assert torch.equal(torch.isinf(got)[sure], torch.isinf(want)[sure]), name
+        fin = want.abs() < 3.3e38
+        assert float(((got[fin].double() - want[fin]).abs() / want[fin].abs().clamp_min(1.0)).max()) < 1e-3, name
+    # dw sums over all positions, and nearly infinite terms may overflow in one order and not in another: no finite term
+    # may turn into anything else, no infinite one may vanish
+    got, want = dw.cpu(), want_w.grad
+    assert bool(torch.isfinite(got)[want.abs() < 1e30].all()) and not bool(torch.isfinite(got)[~torch.isfinite(want)].any())
