@@ -13,6 +13,7 @@
 #include "conv_any.h"
 #include "conv_core.h"
 #include "conv_mfma.h"
+#include "conv_split.h"
 #include "profile.h"
 
 namespace distdl {
@@ -334,6 +335,11 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
     DISTDL_HIP_TRY(hipGetLastError());
     return DISTDL_OK;
   }
+  if (xvec && corr_split_supported(plan)) {
+    if ((rc = conv_fwd_split(plan, (const float*)w_dev, (const float*)bias_dev, st))) return rc;
+    DISTDL_HIP_TRY(hipGetLastError());
+    return DISTDL_OK;
+  }
   if (aligned && corr_mfma_supported(plan)) {
     if ((rc = conv_fwd_mfma(plan, w_dev, bias_dev, st))) return rc;
     DISTDL_HIP_TRY(hipGetLastError());
@@ -396,6 +402,8 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   int64_t total = plan->n_b * plan->max_buf_cells * c.ci;
   if (corr16_bwd_supported(plan, aligned)) {
     if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
+  } else if (aligned && corr_split_supported(plan)) {
+    if ((rc = conv_bwd_data_split(plan, (const float*)w_dev, st))) return rc;
   } else if (data_mfma) {
     if ((rc = conv_bwd_data_mfma(plan, w_dev, st))) return rc;
   } else if (conv_any_supported(plan)) {

@@ -801,13 +801,14 @@ int conv_bwd_data_any(distdl_plan* p, const void* w, bool aligned, hipStream_t s
   return run_corr_any(p, 1, w, nullptr, aligned, p->tab_dy.dev, p->tab_dx.dev, "conv_bwd_data_any", st);
 }
 
-// position chunks per worker: about two workgroups per compute unit, at least four stages each
+// position chunks per worker: about two workgroups per compute unit
 int wgrad_any_chunks(const distdl_plan* p) {
   const int64_t rows = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci;
   const int NT = nt_of(p->n_co);
   const int64_t tiles = (rows + 255) / 256 * ((p->n_co + 32 * NT - 1) / (32 * NT)) * p->n_workers;
   const int64_t stages = (p->n_b * p->max_out_cells + 31) / 32;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((512 + tiles - 1) / tiles, stages / 4), 512));
+  // (a stage of a workgroup takes about 1.2 us, adding one more partial almost nothing: small layers one stage each)
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((512 + tiles - 1) / tiles, std::max<int64_t>(std::min<int64_t>(stages, 64), stages / 4)), 512));
 }
 
 int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st) {

@@ -1,0 +1,609 @@
+// Local convolution of fp32 tensors on the bf16 matrix cores (split_bf16.h): forward and data gradient of the layers
+// whose channel counts are multiples of 4, as an implicit GEMM over staged patches (Sec. 4, "Conv" and "[dConv]*").
+//
+//   out[q][n] = sum_taps sum_k W[tap][k][n] * in[base + q * step + tapoff][k]
+//
+// as in conv_mfma.hip: forward in = x^, out = y; data gradient one launch per stride-parity class of dx^, in = dy.
+// A workgroup of four waves owns a tr x tc window of 128 MT output positions and walks output planes.  A stage is
+//   (kernel plane t0, tap group, 16 channels):
+// the input cells that the group's taps read are loaded, split into three bf16 planes and written to LDS, as are the
+// group's weights (split once per call by the re-layout kernel); then every tap multiplies 6 MT MFMAs per wave.
+// The taps of a kernel plane are grouped by the residue of their input offset modulo the step: a group's cells are then
+// the cells of one residue only, the cell of (position, tap) is position + constant, and a stage of a stride-2 layer is a
+// quarter of the patch with a quarter of the taps.  Three planes of a whole 5 x 5 stride-2 stage would be 200 KB; the
+// groups (9, 6, 6 and 4 taps) take 64 KB at most, so two workgroups share a compute unit and one's loads, splits and
+// barriers run under the other's MFMAs.  Groups of more than 10 taps are cut by kernel rows.
+// Bound: MFMAs (at the clock that the power limit leaves them with real data, about 2/3 of the peak) and LDS: with
+// MT = 2 a tap reads 9 KB per 12 MFMAs and wave, 3/4 of what LDS can deliver in that time.
+#include <algorithm>
+#include <memory>
+
+#include "common.h"
+#include "conv_mfma.h"
+#include "conv_split.h"
+#include "profile.h"
+#include "split_bf16.h"
+
+namespace distdl {
+
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GiB)
+constexpr int kMaxGroups = 32, kMaxTaps = 64, kGroupTaps = 10;
+
+struct SplitArgs {
+  CorrArgs c;
+  const u32x4* wt;  // weights as operand pieces
+  const float* w;   // the caller's weights
+  int32_t ci, co, taps, k1, k2;
+  int32_t ngroups;
+  int32_t gbegin[kMaxGroups + 1];           // taps of group i: gbegin[i] ... gbegin[i + 1]
+  int32_t gbase[kMaxGroups][2];             // input offset of the group's first patch row / cell (of position 0)
+  int32_t tapcell[kMaxTaps];                // patch cell of a tap for position 0
+  uint8_t tap12[kMaxTaps][2];               // its indices along dimensions 1 and 2
+};
+
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
+// Bytes of half an LDS plane of the patch (8 channels of PA * 128 cells), of a plane.  The halves lie a multiple of 256
+// bytes apart, as the two half-waves of an operand read want it (64 or 128 more bytes between them: 1.4 times the LDS
+// cycles), and a half-wave writes one half of 32 cells.
+constexpr uint32_t half_bytes(int PA) { return PA * 2048; }
+constexpr uint32_t plane_bytes(int PA) { return 2 * half_bytes(PA); }
+constexpr int split_lds_bytes(int PA, int taps) { return 3 * plane_bytes(PA) + taps * 3072; }
+
+// output (position q, channel ch) term by term in fp32
+__device__ inline float split_direct(const SplitArgs& a, const PerWorker& g, const float* in, int n, int q0, int q1, int q2, int ch) {
+  const CorrArgs& c = a.c;
+  float sum = 0.f;
+  for (int t0 = 0; t0 < c.nt[0]; ++t0)
+    for (int t1 = 0; t1 < c.nt[1]; ++t1)
+      for (int t2 = 0; t2 < c.nt[2]; ++t2) {
+        const int i0 = g.in_base[0] + q0 * c.is[0] + c.tapoff[0][t0], i1 = g.in_base[1] + q1 * c.is[1] + c.tapoff[1][t1],
+                  i2 = g.in_base[2] + q2 * c.is[2] + c.tapoff[2][t2];
+        if (i0 < 0 || i0 >= g.in_ext[0] || i1 < 0 || i1 >= g.in_ext[1] || i2 < 0 || i2 >= g.in_ext[2]) continue;
+        const int tap = (c.tapid[0][t0] * a.k1 + c.tapid[1][t1]) * a.k2 + c.tapid[2][t2];
+        const float* x = in + ((((size_t)n * g.in_ext[0] + i0) * g.in_ext[1] + i1) * g.in_ext[2] + i2) * c.kc;
+        for (int k = 0; k < c.kc; ++k) {
+          const int o = c.mode == 0 ? ch : k, i = c.mode == 0 ? k : ch;
+          sum = fmaf(x[k], a.w[((size_t)o * a.ci + i) * a.taps + tap], sum);
+        }
+      }
+  return sum;
+}
+
+// MT: 32-position M-tiles per wave; PA: pairs of 16-byte pieces (8 channels of a cell) per thread and stage; PB: weight
+// pieces per thread and stage
+template <int MT, int PA, int PB>
+__global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __restrict__ workers, void* const* in_bufs,
+                                                            void* const* out_bufs, SplitArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const CorrArgs& c = a.c;
+  constexpr uint32_t HB = half_bytes(PA), PS = plane_bytes(PA);
+  // consecutive tiles (which share input rows) stay on one XCD, i.e. behind one L2
+  const uint32_t nblk = gridDim.x, r = (blockIdx.x & 7u) * (nblk >> 3) + (blockIdx.x >> 3);
+  const uint32_t worker = r / c.tiles_max;
+  uint32_t tile = r - worker * c.tiles_max;
+  if (worker >= (uint32_t)c.n_workers) return;
+  const WorkerDev wd = workers[worker];
+  const PerWorker g = derive(wd, c);
+  const int nt2tiles = (g.nq[2] + c.tc - 1) / c.tc, nt1tiles = (g.nq[1] + c.tr - 1) / c.tr;
+  const int nq0 = g.nq[0], ptotal = c.n_b * nq0, ngroups = (ptotal + c.g0 - 1) / c.g0;
+  if ((int64_t)tile >= (int64_t)ngroups * nt1tiles * nt2tiles * c.ntn) return;
+  const int q2_0 = (tile % nt2tiles) * c.tc; tile /= nt2tiles;
+  const int q1_0 = (tile % nt1tiles) * c.tr; tile /= nt1tiles;
+  const int ntile = tile % c.ntn; tile /= c.ntn;  // `tile` is now this workgroup's place among the plane groups
+
+  const int si2 = c.kc, si1 = g.in_ext[2] * si2, si0 = g.in_ext[1] * si1;
+  const uint32_t sin = (uint32_t)g.in_ext[0] * si0;
+  const uint32_t so2 = c.nc, so1 = g.out_ext[2] * so2, so0 = g.out_ext[1] * so1, son = g.out_ext[0] * so0;
+  const __amdgpu_buffer_rsrc_t rin = rsrc_of(in_bufs[worker], (uint32_t)c.n_b * sin * 4u);
+  const __amdgpu_buffer_rsrc_t rout = rsrc_of(out_bufs[worker], (uint32_t)c.n_b * son * 4u);
+  const int ncc = (c.kc + 15) / 16, nt0 = c.nt[0], ntaps = a.gbegin[a.ngroups];
+  const uint32_t wplane = (uint32_t)ntaps * 192u;  // weight pieces of one (t0, chunk)
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wt + (size_t)ntile * nt0 * ncc * wplane, (uint32_t)(nt0 * ncc) * wplane * 16u);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, m = lane & 31;
+
+  // this thread's patch pieces: 8 channels (half ph) of cell `cell`; row and column in input steps
+  int prow[PA], pcol[PA];
+  uint32_t plin[PA];
+#pragma unroll
+  for (int i = 0; i < PA; ++i) {
+    const int ph = (tid >> 5) & 1, cell = (tid & 31) + 32 * (tid >> 6) + 128 * i;
+    const int rr = (int)fd_div((uint32_t)cell, c.div_cw), cc = cell - rr * c.Cw;
+    prow[i] = cell < c.R * c.Cw ? g.in_base[1] + q1_0 * c.is[1] + rr * c.is[1] : -0x40000000;  // never in range
+    pcol[i] = g.in_base[2] + q2_0 * c.is[2] + cc * c.is[2];
+    plin[i] = (uint32_t)(prow[i] * si1 + pcol[i] * si2 + ph * 8) * 4u;
+  }
+  const uint32_t pl0 = (uint32_t)((tid >> 5) & 1) * HB + (uint32_t)((tid & 31) + 32 * (tid >> 6)) * 16u;  // piece i lies 128 * i cells further
+  char* const wlds = smem + 3 * PS;
+
+  // lane m of M-tile (wave, mt) multiplies window position (wave * MT + mt) * 32 + m.  The tile is accumulated transposed
+  // (the weights are the first MFMA operand): register v of lane (h, m) is channel ntile * 32 + 8 (v / 4) + 4 h + v % 4 of
+  // that position, so that a register quad is four consecutive channels and goes out as one 16-byte store.
+  uint32_t abase[MT], soff[MT];
+  const int ch0 = ntile * 32 + 4 * h;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int pidx = (wave * MT + mt) * 32 + m;
+    int wr = (int)fd_div((uint32_t)pidx, c.div_tc), wc = pidx - wr * c.tc;
+    const int q1 = q1_0 + wr, q2 = q2_0 + wc;
+    soff[mt] = kOob;
+    if (wr < c.tr && q1 < g.nq[1] && q2 < g.nq[2])
+      soff[mt] = ((g.out_base[1] + g.os[1] * q1) * so1 + (g.out_base[2] + g.os[2] * q2) * so2 + ch0) * 4u;
+    if (wr >= c.tr) wr = 0, wc = 0;  // idle position: multiplies something in range, never stored
+    abase[mt] = (uint32_t)h * HB + (uint32_t)(wr * c.Cw + wc) * 16u;
+  }
+  float bias[4][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bias[q][e] = (c.bias && ch0 + 8 * q + e < c.nc) ? ((const float*)c.bias)[ch0 + 8 * q + e] : 0.f;
+  const uint32_t wread = (uint32_t)(h * 32 + m) * 16u;
+
+  // stage order: output planes dealt to the groups in turn, kernel planes rotated so that neighbouring groups stand on
+  // the same input plane at the same moment (see conv_mfma.hip)
+  const int toff0 = c.tapoff[0][0], tstep = nt0 > 1 ? c.tapoff[0][1] - c.tapoff[0][0] : 0;
+  auto plane_of = [&](int q0, int t0) { return g.in_base[0] + q0 * c.is[0] + toff0 + t0 * tstep; };
+  const int rot_d = (nt0 > 1 && tstep != 0 && c.is[0] % tstep == 0) ? (c.is[0] / tstep) % nt0 : 0;
+  const bool dealt = rot_d != 0 && ngroups > 1;
+  const int pfirst = dealt ? (int)tile : (int)tile * c.g0, pstride = dealt ? ngroups : 1;
+  const int pcnt = dealt ? (ptotal - (int)tile + ngroups - 1) / ngroups : min(c.g0, ptotal - (int)tile * c.g0);
+  auto skew_of = [&](int q0) {
+    const int s = (rot_d * q0) % nt0;
+    return s == 0 ? 0 : (s > 0 ? nt0 - s : -s);  // (-d * q0) mod nt0
+  };
+  struct StagePos {
+    int p, n, q0, t0, cc, gr, j, sk;
+  };
+  auto advance = [&](StagePos& sp) {  // next valid stage after sp, or sp.p == pcnt
+    if (++sp.cc < ncc) return;
+    sp.cc = 0;
+    if (++sp.gr < a.ngroups) return;
+    sp.gr = 0;
+    ++sp.j;
+    while (sp.p < pcnt) {
+      while (sp.j < nt0) {
+        sp.t0 = sp.j + sp.sk < nt0 ? sp.j + sp.sk : sp.j + sp.sk - nt0;
+        const int i0 = plane_of(sp.q0, sp.t0);
+        if (i0 >= 0 && i0 < g.in_ext[0] && a.ngroups > 0) return;
+        ++sp.j;
+      }
+      ++sp.p;
+      sp.j = 0;
+      sp.q0 += pstride;
+      while (sp.q0 >= nq0) sp.q0 -= nq0, ++sp.n;
+      sp.sk = rot_d ? skew_of(sp.q0) : 0;
+    }
+  };
+
+  u32x4 ra[PA][2], rb[PB];
+  const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+  uint32_t wpieces = 0;  // weight pieces of the stage in the registers
+  auto load_stage = [&](const StagePos& sp) {
+    const int b1 = a.gbase[sp.gr][0], b2 = a.gbase[sp.gr][1];
+    const uint32_t shift = (uint32_t)(b1 * si1 + b2 * si2) * 4u;
+    const uint32_t sbase = ((uint32_t)sp.n * sin + (uint32_t)plane_of(sp.q0, sp.t0) * si0 + sp.cc * 16) * 4u;
+    const int left = c.kc - sp.cc * 16 - ((tid >> 5) & 1) * 8;  // channels of this thread's half
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+      const bool ok = (uint32_t)(prow[i] + b1) < (uint32_t)g.in_ext[1] && (uint32_t)(pcol[i] + b2) < (uint32_t)g.in_ext[2];
+      const uint32_t vo = plin[i] + shift;
+      ra[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rin, ok && left > 0 ? vo : kOob, sbase, 0);
+      ra[i][1] = __builtin_amdgcn_raw_buffer_load_b128(rin, ok && left > 4 ? vo + 16u : kOob, sbase, 0);
+    }
+    const int tb = a.gbegin[sp.gr];
+    const uint32_t np = (uint32_t)(a.gbegin[sp.gr + 1] - tb) * 192u;
+    const uint32_t wbase = ((uint32_t)(sp.t0 * ncc + sp.cc) * wplane + (uint32_t)tb * 192u) * 16u;
+#pragma unroll
+    for (int i = 0; i < PB; ++i)  // (a wave's 64 pieces are all there or all not)
+      if (i * 256 + wave_u * 64 < np) rb[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, tid * 16u, wbase + i * 4096u, 0);
+    wpieces = np;
+  };
+  auto write_stage = [&]() {
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(ra[i][e >> 2][e & 3]);
+      u32x4 hi, mid, lo;
+      split_eight(v, hi, mid, lo);
+      char* const at = smem + pl0 + i * 2048;
+      *(u32x4*)at = hi;
+      *(u32x4*)(at + PS) = mid;
+      *(u32x4*)(at + 2 * PS) = lo;
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i)
+      if (i * 256 + wave_u * 64 < wpieces) *(u32x4*)(wlds + (tid + i * 256) * 16) = rb[i];
+  };
+
+  union Frag {
+    u32x4 u;
+    bf16x8 v;
+  };
+  floatx16 acc[MT];
+  auto zero_acc = [&]() {
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+      for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+  };
+  // One set of operand registers: a tap's six products are ordered so that every operand of the next tap is read right
+  // after the last product that needs its register, two to four products before its own first use.
+  Frag fw[3], fx[3][MT];
+  auto read_w = [&](int p, int t) { fw[p].u = *(const u32x4*)(wlds + t * 3072 + p * 1024 + wread); };
+  auto read_x = [&](int p, uint32_t cell16) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) fx[p][mt].u = *(const u32x4*)(smem + abase[mt] + cell16 + p * PS);
+  };
+  auto mm = [&](int pw, int px) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[pw].v, fx[px][mt].v, acc[mt], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int my_cell = lane < ntaps ? a.tapcell[lane] * 16 : 0;  // lane t keeps the patch offset of tap t
+  auto compute = [&](int gr) {
+    const int tb = a.gbegin[gr], nt = a.gbegin[gr + 1] - tb;
+    uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb);
+    read_w(2, 0);
+    read_x(0, cell);
+    read_w(1, 0);
+    read_w(0, 0);
+    read_x(2, cell);
+    read_x(1, cell);
+    for (int t = 0; t < nt; ++t) {
+      const int tn = t + 1 < nt ? t + 1 : t;  // (past the last tap: its own operands again)
+      cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + tn);
+      mm(2, 0);
+      read_w(2, tn);
+      mm(1, 0);
+      mm(0, 0);
+      read_x(0, cell);
+      mm(0, 2);
+      read_x(2, cell);
+      mm(1, 1);
+      read_w(1, tn);
+      mm(0, 1);
+      read_w(0, tn);
+      read_x(1, cell);
+    }
+  };
+
+  StagePos sp{0, pfirst / nq0, pfirst % nq0, 0, ncc - 1, a.ngroups - 1, -1, 0};  // the stage whose loads are in flight
+  sp.sk = rot_d ? skew_of(sp.q0) : 0;
+  advance(sp);
+  int on = pfirst / nq0, oq0 = pfirst % nq0;  // the output plane that is stored next
+  auto store_plane = [&]() {
+    const uint32_t obase = ((uint32_t)on * son + (uint32_t)(g.out_base[0] + g.os[0] * oq0) * so0) * 4u;
+    bool bad = false;
+    // (the plane's offset is added into the per-lane offset: with a scalar offset the compiler leaves out the wait states
+    // a 16-byte store needs before its data registers are written again)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool live = ch0 + 8 * q < c.nc;  // channel counts are multiples of 4: a quad is whole or absent
+        const uint32_t off = (live ? soff[mt] + (uint32_t)(8 * q) * 4u : kOob) + obase;
+        u32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          bad |= live && not_finite(acc[mt][4 * q + e]);
+          o[e] = __float_as_uint(acc[mt][4 * q + e] + bias[q][e]);
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(o, rout, off, 0, 0);
+      }
+    if (bad)  // rare: this lane's sums term by term in fp32
+      for (int t = 0; t < MT * 16; ++t) {
+        const int pidx = (wave * MT + (t >> 4)) * 32 + m, wr = pidx / c.tc, wc = pidx - wr * c.tc;
+        const int q1 = q1_0 + wr, q2 = q2_0 + wc, ch = ch0 + 8 * ((t >> 2) & 3) + (t & 3);
+        if (wr >= c.tr || q1 >= g.nq[1] || q2 >= g.nq[2] || ch >= c.nc) continue;
+        const float s = split_direct(a, g, (const float*)in_bufs[worker], on, oq0, q1, q2, ch) + (c.bias ? ((const float*)c.bias)[ch] : 0.f);
+        ((float*)out_bufs[worker])[(size_t)on * son + (size_t)(g.out_base[0] + g.os[0] * oq0) * so0 +
+                                   (size_t)(g.out_base[1] + g.os[1] * q1) * so1 + (size_t)(g.out_base[2] + g.os[2] * q2) * so2 + ch] = s;
+      }
+    oq0 += pstride;
+    while (oq0 >= nq0) oq0 -= nq0, ++on;
+  };
+  if (sp.p < pcnt) load_stage(sp);
+  for (int po = 0; po < pcnt; ++po) {  // output planes of this workgroup
+    zero_acc();
+    while (sp.p == po) {  // the stages that feed output plane po
+      const int gr = sp.gr;
+      write_stage();
+      __syncthreads();
+      advance(sp);
+      if (sp.p < pcnt) load_stage(sp);  // in flight while this stage multiplies
+      compute(gr);
+      __syncthreads();
+    }
+    store_plane();
+  }
+}
+
+// Weights in the order the kernel stages them: pieces [ntile][t0][chunk][tap in group order][plane][h][nn], 8 channels
+// k = 16 chunk + 8 h ... each of output channel ntile * 32 + nn; zero beyond the channel counts.  One thread per piece
+// of all three planes.
+__global__ __launch_bounds__(256) void corr_split_weights_kernel(SplitArgs a, u32x4* __restrict__ dst) {
+  const CorrArgs& c = a.c;
+  const int ncc = (c.kc + 15) / 16, ntaps = a.gbegin[a.ngroups];
+  const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (idx >= c.ntn * c.nt[0] * ncc * ntaps * 64) return;
+  const int hn = idx & 63;
+  int r = idx >> 6;
+  const int tap = r % ntaps; r /= ntaps;
+  const int cc = r % ncc; r /= ncc;
+  const int t0 = r % c.nt[0], ntile = r / c.nt[0];
+  const int ch = ntile * 32 + (hn & 31);
+  const int ft = (c.tapid[0][t0] * a.k1 + c.tapid[1][a.tap12[tap][0]]) * a.k2 + c.tapid[2][a.tap12[tap][1]];
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int k = cc * 16 + (hn >> 5) * 8 + e;
+    const int o = c.mode == 0 ? ch : k, i = c.mode == 0 ? k : ch;
+    v[e] = k < c.kc && ch < c.nc ? a.w[((size_t)o * a.ci + i) * a.taps + ft] : 0.f;
+  }
+  u32x4 hi, mid, lo;
+  split_eight(v, hi, mid, lo);
+  u32x4* const at = dst + (size_t)(idx >> 6) * 192 + hn;
+  at[0] = hi;
+  at[64] = mid;
+  at[128] = lo;
+}
+
+// ---- host side ------------------------------------------------------------------
+
+// Tap groups of a launch; false when there are more than the arguments hold.
+bool group_taps(SplitArgs& a) {
+  const CorrArgs& c = a.c;
+  if (c.nt[1] * c.nt[2] > kMaxTaps) return false;
+  int at = 0, most = 0;
+  a.ngroups = 0;
+  a.gbegin[0] = 0;
+  int span1 = 0, span2 = 0;
+  // first the groups with their tap indices, then the patch they need
+  for (int r1 = 0; r1 < c.is[1]; ++r1)
+    for (int r2 = 0; r2 < c.is[2]; ++r2) {
+      int i1[8], n1 = 0, i2[8], n2 = 0;
+      for (int t = 0; t < c.nt[1]; ++t)
+        if (((c.tapoff[1][t] - r1) % c.is[1] + c.is[1]) % c.is[1] == 0) i1[n1++] = t;
+      for (int t = 0; t < c.nt[2]; ++t)
+        if (((c.tapoff[2][t] - r2) % c.is[2] + c.is[2]) % c.is[2] == 0) i2[n2++] = t;
+      if (n1 == 0 || n2 == 0) continue;
+      const int rows = std::max(1, kGroupTaps / n2), parts = (n1 + rows - 1) / rows, per = (n1 + parts - 1) / parts;
+      for (int b = 0; b < n1; b += per) {
+        if (a.ngroups >= kMaxGroups) return false;
+        const int e = std::min(n1, b + per);
+        int lo1 = INT32_MAX, hi1 = INT32_MIN, lo2 = INT32_MAX, hi2 = INT32_MIN;
+        for (int i = b; i < e; ++i) lo1 = std::min(lo1, c.tapoff[1][i1[i]]), hi1 = std::max(hi1, c.tapoff[1][i1[i]]);
+        for (int j = 0; j < n2; ++j) lo2 = std::min(lo2, c.tapoff[2][i2[j]]), hi2 = std::max(hi2, c.tapoff[2][i2[j]]);
+        a.gbase[a.ngroups][0] = lo1;
+        a.gbase[a.ngroups][1] = lo2;
+        span1 = std::max(span1, (hi1 - lo1) / c.is[1]);
+        span2 = std::max(span2, (hi2 - lo2) / c.is[2]);
+        for (int i = b; i < e; ++i)
+          for (int j = 0; j < n2; ++j) {
+            a.tap12[at][0] = (uint8_t)i1[i];
+            a.tap12[at][1] = (uint8_t)i2[j];
+            ++at;
+          }
+        most = std::max(most, at - a.gbegin[a.ngroups]);
+        a.gbegin[++a.ngroups] = at;
+      }
+    }
+  a.c.tapspan[1] = span1;
+  a.c.tapspan[2] = span2;
+  a.c.ck = most;
+  return true;
+}
+
+// window tr x tc of 128 mt positions and the patch of its groups
+void set_window(SplitArgs& a, int mt, int tc) {
+  CorrArgs& c = a.c;
+  const int cap = 128 * mt;
+  c.tc = std::max(1, std::min(tc, cap));
+  c.tr = std::max(1, cap / c.tc);
+  c.R = c.tr + c.tapspan[1];
+  c.Cw = c.tc + c.tapspan[2];
+  c.div_cw = make_fastdiv((uint32_t)c.Cw);
+  c.div_tc = make_fastdiv((uint32_t)c.tc);
+  for (int gr = 0; gr < a.ngroups; ++gr)
+    for (int t = a.gbegin[gr]; t < a.gbegin[gr + 1]; ++t)
+      a.tapcell[t] = ((c.tapoff[1][a.tap12[t][0]] - a.gbase[gr][0]) / c.is[1] * c.Cw +
+                                (c.tapoff[2][a.tap12[t][1]] - a.gbase[gr][1]) / c.is[2]);
+}
+
+double window_share(int cap, int tc, int nq1, int nq2) {  // fraction of the multiplied positions that are outputs
+  const int tr = std::max(1, cap / tc);
+  return (double)nq1 * nq2 / ((double)((nq2 + tc - 1) / tc) * ((nq1 + tr - 1) / tr) * cap);
+}
+
+int pieces_of(const SplitArgs& a) { return (a.c.R * a.c.Cw * 2 + 255) / 256; }  // per thread
+
+// The window of a launch: M-tiles per wave (0: none fits).  The window that wastes the fewest multiplied positions; of
+// equal ones the one with the smallest patch per position.
+int choose_window(const distdl_plan* p, SplitArgs& a) {
+  int nq1 = 1, nq2 = 1;
+  for (const WorkerDev& wd : p->workers) {
+    const PerWorker g = derive(wd, a.c);
+    nq1 = std::max(nq1, g.nq[1]);
+    nq2 = std::max(nq2, g.nq[2]);
+  }
+  double best = -1;
+  int best_mt = 0, best_tc = 0;
+  for (int mt : {3, 2, 1})
+    for (int tc = 1; tc <= std::min(128 * mt, nq2); ++tc) {
+      set_window(a, mt, tc);
+      const int pa = pieces_of(a);
+      if (pa > 4 || split_lds_bytes(pa <= 3 && mt == 2 ? 3 : 4, a.c.ck) > 80 * 1024 || (mt == 3 && a.c.ck > 9)) continue;
+      // a tap costs a wave 6 mt MFMAs and 3 mt + 3 operand reads: fewer M-tiles pay relatively more for the weights
+      const double share = window_share(128 * mt, tc, nq1, nq2), patch = (double)(a.c.R * a.c.Cw) / (128 * mt);
+      const double score = share * (mt == 1 ? 0.75 : 1.0) / (1.0 + 0.05 * patch);
+      if (score > best * 1.001) best = score, best_mt = mt, best_tc = tc;
+    }
+  if (best_mt) set_window(a, best_mt, best_tc);
+  return best_mt;
+}
+
+SplitArgs split_args(const distdl_plan* p, const CorrArgs& c, bool& ok) {
+  SplitArgs a{};
+  a.c = c;
+  a.ci = (int32_t)p->n_ci;
+  a.co = (int32_t)p->n_co;
+  a.taps = p->ksize[0] * p->ksize[1] * p->ksize[2];
+  a.k1 = p->ksize[1];
+  a.k2 = p->ksize[2];
+  ok = group_taps(a);
+  return a;
+}
+
+size_t weight_floats(const SplitArgs& a) {
+  return (size_t)a.c.ntn * a.c.nt[0] * ((a.c.kc + 15) / 16) * a.gbegin[a.ngroups] * 192 * 4;
+}
+
+int64_t tiles_of_worker(const PerWorker& g, const CorrArgs& c) {
+  return (((int64_t)c.n_b * g.nq[0] + c.g0 - 1) / c.g0) * ((g.nq[1] + c.tr - 1) / c.tr) * ((g.nq[2] + c.tc - 1) / c.tc) * c.ntn;
+}
+
+// One launch of a layer, everything but the pointers; kept in the plan.
+struct Launch {
+  SplitArgs a;
+  int mt = 0;
+  size_t floats = 0;  // of weights
+  unsigned blocks = 0;
+};
+struct Launches {
+  std::vector<Launch> v;  // forward, then the classes of the data gradient
+  size_t scratch = 0;
+};
+
+bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
+  bool ok;
+  l.a = split_args(p, c, ok);
+  SplitArgs& a = l.a;
+  if (!ok) return false;
+  l.mt = choose_window(p, a);
+  if (l.mt == 0) return false;
+  l.floats = weight_floats(a);
+  // Output planes per workgroup: a fixed set-up (its address tables, about 8 * 10^3 clocks) against the number of rounds
+  // of 512 workgroups; at least four groups per worker where neighbouring planes share input planes (conv_mfma.hip).
+  int64_t planes_max = 0, per_plane = 0;
+  for (const WorkerDev& wd : p->workers) {
+    const PerWorker g = derive(wd, a.c);
+    planes_max = std::max<int64_t>(planes_max, p->n_b * g.nq[0]);
+    per_plane = std::max<int64_t>(per_plane, (int64_t)((g.nq[1] + a.c.tr - 1) / a.c.tr) * ((g.nq[2] + a.c.tc - 1) / a.c.tc) * a.c.ntn);
+  }
+  per_plane *= p->n_workers;
+  const double stage = (double)a.c.nt[0] * ((a.c.kc + 15) / 16) * (a.gbegin[a.ngroups] * l.mt * 6 * 32.0 * 2 * 1.4 + a.ngroups * 1500.0);
+  const int tstep0 = a.c.nt[0] > 1 ? a.c.tapoff[0][1] - a.c.tapoff[0][0] : 0;
+  const bool shares = tstep0 != 0 && a.c.is[0] % tstep0 == 0 && (a.c.is[0] / tstep0) % a.c.nt[0] != 0;
+  const int64_t g0_max = shares ? std::max<int64_t>(1, planes_max / 4) : std::max<int64_t>(1, planes_max);
+  double best = 1e300;
+  a.c.g0 = 1;
+  for (int64_t g0 = 1; g0 <= g0_max; ++g0) {
+    const int64_t wgs = (planes_max + g0 - 1) / g0 * per_plane;
+    const double cost = (double)((wgs + 511) / 512) * (8.0e3 + g0 * stage);
+    if (cost < best * 0.97) best = cost, a.c.g0 = (int32_t)g0;
+  }
+  int64_t tiles = 0;
+  for (const WorkerDev& wd : p->workers) tiles = std::max(tiles, tiles_of_worker(derive(wd, a.c), a.c));
+  const int64_t blocks = (tiles * p->n_workers + 7) / 8 * 8;
+  if (blocks > 0x7fffff00) return false;
+  a.c.tiles_max = (int32_t)tiles;
+  l.blocks = (unsigned)blocks;
+  return true;
+}
+
+template <int MT, int PA, int PB>
+int launch_variant(distdl_plan* p, const SplitArgs& a, unsigned blocks, void** in_tab, void** out_tab, hipStream_t st) {
+  const int lds = split_lds_bytes(PA, a.c.ck);
+  if (lds > 64 * 1024)
+    if (int rc = allow_large_lds<corr_split_kernel<MT, PA, PB>>()) return rc;
+  hipLaunchKernelGGL((corr_split_kernel<MT, PA, PB>), dim3(blocks), dim3(256), lds, st, p->d_workers, in_tab, out_tab, a);
+  return DISTDL_OK;
+}
+
+int launch_corr_split(distdl_plan* p, const Launch& l, const float* w, float* wscratch, const float* bias, void** in_tab,
+                      void** out_tab, const char* name, hipStream_t st) {
+  if (l.blocks == 0) return DISTDL_OK;
+  SplitArgs a = l.a;
+  a.w = w;
+  a.wt = (const u32x4*)wscratch;
+  a.c.bias = bias;
+  const int64_t n = (int64_t)(l.floats / 12);  // threads: three pieces of four floats each
+  if (n > 0) {
+    ProfScope prof("conv_relayout_w", st);
+    hipLaunchKernelGGL(corr_split_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a, (u32x4*)wscratch);
+  }
+  constexpr int kPb = (kGroupTaps * 192 + 255) / 256, kPb3 = (9 * 192 + 255) / 256;
+  ProfScope prof(name, st);
+  if (l.mt == 3) return launch_variant<3, 4, kPb3>(p, a, l.blocks, in_tab, out_tab, st);
+  if (l.mt == 2 && pieces_of(a) <= 3) return launch_variant<2, 3, kPb>(p, a, l.blocks, in_tab, out_tab, st);
+  if (l.mt == 2) return launch_variant<2, 4, kPb>(p, a, l.blocks, in_tab, out_tab, st);
+  return launch_variant<1, 4, kPb>(p, a, l.blocks, in_tab, out_tab, st);
+}
+
+template <class F>
+bool for_classes(const distdl_plan* p, F&& f) {
+  for (int p0 = 0; p0 < p->stride[0]; ++p0)
+    for (int p1 = 0; p1 < p->stride[1]; ++p1)
+      for (int p2 = 0; p2 < p->stride[2]; ++p2) {
+        const int par[3] = {p0, p1, p2};
+        if (!f(class_args(p, par))) return false;
+      }
+  return true;
+}
+
+}  // namespace
+
+bool corr_split_supported(const distdl_plan* p) {
+  if (p->corr_split_ok >= 0) return p->corr_split_ok != 0;
+  auto all = std::make_shared<Launches>();
+  auto add = [&](const CorrArgs& c) {
+    all->v.emplace_back();
+    return plan_launch(p, c, all->v.back());
+  };
+  auto decide = [&]() {
+    if (p->explicit_halo || p->dtype != DISTDL_F32) return false;
+    if (p->n_ci % 4 || p->n_co % 4) return false;  // 16-byte channel pieces
+    if ((double)p->n_b * p->max_buf_cells * std::max(p->n_ci, p->n_co) * 4.0 >= 2147480000.0) return false;
+    if ((double)p->n_b * p->max_out_cells * std::max(p->n_ci, p->n_co) * 4.0 >= 2147480000.0) return false;
+    for (int d = 0; d < 3; ++d)
+      if (p->ksize[d] > 8) return false;
+    if (p->stride[0] > 4 || p->stride[1] > 4 || p->stride[2] > 4) return false;
+    return add(forward_args(p)) && for_classes(p, add);
+  };
+  p->corr_split_ok = decide() ? 1 : 0;
+  if (p->corr_split_ok == 0) return false;
+  size_t bwd = 0;
+  for (size_t i = 1; i < all->v.size(); ++i) bwd += all->v[i].floats;
+  all->scratch = std::max(all->v[0].floats, bwd);
+  p->corr_split_launches = all;
+  return true;
+}
+
+int conv_fwd_split(distdl_plan* p, const float* w, const float* bias, hipStream_t st) {
+  const Launches& all = *(const Launches*)p->corr_split_launches.get();
+  if (int rc = ensure_wscratch(p, all.scratch)) return rc;
+  return launch_corr_split(p, all.v[0], w, p->d_wt, bias, p->tab_x.dev, p->tab_y.dev, "conv_fwd_split", st);
+}
+
+int conv_bwd_data_split(distdl_plan* p, const float* w, hipStream_t st) {
+  const Launches& all = *(const Launches*)p->corr_split_launches.get();
+  if (int rc = ensure_wscratch(p, all.scratch)) return rc;
+  float* at = p->d_wt;
+  for (size_t i = 1; i < all.v.size(); ++i) {
+    if (int rc = launch_corr_split(p, all.v[i], w, at, nullptr, p->tab_dy.dev, p->tab_dx.dev, "conv_bwd_data_split", st)) return rc;
+    at += all.v[i].floats;
+  }
+  return DISTDL_OK;
+}
+
+}  // namespace distdl
