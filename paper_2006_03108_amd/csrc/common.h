@@ -254,9 +254,9 @@ struct distdl_plan {
   float* d_wt = nullptr;
   distdl::FastDiv* d_pooldiv = nullptr;  // per worker: division by buf[1], buf[2], out[1], out[2] (pooling kernels)
   size_t wt_elems = 0;
+  std::vector<float*> wt_retired;  // smaller ones that d_wt took the place of
   mutable int maxpool_ok = -1;    // 1 once every max-pool window is known to hold an in-domain cell
-  mutable int corr_split_ok = -1;  // likewise of corr_split_supported()
-  mutable std::shared_ptr<void> corr_split_launches;  // its launches, without the pointers
+  mutable std::shared_ptr<void> corr_split_plan;  // the launches of conv_split.hip, once asked for
   mutable int corr_mfma_ok = -1;  // cached answer of corr_mfma_supported(): -1 not asked yet
 
   int coords(int w, int d) const {

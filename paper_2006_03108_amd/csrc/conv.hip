@@ -232,13 +232,7 @@ static int check_conv_plan(const distdl_plan* p) {
 static int prepare_weights(distdl_plan* p, const void* w, hipStream_t st) {
   ConvDev c = conv_params(p);
   size_t n = (size_t)c.taps * c.ci * c.co;
-  if (p->wt_elems < n) {
-    if (p->d_wt) (void)hipFree(p->d_wt);  // waits for kernels still reading it
-    p->d_wt = nullptr;
-    p->wt_elems = 0;
-    DISTDL_HIP_TRY(hipMalloc((void**)&p->d_wt, n * sizeof(float)));
-    p->wt_elems = n;
-  }
+  if (int rc = ensure_wscratch(p, n)) return rc;
   ProfScope prof("conv_relayout_w", st);
   if (p->dtype == DISTDL_BF16)
     hipLaunchKernelGGL(relayout_w_kernel<uint16_t>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
@@ -335,7 +329,7 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
     DISTDL_HIP_TRY(hipGetLastError());
     return DISTDL_OK;
   }
-  if (xvec && corr_split_supported(plan)) {
+  if (xvec && corr_split_supported(plan, false)) {
     if ((rc = conv_fwd_split(plan, (const float*)w_dev, (const float*)bias_dev, st))) return rc;
     DISTDL_HIP_TRY(hipGetLastError());
     return DISTDL_OK;
@@ -402,7 +396,7 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   int64_t total = plan->n_b * plan->max_buf_cells * c.ci;
   if (corr16_bwd_supported(plan, aligned)) {
     if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
-  } else if (aligned && corr_split_supported(plan)) {
+  } else if (aligned && corr_split_supported(plan, true)) {
     if ((rc = conv_bwd_data_split(plan, (const float*)w_dev, st))) return rc;
   } else if (data_mfma) {
     if ((rc = conv_bwd_data_mfma(plan, w_dev, st))) return rc;

@@ -1480,10 +1480,12 @@ static int launch_corr(distdl_plan* p, CorrArgs a, const void* w, float* wscratc
 // gradient one per parity class (used one after the other on the stream).
 int ensure_wscratch(distdl_plan* p, size_t elems) {
   if (p->wt_elems >= elems) return DISTDL_OK;
-  if (p->d_wt) (void)hipFree(p->d_wt);
-  p->d_wt = nullptr;
-  p->wt_elems = 0;
-  DISTDL_HIP_TRY(hipMalloc((void**)&p->d_wt, elems * sizeof(float)));
+  float* grown = nullptr;
+  DISTDL_HIP_TRY(hipMalloc((void**)&grown, elems * sizeof(float)));
+  // A block that is too small goes with the plan: a recorded graph may hold its address.  There is one size per
+  // direction, type of kernel and alignment, so they are few.
+  if (p->d_wt) p->wt_retired.push_back(p->d_wt);
+  p->d_wt = grown;
   p->wt_elems = elems;
   return DISTDL_OK;
 }

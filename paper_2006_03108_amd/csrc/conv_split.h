@@ -1,11 +1,12 @@
 // Convolution of fp32 tensors on the bf16 matrix cores (conv_split.hip).  The entry points expect the plan's pointer
-// tables to be uploaded and all arrays 16-byte aligned.
+// tables to be uploaded; the tensors that are read, and (channel counts that are multiples of 4) those that are written,
+// are 16-byte aligned.
 #pragma once
 #include "common.h"
 
 namespace distdl {
 
-bool corr_split_supported(const distdl_plan* p);
+bool corr_split_supported(const distdl_plan* p, bool backward);
 int conv_fwd_split(distdl_plan* p, const float* w, const float* bias, hipStream_t st);
 int conv_bwd_data_split(distdl_plan* p, const float* w, hipStream_t st);
 

@@ -1,9 +1,10 @@
 // Local convolution of fp32 tensors on the bf16 matrix cores (split_bf16.h): forward and data gradient of the layers
-// whose channel counts are multiples of 4, as an implicit GEMM over staged patches (Sec. 4, "Conv" and "[dConv]*").
+// whose contraction channels are a multiple of 4, as an implicit GEMM over staged patches (Sec. 4, "Conv" and "[dConv]*").
 //
 //   out[q][n] = sum_taps sum_k W[tap][k][n] * in[base + q * step + tapoff][k]
 //
-// as in conv_mfma.hip: forward in = x^, out = y; data gradient one launch per stride-parity class of dx^, in = dy.
+// as in conv_mfma.hip: forward in = x^, out = y; data gradient once per stride-parity class of dx^, in = dy
+// (the classes that take the same kernel variant are one launch).
 // A workgroup of four waves owns a tr x tc window of 128 MT output positions and walks output planes.  A stage is
 //   (kernel plane t0, tap group, 16 channels):
 // the input cells that the group's taps read are loaded, split into three bf16 planes and written to LDS, as are the
@@ -37,15 +38,27 @@ constexpr int kMaxGroups = 32, kMaxTaps = 64, kGroupTaps = 10;
 
 struct SplitArgs {
   CorrArgs c;
-  const u32x4* wt;  // weights as operand pieces
-  const float* w;   // the caller's weights
   int32_t ci, co, taps, k1, k2;
+  int64_t woff;                             // first weight piece
   int32_t ngroups;
   int32_t gbegin[kMaxGroups + 1];           // taps of group i: gbegin[i] ... gbegin[i + 1]
   int32_t gbase[kMaxGroups][2];             // input offset of the group's first patch row / cell (of position 0)
   int32_t tapcell[kMaxTaps];                // patch cell of a tap for position 0
   uint8_t tap12[kMaxTaps][2];               // its indices along dimensions 1 and 2
 };
+
+// The arguments of a launch of several classes lie in a table of the plan's; read through the constant address space its
+// entries are scalar loads.
+typedef const __attribute__((address_space(4))) SplitArgs* TablePtr;
+__device__ inline TablePtr args_at(const SplitArgs* tab, int i) { return (TablePtr)(uintptr_t)(tab + i); }
+template <class ArgsPtr>
+__device__ inline PerWorker derive_of(const WorkerDev& wd, ArgsPtr a) {
+  CorrArgs c;
+  c.mode = a->c.mode;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) c.s[d] = a->c.s[d], c.par[d] = a->c.par[d];
+  return derive(wd, c);
+}
 
 __device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
@@ -59,8 +72,10 @@ constexpr uint32_t plane_bytes(int PA) { return 2 * half_bytes(PA); }
 constexpr int split_lds_bytes(int PA, int taps) { return 3 * plane_bytes(PA) + taps * 3072; }
 
 // output (position q, channel ch) term by term in fp32
-__device__ inline float split_direct(const SplitArgs& a, const PerWorker& g, const float* in, int n, int q0, int q1, int q2, int ch) {
-  const CorrArgs& c = a.c;
+template <class ArgsPtr>
+__device__ inline float split_direct(ArgsPtr a, const float* w, const PerWorker& g, const float* in, int n, int q0, int q1,
+                                     int q2, int ch) {
+  const auto& c = a->c;
   float sum = 0.f;
   for (int t0 = 0; t0 < c.nt[0]; ++t0)
     for (int t1 = 0; t1 < c.nt[1]; ++t1)
@@ -68,11 +83,11 @@ __device__ inline float split_direct(const SplitArgs& a, const PerWorker& g, con
         const int i0 = g.in_base[0] + q0 * c.is[0] + c.tapoff[0][t0], i1 = g.in_base[1] + q1 * c.is[1] + c.tapoff[1][t1],
                   i2 = g.in_base[2] + q2 * c.is[2] + c.tapoff[2][t2];
         if (i0 < 0 || i0 >= g.in_ext[0] || i1 < 0 || i1 >= g.in_ext[1] || i2 < 0 || i2 >= g.in_ext[2]) continue;
-        const int tap = (c.tapid[0][t0] * a.k1 + c.tapid[1][t1]) * a.k2 + c.tapid[2][t2];
+        const int tap = (c.tapid[0][t0] * a->k1 + c.tapid[1][t1]) * a->k2 + c.tapid[2][t2];
         const float* x = in + ((((size_t)n * g.in_ext[0] + i0) * g.in_ext[1] + i1) * g.in_ext[2] + i2) * c.kc;
         for (int k = 0; k < c.kc; ++k) {
           const int o = c.mode == 0 ? ch : k, i = c.mode == 0 ? k : ch;
-          sum = fmaf(x[k], a.w[((size_t)o * a.ci + i) * a.taps + tap], sum);
+          sum = fmaf(x[k], w[((size_t)o * a->ci + i) * a->taps + tap], sum);
         }
       }
   return sum;
@@ -80,11 +95,11 @@ __device__ inline float split_direct(const SplitArgs& a, const PerWorker& g, con
 
 // MT: 32-position M-tiles per wave; PA: pairs of 16-byte pieces (8 channels of a cell) per thread and stage; PB: weight
 // pieces per thread and stage
-template <int MT, int PA, int PB>
-__global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __restrict__ workers, void* const* in_bufs,
-                                                            void* const* out_bufs, SplitArgs a) {
+template <int MT, int PA, int PB, class ArgsPtr>
+__device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restrict__ workers, void* const* in_bufs,
+                                           void* const* out_bufs, const u32x4* wt, const float* w, const float* bias_in) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const CorrArgs& c = a.c;
+  const auto& c = a->c;
   constexpr uint32_t HB = half_bytes(PA), PS = plane_bytes(PA);
   // consecutive tiles (which share input rows) stay on one XCD, i.e. behind one L2
   const uint32_t nblk = gridDim.x, r = (blockIdx.x & 7u) * (nblk >> 3) + (blockIdx.x >> 3);
@@ -92,7 +107,7 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
   uint32_t tile = r - worker * c.tiles_max;
   if (worker >= (uint32_t)c.n_workers) return;
   const WorkerDev wd = workers[worker];
-  const PerWorker g = derive(wd, c);
+  const PerWorker g = derive_of(wd, a);
   const int nt2tiles = (g.nq[2] + c.tc - 1) / c.tc, nt1tiles = (g.nq[1] + c.tr - 1) / c.tr;
   const int nq0 = g.nq[0], ptotal = c.n_b * nq0, ngroups = (ptotal + c.g0 - 1) / c.g0;
   if ((int64_t)tile >= (int64_t)ngroups * nt1tiles * nt2tiles * c.ntn) return;
@@ -105,18 +120,19 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
   const uint32_t so2 = c.nc, so1 = g.out_ext[2] * so2, so0 = g.out_ext[1] * so1, son = g.out_ext[0] * so0;
   const __amdgpu_buffer_rsrc_t rin = rsrc_of(in_bufs[worker], (uint32_t)c.n_b * sin * 4u);
   const __amdgpu_buffer_rsrc_t rout = rsrc_of(out_bufs[worker], (uint32_t)c.n_b * son * 4u);
-  const int ncc = (c.kc + 15) / 16, nt0 = c.nt[0], ntaps = a.gbegin[a.ngroups];
+  const int ncc = (c.kc + 15) / 16, nt0 = c.nt[0], ntaps = a->gbegin[a->ngroups];
   const uint32_t wplane = (uint32_t)ntaps * 192u;  // weight pieces of one (t0, chunk)
-  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wt + (size_t)ntile * nt0 * ncc * wplane, (uint32_t)(nt0 * ncc) * wplane * 16u);
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(wt + a->woff + (size_t)ntile * nt0 * ncc * wplane, (uint32_t)(nt0 * ncc) * wplane * 16u);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, m = lane & 31;
 
+  const FastDiv div_cw{c.div_cw.mul, c.div_cw.sh1, c.div_cw.sh2, c.div_cw.d}, div_tc{c.div_tc.mul, c.div_tc.sh1, c.div_tc.sh2, c.div_tc.d};
   // this thread's patch pieces: 8 channels (half ph) of cell `cell`; row and column in input steps
   int prow[PA], pcol[PA];
   uint32_t plin[PA];
 #pragma unroll
   for (int i = 0; i < PA; ++i) {
     const int ph = (tid >> 5) & 1, cell = (tid & 31) + 32 * (tid >> 6) + 128 * i;
-    const int rr = (int)fd_div((uint32_t)cell, c.div_cw), cc = cell - rr * c.Cw;
+    const int rr = (int)fd_div((uint32_t)cell, div_cw), cc = cell - rr * c.Cw;
     prow[i] = cell < c.R * c.Cw ? g.in_base[1] + q1_0 * c.is[1] + rr * c.is[1] : -0x40000000;  // never in range
     pcol[i] = g.in_base[2] + q2_0 * c.is[2] + cc * c.is[2];
     plin[i] = (uint32_t)(prow[i] * si1 + pcol[i] * si2 + ph * 8) * 4u;
@@ -132,7 +148,7 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     const int pidx = (wave * MT + mt) * 32 + m;
-    int wr = (int)fd_div((uint32_t)pidx, c.div_tc), wc = pidx - wr * c.tc;
+    int wr = (int)fd_div((uint32_t)pidx, div_tc), wc = pidx - wr * c.tc;
     const int q1 = q1_0 + wr, q2 = q2_0 + wc;
     soff[mt] = kOob;
     if (wr < c.tr && q1 < g.nq[1] && q2 < g.nq[2])
@@ -144,7 +160,7 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) bias[q][e] = (c.bias && ch0 + 8 * q + e < c.nc) ? ((const float*)c.bias)[ch0 + 8 * q + e] : 0.f;
+    for (int e = 0; e < 4; ++e) bias[q][e] = (bias_in && ch0 + 8 * q + e < c.nc) ? bias_in[ch0 + 8 * q + e] : 0.f;
   const uint32_t wread = (uint32_t)(h * 32 + m) * 16u;
 
   // stage order: output planes dealt to the groups in turn, kernel planes rotated so that neighbouring groups stand on
@@ -165,14 +181,14 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
   auto advance = [&](StagePos& sp) {  // next valid stage after sp, or sp.p == pcnt
     if (++sp.cc < ncc) return;
     sp.cc = 0;
-    if (++sp.gr < a.ngroups) return;
+    if (++sp.gr < a->ngroups) return;
     sp.gr = 0;
     ++sp.j;
     while (sp.p < pcnt) {
       while (sp.j < nt0) {
         sp.t0 = sp.j + sp.sk < nt0 ? sp.j + sp.sk : sp.j + sp.sk - nt0;
         const int i0 = plane_of(sp.q0, sp.t0);
-        if (i0 >= 0 && i0 < g.in_ext[0] && a.ngroups > 0) return;
+        if (i0 >= 0 && i0 < g.in_ext[0] && a->ngroups > 0) return;
         ++sp.j;
       }
       ++sp.p;
@@ -187,7 +203,7 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
   const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
   uint32_t wpieces = 0;  // weight pieces of the stage in the registers
   auto load_stage = [&](const StagePos& sp) {
-    const int b1 = a.gbase[sp.gr][0], b2 = a.gbase[sp.gr][1];
+    const int b1 = a->gbase[sp.gr][0], b2 = a->gbase[sp.gr][1];
     const uint32_t shift = (uint32_t)(b1 * si1 + b2 * si2) * 4u;
     const uint32_t sbase = ((uint32_t)sp.n * sin + (uint32_t)plane_of(sp.q0, sp.t0) * si0 + sp.cc * 16) * 4u;
     const int left = c.kc - sp.cc * 16 - ((tid >> 5) & 1) * 8;  // channels of this thread's half
@@ -198,8 +214,8 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
       ra[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rin, ok && left > 0 ? vo : kOob, sbase, 0);
       ra[i][1] = __builtin_amdgcn_raw_buffer_load_b128(rin, ok && left > 4 ? vo + 16u : kOob, sbase, 0);
     }
-    const int tb = a.gbegin[sp.gr];
-    const uint32_t np = (uint32_t)(a.gbegin[sp.gr + 1] - tb) * 192u;
+    const int tb = a->gbegin[sp.gr];
+    const uint32_t np = (uint32_t)(a->gbegin[sp.gr + 1] - tb) * 192u;
     const uint32_t wbase = ((uint32_t)(sp.t0 * ncc + sp.cc) * wplane + (uint32_t)tb * 192u) * 16u;
 #pragma unroll
     for (int i = 0; i < PB; ++i)  // (a wave's 64 pieces are all there or all not)
@@ -249,9 +265,9 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
       acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[pw].v, fx[px][mt].v, acc[mt], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
-  const int my_cell = lane < ntaps ? a.tapcell[lane] * 16 : 0;  // lane t keeps the patch offset of tap t
+  const int my_cell = lane < ntaps ? a->tapcell[lane] * 16 : 0;  // lane t keeps the patch offset of tap t
   auto compute = [&](int gr) {
-    const int tb = a.gbegin[gr], nt = a.gbegin[gr + 1] - tb;
+    const int tb = a->gbegin[gr], nt = a->gbegin[gr + 1] - tb;
     uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb);
     read_w(2, 0);
     read_x(0, cell);
@@ -277,7 +293,7 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
     }
   };
 
-  StagePos sp{0, pfirst / nq0, pfirst % nq0, 0, ncc - 1, a.ngroups - 1, -1, 0};  // the stage whose loads are in flight
+  StagePos sp{0, pfirst / nq0, pfirst % nq0, 0, ncc - 1, a->ngroups - 1, -1, 0};  // the stage whose loads are in flight
   sp.sk = rot_d ? skew_of(sp.q0) : 0;
   advance(sp);
   int on = pfirst / nq0, oq0 = pfirst % nq0;  // the output plane that is stored next
@@ -286,11 +302,23 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
     bool bad = false;
     // (the plane's offset is added into the per-lane offset: with a scalar offset the compiler leaves out the wait states
     // a 16-byte store needs before its data registers are written again)
+    if (c.nc & 3) {  // (uniform) quads need not be whole, nor aligned
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int e = 8 * (v >> 2) + (v & 3);
+          const bool live = ch0 + e < c.nc;
+          bad |= live && not_finite(acc[mt][v]);
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[mt][v] + bias[v >> 2][v & 3]), rout,
+                                                (live ? soff[mt] + (uint32_t)e * 4u : kOob) + obase, 0, 0);
+        }
+    } else
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const bool live = ch0 + 8 * q < c.nc;  // channel counts are multiples of 4: a quad is whole or absent
+        const bool live = ch0 + 8 * q < c.nc;  // a quad is whole or absent
         const uint32_t off = (live ? soff[mt] + (uint32_t)(8 * q) * 4u : kOob) + obase;
         u32x4 o;
 #pragma unroll
@@ -305,7 +333,7 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
         const int pidx = (wave * MT + (t >> 4)) * 32 + m, wr = pidx / c.tc, wc = pidx - wr * c.tc;
         const int q1 = q1_0 + wr, q2 = q2_0 + wc, ch = ch0 + 8 * ((t >> 2) & 3) + (t & 3);
         if (wr >= c.tr || q1 >= g.nq[1] || q2 >= g.nq[2] || ch >= c.nc) continue;
-        const float s = split_direct(a, g, (const float*)in_bufs[worker], on, oq0, q1, q2, ch) + (c.bias ? ((const float*)c.bias)[ch] : 0.f);
+        const float s = split_direct(a, w, g, (const float*)in_bufs[worker], on, oq0, q1, q2, ch) + (bias_in ? bias_in[ch] : 0.f);
         ((float*)out_bufs[worker])[(size_t)on * son + (size_t)(g.out_base[0] + g.os[0] * oq0) * so0 +
                                    (size_t)(g.out_base[1] + g.os[1] * q1) * so1 + (size_t)(g.out_base[2] + g.os[2] * q2) * so2 + ch] = s;
       }
@@ -328,12 +356,30 @@ __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __r
   }
 }
 
+// One class, its arguments in the kernel's (their loads cost nothing to repeat, where those of the table stay in registers:
+// 0.48 against 1.3 ms per class on the 5^3 stride-2 layer), and several, blockIdx.y, from the table: small layers, where
+// it is launches that count (8 -> 64 channels, 3^3, stride 2, 3 x 5 x 6 x 7: 205 us with 16 launches, 71 with 2).
+template <int MT, int PA, int PB>
+__global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __restrict__ workers, void* const* in_bufs,
+                                                            void* const* out_bufs, SplitArgs a, const u32x4* wt,
+                                                            const float* w, const float* bias) {
+  corr_split<MT, PA, PB, const SplitArgs*>(&a, workers, in_bufs, out_bufs, wt, w, bias);
+}
+template <int MT, int PA, int PB>
+__global__ __launch_bounds__(256, 2) void corr_split_classes_kernel(const WorkerDev* __restrict__ workers, void* const* in_bufs,
+                                                                    void* const* out_bufs, const SplitArgs* tab, int first,
+                                                                    const u32x4* wt, const float* w, const float* bias) {
+  corr_split<MT, PA, PB, TablePtr>(args_at(tab, first + (int)blockIdx.y), workers, in_bufs, out_bufs, wt, w, bias);
+}
+
 // Weights in the order the kernel stages them: pieces [ntile][t0][chunk][tap in group order][plane][h][nn], 8 channels
 // k = 16 chunk + 8 h ... each of output channel ntile * 32 + nn; zero beyond the channel counts.  One thread per piece
 // of all three planes.
-__global__ __launch_bounds__(256) void corr_split_weights_kernel(SplitArgs a, u32x4* __restrict__ dst) {
-  const CorrArgs& c = a.c;
-  const int ncc = (c.kc + 15) / 16, ntaps = a.gbegin[a.ngroups];
+__global__ __launch_bounds__(256) void corr_split_weights_kernel(const SplitArgs* tab, int first, const float* __restrict__ w,
+                                                                 u32x4* __restrict__ dst) {
+  const TablePtr a = args_at(tab, first + (int)blockIdx.y);
+  const auto& c = a->c;
+  const int ncc = (c.kc + 15) / 16, ntaps = a->gbegin[a->ngroups];
   const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
   if (idx >= c.ntn * c.nt[0] * ncc * ntaps * 64) return;
   const int hn = idx & 63;
@@ -342,17 +388,17 @@ __global__ __launch_bounds__(256) void corr_split_weights_kernel(SplitArgs a, u3
   const int cc = r % ncc; r /= ncc;
   const int t0 = r % c.nt[0], ntile = r / c.nt[0];
   const int ch = ntile * 32 + (hn & 31);
-  const int ft = (c.tapid[0][t0] * a.k1 + c.tapid[1][a.tap12[tap][0]]) * a.k2 + c.tapid[2][a.tap12[tap][1]];
+  const int ft = (c.tapid[0][t0] * a->k1 + c.tapid[1][a->tap12[tap][0]]) * a->k2 + c.tapid[2][a->tap12[tap][1]];
   float v[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int k = cc * 16 + (hn >> 5) * 8 + e;
     const int o = c.mode == 0 ? ch : k, i = c.mode == 0 ? k : ch;
-    v[e] = k < c.kc && ch < c.nc ? a.w[((size_t)o * a.ci + i) * a.taps + ft] : 0.f;
+    v[e] = k < c.kc && ch < c.nc ? w[((size_t)o * a->ci + i) * a->taps + ft] : 0.f;
   }
   u32x4 hi, mid, lo;
   split_eight(v, hi, mid, lo);
-  u32x4* const at = dst + (size_t)(idx >> 6) * 192 + hn;
+  u32x4* const at = dst + a->woff + (size_t)(idx >> 6) * 192 + hn;
   at[0] = hi;
   at[64] = mid;
   at[128] = lo;
@@ -464,24 +510,32 @@ SplitArgs split_args(const distdl_plan* p, const CorrArgs& c, bool& ok) {
   return a;
 }
 
-size_t weight_floats(const SplitArgs& a) {
-  return (size_t)a.c.ntn * a.c.nt[0] * ((a.c.kc + 15) / 16) * a.gbegin[a.ngroups] * 192 * 4;
+int64_t weight_pieces(const SplitArgs& a) {
+  return (int64_t)a.c.ntn * a.c.nt[0] * ((a.c.kc + 15) / 16) * a.gbegin[a.ngroups] * 192;
 }
 
 int64_t tiles_of_worker(const PerWorker& g, const CorrArgs& c) {
   return (((int64_t)c.n_b * g.nq[0] + c.g0 - 1) / c.g0) * ((g.nq[1] + c.tr - 1) / c.tr) * ((g.nq[2] + c.tc - 1) / c.tc) * c.ntn;
 }
 
-// One launch of a layer, everything but the pointers; kept in the plan.
+// The launches of one direction (forward: one; data gradient: one per class), sorted by kernel variant; kept in the plan.
 struct Launch {
   SplitArgs a;
-  int mt = 0;
-  size_t floats = 0;  // of weights
+  int variant = 0;  // index into the switch of launch_variants
   unsigned blocks = 0;
+  int64_t pieces = 0;  // of weights
 };
 struct Launches {
-  std::vector<Launch> v;  // forward, then the classes of the data gradient
-  size_t scratch = 0;
+  std::vector<Launch> v;
+  int64_t pieces = 0;  // all of them
+};
+struct SplitPlan {
+  Launches dir[2];
+  bool ok[2] = {false, false};
+  SplitArgs* dev = nullptr;  // forward, then the classes
+  ~SplitPlan() {
+    if (dev) (void)hipFree(dev);
+  }
 };
 
 bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
@@ -489,9 +543,10 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
   l.a = split_args(p, c, ok);
   SplitArgs& a = l.a;
   if (!ok) return false;
-  l.mt = choose_window(p, a);
-  if (l.mt == 0) return false;
-  l.floats = weight_floats(a);
+  const int mt = choose_window(p, a);
+  if (mt == 0) return false;
+  l.variant = mt == 3 ? 3 : mt == 1 ? 0 : pieces_of(a) <= 3 ? 1 : 2;
+  l.pieces = weight_pieces(a);
   // Output planes per workgroup: a fixed set-up (its address tables, about 8 * 10^3 clocks) against the number of rounds
   // of 512 workgroups; at least four groups per worker where neighbouring planes share input planes (conv_mfma.hip).
   int64_t planes_max = 0, per_plane = 0;
@@ -501,7 +556,7 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
     per_plane = std::max<int64_t>(per_plane, (int64_t)((g.nq[1] + a.c.tr - 1) / a.c.tr) * ((g.nq[2] + a.c.tc - 1) / a.c.tc) * a.c.ntn);
   }
   per_plane *= p->n_workers;
-  const double stage = (double)a.c.nt[0] * ((a.c.kc + 15) / 16) * (a.gbegin[a.ngroups] * l.mt * 6 * 32.0 * 2 * 1.4 + a.ngroups * 1500.0);
+  const double stage = (double)a.c.nt[0] * ((a.c.kc + 15) / 16) * (a.gbegin[a.ngroups] * mt * 6 * 32.0 * 2 * 1.4 + a.ngroups * 1500.0);
   const int tstep0 = a.c.nt[0] > 1 ? a.c.tapoff[0][1] - a.c.tapoff[0][0] : 0;
   const bool shares = tstep0 != 0 && a.c.is[0] % tstep0 == 0 && (a.c.is[0] / tstep0) % a.c.nt[0] != 0;
   const int64_t g0_max = shares ? std::max<int64_t>(1, planes_max / 4) : std::max<int64_t>(1, planes_max);
@@ -521,89 +576,129 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
   return true;
 }
 
+// launches v[0 ... count) of one variant, which lie at tab[first] ... in the plan's table
 template <int MT, int PA, int PB>
-int launch_variant(distdl_plan* p, const SplitArgs& a, unsigned blocks, void** in_tab, void** out_tab, hipStream_t st) {
-  const int lds = split_lds_bytes(PA, a.c.ck);
+int launch_variant(distdl_plan* p, const SplitArgs* tab, int first, const Launch* v, int count, const u32x4* wt, const float* w,
+                   const float* bias, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
+  unsigned blocks = 0;
+  int lds = 0;
+  for (int i = 0; i < count; ++i) blocks = std::max(blocks, v[i].blocks), lds = std::max(lds, split_lds_bytes(PA, v[i].a.c.ck));
+  if (count > 1 && blocks <= 2048) {
+    if (blocks == 0) return DISTDL_OK;
+    if (lds > 64 * 1024)
+      if (int rc = allow_large_lds<corr_split_classes_kernel<MT, PA, PB>>()) return rc;
+    ProfScope prof(name, st);
+    hipLaunchKernelGGL((corr_split_classes_kernel<MT, PA, PB>), dim3(blocks, (unsigned)count), dim3(256), lds, st, p->d_workers,
+                       in_tab, out_tab, tab, first, wt, w, bias);
+    return DISTDL_OK;
+  }
   if (lds > 64 * 1024)
     if (int rc = allow_large_lds<corr_split_kernel<MT, PA, PB>>()) return rc;
-  hipLaunchKernelGGL((corr_split_kernel<MT, PA, PB>), dim3(blocks), dim3(256), lds, st, p->d_workers, in_tab, out_tab, a);
+  for (int i = 0; i < count; ++i) {
+    if (v[i].blocks == 0) continue;
+    ProfScope prof(name, st);
+    hipLaunchKernelGGL((corr_split_kernel<MT, PA, PB>), dim3(v[i].blocks), dim3(256), split_lds_bytes(PA, v[i].a.c.ck), st,
+                       p->d_workers, in_tab, out_tab, v[i].a, wt, w, bias);
+  }
   return DISTDL_OK;
 }
 
-int launch_corr_split(distdl_plan* p, const Launch& l, const float* w, float* wscratch, const float* bias, void** in_tab,
-                      void** out_tab, const char* name, hipStream_t st) {
-  if (l.blocks == 0) return DISTDL_OK;
-  SplitArgs a = l.a;
-  a.w = w;
-  a.wt = (const u32x4*)wscratch;
-  a.c.bias = bias;
-  const int64_t n = (int64_t)(l.floats / 12);  // threads: three pieces of four floats each
-  if (n > 0) {
+// One direction: the weights of all its launches in one go, then one launch per kernel variant.
+int run_split(distdl_plan* p, int dir, const float* w, const float* bias, void** in_tab, void** out_tab, const char* name,
+              hipStream_t st) {
+  SplitPlan& sp = *(SplitPlan*)p->corr_split_plan.get();
+  if (!sp.dev) {
+    std::vector<SplitArgs> all;
+    for (const Launches& d : sp.dir)
+      for (const Launch& l : d.v) all.push_back(l.a);
+    SplitArgs* dev = nullptr;
+    DISTDL_HIP_TRY(hipMalloc((void**)&dev, all.size() * sizeof(SplitArgs)));
+    if (hipError_t e = hipMemcpy(dev, all.data(), all.size() * sizeof(SplitArgs), hipMemcpyHostToDevice); e != hipSuccess) {
+      (void)hipFree(dev);
+      DISTDL_HIP_TRY(e);
+    }
+    sp.dev = dev;
+  }
+  const Launches& d = sp.dir[dir];
+  const int first = dir == 0 ? 0 : (int)sp.dir[0].v.size();
+  if (int rc = ensure_wscratch(p, (size_t)std::max(sp.dir[0].pieces, sp.dir[1].pieces) * 4)) return rc;
+  u32x4* const wt = (u32x4*)p->d_wt;
+  int64_t most = 0;
+  for (const Launch& l : d.v) most = std::max(most, l.pieces / 3);  // threads: three pieces each
+  if (most > 0) {
     ProfScope prof("conv_relayout_w", st);
-    hipLaunchKernelGGL(corr_split_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a, (u32x4*)wscratch);
+    hipLaunchKernelGGL(corr_split_weights_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)d.v.size()), dim3(256), 0, st,
+                       sp.dev, first, w, wt);
   }
   constexpr int kPb = (kGroupTaps * 192 + 255) / 256, kPb3 = (9 * 192 + 255) / 256;
-  ProfScope prof(name, st);
-  if (l.mt == 3) return launch_variant<3, 4, kPb3>(p, a, l.blocks, in_tab, out_tab, st);
-  if (l.mt == 2 && pieces_of(a) <= 3) return launch_variant<2, 3, kPb>(p, a, l.blocks, in_tab, out_tab, st);
-  if (l.mt == 2) return launch_variant<2, 4, kPb>(p, a, l.blocks, in_tab, out_tab, st);
-  return launch_variant<1, 4, kPb>(p, a, l.blocks, in_tab, out_tab, st);
+  for (size_t i = 0; i < d.v.size();) {
+    size_t e = i;
+    while (e < d.v.size() && d.v[e].variant == d.v[i].variant) ++e;
+    const Launch* const v = &d.v[i];
+    const int at = first + (int)i, n = (int)(e - i);
+    int rc;
+    switch (v->variant) {
+      case 0: rc = launch_variant<1, 4, kPb>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st); break;
+      case 1: rc = launch_variant<2, 3, kPb>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st); break;
+      case 2: rc = launch_variant<2, 4, kPb>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st); break;
+      default: rc = launch_variant<3, 4, kPb3>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st);
+    }
+    if (rc) return rc;
+    i = e;
+  }
+  return DISTDL_OK;
 }
 
-template <class F>
-bool for_classes(const distdl_plan* p, F&& f) {
-  for (int p0 = 0; p0 < p->stride[0]; ++p0)
-    for (int p1 = 0; p1 < p->stride[1]; ++p1)
-      for (int p2 = 0; p2 < p->stride[2]; ++p2) {
-        const int par[3] = {p0, p1, p2};
-        if (!f(class_args(p, par))) return false;
-      }
-  return true;
+SplitPlan* split_plan(const distdl_plan* p) {
+  if (p->corr_split_plan) return (SplitPlan*)p->corr_split_plan.get();
+  auto sp = std::make_shared<SplitPlan>();
+  p->corr_split_plan = sp;
+  if (p->explicit_halo || p->dtype != DISTDL_F32) return sp.get();
+  // buffer instructions address one worker's tensor with 31-bit byte offsets
+  const double most = (double)p->n_b * std::max(p->n_ci, p->n_co) * 4.0;
+  if (most * p->max_buf_cells >= 2147480000.0 || most * p->max_out_cells >= 2147480000.0) return sp.get();
+  for (int d = 0; d < 3; ++d)
+    if (p->ksize[d] > 8 || p->stride[d] > 4) return sp.get();
+  for (int dir = 0; dir < 2; ++dir) {
+    if ((dir == 0 ? p->n_ci : p->n_co) % 4) continue;  // the tensor that is read comes in 16-byte pieces
+    Launches& d = sp->dir[dir];
+    auto add = [&](const CorrArgs& c) {
+      d.v.emplace_back();
+      return plan_launch(p, c, d.v.back());
+    };
+    bool ok = true;
+    if (dir == 0) ok = add(forward_args(p));
+    else
+      for (int p0 = 0; p0 < p->stride[0]; ++p0)
+        for (int p1 = 0; p1 < p->stride[1]; ++p1)
+          for (int p2 = 0; p2 < p->stride[2]; ++p2) {
+            const int par[3] = {p0, p1, p2};
+            ok = ok && add(class_args(p, par));
+          }
+    if (!ok) {
+      d.v.clear();
+      continue;
+    }
+    std::stable_sort(d.v.begin(), d.v.end(), [](const Launch& x, const Launch& y) { return x.variant < y.variant; });
+    for (Launch& l : d.v) {
+      l.a.woff = d.pieces;
+      d.pieces += l.pieces;
+    }
+    sp->ok[dir] = true;
+  }
+  return sp.get();
 }
 
 }  // namespace
 
-bool corr_split_supported(const distdl_plan* p) {
-  if (p->corr_split_ok >= 0) return p->corr_split_ok != 0;
-  auto all = std::make_shared<Launches>();
-  auto add = [&](const CorrArgs& c) {
-    all->v.emplace_back();
-    return plan_launch(p, c, all->v.back());
-  };
-  auto decide = [&]() {
-    if (p->explicit_halo || p->dtype != DISTDL_F32) return false;
-    if (p->n_ci % 4 || p->n_co % 4) return false;  // 16-byte channel pieces
-    if ((double)p->n_b * p->max_buf_cells * std::max(p->n_ci, p->n_co) * 4.0 >= 2147480000.0) return false;
-    if ((double)p->n_b * p->max_out_cells * std::max(p->n_ci, p->n_co) * 4.0 >= 2147480000.0) return false;
-    for (int d = 0; d < 3; ++d)
-      if (p->ksize[d] > 8) return false;
-    if (p->stride[0] > 4 || p->stride[1] > 4 || p->stride[2] > 4) return false;
-    return add(forward_args(p)) && for_classes(p, add);
-  };
-  p->corr_split_ok = decide() ? 1 : 0;
-  if (p->corr_split_ok == 0) return false;
-  size_t bwd = 0;
-  for (size_t i = 1; i < all->v.size(); ++i) bwd += all->v[i].floats;
-  all->scratch = std::max(all->v[0].floats, bwd);
-  p->corr_split_launches = all;
-  return true;
-}
+bool corr_split_supported(const distdl_plan* p, bool backward) { return split_plan(p)->ok[backward ? 1 : 0]; }
 
 int conv_fwd_split(distdl_plan* p, const float* w, const float* bias, hipStream_t st) {
-  const Launches& all = *(const Launches*)p->corr_split_launches.get();
-  if (int rc = ensure_wscratch(p, all.scratch)) return rc;
-  return launch_corr_split(p, all.v[0], w, p->d_wt, bias, p->tab_x.dev, p->tab_y.dev, "conv_fwd_split", st);
+  return run_split(p, 0, w, bias, p->tab_x.dev, p->tab_y.dev, "conv_fwd_split", st);
 }
 
 int conv_bwd_data_split(distdl_plan* p, const float* w, hipStream_t st) {
-  const Launches& all = *(const Launches*)p->corr_split_launches.get();
-  if (int rc = ensure_wscratch(p, all.scratch)) return rc;
-  float* at = p->d_wt;
-  for (size_t i = 1; i < all.v.size(); ++i) {
-    if (int rc = launch_corr_split(p, all.v[i], w, at, nullptr, p->tab_dy.dev, p->tab_dx.dev, "conv_bwd_data_split", st)) return rc;
-    at += all.v[i].floats;
-  }
-  return DISTDL_OK;
+  return run_split(p, 1, w, nullptr, p->tab_dy.dev, p->tab_dx.dev, "conv_bwd_data_split", st);
 }
 
 }  // namespace distdl

@@ -868,6 +868,65 @@ def test_conv_gather_kernels(cfg, dtype, misaligned):
     assert_close(db.float().cpu().numpy(), db_want, tol, "db")
 
 
+# The patch kernels on split planes: one, two and three tiles of pixels per wave; more than ten taps of one residue (several
+# groups); classes of a stride together and apart; output channels that are no multiple of 4 or of 32; dilation; one
+# direction only (the other has a channel count that is no multiple of 4)
+CONV_SPLIT = [
+    dict(D=1, n_b=2, c_in=20, c_out=36, in_shape=(70,), P=(2,), ksize=(3,), stride=(1,), padding=(1,), dilation=(1,)),
+    dict(D=2, n_b=1, c_in=8, c_out=35, in_shape=(50, 61), P=(2, 2), ksize=(7, 7), stride=(1, 1), padding=(3, 3), dilation=(1, 1)),
+    dict(D=2, n_b=2, c_in=33, c_out=64, in_shape=(41, 38), P=(1, 2), ksize=(5, 3), stride=(2, 3), padding=(2, 1), dilation=(1, 1)),
+    dict(D=3, n_b=1, c_in=8, c_out=64, in_shape=(9, 10, 13), P=(1, 2, 2), ksize=(3, 3, 3), stride=(2, 2, 2), padding=(1, 1, 1), dilation=(1, 1, 1)),
+    dict(D=2, n_b=2, c_in=60, c_out=20, in_shape=(40, 37), P=(2, 1), ksize=(3, 3), stride=(1, 1), padding=(2, 2), dilation=(2, 2)),
+    dict(D=2, n_b=1, c_in=36, c_out=40, in_shape=(30, 33), P=(1, 1), ksize=(8, 1), stride=(4, 1), padding=(0, 0), dilation=(1, 1)),
+    dict(D=2, n_b=2, c_in=20, c_out=68, in_shape=(300, 260), P=(1, 1), ksize=(3, 3), stride=(2, 2), padding=(1, 1), dilation=(1, 1)),
+]
+
+
+@pytest.mark.parametrize("cfg", CONV_SPLIT, ids=lambda c: f"c{c['c_in']}-{c['c_out']}k{'x'.join(map(str, c['ksize']))}s{c['stride'][-1]}d{c['dilation'][-1]}")
+def test_conv_split_kernels(cfg):
+    """fp32 values within a few roundings of a sum of fp32 products: 2^-24 a term at most, far less in the mean."""
+    require_gpu()
+    cfg = dict(cfg, seed=78)
+    part = oracle_partition(cfg)
+    case = syn.conv_case(cfg, part.global_out_shape())
+    x_bufs, y, dx_bufs, dw, db = _run_conv(cfg, part, case, True, torch.float32)
+    o_bufs = prim.scatter_bulk(case["x"].astype(np.float64), part, fill=np.nan)
+    y_want = layers.dist_conv_forward(o_bufs, case["w"], case["bias"], part, cfg["stride"], cfg["dilation"])
+    dx_want, dw_want, db_want = layers.dist_conv_adjoint(o_bufs, case["w"], prim.scatter_out(case["dy"], part), part,
+                                                         cfg["stride"], cfg["dilation"], True)
+    for wk in range(part.n_workers):
+        assert_close(from_cl(y[wk]), y_want[wk], TOL32, f"y worker {wk}")
+        assert_close(from_cl(dx_bufs[wk]), dx_want[wk], TOL32, f"dx worker {wk}")
+    assert_close(dw.float().cpu().numpy(), dw_want, TOL32, "dw")
+    assert_close(db.float().cpu().numpy(), db_want, TOL32, "db")
+
+
+def test_conv_weight_scratch_outlives_a_graph():
+    """A forward pass recorded before the first backward pass (whose weights need more room) replays as it was."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(3)
+    plan = dd.distdl_plan_create(2, 1, 8, 33, (20, 20), (1, 1), (3, 3), (2, 2), (1, 1), (1, 1))
+    part = oracle_partition(dict(D=2, in_shape=(20, 20), P=(1, 1), ksize=(3, 3), stride=(2, 2), padding=(1, 1), dilation=(1, 1)))
+    n_buf, n_out = part.buf_shape(0), part.out_shape(0)
+    x, w = torch.randn(1, *n_buf, 8, generator=g, device="cuda"), torch.randn(33, 8, 3, 3, generator=g, device="cuda")
+    y, dy = torch.empty(1, *n_out, 33, device="cuda"), torch.randn(1, *n_out, 33, generator=g, device="cuda")
+    dx, dw = torch.empty_like(x), torch.empty_like(w)
+    ws = torch.empty(max(dd.distdl_conv_bwd_workspace(plan), 16), dtype=torch.uint8, device="cuda")
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        dd.distdl_conv_fwd(plan, [x], w, None, [y])
+        side.synchronize()
+        want, graph = y.clone(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            dd.distdl_conv_fwd(plan, [x], w, None, [y])
+        for _ in range(3):
+            dd.distdl_conv_bwd(plan, [x], w, [dy], [dx], dw, None, ws)
+            y.zero_()
+            graph.replay()
+            side.synchronize()
+            assert torch.equal(y, want)
+
+
 # (channels in, out, kernel): gather kernels with 64 and 256 rows, and the patch kernels
 @pytest.mark.parametrize("c_in,c_out,k,n", [(5, 40, 7, 24), (18, 33, 3, 40), (3, 17, 3, 150), (32, 32, 3, 33), (16, 40, 5, 20)])
 def test_conv_infinities_and_nans_stay_what_fp32_makes_of_them(c_in, c_out, k, n):
