@@ -14,6 +14,7 @@
 #include "conv_core.h"
 #include "conv_mfma.h"
 #include "conv_split.h"
+#include "conv_wsplit.h"
 #include "profile.h"
 
 namespace distdl {
@@ -229,6 +230,47 @@ static int check_conv_plan(const distdl_plan* p) {
   return DISTDL_OK;
 }
 
+// The kernel of the weight gradient: of those that take the layer, the one whose estimated time (us) is the lowest.  The
+// estimates follow 80 measured layers of 1 to 64 channels, one to three dimensions, 10^2 to 10^7 positions:
+//   16 x 16 tiles: a set-up that grows with the taps of a plane, then 7 ps per tap and position (12 with several planes);
+//   gather: workgroups of 32-position stages, 2.4 us a stage while all compute units are busy, twice that with two
+//     column tiles (bf16: about half of that);
+//   bf16 planes: 1.2 us a step of 32 positions or its matrix instructions;
+//   split planes: its own estimate counts matrix instructions; 1.6 times that was taken.
+// 16 -> 16 channels, 3 x 3, 8 x 256 x 256: 38.7 / 83 / 47 us; 4 -> 8, 5^3, 7 x 31 x 23 x 28: 212 / 46 / 83; 32 -> 32, 5^3,
+// stride 2, 256^3: - / 5030 / 3110; 16 -> 4 channels, one dimension, 3 x 42626: - / 25 / 517.
+enum class Wgrad { k16, kSplit, kAny, kMfma, kDirect };
+
+static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {
+  if (p->wgrad_kernel[vec16] >= 0) return (Wgrad)p->wgrad_kernel[vec16];
+  const bool bf16 = p->dtype == DISTDL_BF16;
+  const double T = (double)p->ksize[1] * p->ksize[2], pos = (double)p->n_workers * p->n_b * p->max_out_cells;
+  Wgrad best = Wgrad::kDirect;
+  double least = 1e300;
+  auto consider = [&](Wgrad w, double us) {
+    if (us < least) least = us, best = w;
+  };
+  if (wgrad16_supported(p, vec16))
+    consider(Wgrad::k16, 6.0 + 0.8 * T + pos * p->ksize[0] * T * (p->ksize[0] > 1 ? 12e-6 : 7e-6));
+  if (vec16 && wgrad_split_supported(p)) consider(Wgrad::kSplit, 1.6 * wgrad_split_us(p));
+  if (conv_any_supported(p)) consider(Wgrad::kAny, wgrad_any_us(p));
+  const bool fits = wgrad_mfma_supported(p) && p->n_workers * wgrad_chunks(p) <= 65535;
+  if (fits && bf16 && vec16) consider(Wgrad::kMfma, wgrad_taps_us(p));
+  if (best == Wgrad::kDirect && fits && (!bf16 || vec16)) best = Wgrad::kMfma;
+  p->wgrad_kernel[vec16] = (int)best;
+  return best;
+}
+
+static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per worker
+  switch (w) {
+    case Wgrad::k16: return wgrad16_chunks(p, vec16);
+    case Wgrad::kSplit: return wgrad_split_chunks(p);
+    case Wgrad::kAny: return wgrad_any_chunks(p);
+    case Wgrad::kMfma: return wgrad_chunks(p);
+    default: return direct_chunks(p);
+  }
+}
+
 static int prepare_weights(distdl_plan* p, const void* w, hipStream_t st) {
   ConvDev c = conv_params(p);
   size_t n = (size_t)c.taps * c.ci * c.co;
@@ -253,10 +295,8 @@ size_t distdl_conv_bwd_workspace(const distdl_plan* plan) {
   if (!plan || plan->explicit_halo) return 0;
   ConvDev c = conv_params(plan);
   size_t nw = (size_t)c.taps * c.ci * c.co + c.co;
-  int chunks = direct_chunks(plan);
-  if (wgrad_mfma_supported(plan)) chunks = std::max(chunks, wgrad_chunks(plan));
-  if (conv_any_supported(plan)) chunks = std::max(chunks, wgrad_any_chunks(plan));
-  chunks = std::max(chunks, std::max(wgrad16_chunks(plan, true), wgrad16_chunks(plan, false)));
+  const bool vec = plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;  // (as for aligned and for any other tensors)
+  const int chunks = std::max(wgrad_partials(plan, choose_wgrad(plan, vec), vec), wgrad_partials(plan, choose_wgrad(plan, false), false));
   return nw * sizeof(float) * plan->n_workers * chunks;
 }
 
@@ -386,12 +426,7 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   const bool data_mfma = aligned && corr_mfma_supported(plan);
   bool vec16 = aligned && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
   for (int w = 0; w < plan->n_workers; ++w) vec16 &= (uintptr_t)x_bufs_dev[w] % 16 == 0;
-  const bool wgrad16 = wgrad16_supported(plan, vec16);
-  // 32-wide: the plane-per-workgroup kernel where its shape fits; else the gather kernel, which takes any shape of
-  // tensors under 2 GiB; the kernels that read their operands from memory for what is larger
-  const bool wgrad_fits = !wgrad16 && wgrad_mfma_supported(plan) && plan->n_workers * wgrad_chunks(plan) <= 65535;
-  const bool wgrad_any = !wgrad16 && !(wgrad_fits && vec16 && wgrad_taps_supported(plan)) && conv_any_supported(plan);
-  const bool wgrad_mfma = wgrad_fits && !wgrad_any && (!bf16 || vec16);
+  const Wgrad wgrad = choose_wgrad(plan, vec16);
   // [dConv]* with respect to x, into the whole padded buffers
   int64_t total = plan->n_b * plan->max_buf_cells * c.ci;
   if (corr16_bwd_supported(plan, aligned)) {
@@ -414,13 +449,15 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
                          plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
   }
   // [dConv]* with respect to w and b, then R over the workers
-  int nchunks = wgrad16 ? wgrad16_chunks(plan, vec16) : wgrad_any ? wgrad_any_chunks(plan) : wgrad_mfma ? wgrad_chunks(plan) : direct_chunks(plan);
+  const int nchunks = wgrad_partials(plan, wgrad, vec16);
   int nw = c.taps * c.ci * c.co + c.co;
-  if (wgrad16) {
+  if (wgrad == Wgrad::k16) {
     if ((rc = conv_wgrad16(plan, (float*)workspace_dev, vec16, st))) return rc;
-  } else if (wgrad_any) {
+  } else if (wgrad == Wgrad::kSplit) {
+    if ((rc = conv_wgrad_split(plan, (float*)workspace_dev, st))) return rc;
+  } else if (wgrad == Wgrad::kAny) {
     if ((rc = conv_wgrad_any(plan, (float*)workspace_dev, st))) return rc;
-  } else if (wgrad_mfma) {
+  } else if (wgrad == Wgrad::kMfma) {
     if ((rc = conv_wgrad_mfma(plan, (float*)workspace_dev, st))) return rc;
   } else {
     ProfScope prof("conv_bwd_weight_direct", st);

@@ -811,6 +811,15 @@ int wgrad_any_chunks(const distdl_plan* p) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((512 + tiles - 1) / tiles, std::max<int64_t>(std::min<int64_t>(stages, 64), stages / 4)), 512));
 }
 
+double wgrad_any_us(const distdl_plan* p) {
+  const int64_t rows = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci;
+  const int NT = nt_of(p->n_co);
+  const int64_t tiles = (rows + 255) / 256 * ((p->n_co + 32 * NT - 1) / (32 * NT)) * p->n_workers;
+  const int64_t chunks = wgrad_any_chunks(p), stages = (p->n_b * p->max_out_cells + 31) / 32;
+  const double stage = (tiles * chunks <= 256 ? 1.6 : 2.4) * NT * (p->dtype == DISTDL_BF16 ? 0.56 : 1.0);
+  return 4.5 + (double)((tiles * chunks + 511) / 512) * ((stages + chunks - 1) / chunks) * stage;
+}
+
 int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st) {
   WgradAnyArgs a{};
   a.n_b = (int32_t)p->n_b;

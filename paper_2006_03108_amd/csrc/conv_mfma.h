@@ -81,12 +81,12 @@ int ensure_wscratch(distdl_plan* p, size_t elems);
 
 bool corr_mfma_supported(const distdl_plan* p);
 bool wgrad_mfma_supported(const distdl_plan* p);
-bool wgrad_taps_supported(const distdl_plan* p);  // the plane-per-workgroup kernel's shapes
 size_t bwd_scratch_elems(const distdl_plan* p);
 int wgrad_chunks(const distdl_plan* p);
 // All three expect the plan's pointer tables (tab_x, tab_y, tab_dy, tab_dx) to be uploaded.
 int conv_fwd_mfma(distdl_plan* p, const void* w, const void* bias, hipStream_t st);
 int conv_bwd_data_mfma(distdl_plan* p, const void* w, hipStream_t st);
+double wgrad_taps_us(const distdl_plan* p);  // estimated time of a bf16 layer's
 int conv_wgrad_mfma(distdl_plan* p, float* partial, hipStream_t st);
 
 // Kernels for layers with at most 16 input and 16 output channels (16 x 16 MFMA tiles).  `vec`: channel counts

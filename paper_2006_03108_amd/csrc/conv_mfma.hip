@@ -12,9 +12,9 @@
 // wgrad_mfma_kernel: dw^[tap][ci][co] = sum_pos x^[cell(pos,tap)][ci] dy[pos][co]
 //   per worker; both MFMA operands are read straight from global memory in
 //   their register layout (channels-last makes 32 channels one 128-byte row).
-//   wgrad_lds_kernel stages the row segments in wave-private LDS; wgrad_taps_kernel
-//   (the fast path) gives a workgroup all taps of one kernel plane and shares the
-//   input rows between its waves through an LDS ring.
+//   wgrad_lds_kernel stages the row segments in wave-private LDS; wgrad_taps_kernel (bf16)
+//   gives a workgroup all taps of one kernel plane and shares the input rows between its
+//   waves through an LDS ring.
 //
 // v_mfma_f32_32x32x2_f32 operand layout: A lane l holds A[i = l%32][k = l/32],
 // B lane l holds B[k = l/32][j = l%32], D register v of lane l holds
@@ -803,25 +803,20 @@ __global__ __launch_bounds__(256, 2) void wgrad_lds_kernel(const WorkerDev* __re
 // vector instructions: ring slots advance in scalar registers, out-of-range rows are switched off through
 // the scalar offset of the buffer load, and every LDS read of the inner loop is an immediate offset.
 // A wave with TW - 1 taps repeats its last tap (never stored), so all waves stay in step.
-// SH = 1 (fp32 MFMAs, T = 4 * (TW - 1) + 1 taps, e.g. 3 x 3 and 5 x 5 kernels): every wave owns TW - 1 taps and the
-// last tap is shared, each wave multiplying a quarter of a step's 32 positions for it; the four partial tiles are
-// summed through LDS, in wave order, when the workgroup is done.  That is 16 * (TW - 1) + 4 MFMAs per wave and
-// step instead of 16 * TW.
-// MODE 0: fp32 tensors.  MODE 1: bf16 tensors widened to fp32 while they are staged.  MODE 2: bf16 tensors staged as
-// they are (a 16-byte piece holds 8 channels) and multiplied on v_mfma_f32_32x32x16_bf16, whose operands need 8
-// consecutive *positions* per lane: ds_read_b64_tr_b16 gathers them from the channels-last rows.  Measured lane
+// For bf16 tensors with channel counts that are multiples of 8 (fp32: conv_wsplit.hip; other bf16 layers: conv_any.hip): a
+// 16-byte piece holds 8 channels; v_mfma_f32_32x32x16_bf16 needs 8 consecutive *positions* per lane, which
+// ds_read_b64_tr_b16 gathers from the channels-last rows.  Measured lane
 // layout of that load: in every group of 16 lanes, lane 4 * b + a receives, as element v, the a-th 16-bit element
 // of the 8 bytes addressed by lane b + 4 * v of the group.  With lane s of a group addressing channels
 // 4 * (s % 4) ... + 3 of position s / 4, lane t of the group thus receives channel t of four consecutive positions.
-template <int TW, int S2, int MODE, int SH>
+template <int TW, int S2>
 __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __restrict__ workers, void* const* x_bufs,
                                                             void* const* dy_bufs, float* __restrict__ partial,
                                                             WgradArgs a) {
   extern __shared__ float4 wt_lds[];
   constexpr int NX = 5;  // input-row pieces per thread and step
-  constexpr bool BFM = MODE == 2;
-  constexpr uint32_t ES = MODE ? 2u : 4u;   // bytes per element in memory
-  constexpr int PCH = BFM ? 8 : 4;          // channels per 16-byte piece in LDS
+  constexpr uint32_t ES = 2u;               // bytes per element
+  constexpr int PCH = 8;                    // channels per 16-byte piece
   constexpr int PPC = 32 / PCH;             // pieces per cell of a 32-channel tile
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, m = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -853,16 +848,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __r
   char* const ldsb = (char*)wt_lds;
   const uint32_t ys_base = (uint32_t)ring * pitch;  // two dy segments of 4 KiB behind the ring
 
-  static_assert(SH == 0 || (SH == 1 && MODE != 2), "the shared tap is split by position pairs of fp32 MFMAs");
-  constexpr int NOWN = TW - SH;  // accumulators of taps this wave owns; the rest hold its part of the shared tap
   const int T = a.k[1] * a.k[2];
   const int tbase = T >> 2, trem = T & 3;
-  const int tap_first = SH ? wave * NOWN : wave * tbase + min(wave, trem);
-  const int ntw = SH ? NOWN : tbase + (wave < trem ? 1 : 0);
+  const int tap_first = wave * tbase + min(wave, trem);
+  const int ntw = tbase + (wave < trem ? 1 : 0);
   int tap_t1[TW], tap_t2[TW];
 #pragma unroll
   for (int i = 0; i < TW; ++i) {
-    const int j = i < NOWN ? tap_first + min(i, ntw - 1) : T - 1;
+    const int j = tap_first + min(i, ntw - 1);
     tap_t1[i] = j / a.k[2];
     tap_t2[i] = j - tap_t1[i] * a.k[2];
   }
@@ -915,9 +908,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __r
     for (int i = 0; i < NX; ++i) {
       // rows beyond the buffer (and unused slots) read as zero: the scalar offset fails the range check
       const uint32_t so = (prr[i] < s1 && r_first + prr[i] < wd.buf[1]) ? xb + (uint32_t)prr[i] * sx1 * ES : kOob;
-      rp[i] = load4<MODE == 1>(rx, pg[i], so);
+      rp[i] = load4<false>(rx, pg[i], so);
     }
-    rpy = load4<MODE == 1>(ry, pgy, ((uint32_t)n * syn + (uint32_t)o0 * sy0 + (uint32_t)o1 * sy1) * ES);
+    rpy = load4<false>(ry, pgy, ((uint32_t)n * syn + (uint32_t)o0 * sy0 + (uint32_t)o1 * sy1) * ES);
   };
   // db^ of this (worker, chunk): the workgroups of kernel plane 0 and input-channel tile 0 see every dy element
   // of their output-channel tile exactly once, on its way into LDS, and sum it there
@@ -938,26 +931,19 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __r
     }
     *(u32x4*)(ldsb + ys_base + (uint32_t)(o1 & 1) * 4096u + (uint32_t)tid * 16u) = rpy;
     if (bias_wg) {  // uniform: the dy piece this thread staged joins its part of db^ (pieces out of range are zero)
-      if constexpr (BFM) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          bsum[2 * j] += __uint_as_float(rpy[j] << 16);
-          bsum[2 * j + 1] += __uint_as_float(rpy[j] & 0xffff0000u);
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bsum[j] += __uint_as_float(rpy[j]);
+      for (int j = 0; j < 4; ++j) {
+        bsum[2 * j] += __uint_as_float(rpy[j] << 16);
+        bsum[2 * j + 1] += __uint_as_float(rpy[j] & 0xffff0000u);
       }
     }
   };
 
-  // fp32: lane (h, m) reads channel m of position 2 * pr + h.  bf16 MFMA: lane s of 16-lane group G addresses
-  // channels 16 * (G % 2) + 4 * (s % 4) ... + 3 of position 8 * (G / 2) + s / 4 (64 bytes per cell)
+  // lane s of 16-lane group G addresses channels 16 * (G % 2) + 4 * (s % 4) ... + 3 of position 8 * (G / 2) + s / 4
+  // (64 bytes per cell)
   const int lg = lane >> 4, ls = lane & 15;
-  const uint32_t lane_x = BFM ? (uint32_t)((8 * (lg >> 1) + (ls >> 2)) * S2 * 64 + (16 * (lg & 1) + 4 * (ls & 3)) * 2)
-                              : (uint32_t)(h * S2 * 32 + m) * 4u;
-  const uint32_t lane_y = ys_base + (BFM ? (uint32_t)((8 * (lg >> 1) + (ls >> 2)) * 64 + (16 * (lg & 1) + 4 * (ls & 3)) * 2)
-                                         : (uint32_t)(h * 32 + m) * 4u);
+  const uint32_t lane_x = (uint32_t)((8 * (lg >> 1) + (ls >> 2)) * S2 * 64 + (16 * (lg & 1) + 4 * (ls & 3)) * 2);
+  const uint32_t lane_y = ys_base + (uint32_t)((8 * (lg >> 1) + (ls >> 2)) * 64 + (16 * (lg & 1) + 4 * (ls & 3)) * 2);
   // unit order of this kernel plane: rotated by the output planes that the last kernel plane is ahead of it
   const int unit_begin = chunk * per, unit_cnt = unit_end - unit_begin;
   const int skew = unit_cnt > 0 ? (((a.k[0] - 1 - t0) * a.dil[0]) / a.s[0] * nblk1) % unit_cnt : 0;
@@ -984,7 +970,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __r
             uint32_t off = kOob;
             if (row_ok && cell < a.ncell && seg * 32 * S2 + cell < row_cells && ci_t * 32 + q4 < a.ci)
               off = (cell * sx2 + q4) * ES;
-            *(u32x4*)(ldsb + (uint32_t)(wrow % ring) * pitch + (uint32_t)rest * 16u) = load4<MODE == 1>(rx, off, rb);
+            *(u32x4*)(ldsb + (uint32_t)(wrow % ring) * pitch + (uint32_t)rest * 16u) = load4<false>(rx, off, rb);
           }
         }
       }
@@ -996,50 +982,27 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __r
         const char* ta[TW];
 #pragma unroll
         for (int i = 0; i < TW; ++i)
-          ta[i] = ldsb + (uint32_t)tslot[i] * pitch + (uint32_t)(tap_t2[i] * a.dil[2]) * (BFM ? 64u : 128u) + lane_x;
+          ta[i] = ldsb + (uint32_t)tslot[i] * pitch + (uint32_t)(tap_t2[i] * a.dil[2]) * 64u + lane_x;
         const char* yrow = ldsb + lane_y + (uint32_t)(o1 & 1) * 4096u;
-        if constexpr (BFM) {
-          // two groups of 16 positions; an operand is two transposing loads of four positions each
-          typedef short v4i16 __attribute__((ext_vector_type(4)));
-          typedef __attribute__((address_space(3))) v4i16* lds_v4;
-          union Frag {
-            v4i16 half[2];
-            bf16x8 v;
-          };
+        // two groups of 16 positions; an operand is two transposing loads of four positions each
+        typedef short v4i16 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) v4i16* lds_v4;
+        union Frag {
+          v4i16 half[2];
+          bf16x8 v;
+        };
 #pragma unroll
-          for (int kg = 0; kg < 2; ++kg) {
-            Frag fb, fa[TW];
-            fb.half[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(yrow + kg * 1024));
-            fb.half[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(yrow + kg * 1024 + 256));
+        for (int kg = 0; kg < 2; ++kg) {
+          Frag fb, fa[TW];
+          fb.half[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(yrow + kg * 1024));
+          fb.half[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(yrow + kg * 1024 + 256));
 #pragma unroll
-            for (int i = 0; i < TW; ++i) {
-              fa[i].half[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(ta[i] + kg * (16 * S2 * 64)));
-              fa[i].half[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(ta[i] + kg * (16 * S2 * 64) + 4 * S2 * 64));
-            }
-#pragma unroll
-            for (int i = 0; i < TW; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].v, fb.v, acc[i], 0, 0, 0);
+          for (int i = 0; i < TW; ++i) {
+            fa[i].half[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(ta[i] + kg * (16 * S2 * 64)));
+            fa[i].half[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(ta[i] + kg * (16 * S2 * 64) + 4 * S2 * 64));
           }
-        } else {
-        // 16 x two positions: lanes 0-31 take column 2*pr, lanes 32-63 column 2*pr + 1
 #pragma unroll
-        for (int pr = 0; pr < 16; ++pr) {
-          const float b = *(const float*)(yrow + pr * 256);
-          float av[NOWN];
-#pragma unroll
-          for (int i = 0; i < NOWN; ++i) av[i] = *(const float*)(ta[i] + pr * (2 * S2 * 128));
-#pragma unroll
-          for (int i = 0; i < NOWN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], b, acc[i], 0, 0, 0);
-        }
-        if constexpr (SH > 0) {  // position pairs 4 * wave ... + 3 of the shared tap
-          const char* tsh = ta[NOWN] + wave * (4 * 2 * S2 * 128);
-          const char* ysh = yrow + wave * (4 * 256);
-#pragma unroll
-          for (int pr = 0; pr < 4; ++pr) {
-            const float b = *(const float*)(ysh + pr * 256);
-            const float av = *(const float*)(tsh + pr * (2 * S2 * 128));
-            acc[NOWN] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b, acc[NOWN], 0, 0, 0);
-          }
-        }
+          for (int i = 0; i < TW; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].v, fb.v, acc[i], 0, 0, 0);
         }
         nslot += s1;
         if (nslot >= ring) nslot -= ring;
@@ -1055,32 +1018,13 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __r
   const bool co_ok = co < a.co;
   float* pbase = partial + (size_t)bz * a.slot;
 #pragma unroll
-  for (int i = 0; i < NOWN; ++i) {
+  for (int i = 0; i < TW; ++i) {
     if (i >= ntw) break;
     const int tap = (t0 * a.k[1] + tap_t1[i]) * a.k[2] + tap_t2[i];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int cir = ci_t * 32 + 8 * (v / 4) + 4 * h + (v % 4);
       if (cir < a.ci && co_ok) pbase[((size_t)tap * a.ci + cir) * a.co + co] = acc[i][v];
-    }
-  }
-  if constexpr (SH > 0) {
-    // the shared tap: each wave's partial tile goes to LDS as [wave][register][lane]; thread tid then sums, over
-    // the waves in order, the four elements register tid / 64 + 4 * k of lane tid % 64 and stores them
-    float* red = (float*)wt_lds;
-    __syncthreads();  // the ring is no longer read
-#pragma unroll
-    for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[NOWN][v];
-    __syncthreads();
-    const int tap = (t0 * a.k[1] + tap_t1[NOWN]) * a.k[2] + tap_t2[NOWN];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int v = wave + 4 * k;
-      float sum = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) sum += red[(w * 16 + v) * 64 + lane];
-      const int cir = ci_t * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-      if (cir < a.ci && co_ok) pbase[((size_t)tap * a.ci + cir) * a.co + co] = sum;
     }
   }
   if (bias_wg) {
@@ -1528,8 +1472,8 @@ int conv_bwd_data_mfma(distdl_plan* p, const void* w, hipStream_t st) {
 
 static bool wgrad_rows_shape_ok(const distdl_plan* p);
 
-// bf16 tensors: only the plane-per-workgroup kernel widens its operands while it stages them (it also needs
-// 16-byte aligned arrays, which the caller checks).
+// bf16 tensors: the plane-per-workgroup kernel alone (it also needs 16-byte aligned arrays, which the caller checks);
+// fp32: the kernels that read their operands from memory, for tensors that are too large for the others.
 bool wgrad_mfma_supported(const distdl_plan* p) {
   if (p->explicit_halo || p->ksize[2] > kMaxK2) return false;
   return p->dtype == DISTDL_F32 || wgrad_rows_shape_ok(p);
@@ -1541,21 +1485,15 @@ static int wgrad_taps_per_wave(const distdl_plan* p) {
   return T >= 4 ? (T + 3) / 4 : 0;
 }
 
-// The plane-per-workgroup kernel needs 16-byte channel pieces, a row stride of 1 or 2, a tap count
+// The plane-per-workgroup kernel needs bf16 tensors, channels in pieces of 8, a row stride of 1 or 2, a tap count
 // per wave it is instantiated for, s1 new rows per step that fit the five piece slots of a thread,
 // and a ring that fits in LDS.
-// 0: fp32 tensors; 1: bf16 tensors widened to fp32; 2: bf16 MFMAs (channel counts that are multiples of 8)
-static int wgrad_mode(const distdl_plan* p) {
-  if (p->dtype != DISTDL_BF16) return 0;
-  return (p->n_ci % 8 == 0 && p->n_co % 8 == 0) ? 2 : 1;
-}
-
 static bool wgrad_rows_shape_ok(const distdl_plan* p) {
   const int span = (p->ksize[1] - 1) * p->dilation[1] + 1;
   const int ncell = 31 * p->stride[2] + (p->ksize[2] - 1) * p->dilation[2] + 1;
-  const int rowp = (ncell * (wgrad_mode(p) == 2 ? 4 : 8) + 63) & ~63;
+  const int rowp = (ncell * 4 + 63) & ~63;
   const int tw = wgrad_taps_per_wave(p);
-  if (p->n_ci % 4 || p->n_co % 4) return false;
+  if (p->dtype != DISTDL_BF16 || p->n_ci % 8 || p->n_co % 8) return false;
   if (tw != 3 && tw != 4 && tw != 7) return false;
   if (p->stride[2] > 2 || p->stride[1] > span) return false;
   if (p->stride[1] * rowp > 5 * 256) return false;
@@ -1563,8 +1501,6 @@ static bool wgrad_rows_shape_ok(const distdl_plan* p) {
   if ((double)p->n_b * p->max_buf_cells * std::max(p->n_ci, p->n_co) * 4.0 >= 2147480000.0) return false;
   return true;
 }
-
-bool wgrad_taps_supported(const distdl_plan* p) { return !p->explicit_halo && wgrad_rows_shape_ok(p); }
 
 // Output rows per work unit of the plane-per-workgroup kernel: whole planes when there are enough of them to
 // fill the chip, else blocks of rows (each block re-reads span - s1 rows to prime its ring).
@@ -1608,6 +1544,14 @@ int wgrad_chunks(const distdl_plan* p) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, 32), rows));
 }
 
+double wgrad_taps_us(const distdl_plan* p) {
+  const int tw = wgrad_taps_per_wave(p);
+  double steps = 0;
+  for (const WorkerDev& wd : p->workers) steps += (double)p->n_b * wd.out[0] * wd.out[1] * ((wd.out[2] + 31) / 32);
+  steps *= (double)p->ksize[0] * ((p->n_ci + 31) / 32) * ((p->n_co + 31) / 32);
+  return 8.0 + steps / 512 * std::max(1.2, tw * 0.2);
+}
+
 int conv_wgrad_mfma(distdl_plan* p, float* partial, hipStream_t st) {
   WgradArgs a{};
   a.n_b = (int32_t)p->n_b;
@@ -1633,29 +1577,17 @@ int conv_wgrad_mfma(distdl_plan* p, float* partial, hipStream_t st) {
   const bool bf16 = p->dtype == DISTDL_BF16;
   const bool taps_path = aligned && wgrad_rows_shape_ok(p);
   if (taps_path) {
-    const int mode = wgrad_mode(p);
-    const int rowp = (a.ncell * (mode == 2 ? 4 : 8) + 63) & ~63;
+    const int rowp = (a.ncell * 4 + 63) & ~63;
     const int rlds = (a.span + a.s[1]) * rowp * 16 + 8192;
     const int tw = wgrad_taps_per_wave(p);
     dim3 rgrid((unsigned)a.k[0], grid.y, grid.z), rblock(256);
     ProfScope prof("conv_bwd_weight_mfma", st);
-    // one tap left over after dealing the plane's taps to the four waves: it is shared (fp32 MFMAs only)
-    const int T = a.k[1] * a.k[2];
-    const bool share = mode != 2 && T % 4 == 1 && T / 4 + 1 == tw && rlds >= 4 * 16 * 64 * 4;
-#define DISTDL_LAUNCH_TAPS_T(TW_, S2_, BF_, SH_)                                                                    \
-  do {                                                                                                              \
-    if (rlds > 64 * 1024)                                                                                           \
-      if (int rc_ = allow_large_lds<wgrad_taps_kernel<TW_, S2_, BF_, SH_>>()) return rc_;                           \
-    hipLaunchKernelGGL((wgrad_taps_kernel<TW_, S2_, BF_, SH_>), rgrid, rblock, rlds, st, p->d_workers,              \
-                       p->tab_x.dev, p->tab_dy.dev, partial, a);                                                    \
-  } while (0)
 #define DISTDL_LAUNCH_TAPS(TW_, S2_)                                                                                \
   do {                                                                                                              \
-    if (mode == 2) DISTDL_LAUNCH_TAPS_T(TW_, S2_, 2, 0);                                                            \
-    else if (mode == 1 && share) DISTDL_LAUNCH_TAPS_T(TW_, S2_, 1, 1);                                              \
-    else if (mode == 1) DISTDL_LAUNCH_TAPS_T(TW_, S2_, 1, 0);                                                       \
-    else if (share) DISTDL_LAUNCH_TAPS_T(TW_, S2_, 0, 1);                                                           \
-    else DISTDL_LAUNCH_TAPS_T(TW_, S2_, 0, 0);                                                                      \
+    if (rlds > 64 * 1024)                                                                                           \
+      if (int rc_ = allow_large_lds<wgrad_taps_kernel<TW_, S2_>>()) return rc_;                                     \
+    hipLaunchKernelGGL((wgrad_taps_kernel<TW_, S2_>), rgrid, rblock, rlds, st, p->d_workers, p->tab_x.dev,          \
+                       p->tab_dy.dev, partial, a);                                                                  \
   } while (0)
     if (tw == 3 && a.s[2] == 1) DISTDL_LAUNCH_TAPS(3, 1);
     else if (tw == 3) DISTDL_LAUNCH_TAPS(3, 2);
@@ -1664,7 +1596,6 @@ int conv_wgrad_mfma(distdl_plan* p, float* partial, hipStream_t st) {
     else if (a.s[2] == 1) DISTDL_LAUNCH_TAPS(7, 1);
     else DISTDL_LAUNCH_TAPS(7, 2);
 #undef DISTDL_LAUNCH_TAPS
-#undef DISTDL_LAUNCH_TAPS_T
   } else {
     if (bf16) return set_error(DISTDL_ERR_UNSUPPORTED, "conv: bf16 weight gradient needs 16-byte aligned arrays");
     ProfScope prof("conv_bwd_weight_mfma", st);

@@ -17,6 +17,7 @@
 // Bound: MFMAs (at the clock that the power limit leaves them with real data, about 2/3 of the peak) and LDS: with
 // MT = 2 a tap reads 9 KB per 12 MFMAs and wave, 3/4 of what LDS can deliver in that time.
 #include <algorithm>
+#include <mutex>
 #include <memory>
 
 #include "common.h"
@@ -650,6 +651,8 @@ int run_split(distdl_plan* p, int dir, const float* w, const float* bias, void**
 }
 
 SplitPlan* split_plan(const distdl_plan* p) {
+  static std::mutex lock;
+  std::lock_guard<std::mutex> hold(lock);
   if (p->corr_split_plan) return (SplitPlan*)p->corr_split_plan.get();
   auto sp = std::make_shared<SplitPlan>();
   p->corr_split_plan = sp;

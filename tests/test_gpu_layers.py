@@ -901,6 +901,41 @@ def test_conv_split_kernels(cfg):
     assert_close(db.float().cpu().numpy(), db_want, TOL32, "db")
 
 
+# The weight gradient on split planes: four and eight waves, one to seven row tiles a wave, one to four column tiles, channels
+# in one and in several chunks, steps of one, two and four output rows, strides and dilations, ragged last rows
+CONV_WSPLIT = [
+    dict(D=2, n_b=14, c_in=12, c_out=4, in_shape=(36, 44), P=(2, 3), ksize=(5, 5), stride=(1, 1), padding=(2, 2), dilation=(1, 1)),
+    dict(D=2, n_b=4, c_in=44, c_out=48, in_shape=(59, 80), P=(4, 2), ksize=(5, 5), stride=(1, 1), padding=(0, 0), dilation=(1, 1)),
+    dict(D=3, n_b=8, c_in=20, c_out=64, in_shape=(10, 43, 40), P=(1, 2, 1), ksize=(2, 3, 5), stride=(1, 1, 1), padding=(1, 1, 1), dilation=(1, 1, 1)),
+    dict(D=2, n_b=60, c_in=32, c_out=32, in_shape=(99, 98), P=(2, 1), ksize=(5, 5), stride=(2, 2), padding=(2, 2), dilation=(1, 1)),
+    dict(D=2, n_b=16, c_in=20, c_out=36, in_shape=(61, 33), P=(1, 2), ksize=(3, 3), stride=(1, 1), padding=(2, 2), dilation=(2, 2)),
+    dict(D=2, n_b=64, c_in=28, c_out=36, in_shape=(51, 16), P=(1, 2), ksize=(4, 4), stride=(1, 1), padding=(1, 1), dilation=(1, 1)),
+    dict(D=2, n_b=8, c_in=4, c_out=4, in_shape=(201, 200), P=(2, 2), ksize=(7, 7), stride=(1, 1), padding=(3, 3), dilation=(1, 1)),
+]
+
+
+@pytest.mark.parametrize("cfg", CONV_WSPLIT, ids=lambda c: f"c{c['c_in']}-{c['c_out']}k{'x'.join(map(str, c['ksize']))}s{c['stride'][-1]}d{c['dilation'][-1]}")
+@pytest.mark.parametrize("bias", [True, False], ids=["bias", "nobias"])
+def test_conv_weight_gradient_on_split_planes(cfg, bias):
+    require_gpu()
+    cfg = dict(cfg, seed=79)
+    part = oracle_partition(cfg)
+    case = syn.conv_case(cfg, part.global_out_shape())
+    dd.distdl_profile_enable(True)
+    dd.distdl_profile_report()
+    _, _, _, dw, db = _run_conv(cfg, part, case, bias)
+    names = set(dd.distdl_profile_report())
+    dd.distdl_profile_enable(False)
+    assert "conv_bwd_weight_split" in names
+    o_bufs = prim.scatter_bulk(case["x"].astype(np.float64), part, fill=np.nan)
+    layers.dist_conv_forward(o_bufs, case["w"], case["bias"], part, cfg["stride"], cfg["dilation"])  # (the exchange)
+    _, dw_want, db_want = layers.dist_conv_adjoint(o_bufs, case["w"], prim.scatter_out(case["dy"], part), part,
+                                                   cfg["stride"], cfg["dilation"], bias)
+    assert_close(dw.cpu().numpy(), dw_want, TOL32, "dw")
+    if bias:
+        assert_close(db.cpu().numpy(), db_want, TOL32, "db")
+
+
 def test_conv_weight_scratch_outlives_a_graph():
     """A forward pass recorded before the first backward pass (whose weights need more room) replays as it was."""
     require_gpu()
@@ -927,8 +962,8 @@ def test_conv_weight_scratch_outlives_a_graph():
             assert torch.equal(y, want)
 
 
-# (channels in, out, kernel): gather kernels with 64 and 256 rows, and the patch kernels
-@pytest.mark.parametrize("c_in,c_out,k,n", [(5, 40, 7, 24), (18, 33, 3, 40), (3, 17, 3, 150), (32, 32, 3, 33), (16, 40, 5, 20)])
+# (channels in, out, kernel): gather kernels with 64 and 256 rows, the patch kernels, the weight gradient on split planes
+@pytest.mark.parametrize("c_in,c_out,k,n", [(5, 40, 7, 24), (18, 33, 3, 40), (3, 17, 3, 150), (32, 32, 3, 33), (16, 40, 5, 20), (32, 32, 7, 200)])
 def test_conv_infinities_and_nans_stay_what_fp32_makes_of_them(c_in, c_out, k, n):
     """As for the affine layer: a sum with an infinite, a NaN or a nearly infinite term is what fp32 products give."""
     require_gpu()
