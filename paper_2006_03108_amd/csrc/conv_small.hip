@@ -14,6 +14,9 @@
 // position of the unit, rows, planes and all, so a wave multiplies 16 consecutive padded positions at a time and
 // the 64 lanes of an operand read are 64 consecutive floats.  Zero dy entries cancel the padded positions.
 #include <algorithm>
+#include <array>
+#include <memory>
+#include <vector>
 
 #include "common.h"
 #include "conv_mfma.h"
@@ -336,7 +339,9 @@ struct Corr16Args {
   int32_t tapmin1, tapmin2;    // smallest tap offset along dimensions 1, 2
   int32_t wpw, g0, ntaps;      // workgroups per worker; steps per workgroup (large patches); taps per kernel plane
   int32_t tapo[64];            // patch byte offset of tap (t1, t2)
-  const float* wt;             // weights: [t0][tap][lane][KM]
+  const float* wt;             // weights: [t0][tap][lane][KM]; null: taken from w
+  const float* w;              // the layer's weights [co][ci][tap]
+  int32_t ci_n, taps, k1, k2;  // their input channels, taps, and the kernel's extents in dimensions 1, 2
   const float* bias;           // may be null
 };
 
@@ -360,6 +365,16 @@ __device__ inline float comp(const float4& v, int g) { return g == 0 ? v.x : g =
 
 constexpr int kPA16 = 14, kPB16 = 7;
 constexpr uint32_t kSkip = 0xffffffffu;
+
+// W[tap (t0, t1, t2)][k][n] of a launch: w[n][k][tap] (forward) or w[k][n][tap] (data gradient), zero beyond the channels
+__device__ inline float corr16_weight(const float* __restrict__ w, const CorrArgs& c, int t0, int tap, int k, int nch, int ci_n,
+                                      int taps, int k1, int k2) {
+  if (k >= c.kc || nch >= c.nc) return 0.f;
+  const int t1 = tap / c.nt[2], t2 = tap - t1 * c.nt[2];
+  const int ftap = (c.tapid[0][t0] * k1 + c.tapid[1][t1]) * k2 + c.tapid[2][t2];
+  const int co = c.mode == 0 ? nch : k, ci = c.mode == 0 ? k : nch;
+  return w[((size_t)co * ci_n + ci) * taps + ftap];
+}
 
 // NT: taps per kernel plane known at compile time (tap loop unrolled, offsets in scalar registers), or 0.
 template <int KM, int V, int NT, int PA>
@@ -406,7 +421,7 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
   const __amdgpu_buffer_rsrc_t rout = rsrc_of(out_bufs[worker], (uint32_t)c.n_b * son * 4u);
   const int nt0 = c.nt[0], ntaps = a.ntaps;
   const uint32_t wfloats = (uint32_t)ntaps * 64u * KM;  // weights of one kernel plane
-  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wt, (uint32_t)max(nt0, 1) * wfloats * 4u);
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wt, a.wt ? (uint32_t)max(nt0, 1) * wfloats * 4u : 0u);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kg = lane >> 4, ij = lane & 15;
   char* const ldsb = (char*)lds;
@@ -607,8 +622,17 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
     }
   };
 
+  // One kernel plane: its weights are staged once, so every workgroup fetches them in the layer's own order (a launch that
+  // rearranges them first took 4.5 us; 1 -> 1 channels, one dimension, forward and backward: 36.1 -> 27.6 us).
+  if (!a.wt)
+#pragma unroll 8
+    for (uint32_t i = tid; i < wfloats; i += 256) {
+      const uint32_t r = i / KM;
+      lds[wl / 4u + i] = corr16_weight(a.w, c, 0, (int)(r >> 6), (int)(KM * ((r & 63u) >> 4) + i % KM), (int)(r & 15u), a.ci_n,
+                                       a.taps, a.k1, a.k2);
+    }
   __syncthreads();  // the zero fill is complete
-  int staged_t0 = -1;  // kernel plane whose weights are in LDS (they stay valid from window to window)
+  int staged_t0 = a.wt ? -1 : 0;  // kernel plane whose weights are in LDS (they stay valid from window to window)
   do {
   {
     const int64_t window = f / nsteps;
@@ -645,8 +669,7 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
   } while (MULTI && f < f_end);
 }
 
-// weights in staging order: dst[t0][tap][lane = kg * 16 + j][gk] = W[tap(t0, t1, t2)][k = KM * kg + gk][n = j], with
-// W[tap][k][n] = w[n][k][tap] (forward) or w[k][n][tap] (data gradient), zero beyond the channel counts
+// weights in staging order: dst[t0][tap][lane = kg * 16 + j][gk] = W[tap(t0, t1, t2)][k = KM * kg + gk][n = j]
 __global__ __launch_bounds__(256) void corr16_weights_kernel(const float* __restrict__ w, float* __restrict__ dst,
                                                              CorrArgs c, int km, int ci_n, int taps, int k1, int k2) {
   const int ntaps = c.nt[1] * c.nt[2];
@@ -658,15 +681,7 @@ __global__ __launch_bounds__(256) void corr16_weights_kernel(const float* __rest
   const int lane = r & 63;
   r >>= 6;
   const int tap = r % ntaps, t0 = r / ntaps;
-  const int t1 = tap / c.nt[2], t2 = tap - t1 * c.nt[2];
-  const int k = km * (lane >> 4) + gk, nch = lane & 15;
-  float v = 0.f;
-  if (k < c.kc && nch < c.nc) {
-    const int ftap = (c.tapid[0][t0] * k1 + c.tapid[1][t1]) * k2 + c.tapid[2][t2];
-    const int co = c.mode == 0 ? nch : k, ci = c.mode == 0 ? k : nch;
-    v = w[((size_t)co * ci_n + ci) * taps + ftap];
-  }
-  dst[idx] = v;
+  dst[idx] = corr16_weight(w, c, t0, tap, km * (lane >> 4) + gk, lane & 15, ci_n, taps, k1, k2);
 }
 
 struct Corr16Shape {
@@ -776,10 +791,32 @@ size_t corr16_weight_elems(const CorrArgs& c) {
   return (size_t)std::max(c.nt[0], 1) * c.nt[1] * c.nt[2] * 64 * km + 64;
 }
 
-int launch_corr16(distdl_plan* p, const CorrArgs& c, bool vec, const float* w, float* wscratch, const float* bias,
+// The shapes of a plan's launches, found when first asked for: 0 the forward one, 1 ... the parity classes.  (The search
+// tries a thousand windows: tens of microseconds, which no call has to spend again.)
+struct Corr16Plan {
+  struct Entry {
+    int known = 0;  // 0: not asked yet, 1: covered, -1: not covered
+    Corr16Shape s;
+  };
+  std::vector<std::array<Entry, 2>> launches;  // [which][vec]
+};
+
+bool corr16_shape_of(const distdl_plan* p, int which, const CorrArgs& c, bool vec, Corr16Shape& s) {
+  if (!p->corr16_plan) {
+    auto made = std::make_shared<Corr16Plan>();
+    made->launches.resize(1 + (size_t)p->stride[0] * p->stride[1] * p->stride[2]);
+    p->corr16_plan = made;
+  }
+  Corr16Plan::Entry& e = ((Corr16Plan*)p->corr16_plan.get())->launches[which][vec];
+  if (e.known == 0) e.known = corr16_shape(p, c, vec, e.s) ? 1 : -1;
+  s = e.s;
+  return e.known == 1;
+}
+
+int launch_corr16(distdl_plan* p, int which, const CorrArgs& c, bool vec, const float* w, float* wscratch, const float* bias,
                   void** in_tab, void** out_tab, const char* name, hipStream_t st) {
   Corr16Shape s;
-  if (!corr16_shape(p, c, vec, s)) return set_error(DISTDL_ERR_UNSUPPORTED, "conv: shape not covered by the small-channel kernel");
+  if (!corr16_shape_of(p, which, c, vec, s)) return set_error(DISTDL_ERR_UNSUPPORTED, "conv: shape not covered by the small-channel kernel");
   if (s.steps == 0) return DISTDL_OK;
   Corr16Args a{};
   a.c = c;
@@ -791,11 +828,13 @@ int launch_corr16(distdl_plan* p, const CorrArgs& c, bool vec, const float* w, f
   for (int t1 = 0; t1 < c.nt[1]; ++t1)
     for (int t2 = 0; t2 < c.nt[2]; ++t2)
       a.tapo[t1 * c.nt[2] + t2] = ((c.tapoff[1][t1] - s.tapmin1) * s.Cw + (c.tapoff[2][t2] - s.tapmin2)) * s.km * 4;
-  a.wt = wscratch;
-  a.bias = bias;
   const int taps = p->ksize[0] * p->ksize[1] * p->ksize[2];
+  a.wt = c.nt[0] == 1 ? nullptr : wscratch;
+  a.w = w;
+  a.ci_n = (int32_t)p->n_ci, a.taps = taps, a.k1 = p->ksize[1], a.k2 = p->ksize[2];
+  a.bias = bias;
   const int wtotal = c.nt[0] * a.ntaps * 64 * s.km;
-  if (wtotal > 0) {
+  if (a.wt && wtotal > 0) {
     ProfScope prof("conv_relayout_w", st);
     hipLaunchKernelGGL(corr16_weights_kernel, dim3((unsigned)((wtotal + 255) / 256)), dim3(256), 0, st, w, wscratch, c,
                        s.km, (int)p->n_ci, taps, p->ksize[1], p->ksize[2]);
@@ -861,7 +900,7 @@ static bool corr16_plan_ok(const distdl_plan* p) {
 bool corr16_fwd_supported(const distdl_plan* p, bool vec) {
   if (!corr16_plan_ok(p)) return false;
   Corr16Shape s;
-  return corr16_shape(p, forward_args(p), vec && p->n_ci % 4 == 0, s);
+  return corr16_shape_of(p, 0, forward_args(p), vec && p->n_ci % 4 == 0, s);
 }
 
 bool corr16_bwd_supported(const distdl_plan* p, bool vec) {
@@ -873,7 +912,7 @@ bool corr16_bwd_supported(const distdl_plan* p, bool vec) {
         Corr16Shape s;
         const CorrArgs c = class_args(p, par);
         if (c.nt[0] * c.nt[1] * c.nt[2] == 0) continue;  // no tap reaches this class: the launch only writes zeros
-        if (!corr16_shape(p, c, vec && p->n_co % 4 == 0, s)) return false;
+        if (!corr16_shape_of(p, 1 + (p0 * p->stride[1] + p1) * p->stride[2] + p2, c, vec && p->n_co % 4 == 0, s)) return false;
       }
   return true;
 }
@@ -893,7 +932,7 @@ static size_t corr16_scratch_total(const distdl_plan* p) {
 int conv_fwd16(distdl_plan* p, const float* w, const float* bias, bool vec, hipStream_t st) {
   int rc = ensure_wscratch(p, corr16_scratch_total(p));
   if (rc) return rc;
-  return launch_corr16(p, forward_args(p), vec && p->n_ci % 4 == 0, w, p->d_wt, bias, p->tab_x.dev, p->tab_y.dev,
+  return launch_corr16(p, 0, forward_args(p), vec && p->n_ci % 4 == 0, w, p->d_wt, bias, p->tab_x.dev, p->tab_y.dev,
                        "conv_fwd_mfma16", st);
 }
 
@@ -906,7 +945,8 @@ int conv_bwd_data16(distdl_plan* p, const float* w, bool vec, hipStream_t st) {
       for (int p2 = 0; p2 < p->stride[2]; ++p2) {
         const int par[3] = {p0, p1, p2};
         const CorrArgs c = class_args(p, par);
-        if ((rc = launch_corr16(p, c, vec && p->n_co % 4 == 0, w, p->d_wt + at, nullptr, p->tab_dy.dev, p->tab_dx.dev,
+        if ((rc = launch_corr16(p, 1 + (p0 * p->stride[1] + p1) * p->stride[2] + p2, c, vec && p->n_co % 4 == 0, w, p->d_wt + at,
+                                nullptr, p->tab_dy.dev, p->tab_dx.dev,
                                 "conv_bwd_data_mfma16", st)))
           return rc;
         at += corr16_weight_elems(c);
