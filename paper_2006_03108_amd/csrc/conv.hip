@@ -429,7 +429,13 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   const Wgrad wgrad = choose_wgrad(plan, vec16);
   // [dConv]* with respect to x, into the whole padded buffers
   int64_t total = plan->n_b * plan->max_buf_cells * c.ci;
-  if (corr16_bwd_supported(plan, aligned)) {
+  // Few channels and several stride classes: the 16 x 16 kernel takes a launch (with planes of taps, two) for each, the others
+  // two in all, which is what counts up to 2^18 cells for four classes (us; 4 -> 16 channels, 3 x 3, stride 2, 12 x 28 x 29:
+  // 41 and 16; 2 -> 6, 2 x 772 x 887: 74 and 118).
+  const int64_t classes = (int64_t)plan->stride[0] * plan->stride[1] * plan->stride[2];
+  const bool together = classes >= 4 && plan->n_workers * plan->n_b * plan->max_buf_cells <= (classes << 16) &&
+                        ((aligned && corr_split_supported(plan, true)) || conv_any_supported(plan));
+  if (!together && corr16_bwd_supported(plan, aligned)) {
     if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
   } else if (aligned && corr_split_supported(plan, true)) {
     if ((rc = conv_bwd_data_split(plan, (const float*)w_dev, st))) return rc;

@@ -840,6 +840,8 @@ CONV_ANY = [
     dict(D=3, n_b=1, c_in=18, c_out=22, in_shape=(9, 10, 11), P=(1, 2, 2), ksize=(3, 1, 2), stride=(2, 2, 2), padding=(1, 0, 1), dilation=(2, 1, 2)),
     dict(D=2, n_b=2, c_in=32, c_out=36, in_shape=(20, 24), P=(2, 2), ksize=(9, 1), stride=(1, 2), padding=(4, 0), dilation=(1, 1)),
     dict(D=2, n_b=5, c_in=40, c_out=70, in_shape=(33, 30), P=(1, 1), ksize=(1, 1), stride=(1, 1), padding=(0, 0), dilation=(1, 1)),
+    dict(D=2, n_b=5, c_in=5, c_out=1, in_shape=(11, 10), P=(2, 1), ksize=(2, 2), stride=(2, 2), padding=(1, 1), dilation=(1, 1)),
+    dict(D=3, n_b=2, c_in=3, c_out=6, in_shape=(7, 9, 8), P=(1, 2, 1), ksize=(3, 3, 3), stride=(2, 2, 1), padding=(1, 1, 1), dilation=(1, 1, 1)),
     dict(D=2, n_b=40, c_in=19, c_out=24, in_shape=(40, 41), P=(2, 2), ksize=(3, 3), stride=(1, 1), padding=(1, 1), dilation=(1, 1)),
 ]
 
@@ -878,6 +880,8 @@ CONV_SPLIT = [
     dict(D=3, n_b=1, c_in=8, c_out=64, in_shape=(9, 10, 13), P=(1, 2, 2), ksize=(3, 3, 3), stride=(2, 2, 2), padding=(1, 1, 1), dilation=(1, 1, 1)),
     dict(D=2, n_b=2, c_in=60, c_out=20, in_shape=(40, 37), P=(2, 1), ksize=(3, 3), stride=(1, 1), padding=(2, 2), dilation=(2, 2)),
     dict(D=2, n_b=1, c_in=36, c_out=40, in_shape=(30, 33), P=(1, 1), ksize=(8, 1), stride=(4, 1), padding=(0, 0), dilation=(1, 1)),
+    dict(D=2, n_b=3, c_in=4, c_out=4, in_shape=(40, 34), P=(2, 2), ksize=(7, 7), stride=(2, 2), padding=(0, 0), dilation=(1, 1)),
+    dict(D=3, n_b=1, c_in=4, c_out=8, in_shape=(12, 11, 13), P=(2, 1, 2), ksize=(3, 1, 2), stride=(2, 2, 2), padding=(1, 0, 1), dilation=(1, 1, 1)),
     dict(D=2, n_b=2, c_in=20, c_out=68, in_shape=(300, 260), P=(1, 1), ksize=(3, 3), stride=(2, 2), padding=(1, 1), dilation=(1, 1)),
 ]
 
