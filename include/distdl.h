@@ -426,10 +426,11 @@ int distdl_profile_report(char* out, size_t cap);
  * get_task returns the number of ints written.
  * ---------------------------------------------------------------------- */
 int distdl_debug_task_count(const distdl_plan* plan, int adjoint);
-/* Kernel family the convolution calls would pick for this plan when every
- * array is 16-byte aligned: out[0] forward, out[1] data gradient, out[2]
- * weight gradient; 0 = direct kernels (any shape), 1 = 32-wide matrix-core
- * tiles, 2 = 16-wide matrix-core tiles (at most 16 channels). */
+/* Tiled kernel family whose shapes cover this plan when every array is
+ * 16-byte aligned: out[0] forward, out[1] data gradient, out[2] weight
+ * gradient; 0 = none (gather or direct kernels, any shape), 1 = 32-wide
+ * matrix-core tiles, 2 = 16-wide matrix-core tiles (at most 16 channels).
+ * The convolution calls may prefer a kernel of another family. */
 int distdl_debug_conv_path(const distdl_plan* plan, int32_t out[3]);
 /* Runs the replacement policy of the cached device tables (see Conventions)
  * on a sequence of n calls without touching a device: call i arrives on

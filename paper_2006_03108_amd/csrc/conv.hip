@@ -315,7 +315,8 @@ int distdl_conv_bwd(distdl_plan* plan, const void* const x_bufs_dev[], const voi
 int distdl_debug_conv_path(const distdl_plan* plan, int32_t out[3]) {
   if (!plan || !out) return set_error(DISTDL_ERR_NULL, "conv_path: null argument");
   if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_path: plan has no kernel");
-  // the choices of conv_fwd_core / conv_bwd_core for 16-byte aligned arrays
+  // by shape and 16-byte aligned arrays; the split and gather kernels, which conv_fwd_core and conv_bwd_core may prefer, are
+  // not told apart here
   const bool vec = plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
   const bool mfma = corr_mfma_supported(plan);
   out[0] = corr16_fwd_supported(plan, true) ? 2 : mfma ? 1 : 0;

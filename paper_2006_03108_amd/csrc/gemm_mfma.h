@@ -49,7 +49,7 @@ int launch_gemm_mfma(const GemmBlock* d_blocks, const std::vector<GemmBlock>& bl
 // B, N) is a multiple of a 16-byte piece (8 bf16, 4 fp32); with both operands as k lines (weight gradient, bf16 only):
 // one segment, M and N multiples of 8.
 bool gemm_stream_usable(const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc);
-int launch_gemm_stream(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool bf16, bool b_kc,
+int launch_gemm_stream(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool b_kc,
                        hipStream_t st);
 // the weight-gradient layout (both operands as k lines), 128 x 128 tiles
 // d_colsum (or null): column sums (the bias gradient) computed by extra workgroups of the same launch

@@ -13,10 +13,8 @@
 // 16-byte buffer loads (rows beyond the matrix fail the range check and read as zero) that run one or two
 // stages ahead in registers; LDS is double buffered: one barrier per stage.
 //
-// fp32: v_mfma_f32_32x32x2_f32, A lane l holds A[i = l%32][k = l/32]; a 16-byte LDS read gives a lane
-//       4 consecutive k, used by 4 MFMAs whose k-pairs are (j, 4+j) -- the same pairing on both operands.
-// bf16: v_mfma_f32_32x32x16_bf16, A lane l holds A[i = l%32][k = 8*(l/32) .. +7], one 16-byte read.
-// D register v of lane l is D[i = 8*(v/4) + 4*(l/32) + v%4][j = l%32] for both.
+// bf16 (fp32 products: gemm_split.hip): v_mfma_f32_32x32x16_bf16, A lane l holds A[i = l%32][k = 8*(l/32) .. +7], one 16-byte read.
+// D register v of lane l is D[i = 8*(v/4) + 4*(l/32) + v%4][j = l%32].
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -54,9 +52,9 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// BF16 = false: T is float, BK = 32 floats per stage.  BF16 = true: T is bf16 bits, BK = 64 per stage.
+// bf16 operands, BK = 64 per stage.
 // TM x TN: 32 x 32 MFMA tiles per wave; the workgroup tile is 64*TM x 64*TN (4 waves, 2 x 2).
-// Row pitch in LDS is BK + 16 bytes for the K-contiguous layout, tile extent + 16 (bf16: 32) bytes for the other.
+// Row pitch in LDS is BK + 16 bytes for the K-contiguous layout, tile extent + 32 bytes for the other.
 //
 // D: stages the global loads run ahead of the multiplication (a ring of D register sets).
 // SB: one LDS buffer and two barriers per stage instead of two buffers and one barrier.
@@ -66,17 +64,17 @@ __device__ __forceinline__ void static_for(F&& f) {
 // writes its fp32 partial tile to `partial` ([block][split][M][N]); gemm_reduce_kernel then sums the splits
 // in ascending order, adds the bias and rounds.  This is the sum-reduce R of the layer left un-fused: with a
 // small batch a launch has too few tiles to fill the chip, and the splits supply the missing workgroups.
-template <bool BF16, bool A_KC, bool B_KC, int TM, int TN, int D, bool SB>
+template <bool A_KC, bool B_KC, int TM, int TN, int D, bool SB>
 __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restrict__ blocks, float* __restrict__ partial,
                                                         int64_t partial_stride) {
-  constexpr int ES = BF16 ? 2 : 4;             // element size
-  constexpr int GK = BF16 ? 16 : 8;            // k per group: one bf16 MFMA, or four fp32 ones, per tile
+  constexpr int ES = 2;                        // element size
+  constexpr int GK = 16;                       // k per group: one MFMA per tile
   constexpr int KG = 4;                        // k groups per stage
   constexpr int BK = GK * KG;                  // k per stage
   constexpr int VE = 16 / ES;                  // elements per 16-byte piece
   constexpr int TILE_M = 64 * TM, TILE_N = 64 * TN;
   constexpr int PITCH_KC = BK * ES + 16;       // bytes per tile row, K-contiguous staging [row][k]
-  constexpr int TPAD = BF16 ? 32 : 16;         // bf16: four k lines read together fall 8 banks apart
+  constexpr int TPAD = 32;                     // four k lines read together fall 8 banks apart
   constexpr int PITCH_TA = TILE_M * ES + TPAD;  // bytes per k line, transposed staging [k][row]
   constexpr int PITCH_TB = TILE_N * ES + TPAD;
   constexpr int A_BYTES = A_KC ? TILE_M * PITCH_KC : BK * PITCH_TA;
@@ -218,104 +216,56 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
       // The LDS reads of k group g + 1 are issued before the MFMAs of group g; the scheduling barriers
       // pin that order (left alone, the compiler sinks the reads to their first use and the LDS latency
       // is paid once per group).
-      if constexpr (!BF16) {
-        auto rd = [&](int kk, float (&av)[TM][4], float (&bv)[TN][4]) {
+      // An operand staged [k][row] (rows contiguous) is read with ds_read_b64_tr_b16.  Measured lane layout of
+      // that load: in every group of 16 lanes, lane 4 * b + a receives, as element v, the a-th 16-bit element of
+      // the 8 bytes addressed by lane b + 4 * v of the group.  Lane s of group G addresses rows
+      // 16 * (G % 2) + 4 * (s % 4) ... + 3 of k line 8 * (G / 2) + s / 4, so lane t of the group receives row
+      // 16 * (G % 2) + t of four consecutive k: two loads make the operand of lane l = (row l % 32, k 8 * (l / 32) ...).
+      typedef short v4i16 __attribute__((ext_vector_type(4)));
+      typedef __attribute__((address_space(3))) v4i16* lds_v4;
+      union Frag { u32x4 u; bf16x8 v; v4i16 t[2]; };
+      const int tk = 8 * (lane >> 5) + ((lane & 15) >> 2), tr = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+      auto rd = [&](int kk, Frag (&av)[TM], Frag (&bv)[TN]) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const int row = 32 * (wy * TM + i) + ml;
-            if (A_KC) {
-              const float4 t = *(const float4*)(sa + row * PITCH_KC + (kk + 4 * h) * 4);
-              av[i][0] = t.x; av[i][1] = t.y; av[i][2] = t.z; av[i][3] = t.w;
-            } else {
-#pragma unroll
-              for (int j = 0; j < 4; ++j) av[i][j] = *(const float*)(sa + (kk + 4 * h + j) * PITCH_TA + row * 4);
-            }
+        for (int i = 0; i < TM; ++i) {
+          const int row = 32 * (wy * TM + i) + ml;
+          if (A_KC) {
+            av[i].u = *(const u32x4*)(sa + row * PITCH_KC + (kk + 8 * h) * 2);
+          } else {
+            av[i].t[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(sa + (kk + tk) * PITCH_TA + (row - ml + tr) * 2));
+            av[i].t[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(sa + (kk + tk + 4) * PITCH_TA + (row - ml + tr) * 2));
           }
+        }
 #pragma unroll
-          for (int i = 0; i < TN; ++i) {
-            const int row = 32 * (wx * TN + i) + ml;
-            if (B_KC) {
-              const float4 t = *(const float4*)(sb + row * PITCH_KC + (kk + 4 * h) * 4);
-              bv[i][0] = t.x; bv[i][1] = t.y; bv[i][2] = t.z; bv[i][3] = t.w;
-            } else {
-#pragma unroll
-              for (int j = 0; j < 4; ++j) bv[i][j] = *(const float*)(sb + (kk + 4 * h + j) * PITCH_TB + row * 4);
-            }
+        for (int i = 0; i < TN; ++i) {
+          const int row = 32 * (wx * TN + i) + ml;
+          if (B_KC) {
+            bv[i].u = *(const u32x4*)(sb + row * PITCH_KC + (kk + 8 * h) * 2);
+          } else {
+            bv[i].t[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(sb + (kk + tk) * PITCH_TB + (row - ml + tr) * 2));
+            bv[i].t[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(sb + (kk + tk + 4) * PITCH_TB + (row - ml + tr) * 2));
           }
-        };
-        auto mm = [&](const float (&av)[TM][4], const float (&bv)[TN][4]) {
+        }
+      };
+      auto mm = [&](const Frag (&av)[TM], const Frag (&bv)[TN]) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+        for (int im = 0; im < TM; ++im)
 #pragma unroll
-            for (int im = 0; im < TM; ++im)
-#pragma unroll
-              for (int in = 0; in < TN; ++in)
-                acc[im][in] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[im][j], bv[in][j], acc[im][in], 0, 0, 0);
-        };
-        float av[2][TM][4], bv[2][TN][4];
-        rd(0, av[0], bv[0]);
-        rd(GK, av[1], bv[1]);
-        static_for<KG>([&](auto g) __attribute__((always_inline)) {
-          constexpr int gv = decltype(g)::value;
+          for (int in = 0; in < TN; ++in)
+            acc[im][in] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[im].v, bv[in].v, acc[im][in], 0, 0, 0);
+      };
+      Frag av[2][TM], bv[2][TN];
+      rd(0, av[0], bv[0]);
+      rd(GK, av[1], bv[1]);
+      static_for<KG>([&](auto g) __attribute__((always_inline)) {
+        constexpr int gv = decltype(g)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        mm(av[gv & 1], bv[gv & 1]);
+        if constexpr (gv + 2 < KG) {
           __builtin_amdgcn_sched_barrier(0);
-          mm(av[gv & 1], bv[gv & 1]);
-          if constexpr (gv + 2 < KG) {
-            __builtin_amdgcn_sched_barrier(0);
-            rd((gv + 2) * GK, av[gv & 1], bv[gv & 1]);
-          }
-        });
-      } else {
-        // An operand staged [k][row] (rows contiguous) is read with ds_read_b64_tr_b16.  Measured lane layout of
-        // that load: in every group of 16 lanes, lane 4 * b + a receives, as element v, the a-th 16-bit element of
-        // the 8 bytes addressed by lane b + 4 * v of the group.  Lane s of group G addresses rows
-        // 16 * (G % 2) + 4 * (s % 4) ... + 3 of k line 8 * (G / 2) + s / 4, so lane t of the group receives row
-        // 16 * (G % 2) + t of four consecutive k: two loads make the operand of lane l = (row l % 32, k 8 * (l / 32) ...).
-        typedef short v4i16 __attribute__((ext_vector_type(4)));
-        typedef __attribute__((address_space(3))) v4i16* lds_v4;
-        union Frag { u32x4 u; bf16x8 v; v4i16 t[2]; };
-        const int tk = 8 * (lane >> 5) + ((lane & 15) >> 2), tr = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-        auto rd = [&](int kk, Frag (&av)[TM], Frag (&bv)[TN]) {
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const int row = 32 * (wy * TM + i) + ml;
-            if (A_KC) {
-              av[i].u = *(const u32x4*)(sa + row * PITCH_KC + (kk + 8 * h) * 2);
-            } else {
-              av[i].t[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(sa + (kk + tk) * PITCH_TA + (row - ml + tr) * 2));
-              av[i].t[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(sa + (kk + tk + 4) * PITCH_TA + (row - ml + tr) * 2));
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < TN; ++i) {
-            const int row = 32 * (wx * TN + i) + ml;
-            if (B_KC) {
-              bv[i].u = *(const u32x4*)(sb + row * PITCH_KC + (kk + 8 * h) * 2);
-            } else {
-              bv[i].t[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(sb + (kk + tk) * PITCH_TB + (row - ml + tr) * 2));
-              bv[i].t[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(sb + (kk + tk + 4) * PITCH_TB + (row - ml + tr) * 2));
-            }
-          }
-        };
-        auto mm = [&](const Frag (&av)[TM], const Frag (&bv)[TN]) {
-#pragma unroll
-          for (int im = 0; im < TM; ++im)
-#pragma unroll
-            for (int in = 0; in < TN; ++in)
-              acc[im][in] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[im].v, bv[in].v, acc[im][in], 0, 0, 0);
-        };
-        Frag av[2][TM], bv[2][TN];
-        rd(0, av[0], bv[0]);
-        rd(GK, av[1], bv[1]);
-        static_for<KG>([&](auto g) __attribute__((always_inline)) {
-          constexpr int gv = decltype(g)::value;
-          __builtin_amdgcn_sched_barrier(0);
-          mm(av[gv & 1], bv[gv & 1]);
-          if constexpr (gv + 2 < KG) {
-            __builtin_amdgcn_sched_barrier(0);
-            rd((gv + 2) * GK, av[gv & 1], bv[gv & 1]);
-          }
-        });
-      }
+          rd((gv + 2) * GK, av[gv & 1], bv[gv & 1]);
+        }
+      });
   };
 
   if (n > 0) {
@@ -353,39 +303,37 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
   //   C[m0 + 32*(wy*TM + im) + 8*(v/4) + 4*h + v%4][n0 + 32*(wx*TN + in) + ml]
   float* pc = nullptr;
   if (gridDim.y > 1) pc = partial + ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * partial_stride;
-  if constexpr (BF16) {
-    // bf16 results: lane = column in the MFMA layout, so storing from registers is one 2-byte store per element
-    // (64 per thread with 128-tiles: measured, that epilogue was 60 % of a weight-gradient workgroup's lifetime).
-    // Instead the tile is rounded into LDS (the stage buffers are done with) and written out in 16-byte pieces,
-    // 256 contiguous bytes per tile row.
-    if (!pc && gb.ldc % 8 == 0 && gb.N % 8 == 0 && ((uintptr_t)gb.c & 15) == 0) {  // uniform
-      constexpr int CP = TILE_N * 2 + 16;  // bytes per staged row
-      static_assert(TILE_M * CP <= (SB ? 1 : 2) * (A_BYTES + B_BYTES), "output tile must fit the stage buffers");
-      __syncthreads();
+  // bf16 results: lane = column in the MFMA layout, so storing from registers is one 2-byte store per element
+  // (64 per thread with 128-tiles: measured, that epilogue was 60 % of a weight-gradient workgroup's lifetime).
+  // Instead the tile is rounded into LDS (the stage buffers are done with) and written out in 16-byte pieces,
+  // 256 contiguous bytes per tile row.
+  if (!pc && gb.ldc % 8 == 0 && gb.N % 8 == 0 && ((uintptr_t)gb.c & 15) == 0) {  // uniform
+    constexpr int CP = TILE_N * 2 + 16;  // bytes per staged row
+    static_assert(TILE_M * CP <= (SB ? 1 : 2) * (A_BYTES + B_BYTES), "output tile must fit the stage buffers");
+    __syncthreads();
 #pragma unroll
-      for (int in = 0; in < TN; ++in) {
-        const int cl = 32 * (wx * TN + in) + ml, col = n0 + cl;
-        float bias = 0.f;
-        if (gb.bias && col < gb.N) bias = __uint_as_float((uint32_t)((const uint16_t*)gb.bias)[col] << 16);
+    for (int in = 0; in < TN; ++in) {
+      const int cl = 32 * (wx * TN + in) + ml, col = n0 + cl;
+      float bias = 0.f;
+      if (gb.bias && col < gb.N) bias = __uint_as_float((uint32_t)((const uint16_t*)gb.bias)[col] << 16);
 #pragma unroll
-        for (int im = 0; im < TM; ++im)
+      for (int im = 0; im < TM; ++im)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int rl = 32 * (wy * TM + im) + 8 * (v / 4) + 4 * h + (v % 4);
-            *(__bf16*)(smem + rl * CP + cl * 2) = (__bf16)(acc[im][in][v] + bias);  // round to nearest even
-          }
-      }
-      __syncthreads();
-      constexpr int PPR = TILE_N / 8;  // 16-byte pieces per row
-#pragma unroll
-      for (int p = tid; p < TILE_M * PPR; p += 256) {
-        const int rl = p / PPR, q = p - rl * PPR;
-        const int row = m0 + rl, col = n0 + q * 8;
-        if (row < gb.M && col < gb.N)
-          *(u32x4*)((uint16_t*)gb.c + (size_t)row * gb.ldc + col) = *(const u32x4*)(smem + rl * CP + q * 16);
-      }
-      return;
+        for (int v = 0; v < 16; ++v) {
+          const int rl = 32 * (wy * TM + im) + 8 * (v / 4) + 4 * h + (v % 4);
+          *(__bf16*)(smem + rl * CP + cl * 2) = (__bf16)(acc[im][in][v] + bias);  // round to nearest even
+        }
     }
+    __syncthreads();
+    constexpr int PPR = TILE_N / 8;  // 16-byte pieces per row
+#pragma unroll
+    for (int p = tid; p < TILE_M * PPR; p += 256) {
+      const int rl = p / PPR, q = p - rl * PPR;
+      const int row = m0 + rl, col = n0 + q * 8;
+      if (row < gb.M && col < gb.N)
+        *(u32x4*)((uint16_t*)gb.c + (size_t)row * gb.ldc + col) = *(const u32x4*)(smem + rl * CP + q * 16);
+    }
+    return;
   }
 #pragma unroll
   for (int in = 0; in < TN; ++in) {
@@ -393,7 +341,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
     if (col >= gb.N) continue;
     float bias = 0.f;
     if (!pc && gb.bias)
-      bias = BF16 ? __uint_as_float((uint32_t)((const uint16_t*)gb.bias)[col] << 16) : ((const float*)gb.bias)[col];
+      bias = __uint_as_float((uint32_t)((const uint16_t*)gb.bias)[col] << 16);
 #pragma unroll
     for (int im = 0; im < TM; ++im) {
 #pragma unroll
@@ -405,8 +353,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
           continue;
         }
         const float r = acc[im][in][v] + bias;
-        if (BF16) ((uint16_t*)gb.c)[(size_t)row * gb.ldc + col] = (uint16_t)f32_to_bf16_rne(r);
-        else ((float*)gb.c)[(size_t)row * gb.ldc + col] = r;
+        ((uint16_t*)gb.c)[(size_t)row * gb.ldc + col] = (uint16_t)f32_to_bf16_rne(r);
       }
     }
   }
@@ -414,7 +361,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
 
 // C_o = sum over the splits (ascending) of the fp32 partials + bias, rounded to the output type.
 // grid: (ceil(max M*N / 4 / 256), blocks); M*N is a multiple of 4 whenever the MFMA path is used.
-template <bool BF16>
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmBlock* __restrict__ blocks,
                                                           const float* __restrict__ partial, int64_t partial_stride,
                                                           int nsplit) {
@@ -430,23 +376,13 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmBlock* __res
     acc.x += t.x; acc.y += t.y; acc.z += t.z; acc.w += t.w;
   }
   if (gb.bias) {
-    if (BF16) {
-      const uint16_t* b = (const uint16_t*)gb.bias + col;
-      acc.x += __uint_as_float((uint32_t)b[0] << 16); acc.y += __uint_as_float((uint32_t)b[1] << 16);
-      acc.z += __uint_as_float((uint32_t)b[2] << 16); acc.w += __uint_as_float((uint32_t)b[3] << 16);
-    } else {
-      const float* b = (const float*)gb.bias + col;
-      acc.x += b[0]; acc.y += b[1]; acc.z += b[2]; acc.w += b[3];
-    }
+    const uint16_t* b = (const uint16_t*)gb.bias + col;
+    acc.x += __uint_as_float((uint32_t)b[0] << 16); acc.y += __uint_as_float((uint32_t)b[1] << 16);
+    acc.z += __uint_as_float((uint32_t)b[2] << 16); acc.w += __uint_as_float((uint32_t)b[3] << 16);
   }
-  if (BF16) {
-    uint16_t* c = (uint16_t*)gb.c + (size_t)row * gb.ldc + col;
-    c[0] = (uint16_t)f32_to_bf16_rne(acc.x); c[1] = (uint16_t)f32_to_bf16_rne(acc.y);
-    c[2] = (uint16_t)f32_to_bf16_rne(acc.z); c[3] = (uint16_t)f32_to_bf16_rne(acc.w);
-  } else {
-    float* c = (float*)gb.c + (size_t)row * gb.ldc + col;
-    c[0] = acc.x; c[1] = acc.y; c[2] = acc.z; c[3] = acc.w;
-  }
+  uint16_t* c = (uint16_t*)gb.c + (size_t)row * gb.ldc + col;
+  c[0] = (uint16_t)f32_to_bf16_rne(acc.x); c[1] = (uint16_t)f32_to_bf16_rne(acc.y);
+  c[2] = (uint16_t)f32_to_bf16_rne(acc.z); c[3] = (uint16_t)f32_to_bf16_rne(acc.w);
 }
 
 // db_i[f] = sum over the batch of dy_i[n][f]: one block per 16 features, 16 batch lanes each (many small
@@ -485,8 +421,9 @@ __global__ __launch_bounds__(256) void colsum_kernel(const ColsumBlock* __restri
 // ---- host side ------------------------------------------------------------------
 
 bool gemm_mfma_usable(const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc) {
-  const int ve = bf16 ? 8 : 4;
-  const size_t es = bf16 ? 2 : 4;
+  const int ve = 8;
+  const size_t es = 2;
+  if (!bf16) return false;           // gemm_split.hip
   if (!a_kc && b_kc) return false;  // not a layout of the affine layer: not built
   for (const GemmBlock& b : blocks) {
     if (b.nseg < 1 || b.nseg > kGemmMaxSeg) return false;
@@ -559,19 +496,19 @@ size_t gemm_mfma_partial_floats(const std::vector<GemmBlock>& blocks, int nsplit
 
 // T: workgroup tile / 64; the 64-tiles load two stages ahead (one workgroup per compute unit has nothing else
 // to cover a stage's latency with), the 128-tiles one.
-template <bool BF16, bool A_KC, bool B_KC, int T>
+template <bool A_KC, bool B_KC, int T>
 static int launch_gemm_variant(dim3 grid, const GemmBlock* d_blocks, float* partial, int64_t max_mn, hipStream_t st) {
-  constexpr int ES = BF16 ? 2 : 4, BK = BF16 ? 64 : 32, TILE = 64 * T, D = T == 1 ? 2 : 1;
-  constexpr int A_BYTES = A_KC ? TILE * (BK * ES + 16) : BK * (TILE * ES + (BF16 ? 32 : 16));
-  constexpr int B_BYTES = B_KC ? TILE * (BK * ES + 16) : BK * (TILE * ES + (BF16 ? 32 : 16));
+  constexpr int ES = 2, BK = 64, TILE = 64 * T, D = T == 1 ? 2 : 1;
+  constexpr int A_BYTES = A_KC ? TILE * (BK * ES + 16) : BK * (TILE * ES + 32);
+  constexpr int B_BYTES = B_KC ? TILE * (BK * ES + 16) : BK * (TILE * ES + 32);
   // The weight-gradient layout (both operands with their rows contiguous: short K loops, many tiles) keeps one LDS
   // buffer and pays a second barrier per stage: a third workgroup then fits a compute unit, which is worth 4-5 %
   // there; the forward and data-gradient layouts lose 1-3 % that way and keep two buffers.
   constexpr bool SB = !A_KC && !B_KC;
   constexpr int LDS = (SB ? 1 : 2) * (A_BYTES + B_BYTES);
   if (LDS > 64 * 1024)
-    if (int rc = allow_large_lds<gemm_mfma_kernel<BF16, A_KC, B_KC, T, T, D, SB>>()) return rc;
-  hipLaunchKernelGGL((gemm_mfma_kernel<BF16, A_KC, B_KC, T, T, D, SB>), grid, dim3(256), LDS, st, d_blocks, partial, max_mn);
+    if (int rc = allow_large_lds<gemm_mfma_kernel<A_KC, B_KC, T, T, D, SB>>()) return rc;
+  hipLaunchKernelGGL((gemm_mfma_kernel<A_KC, B_KC, T, T, D, SB>), grid, dim3(256), LDS, st, d_blocks, partial, max_mn);
   return DISTDL_OK;
 }
 
@@ -591,32 +528,25 @@ int launch_gemm_mfma(const GemmBlock* d_blocks, const std::vector<GemmBlock>& bl
   ProfScope prof(name, st);
   // launches that take 64-tiles over the whole K range (about one tile per compute unit: the small-batch forward
   // and data-gradient products) run on the streaming kernel
-  if (t == 64 && nsplit <= 1 && a_kc && gemm_stream_usable(blocks, bf16, a_kc, b_kc)) return launch_gemm_stream(d_blocks, blocks, bf16, b_kc, st);
+  if (t == 64 && nsplit <= 1 && a_kc && gemm_stream_usable(blocks, bf16, a_kc, b_kc)) return launch_gemm_stream(d_blocks, blocks, b_kc, st);
   if (t == 128 && nsplit <= 1 && !a_kc && !b_kc && gemm_stream_usable(blocks, bf16, a_kc, b_kc)) {
     if (colsum) colsum->done = true;  // M is a multiple of a piece for every block: the feature counts fit the fused column sums
     return launch_gemm_stream_tt(d_blocks, blocks, bf16, colsum ? colsum->d_blocks : nullptr,
                                  colsum ? colsum->n_blocks : 0, colsum ? colsum->max_f : 0, st);
   }
   int rc;
-#define DISTDL_GEMM(BF_, A_, B_)                                                                \
-  rc = t == 128 ? launch_gemm_variant<BF_, A_, B_, 2>(grid, d_blocks, partial, max_mn, st)      \
-                : launch_gemm_variant<BF_, A_, B_, 1>(grid, d_blocks, partial, max_mn, st)
+#define DISTDL_GEMM(A_, B_)                                                                \
+  rc = t == 128 ? launch_gemm_variant<A_, B_, 2>(grid, d_blocks, partial, max_mn, st)      \
+                : launch_gemm_variant<A_, B_, 1>(grid, d_blocks, partial, max_mn, st)
   // the three operand layouts of the affine layer: forward (K, K), data gradient (K, N), weight gradient (M, N)
-  if (!bf16) {
-    if (a_kc && b_kc) DISTDL_GEMM(false, true, true);
-    else if (a_kc) DISTDL_GEMM(false, true, false);
-    else DISTDL_GEMM(false, false, false);
-  } else {
-    if (a_kc && b_kc) DISTDL_GEMM(true, true, true);
-    else if (a_kc) DISTDL_GEMM(true, true, false);
-    else DISTDL_GEMM(true, false, false);
-  }
+  if (a_kc && b_kc) DISTDL_GEMM(true, true);
+  else if (a_kc) DISTDL_GEMM(true, false);
+  else DISTDL_GEMM(false, false);
 #undef DISTDL_GEMM
   if (rc) return rc;
   if (nsplit > 1) {
     dim3 rgrid((unsigned)((max_mn / 4 + 255) / 256), (unsigned)blocks.size());
-    if (bf16) hipLaunchKernelGGL(gemm_reduce_kernel<true>, rgrid, block, 0, st, d_blocks, partial, max_mn, nsplit);
-    else hipLaunchKernelGGL(gemm_reduce_kernel<false>, rgrid, block, 0, st, d_blocks, partial, max_mn, nsplit);
+    hipLaunchKernelGGL(gemm_reduce_kernel, rgrid, block, 0, st, d_blocks, partial, max_mn, nsplit);
   }
   return DISTDL_OK;
 }

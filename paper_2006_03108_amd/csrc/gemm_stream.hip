@@ -63,18 +63,14 @@ union Frag {
 
 }  // namespace
 
-// BF16: bf16 operands and output (v_mfma_f32_32x32x16_bf16, 64 k per step), else fp32 (v_mfma_f32_32x32x2_f32, 32 k
-// per step; a 16-byte fragment read gives a lane four consecutive k, used by four MFMAs whose k pairs are (j, 4 + j),
-// the same pairing on both operands).  Either way a staged row of a K-contiguous operand is 128 bytes (8 pieces),
-// so the staging geometry and its swizzle are the same.  An N-contiguous fp32 B is staged as 32 k lines x 256 bytes
-// (64 columns), line l keeping piece c at position c ^ (8 * ((l >> 2) & 1)), and read one float per lane: the 32
-// lanes of a half-wave read 128 contiguous bytes, and the two half-waves (lines l, l + 4) different bank halves.
-template <bool BF16, bool B_KC>
+// bf16 operands and output, v_mfma_f32_32x32x16_bf16, 64 k per step: a staged row of a K-contiguous operand is 128 bytes
+// (8 pieces).  (fp32 products: gemm_split.hip.)
+template <bool B_KC>
 __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __restrict__ blocks) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int ES = BF16 ? 2 : 4;        // element size
+  constexpr int ES = 2;                   // element size
   constexpr int VE = 16 / ES;             // elements per 16-byte piece
-  constexpr int SK = BF16 ? 64 : 32;      // k per step: 128 bytes of a K-contiguous row
+  constexpr int SK = 64;                  // k per step: 128 bytes of a K-contiguous row
   const GemmBlock& gb = blocks[blockIdx.z];
   const int tiles_m = (gb.M + 63) / 64, tiles_n = (gb.N + 63) / 64;
   // consecutive tiles share the B rows (m walks fastest) and stay behind one L2
@@ -104,8 +100,7 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __
   uint32_t l_ldb = 0;
   u32x4 ra = lds_direct_rsrc(nullptr, 0), rb = lds_direct_rsrc(nullptr, 0);
   uint32_t goff[16];
-  // K-contiguous operand, load i: row 8 i + lane / 8, position lane % 8.  N-contiguous bf16 B: the same with k
-  // lines for rows; N-contiguous fp32 B: k line 4 i + lane / 16, position lane % 16.
+  // K-contiguous operand, load i: row 8 i + lane / 8, position lane % 8.  N-contiguous B: the same with k lines for rows.
   auto enter_segment = [&]() __attribute__((always_inline)) {
     const GemmSeg& sg = gb.seg[ls];
     l_K = sg.K;
@@ -121,15 +116,10 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __
       goff[i] = ((uint32_t)(m0 + r) * sg.lda + ca * VE) * ES;
       if (B_KC) {
         goff[8 + i] = ((uint32_t)(n0 + r) * sg.ldb + ca * VE) * ES;
-      } else if (BF16) {
+      } else {
         const int cb = (lane & 7) ^ (4 * ((r >> 1) & 1));
         goff[8 + i] = ((uint32_t)r * sg.ldb + n0 + cb * VE) * ES;
         if (n0 + cb * VE >= gb.N) goff[8 + i] = kOobOff;  // columns beyond N (whole pieces: N % 8 == 0)
-      } else {
-        const int l = 4 * i + (lane >> 4);
-        const int cb = (lane & 15) ^ (8 * ((l >> 2) & 1));
-        goff[8 + i] = ((uint32_t)l * sg.ldb + n0 + cb * VE) * ES;
-        if (n0 + cb * VE >= gb.N) goff[8 + i] = kOobOff;  // whole pieces: N % 4 == 0
       }
     }
   };
@@ -180,22 +170,6 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __
       }
     }
   };
-  // loads 2 k and 2 k + 1 of the step; TAIL (compile time) says whether the K-tail select is needed at all
-  auto issue_pair = [&](auto k_c, auto tail_c) __attribute__((always_inline)) {
-    constexpr int k = decltype(k_c)::value;
-    constexpr bool TAIL = decltype(tail_c)::value && (k < 4 || B_KC);
-#pragma unroll
-    for (int i = 2 * k; i < 2 * k + 2; ++i) {
-      uint32_t off = goff[i];
-      if constexpr (TAIL) {
-        const int r = 8 * (i & 7) + (lane >> 3);
-        const int ca = (lane & 7) ^ ((r >> 1) & 7);
-        if (ca * VE >= is_kleft) off = kOobOff;
-      }
-      if (i < 8) load_to_lds(ra, is_d + i * 1024, off, is_a);
-      else load_to_lds(rb, is_d + kOperandBytes + (i - 8) * 1024, off, is_b);
-    }
-  };
   auto issue = [&](int buf, bool valid) __attribute__((always_inline)) {
     issue_begin(buf, valid);
     static_for4([&](auto q) __attribute__((always_inline)) { issue_part(q); });
@@ -212,14 +186,8 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __
 #pragma unroll
   for (int t = 0; t < 2; ++t)
     rdt[t] = kOperandBytes + tk * 128 + ((((4 * t + (tr >> 3)) ^ (4 * ((tk >> 1) & 1)))) * 16) + (tr & 7) * 2;
-  //   fp32 B when N-contiguous: k line 8 g + 4 h + j, column 32 t + ml: one float of piece (8 t + ml / 4) ^ (8 h)
-  uint32_t rdn[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-    rdn[t] = kOperandBytes + 4 * h * 256 + (((8 * t + (ml >> 2)) ^ (8 * h)) * 16) + (ml & 3) * 4;
 
-  // fragments of k groups g0, g0 + 1 of the step in buffer buf.  fp32: fa / fb hold four k per lane; an N-contiguous
-  // fp32 B is read float by float into the same four slots.
+  // fragments of k groups g0, g0 + 1 of the step in buffer buf
   auto read_half = [&](int buf, int g0, Frag (&fa)[2][2], Frag (&fb)[2][2]) __attribute__((always_inline)) {
     const char* s = my + buf * kStepBytes;
 #pragma unroll
@@ -229,12 +197,9 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __
         fa[g][t].u = *(const u32x4*)(s + rdk[g0 + g] + t * 4096);
         if constexpr (B_KC) {
           fb[g][t].u = *(const u32x4*)(s + kOperandBytes + rdk[g0 + g] + t * 4096);
-        } else if constexpr (BF16) {
+        } else {
           fb[g][t].t[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(s + rdt[t] + (g0 + g) * 16 * 128));
           fb[g][t].t[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(s + rdt[t] + (g0 + g) * 16 * 128 + 4 * 128));
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) fb[g][t].u[j] = *(const uint32_t*)(s + rdn[t] + ((g0 + g) * 8 + j) * 256);
         }
       }
   };
@@ -242,22 +207,11 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __
   auto mm_half = [&](const Frag (&fa)[2][2], const Frag (&fb)[2][2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-      if constexpr (BF16) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[g][j].v, fa[g][i].v, acc[i][j], 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[g][j].u[e]), __uint_as_float(fa[g][i].u[e]),
-                                                               acc[i][j], 0, 0, 0);
-      }
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[g][j].v, fa[g][i].v, acc[i][j], 0, 0, 0);
     }
   };
 
@@ -265,111 +219,29 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __
     enter_segment();
     issue(0, true);
     issue(1, 1 < n);
-    if constexpr (BF16) {
-      Frag xa[2][2], xb[2][2], ya[2][2], yb[2][2];
-      // One step: its 16 loads have landed when at most the 16 of the next step are outstanding.  The buffer is
-      // handed to the loads of the step after next as soon as every fragment of it is in registers.
-      auto step = [&](int st, int buf) __attribute__((always_inline)) {
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt16);
-        __builtin_amdgcn_sched_barrier(0);
-        read_half(buf, 0, xa, xb);
-        read_half(buf, 2, ya, yb);
-        __builtin_amdgcn_sched_barrier(0);
-        mm_half(xa, xb);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
-        issue(buf, st + 2 < n);
-        __builtin_amdgcn_sched_barrier(0);
-        mm_half(ya, yb);
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      int st = 0;
-      for (; st + 2 <= n; st += 2) {
-        step(st, 0);
-        step(st + 1, 1);
-      }
-      if (st < n) step(st, 0);
-    } else {
-      // fp32: a step is 64 MFMAs of 64 clocks and this wave is alone on its SIMD (512 registers), so the pipeline is
-      // one step deeper in registers and everything else is issued in the shadow of the MFMAs, in 16 slots, one
-      // after every four of them.  While step s multiplies out of one register set, the fragments of step s + 1 are
-      // read from the other staging buffer into the other set (its loads were issued during step s - 2: at most the
-      // 16 of step s + 2 are outstanding when they have landed), and when those reads are done the buffer takes the
-      // loads of step s + 3.  Every load has more than a step to land and every LDS read a step before its use.
-      Frag pa[4][2], pb[4][2], qa[4][2], qb[4][2];
-      auto rd_a = [&](int buf, int g, Frag (&fa)[4][2]) __attribute__((always_inline)) {
-        const char* s = my + buf * kStepBytes;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) fa[g][t].u = *(const u32x4*)(s + rdk[g] + t * 4096);
-      };
-      auto rd_b = [&](int buf, int g, Frag (&fb)[4][2]) __attribute__((always_inline)) {
-        const char* s = my + buf * kStepBytes;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          if constexpr (B_KC) {
-            fb[g][t].u = *(const u32x4*)(s + kOperandBytes + rdk[g] + t * 4096);
-          } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) fb[g][t].u[j] = *(const uint32_t*)(s + rdn[t] + (g * 8 + j) * 256);
-          }
-        }
-      };
-      auto mm4 = [&](const Frag (&fa)[4][2], const Frag (&fb)[4][2], int g, int e) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[g][j].u[e]), __uint_as_float(fa[g][i].u[e]),
-                                                             acc[i][j], 0, 0, 0);
-      };
-      __builtin_amdgcn_s_waitcnt(kWaitVmcnt16);  // step 0 has landed
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        rd_a(0, g, pa);
-        rd_b(0, g, pb);
-      }
+    Frag xa[2][2], xb[2][2], ya[2][2], yb[2][2];
+    // One step: its 16 loads have landed when at most the 16 of the next step are outstanding.  The buffer is
+    // handed to the loads of the step after next as soon as every fragment of it is in registers.
+    auto step = [&](int st, int buf) __attribute__((always_inline)) {
+      __builtin_amdgcn_s_waitcnt(kWaitVmcnt16);
+      __builtin_amdgcn_sched_barrier(0);
+      read_half(buf, 0, xa, xb);
+      read_half(buf, 2, ya, yb);
+      __builtin_amdgcn_sched_barrier(0);
+      mm_half(xa, xb);
+      __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
-      issue(0, 2 < n);
-      // step st out of (ca, cb), whose buffer is buf; (na, nb) take step st + 1.  Slots: 0 waits for the loads of
-      // step st + 1, 1 - 4 read its fragments, 6 - 13 issue two loads each.  The wave has about 60 clocks per slot
-      // before the matrix pipe runs dry, and a taken branch costs a good part of that, so the one decision of the
-      // step (does its load have a K tail) is taken once, in front of two copies of the body.
-      auto body = [&](int buf, const Frag (&ca)[4][2], const Frag (&cb)[4][2], Frag (&na)[4][2], Frag (&nb)[4][2],
-                      auto tail_c) __attribute__((always_inline)) {
-#pragma unroll
-        for (int slot = 0; slot < 16; ++slot) {
-          mm4(ca, cb, slot >> 2, slot & 3);
-          __builtin_amdgcn_sched_barrier(0);
-          if (slot == 0) __builtin_amdgcn_s_waitcnt(kWaitVmcnt16);
-          if (slot >= 1 && slot <= 4) {
-            rd_a(buf ^ 1, slot - 1, na);
-            rd_b(buf ^ 1, slot - 1, nb);
-          }
-          if (slot == 6) __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
-          if (slot == 6) issue_pair(std::integral_constant<int, 0>{}, tail_c);
-          if (slot == 7) issue_pair(std::integral_constant<int, 1>{}, tail_c);
-          if (slot == 8) issue_pair(std::integral_constant<int, 2>{}, tail_c);
-          if (slot == 9) issue_pair(std::integral_constant<int, 3>{}, tail_c);
-          if (slot == 10) issue_pair(std::integral_constant<int, 4>{}, tail_c);
-          if (slot == 11) issue_pair(std::integral_constant<int, 5>{}, tail_c);
-          if (slot == 12) issue_pair(std::integral_constant<int, 6>{}, tail_c);
-          if (slot == 13) issue_pair(std::integral_constant<int, 7>{}, tail_c);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      };
-      auto step = [&](int st, int buf, const Frag (&ca)[4][2], const Frag (&cb)[4][2], Frag (&na)[4][2],
-                      Frag (&nb)[4][2]) __attribute__((always_inline)) {
-        issue_begin(buf ^ 1, st + 3 < n);  // (scalars only; the loads follow in the body)
-        if (is_tail) body(buf, ca, cb, na, nb, std::true_type{});
-        else body(buf, ca, cb, na, nb, std::false_type{});
-      };
-      int st = 0;
-      for (; st + 2 <= n; st += 2) {
-        step(st, 0, pa, pb, qa, qb);
-        step(st + 1, 1, qa, qb, pa, pb);
-      }
-      if (st < n) step(st, 0, pa, pb, qa, qb);
+      issue(buf, st + 2 < n);
+      __builtin_amdgcn_sched_barrier(0);
+      mm_half(ya, yb);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    int st = 0;
+    for (; st + 2 <= n; st += 2) {
+      step(st, 0);
+      step(st + 1, 1);
     }
+    if (st < n) step(st, 0);
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // nothing may still land in LDS when the epilogue reuses it
   }
 
@@ -407,51 +279,29 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_kernel(const GemmBlock* __
   if (grow >= gb.M || gcol >= gb.N) return;
   const bool full = gcol + 16 <= gb.N;
   if (gb.bias) {
-    if constexpr (BF16) {
-      const uint16_t* bp = (const uint16_t*)gb.bias + gcol;
-      if (full) {
+    const uint16_t* bp = (const uint16_t*)gb.bias + gcol;
+    if (full) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) s[q] += __uint_as_float((uint32_t)bp[q] << 16);
-      } else {
-        for (int q = 0; gcol + q < gb.N; ++q) s[q] += __uint_as_float((uint32_t)bp[q] << 16);
-      }
+      for (int q = 0; q < 16; ++q) s[q] += __uint_as_float((uint32_t)bp[q] << 16);
     } else {
-      const float* bp = (const float*)gb.bias + gcol;
-      if (full) {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) s[q] += bp[q];
-      } else {
-        for (int q = 0; gcol + q < gb.N; ++q) s[q] += bp[q];
-      }
+      for (int q = 0; gcol + q < gb.N; ++q) s[q] += __uint_as_float((uint32_t)bp[q] << 16);
     }
   }
-  if constexpr (BF16) {
-    union {
-      __bf16 b[16];
-      uint16_t h16[16];
-      u32x4 u[2];
-    } o;
+  union {
+    __bf16 b[16];
+    uint16_t h16[16];
+    u32x4 u[2];
+  } o;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) o.b[q] = (__bf16)s[q];  // round to nearest even
-    uint16_t* dst = (uint16_t*)gb.c + (size_t)grow * gb.ldc + gcol;
-    if (full && gb.ldc % 8 == 0 && ((uintptr_t)gb.c & 15) == 0) {
-      ((u32x4*)dst)[0] = o.u[0];
-      ((u32x4*)dst)[1] = o.u[1];
-    } else {
-#pragma unroll
-      for (int q = 0; q < 16; ++q)
-        if (gcol + q < gb.N) dst[q] = o.h16[q];
-    }
+  for (int q = 0; q < 16; ++q) o.b[q] = (__bf16)s[q];  // round to nearest even
+  uint16_t* dst = (uint16_t*)gb.c + (size_t)grow * gb.ldc + gcol;
+  if (full && gb.ldc % 8 == 0 && ((uintptr_t)gb.c & 15) == 0) {
+    ((u32x4*)dst)[0] = o.u[0];
+    ((u32x4*)dst)[1] = o.u[1];
   } else {
-    float* dst = (float*)gb.c + (size_t)grow * gb.ldc + gcol;
-    if (full && gb.ldc % 4 == 0 && ((uintptr_t)gb.c & 15) == 0) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) ((float4*)dst)[q] = float4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
-    } else {
-#pragma unroll
-      for (int q = 0; q < 16; ++q)
-        if (gcol + q < gb.N) dst[q] = s[q];
-    }
+    for (int q = 0; q < 16; ++q)
+      if (gcol + q < gb.N) dst[q] = o.h16[q];
   }
 }
 
@@ -784,21 +634,19 @@ int launch_gemm_stream_tt(const GemmBlock* d_blocks, const std::vector<GemmBlock
   return DISTDL_OK;
 }
 
-template <bool BF16, bool B_KC>
+template <bool B_KC>
 static int launch_stream_variant(dim3 grid, const GemmBlock* d_blocks, hipStream_t st) {
-  if (int rc = allow_large_lds<gemm_stream_kernel<BF16, B_KC>>()) return rc;
-  hipLaunchKernelGGL((gemm_stream_kernel<BF16, B_KC>), grid, dim3(256), kStreamLds, st, d_blocks);
+  if (int rc = allow_large_lds<gemm_stream_kernel<B_KC>>()) return rc;
+  hipLaunchKernelGGL((gemm_stream_kernel<B_KC>), grid, dim3(256), kStreamLds, st, d_blocks);
   return DISTDL_OK;
 }
 
-int launch_gemm_stream(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool bf16, bool b_kc,
-                       hipStream_t st) {
+int launch_gemm_stream(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool b_kc, hipStream_t st) {
   int tiles = 0;
   for (const GemmBlock& b : blocks) tiles = std::max(tiles, ((b.M + 63) / 64) * ((b.N + 63) / 64));
   tiles = (tiles + 7) / 8 * 8;
   const dim3 grid((unsigned)tiles, 1, (unsigned)blocks.size());
-  if (bf16) return b_kc ? launch_stream_variant<true, true>(grid, d_blocks, st) : launch_stream_variant<true, false>(grid, d_blocks, st);
-  return b_kc ? launch_stream_variant<false, true>(grid, d_blocks, st) : launch_stream_variant<false, false>(grid, d_blocks, st);
+  return b_kc ? launch_stream_variant<true>(grid, d_blocks, st) : launch_stream_variant<false>(grid, d_blocks, st);
 }
 
 }  // namespace distdl
