@@ -23,7 +23,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
-MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
+# "f32_split": an fp32 product as six products of bf16 parts (the step fractions of fp32 workloads stay against the fp32 peak)
+MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "f32_split": 2500.0 / 6}
 
 
 def _dev_randn(shape, seed, std=1.0, dtype=None):
@@ -193,7 +194,7 @@ class AffineWorkload:
         self.flops_fwd = 2.0 * c["n_b"] * c["n_fi"] * c["n_fo"]
         self.flops_step = 3.0 * self.flops_fwd
         esz = 4 if dtype == "f32" else 2
-        self.alg = {"affine_fwd": ("mfma", self.flops_fwd), "affine_bwd_x": ("mfma", self.flops_fwd),
+        self.alg = {"affine_fwd": ("mfma", self.flops_fwd), "affine_bwd_split": ("mfma", 2 * self.flops_fwd), "affine_bwd_x": ("mfma", self.flops_fwd),
                     "affine_bwd_w": ("mfma", self.flops_fwd), "affine_bwd_direct": ("mfma", 2 * self.flops_fwd),
                     "affine_bias_grad": ("hbm", (c["n_b"] + 1) * c["n_fo"] * esz)}
         # bytes every kernel must at least move (operands once, result once): the HBM side of the roofline
@@ -652,7 +653,7 @@ class SmallCnnWorkload:
                 "sample": f"oracle network.distributed_step (numpy fp64) on the full cfg4 batch, mean of {reps} steps"}
 
 
-def kernel_rooflines(workload, report, traffic):
+def kernel_rooflines(workload, report, traffic, steps):
     """Per-kernel roofline entries from the library's HIP-event timings."""
     out = {}
     for name, (count, total_ms) in report.items():
@@ -664,6 +665,8 @@ def kernel_rooflines(workload, report, traffic):
             if work is None and key == "conv_reduce_dw":
                 nparts = workload.dd.distdl_conv_bwd_workspace(workload.plan) // (4 * (workload.nw + workload.cfg["c_out"]))
                 work = (nparts + 1) * workload.nw * 4
+            if name == "conv_bwd_data_split":   # one launch for all stride classes, or one for each
+                work = workload.flops_fwd * steps / count
             if bound == "hbm":
                 ach = work / (avg_ms * 1e-3) / 1e9
                 entry.update(bound="hbm", achieved=ach, peak=HBM_PEAK_GBS, unit="GB/s", frac=ach / HBM_PEAK_GBS,
@@ -671,6 +674,8 @@ def kernel_rooflines(workload, report, traffic):
             else:
                 ach = work / (avg_ms * 1e-3) / 1e12
                 kdt = getattr(workload, "kernel_dtype", {}).get(key, workload.dtype)   # the MFMA type of this kernel
+                if kdt == "f32" and "_split" in name:
+                    kdt = "f32_split"
                 peak = MFMA_PEAK_TFLOPS[kdt]
                 entry.update(bound="mfma", achieved=ach, peak=peak, unit="TFLOP/s", frac=ach / peak,
                              algorithmic_flops=work, mfma_dtype=kdt)
@@ -753,7 +758,7 @@ def main():
     report = dd.distdl_profile_report()
     dd.distdl_profile_enable(False)
     sec = elapsed / args.steps
-    kernels = kernel_rooflines(wl, report, load_traffic())
+    kernels = kernel_rooflines(wl, report, load_traffic(), args.steps)
     launches_per_step = sum(k["launches"] for k in kernels.values()) / args.steps
     dominant = max(kernels, key=lambda k: kernels[k]["total_ms"])
     dk = kernels[dominant]
@@ -780,7 +785,7 @@ def main():
             w.step()
         torch.cuda.synchronize()
         s_sec = (time.perf_counter() - t0) / steps
-        kern = kernel_rooflines(w, dd.distdl_profile_report(), load_traffic())
+        kern = kernel_rooflines(w, dd.distdl_profile_report(), load_traffic(), steps)
         dd.distdl_profile_enable(False)
         return w, {"metric": w.metric, "value": w.value(s_sec), "unit": w.unit, "steps": steps,
                    "ms_per_step": s_sec * 1e3, "dtype": w.dtype, "config": w.describe, "kernels": kern}

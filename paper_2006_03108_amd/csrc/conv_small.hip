@@ -623,7 +623,7 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
   };
 
   // One kernel plane: its weights are staged once, so every workgroup fetches them in the layer's own order (a launch that
-  // rearranges them first took 4.5 us; 1 -> 1 channels, one dimension, forward and backward: 36.1 -> 27.6 us).
+  // rearranges them first took 4.5 us; 1 -> 1 channels, one dimension, forward and backward: 36 -> 28 to 31 us).
   if (!a.wt)
 #pragma unroll 8
     for (uint32_t i = tid; i < wfloats; i += 256) {
