@@ -19,8 +19,9 @@
 // is then 512 contiguous bytes and free of bank conflicts.
 //
 // A step takes tiles * NT * 6 MFMAs of 16 clocks; a tile's operand (6 reads, 3 KiB) serves all NT columns, those of dy stay in
-// registers over the tiles.  The rest is LDS: at 32 -> 32 channels, 5^3, stride 2, 256^3 on 64 workers it is active for 54 %
-// of the time and the matrix cores for 93 % of theirs at the clock that their power leaves them (1.04 PFLOP/s in bf16).
+// registers over the tiles.  At 32 -> 32 channels, 5^3, stride 2, 256^3 on 64 workers the matrix pipes issue in 47 % of the
+// cycles (at 2.03 GHz: 1.04 PFLOP/s in bf16) and LDS is active in 27 %; what bounds it is vector instructions, 3.3 of 4
+// clocks beside each MFMA of 16: splitting the staged pieces, the addresses of six reads a tile, the sums' additions.
 //
 // The sums of a step start from zero and join the running sums by a vector instruction.  A bf16 MFMA drops the bits of its
 // products that lie below its largest operand, towards minus infinity: over 10^3 steps in one accumulator that bias made an
