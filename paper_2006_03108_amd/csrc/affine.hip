@@ -23,8 +23,7 @@ struct distdl_affine_plan {
   int32_t* d_sizes = nullptr;  // [P_fo fo sizes][P_fi fi sizes]
   distdl::DevArray<distdl::GemmBlock> g_fwd, g_dx, g_dw;
   distdl::DevArray<distdl::ColsumBlock> g_db;
-  float* d_partial = nullptr;  // fp32 partial tiles of K-split GEMM launches
-  size_t partial_floats = 0;
+  distdl::StreamScratch partial;  // fp32 partial tiles of K-split GEMM launches
 };
 
 namespace distdl {
@@ -220,18 +219,8 @@ int distdl_affine_plan_destroy(distdl_affine_plan* p) {
   p->g_dx.release();
   p->g_dw.release();
   p->g_db.release();
-  if (p->d_partial) (void)hipFree(p->d_partial);
+  p->partial.release();
   delete p;
-  return DISTDL_OK;
-}
-
-static int ensure_partial(distdl_affine_plan* p, size_t floats) {
-  if (floats <= p->partial_floats) return DISTDL_OK;
-  if (p->d_partial) (void)hipFree(p->d_partial);
-  p->d_partial = nullptr;
-  p->partial_floats = 0;
-  DISTDL_HIP_TRY(hipMalloc((void**)&p->d_partial, floats * sizeof(float)));
-  p->partial_floats = floats;
   return DISTDL_OK;
 }
 
@@ -240,6 +229,7 @@ int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const vo
   if (!p || !x_dev || !W_dev || !y_dev) return set_error(DISTDL_ERR_NULL, "affine_fwd: null argument");
   const size_t esz = dtype_size(p->dtype);
   hipStream_t st_ = (hipStream_t)stream;
+  float* partial = nullptr;
   int rc;
   if ((rc = check_ptrs(x_dev, p->P_fi, esz, "x")) || (rc = check_ptrs(W_dev, p->P_fo * p->P_fi, esz, "W")) ||
       (rc = check_ptrs((const void* const*)y_dev, p->P_fo, esz, "y")))
@@ -262,15 +252,15 @@ int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const vo
     }
     if ((!bf16 || !gemm_mfma_usable(blocks, bf16, true, true)) && gemm_split_usable(blocks, bf16, true, true)) {
       const GemmSplitPlan sp = gemm_split_plan(blocks, gemm_split_vec(blocks, bf16, true, true));
-      if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = ensure_partial(p, sp.partial_floats))) return rc;
-      if ((rc = launch_gemm_split_fwd(p->g_fwd.dev, blocks, bf16, sp, p->d_partial, st_))) return rc;
+      if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = p->partial.get(sp.partial_floats, st_, &partial))) return rc;
+      if ((rc = launch_gemm_split_fwd(p->g_fwd.dev, blocks, bf16, sp, partial, st_))) return rc;
       DISTDL_HIP_TRY(hipGetLastError());
       return DISTDL_OK;
     }
     if (gemm_mfma_usable(blocks, bf16, true, true)) {
       const int ns = gemm_mfma_splits(blocks, bf16, true);
-      if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = ensure_partial(p, gemm_mfma_partial_floats(blocks, ns)))) return rc;
-      if ((rc = launch_gemm_mfma(p->g_fwd.dev, blocks, bf16, true, true, ns, p->d_partial, "affine_fwd_mfma", st_))) return rc;
+      if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = p->partial.get(gemm_mfma_partial_floats(blocks, ns), st_, &partial))) return rc;
+      if ((rc = launch_gemm_mfma(p->g_fwd.dev, blocks, bf16, true, true, ns, partial, "affine_fwd_mfma", st_))) return rc;
       DISTDL_HIP_TRY(hipGetLastError());
       return DISTDL_OK;
     }
@@ -291,6 +281,7 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
   if (!p || !x_dev || !W_dev || !dy_dev || !dx_dev || !dW_dev) return set_error(DISTDL_ERR_NULL, "affine_bwd: null argument");
   const size_t esz = dtype_size(p->dtype);
   hipStream_t st_ = (hipStream_t)stream;
+  float* partial = nullptr;
   int rc;
   if ((rc = check_ptrs(x_dev, p->P_fi, esz, "x")) || (rc = check_ptrs(W_dev, p->P_fo * p->P_fi, esz, "W")) ||
       (rc = check_ptrs(dy_dev, p->P_fo, esz, "dy")) || (rc = check_ptrs((const void* const*)dx_dev, p->P_fi, esz, "dx")) ||
@@ -335,11 +326,11 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       const bool dw_stream = !bf16 && vec && pw.T == 2 && p->n_b <= 32 && gemm_stream_usable(bw, false, false, false);
       if (dw_stream) pw.wgs = 0, pw.nsplit = 1, pw.partial_floats = 0;
       if ((rc = p->g_dx.upload(bx, st_)) || (rc = p->g_dw.upload(bw, st_)) || (db_dev && (rc = p->g_db.upload(bb, st_))) ||
-          (rc = ensure_partial(p, px.partial_floats + pw.partial_floats)))
+          (rc = p->partial.get(px.partial_floats + pw.partial_floats, st_, &partial)))
         return rc;
       const ColsumBlock* cs = db_dev ? p->g_db.dev : nullptr;
       if ((rc = launch_gemm_split_bwd(p->g_dx.dev, bx, px, p->g_dw.dev, bw, pw, cs, p->P_fo, (int)p->max_fo, bf16,
-                                      p->d_partial, st_)))
+                                      partial, st_)))
         return rc;
       if (dw_stream) {
         ProfScope prof("affine_bwd_w_mfma", st_);
@@ -351,7 +342,7 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
     if (gemm_mfma_usable(bx, bf16, true, false) && gemm_mfma_usable(bw, bf16, false, false)) {
       const int nsx = gemm_mfma_splits(bx, bf16, true), nsw = gemm_mfma_splits(bw, bf16, false);
       if ((rc = p->g_dx.upload(bx, st_)) || (rc = p->g_dw.upload(bw, st_)) ||
-          (rc = ensure_partial(p, std::max(gemm_mfma_partial_floats(bx, nsx), gemm_mfma_partial_floats(bw, nsw)))))
+          (rc = p->partial.get(std::max(gemm_mfma_partial_floats(bx, nsx), gemm_mfma_partial_floats(bw, nsw)), st_, &partial)))
         return rc;
       // the two launches use the partial buffer one after the other on the stream
       if (db_dev && (rc = p->g_db.upload(bb, st_))) return rc;
@@ -362,9 +353,9 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       // dx and dW on one stream, one after the other.  Measured: dW on a side stream between a fork and a join event
       // (its 32 KB workgroups fit next to the 128 KB ones of dx) makes the step slower, eager and from a graph
       // (72 against 61 us at 256 x 4096 x 4096): both launches are bound by what a compute unit can take in.
-      rc = launch_gemm_mfma(p->g_dx.dev, bx, bf16, true, false, nsx, p->d_partial, "affine_bwd_x_mfma", st_);
+      rc = launch_gemm_mfma(p->g_dx.dev, bx, bf16, true, false, nsx, partial, "affine_bwd_x_mfma", st_);
       if (!rc)
-        rc = launch_gemm_mfma(p->g_dw.dev, bw, bf16, false, false, nsw, p->d_partial, "affine_bwd_w_mfma", st_,
+        rc = launch_gemm_mfma(p->g_dw.dev, bw, bf16, false, false, nsw, partial, "affine_bwd_w_mfma", st_,
                               db_aligned ? &cs : nullptr);
       if (!rc && db_dev && !cs.done) launch_colsum(p->g_db.dev, p->P_fo, (int)p->max_fo, bf16, st_);
       if (rc) return rc;

@@ -229,6 +229,36 @@ struct DevArray {
   }
 };
 
+// Scratch of a plan's launches: one block per stream, so that calls on two streams may overlap.  A block that is too small
+// for a later call is kept until release(): a recorded graph may hold its address.  (A stream asks for as many sizes as
+// the plan has kinds of call and alignment, so its blocks are few.)
+struct StreamScratch {
+  struct Block {
+    hipStream_t stream;
+    float* dev;
+    size_t floats;
+  };
+  std::vector<Block> blocks;
+  int get(size_t floats, hipStream_t stream, float** out) {
+    *out = nullptr;
+    if (floats == 0) return DISTDL_OK;
+    for (const Block& b : blocks)
+      if (b.stream == stream && b.floats >= floats) {
+        *out = b.dev;
+        return DISTDL_OK;
+      }
+    float* dev = nullptr;
+    DISTDL_HIP_TRY(hipMalloc((void**)&dev, floats * sizeof(float)));
+    blocks.push_back(Block{stream, dev, floats});
+    *out = dev;
+    return DISTDL_OK;
+  }
+  void release() {
+    for (const Block& b : blocks) (void)hipFree(b.dev);
+    blocks.clear();
+  }
+};
+
 }  // namespace distdl
 
 struct distdl_plan {

@@ -966,6 +966,46 @@ def test_conv_weight_scratch_outlives_a_graph():
             assert torch.equal(y, want)
 
 
+@pytest.mark.parametrize("n_b,n_fi,n_fo", [(256, 784, 512), (1000, 1024, 1024)])
+def test_affine_scratch_outlives_a_graph(n_b, n_fi, n_fo):
+    """A forward pass whose K is split, recorded before the first adjoint (whose partial tiles need more room), replays
+    as it was; and the same plan on a second stream has partial tiles of its own."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(4)
+    new = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, 1, 1)
+    x, W, b, dy = new(n_b, n_fi), new(n_fo, n_fi), new(n_fo), new(n_b, n_fo)
+    y, dx, dW, db = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(W), torch.empty_like(b)
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        dd.distdl_affine_fwd(plan, [x], [W], [b], [y])
+        side.synchronize()
+        want, graph = y.clone(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            dd.distdl_affine_fwd(plan, [x], [W], [b], [y])
+        for _ in range(3):
+            dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], [db])
+            # memory that a freed block would have left
+            junk = [torch.full((1 << 18,), float("nan"), device="cuda") for _ in range(8)]
+            y.zero_()
+            graph.replay()
+            side.synchronize()
+            assert torch.equal(y, want)
+            del junk
+    x2, y2 = -x, torch.empty_like(y)
+    torch.cuda.synchronize()
+    for _ in range(20):
+        with torch.cuda.stream(side):
+            graph.replay()
+        with torch.cuda.stream(other):
+            dd.distdl_affine_fwd(plan, [x2], [W], None, [y2])
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
+    err = (y2.double() + x.double() @ W.double().t()).norm() / want.double().norm()
+    assert float(err) < 1e-6
+
+
 # (channels in, out, kernel): gather kernels with 64 and 256 rows, the patch kernels, the weight gradient on split planes
 @pytest.mark.parametrize("c_in,c_out,k,n", [(5, 40, 7, 24), (18, 33, 3, 40), (3, 17, 3, 150), (32, 32, 3, 33), (16, 40, 5, 20), (32, 32, 7, 200)])
 def test_conv_infinities_and_nans_stay_what_fp32_makes_of_them(c_in, c_out, k, n):
