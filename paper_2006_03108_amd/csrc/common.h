@@ -280,11 +280,9 @@ struct distdl_plan {
   distdl::PtrTable tab_x, tab_y, tab_dx, tab_dy;
   int64_t max_out_cells = 0, max_buf_cells = 0;
 
-  // weight re-layout scratch for the convolution kernels (library-owned)
-  float* d_wt = nullptr;
+  distdl::StreamScratch wt;  // weight re-layout scratch of the convolution kernels
+  float* d_wt = nullptr;     // the block of the call at hand (ensure_wscratch)
   distdl::FastDiv* d_pooldiv = nullptr;  // per worker: division by buf[1], buf[2], out[1], out[2] (pooling kernels)
-  size_t wt_elems = 0;
-  std::vector<float*> wt_retired;  // smaller ones that d_wt took the place of
   mutable int maxpool_ok = -1;    // 1 once every max-pool window is known to hold an in-domain cell
   mutable std::shared_ptr<void> corr_split_plan;  // the launches of conv_split.hip, once asked for
   mutable std::shared_ptr<void> corr16_plan;       // the shapes of conv_small.hip's launches, ditto

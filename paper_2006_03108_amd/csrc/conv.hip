@@ -274,7 +274,7 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
 static int prepare_weights(distdl_plan* p, const void* w, hipStream_t st) {
   ConvDev c = conv_params(p);
   size_t n = (size_t)c.taps * c.ci * c.co;
-  if (int rc = ensure_wscratch(p, n)) return rc;
+  if (int rc = ensure_wscratch(p, n, st)) return rc;
   ProfScope prof("conv_relayout_w", st);
   if (p->dtype == DISTDL_BF16)
     hipLaunchKernelGGL(relayout_w_kernel<uint16_t>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,

@@ -758,7 +758,7 @@ int run_corr_any(distdl_plan* p, int mode, const void* w, const void* bias, bool
   const bool few = (pos + 255) / 256 * a.ntn * p->n_workers * a.ncls < 384 && most > kOctPad;
   const int rows = few ? 64 : 256;
   if (few) NT = 1, a.ntn = (a.nc + 31) / 32;
-  if (int rc = ensure_wscratch(p, std::max(weight_floats(p, 0), weight_floats(p, 1)))) return rc;
+  if (int rc = ensure_wscratch(p, std::max(weight_floats(p, 0), weight_floats(p, 1)), st)) return rc;
   a.w = w;
   a.bias = bias;
   a.wt = (const u32x4*)p->d_wt;

@@ -77,7 +77,7 @@ __host__ __device__ inline PerWorker derive(const WorkerDev& wd, const CorrArgs&
 CorrArgs forward_args(const distdl_plan* p);
 CorrArgs class_args(const distdl_plan* p, const int par[3]);
 // Grows the plan's weight re-layout scratch to at least `elems` floats.
-int ensure_wscratch(distdl_plan* p, size_t elems);
+int ensure_wscratch(distdl_plan* p, size_t elems, hipStream_t st);  // p->d_wt
 
 bool corr_mfma_supported(const distdl_plan* p);
 bool wgrad_mfma_supported(const distdl_plan* p);

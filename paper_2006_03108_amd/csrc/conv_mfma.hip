@@ -1422,21 +1422,11 @@ static int launch_corr(distdl_plan* p, CorrArgs a, const void* w, float* wscratc
 
 // Scratch for the re-laid-out weights: forward needs one set, the data
 // gradient one per parity class (used one after the other on the stream).
-int ensure_wscratch(distdl_plan* p, size_t elems) {
-  if (p->wt_elems >= elems) return DISTDL_OK;
-  float* grown = nullptr;
-  DISTDL_HIP_TRY(hipMalloc((void**)&grown, elems * sizeof(float)));
-  // A block that is too small goes with the plan: a recorded graph may hold its address.  There is one size per
-  // direction, type of kernel and alignment, so they are few.
-  if (p->d_wt) p->wt_retired.push_back(p->d_wt);
-  p->d_wt = grown;
-  p->wt_elems = elems;
-  return DISTDL_OK;
-}
+int ensure_wscratch(distdl_plan* p, size_t elems, hipStream_t st) { return p->wt.get(elems, st, &p->d_wt); }
 
 int conv_fwd_mfma(distdl_plan* p, const void* w, const void* bias, hipStream_t st) {
   CorrArgs a = forward_args(p);
-  int rc = ensure_wscratch(p, std::max(corr_scratch_elems(a), bwd_scratch_elems(p)));
+  int rc = ensure_wscratch(p, std::max(corr_scratch_elems(a), bwd_scratch_elems(p)), st);
   if (rc) return rc;
   return launch_corr(p, a, w, p->d_wt, bias, p->tab_x.dev, p->tab_y.dev, "conv_fwd_mfma", st);
 }
@@ -1455,7 +1445,7 @@ size_t bwd_scratch_elems(const distdl_plan* p) {
 
 int conv_bwd_data_mfma(distdl_plan* p, const void* w, hipStream_t st) {
   CorrArgs fa = forward_args(p);
-  int rc = ensure_wscratch(p, std::max(corr_scratch_elems(fa), bwd_scratch_elems(p)));
+  int rc = ensure_wscratch(p, std::max(corr_scratch_elems(fa), bwd_scratch_elems(p)), st);
   if (rc) return rc;
   size_t at = 0;
   for (int p0 = 0; p0 < p->stride[0]; ++p0)

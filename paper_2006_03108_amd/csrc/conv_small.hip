@@ -930,14 +930,14 @@ static size_t corr16_scratch_total(const distdl_plan* p) {
 }
 
 int conv_fwd16(distdl_plan* p, const float* w, const float* bias, bool vec, hipStream_t st) {
-  int rc = ensure_wscratch(p, corr16_scratch_total(p));
+  int rc = ensure_wscratch(p, corr16_scratch_total(p), st);
   if (rc) return rc;
   return launch_corr16(p, 0, forward_args(p), vec && p->n_ci % 4 == 0, w, p->d_wt, bias, p->tab_x.dev, p->tab_y.dev,
                        "conv_fwd_mfma16", st);
 }
 
 int conv_bwd_data16(distdl_plan* p, const float* w, bool vec, hipStream_t st) {
-  int rc = ensure_wscratch(p, corr16_scratch_total(p));
+  int rc = ensure_wscratch(p, corr16_scratch_total(p), st);
   if (rc) return rc;
   size_t at = 0;
   for (int p0 = 0; p0 < p->stride[0]; ++p0)

@@ -622,7 +622,7 @@ int run_split(distdl_plan* p, int dir, const float* w, const float* bias, void**
   }
   const Launches& d = sp.dir[dir];
   const int first = dir == 0 ? 0 : (int)sp.dir[0].v.size();
-  if (int rc = ensure_wscratch(p, (size_t)std::max(sp.dir[0].pieces, sp.dir[1].pieces) * 4)) return rc;
+  if (int rc = ensure_wscratch(p, (size_t)std::max(sp.dir[0].pieces, sp.dir[1].pieces) * 4, st)) return rc;
   u32x4* const wt = (u32x4*)p->d_wt;
   int64_t most = 0;
   for (const Launch& l : d.v) most = std::max(most, l.pieces / 3);  // threads: three pieces each

@@ -966,6 +966,30 @@ def test_conv_weight_scratch_outlives_a_graph():
             assert torch.equal(y, want)
 
 
+def test_conv_passes_of_one_plan_on_two_streams():
+    """Forward passes on one stream and backward passes with other weights on another: each has weight scratch of its own."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(8)
+    new = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    plan = dd.distdl_plan_create(2, 4, 32, 32, (96, 96), (1, 1), (3, 3), (1, 1), (1, 1), (1, 1))
+    x, w, w2, dy = new(4, 98, 98, 32), new(32, 32, 3, 3), new(32, 32, 3, 3), new(4, 96, 96, 32)
+    x2, y, dx, dw = x.clone(), torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w)
+    ws = torch.empty(max(dd.distdl_conv_bwd_workspace(plan), 16), dtype=torch.uint8, device="cuda")
+    fwd = lambda: dd.distdl_conv_fwd(plan, [x], w, None, [y])
+    bwd = lambda: dd.distdl_conv_bwd(plan, [x2], w2, [dy], [dx], dw, None, ws)
+    fwd(), bwd()
+    torch.cuda.synchronize()
+    want = y.clone(), dx.clone(), dw.clone()
+    one, other = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(30):
+        with torch.cuda.stream(one):
+            fwd()
+        with torch.cuda.stream(other):
+            bwd()
+    torch.cuda.synchronize()
+    assert torch.equal(y, want[0]) and torch.equal(dx, want[1]) and torch.equal(dw, want[2])
+
+
 @pytest.mark.parametrize("n_b,n_fi,n_fo", [(256, 784, 512), (1000, 1024, 1024)])
 def test_affine_scratch_outlives_a_graph(n_b, n_fi, n_fo):
     """A forward pass whose K is split, recorded before the first adjoint (whose partial tiles need more room), replays
