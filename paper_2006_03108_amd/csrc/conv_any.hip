@@ -22,6 +22,7 @@
 // Offsets that the lanes share are computed by the lanes, one each, and read out with v_readlane.
 // fp32: the hi * hi products have an accumulator of their own, see gemm_split.hip.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "conv_any.h"
@@ -112,7 +113,10 @@ __host__ __device__ inline void class_taps(int k, int s, int dil, int par, int& 
   while (tf < ts && (tf * dil) % s != par) ++tf;
   nt = tf < ts && tf < k ? (k - 1 - tf) / ts + 1 : 0;
 }
-__device__ inline DimAny dim_any(const WorkerDev& wd, const AnyArgs& a, int d, int par) {
+// (d is a template argument: indexed at run time the geometry would lie in scratch memory, and what is read from there counts
+// as different in every lane, the buffers' descriptors too)
+template <int d>
+__device__ __forceinline__ DimAny dim_any(const WorkerDev& wd, const AnyArgs& a, int par) {
   DimAny g;
   if (a.mode == 0) {
     g.nt = a.k[d], g.tf = 0, g.ts = 1;
@@ -137,7 +141,8 @@ constexpr uint32_t a_pitch(int ROWS, bool bf16) { return planes_of(bf16) * ROWS 
 constexpr uint32_t b_pitch(int NT, bool bf16) { return planes_of(bf16) * 32 * NT * 16 + 16; }
 constexpr int any_lds(int ROWS, int NT, bool bf16) {
   const int stage = octets_of(ROWS) * (int)(a_pitch(ROWS, bf16) + b_pitch(NT, bf16));
-  return std::max(stage, ROWS == 64 ? 4 * 64 * 32 * NT * 4 : 0) + ROWS * 4;  // (64 rows: four partial tiles at the end)
+  // (64 rows: four partial tiles at the end); the outputs of the rows, the word that asks for fp32 products
+  return std::max(stage, ROWS == 64 ? 4 * 64 * 32 * NT * 4 : 0) + ROWS * 4 + 16;
 }
 constexpr int kOctPad = 16;  // a class's weights are padded to whole stages of either kind
 
@@ -149,17 +154,22 @@ __device__ inline int div_by(int n, int d, float rcp) {
   return q;
 }
 
-// eight values -> the operand pieces of one (octet, row)
-template <bool BF16>
+// eight values -> the operand pieces of one (octet, row); RAW: as they are, for fp32 MFMAs
+template <bool BF16, bool RAW = false>
 __device__ inline void put_octet(char* at, uint32_t plane, const float (&v)[8]) {
   if constexpr (BF16) {
     u32x4 h;
 #pragma unroll
     for (int j = 0; j < 4; ++j) h[j] = pack_bf16(v[2 * j], v[2 * j + 1]);  // exact
     *(u32x4*)at = h;
+  } else if constexpr (RAW) {
+    u32x4 u, w;
+    halve_eight(v, u, w);
+    *(u32x4*)at = u;
+    *(u32x4*)(at + plane) = w;
   } else {
     u32x4 h, m, l;
-    split_eight(v, h, m, l);
+    split_eight(v, kSplitScale, h, m, l);
     *(u32x4*)at = h;
     *(u32x4*)(at + plane) = m;
     *(u32x4*)(at + 2 * plane) = l;
@@ -204,27 +214,83 @@ __device__ inline void multiply_stage(floatx16 (&acc)[2][NT], floatx16 (&low)[2]
     mm(acc, 0, 0);
   }
 }
+template <int ROWS, int NT>
+__device__ inline void multiply_stage_halves(floatx16 (&acc)[2][NT], const char* la, const char* lb, int lane) {
+  const int h = lane >> 5, ml = lane & 31;
+#pragma unroll
+  for (int sl = 0; sl < 2; ++sl) {
+    Eight a[2], b[NT];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const char* const at = la + (2 * sl + h) * a_pitch(ROWS, false) + (32 * t + ml) * 16;
+      a[t] = join_halves(*(const u32x4*)at, *(const u32x4*)(at + ROWS * 16));
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const char* const at = lb + (2 * sl + h) * b_pitch(NT, false) + (32 * t + ml) * 16;
+      b[t] = join_halves(*(const u32x4*)at, *(const u32x4*)(at + 32 * NT * 16));
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = multiply_fp32(a[i], b[j], acc[i][j]);
+  }
+}
 template <int NT, bool BF16>
 struct Sums {
   floatx16 acc[2][NT], low[2][NT];
-  __device__ inline Sums() {
+  __device__ inline void zero() {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < NT; ++j)
         for (int e = 0; e < 16; ++e) acc[i][j][e] = low[i][j][e] = 0.f;
   }
-  __device__ inline void finish() {
-    if constexpr (!BF16) {
+  // the sums of split operands; false if one of them is not finite
+  __device__ inline bool finish() {
+    float seen = 0.f;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] += low[i][j];
-    }
+      for (int j = 0; j < NT; ++j) {
+        acc[i][j] += low[i][j];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) seen = note_not_finite(acc[i][j][e] *= kUnsplit, seen);
+      }
+    return !any_not_finite(seen);
   }
 };
 
-// output element (position, channel) once more, term by term in fp32
+// octet `oct` of output channel ch of a class: the weights, or zero beyond the channels and taps
+template <bool BF16, bool FLAT>
+__device__ inline void weight_octet(const AnyArgs& a, const int (&nt)[3], const int (&tf)[3], const int (&ts)[3], int oct, int ch,
+                                    float (&v)[8]) {
+  const int ntaps = nt[0] * nt[1] * nt[2], noct = (a.kc + 7) / 8;
+  bool ok[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    int tap, c;
+    if (FLAT) {
+      const int k = oct * 8 + e;
+      tap = k / a.kc, c = k - tap * a.kc;
+    } else {
+      tap = oct / noct, c = (oct - tap * noct) * 8 + e;
+    }
+    ok[e] = tap < ntaps && c < a.kc && ch < a.nc;
+    const int i2 = tap % nt[2], i01 = tap / nt[2], i1 = i01 % nt[1], i0 = i01 / nt[1];
+    const int t = ((tf[0] + i0 * ts[0]) * a.k[1] + tf[1] + i1 * ts[1]) * a.k[2] + tf[2] + i2 * ts[2];
+    const int oc = a.mode == 0 ? ch : c, ic = a.mode == 0 ? c : ch;
+    v[e] = ld((const typename Elem<BF16>::T*)a.w, ok[e] ? ((size_t)oc * a.ci + ic) * a.taps + t : (size_t)0);
+  }
+  // (loaded in any case and all at once: left alone the compiler makes a branch, and a wait, of each)
+#pragma unroll
+  for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(v[e]));
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = ok[e] ? v[e] : 0.f;
+}
+
+// Data gradient, output element (position, channel) term by term: only those taps whose output exists (in the product of a
+// tile the others are zeros, which do not cancel a weight that is not finite).  A NaN ends it.
 __device__ inline float corr_direct(const AnyArgs& a, const DimAny& g0, const DimAny& g1, const DimAny& g2, const float* in, int q0,
                                    int q1, int q2, int n, int ch) {
   float sum = 0.f;
@@ -236,10 +302,8 @@ __device__ inline float corr_direct(const AnyArgs& a, const DimAny& g0, const Di
         if (c0 < 0 || c0 >= g0.in_ext || c1 < 0 || c1 >= g1.in_ext || c2 < 0 || c2 >= g2.in_ext) continue;
         const int tap = ((g0.tf + i0 * g0.ts) * a.k[1] + g1.tf + i1 * g1.ts) * a.k[2] + g2.tf + i2 * g2.ts;
         const float* x = in + ((((size_t)n * g0.in_ext + c0) * g1.in_ext + c1) * g2.in_ext + c2) * a.kc;
-        for (int c = 0; c < a.kc; ++c) {
-          const int o = a.mode == 0 ? ch : c, i = a.mode == 0 ? c : ch;
-          sum = fmaf(x[c], ((const float*)a.w)[((size_t)o * a.ci + i) * a.taps + tap], sum);
-        }
+        for (int c = 0; c < a.kc; ++c) sum = fmaf(x[c], ((const float*)a.w)[((size_t)c * a.ci + ch) * a.taps + tap], sum);
+        if (sum != sum) return sum;
       }
   return sum;
 }
@@ -259,8 +323,8 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
   const WorkerDev wd = workers[worker];
   const int cls = (int)blockIdx.y;
   const int c12 = a.s[1] * a.s[2];
-  const DimAny g0 = dim_any(wd, a, 0, MODE == 0 ? 0 : cls / c12), g1 = dim_any(wd, a, 1, MODE == 0 ? 0 : cls / a.s[2] % a.s[1]),
-               g2 = dim_any(wd, a, 2, MODE == 0 ? 0 : cls % a.s[2]);
+  const DimAny g0 = dim_any<0>(wd, a, MODE == 0 ? 0 : cls / c12), g1 = dim_any<1>(wd, a, MODE == 0 ? 0 : cls / a.s[2] % a.s[1]),
+               g2 = dim_any<2>(wd, a, MODE == 0 ? 0 : cls % a.s[2]);
   const int ntile = tile % a.ntn;
   tile /= a.ntn;
   const int64_t total = (int64_t)a.n_b * g0.nq * g1.nq * g2.nq;
@@ -301,7 +365,7 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
   }
   char* const la = smem;
   char* const lb = smem + KS * a_pitch(ROWS, BF16);
-  uint32_t* const row_out = (uint32_t*)(smem + any_lds(ROWS, NT, BF16) - ROWS * 4);  // byte offset of a row's outputs
+  uint32_t* const row_out = (uint32_t*)(smem + any_lds(ROWS, NT, BF16) - ROWS * 4 - 16);  // byte offset of a row's outputs
   if (tid < ROWS) {
     int n, q0, q1, q2;
     row_out[tid] = position(tid, n, q0, q1, q2)
@@ -326,7 +390,7 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
   float v[4][8];
   constexpr int BP = KS * PL * 32 * NT, BPT = (BP + 255) / 256;  // weight pieces of a stage
   u32x4 wp[BPT];
-  auto load_stage = [&](int st) {
+  auto load_stage = [&](int st, bool weights) {
     if constexpr (VEC) {
       // two groups of four channels, each within one tap
 #pragma unroll
@@ -375,18 +439,22 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
           v[o][e] = load1<BF16>(rin, ok ? vo + e * ES : kOob, c0 + e < a.kc ? 0u : kOob);
       }
     }
+    if (!weights) return;
 #pragma unroll
     for (int i = 0; i < BPT; ++i) {
       const int piece = tid + i * 256;
       wp[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, piece < BP ? piece * 16u : kOob, (uint32_t)st * (BP * 16u), 0);
     }
   };
-  auto write_stage = [&]() {
+  auto write_octets = [&](auto raw) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int oct = VEC ? tid % KS : tid / ROWS + (256 / ROWS) * i, row = VEC ? tid / KS + i * (256 / KS) : tid % ROWS;
-      put_octet<BF16>(la + oct * a_pitch(ROWS, BF16) + row * 16, ROWS * 16, v[i]);
+      put_octet<BF16, decltype(raw)::value>(la + oct * a_pitch(ROWS, BF16) + row * 16, ROWS * 16, v[i]);
     }
+  };
+  auto write_stage = [&]() {
+    write_octets(std::false_type{});
 #pragma unroll
     for (int i = 0; i < BPT; ++i) {
       const int piece = tid + i * 256;  // [octet][plane][column]
@@ -397,31 +465,61 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
   Sums<NT, BF16> sums;
   const char* const wa = la + (ROWS == 256 ? wave * 64 * 16 : wave * 4 * a_pitch(ROWS, BF16));
   const char* const wb = lb + (ROWS == 256 ? 0 : wave * 4 * b_pitch(NT, BF16));
-  if (stages > 0) load_stage(0);
+  // set if a sum of the tile is not finite; if a weight is not
+  int* const redo = (int*)(smem + any_lds(ROWS, NT, BF16) - 16);
+  if (!BF16 && tid == 0) redo[0] = redo[1] = 0;
+  sums.zero();
+  if (stages > 0) load_stage(0, true);
   for (int st = 0; st < stages; ++st) {
     write_stage();
     __syncthreads();
-    if (st + 1 < stages) load_stage(st + 1);  // in flight while this stage multiplies
+    if (st + 1 < stages) load_stage(st + 1, true);  // in flight while this stage multiplies
     multiply_stage<ROWS, NT, BF16>(sums.acc, sums.low, wa, wb, lane);
+    if constexpr (!BF16) {
+      if (st + 1 == stages && !sums.finish()) *redo = 1;
+    }
     __syncthreads();
   }
   if (stages == 0) __syncthreads();  // row_out
-  sums.finish();
+  if constexpr (!BF16) {
+    if (stages > 0 && __builtin_amdgcn_readfirstlane(*redo)) {  // (uniform, rare) the tile once more in fp32, its weights from the caller's
+      const int nt3[3] = {g0.nt, g1.nt, g2.nt}, tf3[3] = {g0.tf, g1.tf, g2.tf}, ts3[3] = {g0.ts, g1.ts, g2.ts};
+      sums.zero();
+#pragma unroll 1
+      for (int st = 0; st < stages; ++st) {
+        load_stage(st, false);
+        write_octets(std::true_type{});
+#pragma unroll 1
+        for (int piece = tid; piece < KS * 32 * NT; piece += 256) {  // [octet][column]
+          const int col = piece % (32 * NT), oct = piece / (32 * NT);
+          float wv[8];
+          weight_octet<BF16, FLAT>(a, nt3, tf3, ts3, st * KS + oct, ntile * 32 * NT + col, wv);
+          put_octet<BF16, true>(lb + oct * b_pitch(NT, BF16) + col * 16, 32 * NT * 16, wv);
+          if constexpr (MODE == 1) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (not_finite(wv[e])) redo[1] = 1;
+          }
+        }
+        __syncthreads();
+        multiply_stage_halves<ROWS, NT>(sums.acc, wa, wb, lane);
+        __syncthreads();
+      }
+    }
+  }
 
-  bool bad = false;
   auto store = [&](int row, int ch, float bias, float s) {
     const uint32_t ro = row_out[row];
-    bad |= not_finite(s) && ro != kOob && ch < a.nc;
     const uint32_t off = ch < a.nc ? ro + (uint32_t)ch * ES : kOob;
     if constexpr (BF16) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)pack_bf16(s + bias, 0.f), rout, off, 0, 0);
     else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s + bias), rout, off, 0, 0);
   };
-  // the sum term by term in fp32, where the split's is not finite (rare)
+  bool terms = false;  // the tile has weights that are not finite
+  if constexpr (!BF16 && MODE == 1) terms = __builtin_amdgcn_readfirstlane(redo[1]) != 0;
   auto again = [&](int row, int ch) {
     int n, q0, q1, q2;
-    if (ch >= a.nc || !position(row, n, q0, q1, q2)) return;
-    const float s = corr_direct(a, g0, g1, g2, (const float*)in_bufs[worker], q0, q1, q2, n, ch) + (a.bias ? ((const float*)a.bias)[ch] : 0.f);
-    ((float*)out_bufs[worker])[row_out[row] / 4 + ch] = s;
+    if (ch < a.nc && position(row, n, q0, q1, q2))
+      ((float*)out_bufs[worker])[row_out[row] / 4 + ch] = corr_direct(a, g0, g1, g2, (const float*)in_bufs[worker], q0, q1, q2, n, ch);
   };
   auto bias_of = [&](int ch) { return a.bias && ch < a.nc ? ld((const typename Elem<BF16>::T*)a.bias, ch) : 0.f; };
   const int ch0 = ntile * 32 * NT;
@@ -436,12 +534,16 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
         for (int e = 0; e < 16; ++e)
           store(wave * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4), ch0 + 32 * j + ml, bias, sums.acc[i][j][e]);
     }
-    if constexpr (!BF16) {
-      if (bad)
-        for (int t = 0; t < 32 * NT; ++t) {
-          const int e = (t >> 1) & 15;
+    if constexpr (!BF16 && MODE == 1) {
+      if (terms) {
+        uint64_t which = 0;
+#pragma unroll
+        for (int t = 0; t < 32 * NT; ++t) which |= (uint64_t)not_finite(sums.acc[t & 1][t >> 5][(t >> 1) & 15]) << t;
+        for (; which; which &= which - 1) {
+          const int t = __ffsll((unsigned long long)which) - 1, e = (t >> 1) & 15;
           again(wave * 64 + 32 * (t & 1) + 8 * (e >> 2) + 4 * h + (e & 3), ch0 + 32 * (t >> 5) + ml);
         }
+      }
     }
   } else {
     float* const red = (float*)smem;  // [wave][row][column]; the last barrier above came after the last read of a stage
@@ -460,11 +562,11 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
     for (int t = 0; t < 64 * NB / 256; ++t) {
       const int row = tid / NB + t * (256 / NB);
       const float* p = red + row * NB + col;
-      store(row, ch0 + col, bias, ((p[0] + p[64 * NB]) + p[2 * 64 * NB]) + p[3 * 64 * NB]);
-    }
-    if constexpr (!BF16) {
-      if (bad)
-        for (int t = 0; t < 64 * NB / 256; ++t) again(tid / NB + t * (256 / NB), ch0 + col);
+      const float s = ((p[0] + p[64 * NB]) + p[2 * 64 * NB]) + p[3 * 64 * NB];
+      store(row, ch0 + col, bias, s);
+      if constexpr (!BF16 && MODE == 1) {
+        if (terms && not_finite(s)) again(row, ch0 + col);
+      }
     }
   }
 }
@@ -487,25 +589,8 @@ __global__ __launch_bounds__(256) void corr_any_weights_kernel(AnyArgs a, u32x4*
   const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
   if (idx >= a.ntn * octs * 32 * NT) return;
   const int col = idx % (32 * NT), r = idx / (32 * NT), oct = r % octs, ntile = r / octs;
-  const int ch = ntile * 32 * NT + col;
   float v[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    int tap, c;
-    if (FLAT) {
-      const int k = oct * 8 + e;
-      tap = k / a.kc, c = k - tap * a.kc;
-    } else {
-      tap = oct / noct, c = (oct - tap * noct) * 8 + e;
-    }
-    v[e] = 0.f;
-    if (tap < ntaps && c < a.kc && ch < a.nc) {
-      const int i2 = tap % nt[2], i01 = tap / nt[2], i1 = i01 % nt[1], i0 = i01 / nt[1];
-      const int t = ((tf[0] + i0 * ts[0]) * a.k[1] + tf[1] + i1 * ts[1]) * a.k[2] + tf[2] + i2 * ts[2];
-      const int oc = a.mode == 0 ? ch : c, ic = a.mode == 0 ? c : ch;
-      v[e] = ld((const typename Elem<BF16>::T*)a.w, ((size_t)oc * a.ci + ic) * a.taps + t);
-    }
-  }
+  weight_octet<BF16, FLAT>(a, nt, tf, ts, oct, ntile * 32 * NT + col, v);
   u32x4* const at = dst + ((size_t)a.woff[cls] * a.ntn + (size_t)ntile * octs + oct) * (PL * 32 * NT) + col;
   put_octet<BF16>((char*)at, 32 * NT * 16, v);
 }
@@ -574,29 +659,47 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
   float bsum[YO];
 #pragma unroll
   for (int i = 0; i < YO; ++i) bsum[i] = 0.f;
-  auto write_stage = [&]() {
+  auto write_stage = [&](auto raw) {
+    constexpr bool RAW = decltype(raw)::value;
 #pragma unroll
-    for (int o = 0; o < kKp; ++o) put_octet<BF16>(la + o * a_pitch(kRows, BF16) + tid * 16, kRows * 16, v[o]);
+    for (int o = 0; o < kKp; ++o) put_octet<BF16, RAW>(la + o * a_pitch(kRows, BF16) + tid * 16, kRows * 16, v[o]);
 #pragma unroll
     for (int i = 0; i < YO; ++i) {
       const int u = tid + i * 256;
-      if (u < kKp * NB) put_octet<BF16>(lb + (u / NB) * b_pitch(NT, BF16) + u % NB * 16, NB * 16, y[i]);
-      if (bias_wg)
+      if (u < kKp * NB) put_octet<BF16, RAW>(lb + (u / NB) * b_pitch(NT, BF16) + u % NB * 16, NB * 16, y[i]);
+      if (bias_wg && !RAW)
         bsum[i] += ((y[i][0] + y[i][1]) + (y[i][2] + y[i][3])) + ((y[i][4] + y[i][5]) + (y[i][6] + y[i][7]));
     }
   };
   Sums<NT, BF16> sums;
+  int* const redo = (int*)(smem + any_lds(kRows, NT, BF16) - 16);  // set if a sum of the tile is not finite
+  if (!BF16 && tid == 0) *redo = 0;
+  sums.zero();
   if (s_begin < s_end) load_stage(s_begin);
   for (int st = s_begin; st < s_end; ++st) {
-    write_stage();
+    write_stage(std::false_type{});
     __syncthreads();
     if (st + 1 < s_end) load_stage(st + 1);
     multiply_stage<kRows, NT, BF16>(sums.acc, sums.low, la + wave * 64 * 16, lb, lane);
+    if constexpr (!BF16) {
+      if (st + 1 == s_end && !sums.finish()) *redo = 1;
+    }
     __syncthreads();
   }
-  sums.finish();
+  if constexpr (!BF16) {
+    if (s_begin < s_end && __builtin_amdgcn_readfirstlane(*redo)) {  // (uniform, rare) the tile once more in fp32
+      sums.zero();
+#pragma unroll 1
+      for (int st = s_begin; st < s_end; ++st) {
+        load_stage(st);
+        write_stage(std::true_type{});
+        __syncthreads();
+        multiply_stage_halves<kRows, NT>(sums.acc, la + wave * 64 * 16, lb, lane);
+        __syncthreads();
+      }
+    }
+  }
   float* const slot = partial + ((size_t)worker * a.nchunks + chunk) * a.slot;
-  bool bad = false;
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int ch = ntile * NB + 32 * j + ml;
@@ -605,32 +708,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int k = mt * kRows + wave * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4);
-        if (k < a.rows && ch < a.co) {
-          bad |= not_finite(sums.acc[i][j][e]);
-          slot[(size_t)k * a.co + ch] = sums.acc[i][j][e];
-        }
-      }
-  }
-  if constexpr (!BF16) {
-    if (bad)  // rare: this lane's sums term by term
-      for (int t = 0; t < 32 * NT; ++t) {
-        const int k = mt * kRows + wave * 64 + 32 * (t & 1) + 8 * ((t >> 1) >> 2 & 3) + 4 * h + (t >> 1 & 3);
-        const int ch = ntile * NB + 32 * (t >> 5) + ml;
-        if (k >= a.rows || ch >= a.co) continue;
-        const int tap = k / a.ci, c = k - tap * a.ci;
-        const int t2 = tap % a.k[2], t01 = tap / a.k[2], t1 = t01 % a.k[1], t0 = t01 / a.k[1];
-        float sum = 0.f;
-        for (int p = s_begin * 32; p < min(npos, s_end * 32); ++p) {
-          int u = p;
-          const int o2 = u % wd.out[2]; u /= wd.out[2];
-          const int o1 = u % wd.out[1]; u /= wd.out[1];
-          const int o0 = u % wd.out[0], n = u / wd.out[0];
-          const size_t at = (size_t)n * sxn + (size_t)(wd.origin[0] + o0 * a.s[0] + t0 * a.dil[0]) * sx0 +
-                            (size_t)(wd.origin[1] + o1 * a.s[1] + t1 * a.dil[1]) * sx1 +
-                            (size_t)(wd.origin[2] + o2 * a.s[2] + t2 * a.dil[2]) * a.ci + c;
-          sum = fmaf(((const float*)dy_bufs[worker])[(size_t)p * a.co + ch], ((const float*)x_bufs[worker])[at], sum);
-        }
-        slot[(size_t)k * a.co + ch] = sum;
+        if (k < a.rows && ch < a.co) slot[(size_t)k * a.co + ch] = sums.acc[i][j][e];
       }
   }
   if (bias_wg) {  // the octets of a column, in order

@@ -70,28 +70,23 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) 
 // cycles), and a half-wave writes one half of 32 cells.
 constexpr uint32_t half_bytes(int PA) { return PA * 2048; }
 constexpr uint32_t plane_bytes(int PA) { return 2 * half_bytes(PA); }
-constexpr int split_lds_bytes(int PA, int taps) { return 3 * plane_bytes(PA) + taps * 3072; }
+constexpr int split_lds_bytes(int PA, int taps) { return 3 * plane_bytes(PA) + taps * 3072 + 16; }
 
-// output (position q, channel ch) term by term in fp32
+// eight channels of a weight piece: k = 16 cc + 8 h ... of channel ch, tap `tap` (in group order) of kernel plane t0
 template <class ArgsPtr>
-__device__ inline float split_direct(ArgsPtr a, const float* w, const PerWorker& g, const float* in, int n, int q0, int q1,
-                                     int q2, int ch) {
+__device__ inline void weight_octet(ArgsPtr a, const float* __restrict__ w, int t0, int cc, int tap, int h, int ch, float (&v)[8]) {
   const auto& c = a->c;
-  float sum = 0.f;
-  for (int t0 = 0; t0 < c.nt[0]; ++t0)
-    for (int t1 = 0; t1 < c.nt[1]; ++t1)
-      for (int t2 = 0; t2 < c.nt[2]; ++t2) {
-        const int i0 = g.in_base[0] + q0 * c.is[0] + c.tapoff[0][t0], i1 = g.in_base[1] + q1 * c.is[1] + c.tapoff[1][t1],
-                  i2 = g.in_base[2] + q2 * c.is[2] + c.tapoff[2][t2];
-        if (i0 < 0 || i0 >= g.in_ext[0] || i1 < 0 || i1 >= g.in_ext[1] || i2 < 0 || i2 >= g.in_ext[2]) continue;
-        const int tap = (c.tapid[0][t0] * a->k1 + c.tapid[1][t1]) * a->k2 + c.tapid[2][t2];
-        const float* x = in + ((((size_t)n * g.in_ext[0] + i0) * g.in_ext[1] + i1) * g.in_ext[2] + i2) * c.kc;
-        for (int k = 0; k < c.kc; ++k) {
-          const int o = c.mode == 0 ? ch : k, i = c.mode == 0 ? k : ch;
-          sum = fmaf(x[k], w[((size_t)o * a->ci + i) * a->taps + tap], sum);
-        }
-      }
-  return sum;
+  const int ft = (c.tapid[0][t0] * a->k1 + c.tapid[1][a->tap12[tap][0]]) * a->k2 + c.tapid[2][a->tap12[tap][1]];
+  const int k0 = cc * 16 + h * 8, left = ch < c.nc ? c.kc - k0 : 0;
+  const size_t per_k = c.mode == 0 ? (size_t)a->taps : (size_t)a->ci * a->taps;
+  const float* const at = w + (left <= 0 ? (size_t)0 : c.mode == 0 ? ((size_t)ch * a->ci + k0) * a->taps + ft : ((size_t)k0 * a->ci + ch) * a->taps + ft);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = at[e < left ? e * per_k : (size_t)0];
+  // (loaded in any case and all at once: left alone the compiler makes a branch, and a wait, of each)
+#pragma unroll
+  for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(v[e]));
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = e < left ? v[e] : 0.f;
 }
 
 // MT: 32-position M-tiles per wave; PA: pairs of 16-byte pieces (8 channels of a cell) per thread and stage; PB: weight
@@ -157,11 +152,6 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
     if (wr >= c.tr) wr = 0, wc = 0;  // idle position: multiplies something in range, never stored
     abase[mt] = (uint32_t)h * HB + (uint32_t)(wr * c.Cw + wc) * 16u;
   }
-  float bias[4][4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bias[q][e] = (bias_in && ch0 + 8 * q + e < c.nc) ? bias_in[ch0 + 8 * q + e] : 0.f;
   const uint32_t wread = (uint32_t)(h * 32 + m) * 16u;
 
   // stage order: output planes dealt to the groups in turn, kernel planes rotated so that neighbouring groups stand on
@@ -203,7 +193,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
   u32x4 ra[PA][2], rb[PB];
   const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
   uint32_t wpieces = 0;  // weight pieces of the stage in the registers
-  auto load_stage = [&](const StagePos& sp) {
+  auto load_cells = [&](const StagePos& sp) {
     const int b1 = a->gbase[sp.gr][0], b2 = a->gbase[sp.gr][1];
     const uint32_t shift = (uint32_t)(b1 * si1 + b2 * si2) * 4u;
     const uint32_t sbase = ((uint32_t)sp.n * sin + (uint32_t)plane_of(sp.q0, sp.t0) * si0 + sp.cc * 16) * 4u;
@@ -215,6 +205,9 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
       ra[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rin, ok && left > 0 ? vo : kOob, sbase, 0);
       ra[i][1] = __builtin_amdgcn_raw_buffer_load_b128(rin, ok && left > 4 ? vo + 16u : kOob, sbase, 0);
     }
+  };
+  auto load_stage = [&](const StagePos& sp) {
+    load_cells(sp);
     const int tb = a->gbegin[sp.gr];
     const uint32_t np = (uint32_t)(a->gbegin[sp.gr + 1] - tb) * 192u;
     const uint32_t wbase = ((uint32_t)(sp.t0 * ncc + sp.cc) * wplane + (uint32_t)tb * 192u) * 16u;
@@ -223,14 +216,14 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
       if (i * 256 + wave_u * 64 < np) rb[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, tid * 16u, wbase + i * 4096u, 0);
     wpieces = np;
   };
-  auto write_stage = [&]() {
+  auto write_stage = [&](float scale) {
 #pragma unroll
     for (int i = 0; i < PA; ++i) {
       float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(ra[i][e >> 2][e & 3]);
       u32x4 hi, mid, lo;
-      split_eight(v, hi, mid, lo);
+      split_eight(v, scale, hi, mid, lo);
       char* const at = smem + pl0 + i * 2048;
       *(u32x4*)at = hi;
       *(u32x4*)(at + PS) = mid;
@@ -299,8 +292,12 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
   advance(sp);
   int on = pfirst / nq0, oq0 = pfirst % nq0;  // the output plane that is stored next
   auto store_plane = [&]() {
+    float bias[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias[q][e] = (bias_in && ch0 + 8 * q + e < c.nc) ? bias_in[ch0 + 8 * q + e] : 0.f;
     const uint32_t obase = ((uint32_t)on * son + (uint32_t)(g.out_base[0] + g.os[0] * oq0) * so0) * 4u;
-    bool bad = false;
     // (the plane's offset is added into the per-lane offset: with a scalar offset the compiler leaves out the wait states
     // a 16-byte store needs before its data registers are written again)
     if (c.nc & 3) {  // (uniform) quads need not be whole, nor aligned
@@ -310,7 +307,6 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
         for (int v = 0; v < 16; ++v) {
           const int e = 8 * (v >> 2) + (v & 3);
           const bool live = ch0 + e < c.nc;
-          bad |= live && not_finite(acc[mt][v]);
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[mt][v] + bias[v >> 2][v & 3]), rout,
                                                 (live ? soff[mt] + (uint32_t)e * 4u : kOob) + obase, 0, 0);
         }
@@ -324,34 +320,120 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
         u32x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          bad |= live && not_finite(acc[mt][4 * q + e]);
           o[e] = __float_as_uint(acc[mt][4 * q + e] + bias[q][e]);
         }
         __builtin_amdgcn_raw_buffer_store_b128(o, rout, off, 0, 0);
       }
-    if (bad)  // rare: this lane's sums term by term in fp32
-      for (int t = 0; t < MT * 16; ++t) {
-        const int pidx = (wave * MT + (t >> 4)) * 32 + m, wr = pidx / c.tc, wc = pidx - wr * c.tc;
-        const int q1 = q1_0 + wr, q2 = q2_0 + wc, ch = ch0 + 8 * ((t >> 2) & 3) + (t & 3);
-        if (wr >= c.tr || q1 >= g.nq[1] || q2 >= g.nq[2] || ch >= c.nc) continue;
-        const float s = split_direct(a, w, g, (const float*)in_bufs[worker], on, oq0, q1, q2, ch) + (bias_in ? bias_in[ch] : 0.f);
-        ((float*)out_bufs[worker])[(size_t)on * son + (size_t)(g.out_base[0] + g.os[0] * oq0) * so0 +
-                                   (size_t)(g.out_base[1] + g.os[1] * q1) * so1 + (size_t)(g.out_base[2] + g.os[2] * q2) * so2 + ch] = s;
-      }
     oq0 += pstride;
     while (oq0 >= nq0) oq0 -= nq0, ++on;
   };
+  int* const redo = (int*)(wlds + c.ck * 3072);  // set if a sum of the plane is not finite; if a weight is not
+  if (tid == 0) redo[0] = redo[1] = 0;
+  __syncthreads();
   if (sp.p < pcnt) load_stage(sp);
   for (int po = 0; po < pcnt; ++po) {  // output planes of this workgroup
     zero_acc();
     while (sp.p == po) {  // the stages that feed output plane po
       const int gr = sp.gr;
-      write_stage();
+      write_stage(kSplitScale);
       __syncthreads();
       advance(sp);
       if (sp.p < pcnt) load_stage(sp);  // in flight while this stage multiplies
       compute(gr);
+      if (sp.p != po) {
+        float seen = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) seen = note_not_finite(acc[mt][v] *= kUnsplit, seen);
+        }
+        if (any_not_finite(seen)) *redo = 1;
+      }
       __syncthreads();
+    }
+    if (__builtin_amdgcn_readfirstlane(*redo)) {  // (uniform, rare) the plane once more in fp32, its weights from the caller's
+      StagePos rp{po, on, oq0, 0, ncc - 1, a->ngroups - 1, -1, rot_d ? skew_of(oq0) : 0};
+      zero_acc();
+      __syncthreads();  // every wave has read the word
+      if (tid == 0) redo[0] = redo[1] = 0;
+      __syncthreads();
+      for (advance(rp); rp.p == po; advance(rp)) {
+        load_cells(rp);
+        const int tb = a->gbegin[rp.gr], nt = a->gbegin[rp.gr + 1] - tb;
+#pragma unroll
+        for (int i = 0; i < PA; ++i) {
+          float v[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(ra[i][e >> 2][e & 3]);
+          u32x4 u, l;
+          halve_eight(v, u, l);
+          *(u32x4*)(smem + pl0 + i * 2048) = u;
+          *(u32x4*)(smem + pl0 + i * 2048 + PS) = l;
+        }
+#pragma unroll 1
+        for (int i = tid; i < nt * 64; i += 256) {  // [tap][h][nn]
+          float v[8];
+          weight_octet(a, w, rp.t0, rp.cc, tb + (i >> 6), (i >> 5) & 1, ntile * 32 + (i & 31), v);
+          u32x4 u, l;
+          halve_eight(v, u, l);
+          char* const at = wlds + (i >> 6) * 3072 + (i & 63) * 16;
+          *(u32x4*)at = u;
+          *(u32x4*)(at + 1024) = l;
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (not_finite(v[e])) redo[1] = 1;
+        }
+        __syncthreads();
+        // A cell of dx lacks the taps whose output does not exist.  They read zeros, which do not cancel a weight that is not
+        // finite: once there is one, lane by lane and without those terms.
+        const bool lanes = c.mode == 1 && __builtin_amdgcn_readfirstlane(redo[1]);
+#pragma unroll 1
+        for (int t = 0; lanes && t < nt; ++t) {
+          const uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + t) - (uint32_t)h * HB;
+          bool there[MT];
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            const int pidx = (wave * MT + mt) * 32 + m, wr = (int)fd_div((uint32_t)pidx, div_tc), wc = pidx - wr * c.tc;
+            const int i1 = g.in_base[1] + (q1_0 + wr) * c.is[1] + c.tapoff[1][a->tap12[tb + t][0]],
+                      i2 = g.in_base[2] + (q2_0 + wc) * c.is[2] + c.tapoff[2][a->tap12[tb + t][1]];
+            there[mt] = (uint32_t)i1 < (uint32_t)g.in_ext[1] && (uint32_t)i2 < (uint32_t)g.in_ext[2];
+          }
+#pragma unroll 1
+          for (int o = 0; o < 2; ++o) {  // octets of the chunk
+            Eight xx[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+              const char* const xp = smem + abase[mt] + cell + o * HB;
+              xx[mt] = join_halves(*(const u32x4*)xp, *(const u32x4*)(xp + PS));
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              const char* const wp = wlds + t * 3072 + (o * 32 + 8 * (v >> 2) + 4 * h + (v & 3)) * 16;
+              const Eight xw = join_halves(*(const u32x4*)wp, *(const u32x4*)(wp + 1024));
+#pragma unroll
+              for (int mt = 0; mt < MT; ++mt) {
+                float sum = acc[mt][v];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sum = fmaf(xw.v[e], xx[mt].v[e], sum);
+                acc[mt][v] = there[mt] ? sum : acc[mt][v];
+              }
+            }
+          }
+        }
+#pragma unroll 1
+        for (int t = 0; !lanes && t < nt; ++t) {
+          const uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + t);
+          const char* const wp = wlds + t * 3072 + wread;
+          const Eight xw = join_halves(*(const u32x4*)wp, *(const u32x4*)(wp + 1024));
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            const char* const xp = smem + abase[mt] + cell;
+            acc[mt] = multiply_fp32(xw, join_halves(*(const u32x4*)xp, *(const u32x4*)(xp + PS)), acc[mt]);
+          }
+        }
+        __syncthreads();
+      }
+      if (sp.p < pcnt) load_cells(sp);  // the next plane's cells again: their registers were used
     }
     store_plane();
   }
@@ -388,17 +470,10 @@ __global__ __launch_bounds__(256) void corr_split_weights_kernel(const SplitArgs
   const int tap = r % ntaps; r /= ntaps;
   const int cc = r % ncc; r /= ncc;
   const int t0 = r % c.nt[0], ntile = r / c.nt[0];
-  const int ch = ntile * 32 + (hn & 31);
-  const int ft = (c.tapid[0][t0] * a->k1 + c.tapid[1][a->tap12[tap][0]]) * a->k2 + c.tapid[2][a->tap12[tap][1]];
   float v[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int k = cc * 16 + (hn >> 5) * 8 + e;
-    const int o = c.mode == 0 ? ch : k, i = c.mode == 0 ? k : ch;
-    v[e] = k < c.kc && ch < c.nc ? w[((size_t)o * a->ci + i) * a->taps + ft] : 0.f;
-  }
+  weight_octet(a, w, t0, cc, tap, hn >> 5, ntile * 32 + (hn & 31), v);
   u32x4 hi, mid, lo;
-  split_eight(v, hi, mid, lo);
+  split_eight(v, kSplitScale, hi, mid, lo);
   u32x4* const at = dst + a->woff + (size_t)(idx >> 6) * 192 + hn;
   at[0] = hi;
   at[64] = mid;

@@ -35,6 +35,7 @@
 //   4 -> 4, 5 x 5, 6 x 528 x 776:                     1303 -> 140
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "conv_wsplit.h"
 #include "profile.h"
@@ -84,12 +85,30 @@ __device__ inline bf16x8 operand(const char* first, const char* second) {
   return f.v;
 }
 
-__device__ inline void put_split(char* at, uint32_t plane, u32x4 v, uint32_t flip = 0) {
+// the operand's numbers, from its upper and lower halves
+__device__ inline Eight halves(const char* first, const char* second, uint32_t plane) {
+  return join_halves(__builtin_bit_cast(u32x4, operand(first, second)), __builtin_bit_cast(u32x4, operand(first + plane, second + plane)));
+}
+
+// four channels of a cell or position; RAW: as they are, for fp32 MFMAs
+template <bool RAW>
+__device__ inline void put_split(char* at, uint32_t plane, u32x4 v, float scale = kSplitScale) {
   u32x2 hi, mid, lo;
+  if constexpr (RAW) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      uint32_t a, b;
+      halve_pair(v[2 * j], v[2 * j + 1], a, b);
+      hi[j] = a, mid[j] = b;
+    }
+    *(u32x2*)at = hi;
+    *(u32x2*)(at + plane) = mid;
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     uint32_t a, b, c;
-    split_pair(__uint_as_float(v[2 * j] ^ flip), __uint_as_float(v[2 * j + 1] ^ flip), a, b, c);
+    split_pair(__uint_as_float(v[2 * j]), __uint_as_float(v[2 * j + 1]), scale, a, b, c);
     hi[j] = a, mid[j] = b, lo[j] = c;
   }
   *(u32x2*)at = hi;
@@ -158,10 +177,6 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
     trow[i] = t1 * a.dil[1] + (pos >> (a.lc - 1)) * s1;
   }
   floatx4 acc[MT][NT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   const int row_cells = wd.buf[2] - wd.origin[2];
   const int O1 = wd.out[1], O2 = wd.out[2], nseg = (O2 + cols - 1) >> a.lc;
@@ -217,20 +232,22 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
     for (int j = 0; j < 4; ++j) bsum[i][j] = 0.f;
   uint32_t nslot = 0;  // ring place of the step's new row 0
   auto wrap = [&](uint32_t at) { return min(at, at - ringb); };  // at < 2 ringb
-  auto stash = [&](uint32_t odd) {
+  auto stash = [&](auto raw, uint32_t odd) {
+    constexpr bool RAW = decltype(raw)::value;
     // All loads are in.  (Said here because on the paths that skip a piece the compiler cannot see it, and would wait for the
     // next step's loads before it multiplies.)
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 #pragma unroll
     for (int i = 0; i < kNx; ++i)
       if (i * TH < npieces) {
-        if (i * TH + tid < npieces) put_split(smem + wrap(pdst[i] + nslot), planeb, rp[i]);
+        if (i * TH + tid < npieces) put_split<RAW>(smem + wrap(pdst[i] + nslot), planeb, rp[i]);
       }
 #pragma unroll
     for (int i = 0; i < NY; ++i) {
       const int u = i * TH + tid, pos = u / (4 * NT), q = u % (4 * NT);
-      if (pos < 32) put_split(ys + odd * kYBuf + (q >> 2) * 1024 + pos * 32 + (q & 3) * 8, kYPlane, rpy[i], odd << 31);
-      if (bias_wg)
+      if (pos < 32)
+        put_split<RAW>(ys + odd * kYBuf + (q >> 2) * 1024 + pos * 32 + (q & 3) * 8, kYPlane, rpy[i], odd ? -kSplitScale : kSplitScale);
+      if (bias_wg && !RAW)
 #pragma unroll
         for (int j = 0; j < 4; ++j) bsum[i][j] += __uint_as_float(rpy[i][j]);
     }
@@ -238,9 +255,16 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
   const uint32_t lane_y = (uint32_t)((4 * lg + (ls >> 2)) * 32 + (ls & 3) * 8);
   const uint32_t more = (uint32_t)(cols / 2) * cellb;  // to the other sixteen positions
   const uint32_t tstep = (uint32_t)nr * rowb;
-  uint32_t odd = 0;  // which dy buffer, and sign, the next step takes
   const int unit_begin = chunk * per, unit_cnt = unit_end - unit_begin;
   const int skew = unit_cnt > 0 ? (((a.k[0] - 1 - t0) * a.dil[0]) / a.s[0] * nblk1) % unit_cnt : 0;
+  // All units of this workgroup, with operands that are split, or (RAW) multiplied as they are.
+  auto pass = [&](auto raw) __attribute__((always_inline)) {
+  constexpr bool RAW = decltype(raw)::value;
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  uint32_t odd = 0;  // which dy buffer, and sign, the next step takes
   for (int uj = 0; uj < unit_cnt; ++uj) {
     const int unit = unit_begin + (uj + skew < unit_cnt ? uj + skew : uj + skew - unit_cnt);
     const int plane = unit / nblk1, o1_begin = (unit - plane * nblk1) * a.ob, o1_end = min(O1, o1_begin + a.ob);
@@ -270,15 +294,37 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (base + i * TH + tid < total) put_split(smem + at[i], planeb, v[i]);
+            if (base + i * TH + tid < total) put_split<RAW>(smem + at[i], planeb, v[i]);
         }
       }
       for (int o1 = o1_begin; o1 < o1_end; o1 += a.r, odd ^= 1u) {
-        stash(odd);
+        stash(raw, odd);
         __syncthreads();  // step o1 staged; every wave has finished step o1 - 1
         if (o1 + a.r < o1_end) fetch(n, o0, o1 + a.r, o1_end, seg);  // in flight while this step multiplies
         const char* const yb = ys + odd * kYBuf + lane_y;
-        const float sign = odd ? -1.f : 1.f;
+        if constexpr (RAW) {
+          Eight xb[NT];
+#pragma unroll
+          for (int j = 0; j < NT; ++j) xb[j] = halves(yb + j * 1024, yb + j * 1024 + 512, kYPlane);
+          // a position beyond the output has a dy of zero, which does not cancel a cell that is not finite
+          bool there[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int pos = 4 * lg + (e & 3), row = pos >> (a.lc - 1), col = seg * cols + (pos & (cols / 2 - 1)) + (e >> 2) * (cols / 2);
+            there[e] = o1 + row < o1_end && col < O2;
+          }
+#pragma unroll
+          for (int i = 0; i < MT; ++i) {
+            Eight xa = halves(smem + taddr[i], smem + taddr[i] + more, planeb);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xa.v[e] = there[e] ? xa.v[e] : 0.f;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa.v[e], xb[j].v[e], acc[i][j], 0, 0, 0);
+          }
+        } else {
+        const float sign = odd ? -kUnsplit : kUnsplit;
         bf16x8 fb[NT][3];
 #pragma unroll
         for (int j = 0; j < NT; ++j)
@@ -327,14 +373,32 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
         } else if constexpr (MT > 1) {
           add(MT - 2);
         }
+        }
         nslot = wrap(nslot + tstep);
 #pragma unroll
         for (int i = 0; i < MT; ++i) taddr[i] = wrap(taddr[i] + tstep);
       }
     }
   }
+  };
+  pass(std::false_type{});
+  {
+    int* const redo = (int*)ys;  // set if a sum of this workgroup's is not finite
+    __syncthreads();  // the last step is consumed
+    if (tid == 0) *redo = 0;
+    __syncthreads();
+    float seen = 0.f;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) seen = note_not_finite(acc[i][j][e], seen);
+    if (any_not_finite(seen)) *redo = 1;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(*redo)) pass(std::true_type{});  // (uniform, rare)
+  }
   float* const slot = partial + (size_t)bz * a.slot;
-  bool bad = false;
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const int r = (first + i) * 16 + 4 * lg;  // four rows of one tap
@@ -345,34 +409,11 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
         const int ch = co0 + 16 * j + ls;
         if (ch < a.co) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            bad |= not_finite(acc[i][j][e]);
-            slot[((size_t)(t0 * T + tap) * a.ci + c + e) * a.co + ch] = acc[i][j][e];
-          }
+          for (int e = 0; e < 4; ++e) slot[((size_t)(t0 * T + tap) * a.ci + c + e) * a.co + ch] = acc[i][j][e];
         }
       }
     }
   }
-  if (bad)  // rare: this lane's sums term by term
-    for (int t = 0; t < ntw * NT * 4; ++t) {
-      const int r = (first + t / (4 * NT)) * 16 + 4 * lg, tap = r / a.cc, c = ci0 + r - tap * a.cc + t % 4;
-      const int ch = co0 + 16 * (t / 4 % NT) + ls, t1 = tap / a.k[2], t2 = tap - t1 * a.k[2];
-      if (r >= rows || c >= a.ci || ch >= a.co) continue;
-      float sum = 0.f;
-      for (int unit = unit_begin; unit < unit_end; ++unit) {
-        const int plane = unit / nblk1, o1_begin = (unit - plane * nblk1) * a.ob, o1_end = min(O1, o1_begin + a.ob);
-        const int o0 = plane % wd.out[0], n = plane / wd.out[0];
-        for (int o1 = o1_begin; o1 < o1_end; ++o1)
-          for (int o2 = 0; o2 < O2; ++o2) {
-            const size_t px = (size_t)n * sxn + (size_t)(wd.origin[0] + o0 * a.s[0] + t0 * a.dil[0]) * sx0 +
-                              (size_t)(wd.origin[1] + o1 * s1 + t1 * a.dil[1]) * sx1 +
-                              (size_t)(wd.origin[2] + o2 * a.s[2] + t2 * a.dil[2]) * sx2 + c;
-            const size_t py = (size_t)n * syn + (size_t)o0 * sy0 + (size_t)o1 * sy1 + (size_t)o2 * sy2 + ch;
-            sum = fmaf(((const float*)dy_bufs[worker])[py], ((const float*)x_bufs[worker])[px], sum);
-          }
-      }
-      slot[((size_t)(t0 * T + tap) * a.ci + c) * a.co + ch] = sum;
-    }
   if (bias_wg) {  // each column's positions of a row, in order
     float* const red = (float*)smem;
     __syncthreads();

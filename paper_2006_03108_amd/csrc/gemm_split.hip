@@ -15,6 +15,7 @@
 // An operand whose rows are contiguous in memory instead of its k (W in dx, both operands of dW) is loaded two rows
 // wide for eight k lines by each thread: the transpose happens in registers and costs nothing.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "gemm_mfma.h"
@@ -51,7 +52,7 @@ constexpr int planes_of(bool bf16) { return bf16 ? 1 : 3; }
 constexpr int kStageKp(int T) { return 8 / T; }  // octets of k per stage
 constexpr int operand_bytes(int T, bool bf16) { return kStageKp(T) * (planes_of(bf16) * 64 * T * 16) + 128; }
 constexpr int split_lds(int T, bool bf16) {
-  return T == 1 ? std::max(2 * operand_bytes(T, bf16), 4 * 64 * 64 * 4) : 2 * operand_bytes(T, bf16);  // (T = 1: four partial tiles at the end)
+  return (T == 1 ? std::max(2 * operand_bytes(T, bf16), 4 * 64 * 64 * 4) : 2 * operand_bytes(T, bf16)) + 16;  // (T = 1: four partial tiles at the end)
 }
 
 // The NP x 8 values a thread takes per operand and stage.  K-contiguous operand: NP pieces of 8 k; otherwise NP rows of
@@ -135,6 +136,7 @@ struct Stager {
     if constexpr (BF16) return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, so, 0) << 16);
     else return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, so, 0));
   }
+  template <bool RAW>
   __device__ inline void write(char* lds, int tid) const {
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
@@ -147,9 +149,14 @@ struct Stager {
 #pragma unroll
         for (int j = 0; j < 4; ++j) h[j] = pack_bf16(v[i][2 * j], v[i][2 * j + 1]);  // exact
         *(u32x4*)at = h;
+      } else if constexpr (RAW) {
+        u32x4 u, w;
+        halve_eight(v[i], u, w);
+        *(u32x4*)at = u;
+        *(u32x4*)(at + R * 16) = w;
       } else {
         u32x4 h, m, l;
-        split_eight(v[i], h, m, l);
+        split_eight(v[i], kSplitScale, h, m, l);
         *(u32x4*)at = h;
         *(u32x4*)(at + R * 16) = m;
         *(u32x4*)(at + 2 * R * 16) = l;
@@ -157,26 +164,6 @@ struct Stager {
     }
   }
 };
-
-// sum of A[row][k] B[k][col] over the stages [s_begin, s_end) of a block, in fp32: for the sums the split cannot give
-template <bool A_KC, bool B_KC, int T>
-__device__ inline float fp32_sum(const GemmBlock& gb, int row, int col, int s_begin, int s_end) {
-  constexpr int SK = 8 * kStageKp(T);
-  float sum = 0.f;
-  int at = 0;
-  for (int s = 0; s < gb.nseg; ++s) {
-    const GemmSeg& sg = gb.seg[s];
-    const int n = (sg.K + SK - 1) / SK;
-    const int k_lo = max(0, s_begin - at) * SK, k_hi = min(sg.K, (s_end - at) * SK);
-    at += n;
-    for (int k = k_lo; k < k_hi; ++k) {
-      const float a = ((const float*)sg.a)[A_KC ? (size_t)row * sg.lda + k : (size_t)k * sg.lda + row];
-      const float b = ((const float*)sg.b)[B_KC ? (size_t)col * sg.ldb + k : (size_t)k * sg.ldb + col];
-      sum = fmaf(a, b, sum);
-    }
-  }
-  return sum;
-}
 
 // Workgroup `wg` of one launch over `blocks`: wg = (block, split, tile), tile fastest.
 struct SplitGrid {
@@ -195,7 +182,9 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
   constexpr uint32_t kPitch = SA::kPitch;
   int tile = wg % sg_.tiles;
   const int rest = wg / sg_.tiles, split = rest % sg_.nsplit, block = rest / sg_.nsplit;
-  const GemmBlock& gb = sg_.blocks[block];
+  // (nothing writes the descriptors while the kernel runs: read through the constant address space they are scalar loads
+  // wherever they stand)
+  const auto& gb = *(const __attribute__((address_space(4))) GemmBlock*)(uintptr_t)(sg_.blocks + block);
   const int tiles_m = (gb.M + R - 1) / R, tiles_n = (gb.N + R - 1) / R;
   if (tile >= tiles_m * tiles_n) return;
   const int m0 = (tile % tiles_m) * R, n0 = (tile / tiles_m) * R;
@@ -213,14 +202,16 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
   // of it, so that its roundings do not count.  With all six in one accumulator the sums of a 2048^3 product were
   // 7.0e-7 off, with two 2.6e-7 (fp32 MFMAs, K split in two: 5.7e-7).
   floatx16 acc[2][2], low[2][2];
+  auto zero = [&]() {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.f;
+      for (int j = 0; j < 2; ++j)
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.f;
+  };
 
   // cursor of the next stage to load: its segment, its stage there, stages left there
-  int seg = -1, kin = s_begin, left = 0;
+  int seg, kin, left;
   SA sa;
   SB sb;
   typename SA::Op oa;
@@ -231,7 +222,7 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
       ++seg;
       left = (gb.seg[seg].K + SK - 1) / SK - kin;
       if (left > 0) {
-        const GemmSeg& g = gb.seg[seg];
+        const auto& g = gb.seg[seg];
         oa.enter(g.a, g.lda, gb.M, g.K, m0, tid);
         ob.enter(g.b, g.ldb, gb.N, g.K, n0, tid);
       }
@@ -271,26 +262,63 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
     }
     mm(acc, 0, 0);
   };
-  if (s_begin < s_end) load_stage();
-  for (int s = s_begin; s < s_end; ++s) {
-    sa.write(la, tid);
-    sb.write(lb, tid);
-    __syncthreads();
-    if (s + 1 < s_end) load_stage();  // in flight while this stage multiplies
+  auto multiply_halves = [&](const char* a, const char* b) {
+    Eight xa[2], xb[2];
 #pragma unroll
-    for (int sl = 0; sl < (T == 2 ? 2 : 1); ++sl) {
-      read(la + sl * 2 * kPitch, lb + sl * 2 * kPitch);
-      multiply();
+    for (int t = 0; t < 2; ++t) {
+      const char *const pa = a + fra + 32 * t * 16, *const pb = b + frb + 32 * t * 16;
+      xa[t] = join_halves(*(const u32x4*)pa, *(const u32x4*)(pa + R * 16));
+      xb[t] = join_halves(*(const u32x4*)pb, *(const u32x4*)(pb + R * 16));
     }
-    __syncthreads();
-  }
-
-  if constexpr (TWO) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] += low[i][j];
+      for (int j = 0; j < 2; ++j) acc[i][j] = multiply_fp32(xb[j], xa[i], acc[i][j]);
+  };
+  int* const redo = (int*)(smem + split_lds(T, BF16) - 16);  // set if a sum of the tile is not finite
+  // The whole sum, from operands that are split, or (RAW) multiplied as they are.
+  auto pass = [&](auto raw) __attribute__((always_inline)) {
+    constexpr bool RAW = decltype(raw)::value;
+    seg = -1, kin = s_begin, left = 0;
+    zero();
+    if (s_begin < s_end) load_stage();
+    for (int s = s_begin; s < s_end; ++s) {
+      sa.template write<RAW>(la, tid);
+      sb.template write<RAW>(lb, tid);
+      __syncthreads();
+      if (s + 1 < s_end) load_stage();  // in flight while this stage multiplies
+#pragma unroll
+      for (int sl = 0; sl < (T == 2 ? 2 : 1); ++sl) {
+        if constexpr (RAW) {
+          multiply_halves(la + sl * 2 * kPitch, lb + sl * 2 * kPitch);
+        } else {
+          read(la + sl * 2 * kPitch, lb + sl * 2 * kPitch);
+          multiply();
+        }
+      }
+      if constexpr (!BF16 && !RAW) {
+        if (s + 1 == s_end) {
+          float seen = 0.f;
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              if constexpr (TWO) acc[i][j] += low[i][j];
+#pragma unroll
+              for (int v = 0; v < 16; ++v) seen = note_not_finite(acc[i][j][v] *= kUnsplit, seen);
+            }
+          if (any_not_finite(seen)) *redo = 1;
+        }
+      }
+      __syncthreads();
+    }
+  };
+  if (!BF16 && tid == 0) *redo = 0;
+  pass(std::false_type{});
+  if constexpr (!BF16) {
+    if (s_begin < s_end && __builtin_amdgcn_readfirstlane(*redo)) pass(std::true_type{});  // (uniform)
   }
+
   // The products were accumulated transposed: register v of lane (h, ml) of MFMA tile (i, j) is
   // C[32 i + ml][32 j + 8 (v / 4) + 4 h + v % 4], so that a register quad is four consecutive columns.  The tile goes
   // through LDS (the last barrier above came after the last read of the stage) and leaves in whole lines: 16 bytes per
@@ -307,9 +335,7 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
   };
   // four columns from `col` of a row (VEC: whole quads, 16-byte aligned rows)
   const bool vec_out = VEC && !BF16 && ldc % 4 == 0 && ((uintptr_t)(pc ? (void*)pc : gb.c) & 15) == 0;
-  bool bad = false;
   auto quad = [&](int row, int col, const float (&b)[4], float4 s) {
-    bad |= not_finite(s.x) | not_finite(s.y) | not_finite(s.z) | not_finite(s.w);
     const float o[4] = {s.x + b[0], s.y + b[1], s.z + b[2], s.w + b[3]};
     if (row >= gb.M) return;
     if (vec_out && col + 4 <= gb.N) {
@@ -325,13 +351,6 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
   auto bias_of = [&](int col, float (&b)[4]) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) b[e] = bias && col + e < gb.N ? load_one<BF16>(bias, col + e) : 0.f;
-  };
-  // the sums of this lane's quad that are not finite, once more in fp32 (rare)
-  auto again = [&](int row, int col) {
-    if (row >= gb.M) return;
-    for (int e = 0; e < 4; ++e)
-      if (col + e < gb.N)
-        put(row, col + e, fp32_sum<A_KC, B_KC, T>(gb, row, col + e, s_begin, s_end) + (bias ? load_one<BF16>(bias, col + e) : 0.f));
   };
   if constexpr (T == 2) {
     // each wave 32 rows of its quarter at a time, in 8 KB of its own; row r keeps its quad c at c ^ (r & 15)
@@ -352,10 +371,6 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
         const int r = 4 * r8 + (lane >> 4);
         quad(m0 + 64 * wy + 32 * i + r, col, b, mine[r * 16 + ((lane & 15) ^ (r & 15))]);
       }
-    }
-    if constexpr (!BF16) {
-      if (bad)
-        for (int e = 0; e < 16; ++e) again(m0 + 64 * wy + 4 * e + (lane >> 4), col);
     }
   } else {
     // the four waves' partial tiles, [wave][64 rows][16 quads], added in wave order
@@ -382,10 +397,6 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
         s.x += u.x, s.y += u.y, s.z += u.z, s.w += u.w;
       }
       quad(m0 + r, col, b, s);
-    }
-    if constexpr (!BF16) {
-      if (bad)
-        for (int q = 0; q < 4; ++q) again(m0 + (tid >> 4) + 16 * q, col);
     }
   }
 }

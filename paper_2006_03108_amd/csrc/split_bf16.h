@@ -2,19 +2,20 @@
 //
 // A bf16 MFMA does sixteen times the work of an fp32 one in the same time (measured on loops of MFMAs alone: 2250
 // against 146 TFLOP/s), and vector instructions issue beside it, which they do not beside an fp32 MFMA.  An fp32
-// number is the exact sum of three bf16 numbers (24 significant bits = 3 x 8):
+// number is the exact sum of three bf16 numbers (24 significant bits = 3 x 8; Henry, Tang and Heinecke, "Leveraging the
+// bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019):
 //     x = hi + mid + lo,   hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid)   (the differences are exact)
-// so x * w is nine products of bf16 numbers, each exact in the fp32 accumulator of an MFMA.  The three smallest,
-// mid * lo, lo * mid and lo * lo, are below 2^-25 |x w| and are left out: six MFMAs, smallest products first.
-// Measured against 64-bit sums on N(0, 1) data, relative error (2-norm) for K = 64 / 1024 / 4096: 1.1e-7 / 4.6e-7 /
-// 9.9e-7 here and 1.5e-7 / 5.8e-7 / 1.15e-6 with fp32 MFMAs (the same with all nine products): what is left is the
-// rounding of the running sum, and a bf16 MFMA rounds it once for 16 products where an fp32 one rounds it for 2.
+// so x * w is nine products of bf16 numbers.  The three smallest, mid * lo, lo * mid and lo * lo, are below 2^-25 |x w|
+// and are left out: six MFMAs, smallest products first.  (Short sums therefore know a product to about half an ulp.)
 //
-// Numbers that the split cannot carry: an infinity or a NaN, or a finite number that rounds to an infinite bf16
-// (above 3.39e38), makes every sum it enters infinite or NaN (inf - inf, inf * 0), also where the fp32 sum would be a
-// plain infinity or finite.  Kernels that use the split therefore look at their finished sums and take those that
-// are not finite again, in fp32, from the operands.  Below 2^-110 a number's lo, then mid part is smaller than the
-// smallest normal bf16 and is flushed: products lose what is below 2^-126 |w|.
+// Measured against 64-bit sums on N(0, 1) data, relative error (2-norm) for K = 64 / 1024 / 4096: 1.1e-7 / 4.6e-7 /
+// 9.9e-7 here and 1.5e-7 / 5.8e-7 / 1.15e-6 with fp32 MFMAs.
+//
+// Numbers that the split cannot carry: an infinity or a NaN, or a finite number that rounds to an infinite bf16 (above
+// 3.39e38), makes every sum it enters infinite or NaN, also where the fp32 sum would be a plain infinity or finite.
+// Kernels that use the split look at their finished sums; a workgroup with one that is not finite makes its whole tile
+// again with fp32 MFMAs from operands staged as they are, so that these too are what fp32 products give.  Below 2^-110 a
+// number's lo, then mid part is smaller than the smallest normal bf16 and is flushed.
 #pragma once
 #include <cstdint>
 
@@ -25,13 +26,19 @@ namespace distdl {
 typedef __bf16 split_bf16x2 __attribute__((ext_vector_type(2)));
 typedef float split_f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t split_u32x4 __attribute__((ext_vector_type(4)));
+typedef float split_f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr float kSplitScale = 1.f;                             // of either operand
+constexpr float kUnsplit = 1.f / kSplitScale / kSplitScale;    // of the sums
 
 __device__ inline uint32_t pack_bf16(float a, float b) {  // round to nearest even, one instruction
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(split_f32x2{a, b}, split_bf16x2));
 }
 
-// two numbers -> their hi, mid and lo parts, packed (eleven vector instructions)
-__device__ inline void split_pair(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+// two numbers -> the hi, mid and lo parts, packed, of their multiples (eleven vector instructions); scale: +-kSplitScale
+__device__ inline void split_pair(float a, float b, float scale, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  a *= scale;
+  b *= scale;
   hi = pack_bf16(a, b);
   a -= __uint_as_float(hi << 16);
   b -= __uint_as_float(hi & 0xffff0000u);
@@ -42,17 +49,56 @@ __device__ inline void split_pair(float a, float b, uint32_t& hi, uint32_t& mid,
 }
 
 // eight numbers -> three MFMA operand pieces
-__device__ inline void split_eight(const float (&x)[8], split_u32x4& hi, split_u32x4& mid, split_u32x4& lo) {
+__device__ inline void split_eight(const float (&x)[8], float scale, split_u32x4& hi, split_u32x4& mid, split_u32x4& lo) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t a, b, c;
-    split_pair(x[2 * j], x[2 * j + 1], a, b, c);
+    split_pair(x[2 * j], x[2 * j + 1], scale, a, b, c);
     hi[j] = a;
     mid[j] = b;
     lo[j] = c;
   }
 }
 
+// The other way to stage numbers, for a tile that is made again: their upper and their lower halves.
+__device__ inline void halve_pair(uint32_t a, uint32_t b, uint32_t& upper, uint32_t& lower) {
+  upper = __builtin_amdgcn_perm(b, a, 0x07060302u);
+  lower = __builtin_amdgcn_perm(b, a, 0x05040100u);
+}
+__device__ inline void halve_eight(const float (&x)[8], split_u32x4& upper, split_u32x4& lower) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t a, b;
+    halve_pair(__float_as_uint(x[2 * j]), __float_as_uint(x[2 * j + 1]), a, b);
+    upper[j] = a;
+    lower[j] = b;
+  }
+}
+// the numbers of a lane's operand pieces
+struct Eight {
+  float v[8];
+};
+__device__ inline Eight join_halves(split_u32x4 upper, split_u32x4 lower) {
+  Eight o;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    o.v[2 * j] = __uint_as_float(__builtin_amdgcn_perm(upper[j], lower[j], 0x05040100u));
+    o.v[2 * j + 1] = __uint_as_float(__builtin_amdgcn_perm(upper[j], lower[j], 0x07060302u));
+  }
+  return o;
+}
+// c += a b over the 16 k of two operand pieces: element e of the lanes is k e and 8 + e
+__device__ inline split_f32x16 multiply_fp32(const Eight& a, const Eight& b, split_f32x16 c) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[e], b.v[e], c, 0, 0, 0);
+  return c;
+}
+
+// (fp32 bits) an infinity or a NaN
 __device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
+// 0, or NaN if v or `seen` is not finite: one instruction a sum
+__device__ inline float note_not_finite(float v, float seen) { return fmaf(v, 0.f, seen); }
+// the same for all lanes, so that what depends on it branches for whole waves
+__device__ inline bool any_not_finite(float seen) { return __builtin_amdgcn_ballot_w64(seen != 0.f) != 0; }
 
 }  // namespace distdl

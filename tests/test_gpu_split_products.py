@@ -1,0 +1,128 @@
+"""fp32 sums on the split bf16 products: what becomes of infinities and NaNs, and what a pass with an infinity in it costs.
+References in fp64 on the device."""
+import itertools
+
+import pytest
+import torch
+
+import paper_2006_03108_amd as dd
+from tests.gpu_util import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _rel(got, want):
+    return float((got.double() - want).norm() / want.norm().clamp_min(1e-300))
+
+
+class _Layer:
+    """A convolution layer on one worker, its tensors padded and channels-last, and the same in fp64, tap by tap."""
+
+    def __init__(self, n_b, c_in, c_out, shape, k, s, seed=11):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        D, p = len(shape), k // 2
+        self.k, self.s, self.D = k, s, D
+        out = [(n + 2 * p - k) // s + 1 for n in shape]
+        self.plan = dd.distdl_plan_create(D, n_b, c_in, c_out, shape, (1,) * D, (k,) * D, (s,) * D, (p,) * D, (1,) * D)
+        buf = self.plan.query(0)["buf_shape"][:D]
+        self.bulk = (slice(None), *(slice(p, p + n) for n in shape))
+        self.x = torch.zeros(n_b, *buf, c_in, device="cuda")
+        self.x[self.bulk] = torch.randn(n_b, *shape, c_in, generator=g, device="cuda")
+        self.w = torch.randn(c_out, c_in, *[k] * D, generator=g, device="cuda")
+        self.dy = torch.randn(n_b, *out, c_out, generator=g, device="cuda")
+        self.y, self.dx, self.dw = torch.empty_like(self.dy), torch.empty_like(self.x), torch.empty_like(self.w)
+        self.ws = torch.empty(max(dd.distdl_conv_bwd_workspace(self.plan), 16), dtype=torch.uint8, device="cuda")
+
+    def run(self):
+        dd.distdl_conv_fwd(self.plan, [self.x], self.w, None, [self.y])
+        dd.distdl_conv_bwd(self.plan, [self.x], self.w, [self.dy], [self.dx], self.dw, None, self.ws)
+        return self.y, self.dx[self.bulk], self.dw
+
+    def exact(self):
+        x, w, dy = self.x.double(), self.w.double(), self.dy.double()
+        y, dx, dw = torch.zeros_like(dy), torch.zeros_like(x), torch.zeros_like(w)
+        rows = dy.reshape(-1, dy.shape[-1])
+        for t in itertools.product(*[range(self.k)] * self.D):
+            at = (slice(None), *(slice(i, i + (n - 1) * self.s + 1, self.s) for i, n in zip(t, dy.shape[1:])))
+            wt = w[(slice(None), slice(None), *t)]
+            cells = x[at].reshape(-1, x.shape[-1])
+            y += (cells @ wt.t()).view_as(dy)
+            dx[at] += (rows @ wt).view_as(x[at])
+            dw[(slice(None), slice(None), *t)] = rows.t() @ cells
+        return y, dx[self.bulk], dw
+
+
+# (batch, channels, extents, kernel, stride): gather kernels with 256 and 64 rows, patch kernels with one to three M-tiles,
+# classes of a stride, several output planes per workgroup; the weight gradient of each
+LAYERS = [(1, 5, 40, (24, 24), 7, 1), (12, 32, 32, (120, 116), 3, 1), (2, 18, 33, (40, 44), 3, 2), (1, 32, 32, (20, 22, 24), 5, 2),
+          (3, 8, 64, (300,), 3, 1), (2, 60, 36, (37, 40), 3, 1), (2, 4, 4, (150, 140), 5, 1)]
+IDS = ["x".join(map(str, v[3])) + f"c{v[1]}-{v[2]}s{v[5]}" for v in LAYERS]
+
+
+@pytest.mark.parametrize("shape", LAYERS, ids=IDS)
+def test_conv_with_infinities_and_nans(shape):
+    """Every sum without such a term is as exact as ever, also those of the same tile and of the planes after it; every
+    other one is the infinity or NaN that fp64 gives."""
+    require_gpu()
+    n_b, c_in, c_out, n, k, s = shape
+    L = _Layer(*shape)
+    inner, last = L.x[L.bulk], n_b - 1
+    inner[(last, *(v // 2 for v in n), 1)], inner[(0, *(v - 1 for v in n), 0)] = float("inf"), float("nan")
+    inner[(n_b // 2, *([3] * len(n)), c_in - 1)] = 3.0e38          # finite, and so are its products with 1e-3
+    L.w[:, c_in - 1] *= 1e-3
+    out = L.dy.shape[1:-1]
+    L.dy[(last, *(v // 3 for v in out), c_out - 1)], L.dy[(0, *(v // 2 for v in out), 2)] = float("-inf"), float("nan")
+    for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
+        if name == "dw":                                             # (3e38 times dy overflows in one order and not in another)
+            got, want = got[:, :-1], want[:, :-1]
+        sure = (want.abs() < 1e38) | ~torch.isfinite(want)           # (those next to the largest number may go either way)
+        assert torch.equal(torch.isnan(got)[sure], torch.isnan(want)[sure]), name
+        assert torch.equal((got == float("inf"))[sure], (want == float("inf"))[sure]), name
+        assert torch.equal((got == float("-inf"))[sure], (want == float("-inf"))[sure]), name
+        plain = want.abs() < 1e30
+        assert bool(plain.any()) or name == "dw"
+        if bool(plain.any()):
+            assert _rel(got[plain], want[plain]) < 5e-6, name
+
+
+@pytest.mark.parametrize("shape", LAYERS[:-1], ids=IDS[:-1])
+def test_conv_with_a_weight_that_is_not_finite(shape):
+    """A cell of dx that the weight's tap does not reach has no such term.  (The last layer's dx is not made of split
+    products.)"""
+    require_gpu()
+    n_b, c_in, c_out, n, k, s = shape
+    L = _Layer(*shape)
+    L.w[(1, 2, *[0] * len(n))], L.w[(c_out - 1, 0, *[k - 1] * len(n))] = float("inf"), float("nan")
+    L.w[(c_out // 2, 1, *[k // 2] * len(n))] = float("-inf")
+    for name, got, want in zip(("y", "dx"), L.run(), L.exact()):
+        assert torch.equal(torch.isnan(got), torch.isnan(want)), name
+        assert torch.equal(got == float("inf"), want == float("inf")) and torch.equal(got == float("-inf"), want == float("-inf")), name
+        plain = torch.isfinite(want)
+        assert bool(plain.any()) and _rel(got[plain], want[plain]) < 5e-6, name
+
+
+def _time(fn):
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    fn()
+    best = float("inf")
+    for _ in range(3):
+        a.record()
+        fn()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+def test_a_pass_with_nans_costs_what_fp32_products_do():
+    """A tile that has to be made again takes fp32 MFMAs, at 6 / 16 of the rate, and a pass over NaNs alone makes every tile
+    twice: 1 + 16 / 6 times a clean pass, and twice that is allowed for here.  One infinity touches a few tiles."""
+    require_gpu()
+    L = _Layer(2, 32, 32, (64, 64, 64), 3, 1)
+    clean = _time(L.run)
+    L.x[L.bulk][(0, 30, 30, 30, 5)] = float("inf")
+    assert _time(L.run) < 3 * clean
+    L.x.fill_(float("nan"))
+    L.dy.fill_(float("nan"))
+    assert _time(L.run) < 2 * (1 + 16 / 6) * clean
+    assert bool(torch.isnan(L.dw).all()) and bool(torch.isnan(L.y).all())
