@@ -21,6 +21,9 @@
  *    call is an out-of-place adjoint (Sec. 3, first paragraph).
  *  - Device pointers must be aligned to the element size; 16-byte alignment
  *    (what any allocator gives) enables the vectorised kernels.
+ *  - fp32 contractions keep the whole range of normal numbers.  Numbers from
+ *    2^103 and sums from 2^80 in magnitude, infinities and NaNs are what fp32
+ *    products give too, but the tile of results that they enter is made twice.
  *  - One plan may be used from one host thread at a time.
  *  - A plan keeps device copies of the pointer arrays it has been called with
  *    (the last eight per argument and stream) and whatever scratch it needs;

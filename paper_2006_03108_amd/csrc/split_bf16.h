@@ -11,11 +11,11 @@
 // Measured against 64-bit sums on N(0, 1) data, relative error (2-norm) for K = 64 / 1024 / 4096: 1.1e-7 / 4.6e-7 /
 // 9.9e-7 here and 1.5e-7 / 5.8e-7 / 1.15e-6 with fp32 MFMAs.
 //
-// Numbers that the split cannot carry: an infinity or a NaN, or a finite number that rounds to an infinite bf16 (above
-// 3.39e38), makes every sum it enters infinite or NaN, also where the fp32 sum would be a plain infinity or finite.
-// Kernels that use the split look at their finished sums; a workgroup with one that is not finite makes its whole tile
-// again with fp32 MFMAs from operands staged as they are, so that these too are what fp32 products give.  Below 2^-110 a
-// number's lo, then mid part is smaller than the smallest normal bf16 and is flushed.
+// Range.  The operands are multiplied by 2^24 as they are split, and the sums by 2^-48: so the lo part of every normal
+// fp32 number is itself a normal bf16 (it would be flushed for numbers below 2^-110).  In exchange numbers from 2^103,
+// sums from 2^80, infinities and NaNs make the sums that they enter infinite or NaN.  Kernels that use the split look at
+// their finished sums; a workgroup with one that is not finite makes its whole tile again with fp32 MFMAs from operands
+// staged as they are, so that these too are what fp32 products give.
 #pragma once
 #include <cstdint>
 
@@ -28,14 +28,14 @@ typedef float split_f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t split_u32x4 __attribute__((ext_vector_type(4)));
 typedef float split_f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr float kSplitScale = 1.f;                             // of either operand
+constexpr float kSplitScale = 16777216.f;                      // 2^24, of either operand
 constexpr float kUnsplit = 1.f / kSplitScale / kSplitScale;    // of the sums
 
 __device__ inline uint32_t pack_bf16(float a, float b) {  // round to nearest even, one instruction
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(split_f32x2{a, b}, split_bf16x2));
 }
 
-// two numbers -> the hi, mid and lo parts, packed, of their multiples (eleven vector instructions); scale: +-kSplitScale
+// two numbers -> the hi, mid and lo parts, packed, of their multiples (thirteen vector instructions); scale: +-kSplitScale
 __device__ inline void split_pair(float a, float b, float scale, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
   a *= scale;
   b *= scale;

@@ -1,5 +1,5 @@
-"""fp32 sums on the split bf16 products: what becomes of infinities and NaNs, and what a pass with an infinity in it costs.
-References in fp64 on the device."""
+"""fp32 sums on the split bf16 products: what becomes of infinities, NaNs and very small numbers, and what a pass with an
+infinity in it costs.  References in fp64 on the device."""
 import itertools
 
 import pytest
@@ -99,6 +99,35 @@ def test_conv_with_a_weight_that_is_not_finite(shape):
         assert torch.equal(got == float("inf"), want == float("inf")) and torch.equal(got == float("-inf"), want == float("-inf")), name
         plain = torch.isfinite(want)
         assert bool(plain.any()) and _rel(got[plain], want[plain]) < 5e-6, name
+
+
+@pytest.mark.parametrize("small", ["x", "w", "dy"])
+@pytest.mark.parametrize("shape", LAYERS, ids=IDS)
+def test_conv_of_very_small_numbers(shape, small):
+    """Numbers around 1e-36 have as many bits as any other (a bf16 number below 2^-126 = 1.2e-38 has not): 5e-6 is the bound
+    of the other tests, far above what these sums show with operands around 1."""
+    require_gpu()
+    L = _Layer(*shape)
+    getattr(L, small).mul_(1e-36)
+    for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
+        assert _rel(got, want) < 5e-6, name
+
+
+@pytest.mark.parametrize("small", ["x", "W", "dy"])
+@pytest.mark.parametrize("n_b,n_fi,n_fo", [(70, 100, 130), (256, 1024, 1024), (37, 333, 77), (256, 4096, 4096)])
+def test_affine_of_very_small_numbers(n_b, n_fi, n_fo, small):
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(6)
+    new = lambda *sh: torch.randn(sh, generator=g, device="cuda")
+    t = dict(x=new(n_b, n_fi), W=new(n_fo, n_fi), dy=new(n_b, n_fo))
+    t[small].mul_(1e-36)
+    x, W, dy = t["x"], t["W"], t["dy"]
+    y, dx, dW = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(W)
+    plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, 1, 1)
+    dd.distdl_affine_fwd(plan, [x], [W], None, [y])
+    dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], None)
+    for got, want in ((y, x.double() @ W.double().t()), (dx, dy.double() @ W.double()), (dW, dy.double().t() @ x.double())):
+        assert _rel(got, want) < 1e-6
 
 
 def _time(fn):
