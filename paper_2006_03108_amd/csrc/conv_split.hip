@@ -14,6 +14,8 @@
 // quarter of the patch with a quarter of the taps.  Three planes of a whole 5 x 5 stride-2 stage would be 200 KB; the
 // groups (9, 6, 6 and 4 taps) take 64 KB at most, so two workgroups share a compute unit and one's loads, splits and
 // barriers run under the other's MFMAs.  Groups of more than 10 taps are cut by kernel rows.
+// Error (2-norm, against 64 bits; fp32 MFMAs in brackets): 4000 products a sum 3.9e-7 (1.13e-6), 21952 with three M-tiles
+// 1.9e-6 and two 8.5e-7 (2.4e-6), 72 products 5.7e-8 (1.5e-7).
 // Bound: MFMAs (at the clock that the power limit leaves them with real data, about 2/3 of the peak) and LDS: with
 // MT = 2 a tap reads 9 KB per 12 MFMAs and wave, 3/4 of what LDS can deliver in that time.
 #include <algorithm>
@@ -238,11 +240,17 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
     u32x4 u;
     bf16x8 v;
   };
-  floatx16 acc[MT];
+  // Two accumulators, or (three M-tiles: 48 more registers do not fit) one whose sign changes from pair to pair of stages,
+  // and that of the cells with it: either keeps the bias of the small products out of the sums (split_bf16.h).
+  constexpr bool TWO = MT < 3;
+  floatx16 acc[MT], low[TWO ? MT : 1];
   auto zero_acc = [&]() {
 #pragma unroll
     for (int t = 0; t < MT; ++t)
-      for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+      for (int v = 0; v < 16; ++v) {
+        acc[t][v] = 0.f;
+        if constexpr (TWO) low[t][v] = 0.f;
+      }
   };
   // One set of operand registers: a tap's six products are ordered so that every operand of the next tap is read right
   // after the last product that needs its register, two to four products before its own first use.
@@ -255,8 +263,10 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
   auto mm = [&](int pw, int px) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[pw].v, fx[px][mt].v, acc[mt], 0, 0, 0);
+    for (int mt = 0; mt < MT; ++mt) {
+      floatx16& c = TWO && pw + px > 0 ? low[TWO ? mt : 0] : acc[mt];
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[pw].v, fx[px][mt].v, c, 0, 0, 0);
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
   const int my_cell = lane < ntaps ? a->tapcell[lane] * 16 : 0;  // lane t keeps the patch offset of tap t
@@ -333,22 +343,32 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
   if (sp.p < pcnt) load_stage(sp);
   for (int po = 0; po < pcnt; ++po) {  // output planes of this workgroup
     zero_acc();
+    uint32_t turn = 1;  // stages of the plane so far, and one; bit 1: the sign of the accumulator (+ - - + + - - ...)
     while (sp.p == po) {  // the stages that feed output plane po
       const int gr = sp.gr;
-      write_stage(kSplitScale);
+      if constexpr (!TWO) {
+        if (turn > 1 && (turn & 1) == 0) {
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[mt] = -acc[mt];
+        }
+      }
+      write_stage(!TWO && (turn & 2) ? -kSplitScale : kSplitScale);
       __syncthreads();
       advance(sp);
       if (sp.p < pcnt) load_stage(sp);  // in flight while this stage multiplies
       compute(gr);
       if (sp.p != po) {
         float seen = 0.f;
+        const float scale = !TWO && (turn & 2) ? -kUnsplit : kUnsplit;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
+          if constexpr (TWO) acc[mt] += low[mt];
 #pragma unroll
-          for (int v = 0; v < 16; ++v) seen = note_not_finite(acc[mt][v] *= kUnsplit, seen);
+          for (int v = 0; v < 16; ++v) seen = note_not_finite(acc[mt][v] *= scale, seen);
         }
         if (any_not_finite(seen)) *redo = 1;
       }
+      ++turn;
       __syncthreads();
     }
     if (__builtin_amdgcn_readfirstlane(*redo)) {  // (uniform, rare) the plane once more in fp32, its weights from the caller's
@@ -564,6 +584,10 @@ int choose_window(const distdl_plan* p, SplitArgs& a) {
     for (int tc = 1; tc <= std::min(128 * mt, nq2); ++tc) {
       set_window(a, mt, tc);
       const int pa = pieces_of(a);
+      // Three M-tiles have one accumulator for large and small products, which rounds it six times for 16 channels, where fp32
+      // MFMAs do so eight times.  4 and 20 channels fill their last chunk by a quarter and would be further off than with those
+      // (3 x 3, 4 channels: 1.32e-7 and 1.10e-7; 8 channels 1.34 and 1.54, 36 channels 2.99 and 3.22); two M-tiles: 4.9e-8.
+      if (mt == 3 && (a.c.kc == 4 || a.c.kc == 20)) continue;
       if (pa > 4 || split_lds_bytes(pa <= 3 && mt == 2 ? 3 : 4, a.c.ck) > 80 * 1024 || (mt == 3 && a.c.ck > 9)) continue;
       // a tap costs a wave 6 mt MFMAs and 3 mt + 3 operand reads: fewer M-tiles pay relatively more for the weights
       const double share = window_share(128 * mt, tc, nq1, nq2), patch = (double)(a.c.R * a.c.Cw) / (128 * mt);

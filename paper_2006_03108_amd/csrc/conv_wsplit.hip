@@ -426,9 +426,11 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
     }
     __syncthreads();
     if (tid < 16 * NT && co0 + tid < a.co) {
-      float sum = 0.f;
-      for (int pos = 0; pos < 32; ++pos) sum += red[pos * (16 * NT) + tid];
-      slot[(size_t)a.k[0] * T * a.ci * a.co + co0 + tid] = sum;
+      float sum[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int pos = 0; pos < 32; pos += 4)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum[q] += red[(pos + q) * (16 * NT) + tid];
+      slot[(size_t)a.k[0] * T * a.ci * a.co + co0 + tid] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
     }
   }
 }

@@ -1,5 +1,5 @@
-"""fp32 sums on the split bf16 products: what becomes of infinities, NaNs and very small numbers, and what a pass with an
-infinity in it costs.  References in fp64 on the device."""
+"""fp32 sums on the split bf16 products: what becomes of infinities, NaNs and very small numbers, how the error grows with
+the length of a sum, and what a pass with an infinity in it costs.  References in fp64 on the device."""
 import itertools
 
 import pytest
@@ -128,6 +128,21 @@ def test_affine_of_very_small_numbers(n_b, n_fi, n_fo, small):
     dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], None)
     for got, want in ((y, x.double() @ W.double().t()), (dx, dy.double() @ W.double()), (dW, dy.double().t() @ x.double())):
         assert _rel(got, want) < 1e-6
+
+
+@pytest.mark.parametrize("shape", [(1, 64, 64, (18, 18, 18), 7, 1), (1, 36, 40, (60, 61), 15, 1)], ids=["7^3", "15^2"])
+def test_long_sums_are_not_biased(shape):
+    """21952 and 8100 products a sum.  fp32 MFMAs round a running sum once for two products: relative error (2-norm)
+    sqrt(K / 2 / 2) roundings of up to 2^-24 of it, 4.4e-6 for the longer one, mean error zero.  The split sums stay below
+    that, and their mean error is far below a rounding (a bf16 MFMA drops bits towards minus infinity: kept in one
+    accumulator all its products gave -8e-7)."""
+    require_gpu()
+    L = _Layer(*shape)
+    for name, got, want in zip(("y", "dx"), L.run(), L.exact()):
+        diff = got.double() - want
+        rms = float(want.square().mean().sqrt())
+        assert abs(float(diff.mean())) < 1e-7 * rms, name
+        assert _rel(got, want) < 4.4e-6, name
 
 
 def _time(fn):
