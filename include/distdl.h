@@ -435,6 +435,11 @@ int distdl_debug_task_count(const distdl_plan* plan, int adjoint);
  * matrix-core tiles, 2 = 16-wide matrix-core tiles (at most 16 channels).
  * The convolution calls may prefer a kernel of another family. */
 int distdl_debug_conv_path(const distdl_plan* plan, int32_t out[3]);
+/* The kernels that the convolution calls run for this plan when every array is
+ * 16-byte aligned (aligned != 0) or none is: out[0] forward, out[1] data
+ * gradient, out[2] weight gradient; 0 = direct, 1 = 32-wide matrix-core tiles,
+ * 2 = 16-wide matrix-core tiles, 3 = split bf16 products of fp32, 4 = gather. */
+int distdl_debug_conv_kernels(const distdl_plan* plan, int aligned, int32_t out[3]);
 /* Runs the replacement policy of the cached device tables (see Conventions)
  * on a sequence of n calls without touching a device: call i arrives on
  * stream stream_id[i] with table contents table_id[i], during stream capture

@@ -69,6 +69,7 @@ _SIGS = {
     "distdl_copy_ref": [_vp, _vp, C.c_size_t, _vp],
     "distdl_debug_slot_policy": [_p32, _p32, _p32, _i, _p32],
     "distdl_debug_conv_path": [_vp, _p32],
+    "distdl_debug_conv_kernels": [_vp, _i, _p32],
     "distdl_affine_plan_create": [C.POINTER(_vp), _i64, _i64, _i64, _i, _i, _i],
     "distdl_affine_plan_destroy": [_vp],
     "distdl_affine_fwd": [_vp, _pp, _pp, _pp, _pp, _vp],
@@ -354,9 +355,16 @@ def distdl_debug_slot_policy(stream_ids, table_ids, capturing):
 
 
 def distdl_debug_conv_path(plan):
-    """(forward, data gradient, weight gradient) kernel families: 0 direct, 1 32-wide MFMA tiles, 2 16-wide."""
+    """(forward, data gradient, weight gradient) tiled kernel families that cover the plan: 0 none, 1 32-wide MFMA tiles, 2 16-wide."""
     out = (C.c_int32 * 3)()
     _check(lib.distdl_debug_conv_path(plan.handle, out))
+    return tuple(out)
+
+
+def distdl_debug_conv_kernels(plan, aligned=True):
+    """(forward, data gradient, weight gradient) kernels that run: 0 direct, 1 32-wide MFMA tiles, 2 16-wide, 3 split, 4 gather."""
+    out = (C.c_int32 * 3)()
+    _check(lib.distdl_debug_conv_kernels(plan.handle, int(aligned), out))
     return tuple(out)
 
 

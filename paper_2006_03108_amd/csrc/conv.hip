@@ -230,6 +230,30 @@ static int check_conv_plan(const distdl_plan* p) {
   return DISTDL_OK;
 }
 
+// The kernel of the forward pass and of the data gradient, by shape and alignment of the arrays (16 bytes).  The split kernels
+// take any weights' alignment, the tiled ones do not.
+enum class Corr { kDirect, kMfma, k16, kSplit, kAny };
+
+static Corr choose_fwd(const distdl_plan* p, bool xy_aligned, bool w_aligned) {
+  if (corr16_fwd_supported(p, xy_aligned)) return Corr::k16;  // few channels: 16 x 16 tiles
+  if (xy_aligned && corr_split_supported(p, false)) return Corr::kSplit;
+  if (xy_aligned && w_aligned && corr_mfma_supported(p)) return Corr::kMfma;
+  return conv_any_supported(p) ? Corr::kAny : Corr::kDirect;
+}
+
+static Corr choose_data(const distdl_plan* p, bool aligned) {
+  const bool split = aligned && corr_split_supported(p, true), any = conv_any_supported(p);
+  // Few channels and several stride classes: the 16 x 16 kernel takes a launch (with planes of taps, two) for each, the others
+  // two in all, which is what counts up to 2^18 cells for four classes (us; 4 -> 16 channels, 3 x 3, stride 2, 12 x 28 x 29:
+  // 41 and 16; 2 -> 6, 2 x 772 x 887: 74 and 118).
+  const int64_t classes = (int64_t)p->stride[0] * p->stride[1] * p->stride[2];
+  const bool together = classes >= 4 && p->n_workers * p->n_b * p->max_buf_cells <= (classes << 16) && (split || any);
+  if (!together && corr16_bwd_supported(p, aligned)) return Corr::k16;
+  if (split) return Corr::kSplit;
+  if (aligned && corr_mfma_supported(p)) return Corr::kMfma;
+  return any ? Corr::kAny : Corr::kDirect;
+}
+
 // The kernel of the weight gradient: of those that take the layer, the one whose estimated time (us) is the lowest.  The
 // estimates follow 80 measured layers of 1 to 64 channels, one to three dimensions, 10^2 to 10^7 positions:
 //   16 x 16 tiles: a set-up that grows with the taps of a plane, then 7 ps per tap and position (12 with several planes);
@@ -315,13 +339,23 @@ int distdl_conv_bwd(distdl_plan* plan, const void* const x_bufs_dev[], const voi
 int distdl_debug_conv_path(const distdl_plan* plan, int32_t out[3]) {
   if (!plan || !out) return set_error(DISTDL_ERR_NULL, "conv_path: null argument");
   if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_path: plan has no kernel");
-  // by shape and 16-byte aligned arrays; the split and gather kernels, which conv_fwd_core and conv_bwd_core may prefer, are
-  // not told apart here
+  // by shape and 16-byte aligned arrays; distdl_debug_conv_kernels says which kernels run
   const bool vec = plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
   const bool mfma = corr_mfma_supported(plan);
   out[0] = corr16_fwd_supported(plan, true) ? 2 : mfma ? 1 : 0;
   out[1] = corr16_bwd_supported(plan, true) ? 2 : mfma ? 1 : 0;
   out[2] = wgrad16_supported(plan, vec) ? 2 : (wgrad_mfma_supported(plan) && (plan->dtype != DISTDL_BF16 || vec)) ? 1 : 0;
+  return DISTDL_OK;
+}
+
+int distdl_debug_conv_kernels(const distdl_plan* plan, int aligned, int32_t out[3]) {
+  if (!plan || !out) return set_error(DISTDL_ERR_NULL, "conv_kernels: null argument");
+  if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_kernels: plan has no kernel");
+  auto code = [](Corr c) { return c == Corr::kMfma ? 1 : c == Corr::k16 ? 2 : c == Corr::kSplit ? 3 : c == Corr::kAny ? 4 : 0; };
+  out[0] = code(choose_fwd(plan, aligned != 0, aligned != 0));
+  out[1] = code(choose_data(plan, aligned != 0));
+  const Wgrad w = choose_wgrad(plan, aligned && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0);
+  out[2] = w == Wgrad::kMfma ? 1 : w == Wgrad::k16 ? 2 : w == Wgrad::kSplit ? 3 : w == Wgrad::kAny ? 4 : 0;
   return DISTDL_OK;
 }
 
@@ -364,24 +398,15 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
   // 16-byte pieces on both sides: the matrix-core kernels load x in them and store y in them
   bool xvec = true;
   for (int w = 0; w < plan->n_workers; ++w) xvec &= (uintptr_t)x_bufs_dev[w] % 16 == 0 && (uintptr_t)y_dev[w] % 16 == 0;
-  const bool aligned = xvec && (uintptr_t)w_dev % 16 == 0;
-  if (corr16_fwd_supported(plan, xvec)) {  // few channels: 16 x 16 tiles
-    if ((rc = conv_fwd16(plan, (const float*)w_dev, (const float*)bias_dev, xvec, st))) return rc;
-    DISTDL_HIP_TRY(hipGetLastError());
-    return DISTDL_OK;
-  }
-  if (xvec && corr_split_supported(plan, false)) {
-    if ((rc = conv_fwd_split(plan, (const float*)w_dev, (const float*)bias_dev, st))) return rc;
-    DISTDL_HIP_TRY(hipGetLastError());
-    return DISTDL_OK;
-  }
-  if (aligned && corr_mfma_supported(plan)) {
-    if ((rc = conv_fwd_mfma(plan, w_dev, bias_dev, st))) return rc;
-    DISTDL_HIP_TRY(hipGetLastError());
-    return DISTDL_OK;
-  }
-  if (conv_any_supported(plan)) {
-    if ((rc = conv_fwd_any(plan, w_dev, bias_dev, xvec, st))) return rc;
+  const Corr kernel = choose_fwd(plan, xvec, (uintptr_t)w_dev % 16 == 0);
+  if (kernel != Corr::kDirect) {
+    switch (kernel) {
+      case Corr::k16: rc = conv_fwd16(plan, (const float*)w_dev, (const float*)bias_dev, xvec, st); break;
+      case Corr::kSplit: rc = conv_fwd_split(plan, (const float*)w_dev, (const float*)bias_dev, st); break;
+      case Corr::kMfma: rc = conv_fwd_mfma(plan, w_dev, bias_dev, st); break;
+      default: rc = conv_fwd_any(plan, w_dev, bias_dev, xvec, st);
+    }
+    if (rc) return rc;
     DISTDL_HIP_TRY(hipGetLastError());
     return DISTDL_OK;
   }
@@ -424,25 +449,19 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   ConvDev c = conv_params(plan);
   bool aligned = true;  // dy is loaded, dx^ stored in 16-byte pieces
   for (int w = 0; w < plan->n_workers; ++w) aligned &= (uintptr_t)dy_dev[w] % 16 == 0 && (uintptr_t)dx_bufs_dev[w] % 16 == 0;
-  const bool data_mfma = aligned && corr_mfma_supported(plan);
   bool vec16 = aligned && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
   for (int w = 0; w < plan->n_workers; ++w) vec16 &= (uintptr_t)x_bufs_dev[w] % 16 == 0;
   const Wgrad wgrad = choose_wgrad(plan, vec16);
   // [dConv]* with respect to x, into the whole padded buffers
   int64_t total = plan->n_b * plan->max_buf_cells * c.ci;
-  // Few channels and several stride classes: the 16 x 16 kernel takes a launch (with planes of taps, two) for each, the others
-  // two in all, which is what counts up to 2^18 cells for four classes (us; 4 -> 16 channels, 3 x 3, stride 2, 12 x 28 x 29:
-  // 41 and 16; 2 -> 6, 2 x 772 x 887: 74 and 118).
-  const int64_t classes = (int64_t)plan->stride[0] * plan->stride[1] * plan->stride[2];
-  const bool together = classes >= 4 && plan->n_workers * plan->n_b * plan->max_buf_cells <= (classes << 16) &&
-                        ((aligned && corr_split_supported(plan, true)) || conv_any_supported(plan));
-  if (!together && corr16_bwd_supported(plan, aligned)) {
+  const Corr kernel = choose_data(plan, aligned);
+  if (kernel == Corr::k16) {
     if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
-  } else if (aligned && corr_split_supported(plan, true)) {
+  } else if (kernel == Corr::kSplit) {
     if ((rc = conv_bwd_data_split(plan, (const float*)w_dev, st))) return rc;
-  } else if (data_mfma) {
+  } else if (kernel == Corr::kMfma) {
     if ((rc = conv_bwd_data_mfma(plan, w_dev, st))) return rc;
-  } else if (conv_any_supported(plan)) {
+  } else if (kernel == Corr::kAny) {
     if ((rc = conv_bwd_data_any(plan, w_dev, aligned, st))) return rc;
   } else {
     if ((rc = prepare_weights(plan, w_dev, st))) return rc;

@@ -1,9 +1,12 @@
 """Helpers for the GPU parity tests: layout marshalling between the oracle's
 logical [n_b, n_c, spatial...] numpy arrays and the library's channels-last
 device buffers, and the parity norms."""
+import itertools
+
 import numpy as np
 import torch
 
+import paper_2006_03108_amd as dd
 from oracle import geometry as geo
 
 
@@ -43,3 +46,51 @@ def rel_errors(got, want):
 def assert_close(got, want, tol, what=""):
     l2, mx = rel_errors(got, want)
     assert l2 <= tol and mx <= tol, f"{what}: rel l2 {l2:.3e}, rel max {mx:.3e} > {tol:.1e}"
+
+
+class ConvLayer:
+    """A convolution layer on one worker, its tensors padded and channels-last, N(0, 1) values; exact() gives the same in
+    fp64 on the device, tap by tap.  offset: the tensors start that many elements into an allocation."""
+
+    def __init__(self, n_b, c_in, c_out, shape, k, s, dtype=torch.float32, p=None, dil=None, offset=0, seed=11):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        D = len(shape)
+        each = lambda v: list(v) if isinstance(v, (list, tuple)) else [v] * D
+        self.k, self.s, self.D = each(k), each(s), D
+        self.dil = each(1 if dil is None else dil)
+        p = [v // 2 for v in self.k] if p is None else each(p)
+
+        def new(*sizes, random=True):
+            n = int(np.prod(sizes))
+            flat = torch.zeros(n + offset, device="cuda", dtype=dtype)
+            if random:
+                flat.copy_(torch.randn(n + offset, generator=g, device="cuda"))
+            return flat[offset:].view(sizes)
+
+        self.plan = dd.distdl_plan_create(D, n_b, c_in, c_out, shape, (1,) * D, self.k, self.s, p, self.dil, dtype)
+        geo_ = self.plan.query(0)
+        self.bulk = (slice(None), *(slice(a, a + n) for a, n in zip(geo_["bulk_off"], shape)))
+        self.x = new(n_b, *geo_["buf_shape"][:D], c_in, random=False)
+        self.x[self.bulk] = new(n_b, *shape, c_in)
+        self.w, self.dy = new(c_out, c_in, *self.k), new(n_b, *geo_["out_size"][:D], c_out)
+        self.y, self.dx, self.dw, self.db = (new(*t, random=False) for t in (self.dy.shape, self.x.shape, self.w.shape, (c_out,)))
+        self.ws = torch.empty(max(dd.distdl_conv_bwd_workspace(self.plan), 16), dtype=torch.uint8, device="cuda")
+
+    def run(self):
+        """y, dx (of the owned cells), dw; db stays in self.db"""
+        dd.distdl_conv_fwd(self.plan, [self.x], self.w, None, [self.y])
+        dd.distdl_conv_bwd(self.plan, [self.x], self.w, [self.dy], [self.dx], self.dw, self.db, self.ws)
+        return self.y, self.dx[self.bulk], self.dw
+
+    def exact(self):
+        x, w, dy = self.x.double(), self.w.double(), self.dy.double()
+        y, dx, dw = torch.zeros_like(dy), torch.zeros_like(x), torch.zeros_like(w)
+        rows = dy.reshape(-1, dy.shape[-1])
+        for t in itertools.product(*[range(k) for k in self.k]):
+            at = (slice(None), *(slice(i * d, i * d + (n - 1) * s + 1, s) for i, d, n, s in zip(t, self.dil, dy.shape[1:], self.s)))
+            wt = w[(slice(None), slice(None), *t)]
+            cells = x[at].reshape(-1, x.shape[-1])
+            y += (cells @ wt.t()).view_as(dy)
+            dx[at] += (rows @ wt).view_as(x[at])
+            dw[(slice(None), slice(None), *t)] = rows.t() @ cells
+        return y, dx[self.bulk], dw

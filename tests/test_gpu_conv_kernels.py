@@ -1,0 +1,89 @@
+"""Each kernel of the convolution layer at shapes where the library picks it: the tiers that take what the split and gather
+kernels do not (strides beyond theirs here, tensors of 2 GiB and more in earnest), and the weight gradients of the 16-wide
+and of the bf16 tiles, which small layers do not reach.  Against fp64 on the device, by the bars of the other parity tests."""
+import pytest
+import torch
+
+import paper_2006_03108_amd as dd
+from tests.gpu_util import ConvLayer, require_gpu
+
+pytestmark = pytest.mark.gpu
+F32, BF16 = torch.float32, torch.bfloat16
+TOL = {F32: 1e-5, BF16: 2e-2}
+
+# (kernels of the forward pass, data gradient, weight gradient: 0 direct, 1 32-wide tiles, 2 16-wide tiles, 3 split, 4 gather),
+# batch, channels, extents, kernel, stride, padding, dilation, type, elements into the allocation
+CASES = [
+    # direct kernels, both types, aligned or not; the weight gradient's operands read from memory (3, 5, 8 taps in a row)
+    ((0, 0, 0), 2, 17, 19, (60, 66), (9, 9), (9, 9), 0, 1, F32, 0),
+    ((0, 0, 0), 1, 3, 4, (61, 65), (9, 9), (9, 9), 4, 1, F32, 1),
+    ((0, 0, 0), 2, 32, 32, (60, 66), (3, 3), (9, 9), 1, 1, BF16, 0),
+    ((0, 0, 0), 1, 5, 7, (50, 49), (4, 5), (9, 9), 0, (1, 2), BF16, 1),
+    ((0, 0, 1), 2, 32, 32, (60, 66), (3, 3), (9, 9), 0, 1, F32, 0),
+    ((0, 0, 1), 2, 17, 19, (60, 66), (5, 5), (9, 9), 0, 1, F32, 0),
+    ((2, 2, 1), 1, 3, 4, (60, 66), (7, 7), (9, 9), 0, 1, F32, 1),
+    # fp32 32-wide tiles, one launch for each of up to 108 classes; the weight gradient staged in LDS (3 and 5 taps in a row)
+    ((1, 1, 1), 1, 32, 36, (30, 31, 40), (2, 2, 3), (9, 9, 1), (0, 0, 1), 1, F32, 0),
+    ((1, 1, 1), 1, 20, 8, (30, 31, 44), (2, 2, 5), (9, 9, 2), (0, 0, 2), 1, F32, 0),
+    ((1, 1, 1), 1, 8, 24, (42, 50, 54), (2, 2, 3), (9, 3, 4), 0, 1, F32, 0),
+    ((1, 1, 3), 1, 40, 36, (46, 43, 50), (3, 3, 3), (9, 2, 4), 1, 1, F32, 0),
+    ((1, 1, 4), 1, 32, 32, (60, 64), (3, 3), (1, 1), 12, 12, F32, 0),
+    # 16-wide weight gradient: aligned and not, one dimension, odd channels
+    ((2, 2, 2), 2, 16, 16, (192, 224), (3, 3), (1, 1), 1, 1, F32, 0),
+    ((2, 2, 2), 24, 16, 12, (36, 42), (3, 3), (1, 1), 1, 1, F32, 1),
+    ((2, 2, 2), 24, 13, 16, (36, 42), (3, 3), (1, 1), 1, 1, F32, 0),
+    ((2, 2, 2), 1, 4, 8, (48, 56), (1, 1), (1, 1), 0, 1, F32, 0),
+    ((2, 2, 2), 16, 16, 16, (300,), (3,), (1,), 1, 1, F32, 0),
+    # bf16 weight gradient, a kernel plane per workgroup: 9, 16 and 25 taps, row strides of 1 and 2, several channel tiles
+    ((1, 1, 1), 1, 64, 64, (96, 112), (3, 3), (1, 1), 1, 1, BF16, 0),
+    ((1, 1, 1), 6, 8, 24, (144, 168), (3, 3), (2, 2), 1, 1, BF16, 0),
+    ((1, 1, 1), 1, 64, 64, (72, 84), (4, 4), (1, 1), 2, 1, BF16, 0),
+    ((1, 1, 1), 1, 64, 64, (144, 168), (4, 4), (2, 2), 2, 1, BF16, 0),
+    ((1, 1, 1), 1, 64, 64, (48, 56), (5, 5), (1, 1), 2, 1, BF16, 0),
+    ((1, 1, 1), 1, 64, 64, (96, 112), (5, 5), (2, 2), 2, 1, BF16, 0),
+    ((1, 1, 1), 1, 32, 32, (24, 28, 34), (3, 5, 5), (2, 2, 2), (1, 2, 2), 1, BF16, 0),
+    ((1, 1, 1), 1, 32, 32, (36, 42, 51), (2, 4, 4), (1, 1, 1), (1, 2, 2), 1, BF16, 0),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"{c[2]}-{c[3]}k{'x'.join(map(str, c[5]))}s{'x'.join(map(str, c[6]))}{str(c[9])[6:]}o{c[10]}" for c in CASES])
+def test_conv_kernel_against_fp64(case):
+    require_gpu()
+    want_kernels, n_b, c_in, c_out, shape, k, s, p, dil, dtype, offset = case
+    L = ConvLayer(n_b, c_in, c_out, shape, k, s, dtype, p, dil, offset)
+    assert dd.distdl_debug_conv_kernels(L.plan, aligned=offset == 0) == want_kernels
+    L.y.fill_(7.0), L.dx.fill_(5.0), L.dw.fill_(9.0), L.db.fill_(9.0)
+    exact = L.exact()
+    for name, got, want in zip(("y", "dx", "dw"), L.run(), exact):
+        diff = got.double() - want
+        assert float(diff.norm() / want.norm()) < TOL[dtype], name
+        assert float(diff.abs().max() / want.abs().max()) < TOL[dtype], name
+    db = L.dy.double().reshape(-1, c_out).sum(0)
+    assert float((L.db.double() - db).norm() / db.norm()) < TOL[dtype]
+
+
+@pytest.mark.parametrize("P_fo,P_fi", [(1, 9), (9, 1), (9, 10)])
+@pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
+def test_affine_of_more_segments_than_a_product_takes(P_fo, P_fi, dtype):
+    """Nine and more blocks to sum over: the direct kernels."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(12)
+    n_b, n_fi, n_fo = 13, 101, 95
+    cut = lambda t, parts, dim: [v.contiguous() for v in torch.tensor_split(t, parts, dim)]
+    x, W, b, dy = (torch.randn(sh, generator=g, device="cuda").to(dtype) for sh in ((n_b, n_fi), (n_fo, n_fi), (n_fo,), (n_b, n_fo)))
+    xs, dys, bs = cut(x, P_fi, 1), cut(dy, P_fo, 1), cut(b, P_fo, 0)
+    Ws = [t for r in cut(W, P_fo, 0) for t in cut(r, P_fi, 1)]
+    y, dx, dW, db = ([torch.empty_like(t) for t in ts] for ts in (dys, xs, Ws, bs))
+    plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, dtype)
+    dd.distdl_profile_enable(True)
+    dd.distdl_profile_report()
+    dd.distdl_affine_fwd(plan, xs, Ws, bs, y)
+    dd.distdl_affine_bwd(plan, xs, Ws, dys, dx, dW, db)
+    names = set(dd.distdl_profile_report())
+    dd.distdl_profile_enable(False)
+    assert ("affine_fwd_direct" in names) == (P_fi > 8) and ("affine_bwd_direct" in names) == (P_fo > 8)
+    x, W, b, dy = (t.double() for t in (x, W, b, dy))
+    whole = lambda ts: torch.cat([t.double() for t in ts], -1)
+    rows = [torch.cat([t.double() for t in dW[i * P_fi:(i + 1) * P_fi]], 1) for i in range(P_fo)]
+    for got, want in ((whole(y), x @ W.t() + b), (whole(dx), dy @ W), (torch.cat(rows, 0), dy.t() @ x), (whole(db), dy.sum(0))):
+        assert float((got - want).norm() / want.norm()) < TOL[dtype]

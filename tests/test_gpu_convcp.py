@@ -16,7 +16,7 @@ TOL32 = 1e-5
 
 CASES = [
     # D, n_b, ci, co, n, P, Pco, Pci, k, s, p
-    (2, 2, 5, 4, (9, 8), (2, 2), 2, 2, (3, 3), (1, 1), (1, 1)),              # direct kernels (odd channel blocks)
+    (2, 2, 5, 4, (9, 8), (2, 2), 2, 2, (3, 3), (1, 1), (1, 1)),              # few channels, odd blocks of them
     (1, 2, 6, 7, (11,), (3,), 3, 2, (5,), (2,), (2,)),
     (3, 1, 64, 64, (16, 14, 18), (2, 1, 2), 2, 2, (3, 3, 3), (2, 1, 1), (1, 1, 1)),   # MFMA kernels, 32-channel blocks
     (2, 2, 16, 24, (20, 20), (2, 2), 1, 2, (3, 3), (1, 1), (1, 1)),          # only the sum-reduce over P_ci

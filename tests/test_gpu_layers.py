@@ -30,9 +30,13 @@ def _off_by_one_element(shape, value, dtype):
     return flat[1:].view(shape)
 
 
-def _run_conv(cfg, part, case, use_bias, dtype=torch.float32, misaligned_outputs=False):
-    plan = dd.distdl_plan_create(cfg["D"], cfg["n_b"], cfg["c_in"], cfg["c_out"], cfg["in_shape"], cfg["P"],
+def _plan(cfg, dtype):
+    return dd.distdl_plan_create(cfg["D"], cfg["n_b"], cfg["c_in"], cfg["c_out"], cfg["in_shape"], cfg["P"],
                                  cfg["ksize"], cfg["stride"], cfg["padding"], cfg["dilation"], dtype)
+
+
+def _run_conv(cfg, part, case, use_bias, dtype=torch.float32, misaligned_outputs=False):
+    plan = _plan(cfg, dtype)
     x_bufs = [to_cl(b, dtype) for b in prim.scatter_bulk(case["x"], part, fill=np.float32(3.0))]
     w = w_to_dev(case["w"]).to(dtype)
     bias = w_to_dev(case["bias"]).to(dtype) if use_bias else None
@@ -95,7 +99,7 @@ CONV_FULL = [
     # a single worker per dimension: no neighbour to exchange with, only the padding to clear
     ("cfg2", dict(in_shape=(40, 44), n_b=1, c_in=16, c_out=16, P=(1, 1)), True),
     ("cfg5", dict(in_shape=(12, 14, 36), P=(1, 1, 1), c_in=32, c_out=32), True),
-    # several channel tiles (the second output tile half full): the weight gradient's shared tap and its db sums
+    # several channel tiles (the second output tile half full): the weight gradient and its db sums
     ("cfg2", dict(in_shape=(40, 70), n_b=2, c_in=64, c_out=48, ksize=(3, 3), padding=(1, 1), P=(2, 2)), True),
     ("cfg2", dict(in_shape=(36, 40), n_b=3, c_in=32, c_out=64, ksize=(5, 5), stride=(2, 2), padding=(2, 2), P=(2, 1)), True),
     # three and four workers per dimension in 3-D: interior workers (halo on both sides of every dimension, no
@@ -103,7 +107,7 @@ CONV_FULL = [
     ("cfg5", dict(in_shape=(40, 38, 44), P=(3, 3, 3)), True),
     ("cfg5u", dict(in_shape=(50, 46, 54), P=(4, 4, 4), c_in=8, c_out=16), False),
     # wide dilated kernels with 32 channels: dilation 12 still finds a (32-wide) window of the matrix-core
-    # correlation, dilation 16 does not and must run on the direct kernels
+    # correlation, dilation 16 does not and must run on the gather kernels
     ("cfg2", dict(in_shape=(60, 64), n_b=1, c_in=32, c_out=32, ksize=(3, 3), padding=(12, 12), dilation=(12, 12)), True),
     ("cfg2", dict(in_shape=(80, 72), n_b=1, c_in=32, c_out=32, ksize=(3, 3), padding=(16, 16), dilation=(16, 16)), True),
 ]
@@ -222,7 +226,7 @@ def test_conv_small_channel_random_layers(cfg):
 
 
 CONV_BF16 = [
-    # matrix-core path (channel counts that are multiples of 4), 3-D strided, 2-D, dilated; then the direct kernels
+    # tiled kernels (channel counts that are multiples of 4), 3-D strided, 2-D, dilated; then the gather kernels
     ("cfg5", dict(in_shape=(24, 22, 40), P=(2, 2, 1), c_in=32, c_out=32), True),
     ("cfg5u", dict(in_shape=(21, 23, 22), P=(2, 2, 2), c_in=32, c_out=32), False),
     ("cfg2", dict(in_shape=(64, 64), n_b=2), True),
@@ -281,10 +285,10 @@ def test_conv_bf16_fwd_bwd_against_partitioned_oracle(name, override, use_bias):
 
 @pytest.mark.parametrize("name,override,dtype", [
     ("cfg2", dict(in_shape=(64, 64), n_b=4), torch.float32),                                   # 16 x 16-tile kernels
-    ("cfg5", dict(in_shape=(24, 22, 40), P=(2, 2, 1)), torch.float32),                          # 32-wide kernels
+    ("cfg5", dict(in_shape=(24, 22, 40), P=(2, 2, 1)), torch.float32),                          # split products
     ("cfg5", dict(in_shape=(24, 22, 40), P=(2, 2, 1)), torch.bfloat16),                         # bf16 matrix cores
-    ("cfg2", dict(in_shape=(19, 23), n_b=3, c_in=3, c_out=5, P=(2, 3), stride=(2, 1)), torch.float32),   # direct kernels
-], ids=["small16", "wide", "bf16", "direct"])
+    ("cfg2", dict(in_shape=(19, 23), n_b=3, c_in=3, c_out=5, P=(2, 3), stride=(2, 1)), torch.float32),   # gather kernels
+], ids=["small16", "wide", "bf16", "gather"])
 def test_conv_is_run_to_run_identical(name, override, dtype):
     """No float atomics anywhere: partial sums are combined in a fixed order (Sec. 2 footnote on floating-point
     addition in parallel), so two runs on the same inputs agree bit for bit."""
@@ -851,6 +855,8 @@ CONV_ANY = [
 @pytest.mark.parametrize("misaligned", [False, True], ids=["aligned", "odd"])
 def test_conv_gather_kernels(cfg, dtype, misaligned):
     require_gpu()
+    kernels = dd.distdl_debug_conv_kernels(_plan(cfg, dtype), not misaligned)
+    assert kernels[2] == 4 and 4 in kernels[:2]
     cfg = dict(cfg, seed=77)
     part = oracle_partition(cfg)
     case = syn.conv_case(cfg, part.global_out_shape())
@@ -888,8 +894,9 @@ CONV_SPLIT = [
 
 @pytest.mark.parametrize("cfg", CONV_SPLIT, ids=lambda c: f"c{c['c_in']}-{c['c_out']}k{'x'.join(map(str, c['ksize']))}s{c['stride'][-1]}d{c['dilation'][-1]}")
 def test_conv_split_kernels(cfg):
-    """fp32 values within a few roundings of a sum of fp32 products: 2^-24 a term at most, far less in the mean."""
+    """By the bar of the other parity tests; how far below it the split products are: test_gpu_split_products.py."""
     require_gpu()
+    assert 3 in dd.distdl_debug_conv_kernels(_plan(cfg, torch.float32))[:2]
     cfg = dict(cfg, seed=78)
     part = oracle_partition(cfg)
     case = syn.conv_case(cfg, part.global_out_shape())

@@ -1,55 +1,16 @@
 """fp32 sums on the split bf16 products: what becomes of infinities, NaNs and very small numbers, how the error grows with
 the length of a sum, and what a pass with an infinity in it costs.  References in fp64 on the device."""
-import itertools
-
 import pytest
 import torch
 
 import paper_2006_03108_amd as dd
-from tests.gpu_util import require_gpu
+from tests.gpu_util import ConvLayer, require_gpu
 
 pytestmark = pytest.mark.gpu
 
 
 def _rel(got, want):
     return float((got.double() - want).norm() / want.norm().clamp_min(1e-300))
-
-
-class _Layer:
-    """A convolution layer on one worker, its tensors padded and channels-last, and the same in fp64, tap by tap."""
-
-    def __init__(self, n_b, c_in, c_out, shape, k, s, seed=11):
-        g = torch.Generator(device="cuda").manual_seed(seed)
-        D, p = len(shape), k // 2
-        self.k, self.s, self.D = k, s, D
-        out = [(n + 2 * p - k) // s + 1 for n in shape]
-        self.plan = dd.distdl_plan_create(D, n_b, c_in, c_out, shape, (1,) * D, (k,) * D, (s,) * D, (p,) * D, (1,) * D)
-        buf = self.plan.query(0)["buf_shape"][:D]
-        self.bulk = (slice(None), *(slice(p, p + n) for n in shape))
-        self.x = torch.zeros(n_b, *buf, c_in, device="cuda")
-        self.x[self.bulk] = torch.randn(n_b, *shape, c_in, generator=g, device="cuda")
-        self.w = torch.randn(c_out, c_in, *[k] * D, generator=g, device="cuda")
-        self.dy = torch.randn(n_b, *out, c_out, generator=g, device="cuda")
-        self.y, self.dx, self.dw = torch.empty_like(self.dy), torch.empty_like(self.x), torch.empty_like(self.w)
-        self.ws = torch.empty(max(dd.distdl_conv_bwd_workspace(self.plan), 16), dtype=torch.uint8, device="cuda")
-
-    def run(self):
-        dd.distdl_conv_fwd(self.plan, [self.x], self.w, None, [self.y])
-        dd.distdl_conv_bwd(self.plan, [self.x], self.w, [self.dy], [self.dx], self.dw, None, self.ws)
-        return self.y, self.dx[self.bulk], self.dw
-
-    def exact(self):
-        x, w, dy = self.x.double(), self.w.double(), self.dy.double()
-        y, dx, dw = torch.zeros_like(dy), torch.zeros_like(x), torch.zeros_like(w)
-        rows = dy.reshape(-1, dy.shape[-1])
-        for t in itertools.product(*[range(self.k)] * self.D):
-            at = (slice(None), *(slice(i, i + (n - 1) * self.s + 1, self.s) for i, n in zip(t, dy.shape[1:])))
-            wt = w[(slice(None), slice(None), *t)]
-            cells = x[at].reshape(-1, x.shape[-1])
-            y += (cells @ wt.t()).view_as(dy)
-            dx[at] += (rows @ wt).view_as(x[at])
-            dw[(slice(None), slice(None), *t)] = rows.t() @ cells
-        return y, dx[self.bulk], dw
 
 
 # (batch, channels, extents, kernel, stride): gather kernels with 256 and 64 rows, patch kernels with one to three M-tiles,
@@ -65,7 +26,7 @@ def test_conv_with_infinities_and_nans(shape):
     other one is the infinity or NaN that fp64 gives."""
     require_gpu()
     n_b, c_in, c_out, n, k, s = shape
-    L = _Layer(*shape)
+    L = ConvLayer(*shape)
     inner, last = L.x[L.bulk], n_b - 1
     inner[(last, *(v // 2 for v in n), 1)], inner[(0, *(v - 1 for v in n), 0)] = float("inf"), float("nan")
     inner[(n_b // 2, *([3] * len(n)), c_in - 1)] = 3.0e38          # finite, and so are its products with 1e-3
@@ -91,7 +52,7 @@ def test_conv_with_a_weight_that_is_not_finite(shape):
     products.)"""
     require_gpu()
     n_b, c_in, c_out, n, k, s = shape
-    L = _Layer(*shape)
+    L = ConvLayer(*shape)
     L.w[(1, 2, *[0] * len(n))], L.w[(c_out - 1, 0, *[k - 1] * len(n))] = float("inf"), float("nan")
     L.w[(c_out // 2, 1, *[k // 2] * len(n))] = float("-inf")
     for name, got, want in zip(("y", "dx"), L.run(), L.exact()):
@@ -107,7 +68,7 @@ def test_conv_of_very_small_numbers(shape, small):
     """Numbers around 1e-36 have as many bits as any other (a bf16 number below 2^-126 = 1.2e-38 has not): 5e-6 is the bound
     of the other tests, far above what these sums show with operands around 1."""
     require_gpu()
-    L = _Layer(*shape)
+    L = ConvLayer(*shape)
     getattr(L, small).mul_(1e-36)
     for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
         assert _rel(got, want) < 5e-6, name
@@ -137,7 +98,7 @@ def test_long_sums_are_not_biased(shape):
     that, and their mean error is far below a rounding (a bf16 MFMA drops bits towards minus infinity: kept in one
     accumulator all its products gave -8e-7)."""
     require_gpu()
-    L = _Layer(*shape)
+    L = ConvLayer(*shape)
     for name, got, want in zip(("y", "dx"), L.run(), L.exact()):
         diff = got.double() - want
         rms = float(want.square().mean().sqrt())
@@ -162,7 +123,7 @@ def test_a_pass_with_nans_costs_what_fp32_products_do():
     """A tile that has to be made again takes fp32 MFMAs, at 6 / 16 of the rate, and a pass over NaNs alone makes every tile
     twice: 1 + 16 / 6 times a clean pass, and twice that is allowed for here.  One infinity touches a few tiles."""
     require_gpu()
-    L = _Layer(2, 32, 32, (64, 64, 64), 3, 1)
+    L = ConvLayer(2, 32, 32, (64, 64, 64), 3, 1)
     clean = _time(L.run)
     L.x[L.bulk][(0, 30, 30, 30, 5)] = float("inf")
     assert _time(L.run) < 3 * clean

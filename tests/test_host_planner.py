@@ -9,6 +9,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2006_03108_amd as dd
 from oracle import geometry as geo
@@ -221,12 +222,12 @@ def test_repartition_plan_blocks_follow_the_balanced_rule_and_errors():
 
 def test_conv_kernel_family_falls_back_when_no_window_fits():
     """Layers whose staged patch fits no window of the matrix-core correlation (wide dilated kernels with many
-    channels) must be routed to the direct kernels by the planner, not fail when the launch is prepared."""
+    channels) are left to the kernels that take any shape by the planner; they do not fail when the launch is prepared."""
     path = lambda *a, **k: dd.distdl_debug_conv_path(dd.distdl_plan_create(*a, **k))
     # the volumetric configuration and the 2-D one: 32-wide and 16-wide matrix-core tiles
     assert path(3, 1, 32, 32, [64, 64, 64], [2, 2, 2], [5] * 3, [2] * 3, [2] * 3, [1] * 3) == (1, 1, 1)
     assert path(2, 8, 16, 16, [256, 256], [2, 2], [3, 3], [1, 1], [1, 1], [1, 1]) == (2, 2, 2)
-    # channel counts that are no multiples of 4: direct kernels throughout (3 -> 5 channels still fit 16-wide tiles)
+    # channel counts that are no multiples of 4: no tiles
     assert path(2, 2, 33, 35, [40, 40], [2, 2], [3, 3], [1, 1], [1, 1], [1, 1])[:2] == (0, 0)
     # k = 3 with dilation 16, k = 7 with dilation 6, 32 channels: the patch of even the narrowest window exceeds
     # the pieces a thread can stage; k = 3 with dilation 3 still fits
@@ -234,6 +235,24 @@ def test_conv_kernel_family_falls_back_when_no_window_fits():
     assert path(2, 1, 32, 32, [90, 90], [2, 2], [7, 7], [1, 1], [18, 18], [6, 6])[:2] == (0, 0)
     assert path(2, 1, 32, 32, [60, 64], [2, 2], [3, 3], [1, 1], [12, 12], [12, 12])[:2] == (1, 1)   # the narrowest window
     assert path(2, 1, 32, 32, [80, 80], [2, 2], [3, 3], [1, 1], [3, 3], [3, 3])[:2] == (1, 1)
+
+
+def test_conv_kernels_for_shapes_at_the_limits():
+    """Which kernels run (0 direct, 1 32-wide tiles, 2 16-wide tiles, 3 split products, 4 gather), where the rules change."""
+    run = lambda *a, aligned=True: dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*a), aligned)
+    f32, bf16 = torch.float32, torch.bfloat16
+    one3 = ([1] * 3,) * 4
+    assert run(3, 1, 32, 32, [256] * 3, [4] * 3, [5] * 3, [2] * 3, [2] * 3, [1] * 3, f32) == (3, 3, 3)
+    assert run(3, 1, 32, 32, [64] * 3, [2] * 3, [5] * 3, [2] * 3, [2] * 3, [1] * 3, f32, aligned=False) == (4, 4, 4)
+    assert run(3, 1, 32, 32, [256] * 3, [4] * 3, [5] * 3, [2] * 3, [2] * 3, [1] * 3, bf16) == (1, 1, 1)
+    # a dilation of 16 fits no staged window
+    assert run(2, 1, 32, 32, [80, 72], [2, 2], [3, 3], [1, 1], [16, 16], [16, 16], f32)[:2] == (4, 4)
+    # 64 stride classes are the last that the gather kernels take, strides of 4 the last of the split ones
+    assert run(2, 2, 17, 19, [60, 66], [1, 2], [9, 9], [8, 8], [0, 0], [1, 1], f32) == (4, 4, 4)
+    assert run(2, 2, 17, 19, [60, 66], [1, 2], [9, 9], [9, 9], [0, 0], [1, 1], f32) == (0, 0, 0)
+    assert run(2, 2, 32, 32, [60, 66], [1, 2], [3, 3], [9, 9], [0, 0], [1, 1], bf16) == (0, 0, 0)
+    # tensors of 2 GiB and more: 32-bit offsets no longer reach every element
+    assert run(3, 1, 17, 20, [512, 512, 240], *one3[:1], [3] * 3, *one3[1:], f32) == (0, 0, 1)
 
 
 def test_table_cache_policy_never_rewrites_a_block_another_reader_may_hold():
