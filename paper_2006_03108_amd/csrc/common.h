@@ -229,6 +229,9 @@ struct DevArray {
   }
 };
 
+// blocks of 256 threads along one dimension of a launch: it has fewer than 2^32 threads there
+constexpr int64_t kMaxBlocks256 = (int64_t(1) << 32) / 256;
+
 // Scratch of a plan's launches: one block per stream, so that calls on two streams may overlap.  A block that is too small
 // for a later call is kept until release(): a recorded graph may hold its address.  (A stream asks for as many sizes as
 // the plan has kinds of call and alignment, so its blocks are few.)

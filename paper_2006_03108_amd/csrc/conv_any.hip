@@ -864,9 +864,9 @@ bool conv_any_supported(const distdl_plan* p) {
   // (k is divided through a float reciprocal: fewer than 2^22)
   if (cls > kMaxCls || taps * (std::max(p->n_ci, p->n_co) + 8) >= (int64_t(1) << 22)) return false;
   if (taps * (p->n_ci + 64) * (p->n_co + 64) >= (int64_t(1) << 28)) return false;
-  for (int mode = 0; mode < 2; ++mode) {  // 32-bit block numbers
-    const AnyArgs a = any_args(p, mode, 1);
-    if ((double)(positions_max(p, a) / 64 + 1) * a.ntn * p->n_workers >= 2147480000.0) return false;
+  for (int mode = 0; mode < 2; ++mode) {  // a launch has fewer than 2^32 threads (64-row tiles: only small layers)
+    const AnyArgs a = any_args(p, mode, nt_of(mode == 0 ? p->n_co : p->n_ci));
+    if ((double)(positions_max(p, a) / 256 + 1) * a.ntn * p->n_workers + 8 >= kMaxBlocks256) return false;
   }
   return p->n_workers <= 65535;
 }

@@ -670,7 +670,7 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
   int64_t tiles = 0;
   for (const WorkerDev& wd : p->workers) tiles = std::max(tiles, tiles_of_worker(derive(wd, a.c), a.c));
   const int64_t blocks = (tiles * p->n_workers + 7) / 8 * 8;
-  if (blocks > 0x7fffff00) return false;
+  if (blocks >= kMaxBlocks256) return false;
   a.c.tiles_max = (int32_t)tiles;
   l.blocks = (unsigned)blocks;
   return true;

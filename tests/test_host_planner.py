@@ -253,6 +253,11 @@ def test_conv_kernels_for_shapes_at_the_limits():
     assert run(2, 2, 32, 32, [60, 66], [1, 2], [3, 3], [9, 9], [0, 0], [1, 1], bf16) == (0, 0, 0)
     # tensors of 2 GiB and more: 32-bit offsets no longer reach every element
     assert run(3, 1, 17, 20, [512, 512, 240], *one3[:1], [3] * 3, *one3[1:], f32) == (0, 0, 1)
+    # more than 2^32 threads in a launch over all workers, each of whose tensors is small
+    many = [3, 1, 17, 17, [1632] * 3, [8] * 3, [3] * 3, [1] * 3, [1] * 3, [1] * 3, f32]
+    assert run(*many) == (0, 0, 1)
+    many[4] = [1280] * 3
+    assert run(*many) == (4, 4, 4)
 
 
 def test_table_cache_policy_never_rewrites_a_block_another_reader_may_hold():
