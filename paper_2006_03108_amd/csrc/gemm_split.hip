@@ -423,6 +423,12 @@ __device__ inline void colsum_16(const ColsumBlock& cb, int f0, float* red) {
   st((std::conditional_t<BF16, uint16_t, float>*)cb.out, f, s);
 }
 
+// A launch of n workgroups: rows of kGridX of them (along one dimension a launch holds fewer than 2^32 threads); the last row
+// may have too many.
+constexpr int kGridX = 1 << 22;
+__device__ inline int workgroup() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
+inline dim3 grid_of_workgroups(int64_t n) { return dim3((unsigned)std::min<int64_t>(n, kGridX), (unsigned)((n + kGridX - 1) / kGridX)); }
+
 // consecutive tiles share rows of an operand: each eighth of a launch's workgroups goes to one XCD (one L2)
 __device__ inline int xcd_order(int wg, int n) {
   return n % 8 == 0 ? (wg & 7) * (n >> 3) + (wg >> 3) : wg;
@@ -431,16 +437,18 @@ __device__ inline int xcd_order(int wg, int n) {
 template <bool BF16, int T, bool VEC>
 __global__ __launch_bounds__(256, 2) void gemm_split_fwd_kernel(SplitGrid g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  gemm_split_tile<BF16, true, true, T, VEC>(g, xcd_order((int)blockIdx.x, (int)gridDim.x), smem);
+  const int b = workgroup(), n = g.tiles * g.nsplit * g.nblocks;
+  if (b < n) gemm_split_tile<BF16, true, true, T, VEC>(g, xcd_order(b, n), smem);
 }
 
 // The adjoint in one launch: the first nx workgroups make dx, the next nw dW, the rest db.  They are independent, and
 // at the sizes that are short of workgroups each is too small to fill the chip alone.
 template <bool BF16, int TX, int TW, bool VEC>
 __global__ __launch_bounds__(256, 2) void gemm_split_bwd_kernel(SplitGrid gx, SplitGrid gw, const ColsumBlock* cs, int nx,
-                                                                int nw, int cs_chunks) {
+                                                                int nw, int n, int cs_chunks) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int b = (int)blockIdx.x;
+  const int b = workgroup();
+  if (b >= n) return;
   if (b < nx) gemm_split_tile<BF16, true, false, TX, VEC>(gx, xcd_order(b, nx), smem);
   else if (b < nx + nw) gemm_split_tile<BF16, false, false, TW, VEC>(gw, xcd_order(b - nx, nw), smem);
   else colsum_16<BF16>(cs[(b - nx - nw) / cs_chunks], (b - nx - nw) % cs_chunks * 16, (float*)smem);
@@ -451,7 +459,8 @@ __global__ __launch_bounds__(256, 2) void gemm_split_bwd_kernel(SplitGrid gx, Sp
 // those of fp32 MFMAs (K = 256: 2.4e-7 against 2.9e-7).
 __global__ __launch_bounds__(256, 3) void gemm_split_dw_kernel(SplitGrid g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  gemm_split_tile<false, false, false, 2, true, false>(g, xcd_order((int)blockIdx.x, (int)gridDim.x), smem);
+  const int b = workgroup(), n = g.tiles * g.nsplit * g.nblocks;
+  if (b < n) gemm_split_tile<false, false, false, 2, true, false>(g, xcd_order(b, n), smem);
 }
 
 // C = sum over the splits, in order, of the partial tiles + bias
@@ -585,7 +594,7 @@ static int fwd_variant(const SplitGrid& g, int wgs, hipStream_t st) {
   constexpr int lds = split_lds(T, BF16);
   if (lds > 64 * 1024)
     if (int rc = allow_large_lds<gemm_split_fwd_kernel<BF16, T, VEC>>()) return rc;
-  hipLaunchKernelGGL((gemm_split_fwd_kernel<BF16, T, VEC>), dim3((unsigned)wgs), dim3(256), lds, st, g);
+  hipLaunchKernelGGL((gemm_split_fwd_kernel<BF16, T, VEC>), grid_of_workgroups(wgs), dim3(256), lds, st, g);
   return DISTDL_OK;
 }
 
@@ -606,8 +615,9 @@ static int bwd_variant(const SplitGrid& gx, const SplitGrid& gw, const ColsumBlo
   constexpr int lds = std::max(split_lds(TX, BF16), split_lds(TW, BF16));
   if (lds > 64 * 1024)
     if (int rc = allow_large_lds<gemm_split_bwd_kernel<BF16, TX, TW, VEC>>()) return rc;
-  hipLaunchKernelGGL((gemm_split_bwd_kernel<BF16, TX, TW, VEC>), dim3((unsigned)(nx + nw + n_cs * cs_chunks)), dim3(256),
-                     lds, st, gx, gw, cs, nx, nw, std::max(cs_chunks, 1));
+  const int n = nx + nw + n_cs * cs_chunks;
+  hipLaunchKernelGGL((gemm_split_bwd_kernel<BF16, TX, TW, VEC>), grid_of_workgroups(n), dim3(256), lds, st, gx, gw, cs, nx, nw, n,
+                     std::max(cs_chunks, 1));
   return DISTDL_OK;
 }
 
@@ -635,7 +645,7 @@ int launch_gemm_split_bwd(const GemmBlock* d_bx, const std::vector<GemmBlock>& b
   else DISTDL_BWD(false, 1, 1, true);
 #undef DISTDL_BWD
   if (rc) return rc;
-  if (dw_alone) hipLaunchKernelGGL(gemm_split_dw_kernel, dim3((unsigned)pw.wgs), dim3(256), split_lds(2, false), st, gw);
+  if (dw_alone) hipLaunchKernelGGL(gemm_split_dw_kernel, grid_of_workgroups(pw.wgs), dim3(256), split_lds(2, false), st, gw);
   launch_reduce(gx, px, bf16, st);
   launch_reduce(gw, pw, bf16, st);
   return DISTDL_OK;

@@ -810,6 +810,25 @@ def test_affine_split_against_fp64(n_b, n_fi, n_fo, P_fo, P_fi, offset):
         assert err(dx[j], sum(dy[i] @ W[i * P_fi + j] for i in range(P_fo))) < 1e-6
 
 
+def test_affine_of_more_workgroups_than_one_dimension_holds():
+    """1.2 * 10^9 features, one sample, one output: dx and dW are 19 million tiles each."""
+    require_gpu()
+    n, P = 1200 * 10 ** 6, 4
+    g = torch.Generator(device="cuda").manual_seed(13)
+    new = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    x, W = [new(1, n // P) for _ in range(P)], [new(1, n // P) for _ in range(P)]
+    dy, y, dx, dW = torch.full((1, 1), 1.5, device="cuda"), torch.empty(1, 1, device="cuda"), [torch.empty_like(t) for t in x], [torch.empty_like(t) for t in W]
+    plan = dd.distdl_affine_plan_create(1, n, 1, 1, P)
+    dd.distdl_affine_fwd(plan, x, W, None, [y])
+    dd.distdl_affine_bwd(plan, x, W, [dy], dx, dW, None)
+    for j in range(P):
+        assert torch.equal(dx[j], 1.5 * W[j]) and torch.equal(dW[j], 1.5 * x[j])
+    want = sum(torch.dot(x[j][0], W[j][0]).double() for j in range(P))
+    # 16 running sums of 7.5e7 products that grow to 10^4, each rounded 4.7e6 times by up to 2^-24 of that: 3e3 if all of them
+    # went one way, far less in fact
+    assert abs(float(y) - float(want)) < 300
+
+
 @pytest.mark.parametrize("n_b,n_fi,n_fo", [(70, 100, 130), (256, 1024, 1024), (37, 333, 77)])
 def test_affine_infinities_and_nans_stay_what_fp32_makes_of_them(n_b, n_fi, n_fo):
     """The split of an infinity, a NaN or a number next to the largest is no number; the sums they enter have to be
