@@ -66,7 +66,9 @@ struct Operand {
   uint32_t line;     // bytes from one row (KC) or k line to the next
   int K;
 
-  // rows r0 ... of an operand with `rows` rows; the resource ends with the operand, so that k lines beyond K read as zero
+  // rows r0 ... of an operand with `rows` rows; the resource ends with the operand, so that k lines beyond K read as zero.
+  // (Lines of a GiB: 64 of them are more than 32 bits; octets of k beyond a K shorter than a stage are left out here, single
+  // lines in load(), and an operand of K >= 64 that is below 2 GiB has lines of at most 32 MiB.)
   __device__ inline void enter(const void* base, int ld, int rows, int K_, int r0, int tid) {
     rs = rsrc_of(base, (uint32_t)(KC ? rows : K_) * (uint32_t)ld * ES);
     line = (uint32_t)ld * ES;
@@ -78,7 +80,7 @@ struct Operand {
         off[i] = r < rows ? (uint32_t)r * line + kp * 8 * ES : kOob;
       } else {
         const int r = r0 + (tid % (R / NP)) * NP + i, kp = tid / (R / NP);
-        off[i] = r < rows ? (uint32_t)(kp * 8) * line + r * ES : kOob;
+        off[i] = r < rows && kp * 8 < K_ ? (uint32_t)(kp * 8) * line + r * ES : kOob;
       }
     }
   }
@@ -120,7 +122,7 @@ struct Stager {
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const uint32_t so = (uint32_t)(k0 + j) * op.line;
+        const uint32_t so = k0 + j < op.K ? (uint32_t)(k0 + j) * op.line : kOob;  // (uniform)
         if constexpr (VEC && NP == 2) {  // the row count is a multiple of 4
           const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(op.rs, op.off[0], so, 0);
           v[0][j] = __uint_as_float(t[0]);

@@ -829,6 +829,18 @@ def test_affine_of_more_workgroups_than_one_dimension_holds():
     assert abs(float(y) - float(want)) < 300
 
 
+@pytest.mark.parametrize("n_b", [1, 3])
+def test_affine_infinities_in_very_long_rows(n_b):
+    """Rows of 600 MB: the lines of samples that do not exist are no terms of dW, whatever address they would have."""
+    require_gpu()
+    n = 150 * 10 ** 6
+    x, W, dy = torch.full((n_b, n), float("inf"), device="cuda"), torch.ones(2, n, device="cuda"), torch.ones(n_b, 2, device="cuda")
+    dx, dW = torch.empty_like(x), torch.empty_like(W)
+    plan = dd.distdl_affine_plan_create(n_b, n, 2, 1, 1)
+    dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], None)
+    assert bool((dW == float("inf")).all()) and bool((dx == 2.0).all())
+
+
 @pytest.mark.parametrize("n_b,n_fi,n_fo", [(70, 100, 130), (256, 1024, 1024), (37, 333, 77)])
 def test_affine_infinities_and_nans_stay_what_fp32_makes_of_them(n_b, n_fi, n_fo):
     """The split of an infinity, a NaN or a number next to the largest is no number; the sums they enter have to be
