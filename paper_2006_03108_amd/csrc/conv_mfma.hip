@@ -1046,13 +1046,12 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __r
 }
 
 // db^ partial of one (worker, chunk): sum of dy over the chunk's positions,
-// written to the slot's trailing Co entries.  One block per slot.
-template <bool BF16>
+// written to the slot's trailing Co entries.  One block per slot.  (fp32: the bf16 kernel sums db^ itself.)
 __global__ __launch_bounds__(256) void bias_partial_kernel(const WorkerDev* __restrict__ workers, void* const* dy_bufs,
                                                            float* __restrict__ partial, WgradArgs a) {
   const int worker = blockIdx.x / a.nchunks, chunk = blockIdx.x - worker * a.nchunks;
   const WorkerDev wd = workers[worker];
-  const void* __restrict__ dy = dy_bufs[worker];
+  const float* __restrict__ dy = (const float*)dy_bufs[worker];
   const int nrows = a.n_b * wd.out[0] * wd.out[1];
   const int per = (nrows + a.nchunks - 1) / a.nchunks;
   const int64_t p0 = (int64_t)chunk * per * wd.out[2];
@@ -1068,8 +1067,8 @@ __global__ __launch_bounds__(256) void bias_partial_kernel(const WorkerDev* __re
       int64_t p = p0 + (threadIdx.x >> 5);
       for (; p + 56 < p1; p += 64)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) part[u] += load_scalar<BF16>(dy, (p + 8 * u) * a.co + co);
-      for (; p < p1; p += 8) part[0] += load_scalar<BF16>(dy, p * a.co + co);
+        for (int u = 0; u < 8; ++u) part[u] += dy[(p + 8 * u) * a.co + co];
+      for (; p < p1; p += 8) part[0] += dy[p * a.co + co];
       acc = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
     }
     red[threadIdx.x] = acc;
@@ -1607,12 +1606,8 @@ int conv_wgrad_mfma(distdl_plan* p, float* partial, hipStream_t st) {
   }
   if (!taps_path) {  // the plane-per-workgroup kernel sums db^ itself
     ProfScope prof("conv_bias_partial", st);
-    if (bf16)
-      hipLaunchKernelGGL(bias_partial_kernel<true>, dim3((unsigned)(p->n_workers * a.nchunks)), dim3(256), 0, st,
-                         p->d_workers, p->tab_dy.dev, partial, a);
-    else
-      hipLaunchKernelGGL(bias_partial_kernel<false>, dim3((unsigned)(p->n_workers * a.nchunks)), dim3(256), 0, st,
-                         p->d_workers, p->tab_dy.dev, partial, a);
+    hipLaunchKernelGGL(bias_partial_kernel, dim3((unsigned)(p->n_workers * a.nchunks)), dim3(256), 0, st, p->d_workers,
+                       p->tab_dy.dev, partial, a);
   }
   return DISTDL_OK;
 }
