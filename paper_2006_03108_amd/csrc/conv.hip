@@ -242,16 +242,16 @@ static Corr choose_fwd(const distdl_plan* p, bool xy_aligned, bool w_aligned) {
 }
 
 static Corr choose_data(const distdl_plan* p, bool aligned) {
-  const bool split = aligned && corr_split_supported(p, true), any = conv_any_supported(p);
+  auto split = [&]() { return aligned && corr_split_supported(p, true); };
   // Few channels and several stride classes: the 16 x 16 kernel takes a launch (with planes of taps, two) for each, the others
   // two in all, which is what counts up to 2^18 cells for four classes (us; 4 -> 16 channels, 3 x 3, stride 2, 12 x 28 x 29:
   // 41 and 16; 2 -> 6, 2 x 772 x 887: 74 and 118).
   const int64_t classes = (int64_t)p->stride[0] * p->stride[1] * p->stride[2];
-  const bool together = classes >= 4 && p->n_workers * p->n_b * p->max_buf_cells <= (classes << 16) && (split || any);
+  const bool together = classes >= 4 && p->n_workers * p->n_b * p->max_buf_cells <= (classes << 16) && (split() || conv_any_supported(p));
   if (!together && corr16_bwd_supported(p, aligned)) return Corr::k16;
-  if (split) return Corr::kSplit;
+  if (split()) return Corr::kSplit;
   if (aligned && corr_mfma_supported(p)) return Corr::kMfma;
-  return any ? Corr::kAny : Corr::kDirect;
+  return conv_any_supported(p) ? Corr::kAny : Corr::kDirect;
 }
 
 // The kernel of the weight gradient: of those that take the layer, the one whose estimated time (us) is the lowest.  The
