@@ -225,11 +225,12 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
   };
   // db of this chunk: the workgroups of plane 0 and channel chunk 0 see each dy element of their columns once
   const bool bias_wg = t0 == 0 && cic == 0;
-  float bsum[NY][4];
+  // (a unit's sums on their own first: one running sum over all steps is further off)
+  float bsum[NY][4], btotal[NY][4];
 #pragma unroll
   for (int i = 0; i < NY; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bsum[i][j] = 0.f;
+    for (int j = 0; j < 4; ++j) bsum[i][j] = btotal[i][j] = 0.f;
   uint32_t nslot = 0;  // ring place of the step's new row 0
   auto wrap = [&](uint32_t at) { return min(at, at - ringb); };  // at < 2 ringb
   auto stash = [&](auto raw, uint32_t odd) {
@@ -269,6 +270,11 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
     const int unit = unit_begin + (uj + skew < unit_cnt ? uj + skew : uj + skew - unit_cnt);
     const int plane = unit / nblk1, o1_begin = (unit - plane * nblk1) * a.ob, o1_end = min(O1, o1_begin + a.ob);
     const int o0 = plane % wd.out[0], n = plane / wd.out[0];
+    if (bias_wg && !RAW)
+#pragma unroll
+      for (int i = 0; i < NY; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) btotal[i][j] += bsum[i][j], bsum[i][j] = 0.f;
     for (int seg = 0; seg < nseg; ++seg) {
       setup_pieces(seg);
       nslot = (uint32_t)((o1_begin * s1 + a.span - s1) % a.ring) * rowb;
@@ -422,7 +428,7 @@ __global__ __launch_bounds__(64 * NW, 2) void wgrad_split_kernel(const WorkerDev
       const int u = i * TH + tid;
       if (u < NT * 128)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) red[u / (4 * NT) * (16 * NT) + u % (4 * NT) * 4 + j] = bsum[i][j];
+        for (int j = 0; j < 4; ++j) red[u / (4 * NT) * (16 * NT) + u % (4 * NT) * 4 + j] = btotal[i][j] + bsum[i][j];
     }
     __syncthreads();
     if (tid < 16 * NT && co0 + tid < a.co) {
