@@ -23,7 +23,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
-# "f32_split": an fp32 product as six products of bf16 parts (the step fractions of fp32 workloads stay against the fp32 peak)
+# "f32_split": an fp32 product as six products of bf16 parts
 MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "f32_split": 2500.0 / 6}
 
 
@@ -449,7 +449,7 @@ class MovementWorkload:
             timed(name, call, 0, reps=3)
             row = rows[-1]
             row.update({"TFLOP/s": round(nfl / (row["ms"] * 1e-3) / 1e12, 1), "algorithmic_flops": nfl,
-                        "frac_mfma_peak": round(nfl / (row["ms"] * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS["f32"], 3),
+                        "frac_mfma_peak": round(nfl / (row["ms"] * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS["f32_split"], 3),
                         "config": "64->64 channels, P_co x P_ci = 2 x 2, 128^3 over 2x2x2 workers, 5^3 stride 2"})
             for key in ("GB/s", "frac_hbm_peak", "algorithmic_bytes"):
                 row.pop(key)
@@ -691,6 +691,12 @@ def kernel_rooflines(workload, report, traffic, steps):
     return out
 
 
+def step_peak(rep):
+    """The peak that a step's fraction is of: that of the matrix instructions of its longest contraction."""
+    mfma = [k for k in rep["kernels"].values() if k.get("bound") == "mfma"]
+    return MFMA_PEAK_TFLOPS[max(mfma, key=lambda k: k["total_ms"])["mfma_dtype"] if mfma else rep["dtype"]]
+
+
 def load_traffic():
     """HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by the
     readings of a plain 1 GiB copy (summaries and commands under profiles/); keyed
@@ -895,7 +901,7 @@ def compact_line(detail, workload):
             line["movement_ms_per_step"] = r3(mv["ms_per_step"])
             kernel_scalars(mv["kernels"])
     if "TFLOP" in detail["unit"]:
-        line["step_frac_mfma"] = r3(detail["value"] / MFMA_PEAK_TFLOPS[detail["dtype"]])
+        line["step_frac_mfma"] = r3(detail["value"] / step_peak(detail))
     if mv:
         for name, k in mv.get("layout", {}).items():
             line[f"{name}_GBs"], line[f"{name}_frac_hbm"] = r3(k["achieved"]), r3(k["frac"])
@@ -909,10 +915,10 @@ def compact_line(detail, workload):
         if rep.get("ms_per_step_graph"):
             line[f"{key}_ms_per_step_graph"] = r3(rep["ms_per_step_graph"])
         if "TFLOP" in rep["unit"]:
-            line[f"{key}_frac_mfma"] = r3(rep["value"] / MFMA_PEAK_TFLOPS[rep["dtype"]])
+            line[f"{key}_frac_mfma"] = r3(rep["value"] / step_peak(rep))
             if rep.get("ms_per_step_graph"):
                 line[f"{key}_frac_mfma_graph"] = r3(rep["value"] * rep["ms_per_step"] / rep["ms_per_step_graph"] /
-                                                    MFMA_PEAK_TFLOPS[rep["dtype"]])
+                                                    step_peak(rep))
         for name, k in rep["kernels"].items():
             if k.get("bound") == "mfma":
                 line[f"{key}_{name}_frac_mfma"] = r3(k["frac"])

@@ -5,8 +5,13 @@
 //
 // Layout: channels-last.  x^ is [n_b][B0][B1][B2][Ci], y is [n_b][O0][O1][O2][Co],
 // weights arrive as [Co][Ci][T] (T = taps, last fastest) and are re-laid out
-// once per call into wt[T][Ci][Co] so that the output-channel axis is the
+// once per call: by each family of kernels in its own order, by the direct
+// kernels here into wt[T][Ci][Co], so that the output-channel axis is the
 // contiguous one.
+//
+// This file: the calls, the choice of kernels, the reduction of dw / db, and
+// the direct kernels, which take what no other does (tensors of 2 GiB and
+// more, over 64 stride classes).
 #include <algorithm>
 
 #include "common.h"
@@ -254,15 +259,17 @@ static Corr choose_data(const distdl_plan* p, bool aligned) {
   return conv_any_supported(p) ? Corr::kAny : Corr::kDirect;
 }
 
-// The kernel of the weight gradient: of those that take the layer, the one whose estimated time (us) is the lowest.  The
-// estimates follow 80 measured layers of 1 to 64 channels, one to three dimensions, 10^2 to 10^7 positions:
+// The kernel of the weight gradient: of those that take the layer, the one whose estimated time (us) is the lowest:
 //   16 x 16 tiles: a set-up that grows with the taps of a plane, then 7 ps per tap and position (12 with several planes);
 //   gather: workgroups of 32-position stages, 2.4 us a stage while all compute units are busy, twice that with two
 //     column tiles (bf16: about half of that);
 //   bf16 planes: 1.2 us a step of 32 positions or its matrix instructions;
 //   split planes: its own estimate counts matrix instructions; 1.6 times that was taken.
-// 16 -> 16 channels, 3 x 3, 8 x 256 x 256: 38.7 / 83 / 47 us; 4 -> 8, 5^3, 7 x 31 x 23 x 28: 212 / 46 / 83; 32 -> 32, 5^3,
-// stride 2, 256^3: - / 5030 / 3110; 16 -> 4 channels, one dimension, 3 x 42626: - / 25 / 517.
+// Measured on 80 layers of 1 to 64 channels, one to three dimensions, 10^3 to 10^6 positions, every kernel that takes each: the
+// choice is the fastest for 69 and within 8 % of it for 76; the others: 6 -> 16 (fp32) and 64 -> 64 (bf16), 2 x 60 x 64, 18 %,
+// bf16 32 -> 32, 2 x 256 x 256, 49 us for 38 and, 5 x 5 with stride 2, 43 for 25.  us, 16 x 16 / gather / split:
+// 16 -> 16 channels, 3 x 3, 8 x 256 x 256: 38.7 / 83 / 47; 64 -> 64, 3^3, 2 x 40 x 44 x 48: - / 384 / 240; 16 -> 4, one
+// dimension, 2 x 4000: - / 17 / 111; 32 -> 32, 5^3, stride 2, 256^3: - / 5030 / 3110.
 enum class Wgrad { k16, kSplit, kAny, kMfma, kDirect };
 
 static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {

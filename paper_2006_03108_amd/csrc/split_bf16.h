@@ -6,7 +6,8 @@
 // bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019):
 //     x = hi + mid + lo,   hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid)   (the differences are exact)
 // so x * w is nine products of bf16 numbers.  The three smallest, mid * lo, lo * mid and lo * lo, are below 2^-25 |x w|
-// and are left out: six MFMAs, smallest products first.  (Short sums therefore know a product to about half an ulp.)
+// and are left out: six MFMAs, smallest products first.  (With all nine the error of a sum of 64 terms is 1.12e-7, with six
+// 1.13e-7, with fp32 MFMAs 1.53e-7.)
 //
 // What an MFMA does with them (measured): a product of two bf16 numbers has 16 bits, but bits that lie far below the
 // largest operand of the instruction, the accumulator among them, are dropped towards minus infinity, where fp32 MFMAs
