@@ -175,8 +175,7 @@ struct SplitGrid {
   int32_t tiles, nsplit, nblocks;
 };
 
-// TWO: two accumulators per output.
-template <bool BF16, bool A_KC, bool B_KC, int T, bool VEC, bool TWO = !BF16>
+template <bool BF16, bool A_KC, bool B_KC, int T, bool VEC>
 __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem) {
   typedef Stager<BF16, A_KC, T, VEC> SA;
   typedef Stager<BF16, B_KC, T, VEC> SB;
@@ -255,12 +254,11 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
           c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[pb][j].v, fa[pa][i].v, c[i][j], 0, 0, 0);
     };
     if constexpr (!BF16) {
-      auto& c = TWO ? low : acc;
-      mm(c, 2, 0);
-      mm(c, 0, 2);
-      mm(c, 1, 1);
-      mm(c, 1, 0);
-      mm(c, 0, 1);
+      mm(low, 2, 0);
+      mm(low, 0, 2);
+      mm(low, 1, 1);
+      mm(low, 1, 0);
+      mm(low, 0, 1);
     }
     mm(acc, 0, 0);
   };
@@ -305,7 +303,7 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
           for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-              if constexpr (TWO) acc[i][j] += low[i][j];
+              acc[i][j] += low[i][j];
 #pragma unroll
               for (int v = 0; v < 16; ++v) seen = note_not_finite(acc[i][j][v] *= kUnsplit, seen);
             }
@@ -454,15 +452,6 @@ __global__ __launch_bounds__(256, 2) void gemm_split_bwd_kernel(SplitGrid gx, Sp
   if (b < nx) gemm_split_tile<BF16, true, false, TX, VEC>(gx, xcd_order(b, nx), smem);
   else if (b < nx + nw) gemm_split_tile<BF16, false, false, TW, VEC>(gw, xcd_order(b - nx, nw), smem);
   else colsum_16<BF16>(cs[(b - nx - nw) / cs_chunks], (b - nx - nw) % cs_chunks * 16, (float*)smem);
-}
-
-// dW alone, for launches of many tiles and a short K: one accumulator per output leaves room for a third workgroup on a
-// compute unit (180 against 189 us for the layer at 256 x 4096 x 4096), and at K <= 512 its sums are no further off than
-// those of fp32 MFMAs (K = 256: 2.4e-7 against 2.9e-7).
-__global__ __launch_bounds__(256, 3) void gemm_split_dw_kernel(SplitGrid g) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int b = workgroup(), n = g.tiles * g.nsplit * g.nblocks;
-  if (b < n) gemm_split_tile<false, false, false, 2, true, false>(g, xcd_order(b, n), smem);
 }
 
 // C = sum over the splits, in order, of the partial tiles + bias
@@ -632,12 +621,7 @@ int launch_gemm_split_bwd(const GemmBlock* d_bx, const std::vector<GemmBlock>& b
   const int chunks = d_cs ? (max_f + 15) / 16 : 0;
   if (!d_cs) n_cs = 0;
   int rc;
-  // many tiles (the chip runs 768 at a time) and a short K: dW in a launch of its own, see the kernel
-  int max_k = 0;
-  for (const GemmBlock& b : bw) max_k = std::max(max_k, b.seg[0].K);
-  const bool dw_alone = px.T == 2 && pw.T == 2 && pw.nsplit == 1 && pw.wgs >= 768 && max_k <= 512;
-  const int nw = dw_alone ? 0 : pw.wgs;
-#define DISTDL_BWD(BF_, TX_, TW_, V_) rc = bwd_variant<BF_, TX_, TW_, V_>(gx, gw, d_cs, px.wgs, nw, n_cs, chunks, st)
+#define DISTDL_BWD(BF_, TX_, TW_, V_) rc = bwd_variant<BF_, TX_, TW_, V_>(gx, gw, d_cs, px.wgs, pw.wgs, n_cs, chunks, st)
   const bool vec = px.vec && pw.vec;
   if (bf16) DISTDL_BWD(true, 1, 1, false);
   else if (!vec) DISTDL_BWD(false, 1, 1, false);
@@ -647,7 +631,6 @@ int launch_gemm_split_bwd(const GemmBlock* d_bx, const std::vector<GemmBlock>& b
   else DISTDL_BWD(false, 1, 1, true);
 #undef DISTDL_BWD
   if (rc) return rc;
-  if (dw_alone) hipLaunchKernelGGL(gemm_split_dw_kernel, grid_of_workgroups(pw.wgs), dim3(256), split_lds(2, false), st, gw);
   launch_reduce(gx, px, bf16, st);
   launch_reduce(gw, pw, bf16, st);
   return DISTDL_OK;
