@@ -319,12 +319,7 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
         gemm_split_usable(bx, bf16, true, false) && gemm_split_usable(bw, bf16, false, false)) {
       const bool vec = gemm_split_vec(bx, bf16, true, false) && gemm_split_vec(bw, bf16, false, false);
       const GemmSplitPlan px = gemm_split_plan(bx, vec);
-      GemmSplitPlan pw = gemm_split_plan(bw, vec);
-      // At most 32 samples: dW is bound by writing it, and the fp32 kernel that holds four 32 KB workgroups per compute
-      // unit writes faster than the split one with three of 49 KB (4096 x 4096 per worker, 16 samples: 57 against 92 us;
-      // 2048 x 2048: 16 samples 20 against 23 us, 32 equal, 64 samples 31 against 28 us).
-      const bool dw_stream = !bf16 && vec && pw.T == 2 && p->n_b <= 32 && gemm_stream_usable(bw, false, false, false);
-      if (dw_stream) pw.wgs = 0, pw.nsplit = 1, pw.partial_floats = 0;
+      const GemmSplitPlan pw = gemm_split_plan(bw, vec);
       if ((rc = p->g_dx.upload(bx, st_)) || (rc = p->g_dw.upload(bw, st_)) || (db_dev && (rc = p->g_db.upload(bb, st_))) ||
           (rc = p->partial.get(px.partial_floats + pw.partial_floats, st_, &partial)))
         return rc;
@@ -332,10 +327,6 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       if ((rc = launch_gemm_split_bwd(p->g_dx.dev, bx, px, p->g_dw.dev, bw, pw, cs, p->P_fo, (int)p->max_fo, bf16,
                                       partial, st_)))
         return rc;
-      if (dw_stream) {
-        ProfScope prof("affine_bwd_w_mfma", st_);
-        if ((rc = launch_gemm_stream_tt(p->g_dw.dev, bw, false, nullptr, 0, 0, st_))) return rc;
-      }
       DISTDL_HIP_TRY(hipGetLastError());
       return DISTDL_OK;
     }

@@ -45,15 +45,15 @@ struct GemmColsum {
 int launch_gemm_mfma(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc,
                      int nsplit, float* partial, const char* name, hipStream_t st, GemmColsum* colsum = nullptr);
 // The small-batch path (gemm_stream.hip): 64 x 64 tiles over the whole K range, every wave its own K-slice pipeline
-// fed by global -> LDS loads, bf16 or fp32.  Usable when A is contiguous along K and every K (and, for an N-contiguous
-// B, N) is a multiple of a 16-byte piece (8 bf16, 4 fp32); with both operands as k lines (weight gradient, bf16 only):
-// one segment, M and N multiples of 8.
-bool gemm_stream_usable(const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc);
+// fed by global -> LDS loads, bf16.  Usable when A is contiguous along K and every K (and, for an N-contiguous B, N) is
+// a multiple of a 16-byte piece (8 elements); with both operands as k lines (weight gradient): one segment, M and N
+// multiples of 8.
+bool gemm_stream_usable(const std::vector<GemmBlock>& blocks, bool a_kc, bool b_kc);
 int launch_gemm_stream(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool b_kc,
                        hipStream_t st);
 // the weight-gradient layout (both operands as k lines), 128 x 128 tiles
 // d_colsum (or null): column sums (the bias gradient) computed by extra workgroups of the same launch
-int launch_gemm_stream_tt(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool bf16,
+int launch_gemm_stream_tt(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks,
                           const ColsumBlock* d_colsum, int n_colsum, int max_f, hipStream_t st);
 // Any shape and alignment (gemm_split.hip): fp32 operands on the bf16 matrix cores, bf16 ones as they are.
 struct GemmSplitPlan {

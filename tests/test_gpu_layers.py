@@ -775,7 +775,7 @@ def test_conv_step_replayed_from_a_graph_matches_eager(dtype):
 
 
 # K tails of 1 .. 15, tiles of 64 and 128 with remainders, K split over workgroups, two and more segments, operands
-# whose rows are no whole 16-byte pieces; the last ones: dW in a launch of its own, and at most 32 samples
+# whose rows are no whole 16-byte pieces; more tiles of dW than compute units, and at most 32 samples
 AFFINE_SPLIT_CASES = [(1, 1, 1, 1, 1), (2, 17, 3, 1, 1), (65, 129, 67, 2, 3), (64, 64, 64, 1, 1), (63, 1025, 130, 1, 2),
                       (129, 260, 388, 2, 2), (128, 2052, 256, 1, 1), (40, 4100, 68, 1, 4), (260, 3600, 3584, 1, 1),
                       (32, 1028, 1028, 2, 2), (33, 1028, 1028, 2, 2)]
