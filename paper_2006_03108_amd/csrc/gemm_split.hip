@@ -454,38 +454,37 @@ __global__ __launch_bounds__(256, 2) void gemm_split_bwd_kernel(SplitGrid gx, Sp
   else colsum_16<BF16>(cs[(b - nx - nw) / cs_chunks], (b - nx - nw) % cs_chunks * 16, (float*)smem);
 }
 
-// C = sum over the splits, in order, of the partial tiles + bias
-template <bool BF16>
-__global__ __launch_bounds__(256) void gemm_split_reduce_kernel(SplitGrid g) {
-  const GemmBlock& gb = g.blocks[blockIdx.y];
-  const float* pp = g.partial + (int64_t)blockIdx.y * g.nsplit * g.partial_stride;
-  const int64_t mn = (int64_t)gb.M * gb.N;
-  typedef std::conditional_t<BF16, uint16_t, float> Out;
-  if (gb.N % 4 == 0 && ((uintptr_t)gb.c & 15) == 0 && g.partial_stride % 4 == 0 && !BF16) {
-    const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (e >= mn) return;
-    float4 s = *(const float4*)(pp + e);
-    for (int t = 1; t < g.nsplit; ++t) {
-      const float4 u = *(const float4*)(pp + t * g.partial_stride + e);
-      s.x += u.x, s.y += u.y, s.z += u.z, s.w += u.w;
-    }
-    const int col = (int)(e % gb.N);
-    if (gb.bias) {
-      const float* bp = (const float*)gb.bias + col;
-      s.x += bp[0], s.y += bp[1], s.z += bp[2], s.w += bp[3];
-    }
-    *(float4*)((float*)gb.c + (e / gb.N) * gb.ldc + col) = s;  // (ldc = N)
-    return;
+// C = sum over the splits, in order, of the partial tiles + bias; both contractions of an adjoint that are split are one
+// launch (`second`: no splits, if there is one).  Bound by latency: a thread makes one element, or where rows, bias and
+// arrays allow one quad, and has eight splits' loads in flight; with one load at a time and four elements a thread the
+// two launches of a 37 x 2000 x 1001 layer (16 splits) took 17.2 and 10.1 us, and its whole pass 57.2 us; now 35.0.
+template <bool BF16, bool QUADS>
+__global__ __launch_bounds__(256) void gemm_split_reduce_kernel(SplitGrid first, SplitGrid second) {
+  const bool in_first = (int)blockIdx.y < first.nblocks;
+  const SplitGrid& g = in_first ? first : second;
+  const int block = in_first ? (int)blockIdx.y : (int)blockIdx.y - first.nblocks;
+  const GemmBlock& gb = g.blocks[block];
+  const float* const pp = g.partial + (int64_t)block * g.nsplit * g.partial_stride;
+  constexpr int V = QUADS ? 4 : 1;
+  typedef float Vec __attribute__((ext_vector_type(V)));
+  const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * V;
+  if (e >= (int64_t)gb.M * gb.N) return;
+  Vec s;
+  for (int t0 = 0; t0 < g.nsplit; t0 += 8) {
+    Vec u[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) u[t] = *(const Vec*)(pp + min(t0 + t, g.nsplit - 1) * g.partial_stride + e);
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (t0 + t < g.nsplit) s = t0 + t == 0 ? u[0] : s + u[t];
   }
-  for (int q = 0; q < 4; ++q) {
-    const int64_t e = (int64_t)blockIdx.x * 1024 + q * 256 + threadIdx.x;
-    if (e >= mn) return;
-    float s = pp[e];
-    for (int t = 1; t < g.nsplit; ++t) s += pp[t * g.partial_stride + e];
-    const int col = (int)(e % gb.N);
-    if (gb.bias) s += load_one<BF16>(gb.bias, col);
-    st((Out*)gb.c, (size_t)(e / gb.N) * gb.ldc + col, s);
+  const int col = (int)(e % gb.N);  // (QUADS: N is a multiple of 4)
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    if (gb.bias) s[i] += load_one<BF16>(gb.bias, col + i);
   }
+  if constexpr (QUADS) *(Vec*)((float*)gb.c + e) = s;  // (ldc = N)
+  else st((std::conditional_t<BF16, uint16_t, float>*)gb.c, (size_t)(e / gb.N) * gb.ldc + col, s[0]);
 }
 
 }  // namespace
@@ -573,11 +572,23 @@ static SplitGrid grid_of(const GemmBlock* d_blocks, size_t n, const GemmSplitPla
   return SplitGrid{d_blocks, partial, p.max_mn, p.tiles, p.nsplit, (int32_t)n};
 }
 
-static void launch_reduce(const SplitGrid& g, const GemmSplitPlan& p, bool bf16, hipStream_t st) {
-  if (p.nsplit <= 1) return;
-  const dim3 rgrid((unsigned)((p.max_mn + 1023) / 1024), (unsigned)g.nblocks);
-  if (bf16) hipLaunchKernelGGL(gemm_split_reduce_kernel<true>, rgrid, dim3(256), 0, st, g);
-  else hipLaunchKernelGGL(gemm_split_reduce_kernel<false>, rgrid, dim3(256), 0, st, g);
+// rows that are whole quads, in 16-byte aligned arrays
+static bool quad_rows(const std::vector<GemmBlock>& blocks) {
+  for (const GemmBlock& b : blocks)
+    if (b.N % 4 || b.ldc != b.N || (uintptr_t)b.c % 16) return false;
+  return true;
+}
+
+// (a launch that is not split: no blocks)
+static void launch_reduce(SplitGrid a, SplitGrid b, bool quads, bool bf16, hipStream_t st) {
+  if (a.nsplit <= 1) a.nblocks = 0;
+  if (b.nsplit <= 1) b.nblocks = 0;
+  if (a.nblocks + b.nblocks == 0) return;
+  const int64_t most = std::max(a.nblocks ? a.partial_stride : 0, b.nblocks ? b.partial_stride : 0), per = quads ? 1024 : 256;
+  const dim3 grid((unsigned)((most + per - 1) / per), (unsigned)(a.nblocks + b.nblocks));
+  if (bf16) hipLaunchKernelGGL((gemm_split_reduce_kernel<true, false>), grid, dim3(256), 0, st, a, b);
+  else if (quads) hipLaunchKernelGGL((gemm_split_reduce_kernel<false, true>), grid, dim3(256), 0, st, a, b);
+  else hipLaunchKernelGGL((gemm_split_reduce_kernel<false, false>), grid, dim3(256), 0, st, a, b);
 }
 
 template <bool BF16, int T, bool VEC>
@@ -596,7 +607,7 @@ int launch_gemm_split_fwd(const GemmBlock* d_blocks, const std::vector<GemmBlock
   int rc = bf16 ? fwd_variant<true, 1, false>(g, p.wgs, st)
                 : p.T == 2 ? fwd_variant<false, 2, true>(g, p.wgs, st)
                            : p.vec ? fwd_variant<false, 1, true>(g, p.wgs, st) : fwd_variant<false, 1, false>(g, p.wgs, st);
-  if (!rc) launch_reduce(g, p, bf16, st);
+  if (!rc) launch_reduce(g, SplitGrid{}, !bf16 && quad_rows(blocks), bf16, st);
   return rc;
 }
 
@@ -631,8 +642,7 @@ int launch_gemm_split_bwd(const GemmBlock* d_bx, const std::vector<GemmBlock>& b
   else DISTDL_BWD(false, 1, 1, true);
 #undef DISTDL_BWD
   if (rc) return rc;
-  launch_reduce(gx, px, bf16, st);
-  launch_reduce(gw, pw, bf16, st);
+  launch_reduce(gx, gw, !bf16 && (px.nsplit <= 1 || quad_rows(bx)) && (pw.nsplit <= 1 || quad_rows(bw)), bf16, st);
   return DISTDL_OK;
 }
 
