@@ -14,6 +14,16 @@
 // quarter of the patch with a quarter of the taps.  Three planes of a whole 5 x 5 stride-2 stage would be 200 KB; the
 // groups (9, 6, 6 and 4 taps) take 64 KB at most, so two workgroups share a compute unit and one's loads, splits and
 // barriers run under the other's MFMAs.  Groups of more than 10 taps are cut by kernel rows.
+// Layers of few channels (FEW).  A tile has 32 columns and an MFMA 16 k; an output tensor of 3 channels and a chunk of 4 or 8
+// input channels leave most of both empty.  Two ways to fill them, each taken where the estimate of the launch's time says so:
+//   fold: `fold` neighbouring cells along dimension 2 are one position with fold * channels columns (contiguous in memory); the
+//     taps of the cells, those of one offset together, are the position's taps: k + fold - 1 of them instead of fold * k.
+//     Data gradient: fold is a multiple of the stride, and the classes of dimension 2 are one launch.
+//   a last chunk of at most 8 channels: the 16 k of an MFMA are those of two taps.
+// us before and after: data gradient of 32 -> 3 channels, 7 x 7, stride 2, 8 x 224 x 224 (fold 4) 71 and 37; 4 -> 8, 3^3, stride 2,
+// 6 x 28 x 30 x 45 (fold 2) 36.7 and 23.7; 20 -> 2, 1^3, stride 2, 7 x 58 x 62 x 60 52 and 37; forward of 28 -> 8, 3 x 3,
+// 2 x 675 x 1013 (fold 3) 145 and 123.  (Whole layers of 24 and 40 channels gain nothing from the second way alone: three M-tiles
+// do not fit its registers.)
 // Error (2-norm, against 64 bits; fp32 MFMAs in brackets): 4000 products a sum 3.9e-7 (1.13e-6), 21952 with three M-tiles
 // 1.9e-6 and two 8.5e-7 (2.4e-6), 72 products 5.7e-8 (1.5e-7).
 // Bound: MFMAs (at the clock that the power limit leaves them with real data, about 2/3 of the peak) and LDS: with
@@ -37,7 +47,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GiB)
-constexpr int kMaxGroups = 32, kMaxTaps = 64, kGroupTaps = 10;
+constexpr int kMaxGroups = 32, kMaxTaps = 64, kGroupTaps = 10, kFewTaps = 8, kMaxOff2 = 40;
 
 struct SplitArgs {
   CorrArgs c;
@@ -48,6 +58,12 @@ struct SplitArgs {
   int32_t gbase[kMaxGroups][2];             // input offset of the group's first patch row / cell (of position 0)
   int32_t tapcell[kMaxTaps];                // patch cell of a tap for position 0
   uint8_t tap12[kMaxTaps][2];               // its indices along dimensions 1 and 2
+  int32_t fold, nch;                        // cells along dimension 2 that are one position's columns; channels of a cell
+  FastDiv div_nch;
+  int32_t dil2;
+  int32_t off2[kMaxOff2];                   // input offset of tap i along dimension 2
+  int32_t nfull, npairs;                    // chunks of 16 channels; MFMAs of a last chunk of at most 8 (0: there is none)
+  int32_t hbegin[kMaxGroups + 1];           // of these those of group i
 };
 
 // The arguments of a launch of several classes lie in a table of the plan's; read through the constant address space its
@@ -55,12 +71,20 @@ struct SplitArgs {
 typedef const __attribute__((address_space(4))) SplitArgs* TablePtr;
 __device__ inline TablePtr args_at(const SplitArgs* tab, int i) { return (TablePtr)(uintptr_t)(tab + i); }
 template <class ArgsPtr>
-__device__ inline PerWorker derive_of(const WorkerDev& wd, ArgsPtr a) {
+__host__ __device__ inline PerWorker derive_of(const WorkerDev& wd, ArgsPtr a) {
   CorrArgs c;
   c.mode = a->c.mode;
 #pragma unroll
   for (int d = 0; d < 3; ++d) c.s[d] = a->c.s[d], c.par[d] = a->c.par[d];
-  return derive(wd, c);
+  PerWorker g = derive(wd, c);
+  if (a->fold > 1) {  // position q2: cells out_base + fold * q2 ...; data gradient: all classes of dimension 2
+    const int s = c.s[2], r = wd.origin[2] % s;
+    g.out_base[2] = c.mode == 0 || r == 0 ? 0 : r - s;
+    g.in_base[2] = c.mode == 0 ? wd.origin[2] : (g.out_base[2] - wd.origin[2]) / s;  // (a whole number)
+    g.nq[2] = (g.out_ext[2] - g.out_base[2] + a->fold - 1) / a->fold;
+    g.os[2] = a->fold;
+  }
+  return g;
 }
 
 __device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
@@ -74,12 +98,23 @@ constexpr uint32_t half_bytes(int PA) { return PA * 2048; }
 constexpr uint32_t plane_bytes(int PA) { return 2 * half_bytes(PA); }
 constexpr int split_lds_bytes(int PA, int taps) { return 3 * plane_bytes(PA) + taps * 3072 + 16; }
 
-// eight channels of a weight piece: k = 16 cc + 8 h ... of channel ch, tap `tap` (in group order) of kernel plane t0
+// The layer's tap along dimension 2 that joins tap `i2` of a launch with cell j of a position's; negative: none.
 template <class ArgsPtr>
-__device__ inline void weight_octet(ArgsPtr a, const float* __restrict__ w, int t0, int cc, int tap, int h, int ch, float (&v)[8]) {
+__device__ inline int tap2_of(ArgsPtr a, int i2, int j) {
   const auto& c = a->c;
-  const int ft = (c.tapid[0][t0] * a->k1 + c.tapid[1][a->tap12[tap][0]]) * a->k2 + c.tapid[2][a->tap12[tap][1]];
-  const int k0 = cc * 16 + h * 8, left = ch < c.nc ? c.kc - k0 : 0;
+  if (a->fold == 1) return c.tapid[2][i2];
+  const int at = c.mode == 0 ? a->off2[i2] - j * c.s[2] : j - a->off2[i2] * c.s[2];
+  return at < 0 || at % a->dil2 != 0 || at / a->dil2 >= a->k2 ? -1 : at / a->dil2;
+}
+
+// eight channels of a weight piece: k0 ... of column col, tap `tap` (in group order) of kernel plane t0
+template <class ArgsPtr>
+__device__ inline void weight_octet(ArgsPtr a, const float* __restrict__ w, int t0, int k0, int tap, int col, float (&v)[8]) {
+  const auto& c = a->c;
+  const FastDiv div_nch{a->div_nch.mul, a->div_nch.sh1, a->div_nch.sh2, a->div_nch.d};
+  const int j = a->fold > 1 ? (int)fd_div((uint32_t)col, div_nch) : 0, ch = col - j * a->nch, t2 = tap2_of(a, a->tap12[tap][1], j);
+  const int ft = (c.tapid[0][t0] * a->k1 + c.tapid[1][a->tap12[tap][0]]) * a->k2 + t2;
+  const int left = col < c.nc && t2 >= 0 ? c.kc - k0 : 0;
   const size_t per_k = c.mode == 0 ? (size_t)a->taps : (size_t)a->ci * a->taps;
   const float* const at = w + (left <= 0 ? (size_t)0 : c.mode == 0 ? ((size_t)ch * a->ci + k0) * a->taps + ft : ((size_t)k0 * a->ci + ch) * a->taps + ft);
 #pragma unroll
@@ -92,8 +127,9 @@ __device__ inline void weight_octet(ArgsPtr a, const float* __restrict__ w, int 
 }
 
 // MT: 32-position M-tiles per wave; PA: pairs of 16-byte pieces (8 channels of a cell) per thread and stage; PB: weight
-// pieces per thread and stage
-template <int MT, int PA, int PB, class ArgsPtr>
+// pieces per thread and stage; FEW: for layers of few channels,
+// fold > 1 or a last chunk of one octet
+template <int MT, int PA, int PB, bool FEW, class ArgsPtr>
 __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restrict__ workers, void* const* in_bufs,
                                            void* const* out_bufs, const u32x4* wt, const float* w, const float* bias_in) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -115,12 +151,14 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
 
   const int si2 = c.kc, si1 = g.in_ext[2] * si2, si0 = g.in_ext[1] * si1;
   const uint32_t sin = (uint32_t)g.in_ext[0] * si0;
-  const uint32_t so2 = c.nc, so1 = g.out_ext[2] * so2, so0 = g.out_ext[1] * so1, son = g.out_ext[0] * so0;
+  const uint32_t so2 = FEW ? a->nch : c.nc, so1 = g.out_ext[2] * so2, so0 = g.out_ext[1] * so1, son = g.out_ext[0] * so0;
   const __amdgpu_buffer_rsrc_t rin = rsrc_of(in_bufs[worker], (uint32_t)c.n_b * sin * 4u);
   const __amdgpu_buffer_rsrc_t rout = rsrc_of(out_bufs[worker], (uint32_t)c.n_b * son * 4u);
   const int ncc = (c.kc + 15) / 16, nt0 = c.nt[0], ntaps = a->gbegin[a->ngroups];
-  const uint32_t wplane = (uint32_t)ntaps * 192u;  // weight pieces of one (t0, chunk)
-  const __amdgpu_buffer_rsrc_t rw = rsrc_of(wt + a->woff + (size_t)ntile * nt0 * ncc * wplane, (uint32_t)(nt0 * ncc) * wplane * 16u);
+  const int nfull = FEW ? a->nfull : ncc;
+  const bool one_octet = FEW && nfull == 0;  // a cell is one piece
+  const uint32_t wplane = (uint32_t)ntaps * 192u, wt0 = (uint32_t)nfull * wplane + (FEW ? a->npairs : 0) * 192u;  // weight pieces of one (t0, chunk), of t0
+  const __amdgpu_buffer_rsrc_t rw = rsrc_of(wt + a->woff + (size_t)ntile * nt0 * wt0, (uint32_t)nt0 * wt0 * 16u);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, m = lane & 31;
 
   const FastDiv div_cw{c.div_cw.mul, c.div_cw.sh1, c.div_cw.sh2, c.div_cw.d}, div_tc{c.div_tc.mul, c.div_tc.sh1, c.div_tc.sh2, c.div_tc.d};
@@ -129,19 +167,21 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
   uint32_t plin[PA];
 #pragma unroll
   for (int i = 0; i < PA; ++i) {
-    const int ph = (tid >> 5) & 1, cell = (tid & 31) + 32 * (tid >> 6) + 128 * i;
+    const int ph = one_octet ? 0 : (tid >> 5) & 1, cell = one_octet ? tid + 256 * i : (tid & 31) + 32 * (tid >> 6) + 128 * i;
     const int rr = (int)fd_div((uint32_t)cell, div_cw), cc = cell - rr * c.Cw;
     prow[i] = cell < c.R * c.Cw ? g.in_base[1] + q1_0 * c.is[1] + rr * c.is[1] : -0x40000000;  // never in range
     pcol[i] = g.in_base[2] + q2_0 * c.is[2] + cc * c.is[2];
     plin[i] = (uint32_t)(prow[i] * si1 + pcol[i] * si2 + ph * 8) * 4u;
   }
-  const uint32_t pl0 = (uint32_t)((tid >> 5) & 1) * HB + (uint32_t)((tid & 31) + 32 * (tid >> 6)) * 16u;  // piece i lies 128 * i cells further
+  // piece i lies 128 * i (256 * i) cells further
+  const uint32_t pl0 = one_octet ? tid * 16u : (uint32_t)((tid >> 5) & 1) * HB + (uint32_t)((tid & 31) + 32 * (tid >> 6)) * 16u;
+  const uint32_t pl1 = one_octet ? 4096u : 2048u;
   char* const wlds = smem + 3 * PS;
 
   // lane m of M-tile (wave, mt) multiplies window position (wave * MT + mt) * 32 + m.  The tile is accumulated transposed
   // (the weights are the first MFMA operand): register v of lane (h, m) is channel ntile * 32 + 8 (v / 4) + 4 h + v % 4 of
   // that position, so that a register quad is four consecutive channels and goes out as one 16-byte store.
-  uint32_t abase[MT], soff[MT];
+  uint32_t abase[MT], soff[MT], live[FEW ? MT : 1];  // live: the columns of the position that are cells of the buffer, first and end
   const int ch0 = ntile * 32 + 4 * h;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
@@ -151,8 +191,12 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
     soff[mt] = kOob;
     if (wr < c.tr && q1 < g.nq[1] && q2 < g.nq[2])
       soff[mt] = ((g.out_base[1] + g.os[1] * q1) * so1 + (g.out_base[2] + g.os[2] * q2) * so2 + ch0) * 4u;
+    if constexpr (FEW) {
+      const int cell = g.out_base[2] + g.os[2] * q2, lo = max(0, -cell * a->nch), hi = min(c.nc, (g.out_ext[2] - cell) * a->nch);
+      live[mt] = soff[mt] == kOob ? 0u : (uint32_t)lo | (uint32_t)hi << 16;
+    }
     if (wr >= c.tr) wr = 0, wc = 0;  // idle position: multiplies something in range, never stored
-    abase[mt] = (uint32_t)h * HB + (uint32_t)(wr * c.Cw + wc) * 16u;
+    abase[mt] = (FEW ? 0u : (uint32_t)h * HB) + (uint32_t)(wr * c.Cw + wc) * 16u;
   }
   const uint32_t wread = (uint32_t)(h * 32 + m) * 16u;
 
@@ -199,7 +243,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
     const int b1 = a->gbase[sp.gr][0], b2 = a->gbase[sp.gr][1];
     const uint32_t shift = (uint32_t)(b1 * si1 + b2 * si2) * 4u;
     const uint32_t sbase = ((uint32_t)sp.n * sin + (uint32_t)plane_of(sp.q0, sp.t0) * si0 + sp.cc * 16) * 4u;
-    const int left = c.kc - sp.cc * 16 - ((tid >> 5) & 1) * 8;  // channels of this thread's half
+    const int left = c.kc - sp.cc * 16 - (one_octet ? 0 : ((tid >> 5) & 1) * 8);  // channels of this thread's half
 #pragma unroll
     for (int i = 0; i < PA; ++i) {
       const bool ok = (uint32_t)(prow[i] + b1) < (uint32_t)g.in_ext[1] && (uint32_t)(pcol[i] + b2) < (uint32_t)g.in_ext[2];
@@ -210,9 +254,10 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
   };
   auto load_stage = [&](const StagePos& sp) {
     load_cells(sp);
-    const int tb = a->gbegin[sp.gr];
-    const uint32_t np = (uint32_t)(a->gbegin[sp.gr + 1] - tb) * 192u;
-    const uint32_t wbase = ((uint32_t)(sp.t0 * ncc + sp.cc) * wplane + (uint32_t)tb * 192u) * 16u;
+    const bool pairs = FEW && sp.cc >= nfull;
+    const int tb = pairs ? a->hbegin[sp.gr] : a->gbegin[sp.gr];
+    const uint32_t np = (uint32_t)((pairs ? a->hbegin[sp.gr + 1] : a->gbegin[sp.gr + 1]) - tb) * 192u;
+    const uint32_t wbase = ((uint32_t)sp.t0 * wt0 + (uint32_t)sp.cc * wplane + (uint32_t)tb * 192u) * 16u;
 #pragma unroll
     for (int i = 0; i < PB; ++i)  // (a wave's 64 pieces are all there or all not)
       if (i * 256 + wave_u * 64 < np) rb[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, tid * 16u, wbase + i * 4096u, 0);
@@ -226,7 +271,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
       for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(ra[i][e >> 2][e & 3]);
       u32x4 hi, mid, lo;
       split_eight(v, scale, hi, mid, lo);
-      char* const at = smem + pl0 + i * 2048;
+      char* const at = smem + pl0 + i * (FEW ? pl1 : 2048u);
       *(u32x4*)at = hi;
       *(u32x4*)(at + PS) = mid;
       *(u32x4*)(at + 2 * PS) = lo;
@@ -270,9 +315,19 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
     __builtin_amdgcn_sched_barrier(0);
   };
   const int my_cell = lane < ntaps ? a->tapcell[lane] * 16 : 0;  // lane t keeps the patch offset of tap t
-  auto compute = [&](int gr) {
-    const int tb = a->gbegin[gr], nt = a->gbegin[gr + 1] - tb;
-    uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb);
+  const uint32_t half = (uint32_t)h * HB;
+  // A chunk of at most 8 channels: the k of an MFMA are those of two taps, one for each half of the wave (the weights of a
+  // tap that there is not are zero).
+  auto compute = [&](int gr, bool pairs) {
+    const int tb = a->gbegin[gr], ntap = a->gbegin[gr + 1] - tb, nt = FEW && pairs ? (ntap + 1) / 2 : ntap;
+    auto cell_of = [&](int t) -> uint32_t {
+      if constexpr (!FEW) return (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + t);
+      if (!pairs) return (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + t) + half;
+      const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + 2 * t),
+                     c1 = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + min(2 * t + 1, ntap - 1));
+      return h ? c1 : c0;
+    };
+    uint32_t cell = cell_of(0);
     read_w(2, 0);
     read_x(0, cell);
     read_w(1, 0);
@@ -281,7 +336,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
     read_x(1, cell);
     for (int t = 0; t < nt; ++t) {
       const int tn = t + 1 < nt ? t + 1 : t;  // (past the last tap: its own operands again)
-      cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + tn);
+      cell = cell_of(tn);
       mm(2, 0);
       read_w(2, tn);
       mm(1, 0);
@@ -301,16 +356,42 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
   sp.sk = rot_d ? skew_of(sp.q0) : 0;
   advance(sp);
   int on = pfirst / nq0, oq0 = pfirst % nq0;  // the output plane that is stored next
+  const FastDiv div_nch{a->div_nch.mul, a->div_nch.sh1, a->div_nch.sh2, a->div_nch.d};
   auto store_plane = [&]() {
     float bias[4][4];
+    int first = ch0;
+    asm volatile("" : "+v"(first));  // (the indexes that follow are not kept in registers from plane to plane)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) bias[q][e] = (bias_in && ch0 + 8 * q + e < c.nc) ? bias_in[ch0 + 8 * q + e] : 0.f;
+      for (int e = 0; e < 4; ++e) {
+        const int col = first + 8 * q + e;
+        bias[q][e] = (bias_in && col < c.nc) ? bias_in[FEW ? col - (int)fd_div((uint32_t)col, div_nch) * a->nch : col] : 0.f;
+      }
     const uint32_t obase = ((uint32_t)on * son + (uint32_t)(g.out_base[0] + g.os[0] * oq0) * so0) * 4u;
     // (the plane's offset is added into the per-lane offset: with a scalar offset the compiler leaves out the wait states
     // a 16-byte store needs before its data registers are written again)
-    if (c.nc & 3) {  // (uniform) quads need not be whole, nor aligned
+    if constexpr (FEW) {
+      // The columns of a position are contiguous in memory: 16-byte stores (of any alignment) of whole quads, single ones at the
+      // ends of a row.
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int n0 = ch0 + 8 * q, lo = (int)(live[mt] & 0xffffu), hi = (int)(live[mt] >> 16);
+          const bool whole = n0 >= lo && n0 + 4 <= hi, some = !whole && n0 + 4 > lo && n0 < hi;
+          const uint32_t off = soff[mt] + (uint32_t)(8 * q) * 4u + obase;
+          u32x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(acc[mt][4 * q + e] + bias[q][e]);
+          __builtin_amdgcn_raw_buffer_store_b128(o, rout, whole ? off : kOob, 0, 0);
+          if (__builtin_amdgcn_ballot_w64(some)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              __builtin_amdgcn_raw_buffer_store_b32(o[e], rout, some && n0 + e >= lo && n0 + e < hi ? off + 4u * e : kOob, 0, 0);
+          }
+        }
+    } else if (c.nc & 3) {  // (uniform) quads need not be whole, nor aligned
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -346,6 +427,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
     uint32_t turn = 1;  // stages of the plane so far, and one; bit 1: the sign of the accumulator (+ - - + + - - ...)
     while (sp.p == po) {  // the stages that feed output plane po
       const int gr = sp.gr;
+      const bool pairs = FEW && sp.cc >= nfull;
       if constexpr (!TWO) {
         if (turn > 1 && (turn & 1) == 0) {
 #pragma unroll
@@ -356,7 +438,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
       __syncthreads();
       advance(sp);
       if (sp.p < pcnt) load_stage(sp);  // in flight while this stage multiplies
-      compute(gr);
+      compute(gr, pairs);
       if (sp.p != po) {
         float seen = 0.f;
         const float scale = !TWO && (turn & 2) ? -kUnsplit : kUnsplit;
@@ -387,13 +469,14 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
           for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(ra[i][e >> 2][e & 3]);
           u32x4 u, l;
           halve_eight(v, u, l);
-          *(u32x4*)(smem + pl0 + i * 2048) = u;
-          *(u32x4*)(smem + pl0 + i * 2048 + PS) = l;
+          char* const at = smem + pl0 + i * (FEW ? pl1 : 2048u);
+          *(u32x4*)at = u;
+          *(u32x4*)(at + PS) = l;
         }
 #pragma unroll 1
         for (int i = tid; i < nt * 64; i += 256) {  // [tap][h][nn]
           float v[8];
-          weight_octet(a, w, rp.t0, rp.cc, tb + (i >> 6), (i >> 5) & 1, ntile * 32 + (i & 31), v);
+          weight_octet(a, w, rp.t0, rp.cc * 16 + ((i >> 5) & 1) * 8, tb + (i >> 6), ntile * 32 + (i & 31), v);
           u32x4 u, l;
           halve_eight(v, u, l);
           char* const at = wlds + (i >> 6) * 3072 + (i & 63) * 16;
@@ -405,21 +488,25 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
         }
         __syncthreads();
         // A cell of dx lacks the taps whose output does not exist.  They read zeros, which do not cancel a weight that is not
-        // finite: once there is one, lane by lane and without those terms.
-        const bool lanes = c.mode == 1 && __builtin_amdgcn_readfirstlane(redo[1]);
+        // finite: once there is one, lane by lane and without those terms.  Ditto where zeros fill up the weights: the taps that
+        // a cell of a position lacks, the second octet of a chunk that has one.
+        const int octets = FEW && rp.cc >= nfull ? 1 : 2;
+        const bool lanes = (FEW && (a->fold > 1 || octets == 1)) || (c.mode == 1 && __builtin_amdgcn_readfirstlane(redo[1]));
 #pragma unroll 1
         for (int t = 0; lanes && t < nt; ++t) {
-          const uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + t) - (uint32_t)h * HB;
+          const uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + t) - (FEW ? 0u : half);
           bool there[MT];
+          int first = ch0;
+          asm volatile("" : "+v"(first));
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
             const int pidx = (wave * MT + mt) * 32 + m, wr = (int)fd_div((uint32_t)pidx, div_tc), wc = pidx - wr * c.tc;
             const int i1 = g.in_base[1] + (q1_0 + wr) * c.is[1] + c.tapoff[1][a->tap12[tb + t][0]],
-                      i2 = g.in_base[2] + (q2_0 + wc) * c.is[2] + c.tapoff[2][a->tap12[tb + t][1]];
+                      i2 = g.in_base[2] + (q2_0 + wc) * c.is[2] + a->off2[a->tap12[tb + t][1]];
             there[mt] = (uint32_t)i1 < (uint32_t)g.in_ext[1] && (uint32_t)i2 < (uint32_t)g.in_ext[2];
           }
 #pragma unroll 1
-          for (int o = 0; o < 2; ++o) {  // octets of the chunk
+          for (int o = 0; o < octets; ++o) {  // of the chunk
             Eight xx[MT];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
@@ -430,6 +517,9 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
             for (int v = 0; v < 16; ++v) {
               const char* const wp = wlds + t * 3072 + (o * 32 + 8 * (v >> 2) + 4 * h + (v & 3)) * 16;
               const Eight xw = join_halves(*(const u32x4*)wp, *(const u32x4*)(wp + 1024));
+              if constexpr (FEW) {
+                if (tap2_of(a, a->tap12[tb + t][1], (int)fd_div((uint32_t)(first + 8 * (v >> 2) + (v & 3)), div_nch)) < 0) continue;
+              }
 #pragma unroll
               for (int mt = 0; mt < MT; ++mt) {
                 float sum = acc[mt][v];
@@ -442,7 +532,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
         }
 #pragma unroll 1
         for (int t = 0; !lanes && t < nt; ++t) {
-          const uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + t);
+          const uint32_t cell = (uint32_t)__builtin_amdgcn_readlane(my_cell, tb + t) + (FEW ? half : 0u);
           const char* const wp = wlds + t * 3072 + wread;
           const Eight xw = join_halves(*(const u32x4*)wp, *(const u32x4*)(wp + 1024));
 #pragma unroll
@@ -462,39 +552,49 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
 // One class, its arguments in the kernel's (their loads cost nothing to repeat, where those of the table stay in registers:
 // 0.48 against 1.3 ms per class on the 5^3 stride-2 layer), and several, blockIdx.y, from the table: small layers, where
 // it is launches that count (8 -> 64 channels, 3^3, stride 2, 3 x 5 x 6 x 7: 205 us with 16 launches, 71 with 2).
-template <int MT, int PA, int PB>
+template <int MT, int PA, int PB, bool FEW>
 __global__ __launch_bounds__(256, 2) void corr_split_kernel(const WorkerDev* __restrict__ workers, void* const* in_bufs,
                                                             void* const* out_bufs, SplitArgs a, const u32x4* wt,
                                                             const float* w, const float* bias) {
-  corr_split<MT, PA, PB, const SplitArgs*>(&a, workers, in_bufs, out_bufs, wt, w, bias);
+  corr_split<MT, PA, PB, FEW, const SplitArgs*>(&a, workers, in_bufs, out_bufs, wt, w, bias);
 }
-template <int MT, int PA, int PB>
+template <int MT, int PA, int PB, bool FEW>
 __global__ __launch_bounds__(256, 2) void corr_split_classes_kernel(const WorkerDev* __restrict__ workers, void* const* in_bufs,
                                                                     void* const* out_bufs, const SplitArgs* tab, int first,
                                                                     const u32x4* wt, const float* w, const float* bias) {
-  corr_split<MT, PA, PB, TablePtr>(args_at(tab, first + (int)blockIdx.y), workers, in_bufs, out_bufs, wt, w, bias);
+  corr_split<MT, PA, PB, FEW, TablePtr>(args_at(tab, first + (int)blockIdx.y), workers, in_bufs, out_bufs, wt, w, bias);
 }
 
 // Weights in the order the kernel stages them: pieces [ntile][t0][chunk][tap in group order][plane][h][nn], 8 channels
-// k = 16 chunk + 8 h ... each of output channel ntile * 32 + nn; zero beyond the channel counts.  One thread per piece
-// of all three planes.
+// k = 16 chunk + 8 h ... each of column ntile * 32 + nn; a last chunk of at most 8 channels instead [pair of taps][plane][h]
+// [nn], those of the pair's tap h; zero beyond the channel counts and taps.  One thread per piece of all three planes.
 __global__ __launch_bounds__(256) void corr_split_weights_kernel(const SplitArgs* tab, int first, const float* __restrict__ w,
                                                                  u32x4* __restrict__ dst) {
   const TablePtr a = args_at(tab, first + (int)blockIdx.y);
   const auto& c = a->c;
-  const int ncc = (c.kc + 15) / 16, ntaps = a->gbegin[a->ngroups];
+  const int ntaps = a->gbegin[a->ngroups], whole = a->nfull * ntaps, per_t0 = whole + a->npairs;
   const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
-  if (idx >= c.ntn * c.nt[0] * ncc * ntaps * 64) return;
-  const int hn = idx & 63;
+  if (idx >= c.ntn * c.nt[0] * per_t0 * 64) return;
+  const int nn = idx & 31, h = (idx >> 5) & 1;
   int r = idx >> 6;
-  const int tap = r % ntaps; r /= ntaps;
-  const int cc = r % ncc; r /= ncc;
+  const int at_t0 = r % per_t0; r /= per_t0;
   const int t0 = r % c.nt[0], ntile = r / c.nt[0];
+  int cc = at_t0 / ntaps, k0 = cc * 16 + h * 8, tap = at_t0 - cc * ntaps;
+  bool there = true;
+  if (at_t0 >= whole) {
+    const int pair = at_t0 - whole;
+    int gr = 0;
+    while (a->hbegin[gr + 1] <= pair) ++gr;
+    tap = a->gbegin[gr] + 2 * (pair - a->hbegin[gr]) + h;
+    there = tap < a->gbegin[gr + 1];
+    if (!there) tap = 0;
+    k0 = a->nfull * 16;
+  }
   float v[8];
-  weight_octet(a, w, t0, cc, tap, hn >> 5, ntile * 32 + (hn & 31), v);
+  weight_octet(a, w, t0, k0, tap, there ? ntile * 32 + nn : c.nc, v);
   u32x4 hi, mid, lo;
   split_eight(v, kSplitScale, hi, mid, lo);
-  u32x4* const at = dst + a->woff + (size_t)(idx >> 6) * 192 + hn;
+  u32x4* const at = dst + a->woff + (size_t)(idx >> 6) * 192 + (idx & 63);
   at[0] = hi;
   at[64] = mid;
   at[128] = lo;
@@ -503,7 +603,7 @@ __global__ __launch_bounds__(256) void corr_split_weights_kernel(const SplitArgs
 // ---- host side ------------------------------------------------------------------
 
 // Tap groups of a launch; false when there are more than the arguments hold.
-bool group_taps(SplitArgs& a) {
+bool group_taps(SplitArgs& a, bool octet, int group) {
   const CorrArgs& c = a.c;
   if (c.nt[1] * c.nt[2] > kMaxTaps) return false;
   int at = 0, most = 0;
@@ -513,19 +613,19 @@ bool group_taps(SplitArgs& a) {
   // first the groups with their tap indices, then the patch they need
   for (int r1 = 0; r1 < c.is[1]; ++r1)
     for (int r2 = 0; r2 < c.is[2]; ++r2) {
-      int i1[8], n1 = 0, i2[8], n2 = 0;
+      int i1[8], n1 = 0, i2[kMaxOff2], n2 = 0;
       for (int t = 0; t < c.nt[1]; ++t)
         if (((c.tapoff[1][t] - r1) % c.is[1] + c.is[1]) % c.is[1] == 0) i1[n1++] = t;
       for (int t = 0; t < c.nt[2]; ++t)
-        if (((c.tapoff[2][t] - r2) % c.is[2] + c.is[2]) % c.is[2] == 0) i2[n2++] = t;
+        if (((a.off2[t] - r2) % c.is[2] + c.is[2]) % c.is[2] == 0) i2[n2++] = t;
       if (n1 == 0 || n2 == 0) continue;
-      const int rows = std::max(1, kGroupTaps / n2), parts = (n1 + rows - 1) / rows, per = (n1 + parts - 1) / parts;
+      const int rows = std::max(1, group / n2), parts = (n1 + rows - 1) / rows, per = (n1 + parts - 1) / parts;
       for (int b = 0; b < n1; b += per) {
         if (a.ngroups >= kMaxGroups) return false;
         const int e = std::min(n1, b + per);
         int lo1 = INT32_MAX, hi1 = INT32_MIN, lo2 = INT32_MAX, hi2 = INT32_MIN;
         for (int i = b; i < e; ++i) lo1 = std::min(lo1, c.tapoff[1][i1[i]]), hi1 = std::max(hi1, c.tapoff[1][i1[i]]);
-        for (int j = 0; j < n2; ++j) lo2 = std::min(lo2, c.tapoff[2][i2[j]]), hi2 = std::max(hi2, c.tapoff[2][i2[j]]);
+        for (int j = 0; j < n2; ++j) lo2 = std::min(lo2, a.off2[i2[j]]), hi2 = std::max(hi2, a.off2[i2[j]]);
         a.gbase[a.ngroups][0] = lo1;
         a.gbase[a.ngroups][1] = lo2;
         span1 = std::max(span1, (hi1 - lo1) / c.is[1]);
@@ -537,12 +637,16 @@ bool group_taps(SplitArgs& a) {
             ++at;
           }
         most = std::max(most, at - a.gbegin[a.ngroups]);
+        a.hbegin[a.ngroups + 1] = a.hbegin[a.ngroups] + (at - a.gbegin[a.ngroups] + 1) / 2;
         a.gbegin[++a.ngroups] = at;
       }
     }
   a.c.tapspan[1] = span1;
   a.c.tapspan[2] = span2;
   a.c.ck = most;
+  const int last = a.c.kc % 16;
+  a.nfull = a.c.kc / 16 + (octet ? 0 : last > 0);
+  a.npairs = octet ? a.hbegin[a.ngroups] : 0;
   return true;
 }
 
@@ -559,7 +663,7 @@ void set_window(SplitArgs& a, int mt, int tc) {
   for (int gr = 0; gr < a.ngroups; ++gr)
     for (int t = a.gbegin[gr]; t < a.gbegin[gr + 1]; ++t)
       a.tapcell[t] = ((c.tapoff[1][a.tap12[t][0]] - a.gbase[gr][0]) / c.is[1] * c.Cw +
-                                (c.tapoff[2][a.tap12[t][1]] - a.gbase[gr][1]) / c.is[2]);
+                                (a.off2[a.tap12[t][1]] - a.gbase[gr][1]) / c.is[2]);
 }
 
 double window_share(int cap, int tc, int nq1, int nq2) {  // fraction of the multiplied positions that are outputs
@@ -567,14 +671,16 @@ double window_share(int cap, int tc, int nq1, int nq2) {  // fraction of the mul
   return (double)nq1 * nq2 / ((double)((nq2 + tc - 1) / tc) * ((nq1 + tr - 1) / tr) * cap);
 }
 
-int pieces_of(const SplitArgs& a) { return (a.c.R * a.c.Cw * 2 + 255) / 256; }  // per thread
+bool one_octet(const SplitArgs& a) { return a.nfull == 0; }
+int pieces_of(const SplitArgs& a) { return (a.c.R * a.c.Cw * (one_octet(a) ? 1 : 2) + 255) / 256; }  // per thread
+bool few_channels(const SplitArgs& a) { return a.fold > 1 || a.npairs > 0; }
 
 // The window of a launch: M-tiles per wave (0: none fits).  The window that wastes the fewest multiplied positions; of
 // equal ones the one with the smallest patch per position.
 int choose_window(const distdl_plan* p, SplitArgs& a) {
   int nq1 = 1, nq2 = 1;
   for (const WorkerDev& wd : p->workers) {
-    const PerWorker g = derive(wd, a.c);
+    const PerWorker g = derive_of(wd, &a);
     nq1 = std::max(nq1, g.nq[1]);
     nq2 = std::max(nq2, g.nq[2]);
   }
@@ -587,7 +693,7 @@ int choose_window(const distdl_plan* p, SplitArgs& a) {
       // Three M-tiles have one accumulator for large and small products, which rounds it six times for 16 channels, where fp32
       // MFMAs do so eight times.  4 and 20 channels fill their last chunk by a quarter and would be further off than with those
       // (3 x 3, 4 channels: 1.32e-7 and 1.10e-7; 8 channels 1.34 and 1.54, 36 channels 2.99 and 3.22); two M-tiles: 4.9e-8.
-      if (mt == 3 && (a.c.kc == 4 || a.c.kc == 20)) continue;
+      if (mt == 3 && (a.c.kc == 4 || a.c.kc == 20 || few_channels(a))) continue;
       if (pa > 4 || split_lds_bytes(pa <= 3 && mt == 2 ? 3 : 4, a.c.ck) > 80 * 1024 || (mt == 3 && a.c.ck > 9)) continue;
       // a tap costs a wave 6 mt MFMAs and 3 mt + 3 operand reads: fewer M-tiles pay relatively more for the weights
       const double share = window_share(128 * mt, tc, nq1, nq2), patch = (double)(a.c.R * a.c.Cw) / (128 * mt);
@@ -598,7 +704,9 @@ int choose_window(const distdl_plan* p, SplitArgs& a) {
   return best_mt;
 }
 
-SplitArgs split_args(const distdl_plan* p, const CorrArgs& c, bool& ok) {
+// fold = 1: the launch as `c` has it; else one that makes `fold` neighbouring cells along dimension 2 in one position, a
+// multiple of the stride where `c` is a class of the data gradient (then of any parity along that dimension)
+SplitArgs split_args(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, bool& ok) {
   SplitArgs a{};
   a.c = c;
   a.ci = (int32_t)p->n_ci;
@@ -606,12 +714,36 @@ SplitArgs split_args(const distdl_plan* p, const CorrArgs& c, bool& ok) {
   a.taps = p->ksize[0] * p->ksize[1] * p->ksize[2];
   a.k1 = p->ksize[1];
   a.k2 = p->ksize[2];
-  ok = group_taps(a);
+  a.dil2 = p->dilation[2];
+  a.fold = fold;
+  a.nch = c.nc;
+  a.div_nch = make_fastdiv((uint32_t)a.nch);
+  if (fold == 1) {
+    for (int t = 0; t < c.nt[2]; ++t) a.off2[t] = c.tapoff[2][t];
+  } else {
+    const int s = p->stride[2];
+    a.c.nc = fold * a.nch;
+    a.c.ntn = (a.c.nc + 31) / 32;
+    a.c.is[2] = c.mode == 0 ? fold * s : fold / s;
+    std::vector<int> off;
+    for (int j = 0; j < fold; ++j)
+      for (int t = 0; t < a.k2; ++t) {
+        const int at = c.mode == 0 ? j * s + t * a.dil2 : j - t * a.dil2;
+        if (c.mode == 0) off.push_back(at);
+        else if (at % s == 0) off.push_back(at / s);
+      }
+    std::sort(off.begin(), off.end());
+    off.erase(std::unique(off.begin(), off.end()), off.end());
+    a.c.nt[2] = (int32_t)off.size();
+    if (off.size() > kMaxOff2) return ok = false, a;
+    std::copy(off.begin(), off.end(), a.off2);
+  }
+  ok = group_taps(a, octet, fold > 1 || octet ? kFewTaps : kGroupTaps);
   return a;
 }
 
 int64_t weight_pieces(const SplitArgs& a) {
-  return (int64_t)a.c.ntn * a.c.nt[0] * ((a.c.kc + 15) / 16) * a.gbegin[a.ngroups] * 192;
+  return (int64_t)a.c.ntn * a.c.nt[0] * (a.nfull * a.gbegin[a.ngroups] + a.npairs) * 192;
 }
 
 int64_t tiles_of_worker(const PerWorker& g, const CorrArgs& c) {
@@ -624,6 +756,7 @@ struct Launch {
   int variant = 0;  // index into the switch of launch_variants
   unsigned blocks = 0;
   int64_t pieces = 0;  // of weights
+  double clocks = 0, share = 1;  // estimates: time alone; part of the chip that it fills
 };
 struct Launches {
   std::vector<Launch> v;
@@ -638,25 +771,26 @@ struct SplitPlan {
   }
 };
 
-bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
+bool plan_launch(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, Launch& l) {
   bool ok;
-  l.a = split_args(p, c, ok);
+  l.a = split_args(p, c, fold, octet, ok);
   SplitArgs& a = l.a;
   if (!ok) return false;
   const int mt = choose_window(p, a);
   if (mt == 0) return false;
-  l.variant = mt == 3 ? 3 : mt == 1 ? 0 : pieces_of(a) <= 3 ? 1 : 2;
+  l.variant = (mt == 3 ? 3 : mt == 1 ? 0 : pieces_of(a) <= 3 ? 1 : 2) + (few_channels(a) ? 4 : 0);
   l.pieces = weight_pieces(a);
   // Output planes per workgroup: a fixed set-up (its address tables, about 8 * 10^3 clocks) against the number of rounds
   // of 512 workgroups; at least four groups per worker where neighbouring planes share input planes (conv_mfma.hip).
   int64_t planes_max = 0, per_plane = 0;
   for (const WorkerDev& wd : p->workers) {
-    const PerWorker g = derive(wd, a.c);
+    const PerWorker g = derive_of(wd, &a);
     planes_max = std::max<int64_t>(planes_max, p->n_b * g.nq[0]);
     per_plane = std::max<int64_t>(per_plane, (int64_t)((g.nq[1] + a.c.tr - 1) / a.c.tr) * ((g.nq[2] + a.c.tc - 1) / a.c.tc) * a.c.ntn);
   }
   per_plane *= p->n_workers;
-  const double stage = (double)a.c.nt[0] * ((a.c.kc + 15) / 16) * (a.gbegin[a.ngroups] * mt * 6 * 32.0 * 2 * 1.4 + a.ngroups * 1500.0);
+  const int ncc = a.nfull + (a.npairs > 0), mfmas = a.nfull * a.gbegin[a.ngroups] + a.npairs;
+  const double stage = (double)a.c.nt[0] * (mfmas * mt * 6 * 32.0 * 2 * 1.4 + ncc * a.ngroups * 1500.0);
   const int tstep0 = a.c.nt[0] > 1 ? a.c.tapoff[0][1] - a.c.tapoff[0][0] : 0;
   const bool shares = tstep0 != 0 && a.c.is[0] % tstep0 == 0 && (a.c.is[0] / tstep0) % a.c.nt[0] != 0;
   const int64_t g0_max = shares ? std::max<int64_t>(1, planes_max / 4) : std::max<int64_t>(1, planes_max);
@@ -667,8 +801,14 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
     const double cost = (double)((wgs + 511) / 512) * (8.0e3 + g0 * stage);
     if (cost < best * 0.97) best = cost, a.c.g0 = (int32_t)g0;
   }
+  {  // stages of a workgroup that is alone on its compute unit are longer than what the matrix cores need
+    const int64_t wgs = (planes_max + a.c.g0 - 1) / a.c.g0 * per_plane;
+    const double one = (double)a.c.nt[0] * (mfmas * mt * 6 * 32.0 * 1.4 * (wgs > 256 ? 2 : 1) + ncc * a.ngroups * 2500.0);
+    l.share = std::min(1.0, wgs / 512.0);
+    l.clocks = (double)((wgs + 511) / 512) * ((few_channels(a) ? 20.0e3 : 12.0e3) + a.c.g0 * one);
+  }
   int64_t tiles = 0;
-  for (const WorkerDev& wd : p->workers) tiles = std::max(tiles, tiles_of_worker(derive(wd, a.c), a.c));
+  for (const WorkerDev& wd : p->workers) tiles = std::max(tiles, tiles_of_worker(derive_of(wd, &a), a.c));
   const int64_t blocks = (tiles * p->n_workers + 7) / 8 * 8;
   if (blocks >= kMaxBlocks256) return false;
   a.c.tiles_max = (int32_t)tiles;
@@ -677,7 +817,7 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, Launch& l) {
 }
 
 // launches v[0 ... count) of one variant, which lie at tab[first] ... in the plan's table
-template <int MT, int PA, int PB>
+template <int MT, int PA, int PB, bool FEW>
 int launch_variant(distdl_plan* p, const SplitArgs* tab, int first, const Launch* v, int count, const u32x4* wt, const float* w,
                    const float* bias, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
   unsigned blocks = 0;
@@ -686,18 +826,18 @@ int launch_variant(distdl_plan* p, const SplitArgs* tab, int first, const Launch
   if (count > 1 && blocks <= 2048) {
     if (blocks == 0) return DISTDL_OK;
     if (lds > 64 * 1024)
-      if (int rc = allow_large_lds<corr_split_classes_kernel<MT, PA, PB>>()) return rc;
+      if (int rc = allow_large_lds<corr_split_classes_kernel<MT, PA, PB, FEW>>()) return rc;
     ProfScope prof(name, st);
-    hipLaunchKernelGGL((corr_split_classes_kernel<MT, PA, PB>), dim3(blocks, (unsigned)count), dim3(256), lds, st, p->d_workers,
+    hipLaunchKernelGGL((corr_split_classes_kernel<MT, PA, PB, FEW>), dim3(blocks, (unsigned)count), dim3(256), lds, st, p->d_workers,
                        in_tab, out_tab, tab, first, wt, w, bias);
     return DISTDL_OK;
   }
   if (lds > 64 * 1024)
-    if (int rc = allow_large_lds<corr_split_kernel<MT, PA, PB>>()) return rc;
+    if (int rc = allow_large_lds<corr_split_kernel<MT, PA, PB, FEW>>()) return rc;
   for (int i = 0; i < count; ++i) {
     if (v[i].blocks == 0) continue;
     ProfScope prof(name, st);
-    hipLaunchKernelGGL((corr_split_kernel<MT, PA, PB>), dim3(v[i].blocks), dim3(256), split_lds_bytes(PA, v[i].a.c.ck), st,
+    hipLaunchKernelGGL((corr_split_kernel<MT, PA, PB, FEW>), dim3(v[i].blocks), dim3(256), split_lds_bytes(PA, v[i].a.c.ck), st,
                        p->d_workers, in_tab, out_tab, v[i].a, wt, w, bias);
   }
   return DISTDL_OK;
@@ -730,7 +870,8 @@ int run_split(distdl_plan* p, int dir, const float* w, const float* bias, void**
     hipLaunchKernelGGL(corr_split_weights_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)d.v.size()), dim3(256), 0, st,
                        sp.dev, first, w, wt);
   }
-  constexpr int kPb = (kGroupTaps * 192 + 255) / 256, kPb3 = (9 * 192 + 255) / 256;
+  constexpr int kPb = (kGroupTaps * 192 + 255) / 256, kPb3 = (9 * 192 + 255) / 256,
+                kPbFew = (kFewTaps * 192 + 255) / 256;
   for (size_t i = 0; i < d.v.size();) {
     size_t e = i;
     while (e < d.v.size() && d.v[e].variant == d.v[i].variant) ++e;
@@ -738,10 +879,16 @@ int run_split(distdl_plan* p, int dir, const float* w, const float* bias, void**
     const int at = first + (int)i, n = (int)(e - i);
     int rc;
     switch (v->variant) {
-      case 0: rc = launch_variant<1, 4, kPb>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st); break;
-      case 1: rc = launch_variant<2, 3, kPb>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st); break;
-      case 2: rc = launch_variant<2, 4, kPb>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st); break;
-      default: rc = launch_variant<3, 4, kPb3>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st);
+#define DISTDL_SPLIT(MT_, PA_, PB_, FEW_) \
+  rc = launch_variant<MT_, PA_, PB_, FEW_>(p, sp.dev, at, v, n, wt, w, bias, in_tab, out_tab, name, st)
+      case 0: DISTDL_SPLIT(1, 4, kPb, false); break;
+      case 1: DISTDL_SPLIT(2, 3, kPb, false); break;
+      case 2: DISTDL_SPLIT(2, 4, kPb, false); break;
+      case 3: DISTDL_SPLIT(3, 4, kPb3, false); break;
+      case 4: DISTDL_SPLIT(1, 4, kPbFew, true); break;
+      case 5: DISTDL_SPLIT(2, 3, kPbFew, true); break;
+      default: DISTDL_SPLIT(2, 4, kPbFew, true);
+#undef DISTDL_SPLIT
     }
     if (rc) return rc;
     i = e;
@@ -764,23 +911,35 @@ SplitPlan* split_plan(const distdl_plan* p) {
   for (int dir = 0; dir < 2; ++dir) {
     if ((dir == 0 ? p->n_ci : p->n_co) % 4) continue;  // the tensor that is read comes in 16-byte pieces
     Launches& d = sp->dir[dir];
-    auto add = [&](const CorrArgs& c) {
-      d.v.emplace_back();
-      return plan_launch(p, c, d.v.back());
-    };
-    bool ok = true;
-    if (dir == 0) ok = add(forward_args(p));
-    else
-      for (int p0 = 0; p0 < p->stride[0]; ++p0)
-        for (int p1 = 0; p1 < p->stride[1]; ++p1)
-          for (int p2 = 0; p2 < p->stride[2]; ++p2) {
-            const int par[3] = {p0, p1, p2};
-            ok = ok && add(class_args(p, par));
-          }
-    if (!ok) {
-      d.v.clear();
-      continue;
+    // The launches with `fold` cells to a position (data gradient: a class per residue of the dimensions that are not folded),
+    // of all folds those that are estimated to take the least time
+    double least = 1e300;
+    const int nch = (int)(dir == 0 ? p->n_co : p->n_ci), kc = (int)(dir == 0 ? p->n_ci : p->n_co), s2 = dir == 0 ? 1 : p->stride[2];
+    for (int fold = 1; fold <= 32; fold = fold < s2 ? s2 : fold + s2) {
+      if (fold > 1 && fold * nch > 32 && fold != s2) break;
+      for (const bool octet : {false, true}) {
+      if (octet && (kc % 16 == 0 || kc % 16 > 8)) continue;
+      Launches l;
+      double sum = 0, most = 0;  // (classes that fill the chip together only are one launch)
+      bool ok = true;
+      auto add = [&](const CorrArgs& c) {
+        l.v.emplace_back();
+        ok = ok && plan_launch(p, c, fold, octet, l.v.back());
+        sum += l.v.back().clocks * l.v.back().share;
+        most = std::max(most, l.v.back().clocks);
+      };
+      if (dir == 0) add(forward_args(p));
+      else
+        for (int p0 = 0; p0 < p->stride[0]; ++p0)
+          for (int p1 = 0; p1 < p->stride[1]; ++p1)
+            for (int p2 = 0; p2 < (fold == 1 ? p->stride[2] : 1); ++p2) {
+              const int par[3] = {p0, p1, p2};
+              add(class_args(p, par));
+            }
+      if (const double clocks = std::max(sum, most); ok && clocks < 0.97 * least) least = clocks, d = l;
+      }
     }
+    if (d.v.empty()) continue;
     std::stable_sort(d.v.begin(), d.v.end(), [](const Launch& x, const Launch& y) { return x.variant < y.variant; });
     for (Launch& l : d.v) {
       l.a.woff = d.pieces;

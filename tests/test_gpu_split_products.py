@@ -62,6 +62,36 @@ def test_conv_with_a_weight_that_is_not_finite(shape):
         assert bool(plain.any()) and _rel(got[plain], want[plain]) < 5e-6, name
 
 
+# few channels: several cells to a position (two, three, four; rows that end within one; strides; classes that are launches of
+# their own), pairs of taps to a product, both; one to three dimensions
+FEW = [(6, 8, 4, (28, 30, 45), 3, 2), (2, 3, 32, (120, 130), 7, 2), (3, 3, 40, (2000,), 7, 2), (2, 8, 36, (90, 100), 5, 2),
+       (2, 40, 3, (260, 250), 3, 1), (1, 6, 20, (25, 30, 26), 4, 3), (4, 20, 8, (300, 280), 3, 1)]
+FEW_IDS = ["x".join(map(str, v[3])) + f"c{v[1]}-{v[2]}s{v[5]}" for v in FEW]
+
+
+@pytest.mark.parametrize("dilation", [1, 2])
+@pytest.mark.parametrize("shape", FEW, ids=FEW_IDS)
+def test_layers_of_few_channels(shape, dilation):
+    """Sums of at most 2000 products: 5e-6, as above."""
+    require_gpu()
+    L = ConvLayer(*shape, dil=dilation)
+    L.y.fill_(7.0), L.dx.fill_(5.0)
+    for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
+        assert _rel(got, want) < 5e-6, name
+        assert float((got.double() - want).abs().max() / want.abs().max()) < 1e-5, name
+
+
+@pytest.mark.parametrize("shape", FEW, ids=FEW_IDS)
+def test_few_channels_with_infinities_and_nans(shape):
+    """The zeros that fill up the weights of a position meet infinities that its cell has nothing to do with."""
+    test_conv_with_infinities_and_nans(shape)
+
+
+@pytest.mark.parametrize("shape", FEW, ids=FEW_IDS)
+def test_few_channels_with_a_weight_that_is_not_finite(shape):
+    test_conv_with_a_weight_that_is_not_finite(shape)
+
+
 @pytest.mark.parametrize("small", ["x", "w", "dy"])
 @pytest.mark.parametrize("shape", LAYERS, ids=IDS)
 def test_conv_of_very_small_numbers(shape, small):
