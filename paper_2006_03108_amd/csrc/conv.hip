@@ -21,6 +21,7 @@
 #include "conv_split.h"
 #include "conv_wsplit.h"
 #include "profile.h"
+#include "weight_job.h"
 
 namespace distdl {
 
@@ -184,9 +185,12 @@ __global__ __launch_bounds__(256) void conv_bwd_weight_direct_kernel(const Worke
 
 // R dw^, R db^ (Sec. 4, adjoint algorithm): sum the partials in worker order
 // and write dw in the caller's [Co][Ci][T] shape.
-template <int E, class T>
+template <int E, class T, bool JOB>
 __global__ __launch_bounds__(256) void conv_reduce_dw_kernel(const float* __restrict__ partial, int nparts,
-                                                             T* __restrict__ dw, T* __restrict__ db, ConvDev c) {
+                                                             T* __restrict__ dw, T* __restrict__ db, ConvDev c, JobArg<JOB> job) {
+  if constexpr (JOB) {  // (the data gradient's weights)
+    if ((int)blockIdx.x >= job.at) return run_weight_job(job, (int)blockIdx.x - job.at);
+  }
   // E elements per block, L = 256 / E lanes of partials each (few elements: more lanes, so that the launch still
   // has enough blocks); every lane adds its partials in ascending order (four independent chains for latency),
   // the lanes are then combined in ascending order
@@ -302,6 +306,12 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
   }
 }
 
+// The weights of a launch of `kernel` that a launch before it can lay out.
+static int weight_job(distdl_plan* p, Corr kernel, bool backward, const void* w, bool aligned, hipStream_t st, WeightJob& job) {
+  if (kernel == Corr::kSplit) return split_weight_job(p, backward, (const float*)w, st, job);
+  return kernel == Corr::kAny ? any_weight_job(p, backward, w, aligned, st, job) : DISTDL_OK;
+}
+
 static int prepare_weights(distdl_plan* p, const void* w, hipStream_t st) {
   ConvDev c = conv_params(p);
   size_t n = (size_t)c.taps * c.ci * c.co;
@@ -393,19 +403,23 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
   const uintptr_t esz = bf16 ? 2 : 4;
   for (int w = 0; w < plan->n_workers; ++w)
     if (!y_dev[w] || (uintptr_t)y_dev[w] % esz) return set_error(DISTDL_ERR_NULL, "conv_fwd: y of worker %d null or misaligned", w);
-  if (halo) {
-    if ((rc = run_halo(plan, false, plan->tab_x, x_bufs_dev, st))) return rc;  // x <- H x
-  } else {
-    if ((rc = plan_prepare_device(plan))) return rc;
-    for (int w = 0; w < plan->n_workers; ++w)
-      if (!x_bufs_dev[w] || (uintptr_t)x_bufs_dev[w] % esz) return set_error(DISTDL_ERR_NULL, "conv_fwd: x of worker %d null or misaligned", w);
-  }
-  if ((rc = plan->tab_x.upload((const void* const*)x_bufs_dev, plan->n_workers, st))) return rc;
-  if ((rc = plan->tab_y.upload((const void* const*)y_dev, plan->n_workers, st))) return rc;
   // 16-byte pieces on both sides: the matrix-core kernels load x in them and store y in them
   bool xvec = true;
   for (int w = 0; w < plan->n_workers; ++w) xvec &= (uintptr_t)x_bufs_dev[w] % 16 == 0 && (uintptr_t)y_dev[w] % 16 == 0;
   const Corr kernel = choose_fwd(plan, xvec, (uintptr_t)w_dev % 16 == 0);
+  WeightJob job;
+  if (halo) {
+    if ((rc = weight_job(plan, kernel, false, w_dev, xvec, st, job))) return rc;
+    if ((rc = run_halo_with(plan, false, plan->tab_x, x_bufs_dev, &job, st))) return rc;  // x <- H x
+  } else {
+    if ((rc = plan_prepare_device(plan))) return rc;
+    for (int w = 0; w < plan->n_workers; ++w)
+      if (!x_bufs_dev[w] || (uintptr_t)x_bufs_dev[w] % esz) return set_error(DISTDL_ERR_NULL, "conv_fwd: x of worker %d null or misaligned", w);
+    if ((rc = weight_job(plan, kernel, false, w_dev, xvec, st, job))) return rc;
+  }
+  if ((rc = plan->tab_x.upload((const void* const*)x_bufs_dev, plan->n_workers, st))) return rc;
+  if ((rc = plan->tab_y.upload((const void* const*)y_dev, plan->n_workers, st))) return rc;
+  if ((rc = launch_weight_job(job, st))) return rc;  // (where H has no launch)
   if (kernel != Corr::kDirect) {
     switch (kernel) {
       case Corr::k16: rc = conv_fwd16(plan, (const float*)w_dev, (const float*)bias_dev, xvec, st); break;
@@ -459,29 +473,11 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   bool vec16 = aligned && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
   for (int w = 0; w < plan->n_workers; ++w) vec16 &= (uintptr_t)x_bufs_dev[w] % 16 == 0;
   const Wgrad wgrad = choose_wgrad(plan, vec16);
-  // [dConv]* with respect to x, into the whole padded buffers
   int64_t total = plan->n_b * plan->max_buf_cells * c.ci;
   const Corr kernel = choose_data(plan, aligned);
-  if (kernel == Corr::k16) {
-    if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
-  } else if (kernel == Corr::kSplit) {
-    if ((rc = conv_bwd_data_split(plan, (const float*)w_dev, st))) return rc;
-  } else if (kernel == Corr::kMfma) {
-    if ((rc = conv_bwd_data_mfma(plan, w_dev, st))) return rc;
-  } else if (kernel == Corr::kAny) {
-    if ((rc = conv_bwd_data_any(plan, w_dev, aligned, st))) return rc;
-  } else {
-    if ((rc = prepare_weights(plan, w_dev, st))) return rc;
-    ProfScope prof("conv_bwd_data_direct", st);
-    const dim3 dgrid((unsigned)((total + 255) / 256), plan->n_workers);
-    if (bf16)
-      hipLaunchKernelGGL(conv_bwd_data_direct_kernel<uint16_t>, dgrid, dim3(256), 0, st, plan->d_workers,
-                         plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
-    else
-      hipLaunchKernelGGL(conv_bwd_data_direct_kernel<float>, dgrid, dim3(256), 0, st, plan->d_workers,
-                         plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
-  }
-  // [dConv]* with respect to w and b, then R over the workers
+  WeightJob job;
+  if ((rc = weight_job(plan, kernel, true, w_dev, aligned, st, job))) return rc;
+  // [dConv]* with respect to w and b, then R over the workers, whose launch lays out the data gradient's weights
   const int nchunks = wgrad_partials(plan, wgrad, vec16);
   int nw = c.taps * c.ci * c.co + c.co;
   if (wgrad == Wgrad::k16) {
@@ -504,20 +500,45 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   }
   {
     ProfScope prof("conv_reduce_dw", st);
-    const float* part = (const float*)workspace_dev;
     const int nparts = nchunks * plan->n_workers;
-    if (nw <= 8192 && bf16)
-      hipLaunchKernelGGL((conv_reduce_dw_kernel<16, uint16_t>), dim3((unsigned)((nw + 15) / 16)), dim3(256), 0, st, part,
-                         nparts, (uint16_t*)dw_dev, (uint16_t*)dbias_dev, c);
-    else if (nw <= 8192)
-      hipLaunchKernelGGL((conv_reduce_dw_kernel<16, float>), dim3((unsigned)((nw + 15) / 16)), dim3(256), 0, st, part,
-                         nparts, (float*)dw_dev, (float*)dbias_dev, c);
-    else if (bf16)
-      hipLaunchKernelGGL((conv_reduce_dw_kernel<64, uint16_t>), dim3((unsigned)((nw + 63) / 64)), dim3(256), 0, st, part,
-                         nparts, (uint16_t*)dw_dev, (uint16_t*)dbias_dev, c);
+    auto reduce = [&](auto e, auto elem) {
+      typedef decltype(elem) T;
+      constexpr int E = decltype(e)::value;
+      dim3 grid((unsigned)((nw + E - 1) / E));
+      if (job.kind != 0 && (int64_t)grid.x + job.blocks < kMaxBlocks256) {
+        job.at = (int32_t)grid.x;
+        grid.x += (unsigned)job.blocks;
+        hipLaunchKernelGGL((conv_reduce_dw_kernel<E, T, true>), grid, dim3(256), 0, st, (const float*)workspace_dev, nparts,
+                           (T*)dw_dev, (T*)dbias_dev, c, job);
+        job.kind = 0;
+      } else {
+        hipLaunchKernelGGL((conv_reduce_dw_kernel<E, T, false>), grid, dim3(256), 0, st, (const float*)workspace_dev, nparts,
+                           (T*)dw_dev, (T*)dbias_dev, c, NoJob{});
+      }
+    };
+    auto by_type = [&](auto e) { bf16 ? reduce(e, uint16_t{}) : reduce(e, float{}); };
+    nw <= 8192 ? by_type(std::integral_constant<int, 16>{}) : by_type(std::integral_constant<int, 64>{});
+  }
+  if ((rc = launch_weight_job(job, st))) return rc;
+  // [dConv]* with respect to x, into the whole padded buffers
+  if (kernel == Corr::k16) {
+    if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
+  } else if (kernel == Corr::kSplit) {
+    if ((rc = conv_bwd_data_split(plan, (const float*)w_dev, st))) return rc;
+  } else if (kernel == Corr::kMfma) {
+    if ((rc = conv_bwd_data_mfma(plan, w_dev, st))) return rc;
+  } else if (kernel == Corr::kAny) {
+    if ((rc = conv_bwd_data_any(plan, w_dev, aligned, st))) return rc;
+  } else {
+    if ((rc = prepare_weights(plan, w_dev, st))) return rc;
+    ProfScope prof("conv_bwd_data_direct", st);
+    const dim3 dgrid((unsigned)((total + 255) / 256), plan->n_workers);
+    if (bf16)
+      hipLaunchKernelGGL(conv_bwd_data_direct_kernel<uint16_t>, dgrid, dim3(256), 0, st, plan->d_workers,
+                         plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
     else
-      hipLaunchKernelGGL((conv_reduce_dw_kernel<64, float>), dim3((unsigned)((nw + 63) / 64)), dim3(256), 0, st, part,
-                         nparts, (float*)dw_dev, (float*)dbias_dev, c);
+      hipLaunchKernelGGL(conv_bwd_data_direct_kernel<float>, dgrid, dim3(256), 0, st, plan->d_workers,
+                         plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
   }
   DISTDL_HIP_TRY(hipGetLastError());
   // dx <- H* dx

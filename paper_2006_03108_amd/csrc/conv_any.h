@@ -2,10 +2,13 @@
 // points expect the plan's pointer tables to be uploaded; `aligned`: the arrays that are read are 16-byte aligned.
 #pragma once
 #include "common.h"
+#include "weight_job.h"
 
 namespace distdl {
 
 bool conv_any_supported(const distdl_plan* p);
+// The job that has to be done before either of the following.
+int any_weight_job(distdl_plan* p, bool backward, const void* w, bool aligned, hipStream_t st, WeightJob& job);
 int conv_fwd_any(distdl_plan* p, const void* w, const void* bias, bool aligned, hipStream_t st);
 int conv_bwd_data_any(distdl_plan* p, const void* w, bool aligned, hipStream_t st);
 int wgrad_any_chunks(const distdl_plan* p);

@@ -29,6 +29,7 @@
 #include "conv_mfma.h"
 #include "profile.h"
 #include "split_bf16.h"
+#include "weight_job.h"
 
 namespace distdl {
 
@@ -40,19 +41,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GiB)
-constexpr int kMaxCls = 64;
-
-struct AnyArgs {
-  int32_t mode;          // 0: forward, 1: data gradient
-  int32_t n_b, kc, nc;   // batch, contraction channels, output channels
-  int32_t k[3], s[3], dil[3];
-  int32_t n_workers, ntn, ncls, tiles_max;
-  int32_t ci, co, taps;
-  const u32x4* wt;         // weights as operand pieces
-  const void* w;           // the caller's weights
-  const void* bias;        // may be null
-  int32_t woff[kMaxCls];   // first octet of a class's weights
-};
 
 struct WgradAnyArgs {
   int32_t n_b, ci, co;
@@ -60,15 +48,6 @@ struct WgradAnyArgs {
   int32_t nchunks, ntm, ntn;  // position chunks per worker, row tiles, column tiles
   int32_t rows;               // taps * ci
   int64_t slot;
-};
-
-template <bool BF16>
-struct Elem {
-  typedef float T;
-};
-template <>
-struct Elem<true> {
-  typedef uint16_t T;
 };
 
 __device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
@@ -99,20 +78,6 @@ struct DimAny {
   int32_t step, in0, dt;   // input coordinate of tap i at position q: in0 + q * step + i * dt
   int32_t nq, in_ext, out_ext, out0, ostep;
 };
-__host__ __device__ inline int gcd_of(int a, int b) {
-  while (b) {
-    const int t = a % b;
-    a = b, b = t;
-  }
-  return a;
-}
-// taps along one dimension of parity class `par`: t * dil == par modulo s
-__host__ __device__ inline void class_taps(int k, int s, int dil, int par, int& nt, int& tf, int& ts) {
-  ts = s / gcd_of(dil, s);
-  tf = 0;
-  while (tf < ts && (tf * dil) % s != par) ++tf;
-  nt = tf < ts && tf < k ? (k - 1 - tf) / ts + 1 : 0;
-}
 // (d is a template argument: indexed at run time the geometry would lie in scratch memory, and what is read from there counts
 // as different in every lane, the buffers' descriptors too)
 template <int d>
@@ -133,7 +98,6 @@ __device__ __forceinline__ DimAny dim_any(const WorkerDev& wd, const AnyArgs& a,
   return g;
 }
 
-constexpr int planes_of(bool bf16) { return bf16 ? 1 : 3; }
 // ROWS rows x KS octets of k per stage: 1024 pieces of A
 constexpr int octets_of(int ROWS) { return 1024 / ROWS; }
 // a little more than the planes, so that the pieces that eight neighbouring lanes write fall into different banks
@@ -144,36 +108,12 @@ constexpr int any_lds(int ROWS, int NT, bool bf16) {
   // (64 rows: four partial tiles at the end); the outputs of the rows, the word that asks for fp32 products
   return std::max(stage, ROWS == 64 ? 4 * 64 * 32 * NT * 4 : 0) + ROWS * 4 + 16;
 }
-constexpr int kOctPad = 16;  // a class's weights are padded to whole stages of either kind
-
 // n / d for n, d < 2^22 through the reciprocal
 __device__ inline int div_by(int n, int d, float rcp) {
   int q = (int)((float)n * rcp);
   q -= q * d > n;
   q += (q + 1) * d <= n;
   return q;
-}
-
-// eight values -> the operand pieces of one (octet, row); RAW: as they are, for fp32 MFMAs
-template <bool BF16, bool RAW = false>
-__device__ inline void put_octet(char* at, uint32_t plane, const float (&v)[8]) {
-  if constexpr (BF16) {
-    u32x4 h;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) h[j] = pack_bf16(v[2 * j], v[2 * j + 1]);  // exact
-    *(u32x4*)at = h;
-  } else if constexpr (RAW) {
-    u32x4 u, w;
-    halve_eight(v, u, w);
-    *(u32x4*)at = u;
-    *(u32x4*)(at + plane) = w;
-  } else {
-    u32x4 h, m, l;
-    split_eight(v, kSplitScale, h, m, l);
-    *(u32x4*)at = h;
-    *(u32x4*)(at + plane) = m;
-    *(u32x4*)(at + 2 * plane) = l;
-  }
 }
 
 // the products of two 16-k slices, smallest first; la, lb: this wave's first row and octet
@@ -260,34 +200,6 @@ struct Sums {
     return !any_not_finite(seen);
   }
 };
-
-// octet `oct` of output channel ch of a class: the weights, or zero beyond the channels and taps
-template <bool BF16, bool FLAT>
-__device__ inline void weight_octet(const AnyArgs& a, const int (&nt)[3], const int (&tf)[3], const int (&ts)[3], int oct, int ch,
-                                    float (&v)[8]) {
-  const int ntaps = nt[0] * nt[1] * nt[2], noct = (a.kc + 7) / 8;
-  bool ok[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    int tap, c;
-    if (FLAT) {
-      const int k = oct * 8 + e;
-      tap = k / a.kc, c = k - tap * a.kc;
-    } else {
-      tap = oct / noct, c = (oct - tap * noct) * 8 + e;
-    }
-    ok[e] = tap < ntaps && c < a.kc && ch < a.nc;
-    const int i2 = tap % nt[2], i01 = tap / nt[2], i1 = i01 % nt[1], i0 = i01 / nt[1];
-    const int t = ((tf[0] + i0 * ts[0]) * a.k[1] + tf[1] + i1 * ts[1]) * a.k[2] + tf[2] + i2 * ts[2];
-    const int oc = a.mode == 0 ? ch : c, ic = a.mode == 0 ? c : ch;
-    v[e] = ld((const typename Elem<BF16>::T*)a.w, ok[e] ? ((size_t)oc * a.ci + ic) * a.taps + t : (size_t)0);
-  }
-  // (loaded in any case and all at once: left alone the compiler makes a branch, and a wait, of each)
-#pragma unroll
-  for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(v[e]));
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = ok[e] ? v[e] : 0.f;
-}
 
 // Data gradient, output element (position, channel) term by term: only those taps whose output exists (in the product of a
 // tile the others are zeros, which do not cancel a weight that is not finite).  A NaN ends it.
@@ -493,7 +405,7 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
         for (int piece = tid; piece < KS * 32 * NT; piece += 256) {  // [octet][column]
           const int col = piece % (32 * NT), oct = piece / (32 * NT);
           float wv[8];
-          weight_octet<BF16, FLAT>(a, nt3, tf3, ts3, st * KS + oct, ntile * 32 * NT + col, wv);
+          any_weight_octet<BF16, FLAT>(a, nt3, tf3, ts3, st * KS + oct, ntile * 32 * NT + col, wv);
           put_octet<BF16, true>(lb + oct * b_pitch(NT, BF16) + col * 16, 32 * NT * 16, wv);
           if constexpr (MODE == 1) {
 #pragma unroll
@@ -569,30 +481,6 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
       }
     }
   }
-}
-
-// Weights as the correlation stages them: pieces [class][column tile][octet][plane][column], 8 k each; zero beyond the
-// channels and taps.  One thread per (column tile, octet, column), all planes; grid.y = class.
-template <int NT, bool BF16, bool FLAT>
-__global__ __launch_bounds__(256) void corr_any_weights_kernel(AnyArgs a, u32x4* __restrict__ dst) {
-  constexpr int PL = planes_of(BF16);
-  const int cls = (int)blockIdx.y;
-  const int par[3] = {cls / (a.s[1] * a.s[2]), cls / a.s[2] % a.s[1], cls % a.s[2]};
-  int nt[3], tf[3], ts[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    if (a.mode == 0) nt[d] = a.k[d], tf[d] = 0, ts[d] = 1;
-    else class_taps(a.k[d], a.s[d], a.dil[d], par[d], nt[d], tf[d], ts[d]);
-  }
-  const int ntaps = nt[0] * nt[1] * nt[2], noct = (a.kc + 7) / 8;
-  const int K = FLAT ? ntaps * a.kc : ntaps * noct * 8, octs = (K + 8 * kOctPad - 1) / (8 * kOctPad) * kOctPad;
-  const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
-  if (idx >= a.ntn * octs * 32 * NT) return;
-  const int col = idx % (32 * NT), r = idx / (32 * NT), oct = r % octs, ntile = r / octs;
-  float v[8];
-  weight_octet<BF16, FLAT>(a, nt, tf, ts, oct, ntile * 32 * NT + col, v);
-  u32x4* const at = dst + ((size_t)a.woff[cls] * a.ntn + (size_t)ntile * octs + oct) * (PL * 32 * NT) + col;
-  put_octet<BF16>((char*)at, 32 * NT * 16, v);
 }
 
 // grid: (row tiles * column tiles, chunks, workers)
@@ -795,15 +683,7 @@ size_t weight_floats(const distdl_plan* p, int mode) {
 }
 
 template <int ROWS, int NT, bool BF16, int MODE, bool VEC>
-int launch_corr_any(distdl_plan* p, const AnyArgs& a, void** in_tab, void** out_tab, int most, const char* name, hipStream_t st) {
-  constexpr bool FLAT = MODE == 0 || VEC;
-  {
-    ProfScope prof("conv_relayout_w", st);
-    const int64_t n = (int64_t)a.ntn * most * 32 * NT;
-    if (n > 0)
-      hipLaunchKernelGGL((corr_any_weights_kernel<NT, BF16, FLAT>), dim3((unsigned)((n + 255) / 256), (unsigned)a.ncls),
-                         dim3(256), 0, st, a, (u32x4*)p->d_wt);
-  }
+int launch_corr_any(distdl_plan* p, const AnyArgs& a, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
   constexpr int lds = any_lds(ROWS, NT, BF16);
   const int64_t blocks = ((int64_t)a.tiles_max * p->n_workers + 7) / 8 * 8;
   if (lds > 64 * 1024)
@@ -815,35 +695,49 @@ int launch_corr_any(distdl_plan* p, const AnyArgs& a, void** in_tab, void** out_
 }
 
 template <int ROWS, int NT, bool BF16>
-int pick_corr_any(distdl_plan* p, const AnyArgs& a, bool vec, void** in_tab, void** out_tab, int most, const char* name, hipStream_t st) {
+int pick_corr_any(distdl_plan* p, const AnyArgs& a, bool vec, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
   if (a.mode == 0)
-    return vec ? launch_corr_any<ROWS, NT, BF16, 0, true>(p, a, in_tab, out_tab, most, name, st)
-               : launch_corr_any<ROWS, NT, BF16, 0, false>(p, a, in_tab, out_tab, most, name, st);
-  return vec ? launch_corr_any<ROWS, NT, BF16, 1, true>(p, a, in_tab, out_tab, most, name, st)
-             : launch_corr_any<ROWS, NT, BF16, 1, false>(p, a, in_tab, out_tab, most, name, st);
+    return vec ? launch_corr_any<ROWS, NT, BF16, 0, true>(p, a, in_tab, out_tab, name, st)
+               : launch_corr_any<ROWS, NT, BF16, 0, false>(p, a, in_tab, out_tab, name, st);
+  return vec ? launch_corr_any<ROWS, NT, BF16, 1, true>(p, a, in_tab, out_tab, name, st)
+             : launch_corr_any<ROWS, NT, BF16, 1, false>(p, a, in_tab, out_tab, name, st);
+}
+
+// The launch of a direction: its arguments, rows of a tile, columns / 32; most: octets of weights of its largest class
+struct AnyLaunch {
+  AnyArgs a;
+  bool vec, few;
+  int NT, most;
+};
+AnyLaunch any_launch(const distdl_plan* p, int mode, bool aligned) {
+  AnyLaunch l;
+  l.NT = nt_of(mode == 0 ? p->n_co : p->n_ci);
+  l.a = any_args(p, mode, l.NT);
+  AnyArgs& a = l.a;
+  l.vec = aligned && a.kc % 4 == 0;
+  class_octets(a, flat_k(a, l.vec), a.woff, l.most);
+  // 64 rows where 256 would leave compute units idle and there is enough k for four waves (32 columns: with 64 their
+  // accumulators and the larger stages of weights do not fit the registers)
+  const int64_t pos = positions_max(p, a);
+  l.few = (pos + 255) / 256 * a.ntn * p->n_workers * a.ncls < 384 && l.most > kOctPad;
+  const int rows = l.few ? 64 : 256;
+  if (l.few) l.NT = 1, a.ntn = (a.nc + 31) / 32;
+  a.tiles_max = (int32_t)((pos + rows - 1) / rows * a.ntn);
+  return l;
 }
 
 int run_corr_any(distdl_plan* p, int mode, const void* w, const void* bias, bool aligned, void** in_tab, void** out_tab,
                  const char* name, hipStream_t st) {
-  int NT = nt_of(mode == 0 ? p->n_co : p->n_ci);
-  AnyArgs a = any_args(p, mode, NT);
-  const bool vec = aligned && a.kc % 4 == 0, bf16 = p->dtype == DISTDL_BF16;
-  int most;
-  class_octets(a, flat_k(a, vec), a.woff, most);
-  // 64 rows where 256 would leave compute units idle and there is enough k for four waves (32 columns: with 64 their
-  // accumulators and the larger stages of weights do not fit the registers)
-  const int64_t pos = positions_max(p, a);
-  const bool few = (pos + 255) / 256 * a.ntn * p->n_workers * a.ncls < 384 && most > kOctPad;
-  const int rows = few ? 64 : 256;
-  if (few) NT = 1, a.ntn = (a.nc + 31) / 32;
-  if (int rc = ensure_wscratch(p, std::max(weight_floats(p, 0), weight_floats(p, 1)), st)) return rc;
+  AnyLaunch l = any_launch(p, mode, aligned);
+  AnyArgs& a = l.a;
+  const bool vec = l.vec, few = l.few, bf16 = p->dtype == DISTDL_BF16;
+  const int NT = l.NT;
   a.w = w;
   a.bias = bias;
   a.wt = (const u32x4*)p->d_wt;
-  a.tiles_max = (int32_t)((pos + rows - 1) / rows * a.ntn);
 #define DISTDL_ANY(ROWS_, NT_)                                                               \
-  (bf16 ? pick_corr_any<ROWS_, NT_, true>(p, a, vec, in_tab, out_tab, most, name, st)        \
-        : pick_corr_any<ROWS_, NT_, false>(p, a, vec, in_tab, out_tab, most, name, st))
+  (bf16 ? pick_corr_any<ROWS_, NT_, true>(p, a, vec, in_tab, out_tab, name, st)        \
+        : pick_corr_any<ROWS_, NT_, false>(p, a, vec, in_tab, out_tab, name, st))
   return few ? DISTDL_ANY(64, 1) : NT == 1 ? DISTDL_ANY(256, 1) : DISTDL_ANY(256, 2);
 #undef DISTDL_ANY
 }
@@ -869,6 +763,21 @@ bool conv_any_supported(const distdl_plan* p) {
     if ((double)(positions_max(p, a) / 256 + 1) * a.ntn * p->n_workers + 8 >= kMaxBlocks256) return false;
   }
   return p->n_workers <= 65535;
+}
+
+int any_weight_job(distdl_plan* p, bool backward, const void* w, bool aligned, hipStream_t st, WeightJob& job) {
+  if (int rc = ensure_wscratch(p, std::max(weight_floats(p, 0), weight_floats(p, 1)), st)) return rc;
+  const AnyLaunch l = any_launch(p, backward ? 1 : 0, aligned);
+  job.any = l.a;
+  job.any.w = w;
+  job.bf16 = p->dtype == DISTDL_BF16;
+  job.flat = flat_k(l.a, l.vec);
+  job.cols = 32 * l.NT;
+  job.dst = (u32x4*)p->d_wt;
+  job.per_class = (int32_t)(((int64_t)l.a.ntn * l.most * job.cols + 255) / 256);
+  job.blocks = job.per_class * l.a.ncls;
+  job.kind = job.blocks > 0 ? 2 : 0;
+  return DISTDL_OK;
 }
 
 int conv_fwd_any(distdl_plan* p, const void* w, const void* bias, bool aligned, hipStream_t st) {

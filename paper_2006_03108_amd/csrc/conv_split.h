@@ -3,10 +3,13 @@
 // are 16-byte aligned.
 #pragma once
 #include "common.h"
+#include "weight_job.h"
 
 namespace distdl {
 
 bool corr_split_supported(const distdl_plan* p, bool backward);
+// The job that has to be done before either of the following.
+int split_weight_job(distdl_plan* p, bool backward, const float* w, hipStream_t st, WeightJob& job);
 int conv_fwd_split(distdl_plan* p, const float* w, const float* bias, hipStream_t st);
 int conv_bwd_data_split(distdl_plan* p, const float* w, hipStream_t st);
 

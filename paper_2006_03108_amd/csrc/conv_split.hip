@@ -37,6 +37,7 @@
 #include "conv_split.h"
 #include "profile.h"
 #include "split_bf16.h"
+#include "weight_job.h"
 
 namespace distdl {
 
@@ -47,29 +48,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GiB)
-constexpr int kMaxGroups = 32, kMaxTaps = 64, kGroupTaps = 10, kFewTaps = 8, kMaxOff2 = 40;
+constexpr int kGroupTaps = 10, kFewTaps = 8;
 
-struct SplitArgs {
-  CorrArgs c;
-  int32_t ci, co, taps, k1, k2;
-  int64_t woff;                             // first weight piece
-  int32_t ngroups;
-  int32_t gbegin[kMaxGroups + 1];           // taps of group i: gbegin[i] ... gbegin[i + 1]
-  int32_t gbase[kMaxGroups][2];             // input offset of the group's first patch row / cell (of position 0)
-  int32_t tapcell[kMaxTaps];                // patch cell of a tap for position 0
-  uint8_t tap12[kMaxTaps][2];               // its indices along dimensions 1 and 2
-  int32_t fold, nch;                        // cells along dimension 2 that are one position's columns; channels of a cell
-  FastDiv div_nch;
-  int32_t dil2;
-  int32_t off2[kMaxOff2];                   // input offset of tap i along dimension 2
-  int32_t nfull, npairs;                    // chunks of 16 channels; MFMAs of a last chunk of at most 8 (0: there is none)
-  int32_t hbegin[kMaxGroups + 1];           // of these those of group i
-};
-
-// The arguments of a launch of several classes lie in a table of the plan's; read through the constant address space its
-// entries are scalar loads.
-typedef const __attribute__((address_space(4))) SplitArgs* TablePtr;
-__device__ inline TablePtr args_at(const SplitArgs* tab, int i) { return (TablePtr)(uintptr_t)(tab + i); }
 template <class ArgsPtr>
 __host__ __device__ inline PerWorker derive_of(const WorkerDev& wd, ArgsPtr a) {
   CorrArgs c;
@@ -97,34 +77,6 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) 
 constexpr uint32_t half_bytes(int PA) { return PA * 2048; }
 constexpr uint32_t plane_bytes(int PA) { return 2 * half_bytes(PA); }
 constexpr int split_lds_bytes(int PA, int taps) { return 3 * plane_bytes(PA) + taps * 3072 + 16; }
-
-// The layer's tap along dimension 2 that joins tap `i2` of a launch with cell j of a position's; negative: none.
-template <class ArgsPtr>
-__device__ inline int tap2_of(ArgsPtr a, int i2, int j) {
-  const auto& c = a->c;
-  if (a->fold == 1) return c.tapid[2][i2];
-  const int at = c.mode == 0 ? a->off2[i2] - j * c.s[2] : j - a->off2[i2] * c.s[2];
-  return at < 0 || at % a->dil2 != 0 || at / a->dil2 >= a->k2 ? -1 : at / a->dil2;
-}
-
-// eight channels of a weight piece: k0 ... of column col, tap `tap` (in group order) of kernel plane t0
-template <class ArgsPtr>
-__device__ inline void weight_octet(ArgsPtr a, const float* __restrict__ w, int t0, int k0, int tap, int col, float (&v)[8]) {
-  const auto& c = a->c;
-  const FastDiv div_nch{a->div_nch.mul, a->div_nch.sh1, a->div_nch.sh2, a->div_nch.d};
-  const int j = a->fold > 1 ? (int)fd_div((uint32_t)col, div_nch) : 0, ch = col - j * a->nch, t2 = tap2_of(a, a->tap12[tap][1], j);
-  const int ft = (c.tapid[0][t0] * a->k1 + c.tapid[1][a->tap12[tap][0]]) * a->k2 + t2;
-  const int left = col < c.nc && t2 >= 0 ? c.kc - k0 : 0;
-  const size_t per_k = c.mode == 0 ? (size_t)a->taps : (size_t)a->ci * a->taps;
-  const float* const at = w + (left <= 0 ? (size_t)0 : c.mode == 0 ? ((size_t)ch * a->ci + k0) * a->taps + ft : ((size_t)k0 * a->ci + ch) * a->taps + ft);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = at[e < left ? e * per_k : (size_t)0];
-  // (loaded in any case and all at once: left alone the compiler makes a branch, and a wait, of each)
-#pragma unroll
-  for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(v[e]));
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = e < left ? v[e] : 0.f;
-}
 
 // MT: 32-position M-tiles per wave; PA: pairs of 16-byte pieces (8 channels of a cell) per thread and stage; PB: weight
 // pieces per thread and stage; FEW: for layers of few channels,
@@ -476,7 +428,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
 #pragma unroll 1
         for (int i = tid; i < nt * 64; i += 256) {  // [tap][h][nn]
           float v[8];
-          weight_octet(a, w, rp.t0, rp.cc * 16 + ((i >> 5) & 1) * 8, tb + (i >> 6), ntile * 32 + (i & 31), v);
+          split_weight_octet(a, w, rp.t0, rp.cc * 16 + ((i >> 5) & 1) * 8, tb + (i >> 6), ntile * 32 + (i & 31), v);
           u32x4 u, l;
           halve_eight(v, u, l);
           char* const at = wlds + (i >> 6) * 3072 + (i & 63) * 16;
@@ -563,41 +515,6 @@ __global__ __launch_bounds__(256, 2) void corr_split_classes_kernel(const Worker
                                                                     void* const* out_bufs, const SplitArgs* tab, int first,
                                                                     const u32x4* wt, const float* w, const float* bias) {
   corr_split<MT, PA, PB, FEW, TablePtr>(args_at(tab, first + (int)blockIdx.y), workers, in_bufs, out_bufs, wt, w, bias);
-}
-
-// Weights in the order the kernel stages them: pieces [ntile][t0][chunk][tap in group order][plane][h][nn], 8 channels
-// k = 16 chunk + 8 h ... each of column ntile * 32 + nn; a last chunk of at most 8 channels instead [pair of taps][plane][h]
-// [nn], those of the pair's tap h; zero beyond the channel counts and taps.  One thread per piece of all three planes.
-__global__ __launch_bounds__(256) void corr_split_weights_kernel(const SplitArgs* tab, int first, const float* __restrict__ w,
-                                                                 u32x4* __restrict__ dst) {
-  const TablePtr a = args_at(tab, first + (int)blockIdx.y);
-  const auto& c = a->c;
-  const int ntaps = a->gbegin[a->ngroups], whole = a->nfull * ntaps, per_t0 = whole + a->npairs;
-  const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
-  if (idx >= c.ntn * c.nt[0] * per_t0 * 64) return;
-  const int nn = idx & 31, h = (idx >> 5) & 1;
-  int r = idx >> 6;
-  const int at_t0 = r % per_t0; r /= per_t0;
-  const int t0 = r % c.nt[0], ntile = r / c.nt[0];
-  int cc = at_t0 / ntaps, k0 = cc * 16 + h * 8, tap = at_t0 - cc * ntaps;
-  bool there = true;
-  if (at_t0 >= whole) {
-    const int pair = at_t0 - whole;
-    int gr = 0;
-    while (a->hbegin[gr + 1] <= pair) ++gr;
-    tap = a->gbegin[gr] + 2 * (pair - a->hbegin[gr]) + h;
-    there = tap < a->gbegin[gr + 1];
-    if (!there) tap = 0;
-    k0 = a->nfull * 16;
-  }
-  float v[8];
-  weight_octet(a, w, t0, k0, tap, there ? ntile * 32 + nn : c.nc, v);
-  u32x4 hi, mid, lo;
-  split_eight(v, kSplitScale, hi, mid, lo);
-  u32x4* const at = dst + a->woff + (size_t)(idx >> 6) * 192 + (idx & 63);
-  at[0] = hi;
-  at[64] = mid;
-  at[128] = lo;
 }
 
 // ---- host side ------------------------------------------------------------------
@@ -843,33 +760,28 @@ int launch_variant(distdl_plan* p, const SplitArgs* tab, int first, const Launch
   return DISTDL_OK;
 }
 
-// One direction: the weights of all its launches in one go, then one launch per kernel variant.
+int table_of(SplitPlan& sp) {
+  if (sp.dev) return DISTDL_OK;
+  std::vector<SplitArgs> all;
+  for (const Launches& d : sp.dir)
+    for (const Launch& l : d.v) all.push_back(l.a);
+  SplitArgs* dev = nullptr;
+  DISTDL_HIP_TRY(hipMalloc((void**)&dev, all.size() * sizeof(SplitArgs)));
+  if (hipError_t e = hipMemcpy(dev, all.data(), all.size() * sizeof(SplitArgs), hipMemcpyHostToDevice); e != hipSuccess) {
+    (void)hipFree(dev);
+    DISTDL_HIP_TRY(e);
+  }
+  sp.dev = dev;
+  return DISTDL_OK;
+}
+
+// One direction, its weights laid out: one launch per kernel variant.
 int run_split(distdl_plan* p, int dir, const float* w, const float* bias, void** in_tab, void** out_tab, const char* name,
               hipStream_t st) {
   SplitPlan& sp = *(SplitPlan*)p->corr_split_plan.get();
-  if (!sp.dev) {
-    std::vector<SplitArgs> all;
-    for (const Launches& d : sp.dir)
-      for (const Launch& l : d.v) all.push_back(l.a);
-    SplitArgs* dev = nullptr;
-    DISTDL_HIP_TRY(hipMalloc((void**)&dev, all.size() * sizeof(SplitArgs)));
-    if (hipError_t e = hipMemcpy(dev, all.data(), all.size() * sizeof(SplitArgs), hipMemcpyHostToDevice); e != hipSuccess) {
-      (void)hipFree(dev);
-      DISTDL_HIP_TRY(e);
-    }
-    sp.dev = dev;
-  }
   const Launches& d = sp.dir[dir];
   const int first = dir == 0 ? 0 : (int)sp.dir[0].v.size();
-  if (int rc = ensure_wscratch(p, (size_t)std::max(sp.dir[0].pieces, sp.dir[1].pieces) * 4, st)) return rc;
-  u32x4* const wt = (u32x4*)p->d_wt;
-  int64_t most = 0;
-  for (const Launch& l : d.v) most = std::max(most, l.pieces / 3);  // threads: three pieces each
-  if (most > 0) {
-    ProfScope prof("conv_relayout_w", st);
-    hipLaunchKernelGGL(corr_split_weights_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)d.v.size()), dim3(256), 0, st,
-                       sp.dev, first, w, wt);
-  }
+  const u32x4* const wt = (const u32x4*)p->d_wt;
   constexpr int kPb = (kGroupTaps * 192 + 255) / 256, kPb3 = (9 * 192 + 255) / 256,
                 kPbFew = (kFewTaps * 192 + 255) / 256;
   for (size_t i = 0; i < d.v.size();) {
@@ -953,6 +865,23 @@ SplitPlan* split_plan(const distdl_plan* p) {
 }  // namespace
 
 bool corr_split_supported(const distdl_plan* p, bool backward) { return split_plan(p)->ok[backward ? 1 : 0]; }
+
+int split_weight_job(distdl_plan* p, bool backward, const float* w, hipStream_t st, WeightJob& job) {
+  SplitPlan& sp = *(SplitPlan*)p->corr_split_plan.get();
+  if (int rc = table_of(sp)) return rc;
+  if (int rc = ensure_wscratch(p, (size_t)std::max(sp.dir[0].pieces, sp.dir[1].pieces) * 4, st)) return rc;
+  const Launches& d = sp.dir[backward ? 1 : 0];
+  int64_t most = 0;
+  for (const Launch& l : d.v) most = std::max(most, l.pieces / 3);  // threads: three pieces each
+  job.kind = most > 0 ? 1 : 0;
+  job.per_class = (int32_t)((most + 255) / 256);
+  job.blocks = job.per_class * (int32_t)d.v.size();
+  job.tab = sp.dev;
+  job.first = backward ? (int32_t)sp.dir[0].v.size() : 0;
+  job.w = w;
+  job.dst = (split_u32x4*)p->d_wt;
+  return DISTDL_OK;
+}
 
 int conv_fwd_split(distdl_plan* p, const float* w, const float* bias, hipStream_t st) {
   return run_split(p, 0, w, bias, p->tab_x.dev, p->tab_y.dev, "conv_fwd_split", st);

@@ -12,6 +12,7 @@
 // atomics, so results are run-to-run identical.
 #include "common.h"
 #include "profile.h"
+#include "weight_job.h"
 
 namespace distdl {
 
@@ -129,11 +130,14 @@ __device__ inline size_t view_offset(const HaloView& v, const UnitPos& p) {
 
 // Forward: copy boxes (nsrc == 1) and zero boxes (nsrc == 0).  A thread
 // handles kUnroll units: all loads are issued before the first store.
-template <class E>
+template <class E, bool JOB>
 __global__ __launch_bounds__(kThreads) void halo_fwd_kernel(const BlockRef* __restrict__ blocks,
                                                             const HaloTaskDev* __restrict__ tasks,
-                                                            void* const* __restrict__ bufs) {
+                                                            void* const* __restrict__ bufs, JobArg<JOB> job) {
   using S = typename E::Store;
+  if constexpr (JOB) {
+    if ((int)blockIdx.x >= job.at) return run_weight_job(job, (int)blockIdx.x - job.at);
+  }
   const BlockRef br = blocks[blockIdx.x];
   const HaloTaskDev t = tasks[br.task];  // by value: the record is read once into scalar registers
   const uint32_t total = t.total;
@@ -228,15 +232,30 @@ __global__ __launch_bounds__(kThreads) void halo_adj_kernel(const BlockRef* __re
 
 int plan_prepare_device(distdl_plan* p);
 
+__global__ __launch_bounds__(kThreads) void weight_job_kernel(WeightJob job) { run_weight_job(job, (int)blockIdx.x); }
+
+int launch_weight_job(const WeightJob& job, hipStream_t st) {
+  if (job.kind == 0) return DISTDL_OK;
+  ProfScope prof("conv_relayout_w", st);
+  hipLaunchKernelGGL(weight_job_kernel, dim3((unsigned)job.blocks), dim3(kThreads), 0, st, job);
+  DISTDL_HIP_TRY(hipGetLastError());
+  return DISTDL_OK;
+}
+
 template <class E>
-static void launch(bool adjoint, const TaskTable& tt, const distdl_plan* p, void* const* bufs, hipStream_t st) {
+static void launch(bool adjoint, const TaskTable& tt, void* const* bufs, WeightJob* job, hipStream_t st) {
   dim3 grid((unsigned)tt.blocks.size()), block(kThreads);
-  (void)p;
   ProfScope prof(adjoint ? "halo_adj" : "halo_fwd", st);
-  if (adjoint)
+  if (adjoint) {
     hipLaunchKernelGGL(halo_adj_kernel<E>, grid, block, 0, st, tt.d_blocks, tt.d_tasks, tt.d_views, bufs);
-  else
-    hipLaunchKernelGGL(halo_fwd_kernel<E>, grid, block, 0, st, tt.d_blocks, tt.d_tasks, bufs);
+  } else if (job && job->kind != 0 && (int64_t)grid.x + job->blocks < kMaxBlocks256) {
+    job->at = (int32_t)grid.x;
+    grid.x += (unsigned)job->blocks;
+    hipLaunchKernelGGL((halo_fwd_kernel<E, true>), grid, block, 0, st, tt.d_blocks, tt.d_tasks, bufs, *job);
+    job->kind = 0;
+  } else {
+    hipLaunchKernelGGL((halo_fwd_kernel<E, false>), grid, block, 0, st, tt.d_blocks, tt.d_tasks, bufs, NoJob{});
+  }
 }
 
 // Copy boxes between arbitrary buffers with the forward kernel (used by the generalized repartition): the
@@ -246,9 +265,9 @@ int run_box_copy(int unit_bytes, const BlockRef* d_blocks, const HaloTaskDev* d_
   if (nblocks == 0) return DISTDL_OK;
   dim3 grid((unsigned)nblocks), block(kThreads);
   ProfScope prof(name, st);
-  if (unit_bytes == 16) hipLaunchKernelGGL(halo_fwd_kernel<F32x4>, grid, block, 0, st, d_blocks, d_tasks, d_bufs);
-  else if (unit_bytes == 4) hipLaunchKernelGGL(halo_fwd_kernel<F32x1>, grid, block, 0, st, d_blocks, d_tasks, d_bufs);
-  else if (unit_bytes == 2) hipLaunchKernelGGL(halo_fwd_kernel<BF16x1>, grid, block, 0, st, d_blocks, d_tasks, d_bufs);
+  if (unit_bytes == 16) hipLaunchKernelGGL((halo_fwd_kernel<F32x4, false>), grid, block, 0, st, d_blocks, d_tasks, d_bufs, NoJob{});
+  else if (unit_bytes == 4) hipLaunchKernelGGL((halo_fwd_kernel<F32x1, false>), grid, block, 0, st, d_blocks, d_tasks, d_bufs, NoJob{});
+  else if (unit_bytes == 2) hipLaunchKernelGGL((halo_fwd_kernel<BF16x1, false>), grid, block, 0, st, d_blocks, d_tasks, d_bufs, NoJob{});
   else return set_error(DISTDL_ERR_INVALID_ARG, "internal: box copy unit of %d bytes", unit_bytes);
   DISTDL_HIP_TRY(hipGetLastError());
   return DISTDL_OK;
@@ -256,6 +275,9 @@ int run_box_copy(int unit_bytes, const BlockRef* d_blocks, const HaloTaskDev* d_
 
 // Shared by the public halo calls and by conv_fwd / conv_bwd.
 int run_halo(distdl_plan* p, bool adjoint, PtrTable& tab, void* const* bufs_host, hipStream_t st) {
+  return run_halo_with(p, adjoint, tab, bufs_host, nullptr, st);
+}
+int run_halo_with(distdl_plan* p, bool adjoint, PtrTable& tab, void* const* bufs_host, WeightJob* job, hipStream_t st) {
   int rc = plan_prepare_device(p);
   if (rc) return rc;
   const size_t esz = dtype_size(p->dtype);
@@ -270,11 +292,11 @@ int run_halo(distdl_plan* p, bool adjoint, PtrTable& tab, void* const* bufs_host
   if (tt.blocks.empty()) return DISTDL_OK;  // a single worker with no padding: H is the identity
   if ((rc = tab.upload((const void* const*)bufs_host, p->n_workers, st))) return rc;
   if (p->dtype == DISTDL_F32) {
-    if (wide) launch<F32x4>(adjoint, tt, p, tab.dev, st);
-    else launch<F32x1>(adjoint, tt, p, tab.dev, st);
+    if (wide) launch<F32x4>(adjoint, tt, tab.dev, job, st);
+    else launch<F32x1>(adjoint, tt, tab.dev, job, st);
   } else {
-    if (wide) launch<BF16x8>(adjoint, tt, p, tab.dev, st);
-    else launch<BF16x1>(adjoint, tt, p, tab.dev, st);
+    if (wide) launch<BF16x8>(adjoint, tt, tab.dev, job, st);
+    else launch<BF16x1>(adjoint, tt, tab.dev, job, st);
   }
   DISTDL_HIP_TRY(hipGetLastError());
   return DISTDL_OK;

@@ -62,6 +62,29 @@ def test_conv_kernel_against_fp64(case):
     assert float((L.db.double() - db).norm() / db.norm()) < TOL[dtype]
 
 
+@pytest.mark.parametrize("c_in,c_out", [(20, 24), (19, 21), (28, 3)], ids=["split", "gather", "both"])
+@pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("pad", [0, 1], ids=["no_halo", "halo"])
+def test_weights_ride_in_the_launch_before(pad, dtype, c_in, c_out):
+    """The weights are laid out by the halo exchange's launch (none without padding: by one of their own) and by the reduction
+    of dw; other weights in the next call are used there."""
+    require_gpu()
+    L = ConvLayer(2, c_in, c_out, (40, 41), 3, 1, dtype, pad)
+    if dtype == BF16 and 4 not in dd.distdl_debug_conv_kernels(L.plan):
+        pytest.skip("the bf16 tiles lay out their weights themselves")
+    for _ in range(3):
+        L.w.copy_(torch.randn_like(L.w))
+        dd.distdl_profile_enable(True)
+        dd.distdl_profile_report()
+        outs = L.run()
+        names = set(dd.distdl_profile_report())
+        dd.distdl_profile_enable(False)
+        if dtype == F32:
+            assert ("conv_relayout_w" in names) == (pad == 0)
+        for name, got, want in zip(("y", "dx", "dw"), outs, L.exact()):
+            assert float((got.double() - want).norm() / want.norm()) < TOL[dtype], name
+
+
 @pytest.mark.parametrize("P_fo,P_fi", [(1, 9), (9, 1), (9, 10)])
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
 def test_affine_of_more_segments_than_a_product_takes(P_fo, P_fi, dtype):
