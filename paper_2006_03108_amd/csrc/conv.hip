@@ -243,25 +243,38 @@ static int check_conv_plan(const distdl_plan* p) {
 // take any weights' alignment, the tiled ones do not.
 enum class Corr { kDirect, kMfma, k16, kSplit, kAny };
 
-static Corr choose_fwd(const distdl_plan* p, bool xy_aligned, bool w_aligned) {
-  if (corr16_fwd_supported(p, xy_aligned)) return Corr::k16;  // few channels: 16 x 16 tiles
-  if (xy_aligned && corr_split_supported(p, false)) return Corr::kSplit;
-  if (xy_aligned && w_aligned && corr_mfma_supported(p)) return Corr::kMfma;
-  return conv_any_supported(p) ? Corr::kAny : Corr::kDirect;
+//
+// Among the three that make fp32 products of small layers, the one whose estimated time is the lowest, with an allowance for
+// what the estimates do not know (each is off by up to a quarter): the 16 x 16 kernel stays unless another one takes less than
+// three quarters of its time, the split one (where it takes the layer) unless the gather kernel takes less than two thirds,
+// or half if the split kernel's windows are full.  What decides: the split kernel's windows
+// lie in one plane of one sample, so planes of a few cells leave them empty, where the gather kernel counts all positions
+// through; the gather kernel fetches a cell for each tap; the 16 x 16 kernel has a launch for each class of a stride.  us,
+// 16 x 16 / split / gather: forward 36 -> 24, 3^3, 6 x 13 x 13 x 11: - / 41 / 21; 8 -> 4, 7^3, stride 2, 13 x 11 x 16 x 15: 214 / 302 /
+// 53; 16 -> 4, 3 x 3, 2 x 808 x 1000: 91 / 67 / 181; data gradient 12 -> 1, 3 x 3, stride 2, 15 x 727 x 494: 148 / 77 / -.
+static Corr choose_small(const distdl_plan* p, bool backward, bool aligned, bool k16, bool split) {
+  Corr best = k16 ? Corr::k16 : Corr::kSplit;
+  double us = k16 ? corr16_us(p, backward) * 0.75 : corr_split_us(p, backward);
+  if (k16 && split)
+    if (const double t = corr_split_us(p, backward); t < us) us = t, best = Corr::kSplit;
+  if (conv_any_supported(p) && corr_any_us(p, backward, aligned) < us * (best == Corr::k16 ? 1.0 : corr_split_used(p, backward) < 0.5 ? 0.66 : 0.5))
+    best = Corr::kAny;
+  return best;
 }
 
-static Corr choose_data(const distdl_plan* p, bool aligned) {
-  auto split = [&]() { return aligned && corr_split_supported(p, true); };
-  // Few channels and several stride classes: the 16 x 16 kernel takes a launch (with planes of taps, two) for each, the others
-  // two in all, which is what counts up to 2^18 cells for four classes (us; 4 -> 16 channels, 3 x 3, stride 2, 12 x 28 x 29:
-  // 41 and 16; 2 -> 6, 2 x 772 x 887: 74 and 118).
-  const int64_t classes = (int64_t)p->stride[0] * p->stride[1] * p->stride[2];
-  const bool together = classes >= 4 && p->n_workers * p->n_b * p->max_buf_cells <= (classes << 16) && (split() || conv_any_supported(p));
-  if (!together && corr16_bwd_supported(p, aligned)) return Corr::k16;
-  if (split()) return Corr::kSplit;
-  if (aligned && corr_mfma_supported(p)) return Corr::kMfma;
-  return conv_any_supported(p) ? Corr::kAny : Corr::kDirect;
+static Corr choose_corr(const distdl_plan* p, bool backward, bool aligned, bool w_aligned) {
+  int8_t& known = p->corr_kernel[backward][aligned][w_aligned];
+  if (known >= 0) return (Corr)known;
+  const bool k16 = backward ? corr16_bwd_supported(p, aligned) : corr16_fwd_supported(p, aligned);
+  const bool split = aligned && corr_split_supported(p, backward);
+  Corr c = conv_any_supported(p) ? Corr::kAny : Corr::kDirect;
+  if (k16 || split) c = choose_small(p, backward, aligned, k16, split);
+  else if (aligned && w_aligned && corr_mfma_supported(p)) c = Corr::kMfma;
+  known = (int8_t)c;
+  return c;
 }
+static Corr choose_fwd(const distdl_plan* p, bool xy_aligned, bool w_aligned) { return choose_corr(p, false, xy_aligned, w_aligned); }
+static Corr choose_data(const distdl_plan* p, bool aligned) { return choose_corr(p, true, aligned, true); }
 
 // The kernel of the weight gradient: of those that take the layer, the one whose estimated time (us) is the lowest:
 //   16 x 16 tiles: a set-up that grows with the taps of a plane, then 7 ps per tap and position (12 with several planes);

@@ -645,9 +645,10 @@ AnyArgs any_args(const distdl_plan* p, int mode, int NT) {
 bool flat_k(const AnyArgs& a, bool vec) { return a.mode == 0 || vec; }
 
 // octets of weights of every class; returns their sum
-int64_t class_octets(const AnyArgs& a, bool flat, int32_t* first, int& most) {
+int64_t class_octets(const AnyArgs& a, bool flat, int32_t* first, int& most, int* k_most = nullptr) {
   int64_t sum = 0;
   most = 0;
+  if (k_most) *k_most = 0;
   for (int cls = 0; cls < a.ncls; ++cls) {
     int ntaps = 1;
     const int par[3] = {cls / (a.s[1] * a.s[2]), cls / a.s[2] % a.s[1], cls % a.s[2]};
@@ -661,6 +662,7 @@ int64_t class_octets(const AnyArgs& a, bool flat, int32_t* first, int& most) {
     if (first) first[cls] = (int32_t)sum;
     sum += octs;
     most = std::max(most, octs);
+    if (k_most) *k_most = std::max(*k_most, K);
   }
   return sum;
 }
@@ -703,11 +705,11 @@ int pick_corr_any(distdl_plan* p, const AnyArgs& a, bool vec, void** in_tab, voi
              : launch_corr_any<ROWS, NT, BF16, 1, false>(p, a, in_tab, out_tab, name, st);
 }
 
-// The launch of a direction: its arguments, rows of a tile, columns / 32; most: octets of weights of its largest class
+// The launch of a direction: its arguments, rows of a tile, columns / 32; of its largest class: octets of weights, k
 struct AnyLaunch {
   AnyArgs a;
   bool vec, few;
-  int NT, most;
+  int NT, most, k;
 };
 AnyLaunch any_launch(const distdl_plan* p, int mode, bool aligned) {
   AnyLaunch l;
@@ -715,7 +717,7 @@ AnyLaunch any_launch(const distdl_plan* p, int mode, bool aligned) {
   l.a = any_args(p, mode, l.NT);
   AnyArgs& a = l.a;
   l.vec = aligned && a.kc % 4 == 0;
-  class_octets(a, flat_k(a, l.vec), a.woff, l.most);
+  class_octets(a, flat_k(a, l.vec), a.woff, l.most, &l.k);
   // 64 rows where 256 would leave compute units idle and there is enough k for four waves (32 columns: with 64 their
   // accumulators and the larger stages of weights do not fit the registers)
   const int64_t pos = positions_max(p, a);
@@ -763,6 +765,18 @@ bool conv_any_supported(const distdl_plan* p) {
     if ((double)(positions_max(p, a) / 256 + 1) * a.ntn * p->n_workers + 8 >= kMaxBlocks256) return false;
   }
   return p->n_workers <= 65535;
+}
+
+// Estimated time of a launch: rounds of 512 workgroups, each a number of stages (32 k, or with 64 rows 128 k, which are shorter
+// while a workgroup is alone on its compute unit) and an epilogue.  Fitted to 186 directions of 93 layers, 1 to 64 channels,
+// 100 to 4 M positions; nine tenths of them are within a quarter of it.
+double corr_any_us(const distdl_plan* p, bool backward, bool aligned) {
+  const AnyLaunch l = any_launch(p, backward ? 1 : 0, aligned);
+  const double tiles = (double)l.a.tiles_max * p->n_workers * l.a.ncls, stages = std::max(1, (l.k + (l.few ? 127 : 31)) / (l.few ? 128 : 32));
+  const double alone = tiles <= 256 ? 0.57 : 1.0, rounds = std::max(1.0, tiles / 512);
+  if (l.few) return l.vec ? 1.4 + rounds * (stages * 3.1 * alone + 5.6) : 4.9 + rounds * stages * 3.7 * alone;
+  if (!l.vec) return 3.4 + rounds * (stages * 4.6 * alone + 2.2) * l.NT;
+  return l.NT == 1 ? 2.6 + rounds * (stages * 2.3 * alone + 5.2) : 1.0 + rounds * (stages * 3.4 * alone + 7.5);
 }
 
 int any_weight_job(distdl_plan* p, bool backward, const void* w, bool aligned, hipStream_t st, WeightJob& job) {

@@ -95,6 +95,7 @@ bool corr16_fwd_supported(const distdl_plan* p, bool vec);
 bool corr16_bwd_supported(const distdl_plan* p, bool vec);
 int conv_fwd16(distdl_plan* p, const float* w, const float* bias, bool vec, hipStream_t st);
 int conv_bwd_data16(distdl_plan* p, const float* w, bool vec, hipStream_t st);
+double corr16_us(const distdl_plan* p, bool backward);  // estimated time of all launches of a direction
 bool wgrad16_supported(const distdl_plan* p, bool vec);
 int wgrad16_chunks(const distdl_plan* p, bool vec);
 int conv_wgrad16(distdl_plan* p, float* partial, bool vec, hipStream_t st);

@@ -15,6 +15,7 @@
 // the 64 lanes of an operand read are 64 consecutive floats.  Zero dy entries cancel the padded positions.
 #include <algorithm>
 #include <array>
+#include <cmath>
 #include <memory>
 #include <vector>
 
@@ -915,6 +916,18 @@ bool corr16_bwd_supported(const distdl_plan* p, bool vec) {
         if (!corr16_shape_of(p, 1 + (p0 * p->stride[1] + p1) * p->stride[2] + p2, c, vec && p->n_co % 4 == 0, s)) return false;
       }
   return true;
+}
+
+// A launch per class of the data gradient, and for kernels of several planes another for its weights; matrix instructions,
+// tensors, and the stages of a kernel of three dimensions.  Fitted to 83 directions; half of them are within a seventh of it.
+double corr16_us(const distdl_plan* p, bool backward) {
+  const double launches = backward ? (double)p->stride[0] * p->stride[1] * p->stride[2] : 1.0;
+  const double taps = (double)p->ksize[0] * p->ksize[1] * p->ksize[2];
+  const int64_t kc = backward ? p->n_co : p->n_ci;
+  const int quads = kc <= 4 ? 1 : kc <= 8 ? 2 : 4;
+  const double pos = (double)p->n_workers * p->n_b * (backward ? p->max_buf_cells : p->max_out_cells);
+  const double mfma = 1.26e-6 * pos * (taps / launches) * quads, mem = 9.0e-6 * pos * std::max<int64_t>(p->n_ci + p->n_co, 8) / 8;
+  return launches * (p->ksize[0] > 1 ? 11.0 : 7.5) + mfma + mem + (p->ksize[0] > 1 ? 2.4 * std::cbrt(taps) : 0.0);
 }
 
 static size_t corr16_scratch_total(const distdl_plan* p) {

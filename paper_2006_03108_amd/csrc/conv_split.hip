@@ -594,7 +594,7 @@ bool few_channels(const SplitArgs& a) { return a.fold > 1 || a.npairs > 0; }
 
 // The window of a launch: M-tiles per wave (0: none fits).  The window that wastes the fewest multiplied positions; of
 // equal ones the one with the smallest patch per position.
-int choose_window(const distdl_plan* p, SplitArgs& a) {
+int choose_window(const distdl_plan* p, SplitArgs& a, double& used) {
   int nq1 = 1, nq2 = 1;
   for (const WorkerDev& wd : p->workers) {
     const PerWorker g = derive_of(wd, &a);
@@ -602,6 +602,7 @@ int choose_window(const distdl_plan* p, SplitArgs& a) {
     nq2 = std::max(nq2, g.nq[2]);
   }
   double best = -1;
+  used = 0;
   int best_mt = 0, best_tc = 0;
   for (int mt : {3, 2, 1})
     for (int tc = 1; tc <= std::min(128 * mt, nq2); ++tc) {
@@ -615,7 +616,7 @@ int choose_window(const distdl_plan* p, SplitArgs& a) {
       // a tap costs a wave 6 mt MFMAs and 3 mt + 3 operand reads: fewer M-tiles pay relatively more for the weights
       const double share = window_share(128 * mt, tc, nq1, nq2), patch = (double)(a.c.R * a.c.Cw) / (128 * mt);
       const double score = share * (mt == 1 ? 0.75 : 1.0) / (1.0 + 0.05 * patch);
-      if (score > best * 1.001) best = score, best_mt = mt, best_tc = tc;
+      if (score > best * 1.001) best = score, best_mt = mt, best_tc = tc, used = share;
     }
   if (best_mt) set_window(a, best_mt, best_tc);
   return best_mt;
@@ -674,10 +675,13 @@ struct Launch {
   unsigned blocks = 0;
   int64_t pieces = 0;  // of weights
   double clocks = 0, share = 1;  // estimates: time alone; part of the chip that it fills
+  double used = 1;               // part of the multiplied positions that are outputs
 };
 struct Launches {
   std::vector<Launch> v;
   int64_t pieces = 0;  // all of them
+  double clocks = 0;   // estimate
+  double used = 1;     // of the launch that uses its windows least
 };
 struct SplitPlan {
   Launches dir[2];
@@ -693,7 +697,7 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, 
   l.a = split_args(p, c, fold, octet, ok);
   SplitArgs& a = l.a;
   if (!ok) return false;
-  const int mt = choose_window(p, a);
+  const int mt = choose_window(p, a, l.used);
   if (mt == 0) return false;
   l.variant = (mt == 3 ? 3 : mt == 1 ? 0 : pieces_of(a) <= 3 ? 1 : 2) + (few_channels(a) ? 4 : 0);
   l.pieces = weight_pieces(a);
@@ -838,6 +842,7 @@ SplitPlan* split_plan(const distdl_plan* p) {
         l.v.emplace_back();
         ok = ok && plan_launch(p, c, fold, octet, l.v.back());
         sum += l.v.back().clocks * l.v.back().share;
+        l.used = std::min(l.used, l.v.back().used);
         most = std::max(most, l.v.back().clocks);
       };
       if (dir == 0) add(forward_args(p));
@@ -848,7 +853,7 @@ SplitPlan* split_plan(const distdl_plan* p) {
               const int par[3] = {p0, p1, p2};
               add(class_args(p, par));
             }
-      if (const double clocks = std::max(sum, most); ok && clocks < 0.97 * least) least = clocks, d = l;
+      if (const double clocks = std::max(sum, most); ok && clocks < 0.97 * least) least = l.clocks = clocks, d = l;
       }
     }
     if (d.v.empty()) continue;
@@ -865,6 +870,14 @@ SplitPlan* split_plan(const distdl_plan* p) {
 }  // namespace
 
 bool corr_split_supported(const distdl_plan* p, bool backward) { return split_plan(p)->ok[backward ? 1 : 0]; }
+
+// Estimated time: that of the clocks that chose the launches (fitted to 144 directions, nine tenths within a fifth where the
+// tensors are small), and the tensors.
+double corr_split_used(const distdl_plan* p, bool backward) { return split_plan(p)->dir[backward ? 1 : 0].used; }
+double corr_split_us(const distdl_plan* p, bool backward) {
+  const double cells = (double)p->n_workers * p->n_b * (backward ? p->max_buf_cells : p->max_out_cells);
+  return 2.7 + split_plan(p)->dir[backward ? 1 : 0].clocks / 2240 + cells * (double)(p->n_ci + p->n_co) * 0.65e-6;
+}
 
 int split_weight_job(distdl_plan* p, bool backward, const float* w, hipStream_t st, WeightJob& job) {
   SplitPlan& sp = *(SplitPlan*)p->corr_split_plan.get();

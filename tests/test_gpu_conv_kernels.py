@@ -62,6 +62,25 @@ def test_conv_kernel_against_fp64(case):
     assert float((L.db.double() - db).norm() / db.norm()) < TOL[dtype]
 
 
+# where the choice among the fp32 kernels lies: planes of a few cells (gather), a class of a stride each (split), full windows
+CHOICE = [((4, 4), 60, 36, 24, (5, 4, 3), (3, 3, 3), (1, 1, 1)), ((4, 3), 1, 8, 64, (5, 6, 9), (3, 3, 3), (2, 2, 2)),
+          ((2, 3), 8, 2, 12, (180, 120), (3, 3), (2, 2)), ((3, 3), 2, 36, 40, (90, 91), (3, 3), (1, 1))]
+
+
+@pytest.mark.parametrize("case", CHOICE, ids=[f"{c[2]}-{c[3]}" for c in CHOICE])
+def test_choice_among_fp32_kernels(case):
+    """Sums of at most 972 products, each within the bar of the other parity tests; and the same for tensors that are not
+    aligned, which the split kernels do not take."""
+    require_gpu()
+    want_kernels, n_b, c_in, c_out, shape, k, s = case
+    for offset in (0, 1):
+        L = ConvLayer(n_b, c_in, c_out, shape, k, s, offset=offset)
+        got_kernels = dd.distdl_debug_conv_kernels(L.plan, aligned=offset == 0)[:2]
+        assert got_kernels == want_kernels if offset == 0 else 3 not in got_kernels
+        for name, got, want in zip(("y", "dx"), L.run(), L.exact()):
+            assert float((got.double() - want).norm() / want.norm()) < TOL[F32], name
+
+
 @pytest.mark.parametrize("c_in,c_out", [(20, 24), (19, 21), (28, 3)], ids=["split", "gather", "both"])
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("pad", [0, 1], ids=["no_halo", "halo"])
