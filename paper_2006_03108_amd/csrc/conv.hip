@@ -262,6 +262,7 @@ static Corr choose_small(const distdl_plan* p, bool backward, bool aligned, bool
   return best;
 }
 
+static bool wgrad_on_tiles(const distdl_plan* p);
 static Corr choose_corr(const distdl_plan* p, bool backward, bool aligned, bool w_aligned) {
   int8_t& known = p->corr_kernel[backward][aligned][w_aligned];
   if (known >= 0) return (Corr)known;
@@ -269,7 +270,20 @@ static Corr choose_corr(const distdl_plan* p, bool backward, bool aligned, bool 
   const bool split = aligned && corr_split_supported(p, backward);
   Corr c = conv_any_supported(p) ? Corr::kAny : Corr::kDirect;
   if (k16 || split) c = choose_small(p, backward, aligned, k16, split);
-  else if (aligned && w_aligned && corr_mfma_supported(p)) c = Corr::kMfma;
+  else if (aligned && w_aligned && corr_mfma_supported(p)) {
+    // bf16: 32-wide tiles or the gather kernel, by estimated time.  The tiles stage a cell once for all taps; they have a launch,
+    // and another for the weights, for each class, windows in one plane of one sample, and channel counts that are no multiples
+    // of 8 on fp32 MFMAs.  us, tiles (with their weights' launches) / gather: forward 32 -> 16, 3^3, stride 2, 2 x 101 x 95 x 100:
+    // 66 / 79, data gradient 156 / 94; forward 44 -> 36, 3^3, 9 x 4 x 4 x 4: 179 / 17; data gradient 56 -> 8, 5 x 5, stride 2, 10 x 44 x 75:
+    // 51 / 13; forward 12 -> 44, 3 x 3, 6 x 602 x 675: 430 / 163.  (Without estimates, tiles wherever they fit, a direction took 2.1
+    // times the faster of the two in the mean of 166, with them 1.1.)
+    // Layers whose weight gradient is on the tiles keep all three directions there: nearly all of them are large and faster that way
+    // (32 -> 32, 5^3, stride 2, 256^3: forward 691 / 3900, data gradient 1090 / 2440; 24 -> 8, 3^3, 3 x 42 x 36 x 38: forward 23 / 42); the
+    // data gradient of the few that are small and strided would not be.
+    const bool gather = p->dtype == DISTDL_BF16 && conv_any_supported(p) && !wgrad_on_tiles(p) &&
+                        corr_any_us(p, backward, aligned) < 0.8 * corr_mfma_us(p, backward);
+    c = gather ? Corr::kAny : Corr::kMfma;
+  }
   known = (int8_t)c;
   return c;
 }
@@ -308,6 +322,8 @@ static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {
   p->wgrad_kernel[vec16] = (int)best;
   return best;
 }
+
+static bool wgrad_on_tiles(const distdl_plan* p) { return choose_wgrad(p, true) == Wgrad::kMfma; }
 
 static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per worker
   switch (w) {

@@ -11,7 +11,7 @@ bool conv_any_supported(const distdl_plan* p);
 int any_weight_job(distdl_plan* p, bool backward, const void* w, bool aligned, hipStream_t st, WeightJob& job);
 int conv_fwd_any(distdl_plan* p, const void* w, const void* bias, bool aligned, hipStream_t st);
 int conv_bwd_data_any(distdl_plan* p, const void* w, bool aligned, hipStream_t st);
-double corr_any_us(const distdl_plan* p, bool backward, bool aligned);  // estimated time (fp32)
+double corr_any_us(const distdl_plan* p, bool backward, bool aligned);  // estimated time
 int wgrad_any_chunks(const distdl_plan* p);
 double wgrad_any_us(const distdl_plan* p);  // estimated time
 int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st);

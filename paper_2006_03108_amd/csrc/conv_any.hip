@@ -769,11 +769,17 @@ bool conv_any_supported(const distdl_plan* p) {
 
 // Estimated time of a launch: rounds of 512 workgroups, each a number of stages (32 k, or with 64 rows 128 k, which are shorter
 // while a workgroup is alone on its compute unit) and an epilogue.  Fitted to 186 directions of 93 layers, 1 to 64 channels,
-// 100 to 4 M positions; nine tenths of them are within a quarter of it.
+// 100 to 4 M positions, and 222 of 111 bf16 layers; nine tenths of them are within a quarter of it.
 double corr_any_us(const distdl_plan* p, bool backward, bool aligned) {
   const AnyLaunch l = any_launch(p, backward ? 1 : 0, aligned);
   const double tiles = (double)l.a.tiles_max * p->n_workers * l.a.ncls, stages = std::max(1, (l.k + (l.few ? 127 : 31)) / (l.few ? 128 : 32));
   const double alone = tiles <= 256 ? 0.57 : 1.0, rounds = std::max(1.0, tiles / 512);
+  if (p->dtype == DISTDL_BF16) {
+    const double short_ = tiles <= 256 ? 0.5 : 1.0;
+    if (l.few) return l.vec ? 4.5 + rounds * (stages * 1.43 * (tiles <= 256 ? 0.8 : 1.0) + 0.9) : 3.2 + rounds * stages * 2.1;
+    if (!l.vec) return 4.0 + rounds * (stages * 1.95 * short_ + 2.2) * (l.NT == 1 ? 1.0 : 1.3);
+    return l.NT == 1 ? 4.7 + rounds * (stages * short_ + 2.7) : 4.5 + rounds * (stages * 1.28 * short_ + 4.8);
+  }
   if (l.few) return l.vec ? 1.4 + rounds * (stages * 3.1 * alone + 5.6) : 4.9 + rounds * stages * 3.7 * alone;
   if (!l.vec) return 3.4 + rounds * (stages * 4.6 * alone + 2.2) * l.NT;
   return l.NT == 1 ? 2.6 + rounds * (stages * 2.3 * alone + 5.2) : 1.0 + rounds * (stages * 3.4 * alone + 7.5);

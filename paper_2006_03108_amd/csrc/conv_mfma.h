@@ -80,6 +80,7 @@ CorrArgs class_args(const distdl_plan* p, const int par[3]);
 int ensure_wscratch(distdl_plan* p, size_t elems, hipStream_t st);  // p->d_wt
 
 bool corr_mfma_supported(const distdl_plan* p);
+double corr_mfma_us(const distdl_plan* p, bool backward);  // estimated time of a bf16 layer's
 bool wgrad_mfma_supported(const distdl_plan* p);
 size_t bwd_scratch_elems(const distdl_plan* p);
 int wgrad_chunks(const distdl_plan* p);

@@ -1278,6 +1278,33 @@ static int64_t max_tiles(const distdl_plan* p, const CorrArgs& a) {
   return mx;
 }
 
+// bf16: a launch for each class and another for its weights; the positions that it multiplies, those that its windows leave
+// idle among them; the tensors.  Pieces of 8 channels; others are widened to fp32 and take fp32 MFMAs.  Fitted to 166 directions:
+// of those in pieces of 8 nine tenths of the ones whose time matters are within a quarter, of the others within a factor of two.
+double corr_mfma_us(const distdl_plan* p, bool backward) {
+  double us = 0;
+  auto add = [&](CorrArgs a) {
+    const int mt = corr_window(p, a);
+    int nq1, nq2, nq0 = 0;
+    max_nq(p, a, nq1, nq2);
+    for (const WorkerDev& wd : p->workers) nq0 = std::max(nq0, derive(wd, a).nq[0]);
+    const double windows = (double)((nq1 + a.tr - 1) / a.tr) * ((nq2 + a.tc - 1) / a.tc) * 128 * mt;
+    const double cells = (double)p->n_workers * p->n_b * nq0, steps = (double)a.nt[0] * a.nt[1] * a.nt[2] * ((a.kc + 15) / 16) * a.ntn;
+    const bool eights = a.kc % 8 == 0;
+    us += (eights ? 13.1 : 14.4) + (eights ? 1.13e-6 : 5.3e-6) * cells * windows * steps +
+          cells * nq1 * nq2 * (p->n_ci + p->n_co) * (eights ? 0.4e-6 : 0.9e-6);
+  };
+  if (!backward) add(forward_args(p));
+  else
+    for (int p0 = 0; p0 < p->stride[0]; ++p0)
+      for (int p1 = 0; p1 < p->stride[1]; ++p1)
+        for (int p2 = 0; p2 < p->stride[2]; ++p2) {
+          const int par[3] = {p0, p1, p2};
+          add(class_args(p, par));
+        }
+  return us;
+}
+
 static size_t corr_weight_elems(const CorrArgs& a) {
   const int ck = a.ck ? a.ck : 8;  // channels per chunk; sized for the smaller chunk until the launch has chosen
   return (size_t)a.ntn * a.nt[0] * ((a.kc + ck - 1) / ck) * a.nt[1] * a.nt[2] * 256;

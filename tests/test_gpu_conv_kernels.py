@@ -81,6 +81,22 @@ def test_choice_among_fp32_kernels(case):
             assert float((got.double() - want).norm() / want.norm()) < TOL[F32], name
 
 
+# the same for bf16: planes of a few cells, classes of a stride, channels that are no multiples of 8, large layers
+CHOICE_BF16 = [((4, 4), 9, 44, 36, (4, 4, 4), 3, 1), ((4, 4), 4, 4, 16, (150, 150), 5, 2), ((4, 4), 6, 12, 44, (60, 67), 3, 1),
+               ((1, 4), 2, 56, 4, (54, 57, 62), 3, 1), ((1, 1), 10, 32, 8, (120, 110), 3, 1)]
+
+
+@pytest.mark.parametrize("case", CHOICE_BF16, ids=[f"{c[2]}-{c[3]}" for c in CHOICE_BF16])
+def test_choice_among_bf16_kernels(case):
+    require_gpu()
+    want_kernels, n_b, c_in, c_out, shape, k, s = case
+    for offset in (0, 1):
+        L = ConvLayer(n_b, c_in, c_out, shape, k, s, BF16, offset=offset)
+        assert dd.distdl_debug_conv_kernels(L.plan, aligned=offset == 0)[:2] == (want_kernels if offset == 0 else (4, 4))
+        for name, got, want in zip(("y", "dx"), L.run(), L.exact()):
+            assert float((got.double() - want).norm() / want.norm()) < TOL[BF16], name
+
+
 @pytest.mark.parametrize("c_in,c_out", [(20, 24), (19, 21), (28, 3)], ids=["split", "gather", "both"])
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("pad", [0, 1], ids=["no_halo", "halo"])
