@@ -18,7 +18,10 @@
 //     k, the same for all lanes, goes into the scalar offset of the load.
 //   wgrad_any_kernel: rows are k, columns output channels, the sum runs over output positions; the offset that all
 //     lanes share is that of the position.  Every (worker, chunk of positions) writes a partial, which also holds the
-//     chunk's part of db^.
+//     chunk's part of db^.  256 rows and 32 positions per stage, or 64 rows and 128 positions (a layer of few channels and
+//     taps has less than 64 rows, and a thread fetches 32 values a stage either way), where the waves take 32 positions
+//     each and their partial tiles are added through LDS, in wave order.  us, 256 and 64 rows: 4 -> 16, 5 taps, 15 x 76551: 187 and 62; 9 -> 27,
+//     5 taps, 2 x 184717: 65 and 25; bf16 20 -> 4, 3 taps, 7 x 455875: 415 and 127.
 // Offsets that the lanes share are computed by the lanes, one each, and read out with v_readlane.
 // fp32: the hi * hi products have an accumulator of their own, see gemm_split.hip.
 #include <algorithm>
@@ -484,19 +487,19 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
 }
 
 // grid: (row tiles * column tiles, chunks, workers)
-template <int NT, bool BF16>
+template <int ROWS, int NT, bool BF16>
 __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __restrict__ workers, void* const* x_bufs,
                                                            void* const* dy_bufs, float* __restrict__ partial, WgradAnyArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr uint32_t ES = BF16 ? 2 : 4;
-  constexpr int kRows = 256, kKp = 4;
+  constexpr int KS = octets_of(ROWS), POS = 8 * KS;  // octets of positions, positions of a stage
   const int mt = (int)blockIdx.x % a.ntm, ntile = (int)blockIdx.x / a.ntm, chunk = (int)blockIdx.y, worker = (int)blockIdx.z;
   const WorkerDev wd = workers[worker];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ml = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t sx1 = (uint32_t)wd.buf[2] * a.ci, sx0 = (uint32_t)wd.buf[1] * sx1, sxn = (uint32_t)wd.buf[0] * sx0;
   const int npos = a.n_b * wd.out[0] * wd.out[1] * wd.out[2];
-  const int all = (npos + 8 * kKp - 1) / (8 * kKp);  // stages of the worker, dealt to the chunks
+  const int all = (npos + POS - 1) / POS;  // stages of the worker, dealt to the chunks
   const int s_begin = (int)((int64_t)all * chunk / a.nchunks), s_end = (int)((int64_t)all * (chunk + 1) / a.nchunks);
   const __amdgpu_buffer_rsrc_t rx = rsrc_of(x_bufs[worker], (uint32_t)a.n_b * sxn * ES);
   const __amdgpu_buffer_rsrc_t ry = rsrc_of(dy_bufs[worker], (uint32_t)npos * a.co * ES);
@@ -504,7 +507,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
   // this thread's row: tap and input channel
   uint32_t base = kOob;
   {
-    const int k = mt * kRows + tid;
+    const int k = mt * ROWS + tid % ROWS;
     if (k < a.rows) {
       const int tap = k / a.ci, c = k - tap * a.ci;
       const int t2 = tap % a.k[2], t01 = tap / a.k[2], t1 = t01 % a.k[1], t0 = t01 / a.k[1];
@@ -513,19 +516,19 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
     }
   }
   // and its column of dy, an octet of positions
-  constexpr int NB = 32 * NT, YO = (kKp * NB + 255) / 256;  // octets of dy per thread
+  constexpr int NB = 32 * NT, YO = (KS * NB + 255) / 256;  // octets of dy per thread
   char* const la = smem;
-  char* const lb = smem + kKp * a_pitch(kRows, BF16);
-  float v[kKp][8], y[YO][8];
+  char* const lb = smem + KS * a_pitch(ROWS, BF16);
+  float v[4][8], y[YO][8];
   uint32_t yoff[YO];
 #pragma unroll
   for (int i = 0; i < YO; ++i) {
     const int u = tid + i * 256, col = u % NB, o = u / NB, ch = ntile * NB + col;
-    yoff[i] = o < kKp && ch < a.co ? ((uint32_t)(o * 8) * a.co + ch) * ES : kOob;
+    yoff[i] = o < KS && ch < a.co ? ((uint32_t)(o * 8) * a.co + ch) * ES : kOob;
   }
   auto load_stage = [&](int st) {
-    // lane l works out where position 32 st + l lies
-    uint32_t t = (uint32_t)(st * 32 + (lane & 31));
+    // lane l works out where position l % 8 of this wave's octet l / 8 lies
+    uint32_t t = (uint32_t)(st * POS + ((ROWS == 256 ? 0 : wave) + (256 / ROWS) * ((lane & 31) >> 3)) * 8 + (lane & 7));
     uint32_t po = kOob;
     if ((int)t < npos) {
       const uint32_t o2 = t % (uint32_t)wd.out[2]; t /= (uint32_t)wd.out[2];
@@ -534,14 +537,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
       po = (n * sxn + o0 * a.s[0] * sx0 + o1 * a.s[1] * sx1 + o2 * a.s[2] * (uint32_t)a.ci) * ES;
     }
 #pragma unroll
-    for (int o = 0; o < kKp; ++o)
+    for (int o = 0; o < 4; ++o)
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[o][e] = load1<BF16>(rx, base, __builtin_amdgcn_readlane(po, 8 * o + e));
     // positions beyond the last lie beyond the resource and read as zero
 #pragma unroll
     for (int i = 0; i < YO; ++i)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[i][e] = load1<BF16>(ry, yoff[i], (uint32_t)(st * 32 + e) * a.co * ES);
+      for (int e = 0; e < 8; ++e) y[i][e] = load1<BF16>(ry, yoff[i], (uint32_t)(st * POS + e) * a.co * ES);
   };
   const bool bias_wg = mt == 0;  // these workgroups see every dy element of their columns and chunk once
   float bsum[YO];
@@ -550,17 +553,20 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
   auto write_stage = [&](auto raw) {
     constexpr bool RAW = decltype(raw)::value;
 #pragma unroll
-    for (int o = 0; o < kKp; ++o) put_octet<BF16, RAW>(la + o * a_pitch(kRows, BF16) + tid * 16, kRows * 16, v[o]);
+    for (int o = 0; o < 4; ++o)
+      put_octet<BF16, RAW>(la + (tid / ROWS + (256 / ROWS) * o) * a_pitch(ROWS, BF16) + tid % ROWS * 16, ROWS * 16, v[o]);
 #pragma unroll
     for (int i = 0; i < YO; ++i) {
       const int u = tid + i * 256;
-      if (u < kKp * NB) put_octet<BF16, RAW>(lb + (u / NB) * b_pitch(NT, BF16) + u % NB * 16, NB * 16, y[i]);
+      if (u < KS * NB) put_octet<BF16, RAW>(lb + (u / NB) * b_pitch(NT, BF16) + u % NB * 16, NB * 16, y[i]);
       if (bias_wg && !RAW)
         bsum[i] += ((y[i][0] + y[i][1]) + (y[i][2] + y[i][3])) + ((y[i][4] + y[i][5]) + (y[i][6] + y[i][7]));
     }
   };
   Sums<NT, BF16> sums;
-  int* const redo = (int*)(smem + any_lds(kRows, NT, BF16) - 16);  // set if a sum of the tile is not finite
+  const char* const wa = la + (ROWS == 256 ? wave * 64 * 16 : wave * 4 * a_pitch(ROWS, BF16));
+  const char* const wb = lb + (ROWS == 256 ? 0 : wave * 4 * b_pitch(NT, BF16));
+  int* const redo = (int*)(smem + any_lds(ROWS, NT, BF16) - 16);  // set if a sum of the tile is not finite
   if (!BF16 && tid == 0) *redo = 0;
   sums.zero();
   if (s_begin < s_end) load_stage(s_begin);
@@ -568,7 +574,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
     write_stage(std::false_type{});
     __syncthreads();
     if (st + 1 < s_end) load_stage(st + 1);
-    multiply_stage<kRows, NT, BF16>(sums.acc, sums.low, la + wave * 64 * 16, lb, lane);
+    multiply_stage<ROWS, NT, BF16>(sums.acc, sums.low, wa, wb, lane);
     if constexpr (!BF16) {
       if (st + 1 == s_end && !sums.finish()) *redo = 1;
     }
@@ -582,12 +588,30 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
         load_stage(st);
         write_stage(std::true_type{});
         __syncthreads();
-        multiply_stage_halves<kRows, NT>(sums.acc, la + wave * 64 * 16, lb, lane);
+        multiply_stage_halves<ROWS, NT>(sums.acc, wa, wb, lane);
         __syncthreads();
       }
     }
   }
   float* const slot = partial + ((size_t)worker * a.nchunks + chunk) * a.slot;
+  if constexpr (ROWS == 64) {
+    float* const red = (float*)smem;  // [wave][row][column]; the last barrier above came after the last read of a stage
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          red[(wave * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4)) * NB + 32 * j + ml] = sums.acc[i][j][e];
+    __syncthreads();
+    const int col = tid % NB, ch = ntile * NB + col;
+#pragma unroll
+    for (int t = 0; t < 64 * NB / 256; ++t) {
+      const int row = tid / NB + t * (256 / NB), k = mt * ROWS + row;
+      const float* p = red + row * NB + col;
+      if (k < a.rows && ch < a.co) slot[(size_t)k * a.co + ch] = ((p[0] + p[64 * NB]) + p[2 * 64 * NB]) + p[3 * 64 * NB];
+    }
+  } else
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const int ch = ntile * NB + 32 * j + ml;
@@ -595,7 +619,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int k = mt * kRows + wave * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4);
+        const int k = mt * ROWS + wave * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4);
         if (k < a.rows && ch < a.co) slot[(size_t)k * a.co + ch] = sums.acc[i][j][e];
       }
   }
@@ -604,12 +628,12 @@ __global__ __launch_bounds__(256, 2) void wgrad_any_kernel(const WorkerDev* __re
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < YO; ++i)
-      if (tid + i * 256 < kKp * NB) red[tid + i * 256] = bsum[i];
+      if (tid + i * 256 < KS * NB) red[tid + i * 256] = bsum[i];
     __syncthreads();
     if (tid < NB && ntile * NB + tid < a.co) {
       float sum = red[tid];
 #pragma unroll
-      for (int o = 1; o < kKp; ++o) sum += red[o * NB + tid];
+      for (int o = 1; o < KS; ++o) sum += red[o * NB + tid];
       slot[(size_t)a.rows * a.co + ntile * NB + tid] = sum;
     }
   }
@@ -808,23 +832,41 @@ int conv_bwd_data_any(distdl_plan* p, const void* w, bool aligned, hipStream_t s
   return run_corr_any(p, 1, w, nullptr, aligned, p->tab_dy.dev, p->tab_dx.dev, "conv_bwd_data_any", st);
 }
 
+namespace {
+// The tiles of a worker's weight gradient: rows, columns / 32.
+struct WgradTiles {
+  int rows, NT;
+  int64_t count, stages;  // of a worker
+};
+WgradTiles wgrad_tiles(const distdl_plan* p) {
+  const int64_t k = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci, pos = p->n_b * p->max_out_cells;
+  WgradTiles t;
+  // 64 rows where two tiles of them are enough for one of 256, and a worker has more than one stage of positions (us, 64 and 256
+  // rows: 49 rows 8 and 19, 120 rows 14 and 21, 147 rows, three tiles, 33 and 24)
+  t.rows = pos > 32 && (k + 63) / 64 <= 2 * ((k + 255) / 256) ? 64 : 256;
+  t.NT = t.rows == 64 ? 1 : nt_of(p->n_co);
+  t.count = (k + t.rows - 1) / t.rows * ((p->n_co + 32 * t.NT - 1) / (32 * t.NT));
+  const int per = 8 * octets_of(t.rows);
+  t.stages = (pos + per - 1) / per;
+  return t;
+}
+}  // namespace
+
 // position chunks per worker: about two workgroups per compute unit
 int wgrad_any_chunks(const distdl_plan* p) {
-  const int64_t rows = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci;
-  const int NT = nt_of(p->n_co);
-  const int64_t tiles = (rows + 255) / 256 * ((p->n_co + 32 * NT - 1) / (32 * NT)) * p->n_workers;
-  const int64_t stages = (p->n_b * p->max_out_cells + 31) / 32;
+  const WgradTiles t = wgrad_tiles(p);
+  const int64_t tiles = t.count * p->n_workers;
   // (a stage of a workgroup takes about 1.2 us, adding one more partial almost nothing: small layers one stage each)
-  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((512 + tiles - 1) / tiles, std::max<int64_t>(std::min<int64_t>(stages, 64), stages / 4)), 512));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((512 + tiles - 1) / tiles, std::max<int64_t>(std::min<int64_t>(t.stages, 64), t.stages / 4)), 512));
 }
 
+bool wgrad_any_few_rows(const distdl_plan* p) { return wgrad_tiles(p).rows == 64; }
+
 double wgrad_any_us(const distdl_plan* p) {
-  const int64_t rows = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci;
-  const int NT = nt_of(p->n_co);
-  const int64_t tiles = (rows + 255) / 256 * ((p->n_co + 32 * NT - 1) / (32 * NT)) * p->n_workers;
-  const int64_t chunks = wgrad_any_chunks(p), stages = (p->n_b * p->max_out_cells + 31) / 32;
-  const double stage = (tiles * chunks <= 256 ? 1.6 : 2.4) * NT * (p->dtype == DISTDL_BF16 ? 0.56 : 1.0);
-  return 4.5 + (double)((tiles * chunks + 511) / 512) * ((stages + chunks - 1) / chunks) * stage;
+  const WgradTiles t = wgrad_tiles(p);
+  const int64_t tiles = t.count * p->n_workers, chunks = wgrad_any_chunks(p);
+  const double stage = (tiles * chunks <= 256 ? 1.6 : 2.4) * t.NT * (p->dtype == DISTDL_BF16 ? 0.56 : 1.0);
+  return (t.rows == 64 ? 5.5 : 4.5) + (double)((tiles * chunks + 511) / 512) * ((t.stages + chunks - 1) / chunks) * stage;
 }
 
 int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st) {
@@ -840,26 +882,29 @@ int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st) {
     a.rows *= a.k[d];
   }
   a.nchunks = wgrad_any_chunks(p);
-  const int NT = nt_of(a.co);
-  a.ntm = (a.rows + 255) / 256;
+  const WgradTiles t = wgrad_tiles(p);
+  const int NT = t.NT;
+  a.ntm = (a.rows + t.rows - 1) / t.rows;
   a.ntn = (a.co + 32 * NT - 1) / (32 * NT);
   a.slot = (int64_t)a.rows * a.co + a.co;
   const dim3 grid((unsigned)(a.ntm * a.ntn), (unsigned)a.nchunks, (unsigned)p->n_workers);
   ProfScope prof("conv_bwd_weight_any", st);
-#define DISTDL_WANY(NT_, BF_)                                                                                          \
+#define DISTDL_WANY(ROWS_, NT_, BF_)                                                                                          \
   do {                                                                                                                 \
-    constexpr int lds = any_lds(256, NT_, BF_);                                                                            \
+    constexpr int lds = any_lds(ROWS_, NT_, BF_);                                                                          \
     if (lds > 64 * 1024)                                                                                               \
-      if (int rc_ = allow_large_lds<wgrad_any_kernel<NT_, BF_>>()) return rc_;                                         \
-    hipLaunchKernelGGL((wgrad_any_kernel<NT_, BF_>), grid, dim3(256), lds, st, p->d_workers, p->tab_x.dev,             \
+      if (int rc_ = allow_large_lds<wgrad_any_kernel<ROWS_, NT_, BF_>>()) return rc_;                                         \
+    hipLaunchKernelGGL((wgrad_any_kernel<ROWS_, NT_, BF_>), grid, dim3(256), lds, st, p->d_workers, p->tab_x.dev,             \
                        p->tab_dy.dev, partial, a);                                                                     \
   } while (0)
   if (p->dtype == DISTDL_BF16) {
-    if (NT == 1) DISTDL_WANY(1, true);
-    else DISTDL_WANY(2, true);
+    if (t.rows == 64) DISTDL_WANY(64, 1, true);
+    else if (NT == 1) DISTDL_WANY(256, 1, true);
+    else DISTDL_WANY(256, 2, true);
   } else {
-    if (NT == 1) DISTDL_WANY(1, false);
-    else DISTDL_WANY(2, false);
+    if (t.rows == 64) DISTDL_WANY(64, 1, false);
+    else if (NT == 1) DISTDL_WANY(256, 1, false);
+    else DISTDL_WANY(256, 2, false);
   }
 #undef DISTDL_WANY
   return DISTDL_OK;

@@ -81,6 +81,33 @@ def test_choice_among_fp32_kernels(case):
             assert float((got.double() - want).norm() / want.norm()) < TOL[F32], name
 
 
+# weight gradient, tiles of 64 rows (taps x input channels): 1, 63, 64, 65, 126 and 128 of them, 129 (256-row tiles), with one and
+# two column tiles, positions that end within an octet, a stage and a chunk, several workers' worth of chunks
+FEW_ROWS = [(1, 1, 4, (33,), 1, 1), (3, 7, 33, (61, 47), 3, 1), (1, 64, 5, (333,), 1, 1), (2, 13, 40, (129,), 5, 2), (2, 14, 3, (50, 41), 3, 1),
+            (5, 16, 32, (9, 10, 11), 2, 1), (2, 43, 64, (127,), 3, 1), (40, 3, 8, (90, 70), 3, 1)]
+
+
+@pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "odd"])
+@pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("case", FEW_ROWS, ids=[f"{c[1] * c[4] ** len(c[3])}rows{c[2]}cols" for c in FEW_ROWS])
+def test_weight_gradient_of_few_rows(case, dtype, offset):
+    """fp32: a sum of n positions in chunks is off by at most sqrt(n / 16) roundings of 2^-24: 252 000 positions 7e-6."""
+    require_gpu()
+    L = ConvLayer(*case, dtype, offset=offset)
+    L.dw.fill_(9.0), L.db.fill_(9.0)
+    got, want = L.run()[2], L.exact()[2]
+    assert float((got.double() - want).norm() / want.norm()) < TOL[dtype]
+    assert float((got.double() - want).abs().max() / want.abs().max()) < TOL[dtype]
+    db = L.dy.double().reshape(-1, case[2]).sum(0)
+    assert float((L.db.double() - db).norm() / db.norm()) < TOL[dtype]
+    if dtype == F32:  # an infinity stays with its rows and columns
+        L.dy[(0, *[0] * L.D, 1)] = float("inf")
+        got, want = L.run()[2], L.exact()[2]
+        sure = torch.isfinite(want)
+        assert torch.equal(torch.isfinite(got), sure)
+        assert not bool(sure.any()) or float((got[sure].double() - want[sure]).norm() / want[sure].norm().clamp_min(1e-300)) < TOL[dtype]
+
+
 # the same for bf16: planes of a few cells, classes of a stride, channels that are no multiples of 8, large layers
 CHOICE_BF16 = [((4, 4), 9, 44, 36, (4, 4, 4), 3, 1), ((4, 4), 4, 4, 16, (150, 150), 5, 2), ((4, 4), 6, 12, 44, (60, 67), 3, 1),
                ((1, 4), 2, 56, 4, (54, 57, 62), 3, 1), ((1, 1), 10, 32, 8, (120, 110), 3, 1)]
