@@ -113,10 +113,7 @@ def _check(rc):
 
 def _ptrs(tensors):
     """Host array of device pointers from a list of tensors (None -> NULL)."""
-    arr = (C.c_void_p * len(tensors))()
-    for i, t in enumerate(tensors):
-        arr[i] = None if t is None else t.data_ptr()
-    return arr
+    return (C.c_void_p * len(tensors))(*[None if t is None else t.data_ptr() for t in tensors])
 
 
 def _arr(ctype, values):
@@ -124,7 +121,11 @@ def _arr(ctype, values):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle.  Small passes are bound by the host: torch.cuda.current_stream() makes an object on every
+    call (2.8 us, as long as a launch), the raw handle takes 0.3 us."""
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dtype_code(dtype):

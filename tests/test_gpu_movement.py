@@ -492,3 +492,17 @@ def test_layout_convert_unaligned_and_errors():
     with pytest.raises(dd.DistdlError) as e:
         dd.distdl_layout_convert(plan, 0, True, [g_pf[0], None], g_cl)
     assert e.value.code == dd.ERR_NULL
+
+
+def test_calls_are_enqueued_on_the_current_stream():
+    require_gpu()
+    from paper_2006_03108_amd.binding import _stream
+    assert _stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert _stream() == side.cuda_stream != 0
+        src = [torch.arange(1 << 20, device="cuda", dtype=torch.float32)]   # made on the side stream, used behind it
+        out = [torch.empty_like(src[0]) for _ in range(2)]
+        dd.distdl_bcast_fwd(src, out, 2)
+        assert all(torch.equal(t, src[0]) for t in out)
+    assert _stream() == torch.cuda.current_stream().cuda_stream != side.cuda_stream
