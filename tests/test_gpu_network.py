@@ -178,6 +178,27 @@ def test_bulk_copy_is_scatter_and_gather_of_the_bulk():
         assert torch.equal(back[w], dense[w])
 
 
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("c", [1, 6, 8])
+def test_bulk_copy_by_pieces_of_channels(c, offset):
+    """Pieces of one, two and four channels, in three dimensions on workers of unequal size."""
+    require_gpu()
+    n, one = (7, 9, 8), (1, 1, 1)
+    plan = dd.distdl_plan_create(3, 2, c, c, n, (2, 2, 3), (3, 3, 3), one, one, one)
+    new = lambda shape: torch.randn(int(np.prod(shape)) + offset, device="cuda")[offset:].view(shape)
+    geoms = [plan.query(w) for w in range(plan.n_workers)]
+    dense, bufs = [new([2] + g["in_size"] + [c]) for g in geoms], [new([2] + g["buf_shape"] + [c]) for g in geoms]
+    want = [b.clone() for b in bufs]
+    bulk = [(slice(None), *(slice(a, a + m) for a, m in zip(g["bulk_off"], g["in_size"]))) for g in geoms]
+    for t, d, at in zip(want, dense, bulk):
+        t[at] = d
+    dd.distdl_bulk_copy(plan, dense, bufs, True)
+    assert all(torch.equal(b, t) for b, t in zip(bufs, want))
+    back = [new(list(d.shape)) for d in dense]
+    dd.distdl_bulk_copy(plan, back, bufs, False)
+    assert all(torch.equal(b, d) for b, d in zip(back, dense))
+
+
 def test_glue_rejects_bad_arguments():
     require_gpu()
     plan = dd.distdl_plan_create(2, 2, 4, 6, (8, 8), (2, 2), (2, 2), (2, 2), (0, 0), ONE2)

@@ -88,6 +88,43 @@ def test_maxpool_general_kernels(case):
         assert_close(from_cl(g_dx[w]), dx_want[w], TOL32, f"maxpool dx worker {w}")
 
 
+# windows that do not overlap, in pieces of one, two and four channels: channel counts, arrays that start one or two elements
+# into an allocation, cells that no window covers, zero padding
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("c", [1, 2, 6, 7, 12])
+@pytest.mark.parametrize("k,s,p", [(2, 2, 0), (2, 3, 0), (2, 2, 1)])
+def test_pool_adjoint_by_pieces_of_channels(k, s, p, c, offset):
+    require_gpu()
+    case = (2, 3, c, (14, 17), (2, 2), (k, k), (s, s), (p, p))
+    part, plan, x, dy = _pool_setup(case)
+    x[:, :, ::3] = 1.0                                              # ties: the first maximum counts
+
+    def put(a):
+        t = to_cl(a)
+        flat = torch.empty(t.numel() + offset, device="cuda")
+        flat[offset:] = t.reshape(-1)
+        return flat[offset:].view(t.shape)
+
+    bufs_o = prim.scatter_bulk(x.astype(np.float64), part, fill=np.nan)
+    y_want, args = layers.dist_maxpool_forward(bufs_o, part, (k, k), (s, s))
+    dys = prim.scatter_out(dy.astype(np.float64), part)
+    shapes = [b.shape for b in bufs_o]
+    want = dict(max=layers.dist_maxpool_adjoint(dys, args, part, shapes, (k, k), (s, s)),
+                avg=layers.dist_avgpool_adjoint(dys, part, shapes, (k, k), (s, s)))
+    g_x = [put(b) for b in prim.scatter_bulk(x, part, fill=np.float32(9.0))]
+    g_y = [put(np.zeros((3, c) + part.out_shape(w), np.float32)) for w in range(part.n_workers)]
+    dd.distdl_maxpool_fwd(plan, g_x, g_y)
+    g_dy = [put(t) for t in prim.scatter_out(dy, part)]
+    for kind in ("max", "avg"):
+        g_dx = [put(np.full(b.shape, -5.0, np.float32)) for b in bufs_o]
+        if kind == "max":
+            dd.distdl_maxpool_bwd(plan, g_x, g_dy, g_dx)
+        else:
+            dd.distdl_avgpool_bwd(plan, g_dy, g_dx)
+        for w in range(part.n_workers):
+            assert_close(from_cl(g_dx[w]), want[kind][w], TOL32, f"{kind} dx worker {w}")
+
+
 @pytest.mark.parametrize("case", [POOL_CASES[2], POOL_CASES[3], POOL_CASES[4], POOL_CASES[7]],
                          ids=lambda c: str(c[3]) + "k" + str(c[5]))
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
