@@ -14,6 +14,9 @@
 // pieces that eight neighbouring lanes write fall into different banks.
 // An operand whose rows are contiguous in memory instead of its k (W in dx, both operands of dW) is loaded two rows
 // wide for eight k lines by each thread: the transpose happens in registers and costs nothing.
+// fp32 operands of any alignment are loaded 8 or 16 bytes at a time (buffer loads and global stores of that width ask
+// for 4-byte alignment): an issue of a load is what a small product spends most of its stages on, and eight per octet
+// instead of two made a pass of 128 x 12800 -> 10, whose pieces are no multiples of four wide, 34.8 us instead of 29.6.
 #include <algorithm>
 #include <type_traits>
 
@@ -65,6 +68,7 @@ struct Operand {
   uint32_t off[NP];  // KC: of the pieces; else of the rows on line kp * 8
   uint32_t line;     // bytes from one row (KC) or k line to the next
   int K;
+  bool lone;         // k lines, two rows: the second is beyond the last
 
   // rows r0 ... of an operand with `rows` rows; the resource ends with the operand, so that k lines beyond K read as zero.
   // (Lines of a GiB: 64 of them are more than 32 bits; octets of k beyond a K shorter than a stage are left out here, single
@@ -73,6 +77,7 @@ struct Operand {
     rs = rsrc_of(base, (uint32_t)(KC ? rows : K_) * (uint32_t)ld * ES);
     line = (uint32_t)ld * ES;
     K = K_;
+    lone = false;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
       if constexpr (KC) {
@@ -81,6 +86,7 @@ struct Operand {
       } else {
         const int r = r0 + (tid % (R / NP)) * NP + i, kp = tid / (R / NP);
         off[i] = r < rows && kp * 8 < K_ ? (uint32_t)(kp * 8) * line + r * ES : kOob;
+        if (!VEC && i == 1) lone = off[0] != kOob && off[1] == kOob;
       }
     }
   }
@@ -106,6 +112,13 @@ struct Stager {
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[i][4 * j + e] = __uint_as_float(t[e]);
         }
+      } else if constexpr (!TAIL && !BF16) {  // (buffer loads ask for 4-byte alignment only)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(op.rs, op.off[i] + 16u * j, so, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[i][4 * j + e] = __uint_as_float(t[e]);
+        }
       } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[i][j] = one(op.rs, TAIL && k + j >= left ? kOob : op.off[i] + ES * j, so);
@@ -113,7 +126,7 @@ struct Stager {
     }
   }
   // the values at k0 ... of the operand's segment
-  __device__ inline void load(const Op& op, int k0, int tid) {
+  __device__ __forceinline__ void load(const Op& op, int k0, int tid) {
     if constexpr (KC) {
       const uint32_t so = (uint32_t)k0 * ES;
       const int left = op.K - k0;  // pieces beyond K read as zero
@@ -123,13 +136,22 @@ struct Stager {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const uint32_t so = k0 + j < op.K ? (uint32_t)(k0 + j) * op.line : kOob;  // (uniform)
-        if constexpr (VEC && NP == 2) {  // the row count is a multiple of 4
-          const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(op.rs, op.off[0], so, 0);
+        if constexpr (!BF16 && NP == 2) {  // two rows: where the second is not there (`lone`), the first in a load of its own
+          const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(op.rs, VEC || !op.lone ? op.off[0] : kOob, so, 0);
           v[0][j] = __uint_as_float(t[0]);
           v[1][j] = __uint_as_float(t[1]);
         } else {
 #pragma unroll
           for (int i = 0; i < NP; ++i) v[i][j] = one(op.rs, op.off[i], so);
+        }
+      }
+      if constexpr (!VEC && !BF16 && NP == 2) {
+        if (__builtin_amdgcn_ballot_w64(op.lone)) {  // (a wave at the operand's last row)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float x = one(op.rs, op.lone ? op.off[0] : kOob, k0 + j < op.K ? (uint32_t)(k0 + j) * op.line : kOob);
+            v[0][j] = op.lone ? x : v[0][j];
+          }
         }
       }
     }
@@ -333,15 +355,15 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
     if (pc) pc[(size_t)row * ldc + col] = v;
     else st((Out*)gb.c, (size_t)row * ldc + col, v);
   };
-  // four columns from `col` of a row (VEC: whole quads, 16-byte aligned rows)
-  const bool vec_out = VEC && !BF16 && ldc % 4 == 0 && ((uintptr_t)(pc ? (void*)pc : gb.c) & 15) == 0;
+  // four columns from `col` of a row, in one store whatever its alignment (a store asks for 4 bytes)
+  typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
   auto quad = [&](int row, int col, const float (&b)[4], float4 s) {
     const float o[4] = {s.x + b[0], s.y + b[1], s.z + b[2], s.w + b[3]};
     if (row >= gb.M) return;
-    if (vec_out && col + 4 <= gb.N) {
-      const u32x4 t = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
-      if (pc) *(u32x4*)(pc + (size_t)row * ldc + col) = t;  // read again by the reduction
-      else __builtin_nontemporal_store(t, (u32x4*)((float*)gb.c + (size_t)row * ldc + col));
+    if (!BF16 && col + 4 <= gb.N) {
+      const u32x4_any t = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
+      if (pc) *(u32x4_any*)(pc + (size_t)row * ldc + col) = t;  // read again by the reduction
+      else __builtin_nontemporal_store(t, (u32x4_any*)((float*)gb.c + (size_t)row * ldc + col));
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -374,6 +396,9 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
     }
   } else {
     // the four waves' partial tiles, [wave][64 rows][16 quads], added in wave order
+    const int col = n0 + 4 * (tid & 15);
+    float b[4];
+    bias_of(col, b);  // (in flight while the tiles are written)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -383,9 +408,6 @@ __device__ inline void gemm_split_tile(const SplitGrid& sg_, int wg, char* smem)
           ((float4*)red)[wave * 1024 + (32 * i + ml) * 16 + ((8 * j + 2 * q + h) ^ (ml & 15))] =
               float4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
     __syncthreads();
-    const int col = n0 + 4 * (tid & 15);
-    float b[4];
-    bias_of(col, b);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int r = (tid >> 4) + 16 * q;

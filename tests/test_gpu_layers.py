@@ -781,10 +781,13 @@ AFFINE_SPLIT_CASES = [(1, 1, 1, 1, 1), (2, 17, 3, 1, 1), (65, 129, 67, 2, 3), (6
                       (32, 1028, 1028, 2, 2), (33, 1028, 1028, 2, 2)]
 # reductions of a K split: up to 16 splits, of both contractions of the adjoint (one launch), rows of quads and not
 AFFINE_REDUCE_CASES = [(37, 2000, 1001, 2, 3), (900, 68, 900, 1, 1), (900, 70, 901, 2, 1), (300, 64, 8000, 1, 2)]
+# rows of no whole 16-byte pieces: a last row without its pair, at the first and last lane of a wave, in tiles of 64 and 128;
+# whole stages and tails of 1 .. 7 values of k
+AFFINE_ODD_CASES = [(65, 1027, 191, 1, 1), (191, 65, 2049, 1, 1), (1, 897, 899, 1, 1), (321, 1153, 1025, 1, 1)]
 
 
 @pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "odd"])
-@pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi", AFFINE_SPLIT_CASES + AFFINE_REDUCE_CASES)
+@pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi", AFFINE_SPLIT_CASES + AFFINE_REDUCE_CASES + AFFINE_ODD_CASES)
 def test_affine_split_against_fp64(n_b, n_fi, n_fo, P_fo, P_fi, offset):
     """fp32 layers on the split bf16 products, against fp64 sums on the device; the arrays start `offset` elements into
     an allocation.  A sum of K products of the split is off by at most K / 16 + 2 roundings of 2^-24 of its running
