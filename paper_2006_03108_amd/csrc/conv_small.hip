@@ -340,9 +340,10 @@ struct Corr16Args {
   int32_t tapmin1, tapmin2;    // smallest tap offset along dimensions 1, 2
   int32_t wpw, g0, ntaps;      // workgroups per worker; steps per workgroup (large patches); taps per kernel plane
   int32_t tapo[64];            // patch byte offset of tap (t1, t2)
-  const float* wt;             // weights: [t0][tap][lane][KM]; null: taken from w
+  const float* wt;             // weights: [t0][tap][lane][KM]; null (one kernel plane): taken from w
   const float* w;              // the layer's weights [co][ci][tap]
-  int32_t ci_n, taps, k1, k2;  // their input channels, taps, and the kernel's extents in dimensions 1, 2
+  int32_t ci_n, taps, c_w;     // their input channels, taps, and channel pairs
+  int32_t wtap[68];            // byte offset of tap (t1, t2) among the weights of a pair
   const float* bias;           // may be null
 };
 
@@ -386,6 +387,29 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
   typedef typename Piece<V>::T PT;
   constexpr uint32_t CG = KM * 4;  // bytes per cell and channel group in LDS
   const CorrArgs& c = a.c;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = lane >> 4, ij = lane & 15;
+  // One kernel plane: its weights are staged once, so every workgroup fetches them in the layer's own order (a launch that
+  // rearranges them first took 4.5 us; 1 -> 1 channels, one dimension, forward and backward: 36 -> 28 to 31 us).  A thread's
+  // weights are one pair of channels and every (4 / KM)th tap; those of a known tap count, or the first, are under way before
+  // anything else and written to LDS behind the first stage's loads.  A workgroup's set-up was 20000 of its 67000 clocks for
+  // 16 -> 16 channels, 3 x 3, 8 x 256 x 256 (weights 6000, pieces with 64-bit divisions 6000), now 11000: 36.1 -> 34.3 us; the
+  // rest is its matrix instructions (two waves of a SIMD unit: 37000 clocks) and what they do not cover.
+  const uint32_t wpair = tid / KM & 63;
+  uint32_t wlane;
+  {
+    const int k = KM * (int)(wpair >> 4) + tid % KM, n = wpair & 15;
+    const int co = c.mode == 0 ? n : k, ci = c.mode == 0 ? k : n;
+    wlane = k < c.kc && n < c.nc ? (uint32_t)((co * a.ci_n + ci) * a.taps) * 4u : kOobS;
+  }
+  const __amdgpu_buffer_rsrc_t rlw = rsrc_of(a.w, a.wt ? 0u : (uint32_t)(a.c_w * a.taps) * 4u);
+  auto layer_weight = [&](int j) {  // tap j * 4 / KM + wave / KM of the pair (a.wtap has room for the taps beyond the last)
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rlw, wlane, (uint32_t)a.wtap[j * (4 / KM) + wave / KM], 0));
+  };
+  constexpr int NW = NT > 0 ? (NT * KM + 3) / 4 : 1;
+  float wreg[NW];
+  if (!a.wt)
+#pragma unroll
+    for (int j = 0; j < NW; ++j) wreg[j] = layer_weight(j);
   // XCD-aware order: consecutive tiles stay behind one L2
   const uint32_t nblk = gridDim.x;
   const uint32_t rblk = (blockIdx.x & 7u) * (nblk >> 3) + (blockIdx.x >> 3);
@@ -401,17 +425,18 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
   // Large patches: a.g0 steps of one window per workgroup (the loop over windows costs registers these variants
   // do not have).
   constexpr bool MULTI = PA <= 6;
-  const int64_t total = (int64_t)n1 * n2 * nsteps;
-  int64_t f, f_end;
+  const uint32_t total = (uint32_t)(n1 * n2) * (uint32_t)nsteps;  // (at most the cells of a buffer, fewer than 2^29)
+  if (total == 0) return;
+  uint32_t f, f_end;
   if constexpr (MULTI) {
-    f = total * slice / a.wpw;
-    f_end = total * (slice + 1) / a.wpw;
+    const uint32_t each = total / (uint32_t)a.wpw, more = total - each * (uint32_t)a.wpw;
+    f = each * slice + more * slice / (uint32_t)a.wpw;  // (the longer runs among the others, not on the same units)
+    f_end = each * (slice + 1) + more * (slice + 1) / (uint32_t)a.wpw;
   } else {
-    const int ngrp = (nsteps + a.g0 - 1) / a.g0;
-    const int64_t window = slice / (uint32_t)ngrp;
-    f = window * nsteps + (int64_t)(slice - (uint32_t)window * (uint32_t)ngrp) * a.g0;
-    f_end = min(f + a.g0, (window + 1) * nsteps);
-    if (window >= (int64_t)n1 * n2) return;
+    const uint32_t ngrp = (uint32_t)((nsteps + a.g0 - 1) / a.g0), window = slice / ngrp;
+    if (window >= (uint32_t)(n1 * n2)) return;
+    f = window * (uint32_t)nsteps + (slice - window * ngrp) * (uint32_t)a.g0;
+    f_end = min(f + (uint32_t)a.g0, (window + 1) * (uint32_t)nsteps);
   }
   if (f >= f_end) return;
   int q1_0 = 0, q2_0 = 0, step_begin = 0, step_end = 0;
@@ -424,37 +449,45 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
   const uint32_t wfloats = (uint32_t)ntaps * 64u * KM;  // weights of one kernel plane
   const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wt, a.wt ? (uint32_t)max(nt0, 1) * wfloats * 4u : 0u);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kg = lane >> 4, ij = lane & 15;
   char* const ldsb = (char*)lds;
   const uint32_t plane_cells = (uint32_t)a.R * a.Cw, ncells = a.tp * plane_cells;
   const uint32_t ps = (uint32_t)a.ps, wl = 4u * ps;  // weights behind the patch
   // channel padding of the patch must read as zero
-  for (uint32_t i = tid; i < ps / 4u; i += 256) ((float4*)lds)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c.kc != 4 * KM)
+    for (uint32_t i = tid; i < ps / 4u; i += 256) ((float4*)lds)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
   // per-thread patch pieces: global byte offset inside the first plane of a stage (kOobS: the cell lies outside
   // the input and reads as zero) and LDS byte offset with the piece's plane in bits 24-29
-  uint32_t goff[PA], loff[PA];
+  uint32_t goff[PA], loff[PA], rc[PA];  // rc: the piece's row of the patch, and its cell of the row from bit 16
   uint32_t abase[4], soff[4];
   const int trtc = a.tr * a.tc, npos = a.tp * trtc;
-  auto setup_pieces = [&]() {
+  auto lay_out_pieces = [&]() {
     const uint32_t ppc = c.kc / V, npieces = ncells * ppc;
     const float r_ppc = 1.0f / (float)ppc, r_pc = 1.0f / (float)plane_cells, r_cw = 1.0f / (float)a.Cw;
 #pragma unroll
     for (int i = 0; i < PA; ++i) {
       const uint32_t q = tid + i * 256;
-      goff[i] = kOobS;
       loff[i] = kSkip;
+      goff[i] = rc[i] = 0;
       if (q < npieces) {
         const uint32_t cell = div_small(q, ppc, r_ppc), part = q - cell * ppc;
         const uint32_t wp = div_small(cell, plane_cells, r_pc), rem = cell - wp * plane_cells;
         const uint32_t rr = div_small(rem, a.Cw, r_cw), cc = rem - rr * a.Cw;
-        const int i1 = g.in_base[1] + q1_0 * c.is[1] + a.tapmin1 + (int)rr;
-        const int i2 = g.in_base[2] + q2_0 * c.is[2] + a.tapmin2 + (int)cc;
         const uint32_t ch = part * V;  // first channel of the piece
         loff[i] = (cell * CG + (ch / KM) * ps + (ch % KM) * 4u) | (wp << 24);
-        if (i1 >= 0 && i1 < g.in_ext[1] && i2 >= 0 && i2 < g.in_ext[2])
-          goff[i] = (wp * sin + (uint32_t)i1 * si1 + (uint32_t)i2 * si2 + part * V) * 4u;
+        rc[i] = rr | cc << 16;
+        goff[i] = (wp * sin + rr * si1 + cc * si2 + ch) * 4u;
       }
+    }
+  };
+  uint32_t poff[PA];
+  auto setup_pieces = [&]() {
+    const int i1 = g.in_base[1] + q1_0 * c.is[1] + a.tapmin1, i2 = g.in_base[2] + q2_0 * c.is[2] + a.tapmin2;
+    const uint32_t base = ((uint32_t)i1 * si1 + (uint32_t)i2 * si2) * 4u;  // (modulo 2^32 where it is negative)
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+      const uint32_t r = (uint32_t)i1 + (rc[i] & 0xffffu), q = (uint32_t)i2 + (rc[i] >> 16);
+      poff[i] = loff[i] != kSkip && r < (uint32_t)g.in_ext[1] && q < (uint32_t)g.in_ext[2] ? goff[i] + base : kOobS;
     }
   };
   // operand addresses and store offsets: lane (ij, kg) multiplies window position (wave * 4 + mt) * 16 + ij.  The
@@ -521,7 +554,7 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
     const uint32_t pmax = (uint32_t)min(a.tp, planes - sp.step * a.tp);
     const uint32_t sbase = ((uint32_t)sp.n * sin + (uint32_t)in_plane(sp.q0, t0) * si0) * 4u;
 #pragma unroll
-    for (int i = 0; i < PA; ++i) ra[i] = Piece<V>::load(rin, (loff[i] >> 24) < pmax ? goff[i] : kOobS, sbase);
+    for (int i = 0; i < PA; ++i) ra[i] = Piece<V>::load(rin, (loff[i] >> 24) < pmax ? poff[i] : kOobS, sbase);
     if (weights) {
 #pragma unroll
       for (int i = 0; i < kPB16; ++i) {
@@ -623,25 +656,18 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
     }
   };
 
-  // One kernel plane: its weights are staged once, so every workgroup fetches them in the layer's own order (a launch that
-  // rearranges them first took 4.5 us; 1 -> 1 channels, one dimension, forward and backward: 36 -> 28 to 31 us).
-  if (!a.wt)
-#pragma unroll 8
-    for (uint32_t i = tid; i < wfloats; i += 256) {
-      const uint32_t r = i / KM;
-      lds[wl / 4u + i] = corr16_weight(a.w, c, 0, (int)(r >> 6), (int)(KM * ((r & 63u) >> 4) + i % KM), (int)(r & 15u), a.ci_n,
-                                       a.taps, a.k1, a.k2);
-    }
-  __syncthreads();  // the zero fill is complete
+  lay_out_pieces();
+  if (c.kc != 4 * KM) __syncthreads();  // the zero fill is complete
+  bool weights_there = false;
   int staged_t0 = a.wt ? -1 : 0;  // kernel plane whose weights are in LDS (they stay valid from window to window)
   do {
   {
-    const int64_t window = f / nsteps;
-    step_begin = (int)(f - window * nsteps);
-    step_end = (int)min((int64_t)nsteps, step_begin + (f_end - f));
-    q2_0 = (int)(window % n2) * a.tc;
-    q1_0 = (int)(window / n2) * a.tr;
-    f += step_end - step_begin;
+    const uint32_t window = f / (uint32_t)nsteps, w1 = window / (uint32_t)n2;
+    step_begin = (int)(f - window * (uint32_t)nsteps);
+    step_end = (int)min((uint32_t)nsteps, step_begin + (f_end - f));
+    q2_0 = (int)(window - w1 * (uint32_t)n2) * a.tc;
+    q1_0 = (int)w1 * a.tr;
+    f += (uint32_t)(step_end - step_begin);
   }
   setup_pieces();
   StagePos cur = pos_of(step_begin), out = cur;  // the stage in flight; the step that is being accumulated
@@ -649,6 +675,19 @@ __global__ __launch_bounds__(256, 2) void corr16_kernel(const WorkerDev* __restr
   next_valid(cur);
   if (cur.step < step_end) load_stage(cur, cur.t0 != staged_t0);
   setup_operands();  // while the first stage is on its way
+  if (MULTI ? !weights_there : true) {
+    weights_there = true;
+    if (!a.wt) {
+      const uint32_t at = wl / 4u + tid;
+#pragma unroll
+      for (int j = 0; j < NW; ++j)
+        if (tid + j * 256 < (int)wfloats) lds[at + j * 256] = wreg[j];
+      if constexpr (NT == 0) {
+#pragma unroll 8
+        for (int j = 1; j * 256 + tid < (int)wfloats; ++j) lds[at + j * 256] = layer_weight(j);
+      }
+    }
+  }
   for (int step = step_begin; step < step_end; ++step) {
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) acc[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -832,7 +871,11 @@ int launch_corr16(distdl_plan* p, int which, const CorrArgs& c, bool vec, const 
   const int taps = p->ksize[0] * p->ksize[1] * p->ksize[2];
   a.wt = c.nt[0] == 1 ? nullptr : wscratch;
   a.w = w;
-  a.ci_n = (int32_t)p->n_ci, a.taps = taps, a.k1 = p->ksize[1], a.k2 = p->ksize[2];
+  a.ci_n = (int32_t)p->n_ci, a.taps = taps, a.c_w = (int32_t)(p->n_ci * p->n_co);
+  if (!a.wt)
+    for (int t1 = 0; t1 < c.nt[1]; ++t1)
+      for (int t2 = 0; t2 < c.nt[2]; ++t2)
+        a.wtap[t1 * c.nt[2] + t2] = ((c.tapid[0][0] * p->ksize[1] + c.tapid[1][t1]) * p->ksize[2] + c.tapid[2][t2]) * 4;
   a.bias = bias;
   const int wtotal = c.nt[0] * a.ntaps * 64 * s.km;
   if (a.wt && wtotal > 0) {

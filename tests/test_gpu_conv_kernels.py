@@ -124,6 +124,24 @@ def test_choice_among_bf16_kernels(case):
             assert float((got.double() - want).norm() / want.norm()) < TOL[BF16], name
 
 
+# 16 x 16 tiles: channel quads full and not (the patch's padding), 9, 25 and other tap counts, kernel planes, runs of a
+# workgroup over several windows, samples stacked in a window, and fewer steps than workgroups
+SIXTEEN = [(3, 4, 8, (90, 70), 3, 1), (2, 8, 16, (61, 83), 5, 1), (40, 16, 16, (70, 90), 3, 1), (2, 13, 5, (64, 64), 3, 1), (9, 16, 4, (900,), 7, 2),
+           (5, 7, 16, (33, 47), 2, 1), (2, 16, 12, (12, 40, 36), 3, 1), (2, 5, 9, (40, 50), 4, 2), (1, 1, 1, (16,), 3, 1)]
+
+
+@pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "odd"])
+@pytest.mark.parametrize("case", SIXTEEN, ids=str)
+def test_sixteen_channel_tiles(case, offset):
+    """fp32 sums of at most 432 products, and of up to 250000 in the weight gradient (random walk of their roundings)."""
+    require_gpu()
+    L = ConvLayer(*case, offset=offset)
+    assert dd.distdl_debug_conv_kernels(L.plan, offset == 0)[0] == 2
+    L.y.fill_(7.0), L.dx.fill_(5.0)
+    for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
+        assert float((got.double() - want).norm() / want.norm()) < 5e-6, name
+
+
 @pytest.mark.parametrize("c_in,c_out", [(20, 24), (19, 21), (28, 3)], ids=["split", "gather", "both"])
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("pad", [0, 1], ids=["no_halo", "halo"])
