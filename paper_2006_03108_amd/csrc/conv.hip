@@ -315,12 +315,12 @@ static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {
   if (wgrad16_supported(p, vec16))
     consider(Wgrad::k16, 6.0 + 0.8 * T + pos * p->ksize[0] * T * (p->ksize[0] > 1 ? 12e-6 : 7e-6));
   if (vec16 && wgrad_split_supported(p)) consider(Wgrad::kSplit, 1.6 * wgrad_split_us(p));
-  // (tiles of 64 rows: their estimate is less sure, and the 16 x 16 and bf16 tiles stay unless they take 0.7 of the time)
+  // (tiles of 64 rows: their estimate is less sure, and the 16 x 16 and bf16 tiles stay unless they take 0.75 and 0.7 of the time)
   if (conv_any_supported(p) && !wgrad_any_few_rows(p)) consider(Wgrad::kAny, wgrad_any_us(p));
   const bool fits = wgrad_mfma_supported(p) && p->n_workers * wgrad_chunks(p) <= 65535;
   if (fits && bf16 && vec16) consider(Wgrad::kMfma, wgrad_taps_us(p));
   if (conv_any_supported(p) && wgrad_any_few_rows(p))
-    consider(Wgrad::kAny, wgrad_any_us(p) / (best == Wgrad::k16 || best == Wgrad::kMfma ? 0.7 : 1.0));
+    consider(Wgrad::kAny, wgrad_any_us(p) / (best == Wgrad::k16 ? 0.75 : best == Wgrad::kMfma ? 0.7 : 1.0));
   if (best == Wgrad::kDirect && fits && (!bf16 || vec16)) best = Wgrad::kMfma;
   p->wgrad_kernel[vec16] = (int)best;
   return best;
