@@ -509,7 +509,35 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   const Corr kernel = choose_data(plan, aligned);
   WeightJob job;
   if ((rc = weight_job(plan, kernel, true, w_dev, aligned, st, job))) return rc;
-  // [dConv]* with respect to w and b, then R over the workers, whose launch lays out the data gradient's weights
+  // [dConv]* with respect to x, into the whole padded buffers
+  auto data_gradient = [&]() -> int {
+    int rc = DISTDL_OK;
+    if (kernel == Corr::k16) {
+      if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
+    } else if (kernel == Corr::kSplit) {
+      if ((rc = conv_bwd_data_split(plan, (const float*)w_dev, st))) return rc;
+    } else if (kernel == Corr::kMfma) {
+      if ((rc = conv_bwd_data_mfma(plan, w_dev, st))) return rc;
+    } else if (kernel == Corr::kAny) {
+      if ((rc = conv_bwd_data_any(plan, w_dev, aligned, st))) return rc;
+    } else {
+      if ((rc = prepare_weights(plan, w_dev, st))) return rc;
+      ProfScope prof("conv_bwd_data_direct", st);
+      const dim3 dgrid((unsigned)((total + 255) / 256), plan->n_workers);
+      if (bf16)
+        hipLaunchKernelGGL(conv_bwd_data_direct_kernel<uint16_t>, dgrid, dim3(256), 0, st, plan->d_workers,
+                           plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
+      else
+        hipLaunchKernelGGL(conv_bwd_data_direct_kernel<float>, dgrid, dim3(256), 0, st, plan->d_workers,
+                           plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
+    }
+    return rc;
+  };
+  // Where R's launch can lay out its weights it comes after that; elsewhere before, so that H* does not follow the kernel that
+  // wrote what it reads (32 -> 32 channels, 5^3, stride 2, 256^3, bf16: H* 119 -> 105 us, the pass 0.8 % less).
+  const bool data_last = job.kind != 0;
+  if (!data_last && (rc = data_gradient())) return rc;
+  // [dConv]* with respect to w and b, then R over the workers
   const int nchunks = wgrad_partials(plan, wgrad, vec16);
   int nw = c.taps * c.ci * c.co + c.co;
   if (wgrad == Wgrad::k16) {
@@ -552,26 +580,7 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
     nw <= 8192 ? by_type(std::integral_constant<int, 16>{}) : by_type(std::integral_constant<int, 64>{});
   }
   if ((rc = launch_weight_job(job, st))) return rc;
-  // [dConv]* with respect to x, into the whole padded buffers
-  if (kernel == Corr::k16) {
-    if ((rc = conv_bwd_data16(plan, (const float*)w_dev, aligned, st))) return rc;
-  } else if (kernel == Corr::kSplit) {
-    if ((rc = conv_bwd_data_split(plan, (const float*)w_dev, st))) return rc;
-  } else if (kernel == Corr::kMfma) {
-    if ((rc = conv_bwd_data_mfma(plan, w_dev, st))) return rc;
-  } else if (kernel == Corr::kAny) {
-    if ((rc = conv_bwd_data_any(plan, w_dev, aligned, st))) return rc;
-  } else {
-    if ((rc = prepare_weights(plan, w_dev, st))) return rc;
-    ProfScope prof("conv_bwd_data_direct", st);
-    const dim3 dgrid((unsigned)((total + 255) / 256), plan->n_workers);
-    if (bf16)
-      hipLaunchKernelGGL(conv_bwd_data_direct_kernel<uint16_t>, dgrid, dim3(256), 0, st, plan->d_workers,
-                         plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
-    else
-      hipLaunchKernelGGL(conv_bwd_data_direct_kernel<float>, dgrid, dim3(256), 0, st, plan->d_workers,
-                         plan->tab_dy.dev, plan->d_wt, plan->tab_dx.dev, c);
-  }
+  if (data_last && (rc = data_gradient())) return rc;
   DISTDL_HIP_TRY(hipGetLastError());
   // dx <- H* dx
   return halo ? run_halo(plan, true, plan->tab_dx, dx_bufs_dev, st) : DISTDL_OK;
