@@ -8,7 +8,7 @@
 // A workgroup of four waves owns a tr x tc window of 128 MT output positions and walks output planes.  A stage is
 //   (kernel plane t0, tap group, 16 channels):
 // the input cells that the group's taps read are loaded, split into three bf16 planes and written to LDS, as are the
-// group's weights (split once per call by the re-layout kernel); then every tap multiplies 6 MT MFMAs per wave.
+// group's weights (split once per call, by a launch before: weight_job.h); then every tap multiplies 6 MT MFMAs per wave.
 // The taps of a kernel plane are grouped by the residue of their input offset modulo the step: a group's cells are then
 // the cells of one residue only, the cell of (position, tap) is position + constant, and a stage of a stride-2 layer is a
 // quarter of the patch with a quarter of the taps.  Three planes of a whole 5 x 5 stride-2 stage would be 200 KB; the
