@@ -70,6 +70,7 @@ _SIGS = {
     "distdl_debug_slot_policy": [_p32, _p32, _p32, _i, _p32],
     "distdl_debug_conv_path": [_vp, _p32],
     "distdl_debug_conv_kernels": [_vp, _i, _p32],
+    "distdl_debug_conv_split": [_vp, _i, _p32],
     "distdl_affine_plan_create": [C.POINTER(_vp), _i64, _i64, _i64, _i, _i, _i],
     "distdl_affine_plan_destroy": [_vp],
     "distdl_affine_fwd": [_vp, _pp, _pp, _pp, _pp, _vp],
@@ -366,6 +367,13 @@ def distdl_debug_conv_kernels(plan, aligned=True):
     """(forward, data gradient, weight gradient) kernels that run: 0 direct, 1 32-wide MFMA tiles, 2 16-wide, 3 split, 4 gather."""
     out = (C.c_int32 * 3)()
     _check(lib.distdl_debug_conv_kernels(plan.handle, int(aligned), out))
+    return tuple(out)
+
+
+def distdl_debug_conv_split(plan, backward=False):
+    """(launches, cells to a position, columns of a position, products that two taps share) of the split kernels."""
+    out = (C.c_int32 * 4)()
+    _check(lib.distdl_debug_conv_split(plan.handle, int(backward), out))
     return tuple(out)
 
 

@@ -408,6 +408,13 @@ int distdl_debug_conv_kernels(const distdl_plan* plan, int aligned, int32_t out[
   return DISTDL_OK;
 }
 
+int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[4]) {
+  if (!plan || !out) return set_error(DISTDL_ERR_NULL, "conv_split: null argument");
+  if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_split: plan has no kernel");
+  corr_split_shape(plan, backward != 0, out);
+  return DISTDL_OK;
+}
+
 int distdl_conv_local_fwd(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev, const void* bias_dev,
                           void* const y_dev[], void* stream) {
   return distdl::conv_fwd_core(plan, x_bufs_dev, w_dev, bias_dev, y_dev, (hipStream_t)stream, false);

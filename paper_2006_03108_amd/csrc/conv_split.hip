@@ -48,7 +48,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GiB)
-constexpr int kGroupTaps = 10, kFewTaps = 8;
+constexpr int kGroupTaps = 10, kFewTaps = 8, kMaxFewColumns = 0xffff;
 
 template <class ArgsPtr>
 __host__ __device__ inline PerWorker derive_of(const WorkerDev& wd, ArgsPtr a) {
@@ -145,7 +145,7 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
       soff[mt] = ((g.out_base[1] + g.os[1] * q1) * so1 + (g.out_base[2] + g.os[2] * q2) * so2 + ch0) * 4u;
     if constexpr (FEW) {
       const int cell = g.out_base[2] + g.os[2] * q2, lo = max(0, -cell * a->nch), hi = min(c.nc, (g.out_ext[2] - cell) * a->nch);
-      live[mt] = soff[mt] == kOob ? 0u : (uint32_t)lo | (uint32_t)hi << 16;
+      live[mt] = soff[mt] == kOob ? 0u : (uint32_t)lo | (uint32_t)hi << 16;  // (at most kMaxFewColumns)
     }
     if (wr >= c.tr) wr = 0, wc = 0;  // idle position: multiplies something in range, never stored
     abase[mt] = (FEW ? 0u : (uint32_t)h * HB) + (uint32_t)(wr * c.Cw + wc) * 16u;
@@ -832,9 +832,10 @@ SplitPlan* split_plan(const distdl_plan* p) {
     double least = 1e300;
     const int nch = (int)(dir == 0 ? p->n_co : p->n_ci), kc = (int)(dir == 0 ? p->n_ci : p->n_co), s2 = dir == 0 ? 1 : p->stride[2];
     for (int fold = 1; fold <= 32; fold = fold < s2 ? s2 : fold + s2) {
-      if (fold > 1 && fold * nch > 32 && fold != s2) break;
+      // (one class instead of several along dimension 2 pays for any columns; FEW keeps the bounds of a position's in 16 bits)
+      if (fold > 1 && (int64_t)fold * nch > (fold == s2 ? kMaxFewColumns : 32)) break;
       for (const bool octet : {false, true}) {
-      if (octet && (kc % 16 == 0 || kc % 16 > 8)) continue;
+      if (octet && (kc % 16 == 0 || kc % 16 > 8 || nch > kMaxFewColumns)) continue;
       Launches l;
       double sum = 0, most = 0;  // (classes that fill the chip together only are one launch)
       bool ok = true;
@@ -877,6 +878,17 @@ double corr_split_used(const distdl_plan* p, bool backward) { return split_plan(
 double corr_split_us(const distdl_plan* p, bool backward) {
   const double cells = (double)p->n_workers * p->n_b * (backward ? p->max_buf_cells : p->max_out_cells);
   return 2.7 + split_plan(p)->dir[backward ? 1 : 0].clocks / 2240 + cells * (double)(p->n_ci + p->n_co) * 0.65e-6;
+}
+
+void corr_split_shape(const distdl_plan* p, bool backward, int32_t out[4]) {
+  const Launches& d = split_plan(p)->dir[backward ? 1 : 0];
+  out[0] = (int32_t)d.v.size();
+  out[1] = out[2] = out[3] = 0;
+  for (const Launch& l : d.v) {
+    out[1] = l.a.fold;
+    out[2] = std::max(out[2], l.a.c.nc);
+    out[3] = std::max(out[3], l.a.npairs);
+  }
 }
 
 int split_weight_job(distdl_plan* p, bool backward, const float* w, hipStream_t st, WeightJob& job) {

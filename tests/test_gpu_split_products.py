@@ -92,6 +92,18 @@ def test_few_channels_with_a_weight_that_is_not_finite(shape):
     test_conv_with_a_weight_that_is_not_finite(shape)
 
 
+@pytest.mark.parametrize("c_in,n,k,s,p,fold", [(21736, 9, 8, 3, 3, 3), (24420, 9, 7, 2, 3, 2), (33000, 17, 7, 2, 3, 1)])
+def test_data_gradient_of_very_many_channels(c_in, n, k, s, p, fold):
+    """65208 and 48840 columns of a position, whose bounds still fit 16 bits, and a layer that has too many for that; sums of at
+    most 128 products."""
+    require_gpu()
+    L = ConvLayer(1, c_in, 8, (n, n), k, s, p=p)
+    assert dd.distdl_debug_conv_kernels(L.plan)[1] == 3 and dd.distdl_debug_conv_split(L.plan, True)[1] == fold
+    L.dx.fill_(5.0)
+    got, want = L.run()[1], L.exact()[1]
+    assert _rel(got, want) < 5e-6 and float((got.double() - want).abs().max() / want.abs().max()) < 1e-5
+
+
 @pytest.mark.parametrize("small", ["x", "w", "dy"])
 @pytest.mark.parametrize("shape", LAYERS, ids=IDS)
 def test_conv_of_very_small_numbers(shape, small):

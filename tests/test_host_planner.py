@@ -260,6 +260,18 @@ def test_conv_kernels_for_shapes_at_the_limits():
     assert run(*many) == (4, 4, 4)
 
 
+@pytest.mark.parametrize("plan", [(2, 1, 16640, 32, [9, 9], [1, 1], [5, 5], [4, 4], [2, 2]), (1, 1, 16640, 64, [257], [1], [5], [4], [2]),
+                                  (2, 1, 33000, 8, [17, 17], [1, 1], [7, 7], [2, 2], [3, 3]), (1, 1, 8, 65536, [9], [1], [3], [1], [1]),
+                                  (1, 1, 65540, 20, [9], [1], [3], [1], [1]), (1, 1, 20, 80000, [9], [1], [1], [4], [0])], ids=str)
+def test_columns_of_a_position_fit_16_bits(plan):
+    """The split kernels for few channels hold the bounds of a position's columns in 16 bits each: a launch of more columns is
+    one of the general form, with one cell to a position and no products that two taps share."""
+    p = dd.distdl_plan_create(*plan, [1] * plan[0])
+    for backward in (False, True):
+        _, fold, columns, pairs = dd.distdl_debug_conv_split(p, backward)
+        assert columns <= 0xffff or (fold == 1 and pairs == 0)
+
+
 def test_table_cache_policy_never_rewrites_a_block_another_reader_may_hold():
     """The device-table cache (pointer arrays, GEMM descriptors), run without a device: eight blocks per stream with
     least-recently-used replacement, no replacement across streams, blocks selected during capture pinned for good,
