@@ -542,8 +542,23 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   };
   // Where R's launch can lay out its weights it comes after that; elsewhere before, so that H* does not follow the kernel that
   // wrote what it reads (32 -> 32 channels, 5^3, stride 2, 256^3, bf16: H* 119 -> 105 us, the pass 0.8 % less).
-  const bool data_last = job.kind != 0;
-  if (!data_last && (rc = data_gradient())) return rc;
+  // (also where dw or db lies on the weights or on dy, which the data gradient reads)
+  auto on = [](const void* a, size_t na, const void* b, size_t nb) {
+    return a && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+  };
+  const size_t w_bytes = (size_t)c.taps * c.ci * c.co * esz, b_bytes = (size_t)c.co * esz;
+  bool in_place = on(dw_dev, w_bytes, w_dev, w_bytes) || on(dbias_dev, b_bytes, w_dev, w_bytes);
+  for (int w = 0; w < plan->n_workers; ++w) {
+    const WorkerDev& wd = plan->workers[w];
+    const size_t y_bytes = (size_t)plan->n_b * wd.out[0] * wd.out[1] * wd.out[2] * b_bytes;
+    in_place |= on(dw_dev, w_bytes, dy_dev[w], y_bytes) || on(dbias_dev, b_bytes, dy_dev[w], y_bytes);
+  }
+  const bool data_last = job.kind != 0 && !in_place;
+  if (!data_last) {
+    if ((rc = launch_weight_job(job, st))) return rc;
+    job.kind = 0;
+    if ((rc = data_gradient())) return rc;
+  }
   // [dConv]* with respect to w and b, then R over the workers
   const int nchunks = wgrad_partials(plan, wgrad, vec16);
   int nw = c.taps * c.ci * c.co + c.co;

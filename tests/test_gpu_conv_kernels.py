@@ -142,6 +142,20 @@ def test_sixteen_channel_tiles(case, offset):
         assert float((got.double() - want).norm() / want.norm()) < 5e-6, name
 
 
+@pytest.mark.parametrize("c_in,c_out", [(20, 24), (19, 21), (12, 8)], ids=["split", "gather", "16 x 16"])
+@pytest.mark.parametrize("onto", ["w", "dy"])
+def test_weight_gradient_in_place(onto, c_in, c_out):
+    """dw written onto the weights, or onto a dy that has served: the data gradient reads both as they were."""
+    require_gpu()
+    L = ConvLayer(2, c_in, c_out, (40, 41), 3, 1)
+    want = L.exact()
+    L.run()
+    L.dw = L.w if onto == "w" else L.dy.view(-1)[:L.w.numel()].view(L.w.shape)
+    L.dx.fill_(5.0)
+    for name, got, exact in list(zip(("y", "dx", "dw"), L.run(), want))[1:]:
+        assert float((got.double() - exact).norm() / exact.norm()) < TOL[F32], name
+
+
 @pytest.mark.parametrize("c_in,c_out", [(20, 24), (19, 21), (28, 3)], ids=["split", "gather", "both"])
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("pad", [0, 1], ids=["no_halo", "halo"])
