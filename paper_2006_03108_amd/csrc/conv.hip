@@ -446,18 +446,18 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
   bool xvec = true;
   for (int w = 0; w < plan->n_workers; ++w) xvec &= (uintptr_t)x_bufs_dev[w] % 16 == 0 && (uintptr_t)y_dev[w] % 16 == 0;
   const Corr kernel = choose_fwd(plan, xvec, (uintptr_t)w_dev % 16 == 0);
-  WeightJob job;
-  if (halo) {
-    if ((rc = weight_job(plan, kernel, false, w_dev, xvec, st, job))) return rc;
-    if ((rc = run_halo_with(plan, false, plan->tab_x, x_bufs_dev, &job, st))) return rc;  // x <- H x
-  } else {
-    if ((rc = plan_prepare_device(plan))) return rc;
-    for (int w = 0; w < plan->n_workers; ++w)
-      if (!x_bufs_dev[w] || (uintptr_t)x_bufs_dev[w] % esz) return set_error(DISTDL_ERR_NULL, "conv_fwd: x of worker %d null or misaligned", w);
-    if ((rc = weight_job(plan, kernel, false, w_dev, xvec, st, job))) return rc;
+  if ((rc = plan_prepare_device(plan))) return rc;
+  for (int w = 0; w < plan->n_workers; ++w) {
+    if (!x_bufs_dev[w]) return set_error(DISTDL_ERR_NULL, "conv_fwd: x of worker %d is null", w);
+    if ((uintptr_t)x_bufs_dev[w] % esz) return set_error(halo ? DISTDL_ERR_INVALID_ARG : DISTDL_ERR_NULL, "conv_fwd: x of worker %d is misaligned", w);
   }
+  // The pointer tables first: they refuse a call that has not been made on a stream that is being captured, before anything is
+  // enqueued or allocated (which would end the capture).
   if ((rc = plan->tab_x.upload((const void* const*)x_bufs_dev, plan->n_workers, st))) return rc;
   if ((rc = plan->tab_y.upload((const void* const*)y_dev, plan->n_workers, st))) return rc;
+  WeightJob job;
+  if ((rc = weight_job(plan, kernel, false, w_dev, xvec, st, job))) return rc;
+  if (halo && (rc = run_halo_with(plan, false, plan->tab_x, x_bufs_dev, &job, st))) return rc;  // x <- H x
   if ((rc = launch_weight_job(job, st))) return rc;  // (where H has no launch)
   if (kernel != Corr::kDirect) {
     switch (kernel) {

@@ -1,6 +1,8 @@
 """Each kernel of the convolution layer at shapes where the library picks it: the tiers that take what the split and gather
 kernels do not (strides beyond theirs here, tensors of 2 GiB and more in earnest), and the weight gradients of the 16-wide
 and of the bf16 tiles, which small layers do not reach.  Against fp64 on the device, by the bars of the other parity tests."""
+import gc
+
 import pytest
 import torch
 
@@ -154,6 +156,42 @@ def test_weight_gradient_in_place(onto, c_in, c_out):
     L.dx.fill_(5.0)
     for name, got, exact in list(zip(("y", "dx", "dw"), L.run(), want))[1:]:
         assert float((got.double() - exact).norm() / exact.norm()) < TOL[F32], name
+
+
+@pytest.mark.parametrize("c_in,c_out", [(20, 24), (19, 21), (12, 8)], ids=["split", "gather", "16 x 16"])
+@pytest.mark.parametrize("pad", [0, 1], ids=["no_halo", "halo"])
+def test_a_call_new_to_a_captured_stream_is_refused_and_leaves_the_capture_alone(pad, c_in, c_out):
+    require_gpu()
+    L = ConvLayer(2, c_in, c_out, (40, 41), 3, 1, p=pad)
+    L.run()                                        # (on another stream)
+    calls = [lambda: dd.distdl_conv_fwd(L.plan, [L.x], L.w, None, [L.y]),
+             lambda: dd.distdl_conv_bwd(L.plan, [L.x], L.w, [L.dy], [L.dx], L.dw, L.db, L.ws)]
+    side, graph, mark = torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.zeros(8, device="cuda")
+    torch.cuda.synchronize()
+    before = L.x.clone(), L.y.clone(), L.dx.clone()
+
+    def code_of(call):
+        try:
+            call()
+        except dd.DistdlError as error:
+            return error.code
+
+    gc.collect()                                   # (plans and graphs of other tests: none may be destroyed during the capture)
+    gc.disable()
+    try:
+        with torch.cuda.graph(graph, stream=side):
+            codes = [code_of(call) for call in calls]
+            mark.add_(1.0)
+    finally:
+        gc.enable()
+    assert codes == [dd.ERR_INVALID_ARG] * 2
+    L.y.fill_(7.0), L.dx.fill_(5.0)
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert bool((mark == 3.0).all()) and bool((L.y == 7.0).all()) and bool((L.dx == 5.0).all())
+    L.run()
+    assert all(torch.equal(a, b) for a, b in zip(before, (L.x, L.y, L.dx)))
 
 
 @pytest.mark.parametrize("c_in,c_out", [(20, 24), (19, 21), (28, 3)], ids=["split", "gather", "both"])
