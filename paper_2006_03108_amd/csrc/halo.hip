@@ -232,12 +232,15 @@ __global__ __launch_bounds__(kThreads) void halo_adj_kernel(const BlockRef* __re
 
 int plan_prepare_device(distdl_plan* p);
 
-__global__ __launch_bounds__(kThreads) void weight_job_kernel(WeightJob job) { run_weight_job(job, (int)blockIdx.x); }
+__global__ __launch_bounds__(kThreads) void weight_job_kernel(WeightJob job) {
+  run_weight_job(job, (int)(blockIdx.y * gridDim.x + blockIdx.x));
+}
 
 int launch_weight_job(const WeightJob& job, hipStream_t st) {
   if (job.kind == 0) return DISTDL_OK;
   ProfScope prof("conv_relayout_w", st);
-  hipLaunchKernelGGL(weight_job_kernel, dim3((unsigned)job.blocks), dim3(kThreads), 0, st, job);
+  // (a class a row: 64 of them may have more blocks than a launch has along one dimension)
+  hipLaunchKernelGGL(weight_job_kernel, dim3((unsigned)job.per_class, (unsigned)(job.blocks / job.per_class)), dim3(kThreads), 0, st, job);
   DISTDL_HIP_TRY(hipGetLastError());
   return DISTDL_OK;
 }

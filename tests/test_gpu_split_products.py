@@ -104,6 +104,16 @@ def test_data_gradient_of_very_many_channels(c_in, n, k, s, p, fold):
     assert _rel(got, want) < 5e-6 and float((got.double() - want).abs().max() / want.abs().max()) < 1e-5
 
 
+def test_weights_of_more_blocks_than_a_launch_has_along_one_dimension():
+    """64 classes of a stride, 2 GiB of weights: 16.9 million blocks of them.  Sums of 23232 products."""
+    require_gpu()
+    L = ConvLayer(1, 23232, 23232, (4, 4, 4), 1, 4)
+    assert dd.distdl_debug_conv_kernels(L.plan)[:2] == (3, 3) and dd.distdl_debug_conv_split(L.plan, True)[0] == 64
+    L.dx.fill_(5.0)
+    for name, got, want in list(zip(("y", "dx"), L.run(), L.exact())):
+        assert _rel(got, want) < 5e-6, name
+
+
 @pytest.mark.parametrize("small", ["x", "w", "dy"])
 @pytest.mark.parametrize("shape", LAYERS, ids=IDS)
 def test_conv_of_very_small_numbers(shape, small):
