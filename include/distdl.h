@@ -444,8 +444,9 @@ int distdl_debug_conv_kernels(const distdl_plan* plan, int aligned, int32_t out[
  * or not they are what runs: out[0] how many (0: they do not take it), out[1]
  * neighbouring cells along the last dimension that are one position's columns,
  * out[2] columns of a position, out[3] matrix products of a last chunk of at
- * most eight channels, which two taps share (0: there is no such chunk). */
-int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[4]);
+ * most eight channels, which two taps share (0: there is no such chunk),
+ * out[4] windows that the search for both directions tried. */
+int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5]);
 /* Runs the replacement policy of the cached device tables (see Conventions)
  * on a sequence of n calls without touching a device: call i arrives on
  * stream stream_id[i] with table contents table_id[i], during stream capture

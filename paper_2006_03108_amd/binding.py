@@ -371,8 +371,8 @@ def distdl_debug_conv_kernels(plan, aligned=True):
 
 
 def distdl_debug_conv_split(plan, backward=False):
-    """(launches, cells to a position, columns of a position, products that two taps share) of the split kernels."""
-    out = (C.c_int32 * 4)()
+    """(launches, cells to a position, columns of a position, products that two taps share, windows tried) of the split kernels."""
+    out = (C.c_int32 * 5)()
     _check(lib.distdl_debug_conv_split(plan.handle, int(backward), out))
     return tuple(out)
 

@@ -408,7 +408,7 @@ int distdl_debug_conv_kernels(const distdl_plan* plan, int aligned, int32_t out[
   return DISTDL_OK;
 }
 
-int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[4]) {
+int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5]) {
   if (!plan || !out) return set_error(DISTDL_ERR_NULL, "conv_split: null argument");
   if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_split: plan has no kernel");
   corr_split_shape(plan, backward != 0, out);

@@ -10,7 +10,7 @@ namespace distdl {
 bool corr_split_supported(const distdl_plan* p, bool backward);
 double corr_split_used(const distdl_plan* p, bool backward);  // part of its windows that are outputs
 double corr_split_us(const distdl_plan* p, bool backward);  // estimated time
-void corr_split_shape(const distdl_plan* p, bool backward, int32_t out[4]);  // see distdl_debug_conv_split
+void corr_split_shape(const distdl_plan* p, bool backward, int32_t out[5]);  // see distdl_debug_conv_split
 // The job that has to be done before either of the following.
 int split_weight_job(distdl_plan* p, bool backward, const float* w, hipStream_t st, WeightJob& job);
 int conv_fwd_split(distdl_plan* p, const float* w, const float* bias, hipStream_t st);

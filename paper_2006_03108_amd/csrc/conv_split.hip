@@ -595,12 +595,15 @@ double window_share(int cap, int tc, int nq1, int nq2) {  // fraction of the mul
 }
 
 bool one_octet(const SplitArgs& a) { return a.nfull == 0; }
-int pieces_of(const SplitArgs& a) { return (a.c.R * a.c.Cw * (one_octet(a) ? 1 : 2) + 255) / 256; }  // per thread
+int patch_cells(const SplitArgs& a, int tr, int tc) { return (tr + a.c.tapspan[1]) * (tc + a.c.tapspan[2]); }
+int pieces_of(const SplitArgs& a, int cells) { return (cells * (one_octet(a) ? 1 : 2) + 255) / 256; }  // per thread
 bool few_channels(const SplitArgs& a) { return a.fold > 1 || a.npairs > 0; }
 
 // The window of a launch: M-tiles per wave (0: none fits).  The window that wastes the fewest multiplied positions; of
-// equal ones the one with the smallest patch per position.
-int choose_window(const distdl_plan* p, SplitArgs& a, double& used) {
+// equal ones the one with the smallest patch per position.  Of widths that give as many rows and as many windows side by side
+// only the smallest is tried: the others share its positions and have larger patches (some 60 of 768 widths; a plan is searched
+// in its first call, and asks for every way to fold: 4 -> 4 channels, 5 x 5, 6 x 528 x 776, 2800 us with all widths).
+int choose_window(const distdl_plan* p, SplitArgs& a, double& used, int64_t& tried) {
   int nq1 = 1, nq2 = 1;
   for (const WorkerDev& wd : p->workers) {
     const PerWorker g = derive_of(wd, &a);
@@ -610,20 +613,25 @@ int choose_window(const distdl_plan* p, SplitArgs& a, double& used) {
   double best = -1;
   used = 0;
   int best_mt = 0, best_tc = 0;
-  for (int mt : {3, 2, 1})
-    for (int tc = 1; tc <= std::min(128 * mt, nq2); ++tc) {
-      set_window(a, mt, tc);
-      const int pa = pieces_of(a);
-      // Three M-tiles have one accumulator for large and small products, which rounds it six times for 16 channels, where fp32
-      // MFMAs do so eight times.  4 and 20 channels fill their last chunk by a quarter and would be further off than with those
-      // (3 x 3, 4 channels: 1.32e-7 and 1.10e-7; 8 channels 1.34 and 1.54, 36 channels 2.99 and 3.22); two M-tiles: 4.9e-8.
-      if (mt == 3 && (a.c.kc == 4 || a.c.kc == 20 || few_channels(a))) continue;
-      if (pa > 4 || split_lds_bytes(pa <= 3 && mt == 2 ? 3 : 4, a.c.ck) > 80 * 1024 || (mt == 3 && a.c.ck > 9)) continue;
+  for (int mt : {3, 2, 1}) {
+    // Three M-tiles have one accumulator for large and small products, which rounds it six times for 16 channels, where fp32
+    // MFMAs do so eight times.  4 and 20 channels fill their last chunk by a quarter and would be further off than with those
+    // (3 x 3, 4 channels: 1.32e-7 and 1.10e-7; 8 channels 1.34 and 1.54, 36 channels 2.99 and 3.22); two M-tiles: 4.9e-8.
+    if (mt == 3 && (a.c.kc == 4 || a.c.kc == 20 || a.c.ck > 9 || few_channels(a))) continue;
+    const int cap = 128 * mt, widest = std::min(cap, nq2);
+    for (int tc = 1, next; tc <= widest; tc = next) {
+      const int tr = cap / tc, across = (nq2 + tc - 1) / tc;
+      next = cap / tr + 1;  // fewer rows
+      if (across > 1) next = std::min(next, (nq2 + across - 2) / (across - 1));  // fewer windows side by side
+      ++tried;
+      const int cells = patch_cells(a, tr, tc), pa = pieces_of(a, cells);
+      if (pa > 4 || split_lds_bytes(pa <= 3 && mt == 2 ? 3 : 4, a.c.ck) > 80 * 1024) continue;
       // a tap costs a wave 6 mt MFMAs and 3 mt + 3 operand reads: fewer M-tiles pay relatively more for the weights
-      const double share = window_share(128 * mt, tc, nq1, nq2), patch = (double)(a.c.R * a.c.Cw) / (128 * mt);
+      const double share = window_share(cap, tc, nq1, nq2), patch = (double)cells / cap;
       const double score = share * (mt == 1 ? 0.75 : 1.0) / (1.0 + 0.05 * patch);
       if (score > best * 1.001) best = score, best_mt = mt, best_tc = tc, used = share;
     }
+  }
   if (best_mt) set_window(a, best_mt, best_tc);
   return best_mt;
 }
@@ -692,20 +700,21 @@ struct Launches {
 struct SplitPlan {
   Launches dir[2];
   bool ok[2] = {false, false};
+  int64_t tried = 0;         // windows
   SplitArgs* dev = nullptr;  // forward, then the classes
   ~SplitPlan() {
     if (dev) (void)hipFree(dev);
   }
 };
 
-bool plan_launch(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, Launch& l) {
+bool plan_launch(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, Launch& l, int64_t& tried) {
   bool ok;
   l.a = split_args(p, c, fold, octet, ok);
   SplitArgs& a = l.a;
   if (!ok) return false;
-  const int mt = choose_window(p, a, l.used);
+  const int mt = choose_window(p, a, l.used, tried);
   if (mt == 0) return false;
-  l.variant = (mt == 3 ? 3 : mt == 1 ? 0 : pieces_of(a) <= 3 ? 1 : 2) + (few_channels(a) ? 4 : 0);
+  l.variant = (mt == 3 ? 3 : mt == 1 ? 0 : pieces_of(a, a.c.R * a.c.Cw) <= 3 ? 1 : 2) + (few_channels(a) ? 4 : 0);
   l.pieces = weight_pieces(a);
   // Output planes per workgroup: a fixed set-up (its address tables, about 8 * 10^3 clocks) against the number of rounds
   // of 512 workgroups; at least four groups per worker where neighbouring planes share input planes (conv_mfma.hip).
@@ -723,8 +732,9 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, 
   const int64_t g0_max = shares ? std::max<int64_t>(1, planes_max / 4) : std::max<int64_t>(1, planes_max);
   double best = 1e300;
   a.c.g0 = 1;
-  for (int64_t g0 = 1; g0 <= g0_max; ++g0) {
-    const int64_t wgs = (planes_max + g0 - 1) / g0 * per_plane;
+  for (int64_t g0 = 1, next; g0 <= g0_max; g0 = next) {
+    const int64_t groups = (planes_max + g0 - 1) / g0, wgs = groups * per_plane;
+    next = groups > 1 ? (planes_max + groups - 2) / (groups - 1) : g0_max + 1;  // (more planes in as many groups take longer)
     const double cost = (double)((wgs + 511) / 512) * (8.0e3 + g0 * stage);
     if (cost < best * 0.97) best = cost, a.c.g0 = (int32_t)g0;
   }
@@ -847,7 +857,7 @@ SplitPlan* split_plan(const distdl_plan* p) {
       bool ok = true;
       auto add = [&](const CorrArgs& c) {
         l.v.emplace_back();
-        ok = ok && plan_launch(p, c, fold, octet, l.v.back());
+        ok = ok && plan_launch(p, c, fold, octet, l.v.back(), sp->tried);
         sum += l.v.back().clocks * l.v.back().share;
         l.used = std::min(l.used, l.v.back().used);
         most = std::max(most, l.v.back().clocks);
@@ -886,10 +896,11 @@ double corr_split_us(const distdl_plan* p, bool backward) {
   return 2.7 + split_plan(p)->dir[backward ? 1 : 0].clocks / 2240 + cells * (double)(p->n_ci + p->n_co) * 0.65e-6;
 }
 
-void corr_split_shape(const distdl_plan* p, bool backward, int32_t out[4]) {
+void corr_split_shape(const distdl_plan* p, bool backward, int32_t out[5]) {
   const Launches& d = split_plan(p)->dir[backward ? 1 : 0];
   out[0] = (int32_t)d.v.size();
   out[1] = out[2] = out[3] = 0;
+  out[4] = (int32_t)std::min<int64_t>(split_plan(p)->tried, INT32_MAX);
   for (const Launch& l : d.v) {
     out[1] = l.a.fold;
     out[2] = std::max(out[2], l.a.c.nc);

@@ -268,8 +268,18 @@ def test_columns_of_a_position_fit_16_bits(plan):
     one of the general form, with one cell to a position and no products that two taps share."""
     p = dd.distdl_plan_create(*plan, [1] * plan[0])
     for backward in (False, True):
-        _, fold, columns, pairs = dd.distdl_debug_conv_split(p, backward)
+        _, fold, columns, pairs, _ = dd.distdl_debug_conv_split(p, backward)
         assert columns <= 0xffff or (fold == 1 and pairs == 0)
+
+
+def test_search_of_launch_shapes_is_short():
+    """A plan is searched in its first call: of the hundreds of thousand windows of its folds, classes and M-tiles a few are tried."""
+    for plan, most in (((2, 6, 4, 4, [528, 776], [1, 1], [5, 5], [1, 1], [2, 2]), 2500), ((1, 2, 4, 2, [1170], [1], [7], [1], [3]), 2500),
+                       ((2, 8, 16, 16, [256, 256], [2, 2], [3, 3], [1, 1], [1, 1]), 400), ((2, 8, 3, 32, [224, 224], [2, 2], [7, 7], [2, 2], [3, 3]), 800),
+                       ((3, 1, 4, 4, [300] * 3, [2] * 3, [5] * 3, [2] * 3, [2] * 3), 3000)):
+        p = dd.distdl_plan_create(*plan, [1] * plan[0])
+        dd.distdl_debug_conv_kernels(p)
+        assert dd.distdl_debug_conv_split(p)[4] <= most, plan
 
 
 def test_table_cache_policy_never_rewrites_a_block_another_reader_may_hold():
