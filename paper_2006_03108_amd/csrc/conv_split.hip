@@ -309,21 +309,21 @@ __device__ __forceinline__ void corr_split(ArgsPtr a, const WorkerDev* __restric
   advance(sp);
   int on = pfirst / nq0, oq0 = pfirst % nq0;  // the output plane that is stored next
   const FastDiv div_nch{a->div_nch.mul, a->div_nch.sh1, a->div_nch.sh2, a->div_nch.d};
-  // (loads that a range check cuts off: with a branch for each of 16 values, and its wait, the pass over 44 -> 12 channels,
-  // 3 taps, 5 x 610884 spent 40 of 295 us on the bias)
-  const __amdgpu_buffer_rsrc_t rbias = rsrc_of(bias_in, bias_in ? so2 * 4u : 0u);
   auto store_plane = [&]() {
     float bias[4][4] = {};
     if (bias_in) {
+      // 16 loads of some channel of the layer, all in flight (with a branch and a wait for each of them the forward pass of 8 -> 44
+      // channels, 1^3, 9 x 53 x 29 x 52, took 86 us instead of 73).  Indexes and address are not kept from plane to plane: the
+      // registers are few, and what the scalar ones cannot hold is moved about in the loop over the taps.
       int first = ch0;
-      asm volatile("" : "+v"(first));  // (the indexes that follow are not kept in registers from plane to plane)
+      const float* b = bias_in;
+      asm volatile("" : "+v"(first), "+s"(b));
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int col = first + 8 * q + e;  // (beyond the channels: beyond the resource)
-          const uint32_t at = !FEW ? (uint32_t)col : col < c.nc ? (uint32_t)col - fd_div((uint32_t)col, div_nch) * (uint32_t)a->nch : kOob / 4u;
-          bias[q][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rbias, at * 4u, 0, 0));
+          const uint32_t col = (uint32_t)(first + 8 * q + e);  // (beyond the channels: any of them, it is not stored)
+          bias[q][e] = b[FEW ? col - fd_div(col, div_nch) * (uint32_t)a->nch : min(col, (uint32_t)c.nc - 1u)];
         }
     }
     const uint32_t obase = ((uint32_t)on * son + (uint32_t)(g.out_base[0] + g.os[0] * oq0) * so0) * 4u;
