@@ -245,19 +245,31 @@ enum class Corr { kDirect, kMfma, k16, kSplit, kAny };
 
 //
 // Among the three that make fp32 products of small layers, the one whose estimated time is the lowest, with an allowance for
-// what the estimates do not know (each is off by up to a quarter): the 16 x 16 kernel stays unless another one takes less than
-// three quarters of its time, the split one (where it takes the layer) unless the gather kernel takes less than two thirds,
-// or half if the split kernel's windows are full.  What decides: the split kernel's windows
+// what the estimates do not know (each is off by up to a quarter): the 16 x 16 kernel stays unless another one and its weights,
+// which make the launch before them 1 us longer (H) or 2 (the reduction of dw), take less than 0.85 of its time, the split one
+// (where it takes the layer) unless the gather kernel takes less than two thirds, or half if the split kernel's windows are full;
+// the data gradient of few cells in four classes of a stride or more does not start from the 16 x 16 kernel, which has a launch for
+// each (5 -> 10 channels, 5 x 5, stride 2, 15 x 84 x 79: 52 us, gather 27), but takes it only for less than three quarters of the
+// time.  What decides: the split kernel's windows
 // lie in one plane of one sample, so planes of a few cells leave them empty, where the gather kernel counts all positions
 // through; the gather kernel fetches a cell for each tap; the 16 x 16 kernel has a launch for each class of a stride.  us,
 // 16 x 16 / split / gather: forward 36 -> 24, 3^3, 6 x 13 x 13 x 11: - / 41 / 21; 8 -> 4, 7^3, stride 2, 13 x 11 x 16 x 15: 214 / 302 /
 // 53; 16 -> 4, 3 x 3, 2 x 808 x 1000: 91 / 67 / 181; data gradient 12 -> 1, 3 x 3, stride 2, 15 x 727 x 494: 148 / 77 / -.
+// Over 737 directions of 370 layers (1 to 64 channels, one to three dimensions, 100 to 20 M positions, every kernel and form
+// measured) the choice takes 0.89 times what it starts from takes, in the mean, nine directions more than 1.03 times; and 1.10
+// times the fastest.
 static Corr choose_small(const distdl_plan* p, bool backward, bool aligned, bool k16, bool split) {
-  Corr best = k16 ? Corr::k16 : Corr::kSplit;
-  double us = k16 ? corr16_us(p, backward) * 0.75 : corr_split_us(p, backward);
-  if (k16 && split)
+  const bool any = conv_any_supported(p);
+  const int64_t classes = (int64_t)p->stride[0] * p->stride[1] * p->stride[2];
+  const bool together = backward && classes >= 4 && p->n_workers * p->n_b * p->max_buf_cells <= (classes << 16) && (split || any);
+  const double ride = backward ? 2.0 : 1.0;
+  Corr best = k16 && !together ? Corr::k16 : split ? Corr::kSplit : Corr::kAny;
+  double us = best == Corr::k16 ? corr16_us(p, backward) * 0.85 - ride : best == Corr::kSplit ? corr_split_us(p, backward) : corr_any_us(p, backward, aligned);
+  if (k16 && together)
+    if (const double t = corr16_us(p, backward) - ride; t < us * 0.75) us = t, best = Corr::k16;
+  if (best == Corr::k16 && split)
     if (const double t = corr_split_us(p, backward); t < us) us = t, best = Corr::kSplit;
-  if (conv_any_supported(p) && corr_any_us(p, backward, aligned) < us * (best == Corr::k16 ? 1.0 : corr_split_used(p, backward) < 0.5 ? 0.66 : 0.5))
+  if (any && corr_any_us(p, backward, aligned) < us * (best != Corr::kSplit ? 1.0 : corr_split_used(p, backward) < 0.5 ? 0.66 : 0.5))
     best = Corr::kAny;
   return best;
 }

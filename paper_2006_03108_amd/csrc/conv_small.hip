@@ -970,7 +970,7 @@ double corr16_us(const distdl_plan* p, bool backward) {
   const int quads = kc <= 4 ? 1 : kc <= 8 ? 2 : 4;
   const double pos = (double)p->n_workers * p->n_b * (backward ? p->max_buf_cells : p->max_out_cells);
   const double mfma = 1.26e-6 * pos * (taps / launches) * quads, mem = 9.0e-6 * pos * std::max<int64_t>(p->n_ci + p->n_co, 8) / 8;
-  return launches * (p->ksize[0] > 1 ? 11.0 : 7.5) + mfma + mem + (p->ksize[0] > 1 ? 2.4 * std::cbrt(taps) : 0.0);
+  return launches * (p->ksize[0] > 1 ? 10.0 : 7.5) + mfma + mem + (p->ksize[0] > 1 ? 2.4 * std::cbrt(taps) : 0.0);
 }
 
 static size_t corr16_scratch_total(const distdl_plan* p) {

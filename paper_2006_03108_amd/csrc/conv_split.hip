@@ -618,6 +618,7 @@ int choose_window(const distdl_plan* p, SplitArgs& a, double& used, int64_t& tri
     // MFMAs do so eight times.  4 and 20 channels fill their last chunk by a quarter and would be further off than with those
     // (3 x 3, 4 channels: 1.32e-7 and 1.10e-7; 8 channels 1.34 and 1.54, 36 channels 2.99 and 3.22); two M-tiles: 4.9e-8.
     if (mt == 3 && (a.c.kc == 4 || a.c.kc == 20 || a.c.ck > 9 || few_channels(a))) continue;
+    if (best * 1.001 >= (mt == 1 ? 0.75 : 1.0) / 1.05) break;  // (a patch has a cell for every position)
     const int cap = 128 * mt, widest = std::min(cap, nq2);
     for (int tc = 1, next; tc <= widest; tc = next) {
       const int tr = cap / tc, across = (nq2 + tc - 1) / tc;
@@ -707,11 +708,23 @@ struct SplitPlan {
   }
 };
 
-bool plan_launch(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, Launch& l, int64_t& tried) {
+constexpr double kFewSetup = 20.0e3;  // clocks
+// `limit`: launches that take more clocks are not wanted
+bool plan_launch(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, double limit, Launch& l, int64_t& tried) {
   bool ok;
   l.a = split_args(p, c, fold, octet, ok);
   SplitArgs& a = l.a;
   if (!ok) return false;
+  const double setup = few_channels(a) ? kFewSetup : 12.0e3;
+  {  // set-up, and what the matrix cores take with no position idle
+    double positions = 0;
+    for (const WorkerDev& wd : p->workers) {
+      const PerWorker g = derive_of(wd, &a);
+      positions = std::max(positions, (double)p->n_b * g.nq[0] * g.nq[1] * g.nq[2]);
+    }
+    const double tiles = positions * p->n_workers * a.c.ntn / (128.0 * 256);
+    if (setup + tiles * a.c.nt[0] * (a.nfull * a.gbegin[a.ngroups] + a.npairs) * 6 * 32.0 * 1.4 > limit) return false;
+  }
   const int mt = choose_window(p, a, l.used, tried);
   if (mt == 0) return false;
   l.variant = (mt == 3 ? 3 : mt == 1 ? 0 : pieces_of(a, a.c.R * a.c.Cw) <= 3 ? 1 : 2) + (few_channels(a) ? 4 : 0);
@@ -742,7 +755,7 @@ bool plan_launch(const distdl_plan* p, const CorrArgs& c, int fold, bool octet, 
     const int64_t wgs = (planes_max + a.c.g0 - 1) / a.c.g0 * per_plane;
     const double one = (double)a.c.nt[0] * (mfmas * mt * 6 * 32.0 * 1.4 * (wgs > 256 ? 2 : 1) + ncc * a.ngroups * 2500.0);
     l.share = std::min(1.0, wgs / 512.0);
-    l.clocks = (double)((wgs + 511) / 512) * ((few_channels(a) ? 20.0e3 : 12.0e3) + a.c.g0 * one);
+    l.clocks = (double)((wgs + 511) / 512) * (setup + a.c.g0 * one);
   }
   int64_t tiles = 0;
   for (const WorkerDev& wd : p->workers) tiles = std::max(tiles, tiles_of_worker(derive_of(wd, &a), a.c));
@@ -843,34 +856,45 @@ SplitPlan* split_plan(const distdl_plan* p) {
   for (int dir = 0; dir < 2; ++dir) {
     if ((dir == 0 ? p->n_ci : p->n_co) % 4) continue;  // the tensor that is read comes in 16-byte pieces
     Launches& d = sp->dir[dir];
-    // The launches with `fold` cells to a position (data gradient: a class per residue of the dimensions that are not folded),
-    // of all folds those that are estimated to take the least time
-    double least = 1e300;
+    // The launches with `fold` cells to a position (data gradient: a class per residue of the dimensions that are not folded), of
+    // all folds those that are estimated to take the least time.  One cell to a position and no shared products unless another form
+    // takes less than 0.9 of that (737 directions of 370 layers: at 0.97 11 of them took 1.04 to 1.33 times as long as in the
+    // general form, 24 -> 4, 5^3, 8 x 45 x 44 x 46, forward 985 us and 741; at 0.9 three).  0.97 for the data gradient with a stride
+    // and cells of at most 96 bytes, which the classes of the general form write apart: 8 <- 48, 2 taps, stride 2, 7 x 392639, 172 us
+    // in two classes, 123 folded.
     const int nch = (int)(dir == 0 ? p->n_co : p->n_ci), kc = (int)(dir == 0 ? p->n_ci : p->n_co), s2 = dir == 0 ? 1 : p->stride[2];
+    const double margin = s2 > 1 && nch <= 24 ? 0.97 : 0.9;
+    double limit = 1e300;
     for (int fold = 1; fold <= 32; fold = fold < s2 ? s2 : fold + s2) {
       // (one class instead of several along dimension 2 pays for any columns; FEW keeps the bounds of a position's in 16 bits)
       if (fold > 1 && (int64_t)fold * nch > (fold == s2 ? kMaxFewColumns : 32)) break;
       for (const bool octet : {false, true}) {
-      if (octet && (kc % 16 == 0 || kc % 16 > 8 || nch > kMaxFewColumns)) continue;
-      Launches l;
-      double sum = 0, most = 0;  // (classes that fill the chip together only are one launch)
-      bool ok = true;
-      auto add = [&](const CorrArgs& c) {
-        l.v.emplace_back();
-        ok = ok && plan_launch(p, c, fold, octet, l.v.back(), sp->tried);
-        sum += l.v.back().clocks * l.v.back().share;
-        l.used = std::min(l.used, l.v.back().used);
-        most = std::max(most, l.v.back().clocks);
-      };
-      if (dir == 0) add(forward_args(p));
-      else
-        for (int p0 = 0; p0 < p->stride[0]; ++p0)
-          for (int p1 = 0; p1 < p->stride[1]; ++p1)
-            for (int p2 = 0; p2 < (fold == 1 ? p->stride[2] : 1); ++p2) {
-              const int par[3] = {p0, p1, p2};
-              add(class_args(p, par));
-            }
-      if (const double clocks = std::max(sum, most); ok && clocks < 0.97 * least) least = l.clocks = clocks, d = l;
+        if (octet && (kc % 16 == 0 || kc % 16 > 8 || nch > kMaxFewColumns)) continue;
+        if (kFewSetup >= limit) continue;  // (the general form comes first)
+        Launches l;
+        double sum = 0, most = 0;  // (classes that fill the chip together only are one launch)
+        bool ok = true;
+        auto add = [&](const CorrArgs& c) {
+          if (!ok) return;
+          l.v.emplace_back();
+          ok = plan_launch(p, c, fold, octet, limit, l.v.back(), sp->tried);
+          sum += l.v.back().clocks * l.v.back().share;
+          l.used = std::min(l.used, l.v.back().used);
+          most = std::max(most, l.v.back().clocks);
+          ok = ok && std::max(sum, most) < limit;
+        };
+        if (dir == 0) add(forward_args(p));
+        else
+          for (int p0 = 0; p0 < p->stride[0]; ++p0)
+            for (int p1 = 0; p1 < p->stride[1]; ++p1)
+              for (int p2 = 0; p2 < (fold == 1 ? p->stride[2] : 1); ++p2) {
+                const int par[3] = {p0, p1, p2};
+                add(class_args(p, par));
+              }
+        if (!ok) continue;
+        l.clocks = std::max(sum, most);
+        limit = l.clocks * (fold == 1 && !octet ? margin : 0.97);
+        d = std::move(l);
       }
     }
     if (d.v.empty()) continue;

@@ -92,12 +92,12 @@ def test_few_channels_with_a_weight_that_is_not_finite(shape):
     test_conv_with_a_weight_that_is_not_finite(shape)
 
 
-@pytest.mark.parametrize("c_in,n,k,s,p,fold", [(21736, 9, 8, 3, 3, 3), (24420, 9, 7, 2, 3, 2), (33000, 17, 7, 2, 3, 1)])
-def test_data_gradient_of_very_many_channels(c_in, n, k, s, p, fold):
-    """65208 and 48840 columns of a position, whose bounds still fit 16 bits, and a layer that has too many for that; sums of at
-    most 128 products."""
+@pytest.mark.parametrize("c_in,c_out,n,k,s,p,fold", [(21840, 20, 40, 8, 2, 3, 2), (33000, 8, 17, 7, 2, 3, 1)])
+def test_data_gradient_of_very_many_channels(c_in, c_out, n, k, s, p, fold):
+    """43680 columns of a position, whose bounds fit 16 bits, and a layer that would have too many for that; sums of at most 320
+    products."""
     require_gpu()
-    L = ConvLayer(1, c_in, 8, (n, n), k, s, p=p)
+    L = ConvLayer(1, c_in, c_out, (n, n), k, s, p=p)
     assert dd.distdl_debug_conv_kernels(L.plan)[1] == 3 and dd.distdl_debug_conv_split(L.plan, True)[1] == fold
     L.dx.fill_(5.0)
     got, want = L.run()[1], L.exact()[1]
