@@ -962,7 +962,9 @@ bool corr16_bwd_supported(const distdl_plan* p, bool vec) {
 }
 
 // A launch per class of the data gradient, and for kernels of several planes another for its weights; matrix instructions,
-// tensors, and the stages of a kernel of three dimensions.  Fitted to 83 directions; half of them are within a seventh of it.
+// tensors, and the stages of a kernel of three dimensions.  With one plane half of the shorter of the two hides behind the other
+// (16 -> 16, 3 x 3, 8 x 256 x 256, forward: 7.5 + 24 + 19 / 2 for 32 us).  Of its estimates of 87 such directions above 20 us half
+// are between 0.75 and 1.05 of the time.
 double corr16_us(const distdl_plan* p, bool backward) {
   const double launches = backward ? (double)p->stride[0] * p->stride[1] * p->stride[2] : 1.0;
   const double taps = (double)p->ksize[0] * p->ksize[1] * p->ksize[2];
@@ -970,7 +972,8 @@ double corr16_us(const distdl_plan* p, bool backward) {
   const int quads = kc <= 4 ? 1 : kc <= 8 ? 2 : 4;
   const double pos = (double)p->n_workers * p->n_b * (backward ? p->max_buf_cells : p->max_out_cells);
   const double mfma = 1.26e-6 * pos * (taps / launches) * quads, mem = 9.0e-6 * pos * std::max<int64_t>(p->n_ci + p->n_co, 8) / 8;
-  return launches * (p->ksize[0] > 1 ? 10.0 : 7.5) + mfma + mem + (p->ksize[0] > 1 ? 2.4 * std::cbrt(taps) : 0.0);
+  if (p->ksize[0] > 1) return launches * 10.0 + mfma + mem + 2.4 * std::cbrt(taps);
+  return launches * 7.5 + std::max(mfma, mem) + 0.5 * std::min(mfma, mem);
 }
 
 static size_t corr16_scratch_total(const distdl_plan* p) {

@@ -272,6 +272,13 @@ def test_columns_of_a_position_fit_16_bits(plan):
         assert columns <= 0xffff or (fold == 1 and pairs == 0)
 
 
+def test_kernels_of_wide_layers_of_16_channels():
+    """16 -> 16 channels, 3 x 3: 16 x 16 tiles (2) forward and in the data gradient, on one worker and on four."""
+    for n in (192, 256, 320):
+        for P in ([1, 1], [2, 2]):
+            assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(2, 8, 16, 16, [n, n], P, [3, 3], [1, 1], [1, 1], [1, 1]))[:2] == (2, 2)
+
+
 def test_search_of_launch_shapes_is_short():
     """A plan is searched in its first call: of the hundreds of thousand windows of its folds, classes and M-tiles a few are tried."""
     for plan, most in (((2, 6, 4, 4, [528, 776], [1, 1], [5, 5], [1, 1], [2, 2]), 2500), ((1, 2, 4, 2, [1170], [1], [7], [1], [3]), 2500),
