@@ -304,14 +304,14 @@ static Corr choose_data(const distdl_plan* p, bool aligned) { return choose_corr
 
 // The kernel of the weight gradient: of those that take the layer, the one whose estimated time (us) is the lowest:
 //   16 x 16 tiles: a set-up that grows with the taps of a plane, then 7 ps per tap and position (12 with several planes);
-//   gather: workgroups of 32-position stages, 2.4 us a stage while all compute units are busy, twice that with two
-//     column tiles (bf16: about half of that);
+//   gather: rounds of stages of 32 or 64 positions with tiles of 64 or 256 rows, the tensors, the partials (tiles_of in conv_any.hip);
 //   bf16 planes: 1.2 us a step of 32 positions or its matrix instructions;
 //   split planes: its own estimate counts matrix instructions; 1.6 times that was taken.
-// Measured on 80 layers of 1 to 64 channels, one to three dimensions, 10^3 to 10^6 positions, every kernel that takes each: the
-// choice is the fastest for 69 and within 8 % of it for 76; the others: 6 -> 16 (fp32) and 64 -> 64 (bf16), 2 x 60 x 64, 18 %,
-// bf16 32 -> 32, 2 x 256 x 256, 49 us for 38 and, 5 x 5 with stride 2, 43 for 25.  us, 16 x 16 / gather / split:
-// 16 -> 16 channels, 3 x 3, 8 x 256 x 256: 38.7 / 83 / 47; 64 -> 64, 3^3, 2 x 40 x 44 x 48: - / 384 / 240; 16 -> 4, one
+// Tiles of 64 rows have to be estimated at less than 0.9 of another kernel (0.8 of the 16 x 16 tiles, whose estimate is the surer):
+// where the two are that close, either may be the faster, and their rounds and tensors vary more from layer to layer.
+// Over 680 fp32 layers of 1 to 64 channels, one to three dimensions, 10^2 to 2 x 10^7 positions, every kernel that takes each: the choice
+// is within 3 % of the fastest in the mean (130 bf16 layers: 2 %).  us, 16 x 16 / gather / split: 16 -> 16 channels, 3 x 3, 8 x 256 x 256:
+// 38.7 / 83 / 47; 4 -> 4, 5 x 5, 8 x 660 x 860: - / 318 / 222; 64 -> 64, 3^3, 2 x 40 x 44 x 48: - / 384 / 240; 16 -> 4, one
 // dimension, 2 x 4000: - / 17 / 111; 32 -> 32, 5^3, stride 2, 256^3: - / 5030 / 3110.
 enum class Wgrad { k16, kSplit, kAny, kMfma, kDirect };
 
@@ -327,12 +327,12 @@ static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {
   if (wgrad16_supported(p, vec16))
     consider(Wgrad::k16, 6.0 + 0.8 * T + pos * p->ksize[0] * T * (p->ksize[0] > 1 ? 12e-6 : 7e-6));
   if (vec16 && wgrad_split_supported(p)) consider(Wgrad::kSplit, 1.6 * wgrad_split_us(p));
-  // (tiles of 64 rows: their estimate is less sure, and the 16 x 16 and bf16 tiles stay unless they take 0.75 and 0.7 of the time)
-  if (conv_any_supported(p) && !wgrad_any_few_rows(p)) consider(Wgrad::kAny, wgrad_any_us(p));
   const bool fits = wgrad_mfma_supported(p) && p->n_workers * wgrad_chunks(p) <= 65535;
   if (fits && bf16 && vec16) consider(Wgrad::kMfma, wgrad_taps_us(p));
-  if (conv_any_supported(p) && wgrad_any_few_rows(p))
-    consider(Wgrad::kAny, wgrad_any_us(p) / (best == Wgrad::k16 ? 0.75 : best == Wgrad::kMfma ? 0.7 : 1.0));
+  if (conv_any_supported(p)) {
+    const double room = best == Wgrad::kDirect || !wgrad_any_few_rows(p) ? 1.0 : best == Wgrad::k16 ? 0.8 : 0.9;
+    consider(Wgrad::kAny, wgrad_any_us(p) / room);
+  }
   if (best == Wgrad::kDirect && fits && (!bf16 || vec16)) best = Wgrad::kMfma;
   p->wgrad_kernel[vec16] = (int)best;
   return best;

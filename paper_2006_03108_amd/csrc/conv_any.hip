@@ -833,40 +833,57 @@ int conv_bwd_data_any(distdl_plan* p, const void* w, bool aligned, hipStream_t s
 }
 
 namespace {
-// The tiles of a worker's weight gradient: rows, columns / 32.
+// The tiles of a worker's weight gradient: rows, columns / 32; chunks of positions, about two workgroups per compute unit;
+// the stages of a compute unit, one after the other; estimated time of the launch and of what its partials add to R.
 struct WgradTiles {
-  int rows, NT;
-  int64_t count, stages;  // of a worker
+  int rows, NT, chunks;
+  bool alone;  // no second workgroup on a compute unit
+  int64_t serial;
+  double us;
 };
-WgradTiles wgrad_tiles(const distdl_plan* p) {
+// Rounds of 512 workgroups, the stages of one (shorter while it is alone on its compute unit), the tensors, the partials.  Fitted to
+// 680 fp32 and 130 bf16 layers with tiles of either kind (1 to 64 channels, 100 to 20 M positions): four fifths are within 15 %
+// (fp32) and 20 % of it.
+WgradTiles tiles_of(const distdl_plan* p, int rows) {
   const int64_t k = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci, pos = p->n_b * p->max_out_cells;
   WgradTiles t;
-  // 64 rows where two tiles of them are enough for one of 256, and a worker has more than one stage of positions (us, 64 and 256
-  // rows: 49 rows 8 and 19, 120 rows 14 and 21, 147 rows, three tiles, 33 and 24)
-  t.rows = pos > 32 && (k + 63) / 64 <= 2 * ((k + 255) / 256) ? 64 : 256;
-  t.NT = t.rows == 64 ? 1 : nt_of(p->n_co);
-  t.count = (k + t.rows - 1) / t.rows * ((p->n_co + 32 * t.NT - 1) / (32 * t.NT));
-  const int per = 8 * octets_of(t.rows);
-  t.stages = (pos + per - 1) / per;
+  t.rows = rows;
+  t.NT = rows == 64 ? 1 : nt_of(p->n_co);
+  const int per = 8 * octets_of(rows);
+  const int64_t tiles = (k + rows - 1) / rows * ((p->n_co + 32 * t.NT - 1) / (32 * t.NT)) * p->n_workers, stages = (pos + per - 1) / per;
+  // (a stage of a workgroup takes about 2 us, adding one more partial almost nothing: small layers one stage each)
+  const int64_t most = std::max<int64_t>(std::min<int64_t>(stages, 64), stages / 4);
+  t.chunks = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((512 + tiles - 1) / tiles, most), 512));
+  const bool bf16 = p->dtype == DISTDL_BF16, alone = t.alone = tiles * t.chunks <= 256;
+  const bool spread = p->n_ci == 1 && k > 32;  // a tap to every row: cells loaded one by one, from as many places as rows
+  const double stage = rows == 64 ? (spread ? 1.7 : 1.0) * (bf16 ? (alone ? 0.96 : 1.2) : (alone ? 1.8 : 2.4))
+                       : t.NT == 1 ? (bf16 ? (alone ? 0.61 : 1.06) : (alone ? 1.66 : 2.05)) : (bf16 ? 1.1 : (alone ? 2.85 : 2.57));
+  const double elements = (double)p->n_workers * p->n_b * ((double)p->max_buf_cells * p->n_ci + (double)p->max_out_cells * p->n_co);
+  t.serial = (tiles * t.chunks + 511) / 512 * ((stages + t.chunks - 1) / t.chunks);
+  t.us = (bf16 ? 6.2 : 5.3) + t.serial * stage + (rows == 64 ? 0.21e-6 : 0.33e-6) * elements + 0.045e-3 * k * p->n_co;
   return t;
+}
+// 64 rows where they are estimated to take no more time, 0.95 of it from the third tile on, and a worker has more than one stage of
+// positions (us, 64 and 256 rows: 49 rows 8 and 19, 120 rows 14 and 21, 147 rows, three tiles, 33 and 24; 125 rows and 37 columns,
+// which are two tiles of 32 or one of 64, 1 -> 37 channels, 5^3, stride 2, 12 x 73 x 92 x 57, 213 and 120)
+WgradTiles wgrad_tiles(const distdl_plan* p) {
+  const WgradTiles few = tiles_of(p, 64), many = tiles_of(p, 256);
+  const bool two = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci <= 128;
+  return p->n_b * p->max_out_cells > 32 && few.us < (two ? 1.05 : 0.95) * many.us ? few : many;
 }
 }  // namespace
 
-// position chunks per worker: about two workgroups per compute unit
-int wgrad_any_chunks(const distdl_plan* p) {
-  const WgradTiles t = wgrad_tiles(p);
-  const int64_t tiles = t.count * p->n_workers;
-  // (a stage of a workgroup takes about 1.2 us, adding one more partial almost nothing: small layers one stage each)
-  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>((512 + tiles - 1) / tiles, std::max<int64_t>(std::min<int64_t>(t.stages, 64), t.stages / 4)), 512));
-}
+int wgrad_any_chunks(const distdl_plan* p) { return wgrad_tiles(p).chunks; }
 
 bool wgrad_any_few_rows(const distdl_plan* p) { return wgrad_tiles(p).rows == 64; }
 
+// Against the other kernels.  256 rows by their stages alone, at the price that the factors of the others' estimates were found with:
+// with the estimate above the choice is no better (1.025 of the fastest for 1.026 over the fp32 layers, 1.018 for 1.016 over the bf16
+// ones), and layers whose split estimate is high for its time (44 -> 48, 5 x 5) would change kernels.
 double wgrad_any_us(const distdl_plan* p) {
   const WgradTiles t = wgrad_tiles(p);
-  const int64_t tiles = t.count * p->n_workers, chunks = wgrad_any_chunks(p);
-  const double stage = (tiles * chunks <= 256 ? 1.6 : 2.4) * t.NT * (p->dtype == DISTDL_BF16 ? 0.56 : 1.0);
-  return (t.rows == 64 ? 5.5 : 4.5) + (double)((tiles * chunks + 511) / 512) * ((t.stages + chunks - 1) / chunks) * stage;
+  if (t.rows == 64) return t.us;
+  return 4.5 + (double)t.serial * (t.alone ? 1.6 : 2.4) * t.NT * (p->dtype == DISTDL_BF16 ? 0.56 : 1.0);
 }
 
 int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st) {
@@ -881,8 +898,8 @@ int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st) {
     a.dil[d] = p->dilation[d];
     a.rows *= a.k[d];
   }
-  a.nchunks = wgrad_any_chunks(p);
   const WgradTiles t = wgrad_tiles(p);
+  a.nchunks = t.chunks;
   const int NT = t.NT;
   a.ntm = (a.rows + t.rows - 1) / t.rows;
   a.ntn = (a.co + 32 * NT - 1) / (32 * NT);

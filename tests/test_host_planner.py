@@ -279,6 +279,16 @@ def test_kernels_of_wide_layers_of_16_channels():
             assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(2, 8, 16, 16, [n, n], P, [3, 3], [1, 1], [1, 1], [1, 1]))[:2] == (2, 2)
 
 
+@pytest.mark.parametrize("plan,kernel", [((2, 8, 4, 4, [660, 860], [1, 2], [5, 5], [1, 1], [0, 0]), 3),
+                                         ((2, 1, 28, 60, [794, 1047], [1, 2], [2, 2], [1, 1], [1, 1], [2, 2]), 3),
+                                         ((2, 8, 16, 16, [256, 256], [2, 2], [3, 3], [1, 1], [1, 1]), 2),
+                                         ((1, 2, 16, 4, [4000], [1], [3], [1], [1]), 4)], ids=str)
+def test_weight_gradient_kernel_of_layers_far_from_the_lines(plan, kernel):
+    """Layers where one kernel of the weight gradient (2 16 x 16 tiles, 3 split products, 4 gather) is well ahead of the others."""
+    plan = plan if len(plan) == 10 else (*plan, [1] * plan[0])
+    assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*plan))[2] == kernel
+
+
 def test_search_of_launch_shapes_is_short():
     """A plan is searched in its first call: of the hundreds of thousand windows of its folds, classes and M-tiles a few are tried."""
     for plan, most in (((2, 6, 4, 4, [528, 776], [1, 1], [5, 5], [1, 1], [2, 2]), 2500), ((1, 2, 4, 2, [1170], [1], [7], [1], [3]), 2500),
