@@ -125,7 +125,10 @@ def _stream():
     """The current stream's handle.  Small passes are bound by the host: torch.cuda.current_stream() makes an object on every
     call (2.8 us, as long as a launch), the raw handle takes 0.3 us."""
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:  # (neither is part of torch's public interface: a build may lack them)
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 

@@ -329,3 +329,20 @@ def test_table_cache_policy_never_rewrites_a_block_another_reader_may_hold():
         cap += [0, 1]
     got = pol(streams + [0], tables + [999], cap + [0])
     assert sorted(set(got[:-1])) == list(range(64)) and got[-1] == dd.ERR_NOMEM
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_handle_without_torchs_private_functions(monkeypatch, missing):
+    """A torch build that lacks one of them: the handle comes from the stream object."""
+    from paper_2006_03108_amd import binding
+
+    class Stream:
+        cuda_stream = 7
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    for name, fn in (("_cuda_getCurrentRawStream", lambda device: 5 + device), ("_cuda_getDevice", lambda: 1)):
+        monkeypatch.setattr(torch._C, name, fn, raising=False)
+    assert binding._stream() == 6
+    monkeypatch.delattr(torch._C, missing)
+    assert binding._stream() == 7
