@@ -447,6 +447,10 @@ int distdl_debug_conv_kernels(const distdl_plan* plan, int aligned, int32_t out[
  * most eight channels, which two taps share (0: there is no such chunk),
  * out[4] windows that the search for both directions tried. */
 int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5]);
+/* Rows (taps x input channels) of a tile of the gather kernel's weight
+ * gradient, whether or not it is what runs: 64 or 256, 0 where it does not take
+ * the layer. */
+int distdl_debug_conv_wgrad_rows(const distdl_plan* plan, int32_t* rows);
 /* Runs the replacement policy of the cached device tables (see Conventions)
  * on a sequence of n calls without touching a device: call i arrives on
  * stream stream_id[i] with table contents table_id[i], during stream capture

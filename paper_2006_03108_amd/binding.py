@@ -71,6 +71,7 @@ _SIGS = {
     "distdl_debug_conv_path": [_vp, _p32],
     "distdl_debug_conv_kernels": [_vp, _i, _p32],
     "distdl_debug_conv_split": [_vp, _i, _p32],
+    "distdl_debug_conv_wgrad_rows": [_vp, _p32],
     "distdl_affine_plan_create": [C.POINTER(_vp), _i64, _i64, _i64, _i, _i, _i],
     "distdl_affine_plan_destroy": [_vp],
     "distdl_affine_fwd": [_vp, _pp, _pp, _pp, _pp, _vp],
@@ -378,6 +379,12 @@ def distdl_debug_conv_split(plan, backward=False):
     out = (C.c_int32 * 5)()
     _check(lib.distdl_debug_conv_split(plan.handle, int(backward), out))
     return tuple(out)
+
+
+def distdl_debug_conv_wgrad_rows(plan):
+    rows = C.c_int32()
+    _check(lib.distdl_debug_conv_wgrad_rows(plan.handle, C.byref(rows)))
+    return rows.value
 
 
 class AffinePlan:

@@ -427,6 +427,13 @@ int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5
   return DISTDL_OK;
 }
 
+int distdl_debug_conv_wgrad_rows(const distdl_plan* plan, int32_t* rows) {
+  if (!plan || !rows) return set_error(DISTDL_ERR_NULL, "conv_wgrad_rows: null argument");
+  if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_wgrad_rows: plan has no kernel");
+  *rows = !conv_any_supported(plan) ? 0 : wgrad_any_few_rows(plan) ? 64 : 256;
+  return DISTDL_OK;
+}
+
 int distdl_conv_local_fwd(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev, const void* bias_dev,
                           void* const y_dev[], void* stream) {
   return distdl::conv_fwd_core(plan, x_bufs_dev, w_dev, bias_dev, y_dev, (hipStream_t)stream, false);

@@ -83,19 +83,26 @@ def test_choice_among_fp32_kernels(case):
             assert float((got.double() - want).norm() / want.norm()) < TOL[F32], name
 
 
-# weight gradient, tiles of 64 rows (taps x input channels): 1, 63, 64, 65, 126 and 128 of them, 129 (256-row tiles), with one and
-# two column tiles, positions that end within an octet, a stage and a chunk, several workers' worth of chunks
-FEW_ROWS = [(1, 1, 4, (33,), 1, 1), (3, 7, 33, (61, 47), 3, 1), (1, 64, 5, (333,), 1, 1), (2, 13, 40, (129,), 5, 2), (2, 14, 3, (50, 41), 3, 1),
-            (5, 16, 32, (9, 10, 11), 2, 1), (2, 43, 64, (127,), 3, 1), (40, 3, 8, (90, 70), 3, 1)]
+# weight gradient of the gather kernel, 1, 63, 64, 65, 126, 128 and 129 rows (taps x input channels), with one and two column tiles,
+# positions that end within an octet, a stage and a chunk, several workers' worth of chunks; before each case the rows of its tiles in
+# fp32 and bf16 (0: the 16 x 16 kernel takes it)
+FEW_ROWS = [((0, 256), 1, 1, 4, (33,), 1, 1), ((64, 256), 1, 1, 20, (33,), 1, 1), ((64, 64), 1, 1, 20, (5001,), 1, 1),
+            ((64, 64), 3, 7, 33, (61, 47), 3, 1), ((64, 256), 1, 64, 5, (333,), 1, 1), ((64, 64), 1, 64, 5, (3333,), 1, 1),
+            ((64, 64), 2, 13, 40, (129,), 5, 2), ((64, 64), 2, 14, 3, (50, 41), 3, 1), ((64, 64), 5, 16, 32, (9, 10, 11), 2, 1),
+            ((64, 256), 2, 43, 64, (127,), 3, 1), ((64, 64), 2, 43, 64, (1271,), 3, 1), ((256, 256), 2, 43, 32, (127,), 3, 1),
+            ((64, 64), 40, 3, 8, (90, 70), 3, 1)]
 
 
 @pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "odd"])
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
-@pytest.mark.parametrize("case", FEW_ROWS, ids=[f"{c[1] * c[4] ** len(c[3])}rows{c[2]}cols" for c in FEW_ROWS])
+@pytest.mark.parametrize("case", FEW_ROWS, ids=[f"{c[2] * c[5] ** len(c[4])}rows{c[3]}cols{c[4][0]}" for c in FEW_ROWS])
 def test_weight_gradient_of_few_rows(case, dtype, offset):
     """fp32: a sum of n positions in chunks is off by at most sqrt(n / 16) roundings of 2^-24: 252 000 positions 7e-6."""
     require_gpu()
+    rows, case = case[0][dtype == BF16], case[1:]
     L = ConvLayer(*case, dtype, offset=offset)
+    assert dd.distdl_debug_conv_kernels(L.plan, offset == 0)[2] == (4 if rows else 2)
+    assert not rows or dd.distdl_debug_conv_wgrad_rows(L.plan) == rows
     L.dw.fill_(9.0), L.db.fill_(9.0)
     got, want = L.run()[2], L.exact()[2]
     assert float((got.double() - want).norm() / want.norm()) < TOL[dtype]
