@@ -304,13 +304,13 @@ static Corr choose_data(const distdl_plan* p, bool aligned) { return choose_corr
 
 // The kernel of the weight gradient: of those that take the layer, the one whose estimated time (us) is the lowest:
 //   16 x 16 tiles: a set-up that grows with the taps of a plane, then 7 ps per tap and position (12 with several planes);
-//   gather: rounds of stages of 32 or 64 positions with tiles of 64 or 256 rows, the tensors, the partials (tiles_of in conv_any.hip);
+//   gather: rounds of stages of 128 positions by 64 rows or 32 by 256, the tensors, the partials (tiles_of in conv_any.hip);
 //   bf16 planes: 1.2 us a step of 32 positions or its matrix instructions;
 //   split planes: its own estimate counts matrix instructions; 1.6 times that was taken.
-// Tiles of 64 rows have to be estimated at less than 0.9 of another kernel (0.8 of the 16 x 16 tiles, whose estimate is the surer):
-// where the two are that close, either may be the faster, and their rounds and tensors vary more from layer to layer.
+// Tiles of 64 rows (bf16: of layers of at most 128) have to be estimated at less than 0.9 of another kernel (0.8 of the 16 x 16
+// tiles, whose estimate is the surer): where the two are that close, either may be the faster, and their rounds and tensors vary more from layer to layer.
 // Over 680 fp32 layers of 1 to 64 channels, one to three dimensions, 10^2 to 2 x 10^7 positions, every kernel that takes each: the choice
-// is within 3 % of the fastest in the mean (130 bf16 layers: 2 %).  us, 16 x 16 / gather / split: 16 -> 16 channels, 3 x 3, 8 x 256 x 256:
+// is within 3 % of the fastest in the mean.  us, 16 x 16 / gather / split: 16 -> 16 channels, 3 x 3, 8 x 256 x 256:
 // 38.7 / 83 / 47; 4 -> 4, 5 x 5, 8 x 660 x 860: - / 318 / 222; 64 -> 64, 3^3, 2 x 40 x 44 x 48: - / 384 / 240; 16 -> 4, one
 // dimension, 2 x 4000: - / 17 / 111; 32 -> 32, 5^3, stride 2, 256^3: - / 5030 / 3110.
 enum class Wgrad { k16, kSplit, kAny, kMfma, kDirect };
@@ -330,7 +330,7 @@ static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {
   const bool fits = wgrad_mfma_supported(p) && p->n_workers * wgrad_chunks(p) <= 65535;
   if (fits && bf16 && vec16) consider(Wgrad::kMfma, wgrad_taps_us(p));
   if (conv_any_supported(p)) {
-    const double room = best == Wgrad::kDirect || !wgrad_any_few_rows(p) ? 1.0 : best == Wgrad::k16 ? 0.8 : 0.9;
+    const double room = best == Wgrad::kDirect || !wgrad_any_unsure(p) ? 1.0 : best == Wgrad::k16 ? 0.8 : 0.9;
     consider(Wgrad::kAny, wgrad_any_us(p) / room);
   }
   if (best == Wgrad::kDirect && fits && (!bf16 || vec16)) best = Wgrad::kMfma;
@@ -430,7 +430,7 @@ int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5
 int distdl_debug_conv_wgrad_rows(const distdl_plan* plan, int32_t* rows) {
   if (!plan || !rows) return set_error(DISTDL_ERR_NULL, "conv_wgrad_rows: null argument");
   if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_wgrad_rows: plan has no kernel");
-  *rows = !conv_any_supported(plan) ? 0 : wgrad_any_few_rows(plan) ? 64 : 256;
+  *rows = !conv_any_supported(plan) ? 0 : wgrad_any_rows(plan);
   return DISTDL_OK;
 }
 

@@ -13,7 +13,8 @@ int conv_fwd_any(distdl_plan* p, const void* w, const void* bias, bool aligned, 
 int conv_bwd_data_any(distdl_plan* p, const void* w, bool aligned, hipStream_t st);
 double corr_any_us(const distdl_plan* p, bool backward, bool aligned);  // estimated time
 int wgrad_any_chunks(const distdl_plan* p);
-bool wgrad_any_few_rows(const distdl_plan* p);  // tiles of 64 rows
+int wgrad_any_rows(const distdl_plan* p);       // of a tile: 64 or 256
+bool wgrad_any_unsure(const distdl_plan* p);    // the estimate is one of 64 rows alone
 double wgrad_any_us(const distdl_plan* p);  // estimated time
 int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st);
 

@@ -866,24 +866,31 @@ WgradTiles tiles_of(const distdl_plan* p, int rows) {
 // 64 rows where they are estimated to take no more time, 0.95 of it from the third tile on, and a worker has more than one stage of
 // positions (us, 64 and 256 rows: 49 rows 8 and 19, 120 rows 14 and 21, 147 rows, three tiles, 33 and 24; 125 rows and 37 columns,
 // which are two tiles of 32 or one of 64, 1 -> 37 channels, 5^3, stride 2, 12 x 73 x 92 x 57, 213 and 120)
+bool few_rows(const distdl_plan* p) { return (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci <= 128; }
 WgradTiles wgrad_tiles(const distdl_plan* p) {
   const WgradTiles few = tiles_of(p, 64), many = tiles_of(p, 256);
-  const bool two = (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci <= 128;
-  return p->n_b * p->max_out_cells > 32 && few.us < (two ? 1.05 : 0.95) * many.us ? few : many;
+  return p->n_b * p->max_out_cells > 32 && few.us < (few_rows(p) ? 1.05 : 0.95) * many.us ? few : many;
 }
 }  // namespace
 
 int wgrad_any_chunks(const distdl_plan* p) { return wgrad_tiles(p).chunks; }
 
-bool wgrad_any_few_rows(const distdl_plan* p) { return wgrad_tiles(p).rows == 64; }
+int wgrad_any_rows(const distdl_plan* p) { return wgrad_tiles(p).rows; }
+bool wgrad_any_unsure(const distdl_plan* p) { return wgrad_tiles(p).rows == 64 && (p->dtype != DISTDL_BF16 || few_rows(p)); }
 
 // Against the other kernels.  256 rows by their stages alone, at the price that the factors of the others' estimates were found with:
 // with the estimate above the choice is no better (1.025 of the fastest for 1.026 over the fp32 layers, 1.018 for 1.016 over the bf16
 // ones), and layers whose split estimate is high for its time (44 -> 48, 5 x 5) would change kernels.
+// bf16 layers of more than 128 rows are weighed against the planes of conv_mfma.hip in the same way whichever tiles they get, in one
+// and two dimensions also by the estimate of 64 rows: the planes' estimate is below their time there and above it with several kernel
+// planes (us, planes / gather, kernel and reduction: 32 -> 32, 3 x 3, 2 x 60 x 64, 20 / 13; 24 -> 48, 5 x 5, 7 x 16 x 31, 19 / 12; 48 ->
+// 8, 3^3, 3 x 55 x 30 x 33, 104 / 138).
 double wgrad_any_us(const distdl_plan* p) {
-  const WgradTiles t = wgrad_tiles(p);
-  if (t.rows == 64) return t.us;
-  return 4.5 + (double)t.serial * (t.alone ? 1.6 : 2.4) * t.NT * (p->dtype == DISTDL_BF16 ? 0.56 : 1.0);
+  const WgradTiles t = wgrad_tiles(p), many = tiles_of(p, 256);
+  const bool bf16 = p->dtype == DISTDL_BF16;
+  const double stages = 4.5 + (double)many.serial * (many.alone ? 1.6 : 2.4) * many.NT * (bf16 ? 0.56 : 1.0);
+  if (t.rows == 256) return stages;
+  return bf16 && !few_rows(p) ? (p->ksize[0] > 1 ? stages : std::min(stages, t.us)) : t.us;
 }
 
 int conv_wgrad_any(distdl_plan* p, float* partial, hipStream_t st) {

@@ -289,6 +289,18 @@ def test_weight_gradient_kernel_of_layers_far_from_the_lines(plan, kernel):
     assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*plan))[2] == kernel
 
 
+@pytest.mark.parametrize("plan,kernels", [((2, 2, 32, 32, [60, 64], [1, 1], [3, 3], [1, 1], [1, 1]), (4, 4, 4)),
+                                          ((2, 5, 24, 32, [35, 382], [2, 1], [3, 3], [1, 1], [0, 0]), (4, 1, 4)),
+                                          ((2, 6, 24, 24, [10, 288], [1, 1], [5, 5], [2, 2], [2, 2]), (1, 4, 4)),
+                                          ((2, 7, 24, 48, [16, 31], [1, 1], [5, 5], [1, 1], [0, 0]), (1, 1, 4)),
+                                          ((2, 6, 8, 32, [77, 486], [1, 1], [3, 3], [2, 2], [0, 0]), (4, 4, 4)),
+                                          ((3, 3, 48, 8, [55, 30, 33], [1, 2, 1], [3, 3, 3], [1, 1, 1], [1, 1, 1]), (1, 1, 1))], ids=str)
+def test_bf16_kernels_of_layers_that_the_other_choice_slows_down(plan, kernels):
+    """bf16 layers that take 1.1 to 2.4 times as long with the weight gradient on the other kernel (1 tiles, 4 gather), which the other
+    two directions may follow."""
+    assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*plan, [1] * plan[0], torch.bfloat16)) == kernels
+
+
 def test_search_of_launch_shapes_is_short():
     """A plan is searched in its first call: of the hundreds of thousand windows of its folds, classes and M-tiles a few are tried."""
     for plan, most in (((2, 6, 4, 4, [528, 776], [1, 1], [5, 5], [1, 1], [2, 2]), 2500), ((1, 2, 4, 2, [1170], [1], [7], [1], [3]), 2500),
