@@ -350,6 +350,19 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
   }
 }
 
+// Where the reduction of dw lays out the weights of the data gradient, that comes last, and the launch after it waits for the write-back
+// of dx; the weight gradient, which would hide that where it is long for the tensors it reads (the gather kernel with several taps),
+// comes before.  For a large dx, far larger than dy, that costs more than the launch for the weights, 5 us.  us of a forward and
+// backward pass with the data gradient last / first: 5 x 610884, 44 -> 12, 3 taps, 1052 / 1023 (5 x 305442 547 / 518, 5 x 200000 366 /
+// 359, 5 x 100000 196 / 200); 60 -> 4, 5 x 400000, 732 / 700; but one tap, whose weight gradient reads what the forward pass left in
+// the caches, 722 / 750; 32 -> 16, 5 x 610884, 626 / 628; 12 -> 44 847 / 881; weight gradients of the split kernel 44 -> 12, 2^3,
+// 3 x 100 x 101 x 102, 1585 / 1607; 24 -> 20, 3 x 3, 8 x 512^2, 638 / 643; 32 -> 32, 5^3, stride 2, 256^3, 10250 / 10280.
+static bool write_back_hides(const distdl_plan* p, Corr kernel, Wgrad wgrad) {
+  if (kernel != Corr::kSplit || wgrad != Wgrad::kAny) return false;
+  const double x = 4.0 * p->n_workers * p->n_b * p->max_buf_cells * p->n_ci, dy = 4.0 * p->n_workers * p->n_b * p->max_out_cells * p->n_co;
+  return x > 160e6 && x >= 2.5 * dy && wgrad_any_us(p) > 1.5 * (x + dy) / 4.6e6;
+}
+
 // The weights of a launch of `kernel` that a launch before it can lay out.
 static int weight_job(distdl_plan* p, Corr kernel, bool backward, const void* w, bool aligned, hipStream_t st, WeightJob& job) {
   if (kernel == Corr::kSplit) return split_weight_job(p, backward, (const float*)w, st, job);
@@ -561,7 +574,8 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   };
   // Where R's launch can lay out its weights it comes after that; elsewhere before, so that H* does not follow the kernel that
   // wrote what it reads (32 -> 32 channels, 5^3, stride 2, 256^3, bf16: H* 119 -> 105 us, the pass 0.8 % less).
-  // (also where dw or db lies on the weights or on dy, which the data gradient reads)
+  // (also where dw or db lies on the weights or on dy, which the data gradient reads, and where the weight gradient is the better one
+  // to follow the data gradient)
   auto on = [](const void* a, size_t na, const void* b, size_t nb) {
     return a && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
   };
@@ -572,7 +586,7 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
     const size_t y_bytes = (size_t)plan->n_b * wd.out[0] * wd.out[1] * wd.out[2] * b_bytes;
     in_place |= on(dw_dev, w_bytes, dy_dev[w], y_bytes) || on(dbias_dev, b_bytes, dy_dev[w], y_bytes);
   }
-  const bool data_last = job.kind != 0 && !in_place;
+  const bool data_last = job.kind != 0 && !in_place && !write_back_hides(plan, kernel, wgrad);
   if (!data_last) {
     if ((rc = launch_weight_job(job, st))) return rc;
     job.kind = 0;

@@ -249,3 +249,25 @@ def test_affine_of_more_segments_than_a_product_takes(P_fo, P_fi, dtype):
     rows = [torch.cat([t.double() for t in dW[i * P_fi:(i + 1) * P_fi]], 1) for i in range(P_fo)]
     for got, want in ((whole(y), x @ W.t() + b), (whole(dx), dy @ W), (torch.cat(rows, 0), dy.t() @ x), (whole(db), dy.sum(0))):
         assert float((got - want).norm() / want.norm()) < TOL[dtype]
+
+
+@pytest.mark.parametrize("c_in,c_out,cells,k,first", [(44, 12, 1000000, 3, True), (44, 12, 300000, 3, False), (44, 12, 1000000, 1, False),
+                                                      (32, 16, 1200000, 3, False)], ids=["large", "small", "one tap", "32-16"])
+def test_order_of_the_adjoint(c_in, c_out, cells, k, first):
+    """A large dx that a weight gradient of several taps can hide: the data gradient runs first, its weights laid out by a launch of
+    their own; elsewhere last, its weights laid out by the reduction of dw.  The same results (sums of at most 132 products, and of a
+    million in the weight gradient)."""
+    require_gpu()
+    L = ConvLayer(1, c_in, c_out, (cells,), k, 1)
+    assert dd.distdl_debug_conv_kernels(L.plan)[1:] == (3, 4)
+    L.dx.fill_(5.0)
+    dd.distdl_conv_fwd(L.plan, [L.x], L.w, None, [L.y])
+    dd.distdl_profile_enable(True)
+    try:
+        dd.distdl_conv_bwd(L.plan, [L.x], L.w, [L.dy], [L.dx], L.dw, L.db, L.ws)
+        launches = dd.distdl_profile_report()
+    finally:
+        dd.distdl_profile_enable(False)
+    assert ("conv_relayout_w" in launches) == first
+    for name, got, want in zip(("y", "dx", "dw"), (L.y, L.dx[L.bulk], L.dw), L.exact()):
+        assert float((got.double() - want).norm() / want.norm()) < TOL[F32], name
