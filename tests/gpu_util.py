@@ -48,6 +48,14 @@ def assert_close(got, want, tol, what=""):
     assert l2 <= tol and mx <= tol, f"{what}: rel l2 {l2:.3e}, rel max {mx:.3e} > {tol:.1e}"
 
 
+def split_forms(plan):
+    """Forward and data gradient of aligned tensors: (cells to a position, products that two taps share) where the split kernels
+    run, else None."""
+    kernels = dd.distdl_debug_conv_kernels(plan)
+    forms = [dd.distdl_debug_conv_split(plan, backward) for backward in (False, True)]
+    return tuple((f[1], f[3]) if k == 3 else None for k, f in zip(kernels, forms))
+
+
 class ConvLayer:
     """A convolution layer on one worker, its tensors padded and channels-last, N(0, 1) values; exact() gives the same in
     fp64 on the device, tap by tap.  offset: the tensors start that many elements into an allocation."""

@@ -9,7 +9,7 @@ import synthetic_inputs as syn
 from oracle import geometry as geo
 from oracle import layers
 from oracle import primitives as prim
-from tests.gpu_util import assert_close, from_cl, oracle_partition, require_gpu, to_cl, w_to_dev
+from tests.gpu_util import assert_close, from_cl, oracle_partition, require_gpu, split_forms, to_cl, w_to_dev
 
 pytestmark = pytest.mark.gpu
 TOL32, TOL16 = 1e-5, 2e-2
@@ -218,6 +218,50 @@ def test_conv_small_channel_random_layers(cfg):
     y_want = layers.dist_conv_forward(o_bufs, case["w"], case["bias"], part, cfg["stride"], cfg["dilation"])
     dx_want, dw_want, db_want = layers.dist_conv_adjoint(o_bufs, case["w"], prim.scatter_out(case["dy"], part), part,
                                                          cfg["stride"], cfg["dilation"], True)
+    for wk in range(part.n_workers):
+        assert_close(from_cl(y[wk]), y_want[wk], TOL32, f"y worker {wk}")
+        assert_close(from_cl(dx_bufs[wk]), dx_want[wk], TOL32, f"dx worker {wk}")
+    assert_close(dw.cpu().numpy(), dw_want, TOL32, "dw")
+    assert_close(db.cpu().numpy(), db_want, TOL32, "db")
+
+
+# The split kernels' forms for few channels: (cells to a position, products that two taps share) of the forward pass and of the
+# data gradient, None on another kernel; batch, channels, extents, workers, kernel, stride, padding, dilation.  Up to eight cells
+# to a position, rows that end within one, and workers whose first output lies one or two cells off a multiple of the
+# stride (positions of the data gradient that begin before the buffer).
+CONV_FOLDED = [
+    ((None, (3, 2)), 1, 8, 20, (29, 31, 16), (2, 2, 3), 4, 3, 0, 1),
+    ((None, (2, 2)), 1, 16, 8, (21, 42, 39), (1, 3, 3), 3, 2, 1, 1),
+    ((None, (4, 2)), 4, 2, 20, (227, 219), (1, 3), 5, 4, 1, 1),
+    ((None, (4, 2)), 1, 3, 24, (20, 18, 31), (1, 1, 3), 5, 4, 1, 1),
+    ((None, (4, 2)), 1, 7, 8, (24, 18, 17), (1, 1, 3), 4, 4, 3, 2),
+    ((None, (4, 0)), 8, 3, 32, (224, 224), (2, 2), 7, 2, 3, 1),
+    ((None, (5, 22)), 3, 2, 24, (16, 36, 21), (3, 2, 1), 4, 1, 2, 2),
+    ((None, (6, 6)), 5, 2, 20, (19, 21, 46), (2, 1, 1), 7, 3, 3, 1),
+    ((None, (6, 0)), 6, 3, 40, (30, 45, 47), (1, 1, 1), 2, 2, 0, 1),
+    ((None, (7, 0)), 5, 2, 16, (25, 45, 26), (3, 1, 1), 4, 1, 3, 2),
+    ((None, (8, 28)), 5, 3, 36, (30, 46, 29), (1, 2, 1), 4, 1, 1, 2),
+    (((4, 12), None), 5, 20, 3, (41, 25, 29), (1, 2, 1), 3, 1, 2, 2),
+    (((4, 0), None), 4, 12, 1, (32, 38, 40), (1, 1, 2), 4, 1, 1, 1),
+    (((5, 0), None), 5, 28, 2, (236, 234), (2, 2), 3, 1, 1, 2),
+]
+
+
+@pytest.mark.parametrize("case", CONV_FOLDED, ids=lambda c: f"c{c[2]}-{c[3]}k{c[6]}s{c[7]}P{'x'.join(map(str, c[5]))}")
+def test_conv_few_channels_several_cells_to_a_position(case):
+    """fp32 sums of at most 4000 products; every cell of dx, whose buffers hold 5 before the call."""
+    require_gpu()
+    forms, n_b, c_in, c_out, shape, P, *ksdp = case
+    D = len(shape)
+    k, s, pad, dil = (tuple([v] * D) for v in (ksdp[0], ksdp[1], ksdp[2], ksdp[3]))
+    cfg = dict(D=D, n_b=n_b, c_in=c_in, c_out=c_out, in_shape=shape, P=P, ksize=k, stride=s, padding=pad, dilation=dil, seed=5)
+    assert split_forms(_plan(cfg, torch.float32)) == forms
+    part = oracle_partition(cfg)
+    case = syn.conv_case(cfg, part.global_out_shape())
+    x_bufs, y, dx_bufs, dw, db = _run_conv(cfg, part, case, True)
+    o_bufs = prim.scatter_bulk(case["x"].astype(np.float64), part, fill=np.nan)
+    y_want = layers.dist_conv_forward(o_bufs, case["w"], case["bias"], part, s, dil)
+    dx_want, dw_want, db_want = layers.dist_conv_adjoint(o_bufs, case["w"], prim.scatter_out(case["dy"], part), part, s, dil, True)
     for wk in range(part.n_workers):
         assert_close(from_cl(y[wk]), y_want[wk], TOL32, f"y worker {wk}")
         assert_close(from_cl(dx_bufs[wk]), dx_want[wk], TOL32, f"dx worker {wk}")

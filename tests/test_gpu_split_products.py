@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import paper_2006_03108_amd as dd
-from tests.gpu_util import ConvLayer, require_gpu
+from tests.gpu_util import ConvLayer, require_gpu, split_forms
 
 pytestmark = pytest.mark.gpu
 
@@ -62,11 +62,15 @@ def test_conv_with_a_weight_that_is_not_finite(shape):
         assert bool(plain.any()) and _rel(got[plain], want[plain]) < 5e-6, name
 
 
-# few channels: several cells to a position (two, three, four; rows that end within one; strides; classes that are launches of
-# their own), pairs of taps to a product, both; one to three dimensions
+# few channels: several cells to a position (two, three; rows that end within one; strides; classes that are launches of
+# their own), pairs of taps to a product, both; one to three dimensions.  (More cells, and several workers: the layers of
+# few channels in test_gpu_layers.py.)
 FEW = [(6, 8, 4, (28, 30, 45), 3, 2), (2, 3, 32, (120, 130), 7, 2), (3, 3, 40, (2000,), 7, 2), (2, 8, 36, (90, 100), 5, 2),
        (2, 40, 3, (260, 250), 3, 1), (1, 6, 20, (25, 30, 26), 4, 3), (4, 20, 8, (300, 280), 3, 1)]
 FEW_IDS = ["x".join(map(str, v[3])) + f"c{v[1]}-{v[2]}s{v[5]}" for v in FEW]
+# (cells to a position, products that two taps share) forward and in the data gradient, None on another kernel; by dilation
+FEW_FORMS = {1: [(None, (2, 2)), (None, (1, 0)), (None, (1, 0)), (None, (1, 0)), ((3, 8), None), (None, (1, 0)), ((3, 8), (1, 0))],
+             2: [(None, (2, 5)), (None, (1, 0)), (None, (1, 0)), ((1, 0), (1, 0)), ((1, 0), None), (None, (1, 0)), ((3, 11), (1, 0))]}
 
 
 @pytest.mark.parametrize("dilation", [1, 2])
@@ -75,6 +79,7 @@ def test_layers_of_few_channels(shape, dilation):
     """Sums of at most 2000 products: 5e-6, as above."""
     require_gpu()
     L = ConvLayer(*shape, dil=dilation)
+    assert split_forms(L.plan) == FEW_FORMS[dilation][FEW.index(shape)]
     L.y.fill_(7.0), L.dx.fill_(5.0)
     for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
         assert _rel(got, want) < 5e-6, name
