@@ -270,7 +270,7 @@ def test_conv_few_channels_several_cells_to_a_position(case):
 
 
 CONV_BF16 = [
-    # tiled kernels (channel counts that are multiples of 4), 3-D strided, 2-D, dilated; then the gather kernels
+    # 3-D strided, 2-D and dilated layers of a few thousand positions, on the gather kernels but for the forward passes
     ("cfg5", dict(in_shape=(24, 22, 40), P=(2, 2, 1), c_in=32, c_out=32), True),
     ("cfg5u", dict(in_shape=(21, 23, 22), P=(2, 2, 2), c_in=32, c_out=32), False),
     ("cfg2", dict(in_shape=(64, 64), n_b=2), True),
@@ -279,15 +279,30 @@ CONV_BF16 = [
     ("cfg2", dict(in_shape=(19, 23), n_b=3, c_in=3, c_out=5, P=(2, 3), ksize=(3, 4), stride=(2, 1), padding=(1, 2),
                   dilation=(1, 2)), True),
     ("cfg1", dict(), True),
-    # 24 input channels: the last 16-channel chunk of the bf16 matrix-core kernel is half empty
+    # 24 input channels: the last 16-channel chunk of the bf16 matrix-core kernel (forward) is half empty
     ("cfg5", dict(in_shape=(14, 18, 36), P=(2, 1, 2), c_in=24, c_out=8, ksize=(3, 3, 3), stride=(1, 2, 1),
                   padding=(1, 1, 1)), True),
-    # several channel tiles, the second output tile half full: db sums of the weight-gradient kernel per tile
+    # tiles: several channel tiles, the second output tile half full, db sums of the weight-gradient kernel per tile
     ("cfg2", dict(in_shape=(40, 70), n_b=2, c_in=64, c_out=48, ksize=(3, 3), padding=(1, 1), P=(2, 2)), True),
-    # 20 output channels: not a multiple of 8, so the forward kernel stores 8-byte channel quads instead of 16-byte
-    # pieces, and the data gradient (20 contraction channels) widens bf16 to fp32 while staging
+    # gather: 20 output channels, not a multiple of 8, strided
     ("cfg2", dict(in_shape=(37, 45), n_b=2, c_in=40, c_out=20, ksize=(3, 3), padding=(1, 1), stride=(2, 1), P=(2, 2)), True),
+    # tiles with 4 mod 8 channels in the contraction (60 and 44 forward; 60, 28 and 36 in the data gradient: bf16 is widened to fp32
+    # while it is staged) and in the outputs (quads of 8 bytes instead of pieces of 16), with and without a stride
+    ("cfg1", dict(n_b=1, in_shape=(26,), c_in=60, c_out=60, P=(3,), ksize=(2,), stride=(1,), padding=(0,)), True),
+    ("cfg1", dict(n_b=2, in_shape=(31,), c_in=60, c_out=36, P=(3,), ksize=(2,), stride=(2,), padding=(0,)), True),
+    ("cfg1", dict(n_b=1, in_shape=(69,), c_in=44, c_out=28, P=(2,), ksize=(4,), stride=(1,), padding=(0,)), False),
+    ("cfg5", dict(n_b=1, in_shape=(37, 72, 68), c_in=4, c_out=36, P=(1, 3, 3), ksize=(4, 4, 4), stride=(2, 2, 2), padding=(1, 1, 1),
+                  dilation=(2, 2, 2)), True),
+    ("cfg5", dict(n_b=1, in_shape=(90, 30, 30), c_in=8, c_out=28, P=(3, 1, 1), ksize=(5, 5, 5), stride=(2, 2, 2), padding=(1, 1, 1),
+                  dilation=(2, 2, 2)), True),
+    # tiles in all three directions on several workers, strided in two and three dimensions and not
+    ("cfg2", dict(n_b=1, in_shape=(94, 213), c_in=56, c_out=8, P=(1, 2), ksize=(5, 5), stride=(2, 2), padding=(2, 2)), True),
+    ("cfg2", dict(n_b=1, in_shape=(32, 749), c_in=40, c_out=16, P=(3, 2), ksize=(3, 3), stride=(1, 1), padding=(1, 1)), False),
+    ("cfg5", dict(n_b=1, in_shape=(34, 34, 36), c_in=32, c_out=8, P=(2, 2, 1)), True),
 ]
+# forward pass, data gradient and weight gradient of each: 1 tiles, 4 gather
+CONV_BF16_KERNELS = [(1, 4, 4), (1, 4, 4), (4, 4, 4), (4, 4, 4), (4, 4, 4), (4, 4, 4), (1, 4, 4), (1, 1, 1), (4, 4, 4),
+                     (1, 1, 4), (1, 4, 4), (4, 1, 4), (4, 1, 4), (1, 1, 4), (1, 1, 1), (1, 1, 1), (1, 1, 1)]
 
 
 @pytest.mark.parametrize("name,override,use_bias", CONV_BF16, ids=[f"{n}-{i}" for i, (n, _, _) in enumerate(CONV_BF16)])
@@ -301,6 +316,7 @@ def test_conv_bf16_fwd_bwd_against_partitioned_oracle(name, override, use_bias):
     bias = syn.to_bf16_values(case["bias"] + 0.25) if use_bias else None
     plan = dd.distdl_plan_create(cfg["D"], cfg["n_b"], cfg["c_in"], cfg["c_out"], cfg["in_shape"], cfg["P"],
                                  cfg["ksize"], cfg["stride"], cfg["padding"], cfg["dilation"], bf)
+    assert dd.distdl_debug_conv_kernels(plan) == CONV_BF16_KERNELS[CONV_BF16.index((name, override, use_bias))]
     x_bufs = [to_cl(b, bf) for b in prim.scatter_bulk(x, part, fill=np.float32(3.0))]
     gw = torch.from_numpy(np.ascontiguousarray(w)).to(bf).cuda()
     gb = torch.from_numpy(np.ascontiguousarray(bias)).to(bf).cuda() if use_bias else None
