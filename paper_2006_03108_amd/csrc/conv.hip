@@ -309,6 +309,9 @@ static Corr choose_data(const distdl_plan* p, bool aligned) { return choose_corr
 //   split planes: its own estimate counts matrix instructions; 1.6 times that was taken.
 // Tiles of 64 rows (bf16: of layers of at most 128) have to be estimated at less than 0.9 of another kernel (0.8 of the 16 x 16
 // tiles, whose estimate is the surer): where the two are that close, either may be the faster, and their rounds and tensors vary more from layer to layer.
+// A layer of at most 64 rows, one tile that reads x once, leaves the split kernel up to 1.1 of its estimate: most such layers
+// have one tap, and the split kernel's estimate leaves out the tensors (us, split / gather: 56 -> 4, one tap, 8 x 884 x 841: 451 / 280,
+// 12 -> 36, 7 x 449 x 365: 124 / 109; a forward pass and an adjoint of 56 -> 36, 7 x 66 x 57 x 74: 818 / 762).
 // Over 680 fp32 layers of 1 to 64 channels, one to three dimensions, 10^2 to 2 x 10^7 positions, every kernel that takes each: the choice
 // is within 3 % of the fastest in the mean.  us, 16 x 16 / gather / split: 16 -> 16 channels, 3 x 3, 8 x 256 x 256:
 // 38.7 / 83 / 47; 4 -> 4, 5 x 5, 8 x 660 x 860: - / 318 / 222; 64 -> 64, 3^3, 2 x 40 x 44 x 48: - / 384 / 240; 16 -> 4, one
@@ -330,7 +333,8 @@ static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {
   const bool fits = wgrad_mfma_supported(p) && p->n_workers * wgrad_chunks(p) <= 65535;
   if (fits && bf16 && vec16) consider(Wgrad::kMfma, wgrad_taps_us(p));
   if (conv_any_supported(p)) {
-    const double room = best == Wgrad::kDirect || !wgrad_any_unsure(p) ? 1.0 : best == Wgrad::k16 ? 0.8 : 0.9;
+    const bool one_tile = p->ksize[0] * T * (double)p->n_ci <= 64;
+    const double room = best == Wgrad::kDirect || !wgrad_any_unsure(p) ? 1.0 : best == Wgrad::k16 ? 0.8 : best == Wgrad::kSplit && one_tile ? 1.1 : 0.9;
     consider(Wgrad::kAny, wgrad_any_us(p) / room);
   }
   if (best == Wgrad::kDirect && fits && (!bf16 || vec16)) best = Wgrad::kMfma;

@@ -282,7 +282,10 @@ def test_kernels_of_wide_layers_of_16_channels():
 @pytest.mark.parametrize("plan,kernel", [((2, 8, 4, 4, [660, 860], [1, 2], [5, 5], [1, 1], [0, 0]), 3),
                                          ((2, 1, 28, 60, [794, 1047], [1, 2], [2, 2], [1, 1], [1, 1], [2, 2]), 3),
                                          ((2, 8, 16, 16, [256, 256], [2, 2], [3, 3], [1, 1], [1, 1]), 2),
-                                         ((1, 2, 16, 4, [4000], [1], [3], [1], [1]), 4)], ids=str)
+                                         ((1, 2, 16, 4, [4000], [1], [3], [1], [1]), 4),
+                                         ((3, 7, 56, 36, [66, 57, 74], [2, 2, 2], [1, 1, 1], [1, 1, 1], [0, 0, 0]), 4),
+                                         ((3, 7, 40, 40, [33, 60, 52], [2, 2, 2], [1, 1, 1], [1, 1, 1], [0, 0, 0]), 4),
+                                         ((2, 9, 4, 40, [235, 43], [1, 2], [3, 3], [1, 1], [0, 0]), 4)], ids=str)
 def test_weight_gradient_kernel_of_layers_far_from_the_lines(plan, kernel):
     """Layers where one kernel of the weight gradient (2 16 x 16 tiles, 3 split products, 4 gather) is well ahead of the others."""
     plan = plan if len(plan) == 10 else (*plan, [1] * plan[0])
