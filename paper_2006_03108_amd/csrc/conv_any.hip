@@ -879,8 +879,8 @@ int wgrad_any_rows(const distdl_plan* p) { return wgrad_tiles(p).rows; }
 bool wgrad_any_unsure(const distdl_plan* p) { return wgrad_tiles(p).rows == 64 && (p->dtype != DISTDL_BF16 || few_rows(p)); }
 
 // Against the other kernels.  256 rows by their stages alone, at the price that the factors of the others' estimates were found with:
-// with the estimate above the choice is no better (1.025 of the fastest for 1.026 over the fp32 layers, 1.018 for 1.016 over the bf16
-// ones), and layers whose split estimate is high for its time (44 -> 48, 5 x 5) would change kernels.
+// with the estimate above the choice is no better (1.025 of the fastest for 1.026 over the fp32 layers), and layers whose split
+// estimate is high for its time (44 -> 48, 5 x 5) would change kernels.
 // bf16 layers of more than 128 rows are weighed against the planes of conv_mfma.hip in the same way whichever tiles they get, in one
 // and two dimensions also by the estimate of 64 rows: the planes' estimate is below their time there and above it with several kernel
 // planes (us, planes / gather, kernel and reduction: 32 -> 32, 3 x 3, 2 x 60 x 64, 20 / 13; 24 -> 48, 5 x 5, 7 x 16 x 31, 19 / 12; 48 ->
