@@ -248,9 +248,10 @@ enum class Corr { kDirect, kMfma, k16, kSplit, kAny };
 // what the estimates do not know (each is off by up to a quarter): the 16 x 16 kernel stays unless another one and its weights,
 // which make the launch before them 1 us longer (H) or 2 (the reduction of dw), take less than 0.85 of its time, the split one
 // (where it takes the layer) unless the gather kernel takes less than two thirds, or half if the split kernel's windows are full;
-// the data gradient of few cells in four classes of a stride or more does not start from the 16 x 16 kernel, which has a launch for
-// each (5 -> 10 channels, 5 x 5, stride 2, 15 x 84 x 79: 52 us, gather 27), but takes it only for less than three quarters of the
-// time.  What decides: the split kernel's windows
+// the data gradient of few cells in two classes of a stride or more does not start from the 16 x 16 kernel, which has a launch for
+// each (5 -> 10 channels, 5 x 5, stride 2, 15 x 84 x 79: 52 us, gather 27; 8 -> 9, 7 x 7, stride 1 x 2, 2 x 22 x 134: 34 and 17; of 70
+// layers of two classes the choice is within 3 % of the fastest in the mean, 17 % when they start from it), but takes it only for
+// less than three quarters of the time.  What decides: the split kernel's windows
 // lie in one plane of one sample, so planes of a few cells leave them empty, where the gather kernel counts all positions
 // through; the gather kernel fetches a cell for each tap; the 16 x 16 kernel has a launch for each class of a stride.  us,
 // 16 x 16 / split / gather: forward 36 -> 24, 3^3, 6 x 13 x 13 x 11: - / 41 / 21; 8 -> 4, 7^3, stride 2, 13 x 11 x 16 x 15: 214 / 302 /
@@ -261,7 +262,7 @@ enum class Corr { kDirect, kMfma, k16, kSplit, kAny };
 static Corr choose_small(const distdl_plan* p, bool backward, bool aligned, bool k16, bool split) {
   const bool any = conv_any_supported(p);
   const int64_t classes = (int64_t)p->stride[0] * p->stride[1] * p->stride[2];
-  const bool together = backward && classes >= 4 && p->n_workers * p->n_b * p->max_buf_cells <= (classes << 16) && (split || any);
+  const bool together = backward && classes >= 2 && p->n_workers * p->n_b * p->max_buf_cells <= (classes << 16) && (split || any);
   const double ride = backward ? 2.0 : 1.0;
   Corr best = k16 && !together ? Corr::k16 : split ? Corr::kSplit : Corr::kAny;
   double us = best == Corr::k16 ? corr16_us(p, backward) * 0.85 - ride : best == Corr::kSplit ? corr_split_us(p, backward) : corr_any_us(p, backward, aligned);
