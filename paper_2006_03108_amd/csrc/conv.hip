@@ -246,7 +246,9 @@ enum class Corr { kDirect, kMfma, k16, kSplit, kAny };
 //
 // Among the three that make fp32 products of small layers, the one whose estimated time is the lowest, with an allowance for
 // what the estimates do not know (each is off by up to a quarter): the 16 x 16 kernel stays unless another one and its weights,
-// which make the launch before them 1 us longer (H) or 2 (the reduction of dw), take less than 0.85 of its time, the split one
+// which make the launch before them 1 us longer (H) or 2 (the reduction of dw), take less than 0.85 of its time (all of it where
+// its classes write every second cell of the last dimension: 8 -> 16 channels, 7 taps, stride 2, 9 x 33496, 70 us with an adjoint on
+// it and 61 with the split kernel's), the split one
 // (where it takes the layer) unless the gather kernel takes less than two thirds, or half if the split kernel's windows are full;
 // the data gradient of few cells in two classes of a stride or more does not start from the 16 x 16 kernel, which has a launch for
 // each (5 -> 10 channels, 5 x 5, stride 2, 15 x 84 x 79: 52 us, gather 27; 8 -> 9, 7 x 7, stride 1 x 2, 2 x 22 x 134: 34 and 17; of 70
@@ -263,9 +265,10 @@ static Corr choose_small(const distdl_plan* p, bool backward, bool aligned, bool
   const bool any = conv_any_supported(p);
   const int64_t classes = (int64_t)p->stride[0] * p->stride[1] * p->stride[2];
   const bool together = backward && classes >= 2 && p->n_workers * p->n_b * p->max_buf_cells <= (classes << 16) && (split || any);
+  const bool apart = backward && p->stride[2] > 1;  // each class writes every stride[2]th cell, of at most 64 bytes
   const double ride = backward ? 2.0 : 1.0;
   Corr best = k16 && !together ? Corr::k16 : split ? Corr::kSplit : Corr::kAny;
-  double us = best == Corr::k16 ? corr16_us(p, backward) * 0.85 - ride : best == Corr::kSplit ? corr_split_us(p, backward) : corr_any_us(p, backward, aligned);
+  double us = best == Corr::k16 ? corr16_us(p, backward) * (apart ? 1.0 : 0.85) - ride : best == Corr::kSplit ? corr_split_us(p, backward) : corr_any_us(p, backward, aligned);
   if (k16 && together)
     if (const double t = corr16_us(p, backward) - ride; t < us * 0.75) us = t, best = Corr::k16;
   if (best == Corr::k16 && split)

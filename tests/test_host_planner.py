@@ -292,11 +292,12 @@ def test_weight_gradient_kernel_of_layers_far_from_the_lines(plan, kernel):
     assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*plan))[2] == kernel
 
 
-@pytest.mark.parametrize("plan", [(1, 8, 8, 11, [30], [2], [7], [2], [0]), (2, 2, 8, 9, [22, 134], [1, 1], [7, 7], [1, 2], [3, 3]),
-                                  (2, 15, 5, 10, [84, 79], [1, 1], [5, 5], [2, 2], [2, 2])], ids=str)
-def test_data_gradient_of_few_cells_in_classes_of_a_stride(plan):
-    """One launch of the gather kernel (4) in place of one of the 16 x 16 tiles for each class."""
-    assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*plan, [1] * plan[0]))[1] == 4
+@pytest.mark.parametrize("plan,kernel", [((1, 8, 8, 11, [30], [2], [7], [2], [0]), 4), ((2, 2, 8, 9, [22, 134], [1, 1], [7, 7], [1, 2], [3, 3]), 4),
+                                         ((2, 15, 5, 10, [84, 79], [1, 1], [5, 5], [2, 2], [2, 2]), 4),
+                                         ((1, 9, 8, 16, [33496], [1], [7], [2], [3]), 3), ((1, 10, 1, 4, [36990], [1], [1], [2], [0]), 3)], ids=str)
+def test_data_gradient_in_classes_of_a_stride(plan, kernel):
+    """One launch of the gather kernel (4) or of folded cells (3) in place of one of the 16 x 16 tiles for each class."""
+    assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*plan, [1] * plan[0]))[1] == kernel
 
 
 @pytest.mark.parametrize("plan,kernels", [((2, 2, 32, 32, [60, 64], [1, 1], [3, 3], [1, 1], [1, 1]), (4, 4, 4)),
