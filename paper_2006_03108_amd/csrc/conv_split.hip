@@ -861,16 +861,19 @@ SplitPlan* split_plan(const distdl_plan* p) {
     // takes less than 0.9 of that (737 directions of 370 layers: at 0.97 11 of them took 1.04 to 1.33 times as long as in the
     // general form, 24 -> 4, 5^3, 8 x 45 x 44 x 46, forward 985 us and 741; at 0.9 three).  0.97 for the data gradient with a stride
     // and cells of at most 96 bytes, which the classes of the general form write apart: 8 <- 48, 2 taps, stride 2, 7 x 392639, 172 us
-    // in two classes, 123 folded.
+    // in two classes, 123 folded.  0.65 for a forward pass of three dimensions whose cells are folded under a dilation: the cells of a
+    // position share few offsets, and of eight such layers with estimates between that and 0.9 five took up to 1.3 times as long, 1.10 in
+    // the mean (32 -> 10, 5^3, dilation 2, 4 x 29 x 29 x 38, estimate 0.76: 299 us and 231; 48 -> 5, 7 x 24 x 46 x 47, 0.79: 563 and 653).
     const int nch = (int)(dir == 0 ? p->n_co : p->n_ci), kc = (int)(dir == 0 ? p->n_ci : p->n_co), s2 = dir == 0 ? 1 : p->stride[2];
     const double margin = s2 > 1 && nch <= 24 ? 0.97 : 0.9;
-    double limit = 1e300;
+    double limit = 1e300, general = 1e300;
     for (int fold = 1; fold <= 32; fold = fold < s2 ? s2 : fold + s2) {
       // (one class instead of several along dimension 2 pays for any columns; FEW keeps the bounds of a position's in 16 bits)
       if (fold > 1 && (int64_t)fold * nch > (fold == s2 ? kMaxFewColumns : 32)) break;
       for (const bool octet : {false, true}) {
         if (octet && (kc % 16 == 0 || kc % 16 > 8 || nch > kMaxFewColumns)) continue;
         if (kFewSetup >= limit) continue;  // (the general form comes first)
+        const bool spread = dir == 0 && fold > 1 && !octet && p->dilation[2] > 1 && p->ksize[0] > 1;
         Launches l;
         double sum = 0, most = 0;  // (classes that fill the chip together only are one launch)
         bool ok = true;
@@ -881,7 +884,7 @@ SplitPlan* split_plan(const distdl_plan* p) {
           sum += l.v.back().clocks * l.v.back().share;
           l.used = std::min(l.used, l.v.back().used);
           most = std::max(most, l.v.back().clocks);
-          ok = ok && std::max(sum, most) < limit;
+          ok = ok && std::max(sum, most) < (spread ? std::min(limit, 0.65 * general) : limit);
         };
         if (dir == 0) add(forward_args(p));
         else
@@ -893,6 +896,7 @@ SplitPlan* split_plan(const distdl_plan* p) {
               }
         if (!ok) continue;
         l.clocks = std::max(sum, most);
+        if (fold == 1 && !octet) general = l.clocks;
         limit = l.clocks * (fold == 1 && !octet ? margin : 0.97);
         d = std::move(l);
       }

@@ -312,6 +312,15 @@ def test_bf16_kernels_of_layers_that_the_other_choice_slows_down(plan, kernels):
     assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*plan, [1] * plan[0], torch.bfloat16)) == kernels
 
 
+def test_cells_under_a_dilation_are_folded_only_where_it_pays():
+    """Forward passes of three dimensions, dilation 2: in the general form (one cell to a position) where folding took 1.2 to 1.3 times as
+    long, folded where it takes 0.9."""
+    plan = lambda n_b, c_in, c_out, n: dd.distdl_plan_create(3, n_b, c_in, c_out, n, [1] * 3, [5] * 3, [1] * 3, [4] * 3, [2] * 3)
+    assert dd.distdl_debug_conv_split(plan(4, 48, 8, [30, 41, 36]))[1] == 1
+    assert dd.distdl_debug_conv_split(plan(4, 32, 10, [29, 29, 38]))[1] == 1
+    assert dd.distdl_debug_conv_split(plan(8, 56, 3, [27, 32, 55]))[1] > 1
+
+
 def test_search_of_launch_shapes_is_short():
     """A plan is searched in its first call: of the hundreds of thousand windows of its folds, classes and M-tiles a few are tried."""
     for plan, most in (((2, 6, 4, 4, [528, 776], [1, 1], [5, 5], [1, 1], [2, 2]), 2500), ((1, 2, 4, 2, [1170], [1], [7], [1], [3]), 2500),
