@@ -865,11 +865,13 @@ WgradTiles tiles_of(const distdl_plan* p, int rows) {
 }
 // 64 rows where they are estimated to take no more time, 0.95 of it from the third tile on, and a worker has more than one stage of
 // positions (us, 64 and 256 rows: 49 rows 8 and 19, 120 rows 14 and 21, 147 rows, three tiles, 33 and 24; 125 rows and 37 columns,
-// which are two tiles of 32 or one of 64, 1 -> 37 channels, 5^3, stride 2, 12 x 73 x 92 x 57, 213 and 120)
+// which are two tiles of 32 or one of 64, 1 -> 37 channels, 5^3, stride 2, 12 x 73 x 92 x 57, 213 and 120; bf16 layers of several kernel
+// planes 0.9: 52 -> 3, 3^3, stride 2, 8 x 77 x 50 x 22, estimates 82 and 87, 93 and 73)
 bool few_rows(const distdl_plan* p) { return (int64_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci <= 128; }
 WgradTiles wgrad_tiles(const distdl_plan* p) {
   const WgradTiles few = tiles_of(p, 64), many = tiles_of(p, 256);
-  return p->n_b * p->max_out_cells > 32 && few.us < (few_rows(p) ? 1.05 : 0.95) * many.us ? few : many;
+  const bool planes = p->dtype == DISTDL_BF16 && p->ksize[0] > 1;
+  return p->n_b * p->max_out_cells > 32 && few.us < (few_rows(p) ? 1.05 : planes ? 0.9 : 0.95) * many.us ? few : many;
 }
 }  // namespace
 

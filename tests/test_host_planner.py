@@ -312,6 +312,12 @@ def test_bf16_kernels_of_layers_that_the_other_choice_slows_down(plan, kernels):
     assert dd.distdl_debug_conv_kernels(dd.distdl_plan_create(*plan, [1] * plan[0], torch.bfloat16)) == kernels
 
 
+def test_bf16_weight_gradient_of_wide_rows_and_several_planes():
+    """1404 rows, 3 columns: tiles of 256 rows (73 us, of 64 rows 93)."""
+    plan = dd.distdl_plan_create(3, 8, 52, 3, [77, 50, 22], [1] * 3, [3] * 3, [2] * 3, [1] * 3, [1] * 3, torch.bfloat16)
+    assert dd.distdl_debug_conv_wgrad_rows(plan) == 256
+
+
 def test_cells_under_a_dilation_are_folded_only_where_it_pays():
     """Forward passes of three dimensions, dilation 2: in the general form (one cell to a position) where folding took 1.2 to 1.3 times as
     long, folded where it takes 0.9."""
