@@ -362,13 +362,14 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
 // of dx; the weight gradient, which would hide that where it is long for the tensors it reads (the gather kernel with several taps),
 // comes before.  For a large dx, far larger than dy, that costs more than the launch for the weights, 5 us.  us of a forward and
 // backward pass with the data gradient last / first: 5 x 610884, 44 -> 12, 3 taps, 1052 / 1023 (5 x 305442 547 / 518, 5 x 200000 366 /
-// 359, 5 x 100000 196 / 200); 60 -> 4, 5 x 400000, 732 / 700; but one tap, whose weight gradient reads what the forward pass left in
+// 359, 5 x 100000 196 / 200; the forward pass of 60 -> 20, 5 taps, stride 2, 8 x 81385, after an adjoint of the one order 84 and of the
+// other 74); 60 -> 4, 5 x 400000, 732 / 700; but one tap, whose weight gradient reads what the forward pass left in
 // the caches, 722 / 750; 32 -> 16, 5 x 610884, 626 / 628; 12 -> 44 847 / 881; weight gradients of the split kernel 44 -> 12, 2^3,
 // 3 x 100 x 101 x 102, 1585 / 1607; 24 -> 20, 3 x 3, 8 x 512^2, 638 / 643; 32 -> 32, 5^3, stride 2, 256^3, 10250 / 10280.
 static bool write_back_hides(const distdl_plan* p, Corr kernel, Wgrad wgrad) {
   if (kernel != Corr::kSplit || wgrad != Wgrad::kAny) return false;
   const double x = 4.0 * p->n_workers * p->n_b * p->max_buf_cells * p->n_ci, dy = 4.0 * p->n_workers * p->n_b * p->max_out_cells * p->n_co;
-  return x > 160e6 && x >= 2.5 * dy && wgrad_any_us(p) > 1.5 * (x + dy) / 4.6e6;
+  return x > 130e6 && x >= 2.5 * dy && wgrad_any_us(p) > 1.5 * (x + dy) / 4.6e6;
 }
 
 // The weights of a launch of `kernel` that a launch before it can lay out.
