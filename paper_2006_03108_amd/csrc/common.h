@@ -7,7 +7,9 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
 #include <memory>
+#include <utility>
 #include <vector>
 
 #include "distdl.h"
@@ -152,6 +154,22 @@ struct HaloTaskDev {
   FastDiv div_row, div_e1, div_e0;
 };
 
+// Host tables on their way to one block of device memory, each at a multiple of 16 bytes.
+struct HostTables {
+  std::vector<char> bytes;
+  std::vector<std::pair<void**, size_t>> places;  // where the device address of a table goes, its offset
+  template <class T>
+  void add(const std::vector<T>& v, T** out) {
+    *out = nullptr;
+    if (v.empty()) return;
+    const size_t at = bytes.size(), n = v.size() * sizeof(T);
+    bytes.resize(at + (n + 15) / 16 * 16);
+    std::memcpy(bytes.data() + at, v.data(), n);
+    places.emplace_back((void**)out, at);
+  }
+  int to_device(char** block);
+};
+
 struct TaskTable {
   std::vector<BoxTask> tasks;
   std::vector<BoxSrc> srcs;
@@ -276,7 +294,8 @@ struct distdl_plan {
   int n_workers = 0;
   int device = 0;
 
-  // device-side tables
+  // device-side tables, in one block
+  char* d_tables = nullptr;
   distdl::WorkerDev* d_workers = nullptr;
   std::vector<distdl::WorkerDev> workers;
   distdl::TaskTable fwd16, fwd1, adj16, adj1;  // 16-byte-vector and scalar variants
