@@ -447,6 +447,11 @@ int distdl_debug_conv_kernels(const distdl_plan* plan, int aligned, int32_t out[
  * most eight channels, which two taps share (0: there is no such chunk),
  * out[4] windows that the search for both directions tried. */
 int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5]);
+/* Whether distdl_conv_fwd (out[0]) and distdl_conv_bwd (out[1]) of this plan
+ * run in one launch (distdl_conv_bwd: one or two) instead of as the kernels
+ * that distdl_debug_conv_kernels names with H and H* around them; the
+ * distdl_conv_local_* calls always run those.  aligned: as there. */
+int distdl_debug_conv_fused(const distdl_plan* plan, int aligned, int32_t out[2]);
 /* Rows (taps x input channels) of a tile of the gather kernel's weight
  * gradient, whether or not it is what runs: 64 or 256, 0 where it does not take
  * the layer. */

@@ -71,6 +71,7 @@ _SIGS = {
     "distdl_debug_conv_path": [_vp, _p32],
     "distdl_debug_conv_kernels": [_vp, _i, _p32],
     "distdl_debug_conv_split": [_vp, _i, _p32],
+    "distdl_debug_conv_fused": [_vp, _i, _p32],
     "distdl_debug_conv_wgrad_rows": [_vp, _p32],
     "distdl_affine_plan_create": [C.POINTER(_vp), _i64, _i64, _i64, _i, _i, _i],
     "distdl_affine_plan_destroy": [_vp],
@@ -379,6 +380,13 @@ def distdl_debug_conv_split(plan, backward=False):
     out = (C.c_int32 * 5)()
     _check(lib.distdl_debug_conv_split(plan.handle, int(backward), out))
     return tuple(out)
+
+
+def distdl_debug_conv_fused(plan, aligned=True):
+    """Whether the forward pass and the adjoint run in one launch, H and H* among them."""
+    out = (C.c_int32 * 2)()
+    _check(lib.distdl_debug_conv_fused(plan.handle, int(aligned), out))
+    return bool(out[0]), bool(out[1])
 
 
 def distdl_debug_conv_wgrad_rows(plan):

@@ -306,10 +306,12 @@ struct distdl_plan {
   float* d_wt = nullptr;     // the block of the call at hand (ensure_wscratch)
   distdl::FastDiv* d_pooldiv = nullptr;  // per worker: division by buf[1], buf[2], out[1], out[2] (pooling kernels)
   mutable int maxpool_ok = -1;    // 1 once every max-pool window is known to hold an in-domain cell
+  mutable std::shared_ptr<void> fused_plan[2];     // tables and launches of conv_fused.hip by direction, once asked for
   mutable std::shared_ptr<void> corr_split_plan;  // the launches of conv_split.hip, once asked for
   mutable std::shared_ptr<void> corr16_plan;       // the shapes of conv_small.hip's launches, ditto
   mutable std::shared_ptr<void> wgrad_split_plan;  // the shape of conv_wsplit.hip's launch, once asked for
   mutable int8_t corr_kernel[2][2][2] = {{{-1, -1}, {-1, -1}}, {{-1, -1}, {-1, -1}}};  // conv.hip's choice by direction and alignment, once asked for
+  mutable int8_t fused_kernel[2][2][2] = {{{-1, -1}, {-1, -1}}, {{-1, -1}, {-1, -1}}};  // whether a direction is one launch, by 16-byte accesses and alignment, ditto
   mutable int wgrad_kernel[2] = {-1, -1};          // conv.hip's choice without and with 16-byte aligned tensors, ditto
   mutable int corr_mfma_ok = -1;  // cached answer of corr_mfma_supported(): -1 not asked yet
 

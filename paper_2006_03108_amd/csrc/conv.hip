@@ -13,10 +13,12 @@
 // the direct kernels, which take what no other does (tensors of 2 GiB and
 // more, over 64 stride classes).
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "conv_any.h"
 #include "conv_core.h"
+#include "conv_fused.h"
 #include "conv_mfma.h"
 #include "conv_split.h"
 #include "conv_wsplit.h"
@@ -322,18 +324,18 @@ static Corr choose_data(const distdl_plan* p, bool aligned) { return choose_corr
 // dimension, 2 x 4000: - / 17 / 111; 32 -> 32, 5^3, stride 2, 256^3: - / 5030 / 3110.
 enum class Wgrad { k16, kSplit, kAny, kMfma, kDirect };
 
+static double wgrad_us(const distdl_plan* p, Wgrad w);
 static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {
   if (p->wgrad_kernel[vec16] >= 0) return (Wgrad)p->wgrad_kernel[vec16];
   const bool bf16 = p->dtype == DISTDL_BF16;
-  const double T = (double)p->ksize[1] * p->ksize[2], pos = (double)p->n_workers * p->n_b * p->max_out_cells;
+  const double T = (double)p->ksize[1] * p->ksize[2];
   Wgrad best = Wgrad::kDirect;
   double least = 1e300;
   auto consider = [&](Wgrad w, double us) {
     if (us < least) least = us, best = w;
   };
-  if (wgrad16_supported(p, vec16))
-    consider(Wgrad::k16, 6.0 + 0.8 * T + pos * p->ksize[0] * T * (p->ksize[0] > 1 ? 12e-6 : 7e-6));
-  if (vec16 && wgrad_split_supported(p)) consider(Wgrad::kSplit, 1.6 * wgrad_split_us(p));
+  if (wgrad16_supported(p, vec16)) consider(Wgrad::k16, wgrad_us(p, Wgrad::k16));
+  if (vec16 && wgrad_split_supported(p)) consider(Wgrad::kSplit, wgrad_us(p, Wgrad::kSplit));
   const bool fits = wgrad_mfma_supported(p) && p->n_workers * wgrad_chunks(p) <= 65535;
   if (fits && bf16 && vec16) consider(Wgrad::kMfma, wgrad_taps_us(p));
   if (conv_any_supported(p)) {
@@ -346,6 +348,18 @@ static Wgrad choose_wgrad(const distdl_plan* p, bool vec16) {
   return best;
 }
 
+// estimated time of a kernel; 0: unknown
+static double wgrad_us(const distdl_plan* p, Wgrad w) {
+  const double T = (double)p->ksize[1] * p->ksize[2], pos = (double)p->n_workers * p->n_b * p->max_out_cells;
+  switch (w) {
+    case Wgrad::k16: return 6.0 + 0.8 * T + pos * p->ksize[0] * T * (p->ksize[0] > 1 ? 12e-6 : 7e-6);
+    case Wgrad::kSplit: return 1.6 * wgrad_split_us(p);
+    case Wgrad::kAny: return wgrad_any_us(p);
+    case Wgrad::kMfma: return p->dtype == DISTDL_BF16 ? wgrad_taps_us(p) : 0;
+    default: return 0;
+  }
+}
+
 static bool wgrad_on_tiles(const distdl_plan* p) { return choose_wgrad(p, true) == Wgrad::kMfma; }
 
 static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per worker
@@ -356,6 +370,37 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
     case Wgrad::kMfma: return wgrad_chunks(p);
     default: return direct_chunks(p);
   }
+}
+
+// Small layers: everything of a direction in one launch (conv_fused.hip) where that is estimated at less than 0.85 of the launches
+// it replaces; theirs are H and its kernel, or both contractions, the reduction and H*, each estimated as above, and what the
+// host takes for them.  Without a halo exchange there is one launch less to save in the forward pass, which then goes that way only where
+// it would take little more than a launch.  Of 400 layers of up to 0.4 GFLOP 290 go forward that way and
+// 281 back (us, launches apart / together, forward and back: 1 -> 1, 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 4 -> 28, 3 x 3,
+// stride 2, 4 x 10 x 10 on 2 x 2 17.3 / 7.3 and 22.3 / 10.0; 20 -> 4, 3^3, 4 x 13 x 12 x 17 on 3 x 2 x 2 26.8 / 14.1 and 38.5 / 22.4; but 5 -> 32, 5^3,
+// stride 2, bf16, 13 x 14 x 11 x 15 22 / 45 and 58 / 400): 1.47 and 1.54 times as fast in the mean, where the better of the two would
+// be 1.49 and 1.56, five of them up to 1.2 times slower.
+static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool aligned, bool w_aligned) {
+  int8_t& known = p->fused_kernel[backward][vec][aligned];
+  if (known >= 0) return known != 0;
+  const double us = conv_fused_us(p, backward, vec);
+  const bool boxes = !p->fwd1.blocks.empty() || !p->fwd16.blocks.empty();
+  double apart = backward ? 12.0 : 9.5;  // (what the launches take at least)
+  if (us >= 0.85 * apart && std::isfinite(us) && (backward || boxes)) {
+    const Corr k = choose_corr(p, backward, aligned, w_aligned);
+    double corr = 0, wgrad = 0;
+    if (k == Corr::k16) corr = corr16_us(p, backward);
+    else if (k == Corr::kSplit) corr = corr_split_us(p, backward);
+    else if (k == Corr::kAny) corr = corr_any_us(p, backward, aligned);
+    else if (k == Corr::kMfma && p->dtype == DISTDL_BF16) corr = corr_mfma_us(p, backward);
+    // (a weight gradient on the split kernel or the bf16 planes is one of a layer that fills the chip)
+    const Wgrad wk = backward ? choose_wgrad(p, vec) : Wgrad::kAny;
+    if (backward && (wk == Wgrad::kAny || wk == Wgrad::k16)) wgrad = wgrad_us(p, wk);
+    const double device = backward ? 6.1 + 1.1 * corr + wgrad : 2.2 + 1.2 * corr;
+    apart = corr <= 0 || (backward && wgrad <= 0) ? 0.0 : std::sqrt(std::sqrt(std::pow(apart, 4) + std::pow(device, 4)));
+  }
+  known = us < 0.85 * apart;
+  return known != 0;
 }
 
 // Where the reduction of dw lays out the weights of the data gradient, that comes last, and the launch after it waits for the write-back
@@ -376,6 +421,43 @@ static bool write_back_hides(const distdl_plan* p, Corr kernel, Wgrad wgrad) {
 static int weight_job(distdl_plan* p, Corr kernel, bool backward, const void* w, bool aligned, hipStream_t st, WeightJob& job) {
   if (kernel == Corr::kSplit) return split_weight_job(p, backward, (const float*)w, st, job);
   return kernel == Corr::kAny ? any_weight_job(p, backward, w, aligned, st, job) : DISTDL_OK;
+}
+
+// Whether no output of an adjoint lies on one of its inputs, or on another output: the fused adjoint writes dx, dw and db while
+// the others are still being read.
+static bool separate(const distdl_plan* p, const void* const x[], const void* w, const void* const dy[], void* const dx[], const void* dw,
+                     const void* db, const void* ws, size_t ws_bytes) {
+  struct Range {
+    uintptr_t lo, hi;
+    bool meets(const Range& r) const { return lo < r.hi && r.lo < hi; }
+  };
+  auto range = [](const void* at, size_t bytes) { return Range{(uintptr_t)at, (uintptr_t)at + bytes}; };
+  const size_t esz = dtype_size(p->dtype), wb = (size_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci * p->n_co * esz;
+  const Range one[4] = {range(w, wb), range(ws, ws_bytes), range(dw, wb), range(db, db ? p->n_co * esz : 0)};
+  auto buf = [&](const void* at, int i) {
+    const WorkerDev& wd = p->workers[i];
+    return range(at, (size_t)p->n_b * wd.buf[0] * wd.buf[1] * wd.buf[2] * p->n_ci * esz);
+  };
+  auto out = [&](const void* at, int i) {
+    const WorkerDev& wd = p->workers[i];
+    return range(at, (size_t)p->n_b * wd.out[0] * wd.out[1] * wd.out[2] * p->n_co * esz);
+  };
+  for (int i = 0; i < 4; ++i)
+    for (int j = i + 1; j < 4; ++j)
+      if (one[i].meets(one[j])) return false;
+  Range in_all{UINTPTR_MAX, 0}, dx_all{UINTPTR_MAX, 0};
+  auto widen = [](Range& r, const Range& by) { r.lo = std::min(r.lo, by.lo), r.hi = std::max(r.hi, by.hi); };
+  for (int i = 0; i < p->n_workers; ++i) {
+    const Range rx = buf(x[i], i), ry = out(dy[i], i), rd = buf(dx[i], i);
+    for (int j = 0; j < 4; ++j)
+      if (rd.meets(one[j]) || (j > 0 && (rx.meets(one[j]) || ry.meets(one[j])))) return false;
+    widen(in_all, rx), widen(in_all, ry), widen(dx_all, rd);
+  }
+  if (!in_all.meets(dx_all)) return true;
+  for (int i = 0; i < p->n_workers; ++i)
+    for (int j = 0; j < p->n_workers; ++j)
+      if (buf(dx[i], i).meets(buf(x[j], j)) || buf(dx[i], i).meets(out(dy[j], j))) return false;
+  return true;
 }
 
 static int prepare_weights(distdl_plan* p, const void* w, hipStream_t st) {
@@ -442,6 +524,14 @@ int distdl_debug_conv_kernels(const distdl_plan* plan, int aligned, int32_t out[
   return DISTDL_OK;
 }
 
+int distdl_debug_conv_fused(const distdl_plan* plan, int aligned, int32_t out[2]) {
+  if (!plan || !out) return set_error(DISTDL_ERR_NULL, "conv_fused: null argument");
+  if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_fused: plan has no kernel");
+  const bool vec = aligned && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
+  for (int backward = 0; backward < 2; ++backward) out[backward] = choose_fused(plan, backward != 0, vec, aligned != 0, aligned != 0);
+  return DISTDL_OK;
+}
+
 int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5]) {
   if (!plan || !out) return set_error(DISTDL_ERR_NULL, "conv_split: null argument");
   if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_split: plan has no kernel");
@@ -486,7 +576,11 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
   // 16-byte pieces on both sides: the matrix-core kernels load x in them and store y in them
   bool xvec = true;
   for (int w = 0; w < plan->n_workers; ++w) xvec &= (uintptr_t)x_bufs_dev[w] % 16 == 0 && (uintptr_t)y_dev[w] % 16 == 0;
-  const Corr kernel = choose_fwd(plan, xvec, (uintptr_t)w_dev % 16 == 0);
+  const bool vec = xvec && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
+  const bool w_aligned = (uintptr_t)w_dev % 16 == 0;
+  const bool fused = halo && choose_fused(plan, false, vec, xvec, w_aligned) && conv_fused_ready(plan, false, st);
+  if (fused && !plan->d_workers) (void)conv_fused_us(plan, true, vec);  // (the adjoint's tables, on the way with the others)
+  const Corr kernel = fused ? Corr::kDirect : choose_fwd(plan, xvec, w_aligned);
   if ((rc = plan_prepare_device(plan))) return rc;
   for (int w = 0; w < plan->n_workers; ++w) {
     if (!x_bufs_dev[w]) return set_error(DISTDL_ERR_NULL, "conv_fwd: x of worker %d is null", w);
@@ -496,6 +590,13 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
   // enqueued or allocated (which would end the capture).
   if ((rc = plan->tab_x.upload((const void* const*)x_bufs_dev, plan->n_workers, st))) return rc;
   if ((rc = plan->tab_y.upload((const void* const*)y_dev, plan->n_workers, st))) return rc;
+  if (fused) {
+    bool wide = !plan->fwd16.tasks.empty();
+    for (int w = 0; w < plan->n_workers; ++w) wide &= (uintptr_t)x_bufs_dev[w] % 16 == 0;
+    if ((rc = conv_fwd_fused(plan, w_dev, bias_dev, vec, wide, st))) return rc;
+    DISTDL_HIP_TRY(hipGetLastError());
+    return DISTDL_OK;
+  }
   WeightJob job;
   if ((rc = weight_job(plan, kernel, false, w_dev, xvec, st, job))) return rc;
   if (halo && (rc = run_halo_with(plan, false, plan->tab_x, x_bufs_dev, &job, st))) return rc;  // x <- H x
@@ -552,10 +653,39 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   for (int w = 0; w < plan->n_workers; ++w) aligned &= (uintptr_t)dy_dev[w] % 16 == 0 && (uintptr_t)dx_bufs_dev[w] % 16 == 0;
   bool vec16 = aligned && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
   for (int w = 0; w < plan->n_workers; ++w) vec16 &= (uintptr_t)x_bufs_dev[w] % 16 == 0;
+  WeightJob job;
+  auto reduce_dw = [&](int nparts) {
+    const int nw = c.taps * c.ci * c.co + c.co;
+    ProfScope prof("conv_reduce_dw", st);
+    auto reduce = [&](auto e, auto elem) {
+      typedef decltype(elem) T;
+      constexpr int E = decltype(e)::value;
+      dim3 grid((unsigned)((nw + E - 1) / E));
+      if (job.kind != 0 && (int64_t)grid.x + job.blocks < kMaxBlocks256) {
+        job.at = (int32_t)grid.x;
+        grid.x += (unsigned)job.blocks;
+        hipLaunchKernelGGL((conv_reduce_dw_kernel<E, T, true>), grid, dim3(256), 0, st, (const float*)workspace_dev, nparts,
+                           (T*)dw_dev, (T*)dbias_dev, c, job);
+        job.kind = 0;
+      } else {
+        hipLaunchKernelGGL((conv_reduce_dw_kernel<E, T, false>), grid, dim3(256), 0, st, (const float*)workspace_dev, nparts,
+                           (T*)dw_dev, (T*)dbias_dev, c, NoJob{});
+      }
+    };
+    auto by_type = [&](auto e) { bf16 ? reduce(e, uint16_t{}) : reduce(e, float{}); };
+    nw <= 8192 ? by_type(std::integral_constant<int, 16>{}) : by_type(std::integral_constant<int, 64>{});
+  };
+  if (halo && choose_fused(plan, true, vec16, aligned, true) && conv_fused_ready(plan, true, st) &&
+      separate(plan, x_bufs_dev, w_dev, dy_dev, dx_bufs_dev, dw_dev, dbias_dev, workspace_dev, workspace_bytes)) {
+    int partials = 0;
+    if ((rc = conv_bwd_fused(plan, w_dev, dw_dev, dbias_dev, (float*)workspace_dev, vec16, st, &partials))) return rc;
+    if (partials > 0) reduce_dw(partials);
+    DISTDL_HIP_TRY(hipGetLastError());
+    return DISTDL_OK;
+  }
   const Wgrad wgrad = choose_wgrad(plan, vec16);
   int64_t total = plan->n_b * plan->max_buf_cells * c.ci;
   const Corr kernel = choose_data(plan, aligned);
-  WeightJob job;
   if ((rc = weight_job(plan, kernel, true, w_dev, aligned, st, job))) return rc;
   // [dConv]* with respect to x, into the whole padded buffers
   auto data_gradient = [&]() -> int {
@@ -622,27 +752,7 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
       hipLaunchKernelGGL(conv_bwd_weight_direct_kernel<float>, wgrid, dim3(256), 0, st, plan->d_workers,
                          plan->tab_x.dev, plan->tab_dy.dev, (float*)workspace_dev, c, nchunks);
   }
-  {
-    ProfScope prof("conv_reduce_dw", st);
-    const int nparts = nchunks * plan->n_workers;
-    auto reduce = [&](auto e, auto elem) {
-      typedef decltype(elem) T;
-      constexpr int E = decltype(e)::value;
-      dim3 grid((unsigned)((nw + E - 1) / E));
-      if (job.kind != 0 && (int64_t)grid.x + job.blocks < kMaxBlocks256) {
-        job.at = (int32_t)grid.x;
-        grid.x += (unsigned)job.blocks;
-        hipLaunchKernelGGL((conv_reduce_dw_kernel<E, T, true>), grid, dim3(256), 0, st, (const float*)workspace_dev, nparts,
-                           (T*)dw_dev, (T*)dbias_dev, c, job);
-        job.kind = 0;
-      } else {
-        hipLaunchKernelGGL((conv_reduce_dw_kernel<E, T, false>), grid, dim3(256), 0, st, (const float*)workspace_dev, nparts,
-                           (T*)dw_dev, (T*)dbias_dev, c, NoJob{});
-      }
-    };
-    auto by_type = [&](auto e) { bf16 ? reduce(e, uint16_t{}) : reduce(e, float{}); };
-    nw <= 8192 ? by_type(std::integral_constant<int, 16>{}) : by_type(std::integral_constant<int, 64>{});
-  }
+  reduce_dw(nchunks * plan->n_workers);
   if ((rc = launch_weight_job(job, st))) return rc;
   if (data_last && (rc = data_gradient())) return rc;
   DISTDL_HIP_TRY(hipGetLastError());

@@ -5,6 +5,7 @@
 #include <new>
 
 #include "common.h"
+#include "conv_fused.h"
 
 namespace distdl {
 
@@ -471,6 +472,7 @@ int plan_prepare_device(distdl_plan* p) {
       (rc = add_table(*p, p->adj1, tables)))
     return rc;
   tables.add(p->workers, &p->d_workers);
+  conv_fused_add_tables(p, tables);
   return tables.to_device(&p->d_tables);
 }
 
