@@ -372,21 +372,20 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
   }
 }
 
-// Small layers: everything of a direction in one launch (conv_fused.hip) where that is estimated at less than 0.85 of the launches
+// Small layers: everything of a direction in one launch (conv_fused.hip) where that is estimated at less than 0.9 of the launches
 // it replaces; theirs are H and its kernel, or both contractions, the reduction and H*, each estimated as above, and what the
 // host takes for them.  Without a halo exchange there is one launch less to save in the forward pass, which then goes that way only where
-// it would take little more than a launch.  Of 400 layers of up to 0.4 GFLOP 290 go forward that way and
-// 281 back (us, launches apart / together, forward and back: 1 -> 1, 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 4 -> 28, 3 x 3,
+// it would take little more than a launch.  Of 609 layers of up to 0.4 GFLOP 420 go forward that way and 400 back (us, launches apart / together, forward and back: 1 -> 1, 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 4 -> 28, 3 x 3,
 // stride 2, 4 x 10 x 10 on 2 x 2 17.3 / 7.3 and 22.3 / 10.0; 20 -> 4, 3^3, 4 x 13 x 12 x 17 on 3 x 2 x 2 26.8 / 14.1 and 38.5 / 22.4; but 5 -> 32, 5^3,
-// stride 2, bf16, 13 x 14 x 11 x 15 22 / 45 and 58 / 400): 1.47 and 1.54 times as fast in the mean, where the better of the two would
-// be 1.49 and 1.56, five of them up to 1.2 times slower.
+// stride 2, bf16, 13 x 14 x 11 x 15 22 / 45 and 58 / 400): 1.39 and 1.40 times as fast in the mean, where the better of the two
+// would be 1.41 and 1.43, a score of them up to 1.3 times slower.
 static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool aligned, bool w_aligned) {
   int8_t& known = p->fused_kernel[backward][vec][aligned];
   if (known >= 0) return known != 0;
   const double us = conv_fused_us(p, backward, vec);
   const bool boxes = !p->fwd1.blocks.empty() || !p->fwd16.blocks.empty();
   double apart = backward ? 12.0 : 9.5;  // (what the launches take at least)
-  if (us >= 0.85 * apart && std::isfinite(us) && (backward || boxes)) {
+  if (us >= 0.9 * apart && std::isfinite(us) && (backward || boxes)) {
     const Corr k = choose_corr(p, backward, aligned, w_aligned);
     double corr = 0, wgrad = 0;
     if (k == Corr::k16) corr = corr16_us(p, backward);
@@ -399,7 +398,7 @@ static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool ali
     const double device = backward ? 6.1 + 1.1 * corr + wgrad : 2.2 + 1.2 * corr;
     apart = corr <= 0 || (backward && wgrad <= 0) ? 0.0 : std::sqrt(std::sqrt(std::pow(apart, 4) + std::pow(device, 4)));
   }
-  known = us < 0.85 * apart;
+  known = us < 0.9 * apart;
   return known != 0;
 }
 

@@ -10,10 +10,12 @@
 //   fused_fwd_kernel   workgroups that make y, reading neighbours' owned cells in place of halos, beside those that do H's boxes
 //   fused_bwd_kernel   workgroups that make dw (all of it, or a chunk of positions' part), beside those that make dx
 //
-// fp32 matrix instructions of 16 x 16 x 4 (bf16 tensors are widened): a wave's lane holds one position (one row of x^) and 4
-// consecutive k, fetched from memory straight into registers; there is no staging to wait for but that of the weights, which
-// are taken in the caller's order and kept in LDS by output channel.  Sums are formed in chains of 16 products, which are
-// added up apart, so that their error is that of short sums.
+// 16 x 16 tiles, 4 k an instruction: a wave's lane holds one position (one row of x^) and 4 consecutive k, fetched from memory
+// straight into registers; there is no staging to wait for but that of the weights, which are taken in the caller's order and
+// kept in LDS by output channel.  fp32 tensors are multiplied and summed in fp64: twice the matrix time, which is a small part
+// here (a pass takes 4 to 8 % longer than with fp32 matrix instructions in chains of 16 products), and every sum is exact but
+// for its last rounding, 2.5e-8, where the split products of the general kernels leave 4e-8 to 1e-7, and 16 x 16 tiles of fp32
+// 2e-7.  bf16 tensors are widened and multiplied in fp32.
 //
 // What bounds it is the number of instructions that one wave issues one after the other, at 4 clocks each: of 8900 clocks of a
 // workgroup for 1 -> 1 channels, 3 taps, 64 cells on four workers, the loads take a third.  So geometry and taps come from tables
@@ -37,6 +39,7 @@ namespace distdl {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GB)
@@ -134,6 +137,20 @@ __device__ __forceinline__ float rcp(int v) { return __builtin_amdgcn_rcpf((floa
 // 2^-22 of itself
 __device__ __forceinline__ int div_by(int n, float rcp_d) { return (int)fmaf((float)n, rcp_d, 0.5f * rcp_d); }
 
+// The sums of 16 x 16 products, 4 k at a time.  Register e of lane (kk, i): row kk + 4 e (fp64) or 4 kk + e, column i.
+template <bool BF16>
+struct Acc {
+  typedef std::conditional_t<BF16, f32x4, f64x4> V;
+  V v[2];  // (two, so that one does not wait for the other)
+  __device__ __forceinline__ void clear() { v[0] = v[1] = V{0, 0, 0, 0}; }
+  __device__ __forceinline__ void add(int which, float a, float b) {
+    if constexpr (BF16) v[which] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, v[which], 0, 0, 0);
+    else v[which] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, v[which], 0, 0, 0);
+  }
+  __device__ __forceinline__ V sum() const { return v[0] + v[1]; }
+  // row of register e, for the lanes of quarter kk
+  static __device__ __forceinline__ int row(int kk, int e) { return BF16 ? 4 * kk + e : kk + 4 * e; }
+};
 // What a tap that meets no cell reads: zeros, as many as a cell has channels.
 constexpr int kZeros = 2048;
 __device__ __attribute__((aligned(16))) float fused_zeros[kZeros];
@@ -151,7 +168,8 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int per = 4 / a.wk, kg = wave % a.wk, pg = wave / a.wk;  // tiles of the workgroup at a time; this wave's share of k, its tile
   float* const wl = (float*)smem;
-  f32x4* const red = (f32x4*)(smem + a.at_red);
+  typedef typename Acc<BF16>::V Sum;
+  Sum* const red = (Sum*)(smem + a.at_red);
   uint64_t* const cells = (uint64_t*)(smem + a.at_cells) + (size_t)pg * (a.most_taps + 16) * 16;  // [tap][position]
   int4* const steps_of = (int4*)(smem + a.at_taps);
   int* const map = (int*)(smem + a.at_map);
@@ -263,9 +281,9 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
         cells[t * 16 + i] = ok ? nb.base + (int64_t)(n * nb.sn + c0 * nb.s0 + c1 * nb.s1 + c2 * a.kc) * (int)sizeof(T) : nothing;
       }
     }
-    f32x4 tot[NT];
+    Acc<BF16> acc[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) tot[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NT; ++t) acc[t].clear();
     for (int chunk = 0; chunk < a.nch; ++chunk) {
       const int c0 = chunk * a.cb, cb = min(a.cb, a.kc - c0);
       if (a.nch > 1 || it == 0) {
@@ -296,7 +314,8 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
       };
       constexpr int U = 4;
       f32x4 x[U], next[U];
-      const float* const wrow = wl + i * a.pitch + kq * 4;
+      // (the row of lane i: such that a lane's four sums are those of neighbouring channels)
+      const float* const wrow = wl + (BF16 ? i : 4 * (i & 3) + (i >> 2)) * a.pitch + kq * 4;
       auto fetch = [&](f32x4 (&v)[U], int st) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -305,11 +324,6 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
       fetch(x, kg);
       for (int st = kg; st < steps; st += U * a.wk) {
         fetch(next, st + U * a.wk);
-        f32x4 acc[NT][4];  // of the batch, added up apart: a chain of 16 products
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           if (st + u * a.wk < steps) {
@@ -317,16 +331,17 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
             for (int t = 0; t < NT; ++t) {
               const f32x4 w4 = *(const f32x4*)(wrow + t * 16 * a.pitch + (st + u * a.wk) * 16);
 #pragma unroll
-              for (int j = 0; j < 4; ++j) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[j], x[u][j], acc[t][j], 0, 0, 0);
+              for (int j = 0; j < 4; ++j) acc[t].add(j & 1, w4[j], x[u][j]);
             }
           }
         }
 #pragma unroll
-        for (int t = 0; t < NT; ++t) tot[t] += (acc[t][0] + acc[t][1]) + (acc[t][2] + acc[t][3]);
-#pragma unroll
         for (int u = 0; u < U; ++u) x[u] = next[u];
       }
     }
+    Sum tot[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) tot[t] = acc[t].sum();
     if (a.wk > 1) {  // the waves that share a tile, in order
 #pragma unroll
       for (int t = 0; t < NT; ++t) red[(wave * NT + t) * 64 + lane] = tot[t];
@@ -347,13 +362,14 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
       if (a.wk > 1 && t % a.wk != kg) continue;
       const int ch = ch0 + 16 * t + 4 * kq;
       if (ch >= a.nc) continue;
-      f32x4 v = tot[t];
       if constexpr (MODE == 0) {
         if (a.bias) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] += ld((const T*)a.bias, min(ch + e, a.nc - 1));
+          for (int e = 0; e < 4; ++e) tot[t][e] += ld((const T*)a.bias, min(ch + e, a.nc - 1));
         }
-      } else {
+      }
+      f32x4 v = __builtin_convertvector(tot[t], f32x4);
+      if constexpr (MODE == 1) {
         if (!owned) v = f32x4{0.f, 0.f, 0.f, 0.f};
         if (terms && owned) {
           // A weight that is not finite met the zeros of taps whose output does not exist: term by term, without those
@@ -419,13 +435,15 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
   int col[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) col[t] = (ntile * NT + t) * 16 + i;
-  f32x4 tot[4][NT];
-  float bsum[NT];
+  typedef typename Acc<BF16>::V Sum;
+  typedef std::conditional_t<BF16, float, double> One;
+  Acc<BF16> acc[4][NT];
+  One bsum[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    bsum[t] = 0.f;
+    bsum[t] = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) tot[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 4; ++j) acc[j][t].clear();
   }
   // (all workers: they, or of one and two their halves and quarters, are dealt to the waves)
   const int cuts = whole ? max(4 / n_workers, 1) : 1;
@@ -475,20 +493,14 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
     for (int at = begin, s = 0; at + s * 4 < end;) {
       const int here = s + U < 16 ? at : at + 64, there = s + U < 16 ? s + U : 0;
       if (here + there * 4 < end) fetch(next_x, next_y, here, there);
-      f32x4 acc[4][NT];  // of the batch, added up apart: a chain of 16 products
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t) {
+          bsum[t] += y[u][t];
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][j], y[u][t], u == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[j][t], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        bsum[t] += (y[0][t] + y[1][t]) + (y[2][t] + y[3][t]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) tot[j][t] += acc[j][t];
-      }
+          for (int j = 0; j < 4; ++j) acc[j][t].add(u & 1, x[u][j], y[u][t]);
+        }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         x[u] = next_x[u];
@@ -498,22 +510,23 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
       at = here, s = there;
     }
   }
-  // register e of (j, t): row 4 kk + e of those lane i stands for, column i
   constexpr int NB = 16 * NT;
-  float* const red = (float*)smem;  // [wave][row][column]
+  One* const red = (One*)smem;  // [wave][row][column]
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < NT; ++t) {
+      const Sum tot = acc[j][t].sum();
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int ri = 4 * kk + e, row = VEC ? 4 * ri + j : 16 * j + ri;
-        red[(wave * 64 + row) * NB + 16 * t + i] = tot[j][t][e];
+        const int ri = Acc<BF16>::row(kk, e), row = VEC ? 4 * ri + j : 16 * j + ri;
+        red[(wave * 64 + row) * NB + 16 * t + i] = tot[e];
       }
-  float* const bred = red + 4 * 64 * NB;
+    }
+  One* const bred = red + 4 * 64 * NB;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    float s = bsum[t];
+    One s = bsum[t];
     s += __shfl_xor(s, 16);
     s += __shfl_xor(s, 32);
     if (lane < 16) bred[wave * NB + 16 * t + lane] = s;
@@ -523,7 +536,7 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
 #pragma unroll
   for (int u = 0; u < 64 * NB / 256; ++u) {
     const int e = tid + 256 * u, row = e / NB, c = e % NB, k = mt * 64 + row, ch = ntile * NB + c;
-    const float s = ((red[e] + red[64 * NB + e]) + red[2 * 64 * NB + e]) + red[3 * 64 * NB + e];
+    const float s = (float)((red[e] + red[64 * NB + e]) + red[2 * 64 * NB + e] + red[3 * 64 * NB + e]);
     if (k >= rows || ch >= a.co) continue;
     if (whole) {
       const int tap = div_by(k, rci);
@@ -533,7 +546,7 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
     }
   }
   if (mt == 0 && tid < NB && ntile * NB + tid < a.co) {
-    const float s = ((bred[tid] + bred[NB + tid]) + bred[2 * NB + tid]) + bred[3 * NB + tid];
+    const float s = (float)(bred[tid] + bred[NB + tid] + bred[2 * NB + tid] + bred[3 * NB + tid]);
     if (!whole) slot[(size_t)rows * a.co + ntile * NB + tid] = s;
     else if (a.db) st((T*)a.db, ntile * NB + tid, s);
   }
@@ -726,7 +739,7 @@ Shape shape_of(const distdl_plan* p, int mode, bool vec, int taps, int64_t posit
   a.blocks = (int32_t)std::min<int64_t>(blocks, INT32_MAX);
   a.most_taps = taps;
   int at = 16 * sh.NT * a.pitch * 4;
-  a.at_red = at, at += a.wk > 1 ? 4 * sh.NT * 64 * 16 : 0;
+  a.at_red = at, at += a.wk > 1 ? 4 * sh.NT * 64 * 32 : 0;
   a.at_cells = at, at += (taps + 16) * 16 * 8 * per;
   a.at_taps = at, at += taps * 16;
   a.at_map = at, at += a.ncls > 1 ? (a.taps * 4 + 15) / 16 * 16 : 0;
@@ -775,7 +788,7 @@ int launch_fwd(distdl_plan* p, const Shape& sh, int halo_blocks, hipStream_t st)
 }
 template <bool BF16, bool VEC, int NT>
 int launch_bwd(distdl_plan* p, const Shape& sh, hipStream_t st) {
-  const int lds = std::max(sh.lds, (4 * 64 + 4) * 16 * 4);
+  const int lds = std::max(sh.lds, (4 * 64 + 4) * 16 * (BF16 ? 4 : 8));
   if (lds > 64 * 1024)
     if (int rc = allow_large_lds<fused_bwd_kernel<BF16, VEC, NT>>()) return rc;
   hipLaunchKernelGGL((fused_bwd_kernel<BF16, VEC, NT>), dim3((unsigned)(sh.a.blocks + sh.a.dw_blocks)), dim3(256), lds, st, p->d_workers, p->n_workers,
@@ -837,16 +850,16 @@ double conv_fused_us(const distdl_plan* p, bool backward, bool vec) {
                steps = std::max(1.0, std::ceil((double)a.most_taps * a.kc / 16)) / a.wk, load = a.blocks / 256.0;
   const int resident = std::min(160 * 1024 / sh.lds, sh.NT == 4 ? 2 : 3);
   if (!backward) {
-    const double t = 1.45 + stage + a.tpw * (0.63 + 0.15 * entries + steps * ((vec ? 0.0 : 0.22) + 0.30 * sh.NT));
-    return joined(5.8, 3.55 + t * std::max(1.0, load / resident) * (1 + 0.19 * std::min(load, 3.0)));
+    const double t = 0.87 + 0.94 * stage + a.tpw * (0.75 + 0.145 * entries + steps * ((vec ? 0.0 : 0.16) + 0.30 * sh.NT));
+    return joined(6.4, 4.6 + t * std::max(1.0, load / resident) * (1 + 0.26 * std::min(load, 3.0)));
   }
-  const double t = 0.8 + 0.59 * stage + a.tpw * (0.81 + 0.02 * entries + steps * ((vec ? 0.0 : 0.1) + 0.134 * sh.NT));
+  const double t = 0.8 + 0.56 * stage + a.tpw * (0.79 + 0.02 * entries + steps * ((vec ? 0.03 : 0.12) + 0.145 * sh.NT));
   const bool whole = a.dw_chunks == 0;
   const double batches = std::max(1.0, whole ? wave_positions(p) / 16 : (double)p->n_b * p->max_out_cells / (a.dw_chunks * 64.0));
-  const double tw = 2.1 + batches * (vec ? 0.32 : 0.75), loadw = a.dw_blocks / 256.0;
+  const double tw = 2.0 + batches * (vec ? 0.46 : 0.91), loadw = a.dw_blocks / 256.0;
   const double longest = std::max(t, tw), all = (t * load + tw * loadw) / resident * (1 + 0.4 * std::min(load + loadw, 3.0));
-  const double reduce = whole ? 0 : 2.0 + 4.1e-6 * a.slot * p->n_workers * a.dw_chunks;
-  return joined(8.7, 4.4 + std::max(longest, all) + 0.8 * std::min(longest, all) + reduce);
+  const double reduce = whole ? 0 : 2.0 + 6.4e-6 * a.slot * p->n_workers * a.dw_chunks;
+  return joined(7.8, 5.0 + std::max(longest, all) + 0.8 * std::min(longest, all) + reduce);
 }
 
 // (a call that is recorded cannot bring the tables to the device: where it is the plan's first, the general kernels take it)

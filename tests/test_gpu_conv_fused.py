@@ -30,11 +30,11 @@ def _cfg(n_b, c_in, c_out, shape, P, k, s, p, dil=1):
 # interior workers (neighbours on both sides of every dimension), padding and halo on one side, uneven parts; all of dw in one
 # workgroup and sums over several; channels of 1 ... 164
 FUSED = [
-    _cfg(1, 1, 1, (64,), 4, 3, 1, 1), _cfg(1, 4, 4, (5,), 2, 1, 1, 0), _cfg(3, 3, 5, (19, 23), (2, 3), (3, 4), (2, 1), (1, 2), (1, 2)),
+    _cfg(1, 1, 1, (64,), 4, 3, 1, 1), _cfg(1, 4, 4, (5,), 2, 1, 1, 0), _cfg(1, 3, 5, (19, 23), (2, 3), (3, 4), (2, 1), (1, 2), (1, 2)),
     _cfg(2, 16, 56, (12, 6), (2, 3), 3, 1, 1), _cfg(2, 5, 33, (9, 11, 10), (3, 3, 2), 3, 1, 1), _cfg(15, 4, 40, (29, 20), 2, 3, 2, 1),
     _cfg(1, 164, 8, (50,), 2, 11, 1, 5), _cfg(2, 8, 12, (13, 14, 15), (3, 1, 3), (2, 3, 1), (2, 3, 1), (1, 1, 0)),
     _cfg(3, 18, 10, (40, 44), (2, 3), 5, 2, 2), _cfg(2, 20, 24, (50,), 3, 7, 4, 3), _cfg(1, 61, 7, (14, 18), (4, 4), 3, 1, 1),
-    _cfg(1, 12, 20, (33,), 2, 3, 2, 2, 2), _cfg(4, 8, 8, (4, 4, 4), (2, 2, 2), 2, 1, 1), _cfg(1, 2, 3, (30, 30), (3, 3), 3, 3, 0),
+    _cfg(1, 12, 20, (33,), 2, 3, 2, 2, 2), _cfg(2, 8, 8, (4, 4, 4), (2, 2, 2), 2, 1, 1), _cfg(1, 2, 3, (30, 30), (3, 3), 3, 3, 0),
     _cfg(1, 4, 8, (7,), 2, 7, 1, 3), _cfg(6, 4, 4, (40, 41), 1, 3, 1, 1),
 ]
 
@@ -103,19 +103,20 @@ class _Layer:
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("cfg", FUSED, ids=_ids)
 def test_fused_layer(cfg, dtype, offset):
-    """fp32: sums of at most 10000 products in chains of 16, added up: a random walk of 625 + 16 roundings of 2^-24 at most, 2e-6.
-    bf16: the result's rounding, and a value of the other side of it where the sums differ."""
+    """fp32: a sum is rounded once (3e-8 of its rms in the mean, 6e-8 at most), in dw also for each of up to a hundred chunks and as
+    they are added up: 3e-7; the general kernels' errors, which come on top where the two are compared, are below 5e-7.  bf16: the
+    result's rounding, and a value of the other side of it where the sums differ."""
     require_gpu()
     L = _Layer(cfg, dtype, offset)
     assert dd.distdl_debug_conv_fused(L.plan, offset == 0) == (True, True)
     L.run()
-    L.check(2e-6 if dtype == F32 else 2e-2)
+    L.check(3e-7 if dtype == F32 else 2e-2)
     together = [t.clone() for t in L.outputs()]
     L.run()                                          # the same bits again
     assert all(torch.equal(a, b) for a, b in zip(together, L.outputs()))
     L.run_apart()
     for a, b in zip(together, L.outputs()):
-        assert float((a.double() - b.double()).norm()) <= (2e-6 if dtype == F32 else 4e-3) * float(b.double().norm())
+        assert float((a.double() - b.double()).norm()) <= (8e-7 if dtype == F32 else 4e-3) * float(b.double().norm())
 
 
 @pytest.mark.parametrize("cfg", [FUSED[i] for i in (4, 5, 7, 8, 9, 10, 11)], ids=_ids)
@@ -143,7 +144,7 @@ def test_fused_layer_with_values_that_are_not_finite(cfg):
 
 def test_fused_calls_from_a_graph_and_on_two_streams():
     require_gpu()
-    cfg = _cfg(2, 6, 10, (24, 20), 2, 3, 1, 1)
+    cfg = _cfg(1, 6, 10, (16, 14), 2, 3, 1, 1)
     L, M = _Layer(cfg, F32), _Layer(dict(cfg, seed=84), F32)
     M.plan = L.plan
     assert dd.distdl_debug_conv_fused(L.plan) == (True, True)
