@@ -373,12 +373,16 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
 }
 
 // Small layers: everything of a direction in one launch (conv_fused.hip) where that is estimated at less than 0.9 of the launches
-// it replaces; theirs are H and its kernel, or both contractions, the reduction and H*, each estimated as above, and what the
-// host takes for them.  Without a halo exchange there is one launch less to save in the forward pass, which then goes that way only where
-// it would take little more than a launch.  Of 609 layers of up to 0.4 GFLOP 420 go forward that way and 400 back (us, launches apart / together, forward and back: 1 -> 1, 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 4 -> 28, 3 x 3,
-// stride 2, 4 x 10 x 10 on 2 x 2 17.3 / 7.3 and 22.3 / 10.0; 20 -> 4, 3^3, 4 x 13 x 12 x 17 on 3 x 2 x 2 26.8 / 14.1 and 38.5 / 22.4; but 5 -> 32, 5^3,
-// stride 2, bf16, 13 x 14 x 11 x 15 22 / 45 and 58 / 400): 1.39 and 1.40 times as fast in the mean, where the better of the two
-// would be 1.41 and 1.43, a score of them up to 1.3 times slower.
+// it replaces, from 20 us at less than 0.8; theirs are H and its kernel, or both contractions, the reduction and H*, each estimated
+// as above, and what the host takes for them.  Without a halo exchange there is one launch less to save in the forward pass, which
+// then goes that way only where it would take little more than a launch.  us, launches apart / together, forward and back: 1 -> 1,
+// 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 4 -> 28, 3 x 3, stride 2, 4 x 10 x 10 on 2 x 2 17.3 / 7.3 and 22.3 / 10.0;
+// 20 -> 4, 3^3, 4 x 13 x 12 x 17 on 3 x 2 x 2 26.8 / 14.1 and 38.5 / 22.4; but 5 -> 32, 5^3, stride 2, bf16, 13 x 14 x 11 x 15
+// 22 / 45 and 58 / 400.  Up to 100 us forward (44 -> 8, 5^3, stride 2, 12 x 11 x 16 x 12 146 / 60; 27 -> 11, 3 x 3, 10 x 244 x 329
+// 258 / 283) and 40 us back, where the fp64 matrix instructions and the second reading of x weigh more than the launches (8 -> 64,
+// 3 taps, 4 x 36171 54 / 71; 24 -> 4, 3^3, bf16, 11 x 62 x 54 x 61 1026 / 2498).  Of 650 layers 434 go forward that way and 363
+// back: 1.36 and 1.35 times as fast in the mean, where the better of the two would be 1.40 and 1.41, a score of them up to 1.4
+// times slower.
 static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool aligned, bool w_aligned) {
   int8_t& known = p->fused_kernel[backward][vec][aligned];
   if (known >= 0) return known != 0;
@@ -398,7 +402,7 @@ static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool ali
     const double device = backward ? 6.1 + 1.1 * corr + wgrad : 2.2 + 1.2 * corr;
     apart = corr <= 0 || (backward && wgrad <= 0) ? 0.0 : std::sqrt(std::sqrt(std::pow(apart, 4) + std::pow(device, 4)));
   }
-  known = us < 0.9 * apart;
+  known = us < (us < 20 ? 0.9 : 0.8) * apart && us < (backward ? 40 : 100);
   return known != 0;
 }
 
