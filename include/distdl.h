@@ -452,6 +452,10 @@ int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5
  * that distdl_debug_conv_kernels names with H and H* around them; the
  * distdl_conv_local_* calls always run those.  aligned: as there. */
 int distdl_debug_conv_fused(const distdl_plan* plan, int aligned, int32_t out[2]);
+/* For tests: which kernels the calls of this affine plan take, where they can:
+ * 0 the tiled ones, 1 those of small layers, -1 (as created) the ones that are
+ * estimated to be faster. */
+int distdl_debug_affine_route(distdl_affine_plan* plan, int route);
 /* Rows (taps x input channels) of a tile of the gather kernel's weight
  * gradient, whether or not it is what runs: 64 or 256, 0 where it does not take
  * the layer. */

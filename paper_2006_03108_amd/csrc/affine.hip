@@ -6,9 +6,11 @@
 //                                                  continuation of the sum
 //   adjoint   dW_ij = dy_i^T x_j,  db_i = sum_n dy_i,  dx_j = sum_i dy_i W_ij
 #include <algorithm>
-
+#include <atomic>
+#include <cmath>
 #include <cstring>
 
+#include "affine_small.h"
 #include "common.h"
 #include "gemm_mfma.h"
 #include "profile.h"
@@ -24,6 +26,8 @@ struct distdl_affine_plan {
   distdl::DevArray<distdl::GemmBlock> g_fwd, g_dx, g_dw;
   distdl::DevArray<distdl::ColsumBlock> g_db;
   distdl::StreamScratch partial;  // fp32 partial tiles of K-split GEMM launches
+  int route = -1;                  // 0, 1: the tiled or the small kernels for every call that they take (distdl_debug_affine_route)
+  std::atomic<int8_t> small_fwd[2] = {{-1}, {-1}}, small_bwd[2][2] = {{{-1}, {-1}}, {{-1}, {-1}}};  // choices by alignment, once made: 0, 1, 2 not taken at all
 };
 
 namespace distdl {
@@ -168,6 +172,50 @@ static void bwd_direct(distdl_affine_plan* p, bool has_db, hipStream_t st_) {
                        st_, p->tab_dy.dev, p->tab_db.dev, p->d_sizes, (int)p->n_b);
 }
 
+// Small layers (affine_small.hip): where their launch is estimated at less than 0.95 of the calls on the tiled kernels.  What
+// decides is that those start a tile at a time, and split a long K over two launches; with many tiles, or matrix instructions in
+// earnest, they are the faster ones.  us, tiled / small, forward and back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 295 x 624 -> 28,
+// 2 x 1 10.2 / 6.4 and 12.9 / 7.7; 37 x 2000 -> 1001, 2 x 3 12.9 / 10.3 and 18.1 / 20.5; 327 x 84 -> 7210, 2 x 2 18.9 / 25.1 and 25.5 / 46.9; bf16 of
+// odd rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4 and 16.6 / 12.0.  Of 138 layers 99 go forward that way and 67 back: 1.17 and 1.09 times as fast
+// in the mean over all of them, the better of the two would be 1.18 and 1.12.
+static double joined(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
+static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& blocks, bool bf16) {
+  // (bf16 rows of whole 16-byte pieces take 7 to 9 us either way)
+  if (p->route == 0 || (p->route < 0 && bf16 && gemm_mfma_usable(blocks, bf16, true, true))) return false;
+  const bool vec = gemm_split_vec(blocks, bf16, true, true);
+  int known = p->small_fwd[vec].load(std::memory_order_relaxed);
+  if (known < 0) {
+    const double us = affine_small_fwd_us(blocks, bf16);
+    known = us < 0.95 * joined(9.2, 1.6 + 1.1 * gemm_split_plan(blocks, vec).us) ? 1 : std::isfinite(us) ? 0 : 2;
+    p->small_fwd[vec].store(known, std::memory_order_relaxed);
+  }
+  return known == 1 || (p->route > 0 && known == 0);
+}
+static bool small_bwd(distdl_affine_plan* p, const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16) {
+  if (p->route == 0) return false;
+  const bool vec = gemm_split_vec(bx, bf16, true, false) && gemm_split_vec(bw, bf16, false, false);
+  const bool tiles = bf16 && gemm_mfma_usable(bx, bf16, true, false) && gemm_mfma_usable(bw, bf16, false, false);
+  int known = p->small_bwd[vec][tiles].load(std::memory_order_relaxed);
+  if (known < 0) {
+    const double us = affine_small_bwd_us(bx, bw, bf16), x = gemm_split_plan(bx, vec).us, w = gemm_split_plan(bw, vec).us;
+    // (bf16 tiles: two launches and more, 12 to 20 us; 29 x 32 -> 816 on 1 x 2 15.1 / 9.0, 73 x 176 -> 192 on 2 x 2 13.6 / 9.7, 299 x 3440 -> 96 16.6 / 14.7)
+    const double tiled = tiles ? 12.6 : joined(10.4, 1.28 * std::max(x, w) + 1.37 * std::min(x, w));
+    known = us < 0.95 * tiled ? 1 : std::isfinite(us) ? 0 : 2;
+    p->small_bwd[vec][tiles].store(known, std::memory_order_relaxed);
+  }
+  return known == 1 || (p->route > 0 && known == 0);
+}
+// Whether a dW lies on weights, which dx is made of in the same launch.
+static bool on_weights(const distdl_affine_plan* p, const void* const W[], void* const dW[]) {
+  const size_t esz = dtype_size(p->dtype);
+  const int n = p->P_fo * p->P_fi;
+  auto bytes = [&](int i) { return (uintptr_t)(p->fo_size[i / p->P_fi] * p->fi_size[i % p->P_fi]) * esz; };
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < n; ++j)
+      if ((uintptr_t)dW[i] < (uintptr_t)W[j] + bytes(j) && (uintptr_t)W[j] < (uintptr_t)dW[i] + bytes(i)) return true;
+  return false;
+}
+
 }  // namespace distdl
 
 using namespace distdl;
@@ -224,6 +272,13 @@ int distdl_affine_plan_destroy(distdl_affine_plan* p) {
   return DISTDL_OK;
 }
 
+int distdl_debug_affine_route(distdl_affine_plan* p, int route) {
+  if (!p) return set_error(DISTDL_ERR_NULL, "affine_route: null argument");
+  if (route < -1 || route > 1) return set_error(DISTDL_ERR_INVALID_ARG, "affine_route: %d", route);
+  p->route = route;
+  return DISTDL_OK;
+}
+
 int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const void* const W_dev[],
                       const void* const b_dev[], void* const y_dev[], void* stream) {
   if (!p || !x_dev || !W_dev || !y_dev) return set_error(DISTDL_ERR_NULL, "affine_fwd: null argument");
@@ -249,6 +304,11 @@ int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const vo
       for (int j = 0; j < p->P_fi && j < kGemmMaxSeg; ++j)
         g.seg[j] = GemmSeg{x_dev[j], W_dev[i * p->P_fi + j], (int32_t)p->fi_size[j], (int32_t)p->fi_size[j],
                            (int32_t)p->fi_size[j], 0};
+    }
+    if (small_fwd(p, blocks, bf16)) {
+      if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = launch_affine_small_fwd(p->g_fwd.dev, blocks, bf16, st_))) return rc;
+      DISTDL_HIP_TRY(hipGetLastError());
+      return DISTDL_OK;
     }
     if ((!bf16 || !gemm_mfma_usable(blocks, bf16, true, true)) && gemm_split_usable(blocks, bf16, true, true)) {
       const GemmSplitPlan sp = gemm_split_plan(blocks, gemm_split_vec(blocks, bf16, true, true));
@@ -314,6 +374,13 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
         g.seg[0] = GemmSeg{dy_dev[i], x_dev[j], (int32_t)p->n_b, (int32_t)p->fo_size[i], (int32_t)p->fi_size[j], 0};
       }
       bb[i] = ColsumBlock{dy_dev[i], db_dev ? db_dev[i] : nullptr, (int32_t)p->n_b, (int32_t)p->fo_size[i]};
+    }
+    if (small_bwd(p, bx, bw, bf16) && !on_weights(p, W_dev, dW_dev)) {
+      if ((rc = p->g_dx.upload(bx, st_)) || (rc = p->g_dw.upload(bw, st_)) || (db_dev && (rc = p->g_db.upload(bb, st_)))) return rc;
+      rc = launch_affine_small_bwd(p->g_dx.dev, bx, p->g_dw.dev, bw, db_dev ? p->g_db.dev : nullptr, p->P_fo, (int)p->max_fo, bf16, st_);
+      if (rc) return rc;
+      DISTDL_HIP_TRY(hipGetLastError());
+      return DISTDL_OK;
     }
     if ((!bf16 || !(gemm_mfma_usable(bx, bf16, true, false) && gemm_mfma_usable(bw, bf16, false, false))) &&
         gemm_split_usable(bx, bf16, true, false) && gemm_split_usable(bw, bf16, false, false)) {

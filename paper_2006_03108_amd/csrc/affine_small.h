@@ -1,0 +1,16 @@
+// Small affine layers: one launch forward, one for dx, dW and db (affine_small.hip).
+#pragma once
+#include <vector>
+
+#include "gemm_mfma.h"
+
+namespace distdl {
+
+// Estimated time of a call, launch and all (us); infinite: not taken
+double affine_small_fwd_us(const std::vector<GemmBlock>& blocks, bool bf16);
+double affine_small_bwd_us(const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16);
+int launch_affine_small_fwd(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool bf16, hipStream_t st);
+int launch_affine_small_bwd(const GemmBlock* d_bx, const std::vector<GemmBlock>& bx, const GemmBlock* d_bw, const std::vector<GemmBlock>& bw,
+                            const ColsumBlock* d_cs, int n_cs, int max_f, bool bf16, hipStream_t st);
+
+}  // namespace distdl
