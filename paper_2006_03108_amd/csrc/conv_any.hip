@@ -14,8 +14,16 @@
 //     tiles are added through LDS, in wave order.
 //     Channel counts that are multiples of 4: neighbouring lanes load neighbouring pieces of 4 channels (with a lane per
 //     row the 64 lanes of a load touch 64 lines, and the chip then loads 15 bytes per clock and compute unit: data
-//     gradient of 8 x 224 x 224, 3 -> 32 channels, 7 x 7: 156 us).  Other counts: a lane per row, and the offset of a
-//     k, the same for all lanes, goes into the scalar offset of the load.
+//     gradient of 8 x 224 x 224, 3 -> 32 channels, 7 x 7: 156 us).
+//     fp32, other counts: forward the channels of the taps along dimension 2 lie one behind the other in memory, a run; k is then
+//     (tap of the other dimensions, place in the run), each run in octets of its own, what lies behind its end made zero.  Data
+//     gradient, or taps that are dilated: a run is the channels of one tap.  Neighbouring lanes load neighbouring octets, 16 bytes
+//     at a time whatever the alignment, where every element was a load that touched a line for each row.  us, element by element /
+//     by runs: forward of 3 -> 32, 7 x 7, stride 2, 8 x 224 x 224 32.7 / 27.6; 43 -> 1, 5^3, 5 x 22 x 20 x 34 325 / 193; 31 -> 2, 3^3,
+//     11 x 25 x 34 x 24 264 / 144; back with 29 channels of dy, 5^3, 2 x 31 x 29 x 35 741 / 524.  Not for runs of less than 8, nor
+//     where their ends make more than 1.3 times the stages (2 -> 24, 5^3 67 / 81; 3 -> 22, 3 x 3, dilated 62 / 84), nor for
+//     fewer than 16 k (1 -> 45, 5 taps 27 / 30).
+//     Otherwise: a lane per row, and the offset of a k, the same for all lanes, goes into the scalar offset of the load.
 //   wgrad_any_kernel: rows are k, columns output channels, the sum runs over output positions; the offset that all
 //     lanes share is that of the position.  Every (worker, chunk of positions) writes a partial, which also holds the
 //     chunk's part of db^.  256 rows and 32 positions per stage, or 64 rows and 128 positions (a layer of few channels and
@@ -100,6 +108,11 @@ __device__ __forceinline__ DimAny dim_any(const WorkerDev& wd, const AnyArgs& a,
   }
   return g;
 }
+
+// What a thread gathers: octets of a row element by element, quads of channels, octets of runs (see above)
+enum { kByOne = 0, kByQuad = 1, kByRun = 2 };
+// k without padding, or the octets of a tap or run on their own
+constexpr bool flat_k(int mode, int by) { return by == kByQuad || (mode == 0 && by == kByOne); }
 
 // ROWS rows x KS octets of k per stage: 1024 pieces of A
 constexpr int octets_of(int ROWS) { return 1024 / ROWS; }
@@ -223,13 +236,14 @@ __device__ inline float corr_direct(const AnyArgs& a, const DimAny& g0, const Di
   return sum;
 }
 
-template <int ROWS, int NT, bool BF16, int MODE, bool VEC>
+template <int ROWS, int NT, bool BF16, int MODE, int BY>
 __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __restrict__ workers, void* const* in_bufs,
                                                           void* const* out_bufs, AnyArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr uint32_t ES = BF16 ? 2 : 4;
   constexpr int PL = planes_of(BF16), KS = octets_of(ROWS);
-  constexpr bool FLAT = MODE == 0 || VEC;  // k without padding; else the octets of a tap are its own
+  constexpr bool VEC = BY != kByOne, RUNS = BY == kByRun;  // neighbouring lanes take neighbouring k of a row
+  constexpr bool FLAT = flat_k(MODE, BY);                  // k without padding; else the octets of a run, or a tap, are its own
   // consecutive tiles share input rows and stay on one XCD (one L2)
   const uint32_t nblk = gridDim.x, r = (blockIdx.x & 7u) * (nblk >> 3) + (blockIdx.x >> 3);
   const uint32_t worker = r / a.tiles_max;
@@ -262,7 +276,7 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
     n = (int)(t / (uint32_t)g0.nq);
     return true;
   };
-  // The rows this thread gathers: VEC: octet tid % KS of row tid / KS + i * (256 / KS); else row tid % ROWS, whose octets
+  // The rows this thread gathers: VEC (octets of runs too): octet tid % KS of row tid / KS + i * (256 / KS); else row tid % ROWS, whose octets
   // (wave of the row) + (256 / ROWS) * o it takes.
   constexpr int NR = VEC ? 4 : 1;
   uint32_t base[NR];
@@ -289,24 +303,42 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
                        : kOob;
   }
 
-  const int ntaps = g0.nt * g1.nt * g2.nt, noct = (a.kc + 7) / 8;
+  const int n2 = RUNS ? g2.nt / a.run : g2.nt, ntaps = g0.nt * g1.nt * n2, len = RUNS ? a.run * a.kc : a.kc, noct = (len + 7) / 8;
   const int K = FLAT ? ntaps * a.kc : ntaps * noct * 8;
   const int stages = (K + 8 * KS - 1) / (8 * KS);
   const int octs = (K + 8 * kOctPad - 1) / (8 * kOctPad) * kOctPad;
-  const float rc = 1.0f / (float)(FLAT ? a.kc : noct), r2 = 1.0f / (float)max(g2.nt, 1), r1 = 1.0f / (float)max(g1.nt, 1);
+  const float rc = 1.0f / (float)(FLAT ? a.kc : noct), r2 = 1.0f / (float)max(n2, 1), r1 = 1.0f / (float)max(g1.nt, 1);
   const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.wt + ((size_t)a.woff[cls] * a.ntn + (size_t)ntile * octs) * (PL * 32 * NT),
                                             (uint32_t)octs * (PL * 32 * NT) * 16u);
   // index of a tap -> what its input coordinates add to those of tap 0
   auto steps_of = [&](int tap, int& d0, int& d1, int& d2) {
-    const int t01 = div_by(tap, max(g2.nt, 1), r2), t0 = div_by(t01, max(g1.nt, 1), r1);
-    d2 = (tap - t01 * g2.nt) * g2.dt, d1 = (t01 - t0 * g1.nt) * g1.dt, d0 = t0 * g0.dt;
+    const int t01 = div_by(tap, max(n2, 1), r2), t0 = div_by(t01, max(g1.nt, 1), r1);
+    d2 = (tap - t01 * n2) * g2.dt, d1 = (t01 - t0 * g1.nt) * g1.dt, d0 = t0 * g0.dt;
   };
 
   float v[4][8];
   constexpr int BP = KS * PL * 32 * NT, BPT = (BP + 255) / 256;  // weight pieces of a stage
   u32x4 wp[BPT];
+  int left = 0;  // BY RUN: of the octet that is loaded, the elements in its run
   auto load_stage = [&](int st, bool weights) {
-    if constexpr (VEC) {
+    if constexpr (RUNS) {
+      const int oct = st * KS + tid % KS, tap = div_by(oct, noct, rc), c = (oct - tap * noct) * 8;
+      int d0, d1, d2;
+      steps_of(tap, d0, d1, d2);
+      const uint32_t add = ((uint32_t)d0 * sc0 + (uint32_t)d1 * sc1 + (uint32_t)d2 * (uint32_t)a.kc + (uint32_t)c) * ES;
+      if (tap >= ntaps) d0 = -0x20000000;
+      left = len - c;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        bool ok;
+        if constexpr (MODE == 0) ok = tap < ntaps && base[i] != kOob;
+        else ok = (uint32_t)(p0[i] + d0) < (uint32_t)g0.in_ext && (uint32_t)(p1[i] + d1) < (uint32_t)g1.in_ext &&
+                  (uint32_t)(p2[i] + d2) < (uint32_t)g2.in_ext;
+        const uint32_t off = ok ? base[i] + add : kOob;
+        load4<BF16>(&v[i][0], rin, off, 0);
+        load4<BF16>(&v[i][4], rin, off + 4 * ES, 0);
+      }
+    } else if constexpr (VEC) {
       // two groups of four channels, each within one tap
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
@@ -362,6 +394,12 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
     }
   };
   auto write_octets = [&](auto raw) {
+    if (RUNS && (len & 7) != 0) {  // (what lies behind a run is another cell's)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i][e] = e < left ? v[i][e] : 0.f;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int oct = VEC ? tid % KS : tid / ROWS + (256 / ROWS) * i, row = VEC ? tid / KS + i * (256 / KS) : tid % ROWS;
@@ -660,13 +698,12 @@ AnyArgs any_args(const distdl_plan* p, int mode, int NT) {
     a.taps *= a.k[d];
     if (mode == 1) a.ncls *= a.s[d];
   }
+  a.run = 1;
   a.n_workers = p->n_workers;
   a.ntn = (a.nc + 32 * NT - 1) / (32 * NT);
   return a;
 }
 
-// k without padding, or the octets of a tap on their own (see the kernel)
-bool flat_k(const AnyArgs& a, bool vec) { return a.mode == 0 || vec; }
 
 // octets of weights of every class; returns their sum
 int64_t class_octets(const AnyArgs& a, bool flat, int32_t* first, int& most, int* k_most = nullptr) {
@@ -681,7 +718,7 @@ int64_t class_octets(const AnyArgs& a, bool flat, int32_t* first, int& most, int
       if (a.mode == 1) class_taps(a.k[d], a.s[d], a.dil[d], par[d], nt, tf, ts);
       ntaps *= nt;
     }
-    const int K = flat ? ntaps * a.kc : ntaps * ((a.kc + 7) / 8) * 8;
+    const int K = flat ? ntaps * a.kc : ntaps / a.run * ((a.run * a.kc + 7) / 8) * 8;
     const int octs = (K + 8 * kOctPad - 1) / (8 * kOctPad) * kOctPad;
     if (first) first[cls] = (int32_t)sum;
     sum += octs;
@@ -702,46 +739,54 @@ int64_t positions_max(const distdl_plan* p, const AnyArgs& a) {
 }
 
 size_t weight_floats(const distdl_plan* p, int mode) {
-  const AnyArgs a = any_args(p, mode, 2);
+  AnyArgs a = any_args(p, mode, 2);
   int most;
-  const int64_t octs = std::max(class_octets(a, true, nullptr, most), class_octets(a, false, nullptr, most));
+  int64_t octs = class_octets(a, true, nullptr, most);
+  for (const int run : {1, mode == 0 ? a.k[2] : 1}) a.run = run, octs = std::max(octs, class_octets(a, false, nullptr, most));
   return (size_t)octs * a.ntn * planes_of(p->dtype == DISTDL_BF16) * 32 * 2 * 4;
 }
 
-template <int ROWS, int NT, bool BF16, int MODE, bool VEC>
+template <int ROWS, int NT, bool BF16, int MODE, int BY>
 int launch_corr_any(distdl_plan* p, const AnyArgs& a, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
   constexpr int lds = any_lds(ROWS, NT, BF16);
   const int64_t blocks = ((int64_t)a.tiles_max * p->n_workers + 7) / 8 * 8;
   if (lds > 64 * 1024)
-    if (int rc = allow_large_lds<corr_any_kernel<ROWS, NT, BF16, MODE, VEC>>()) return rc;
+    if (int rc = allow_large_lds<corr_any_kernel<ROWS, NT, BF16, MODE, BY>>()) return rc;
   ProfScope prof(name, st);
-  hipLaunchKernelGGL((corr_any_kernel<ROWS, NT, BF16, MODE, VEC>), dim3((unsigned)blocks, (unsigned)a.ncls), dim3(256), lds,
+  hipLaunchKernelGGL((corr_any_kernel<ROWS, NT, BF16, MODE, BY>), dim3((unsigned)blocks, (unsigned)a.ncls), dim3(256), lds,
                      st, p->d_workers, in_tab, out_tab, a);
   return DISTDL_OK;
 }
 
 template <int ROWS, int NT, bool BF16>
-int pick_corr_any(distdl_plan* p, const AnyArgs& a, bool vec, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
-  if (a.mode == 0)
-    return vec ? launch_corr_any<ROWS, NT, BF16, 0, true>(p, a, in_tab, out_tab, name, st)
-               : launch_corr_any<ROWS, NT, BF16, 0, false>(p, a, in_tab, out_tab, name, st);
-  return vec ? launch_corr_any<ROWS, NT, BF16, 1, true>(p, a, in_tab, out_tab, name, st)
-             : launch_corr_any<ROWS, NT, BF16, 1, false>(p, a, in_tab, out_tab, name, st);
+int pick_corr_any(distdl_plan* p, const AnyArgs& a, int by, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
+#define DISTDL_BY(MODE_, BY_) launch_corr_any<ROWS, NT, BF16, MODE_, BY_>(p, a, in_tab, out_tab, name, st)
+  if (by == kByQuad) return a.mode == 0 ? DISTDL_BY(0, kByQuad) : DISTDL_BY(1, kByQuad);
+  if constexpr (!BF16) {
+    if (by == kByRun) return a.mode == 0 ? DISTDL_BY(0, kByRun) : DISTDL_BY(1, kByRun);
+  }
+  return a.mode == 0 ? DISTDL_BY(0, kByOne) : DISTDL_BY(1, kByOne);
+#undef DISTDL_BY
 }
 
 // The launch of a direction: its arguments, rows of a tile, columns / 32; of its largest class: octets of weights, k
 struct AnyLaunch {
   AnyArgs a;
-  bool vec, few;
-  int NT, most, k;
+  bool few;
+  int by, NT, most, k;
 };
 AnyLaunch any_launch(const distdl_plan* p, int mode, bool aligned) {
   AnyLaunch l;
   l.NT = nt_of(mode == 0 ? p->n_co : p->n_ci);
   l.a = any_args(p, mode, l.NT);
   AnyArgs& a = l.a;
-  l.vec = aligned && a.kc % 4 == 0;
-  class_octets(a, flat_k(a, l.vec), a.woff, l.most, &l.k);
+  l.by = aligned && a.kc % 4 == 0 ? kByQuad : kByOne;
+  if (l.by == kByOne && p->dtype == DISTDL_F32) {
+    const int run = mode == 0 && a.dil[2] == 1 ? a.k[2] : 1, k = a.taps * a.kc;
+    const int64_t runs = (int64_t)a.taps / run * ((run * a.kc + 7) / 8);
+    if (run * a.kc >= 8 && k >= 16 && (mode == 1 || (runs + 3) / 4 <= 1.3 * ((k + 31) / 32))) l.by = kByRun, a.run = run;
+  }
+  class_octets(a, flat_k(mode, l.by), a.woff, l.most, &l.k);
   // 64 rows where 256 would leave compute units idle and there is enough k for four waves (32 columns: with 64 their
   // accumulators and the larger stages of weights do not fit the registers)
   const int64_t pos = positions_max(p, a);
@@ -756,14 +801,14 @@ int run_corr_any(distdl_plan* p, int mode, const void* w, const void* bias, bool
                  const char* name, hipStream_t st) {
   AnyLaunch l = any_launch(p, mode, aligned);
   AnyArgs& a = l.a;
-  const bool vec = l.vec, few = l.few, bf16 = p->dtype == DISTDL_BF16;
+  const bool few = l.few, bf16 = p->dtype == DISTDL_BF16;
   const int NT = l.NT;
   a.w = w;
   a.bias = bias;
   a.wt = (const u32x4*)p->d_wt;
 #define DISTDL_ANY(ROWS_, NT_)                                                               \
-  (bf16 ? pick_corr_any<ROWS_, NT_, true>(p, a, vec, in_tab, out_tab, name, st)        \
-        : pick_corr_any<ROWS_, NT_, false>(p, a, vec, in_tab, out_tab, name, st))
+  (bf16 ? pick_corr_any<ROWS_, NT_, true>(p, a, l.by, in_tab, out_tab, name, st)       \
+        : pick_corr_any<ROWS_, NT_, false>(p, a, l.by, in_tab, out_tab, name, st))
   return few ? DISTDL_ANY(64, 1) : NT == 1 ? DISTDL_ANY(256, 1) : DISTDL_ANY(256, 2);
 #undef DISTDL_ANY
 }
@@ -793,19 +838,20 @@ bool conv_any_supported(const distdl_plan* p) {
 
 // Estimated time of a launch: rounds of 512 workgroups, each a number of stages (32 k, or with 64 rows 128 k, which are shorter
 // while a workgroup is alone on its compute unit) and an epilogue.  Fitted to 186 directions of 93 layers, 1 to 64 channels,
-// 100 to 4 M positions, and 222 of 111 bf16 layers; nine tenths of them are within a quarter of it.
+// 100 to 4 M positions, and 222 of 111 bf16 layers; nine tenths of them are within a quarter of it.  (Runs take what quads take:
+// of 69 layers half are within 12 %.)
 double corr_any_us(const distdl_plan* p, bool backward, bool aligned) {
   const AnyLaunch l = any_launch(p, backward ? 1 : 0, aligned);
   const double tiles = (double)l.a.tiles_max * p->n_workers * l.a.ncls, stages = std::max(1, (l.k + (l.few ? 127 : 31)) / (l.few ? 128 : 32));
   const double alone = tiles <= 256 ? 0.57 : 1.0, rounds = std::max(1.0, tiles / 512);
   if (p->dtype == DISTDL_BF16) {
     const double short_ = tiles <= 256 ? 0.5 : 1.0;
-    if (l.few) return l.vec ? 4.5 + rounds * (stages * 1.43 * (tiles <= 256 ? 0.8 : 1.0) + 0.9) : 3.2 + rounds * stages * 2.1;
-    if (!l.vec) return 4.0 + rounds * (stages * 1.95 * short_ + 2.2) * (l.NT == 1 ? 1.0 : 1.3);
+    if (l.few) return (l.by == kByQuad) ? 4.5 + rounds * (stages * 1.43 * (tiles <= 256 ? 0.8 : 1.0) + 0.9) : 3.2 + rounds * stages * 2.1;
+    if (!(l.by == kByQuad)) return 4.0 + rounds * (stages * 1.95 * short_ + 2.2) * (l.NT == 1 ? 1.0 : 1.3);
     return l.NT == 1 ? 4.7 + rounds * (stages * short_ + 2.7) : 4.5 + rounds * (stages * 1.28 * short_ + 4.8);
   }
-  if (l.few) return l.vec ? 1.4 + rounds * (stages * 3.1 * alone + 5.6) : 4.9 + rounds * stages * 3.7 * alone;
-  if (!l.vec) return 3.4 + rounds * (stages * 4.6 * alone + 2.2) * l.NT;
+  if (l.few) return l.by != kByOne ? 1.4 + rounds * (stages * 3.1 * alone + 5.6) : 4.9 + rounds * stages * 3.7 * alone;
+  if (l.by == kByOne) return 3.4 + rounds * (stages * 4.6 * alone + 2.2) * l.NT;
   return l.NT == 1 ? 2.6 + rounds * (stages * 2.3 * alone + 5.2) : 1.0 + rounds * (stages * 3.4 * alone + 7.5);
 }
 
@@ -815,7 +861,7 @@ int any_weight_job(distdl_plan* p, bool backward, const void* w, bool aligned, h
   job.any = l.a;
   job.any.w = w;
   job.bf16 = p->dtype == DISTDL_BF16;
-  job.flat = flat_k(l.a, l.vec);
+  job.flat = flat_k(l.a.mode, l.by);
   job.cols = 32 * l.NT;
   job.dst = (u32x4*)p->d_wt;
   job.per_class = (int32_t)(((int64_t)l.a.ntn * l.most * job.cols + 255) / 256);

@@ -107,6 +107,7 @@ struct AnyArgs {
   int32_t k[3], s[3], dil[3];
   int32_t n_workers, ntn, ncls, tiles_max;
   int32_t ci, co, taps;
+  int32_t run;             // taps along dimension 2 whose channels are one run of k (octets of runs; 1: of taps)
   const split_u32x4* wt;         // weights as operand pieces
   const void* w;           // the caller's weights
   const void* bias;        // may be null
@@ -161,11 +162,11 @@ __device__ inline void put_octet(char* at, uint32_t plane, const float (&v)[8]) 
   }
 }
 
-// octet `oct` of output channel ch of a class: the weights, or zero beyond the channels and taps
+// octet `oct` of output channel ch of a class: the weights, or zero beyond the channels, runs and taps
 template <bool BF16, bool FLAT>
 __device__ inline void any_weight_octet(const AnyArgs& a, const int (&nt)[3], const int (&tf)[3], const int (&ts)[3], int oct, int ch,
                                     float (&v)[8]) {
-  const int ntaps = nt[0] * nt[1] * nt[2], noct = (a.kc + 7) / 8;
+  const int n2 = FLAT ? nt[2] : nt[2] / a.run, ntaps = nt[0] * nt[1] * n2, len = FLAT ? a.kc : a.run * a.kc, noct = (len + 7) / 8;
   bool ok[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -176,8 +177,10 @@ __device__ inline void any_weight_octet(const AnyArgs& a, const int (&nt)[3], co
     } else {
       tap = oct / noct, c = (oct - tap * noct) * 8 + e;
     }
-    ok[e] = tap < ntaps && c < a.kc && ch < a.nc;
-    const int i2 = tap % nt[2], i01 = tap / nt[2], i1 = i01 % nt[1], i0 = i01 / nt[1];
+    ok[e] = tap < ntaps && c < len && ch < a.nc;
+    int i2 = tap % n2;
+    const int i01 = tap / n2, i1 = i01 % nt[1], i0 = i01 / nt[1];
+    if (!FLAT && a.run > 1) i2 = c / a.kc, c -= i2 * a.kc;
     const int t = ((tf[0] + i0 * ts[0]) * a.k[1] + tf[1] + i1 * ts[1]) * a.k[2] + tf[2] + i2 * ts[2];
     const int oc = a.mode == 0 ? ch : c, ic = a.mode == 0 ? c : ch;
     v[e] = ld((const typename Elem<BF16>::T*)a.w, ok[e] ? ((size_t)oc * a.ci + ic) * a.taps + t : (size_t)0);
@@ -201,8 +204,8 @@ __device__ inline void any_weights(const AnyArgs& a, split_u32x4* __restrict__ d
     if (a.mode == 0) nt[d] = a.k[d], tf[d] = 0, ts[d] = 1;
     else class_taps(a.k[d], a.s[d], a.dil[d], par[d], nt[d], tf[d], ts[d]);
   }
-  const int ntaps = nt[0] * nt[1] * nt[2], noct = (a.kc + 7) / 8;
-  const int K = FLAT ? ntaps * a.kc : ntaps * noct * 8, octs = (K + 8 * kOctPad - 1) / (8 * kOctPad) * kOctPad;
+  const int ntaps = nt[0] * nt[1] * nt[2];
+  const int K = FLAT ? ntaps * a.kc : ntaps / a.run * ((a.run * a.kc + 7) / 8) * 8, octs = (K + 8 * kOctPad - 1) / (8 * kOctPad) * kOctPad;
   if (idx >= a.ntn * octs * cols) return;
   const int col = idx % (cols), r = idx / (cols), oct = r % octs, ntile = r / octs;
   float v[8];
