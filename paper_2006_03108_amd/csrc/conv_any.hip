@@ -15,15 +15,17 @@
 //     Channel counts that are multiples of 4: neighbouring lanes load neighbouring pieces of 4 channels (with a lane per
 //     row the 64 lanes of a load touch 64 lines, and the chip then loads 15 bytes per clock and compute unit: data
 //     gradient of 8 x 224 x 224, 3 -> 32 channels, 7 x 7: 156 us).
-//     fp32, other counts: forward the channels of the taps along dimension 2 lie one behind the other in memory, a run; k is then
+//     Other counts: forward the channels of the taps along dimension 2 lie one behind the other in memory, a run; k is then
 //     (tap of the other dimensions, place in the run), each run in octets of its own, what lies behind its end made zero.  Data
 //     gradient, or taps that are dilated: a run is the channels of one tap.  Neighbouring lanes load neighbouring octets, 16 bytes
-//     at a time whatever the alignment, where every element was a load that touched a line for each row.  us, element by element /
-//     by runs: forward of 3 -> 32, 7 x 7, stride 2, 8 x 224 x 224 32.7 / 27.6; 43 -> 1, 5^3, 5 x 22 x 20 x 34 325 / 193; 31 -> 2, 3^3,
-//     11 x 25 x 34 x 24 264 / 144; back with 29 channels of dy, 5^3, 2 x 31 x 29 x 35 741 / 524.  Not for runs of less than 8, nor
-//     where their ends make more than 1.3 times the stages (2 -> 24, 5^3 67 / 81; 3 -> 22, 3 x 3, dilated 62 / 84), nor for
-//     fewer than 16 k (1 -> 45, 5 taps 27 / 30).
-//     Otherwise: a lane per row, and the offset of a k, the same for all lanes, goes into the scalar offset of the load.
+//     at a time whatever the alignment (bf16: the five words that hold them), where every element was a load that touched a line
+//     for each row.  us, element by element / by runs: forward of 3 -> 32, 7 x 7, stride 2, 8 x 224 x 224 32.7 / 27.6; 43 -> 1,
+//     5^3, 5 x 22 x 20 x 34 325 / 193; bf16 61 -> 2, 5^3, stride 2, 4 x 64 x 89 x 63 1705 / 602, 9 -> 2, 7 x 7, 2 x 252 x 325
+//     63 / 29; back with 29 channels of dy, 5^3, 2 x 31 x 29 x 35 741 / 524; bf16 22 channels, 5 x 5, 9 x 73 x 93 96 / 63.  Not
+//     for runs of less than 8, nor where their ends make more than 1.3 times the stages (2 -> 24, 5^3 67 / 81; 3 -> 22, 3 x 3,
+//     dilated 62 / 84), nor for less than half a stage (1 -> 45, 5 taps 27 / 30), or a whole one back (30 channels of dy, one tap,
+//     bf16 91 / 101).
+//     In those a lane per row, and the offset of a k, the same for all lanes, goes into the scalar offset of the load.
 //   wgrad_any_kernel: rows are k, columns output channels, the sum runs over output positions; the offset that all
 //     lanes share is that of the position.  Every (worker, chunk of positions) writes a partial, which also holds the
 //     chunk's part of db^.  256 rows and 32 positions per stage, or 64 rows and 128 positions (a layer of few channels and
@@ -262,7 +264,10 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t sc1 = (uint32_t)g2.in_ext * a.kc, sc0 = (uint32_t)g1.in_ext * sc1, scn = (uint32_t)g0.in_ext * sc0;
   const uint32_t so1 = (uint32_t)g2.out_ext * a.nc, so0 = (uint32_t)g1.out_ext * so1, son = (uint32_t)g0.out_ext * so0;
-  const __amdgpu_buffer_rsrc_t rin = rsrc_of(in_bufs[worker], (uint32_t)a.n_b * scn * ES);
+  // (bf16 runs are loaded as whole words: the first and the last may hold a value that is not the tensor's)
+  const uint32_t skew = BF16 && RUNS ? (uint32_t)(uintptr_t)in_bufs[worker] & 2u : 0u;
+  const uint32_t in_bytes = (uint32_t)a.n_b * scn * ES + skew;
+  const __amdgpu_buffer_rsrc_t rin = rsrc_of((const char*)in_bufs[worker] - skew, BF16 && RUNS ? (in_bytes + 3u) & ~3u : in_bytes);
   const __amdgpu_buffer_rsrc_t rout = rsrc_of(out_bufs[worker], (uint32_t)a.n_b * son * ES);
 
   // a row's sample and position; false: beyond the last
@@ -317,6 +322,7 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
   };
 
   float v[4][8];
+  uint32_t word[4][5], shift[4];  // bf16 runs: the words that hold an octet, and where it starts in the first
   constexpr int BP = KS * PL * 32 * NT, BPT = (BP + 255) / 256;  // weight pieces of a stage
   u32x4 wp[BPT];
   int left = 0;  // BY RUN: of the octet that is loaded, the elements in its run
@@ -334,9 +340,17 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
         if constexpr (MODE == 0) ok = tap < ntaps && base[i] != kOob;
         else ok = (uint32_t)(p0[i] + d0) < (uint32_t)g0.in_ext && (uint32_t)(p1[i] + d1) < (uint32_t)g1.in_ext &&
                   (uint32_t)(p2[i] + d2) < (uint32_t)g2.in_ext;
-        const uint32_t off = ok ? base[i] + add : kOob;
-        load4<BF16>(&v[i][0], rin, off, 0);
-        load4<BF16>(&v[i][4], rin, off + 4 * ES, 0);
+        const uint32_t off = ok ? base[i] + add + skew : kOob;
+        if constexpr (BF16) {
+          const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rin, off & ~3u, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) word[i][e] = t[e];
+          word[i][4] = __builtin_amdgcn_raw_buffer_load_b32(rin, (off & ~3u) + 16, 0, 0);
+          shift[i] = (off & 2u) * 8u;
+        } else {
+          load4<BF16>(&v[i][0], rin, off, 0);
+          load4<BF16>(&v[i][4], rin, off + 16, 0);
+        }
       }
     } else if constexpr (VEC) {
       // two groups of four channels, each within one tap
@@ -394,6 +408,19 @@ __global__ __launch_bounds__(256, 2) void corr_any_kernel(const WorkerDev* __res
     }
   };
   auto write_octets = [&](auto raw) {
+    if constexpr (RUNS && BF16) {
+      uint32_t keep[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) keep[e] = left >= 2 * e + 2 ? ~0u : left == 2 * e + 1 ? 0xffffu : 0u;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        u32x4 t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = __builtin_amdgcn_alignbit(word[i][e + 1], word[i][e], shift[i]) & keep[e];
+        *(u32x4*)(la + tid % KS * a_pitch(ROWS, BF16) + (tid / KS + i * (256 / KS)) * 16) = t;
+      }
+      return;
+    }
     if (RUNS && (len & 7) != 0) {  // (what lies behind a run is another cell's)
 #pragma unroll
       for (int e = 0; e < 8; ++e)
@@ -762,9 +789,7 @@ template <int ROWS, int NT, bool BF16>
 int pick_corr_any(distdl_plan* p, const AnyArgs& a, int by, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
 #define DISTDL_BY(MODE_, BY_) launch_corr_any<ROWS, NT, BF16, MODE_, BY_>(p, a, in_tab, out_tab, name, st)
   if (by == kByQuad) return a.mode == 0 ? DISTDL_BY(0, kByQuad) : DISTDL_BY(1, kByQuad);
-  if constexpr (!BF16) {
-    if (by == kByRun) return a.mode == 0 ? DISTDL_BY(0, kByRun) : DISTDL_BY(1, kByRun);
-  }
+  if (by == kByRun) return a.mode == 0 ? DISTDL_BY(0, kByRun) : DISTDL_BY(1, kByRun);
   return a.mode == 0 ? DISTDL_BY(0, kByOne) : DISTDL_BY(1, kByOne);
 #undef DISTDL_BY
 }
@@ -781,10 +806,10 @@ AnyLaunch any_launch(const distdl_plan* p, int mode, bool aligned) {
   l.a = any_args(p, mode, l.NT);
   AnyArgs& a = l.a;
   l.by = aligned && a.kc % 4 == 0 ? kByQuad : kByOne;
-  if (l.by == kByOne && p->dtype == DISTDL_F32) {
+  if (l.by == kByOne) {
     const int run = mode == 0 && a.dil[2] == 1 ? a.k[2] : 1, k = a.taps * a.kc;
     const int64_t runs = (int64_t)a.taps / run * ((run * a.kc + 7) / 8);
-    if (run * a.kc >= 8 && k >= 16 && (mode == 1 || (runs + 3) / 4 <= 1.3 * ((k + 31) / 32))) l.by = kByRun, a.run = run;
+    if (run * a.kc >= 8 && k >= (mode == 0 ? 16 : 33 * a.ncls) && (mode == 1 || (runs + 3) / 4 <= 1.3 * ((k + 31) / 32))) l.by = kByRun, a.run = run;
   }
   class_octets(a, flat_k(mode, l.by), a.woff, l.most, &l.k);
   // 64 rows where 256 would leave compute units idle and there is enough k for four waves (32 columns: with 64 their
@@ -846,8 +871,8 @@ double corr_any_us(const distdl_plan* p, bool backward, bool aligned) {
   const double alone = tiles <= 256 ? 0.57 : 1.0, rounds = std::max(1.0, tiles / 512);
   if (p->dtype == DISTDL_BF16) {
     const double short_ = tiles <= 256 ? 0.5 : 1.0;
-    if (l.few) return (l.by == kByQuad) ? 4.5 + rounds * (stages * 1.43 * (tiles <= 256 ? 0.8 : 1.0) + 0.9) : 3.2 + rounds * stages * 2.1;
-    if (!(l.by == kByQuad)) return 4.0 + rounds * (stages * 1.95 * short_ + 2.2) * (l.NT == 1 ? 1.0 : 1.3);
+    if (l.few) return l.by != kByOne ? 4.5 + rounds * (stages * 1.43 * (tiles <= 256 ? 0.8 : 1.0) + 0.9) : 3.2 + rounds * stages * 2.1;
+    if (l.by == kByOne) return 4.0 + rounds * (stages * 1.95 * short_ + 2.2) * (l.NT == 1 ? 1.0 : 1.3);
     return l.NT == 1 ? 4.7 + rounds * (stages * short_ + 2.7) : 4.5 + rounds * (stages * 1.28 * short_ + 4.8);
   }
   if (l.few) return l.by != kByOne ? 1.4 + rounds * (stages * 3.1 * alone + 5.6) : 4.9 + rounds * stages * 3.7 * alone;

@@ -1,4 +1,4 @@
-"""fp32 convolutions on the gather kernel whose channel count is no multiple of 4, or whose arrays are not aligned: k in octets of the
+"""Convolutions on the gather kernel whose channel count is no multiple of 4, or whose arrays are not aligned: k in octets of the
 channels of neighbouring taps, which lie one behind the other in memory."""
 import pytest
 import torch
@@ -17,13 +17,14 @@ RUNS = [
 ]
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("layer", RUNS, ids=lambda c: f"c{c[1]}-{c[2]}k{c[4]}s{c[5]}d{c[6]}x{c[3][-1]}o{c[7]}".replace(" ", ""))
-def test_runs_against_fp64(layer):
+def test_runs_against_fp64(layer, dtype):
     """A sum of K <= 400 split products is off by at most K / 16 + 2 roundings of 2^-24 of its running sum, about sqrt of that many as a
-    random walk: 1e-6 in the 2-norm is four times as much.  With an infinity in x and in dy, what does not read it stays finite."""
+    random walk: 1e-6 in the 2-norm is four times as much.  bf16: 2^-8 for the result's rounding.  With an infinity in x and in dy, what does not read it stays finite."""
     require_gpu()
     n_b, c_in, c_out, shape, k, s, dil, offset = layer
-    L = ConvLayer(n_b, c_in, c_out, shape, k, s, dil=dil, offset=offset)
+    L, tol = ConvLayer(n_b, c_in, c_out, shape, k, s, dtype, dil=dil, offset=offset), 1e-6 if dtype == torch.float32 else 2.0 ** -8
     kernels = dd.distdl_debug_conv_kernels(L.plan, offset == 0)
     assert kernels[0] == 4 and kernels[1] == 4
 
@@ -33,11 +34,11 @@ def test_runs_against_fp64(layer):
         return L.y, L.dx[L.bulk]
 
     for got, want in zip(run(), L.exact()):
-        assert float((got.double() - want).norm()) <= 1e-6 * float(want.norm())
+        assert float((got.double() - want).norm()) <= tol * float(want.norm())
     middle = tuple(n // 2 for n in L.x.shape[1:-1])
     L.x[(0, *middle, c_in - 1)] = float("inf")
     L.dy[(0, *[n // 2 for n in L.dy.shape[1:-1]], 0)] = float("-inf")
     for got, want in zip(run(), L.exact()):
         sure = torch.isfinite(want)
         assert torch.equal(torch.isfinite(got), sure)
-        assert float((got[sure].double() - want[sure]).norm()) <= 1e-6 * float(want[sure].norm())
+        assert float((got[sure].double() - want[sure]).norm()) <= tol * float(want[sure].norm())
