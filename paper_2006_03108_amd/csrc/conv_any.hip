@@ -24,7 +24,9 @@
 //     63 / 29; back with 29 channels of dy, 5^3, 2 x 31 x 29 x 35 741 / 524; bf16 22 channels, 5 x 5, 9 x 73 x 93 96 / 63.  Not
 //     for runs of less than 8, nor where their ends make more than 1.3 times the stages (2 -> 24, 5^3 67 / 81; 3 -> 22, 3 x 3,
 //     dilated 62 / 84), nor for less than half a stage (1 -> 45, 5 taps 27 / 30), or a whole one back (30 channels of dy, one tap,
-//     bf16 91 / 101).
+//     bf16 91 / 101).  bf16 quads are 8 bytes: runs of 16 and more, of whole quads, go by octets too, by quads / by octets
+//     forward of 60 -> 8, 5^3, 4 x 39 x 49 x 30 578 / 402, back with 60 channels, 5 x 5, 4 x 425 x 661 650 / 514, but 4 -> 44, 3^3,
+//     72 x 85 x 77, whose runs of 12 end in half an octet, 21 / 24.
 //     In those a lane per row, and the offset of a k, the same for all lanes, goes into the scalar offset of the load.
 //   wgrad_any_kernel: rows are k, columns output channels, the sum runs over output positions; the offset that all
 //     lanes share is that of the position.  Every (worker, chunk of positions) writes a partial, which also holds the
@@ -805,11 +807,14 @@ AnyLaunch any_launch(const distdl_plan* p, int mode, bool aligned) {
   l.NT = nt_of(mode == 0 ? p->n_co : p->n_ci);
   l.a = any_args(p, mode, l.NT);
   AnyArgs& a = l.a;
-  l.by = aligned && a.kc % 4 == 0 ? kByQuad : kByOne;
-  if (l.by == kByOne) {
+  const bool quads = aligned && a.kc % 4 == 0, bf16 = p->dtype == DISTDL_BF16;
+  l.by = quads ? kByQuad : kByOne;
+  if (!quads || bf16) {
     const int run = mode == 0 && a.dil[2] == 1 ? a.k[2] : 1, k = a.taps * a.kc;
-    const int64_t runs = (int64_t)a.taps / run * ((run * a.kc + 7) / 8);
-    if (run * a.kc >= 8 && k >= (mode == 0 ? 16 : 33 * a.ncls) && (mode == 1 || (runs + 3) / 4 <= 1.3 * ((k + 31) / 32))) l.by = kByRun, a.run = run;
+    const int64_t runs = (int64_t)a.taps / run * ((run * a.kc + 7) / 8), stages = (runs + 3) / 4;
+    if (run * a.kc >= (quads ? 16 : 8) && k >= (mode == 0 && !quads ? 16 : 33 * a.ncls) &&
+        (mode == 1 || stages <= (quads ? 1.1 : 1.3) * ((k + 31) / 32)))
+      l.by = kByRun, a.run = run;
   }
   class_octets(a, flat_k(mode, l.by), a.woff, l.most, &l.k);
   // 64 rows where 256 would leave compute units idle and there is enough k for four waves (32 columns: with 64 their
