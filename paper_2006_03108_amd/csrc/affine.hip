@@ -176,8 +176,8 @@ static void bwd_direct(distdl_affine_plan* p, bool has_db, hipStream_t st_) {
 // decides is that those start a tile at a time, and split a long K over two launches; with many tiles, or matrix instructions in
 // earnest, they are the faster ones.  us, tiled / small, forward and back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 295 x 624 -> 28,
 // 2 x 1 10.2 / 6.4 and 12.9 / 7.7; 37 x 2000 -> 1001, 2 x 3 12.9 / 10.3 and 18.1 / 20.5; 327 x 84 -> 7210, 2 x 2 18.9 / 25.1 and 25.5 / 46.9; bf16 of
-// odd rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4 and 16.6 / 12.0.  Of 138 layers 99 go forward that way and 67 back: 1.17 and 1.09 times as fast
-// in the mean over all of them, the better of the two would be 1.18 and 1.12.
+// odd rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4 and 16.6 / 12.0.  Over 120 layers of 1 to 100 rows the choice is 1.26 and 1.13
+// times as fast as the tiled kernels in the mean, and up to 1.12 times slower in three calls of 240.
 static double joined(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
 static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& blocks, bool bf16) {
   // (bf16 rows of whole 16-byte pieces take 7 to 9 us either way)
@@ -198,9 +198,12 @@ static bool small_bwd(distdl_affine_plan* p, const std::vector<GemmBlock>& bx, c
   int known = p->small_bwd[vec][tiles].load(std::memory_order_relaxed);
   if (known < 0) {
     const double us = affine_small_bwd_us(bx, bw, bf16), x = gemm_split_plan(bx, vec).us, w = gemm_split_plan(bw, vec).us;
-    // (bf16 tiles: two launches and more, 12 to 20 us; 29 x 32 -> 816 on 1 x 2 15.1 / 9.0, 73 x 176 -> 192 on 2 x 2 13.6 / 9.7, 299 x 3440 -> 96 16.6 / 14.7)
+    // (bf16 tiles: two launches and more, 12 to 20 us; 29 x 32 -> 816 on 1 x 2 15.1 / 9.0, 73 x 176 -> 192 on 2 x 2 13.6 / 9.7,
+    // 299 x 3440 -> 96 16.6 / 14.7)
     const double tiled = tiles ? 12.6 : joined(10.4, 1.28 * std::max(x, w) + 1.37 * std::min(x, w));
-    known = us < 0.95 * tiled ? 1 : std::isfinite(us) ? 0 : 2;
+    // (a bf16 dW leaves value by value: above 20 us, 20 x 4901 -> 1974 42 / 49, 9 x 2836 -> 3673 on 1 x 2 45 / 48, that is what
+    // a call takes)
+    known = us < 0.95 * tiled && (!bf16 || us < 20) ? 1 : std::isfinite(us) ? 0 : 2;
     p->small_bwd[vec][tiles].store(known, std::memory_order_relaxed);
   }
   return known == 1 || (p->route > 0 && known == 0);

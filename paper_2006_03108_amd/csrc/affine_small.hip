@@ -471,7 +471,8 @@ double affine_small_fwd_us(const std::vector<GemmBlock>& blocks, bool bf16) {
   if (!in_range(blocks, bf16, true, true)) return INFINITY;
   const SmallShape s = best_fwd(nullptr, blocks, bf16);
   const size_t arrays = blocks.size() * (blocks[0].nseg + 1) + blocks[0].nseg;
-  return joined(6.8 + 0.13 * arrays, std::max(1.0, s.wgs / 512.0) * product_us(s, 2.1, 0.12, bf16 ? 0.48 : 0.60, 0.78));
+  const double us = std::max(1.0, s.wgs / 512.0) * product_us(s, 2.1, 0.12, bf16 ? 0.48 : 0.60, 0.78);
+  return joined(6.8 + 0.13 * arrays, us * (bf16 && !words(blocks) ? 1.5 : 1.0));  // (rows of odd bf16 come value by value)
 }
 double affine_small_bwd_us(const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16) {
   if (!in_range(bx, bf16, true, false) || !in_range(bw, bf16, false, false)) return INFINITY;
