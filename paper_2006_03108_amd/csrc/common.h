@@ -156,8 +156,14 @@ struct HaloTaskDev {
 
 // Host tables on their way to one block of device memory, each at a multiple of 16 bytes.
 struct HostTables {
+  struct Large {
+    const void* from;
+    size_t n;
+    void** out;
+  };
   std::vector<char> bytes;
   std::vector<std::pair<void**, size_t>> places;  // where the device address of a table goes, its offset
+  std::vector<Large> large;                       // behind these, a copy of its own each
   template <class T>
   void add(const std::vector<T>& v, T** out) {
     *out = nullptr;
@@ -166,6 +172,14 @@ struct HostTables {
     bytes.resize(at + (n + 15) / 16 * 16);
     std::memcpy(bytes.data() + at, v.data(), n);
     places.emplace_back((void**)out, at);
+  }
+  // A vector that is there until to_device.  (Gathered with the others the 1.7 MB of a plan of 64 workers of 64^3 cells cost more in
+  // fresh host pages, 100 us, than the copies that were saved.)
+  template <class T>
+  void add_lasting(const std::vector<T>& v, T** out) {
+    if (v.size() * sizeof(T) < 65536) return add(v, out);
+    *out = nullptr;
+    large.push_back({v.data(), v.size() * sizeof(T), (void**)out});
   }
   int to_device(char** block);
 };

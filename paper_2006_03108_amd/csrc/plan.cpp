@@ -381,20 +381,28 @@ static int add_table(const distdl_plan& p, TaskTable& tt, HostTables& to) {
   }
   to.add(tasks, &tt.d_tasks);
   to.add(views, &tt.d_views);
-  to.add(tt.blocks, &tt.d_blocks);
+  to.add_lasting(tt.blocks, &tt.d_blocks);
   return DISTDL_OK;
 }
 
 int HostTables::to_device(char** block) {
   *block = nullptr;
-  if (bytes.empty()) return DISTDL_OK;
+  size_t total = bytes.size();
+  for (const Large& l : large) total += (l.n + 15) / 16 * 16;
+  if (total == 0) return DISTDL_OK;
   char* dev = nullptr;
-  DISTDL_HIP_TRY(hipMalloc((void**)&dev, bytes.size()));
-  if (hipError_t e = hipMemcpy(dev, bytes.data(), bytes.size(), hipMemcpyHostToDevice); e != hipSuccess) {
+  DISTDL_HIP_TRY(hipMalloc((void**)&dev, total));
+  auto copy = [&](size_t at, const void* from, size_t n) { return n > 0 ? hipMemcpy(dev + at, from, n, hipMemcpyHostToDevice) : hipSuccess; };
+  size_t at = bytes.size();
+  hipError_t e = copy(0, bytes.data(), at);
+  for (size_t i = 0; i < large.size() && e == hipSuccess; at += (large[i].n + 15) / 16 * 16, ++i) e = copy(at, large[i].from, large[i].n);
+  if (e != hipSuccess) {
     (void)hipFree(dev);
     return set_error(DISTDL_ERR_HIP, "copy of a plan's tables failed: %s", hipGetErrorString(e));
   }
-  for (const auto& [out, at] : places) *out = dev + at;
+  for (const auto& [out, off] : places) *out = dev + off;
+  at = bytes.size();
+  for (const Large& l : large) *l.out = dev + at, at += (l.n + 15) / 16 * 16;
   *block = dev;
   return DISTDL_OK;
 }
