@@ -817,6 +817,8 @@ AnyLaunch any_launch(const distdl_plan* p, int mode, bool aligned) {
       l.by = kByRun, a.run = run;
   }
   class_octets(a, flat_k(mode, l.by), a.woff, l.most, &l.k);
+  // (the estimates are of quads: octets in their place take no longer, whatever the ends of the runs add)
+  if (int most; quads) class_octets(a, true, nullptr, most, &l.k);
   // 64 rows where 256 would leave compute units idle and there is enough k for four waves (32 columns: with 64 their
   // accumulators and the larger stages of weights do not fit the registers)
   const int64_t pos = positions_max(p, a);
