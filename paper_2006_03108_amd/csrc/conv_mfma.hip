@@ -552,9 +552,20 @@ __global__ __launch_bounds__(256, (PA <= 4 && MT == 2 && MODE == 0 && NT > 0) ? 
 //   dst[ntile][t0][cc][t1][t2][h][nn][j] = W[tap(t0,t1,t2)][k = cc*8 + 4h + j][n = ntile*32 + nn]
 // with W[tap][k][n] = w[n][k][tap] (forward: n = co, k = ci) or w[k][n][tap]
 // (data gradient: k = co, n = ci), zero beyond the channel counts.
-template <int MODE>
-__global__ __launch_bounds__(256) void corr_weights_kernel(const void* __restrict__ w, float* __restrict__ dst,
-                                                           CorrArgs a, int ci_n, int co_n, int taps, int k1, int k2) {
+// The classes of a data gradient (blockIdx.y; their dst is a.wt) share a launch; one each was 4 to 5 us and what the stream waits
+// between them.  Adjoints of strided bf16 layers, us, before / now: 8 -> 40 channels, 5^3, 70 x 97 x 65 171 / 152; 16 -> 8, 5 x 5,
+// 2 x 271 x 252 72 / 64; 32 -> 32, 5^3, 256^3 1971 / 1947.
+constexpr int kWeightSets = 8;
+template <int N>
+struct CorrWeightSets {  // (one: a forward pass does not hand 3 KB over)
+  CorrArgs a[N];
+};
+static_assert(sizeof(CorrWeightSets<kWeightSets>) <= 3840, "kernel arguments");
+template <int MODE, int N>
+__global__ __launch_bounds__(256) void corr_weights_kernel(const void* __restrict__ w, CorrWeightSets<N> sets, int ci_n, int co_n, int taps,
+                                                           int k1, int k2) {
+  const CorrArgs& a = sets.a[N == 1 ? 0 : blockIdx.y];
+  float* __restrict__ const dst = const_cast<float*>((const float*)a.wt);
   // elements per 16-byte piece: 4 floats, or 8 bf16 when the kernel multiplies in bf16
   constexpr int PE = MODE == 2 ? 8 : 4, CK = 2 * PE;
   const int ncc = (a.kc + CK - 1) / CK;
@@ -1375,8 +1386,14 @@ static int resident_workgroups(const void* fn, int lds) {
   return n;
 }
 
-static int launch_corr(distdl_plan* p, CorrArgs a, const void* w, float* wscratch, const void* bias, void** in_tab,
-                       void** out_tab, const char* name, hipStream_t st) {
+struct CorrLaunch {
+  CorrArgs a;
+  CorrVariant kv;
+  int mode, lds;
+  size_t pieces;  // of 256 threads of the weights' launch
+};
+// a -> its launch; no tiles: there is nothing to do
+static int plan_corr(distdl_plan* p, CorrArgs a, float* wscratch, const void* bias, CorrLaunch& l) {
   const int mode = corr_mode(p, a);
   const int mt = corr_window(p, a);
   if (mt == 0) return set_error(DISTDL_ERR_UNSUPPORTED, "conv: kernel footprint does not fit in LDS");  // corr_mfma_supported() rules this out
@@ -1419,30 +1436,38 @@ static int launch_corr(distdl_plan* p, CorrArgs a, const void* w, float* wscratc
     }
   }
   a.tiles_max = (int32_t)max_tiles(p, a);
-  if (a.tiles_max == 0) return DISTDL_OK;
   a.wt = wscratch;
   a.bias = bias;
-  const int taps = p->ksize[0] * p->ksize[1] * p->ksize[2];
   const size_t welems = corr_weight_elems(a);
   a.tapinfo = (const int*)(wscratch + welems);
-  {
-    ProfScope prof("conv_relayout_w", st);
-    const dim3 wgrid((unsigned)std::max<size_t>(1, (welems * (mode == 2 ? 2 : 1) + 255) / 256));
-    if (mode == 2)
-      hipLaunchKernelGGL(corr_weights_kernel<2>, wgrid, dim3(256), 0, st, w, wscratch, a, (int)p->n_ci, (int)p->n_co,
-                         taps, p->ksize[1], p->ksize[2]);
-    else if (mode == 1)
-      hipLaunchKernelGGL(corr_weights_kernel<1>, wgrid, dim3(256), 0, st, w, wscratch, a, (int)p->n_ci, (int)p->n_co,
-                         taps, p->ksize[1], p->ksize[2]);
-    else
-      hipLaunchKernelGGL(corr_weights_kernel<0>, wgrid, dim3(256), 0, st, w, wscratch, a, (int)p->n_ci, (int)p->n_co,
-                         taps, p->ksize[1], p->ksize[2]);
-  }
-  int64_t blocks = (int64_t)a.tiles_max * p->n_workers;
+  l = CorrLaunch{a, kv, mode, lds, std::max<size_t>(1, (welems * (mode == 2 ? 2 : 1) + 255) / 256)};
+  return DISTDL_OK;
+}
+
+// The weights of n <= N launches of one mode
+template <int N>
+static void launch_corr_weights(const distdl_plan* p, const CorrLaunch* l, int n, const void* w, hipStream_t st) {
+  CorrWeightSets<N> sets{};
+  size_t most = 0;
+  for (int i = 0; i < n; ++i) sets.a[i] = l[i].a, most = std::max(most, l[i].pieces);
+  const int taps = p->ksize[0] * p->ksize[1] * p->ksize[2];
+  const dim3 grid((unsigned)most, (unsigned)n);
+  ProfScope prof("conv_relayout_w", st);
+  auto launch = [&](auto mode) {
+    hipLaunchKernelGGL((corr_weights_kernel<decltype(mode)::value, N>), grid, dim3(256), 0, st, w, sets, (int)p->n_ci, (int)p->n_co, taps,
+                       p->ksize[1], p->ksize[2]);
+  };
+  if (l->mode == 2) launch(std::integral_constant<int, 2>{});
+  else if (l->mode == 1) launch(std::integral_constant<int, 1>{});
+  else launch(std::integral_constant<int, 0>{});
+}
+
+static int launch_corr(distdl_plan* p, CorrLaunch& l, void** in_tab, void** out_tab, const char* name, hipStream_t st) {
+  int64_t blocks = (int64_t)l.a.tiles_max * p->n_workers;
   blocks = (blocks + 7) / 8 * 8;
   ProfScope prof(name, st);
-  void* kargs[] = {(void*)&p->d_workers, (void*)&in_tab, (void*)&out_tab, (void*)&a};
-  DISTDL_HIP_TRY(hipLaunchKernel(kv.fn, dim3((unsigned)blocks), dim3(256), kargs, (size_t)lds, st));
+  void* kargs[] = {(void*)&p->d_workers, (void*)&in_tab, (void*)&out_tab, (void*)&l.a};
+  DISTDL_HIP_TRY(hipLaunchKernel(l.kv.fn, dim3((unsigned)blocks), dim3(256), kargs, (size_t)l.lds, st));
   return DISTDL_OK;
 }
 
@@ -1454,7 +1479,10 @@ int conv_fwd_mfma(distdl_plan* p, const void* w, const void* bias, hipStream_t s
   CorrArgs a = forward_args(p);
   int rc = ensure_wscratch(p, std::max(corr_scratch_elems(a), bwd_scratch_elems(p)), st);
   if (rc) return rc;
-  return launch_corr(p, a, w, p->d_wt, bias, p->tab_x.dev, p->tab_y.dev, "conv_fwd_mfma", st);
+  CorrLaunch l;
+  if ((rc = plan_corr(p, a, p->d_wt, bias, l)) || l.a.tiles_max == 0) return rc;
+  launch_corr_weights<1>(p, &l, 1, w, st);
+  return launch_corr(p, l, p->tab_x.dev, p->tab_y.dev, "conv_fwd_mfma", st);
 }
 
 size_t bwd_scratch_elems(const distdl_plan* p) {
@@ -1474,15 +1502,24 @@ int conv_bwd_data_mfma(distdl_plan* p, const void* w, hipStream_t st) {
   int rc = ensure_wscratch(p, std::max(corr_scratch_elems(fa), bwd_scratch_elems(p)), st);
   if (rc) return rc;
   size_t at = 0;
+  std::vector<CorrLaunch> launches;
   for (int p0 = 0; p0 < p->stride[0]; ++p0)
     for (int p1 = 0; p1 < p->stride[1]; ++p1)
       for (int p2 = 0; p2 < p->stride[2]; ++p2) {
         const int par[3] = {p0, p1, p2};
-        CorrArgs a = class_args(p, par);
-        if ((rc = launch_corr(p, a, w, p->d_wt + at, nullptr, p->tab_dy.dev, p->tab_dx.dev, "conv_bwd_data_mfma", st)))
-          return rc;
+        const CorrArgs a = class_args(p, par);
+        CorrLaunch l;
+        if ((rc = plan_corr(p, a, p->d_wt + at, nullptr, l))) return rc;
+        if (l.a.tiles_max > 0) launches.push_back(l);
         at += corr_scratch_elems(a);
       }
+  for (size_t first = 0, n; first < launches.size(); first += n) {
+    for (n = 1; first + n < launches.size() && n < kWeightSets && launches[first + n].mode == launches[first].mode;) ++n;
+    if (n == 1) launch_corr_weights<1>(p, &launches[first], 1, w, st);
+    else launch_corr_weights<kWeightSets>(p, &launches[first], (int)n, w, st);
+  }
+  for (CorrLaunch& l : launches)
+    if ((rc = launch_corr(p, l, p->tab_dy.dev, p->tab_dx.dev, "conv_bwd_data_mfma", st))) return rc;
   return DISTDL_OK;
 }
 
