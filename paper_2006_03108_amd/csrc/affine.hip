@@ -27,7 +27,7 @@ struct distdl_affine_plan {
   distdl::DevArray<distdl::ColsumBlock> g_db;
   distdl::StreamScratch partial;  // fp32 partial tiles of K-split GEMM launches
   int route = -1;                  // 0, 1: the tiled or the small kernels for every call that they take (distdl_debug_affine_route)
-  std::atomic<int8_t> small_fwd[2] = {{-1}, {-1}}, small_bwd[2][2] = {{{-1}, {-1}}, {{-1}, {-1}}};  // choices by alignment, once made: 0, 1, 2 not taken at all
+  std::atomic<int8_t> small_fwd[2] = {{-1}, {-1}}, small_bwd[2][2] = {{{-1}, {-1}}, {{-1}, {-1}}};  // choices by alignment, once made
 };
 
 namespace distdl {
@@ -180,19 +180,20 @@ static void bwd_direct(distdl_affine_plan* p, bool has_db, hipStream_t st_) {
 // times as fast as the tiled kernels in the mean, and up to 1.12 times slower in three calls of 240.
 static double joined(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
 static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& blocks, bool bf16) {
+  if (p->route == 0 || !gemm_split_usable(blocks, bf16, true, true)) return false;  // (their range is the same)
   // (bf16 rows of whole 16-byte pieces take 7 to 9 us either way)
-  if (p->route == 0 || (p->route < 0 && bf16 && gemm_mfma_usable(blocks, bf16, true, true))) return false;
+  if (p->route < 0 && bf16 && gemm_mfma_usable(blocks, bf16, true, true)) return false;
   const bool vec = gemm_split_vec(blocks, bf16, true, true);
   int known = p->small_fwd[vec].load(std::memory_order_relaxed);
   if (known < 0) {
     const double us = affine_small_fwd_us(blocks, bf16);
-    known = us < 0.95 * joined(9.2, 1.6 + 1.1 * gemm_split_plan(blocks, vec).us) ? 1 : std::isfinite(us) ? 0 : 2;
+    known = us < 0.95 * joined(9.2, 1.6 + 1.1 * gemm_split_plan(blocks, vec).us);
     p->small_fwd[vec].store(known, std::memory_order_relaxed);
   }
-  return known == 1 || (p->route > 0 && known == 0);
+  return known || p->route > 0;
 }
 static bool small_bwd(distdl_affine_plan* p, const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16) {
-  if (p->route == 0) return false;
+  if (p->route == 0 || !gemm_split_usable(bx, bf16, true, false) || !gemm_split_usable(bw, bf16, false, false)) return false;
   const bool vec = gemm_split_vec(bx, bf16, true, false) && gemm_split_vec(bw, bf16, false, false);
   const bool tiles = bf16 && gemm_mfma_usable(bx, bf16, true, false) && gemm_mfma_usable(bw, bf16, false, false);
   int known = p->small_bwd[vec][tiles].load(std::memory_order_relaxed);
@@ -203,10 +204,10 @@ static bool small_bwd(distdl_affine_plan* p, const std::vector<GemmBlock>& bx, c
     const double tiled = tiles ? 12.6 : joined(10.4, 1.28 * std::max(x, w) + 1.37 * std::min(x, w));
     // (a bf16 dW leaves value by value: above 20 us, 20 x 4901 -> 1974 42 / 49, 9 x 2836 -> 3673 on 1 x 2 45 / 48, that is what
     // a call takes)
-    known = us < 0.95 * tiled && (!bf16 || us < 20) ? 1 : std::isfinite(us) ? 0 : 2;
+    known = us < 0.95 * tiled && (!bf16 || us < 20);
     p->small_bwd[vec][tiles].store(known, std::memory_order_relaxed);
   }
-  return known == 1 || (p->route > 0 && known == 0);
+  return known || p->route > 0;
 }
 // Whether a dW lies on weights, which dx is made of in the same launch.
 static bool on_weights(const distdl_affine_plan* p, const void* const W[], void* const dW[]) {

@@ -6,7 +6,7 @@
 
 namespace distdl {
 
-// Estimated time of a call, launch and all (us); infinite: not taken
+// Estimated time of a call, launch and all (us).  All of them take what gemm_split_usable says: up to eight segments, 31-bit byte offsets.
 double affine_small_fwd_us(const std::vector<GemmBlock>& blocks, bool bf16);
 double affine_small_bwd_us(const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16);
 int launch_affine_small_fwd(const GemmBlock* d_blocks, const std::vector<GemmBlock>& blocks, bool bf16, hipStream_t st);

@@ -457,9 +457,6 @@ static SmallShape best_dw(const GemmBlock* d, const std::vector<GemmBlock>& b, b
   return shape_us(shared, bf16) < shape_us(own, bf16) ? shared : own;
 }
 
-static bool in_range(const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc) {
-  return gemm_split_usable(blocks, bf16, a_kc, b_kc);  // 31-bit byte offsets, up to eight segments
-}
 // Estimated times of the calls, fitted to 160 layers of 1 to 1024 rows and 10 to 8192 features; four fifths are within 13 %.  A product:
 // a start, and a wave's chunks with their loads and matrix instructions, which take longer with two workgroups on a compute unit.
 // With it, by a fourth power: what the host takes, more for each array of the call.
@@ -468,14 +465,12 @@ static double product_us(const SmallShape& s, double start, double chunk, double
   return start + s.chunks * (chunk + tile * s.mt * s.nt) * (1 + shared * std::min(s.wgs / 256.0, 2.0));
 }
 double affine_small_fwd_us(const std::vector<GemmBlock>& blocks, bool bf16) {
-  if (!in_range(blocks, bf16, true, true)) return INFINITY;
   const SmallShape s = best_fwd(nullptr, blocks, bf16);
   const size_t arrays = blocks.size() * (blocks[0].nseg + 1) + blocks[0].nseg;
   const double us = std::max(1.0, s.wgs / 512.0) * product_us(s, 2.1, 0.12, bf16 ? 0.48 : 0.60, 0.78);
   return joined(6.8 + 0.13 * arrays, us * (bf16 && !words(blocks) ? 1.5 : 1.0));  // (rows of odd bf16 come value by value)
 }
 double affine_small_bwd_us(const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16) {
-  if (!in_range(bx, bf16, true, false) || !in_range(bw, bf16, false, false)) return INFINITY;
   const SmallShape x = best_dx(nullptr, bx, bf16), w = best_dw(nullptr, bw, bf16);
   const double tx = product_us(x, 2.05, 0.64, bf16 ? 0.32 : 0.29, 0.54), tw = product_us(w, 1.46, 0.78, bf16 ? 0.17 : 0.48, 0.46);
   const double longest = std::max(tx, tw), all = tx * x.wgs / 512.0 + tw * w.wgs / 512.0;

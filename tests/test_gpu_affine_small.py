@@ -80,3 +80,36 @@ def test_small_affine_against_fp64(n_b, n_fi, n_fo, P_fo, P_fi, dtype, offset):
         step()
         for a, e in zip(replayed, results()):
             assert all(map(torch.equal, a, e))
+
+
+@pytest.mark.parametrize("route", [-1, 1], ids=["chosen", "small"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("P_fo,P_fi", [(1, 9), (9, 1), (9, 9)])
+def test_more_workers_than_a_block_has_segments(P_fo, P_fi, dtype, route):
+    """A block's sum has room for eight segments: of nine workers the small kernels take neither side, and no estimate reads the
+    ninth.  fp32 sums of at most 72 products in a chain: 72 roundings of 2^-24; bf16: the result's 2^-8."""
+    require_gpu()
+    n_b, n_fi, n_fo = 5, 72, 63
+    g = torch.Generator(device="cuda").manual_seed(9)
+    new = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(dtype)
+    size = lambda s: s.stop - s.start
+    rows, cols = layers.feature_blocks(n_fo, P_fo), layers.feature_blocks(n_fi, P_fi)
+    x, dy = [new(n_b, size(c)) for c in cols], [new(n_b, size(r)) for r in rows]
+    W, b = [new(size(r), size(c)) for r in rows for c in cols], [new(size(r)) for r in rows]
+    y, dx, dW, db = ([torch.full_like(t, 7.0) for t in ts] for ts in (dy, x, W, b))
+    plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, dtype)
+    dd.distdl_debug_affine_route(plan, route)
+    dd.distdl_profile_enable(True)
+    dd.distdl_profile_report()
+    dd.distdl_affine_fwd(plan, x, W, b, y)
+    dd.distdl_affine_bwd(plan, x, W, dy, dx, dW, db)
+    names = set(dd.distdl_profile_report())
+    dd.distdl_profile_enable(False)
+    assert P_fi <= 8 or "affine_fwd_small" not in names
+    assert P_fo <= 8 or "affine_bwd_small" not in names
+    xd, dyd = torch.cat(x, 1).double(), torch.cat(dy, 1).double()
+    Wd = torch.cat([torch.cat(W[i * P_fi:(i + 1) * P_fi], 1) for i in range(P_fo)]).double()
+    got = (torch.cat(y, 1), torch.cat(dx, 1), torch.cat([torch.cat(dW[i * P_fi:(i + 1) * P_fi], 1) for i in range(P_fo)]), torch.cat(db))
+    want = (xd @ Wd.t() + torch.cat(b).double(), dyd @ Wd, dyd.t() @ xd, dyd.sum(0))
+    for name, u, v in zip(("y", "dx", "dW", "db"), got, want):
+        assert float((u.double() - v).norm()) <= (72 * 2.0 ** -24 if dtype == torch.float32 else 2.0 ** -8 + 1e-5) * float(v.norm()), name
