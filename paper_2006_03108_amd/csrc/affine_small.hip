@@ -218,8 +218,15 @@ __device__ __forceinline__ void small_tiles(BlockPtr gb, int m0, int n0, SumOf<B
 #pragma unroll
     for (int d = 0; d < 2; ++d) {
       if (c >= total) break;
-      if constexpr (A_KC) set[d].a.stage(la, lane);
-      if constexpr (B_KC) set[d].b.stage(lb, lane);
+      if constexpr (A_KC || B_KC) {
+        // (the wave's lanes read what others of them wrote: its LDS instructions are carried out in order, and so they have to be compiled)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if constexpr (A_KC) set[d].a.stage(la, lane);
+        if constexpr (B_KC) set[d].b.stage(lb, lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
       if constexpr (A_KC && B_KC) {
         Set at;
         at.left = set[d].left;
