@@ -450,7 +450,8 @@ int distdl_debug_conv_split(const distdl_plan* plan, int backward, int32_t out[5
 /* Whether distdl_conv_fwd (out[0]) and distdl_conv_bwd (out[1]) of this plan
  * run in one launch (distdl_conv_bwd: one or two) instead of as the kernels
  * that distdl_debug_conv_kernels names with H and H* around them; the
- * distdl_conv_local_* calls always run those.  aligned: as there. */
+ * distdl_conv_local_* calls always run those.  aligned: as there; 2: all
+ * arrays but the weights are. */
 int distdl_debug_conv_fused(const distdl_plan* plan, int aligned, int32_t out[2]);
 /* For tests: which kernels the calls of this affine plan take, where they can:
  * 0 the tiled ones, 1 those of small layers, -1 (as created) the ones that are

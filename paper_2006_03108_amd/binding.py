@@ -384,7 +384,7 @@ def distdl_debug_conv_split(plan, backward=False):
 
 
 def distdl_debug_conv_fused(plan, aligned=True):
-    """Whether the forward pass and the adjoint run in one launch, H and H* among them."""
+    """Whether the forward pass and the adjoint run in one launch, H and H* among them.  aligned: False, True, or 2: all but the weights."""
     out = (C.c_int32 * 2)()
     _check(lib.distdl_debug_conv_fused(plan.handle, int(aligned), out))
     return bool(out[0]), bool(out[1])

@@ -325,7 +325,8 @@ struct distdl_plan {
   mutable std::shared_ptr<void> corr16_plan;       // the shapes of conv_small.hip's launches, ditto
   mutable std::shared_ptr<void> wgrad_split_plan;  // the shape of conv_wsplit.hip's launch, once asked for
   mutable int8_t corr_kernel[2][2][2] = {{{-1, -1}, {-1, -1}}, {{-1, -1}, {-1, -1}}};  // conv.hip's choice by direction and alignment, once asked for
-  mutable int8_t fused_kernel[2][2][2] = {{{-1, -1}, {-1, -1}}, {{-1, -1}, {-1, -1}}};  // whether a direction is one launch, by 16-byte accesses and alignment, ditto
+  mutable int8_t fused_kernel[2][2][2][2] = {{{{-1, -1}, {-1, -1}}, {{-1, -1}, {-1, -1}}},
+                                             {{{-1, -1}, {-1, -1}}, {{-1, -1}, {-1, -1}}}};  // whether a direction is one launch, by 16-byte accesses and both alignments, ditto
   mutable int wgrad_kernel[2] = {-1, -1};          // conv.hip's choice without and with 16-byte aligned tensors, ditto
   mutable int corr_mfma_ok = -1;  // cached answer of corr_mfma_supported(): -1 not asked yet
 

@@ -384,7 +384,7 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
 // back: 1.36 and 1.35 times as fast in the mean, where the better of the two would be 1.40 and 1.41, a score of them up to 1.4
 // times slower.
 static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool aligned, bool w_aligned) {
-  int8_t& known = p->fused_kernel[backward][vec][aligned];
+  int8_t& known = p->fused_kernel[backward][vec][aligned][w_aligned];
   if (known >= 0) return known != 0;
   const double us = conv_fused_us(p, backward, vec);
   const bool boxes = !p->fwd1.blocks.empty() || !p->fwd16.blocks.empty();
@@ -531,7 +531,7 @@ int distdl_debug_conv_fused(const distdl_plan* plan, int aligned, int32_t out[2]
   if (!plan || !out) return set_error(DISTDL_ERR_NULL, "conv_fused: null argument");
   if (plan->explicit_halo) return set_error(DISTDL_ERR_UNSUPPORTED, "conv_fused: plan has no kernel");
   const bool vec = aligned && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
-  for (int backward = 0; backward < 2; ++backward) out[backward] = choose_fused(plan, backward != 0, vec, aligned != 0, aligned != 0);
+  for (int backward = 0; backward < 2; ++backward) out[backward] = choose_fused(plan, backward != 0, vec, aligned != 0, backward || aligned == 1);
   return DISTDL_OK;
 }
 
