@@ -457,6 +457,10 @@ int distdl_debug_conv_fused(const distdl_plan* plan, int aligned, int32_t out[2]
  * 0 the tiled ones, 1 those of small layers, -1 (as created) the ones that are
  * estimated to be faster. */
 int distdl_debug_affine_route(distdl_affine_plan* plan, int route);
+/* Whether distdl_affine_fwd (out[0]) and distdl_affine_bwd (out[1]) of this
+ * plan take the kernels of small layers for arrays that are aligned to `align`
+ * bytes and no more (a multiple of the element size). */
+int distdl_debug_affine_small(distdl_affine_plan* plan, int align, int32_t out[2]);
 /* Rows (taps x input channels) of a tile of the gather kernel's weight
  * gradient, whether or not it is what runs: 64 or 256, 0 where it does not take
  * the layer. */

@@ -73,6 +73,7 @@ _SIGS = {
     "distdl_debug_conv_split": [_vp, _i, _p32],
     "distdl_debug_conv_fused": [_vp, _i, _p32],
     "distdl_debug_affine_route": [_vp, _i],
+    "distdl_debug_affine_small": [_vp, _i, _p32],
     "distdl_debug_conv_wgrad_rows": [_vp, _p32],
     "distdl_affine_plan_create": [C.POINTER(_vp), _i64, _i64, _i64, _i, _i, _i],
     "distdl_affine_plan_destroy": [_vp],
@@ -393,6 +394,13 @@ def distdl_debug_conv_fused(plan, aligned=True):
 def distdl_debug_affine_route(plan, route):
     """0: the tiled kernels, 1: those of small layers, -1: the ones estimated to be faster."""
     _check(lib.distdl_debug_affine_route(plan.handle, route))
+
+
+def distdl_debug_affine_small(plan, align=16):
+    """Whether the forward pass and the adjoint take the kernels of small layers, for arrays aligned to `align` bytes and no more."""
+    out = (C.c_int32 * 2)()
+    _check(lib.distdl_debug_affine_small(plan.handle, align, out))
+    return bool(out[0]), bool(out[1])
 
 
 def distdl_debug_conv_wgrad_rows(plan):

@@ -172,6 +172,54 @@ static void bwd_direct(distdl_affine_plan* p, bool has_db, hipStream_t st_) {
                        st_, p->tab_dy.dev, p->tab_db.dev, p->d_sizes, (int)p->n_b);
 }
 
+// y_i = sum_j x_j W_ij^T + b_i, the sum over j inside the K loop.  (More workers than a block has segments: nseg says so.)
+static std::vector<GemmBlock> blocks_y(const distdl_affine_plan* p, const void* const x[], const void* const W[], const void* const b[],
+                                       void* const y[]) {
+  std::vector<GemmBlock> blocks(p->P_fo);
+  for (int i = 0; i < p->P_fo; ++i) {
+    GemmBlock& g = blocks[i];
+    std::memset(&g, 0, sizeof g);
+    g.M = (int32_t)p->n_b;
+    g.N = g.ldc = (int32_t)p->fo_size[i];
+    g.c = y[i];
+    g.bias = b ? b[i] : nullptr;
+    g.nseg = std::min(p->P_fi, kGemmMaxSeg + 1);
+    for (int j = 0; j < p->P_fi && j < kGemmMaxSeg; ++j)
+      g.seg[j] = GemmSeg{x[j], W[i * p->P_fi + j], (int32_t)p->fi_size[j], (int32_t)p->fi_size[j], (int32_t)p->fi_size[j], 0};
+  }
+  return blocks;
+}
+// dx_j = sum_i dy_i W_ij
+static std::vector<GemmBlock> blocks_dx(const distdl_affine_plan* p, const void* const dy[], const void* const W[], void* const dx[]) {
+  std::vector<GemmBlock> blocks(p->P_fi);
+  for (int j = 0; j < p->P_fi; ++j) {
+    GemmBlock& g = blocks[j];
+    std::memset(&g, 0, sizeof g);
+    g.M = (int32_t)p->n_b;
+    g.N = g.ldc = (int32_t)p->fi_size[j];
+    g.c = dx[j];
+    g.nseg = std::min(p->P_fo, kGemmMaxSeg + 1);
+    for (int i = 0; i < p->P_fo && i < kGemmMaxSeg; ++i)
+      g.seg[i] = GemmSeg{dy[i], W[i * p->P_fi + j], (int32_t)p->fo_size[i], (int32_t)p->fo_size[i], (int32_t)p->fi_size[j], 0};
+  }
+  return blocks;
+}
+// dW_ij = dy_i^T x_j
+static std::vector<GemmBlock> blocks_dw(const distdl_affine_plan* p, const void* const x[], const void* const dy[], void* const dW[]) {
+  std::vector<GemmBlock> blocks((size_t)p->P_fo * p->P_fi);
+  for (int i = 0; i < p->P_fo; ++i)
+    for (int j = 0; j < p->P_fi; ++j) {
+      GemmBlock& g = blocks[(size_t)i * p->P_fi + j];
+      std::memset(&g, 0, sizeof g);
+      g.M = (int32_t)p->fo_size[i];
+      g.N = g.ldc = (int32_t)p->fi_size[j];
+      g.c = dW[i * p->P_fi + j];
+      g.nseg = 1;
+      g.seg[0] = GemmSeg{dy[i], x[j], (int32_t)p->n_b, (int32_t)p->fo_size[i], (int32_t)p->fi_size[j], 0};
+    }
+  return blocks;
+}
+
 // Small layers (affine_small.hip): where their launch is estimated at less than 0.95 of the calls on the tiled kernels.  What
 // decides is that those start a tile at a time, and split a long K over two launches; with many tiles, or matrix instructions in
 // earnest, they are the faster ones.  us, tiled / small, forward and back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 295 x 624 -> 28,
@@ -183,12 +231,12 @@ static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& block
   if (p->route == 0 || !gemm_split_usable(blocks, bf16, true, true)) return false;  // (their range is the same)
   // (bf16 rows of whole 16-byte pieces take 7 to 9 us either way)
   if (p->route < 0 && bf16 && gemm_mfma_usable(blocks, bf16, true, true)) return false;
-  const bool vec = gemm_split_vec(blocks, bf16, true, true);
-  int known = p->small_fwd[vec].load(std::memory_order_relaxed);
+  const bool vec = gemm_split_vec(blocks, bf16, true, true), wide = bf16 ? affine_small_words(blocks) : vec;
+  int known = p->small_fwd[wide].load(std::memory_order_relaxed);
   if (known < 0) {
     const double us = affine_small_fwd_us(blocks, bf16);
     known = us < 0.95 * joined(9.2, 1.6 + 1.1 * gemm_split_plan(blocks, vec).us);
-    p->small_fwd[vec].store(known, std::memory_order_relaxed);
+    p->small_fwd[wide].store(known, std::memory_order_relaxed);
   }
   return known || p->route > 0;
 }
@@ -283,6 +331,17 @@ int distdl_debug_affine_route(distdl_affine_plan* p, int route) {
   return DISTDL_OK;
 }
 
+int distdl_debug_affine_small(distdl_affine_plan* p, int align, int32_t out[2]) {
+  if (!p || !out) return set_error(DISTDL_ERR_NULL, "affine_small: null argument");
+  if (align < 2 || align % (int)dtype_size(p->dtype)) return set_error(DISTDL_ERR_INVALID_ARG, "affine_small: arrays aligned to %d bytes", align);
+  const std::vector<void*> at((size_t)p->P_fo * p->P_fi + p->P_fo + p->P_fi, (void*)(uintptr_t)((1 << 20) + align));  // (nobody follows them)
+  const void* const* in = (const void* const*)at.data();
+  const bool bf16 = p->dtype == DISTDL_BF16;
+  out[0] = small_fwd(p, blocks_y(p, in, in, in, at.data()), bf16);
+  out[1] = small_bwd(p, blocks_dx(p, in, in, at.data()), blocks_dw(p, in, in, at.data()), bf16);
+  return DISTDL_OK;
+}
+
 int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const void* const W_dev[],
                       const void* const b_dev[], void* const y_dev[], void* stream) {
   if (!p || !x_dev || !W_dev || !y_dev) return set_error(DISTDL_ERR_NULL, "affine_fwd: null argument");
@@ -295,20 +354,8 @@ int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const vo
     return rc;
   if (b_dev && (rc = check_ptrs(b_dev, p->P_fo, esz, "b", true))) return rc;
   const bool bf16 = p->dtype == DISTDL_BF16;
-  {  // matrix-core path: y_i = sum_j x_j W_ij^T + b_i, the sum over j inside the K loop
-    std::vector<GemmBlock> blocks(p->P_fo);
-    for (int i = 0; i < p->P_fo; ++i) {
-      GemmBlock& g = blocks[i];
-      std::memset(&g, 0, sizeof g);
-      g.M = (int32_t)p->n_b;
-      g.N = g.ldc = (int32_t)p->fo_size[i];
-      g.c = y_dev[i];
-      g.bias = b_dev ? b_dev[i] : nullptr;
-      g.nseg = std::min(p->P_fi, kGemmMaxSeg + 1);
-      for (int j = 0; j < p->P_fi && j < kGemmMaxSeg; ++j)
-        g.seg[j] = GemmSeg{x_dev[j], W_dev[i * p->P_fi + j], (int32_t)p->fi_size[j], (int32_t)p->fi_size[j],
-                           (int32_t)p->fi_size[j], 0};
-    }
+  {  // matrix-core path
+    const std::vector<GemmBlock> blocks = blocks_y(p, x_dev, W_dev, b_dev, y_dev);
     if (small_fwd(p, blocks, bf16)) {
       if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = launch_affine_small_fwd(p->g_fwd.dev, blocks, bf16, st_))) return rc;
       DISTDL_HIP_TRY(hipGetLastError());
@@ -354,31 +401,10 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
   if (db_dev && (rc = check_ptrs((const void* const*)db_dev, p->P_fo, esz, "db", true))) return rc;
   const bool bf16 = p->dtype == DISTDL_BF16;
   {  // matrix-core path
-    std::vector<GemmBlock> bx(p->P_fi), bw((size_t)p->P_fo * p->P_fi);
+    const std::vector<GemmBlock> bx = blocks_dx(p, dy_dev, W_dev, dx_dev), bw = blocks_dw(p, x_dev, dy_dev, dW_dev);
     std::vector<ColsumBlock> bb(p->P_fo);
-    for (int j = 0; j < p->P_fi; ++j) {  // dx_j = sum_i dy_i W_ij
-      GemmBlock& g = bx[j];
-      std::memset(&g, 0, sizeof g);
-      g.M = (int32_t)p->n_b;
-      g.N = g.ldc = (int32_t)p->fi_size[j];
-      g.c = dx_dev[j];
-      g.nseg = std::min(p->P_fo, kGemmMaxSeg + 1);
-      for (int i = 0; i < p->P_fo && i < kGemmMaxSeg; ++i)
-        g.seg[i] = GemmSeg{dy_dev[i], W_dev[i * p->P_fi + j], (int32_t)p->fo_size[i], (int32_t)p->fo_size[i],
-                           (int32_t)p->fi_size[j], 0};
-    }
-    for (int i = 0; i < p->P_fo; ++i) {
-      for (int j = 0; j < p->P_fi; ++j) {  // dW_ij = dy_i^T x_j
-        GemmBlock& g = bw[(size_t)i * p->P_fi + j];
-        std::memset(&g, 0, sizeof g);
-        g.M = (int32_t)p->fo_size[i];
-        g.N = g.ldc = (int32_t)p->fi_size[j];
-        g.c = dW_dev[i * p->P_fi + j];
-        g.nseg = 1;
-        g.seg[0] = GemmSeg{dy_dev[i], x_dev[j], (int32_t)p->n_b, (int32_t)p->fo_size[i], (int32_t)p->fi_size[j], 0};
-      }
+    for (int i = 0; i < p->P_fo; ++i)
       bb[i] = ColsumBlock{dy_dev[i], db_dev ? db_dev[i] : nullptr, (int32_t)p->n_b, (int32_t)p->fo_size[i]};
-    }
     if (small_bwd(p, bx, bw, bf16) && !on_weights(p, W_dev, dW_dev)) {
       if ((rc = p->g_dx.upload(bx, st_)) || (rc = p->g_dw.upload(bw, st_)) || (db_dev && (rc = p->g_db.upload(bb, st_)))) return rc;
       rc = launch_affine_small_bwd(p->g_dx.dev, bx, p->g_dw.dev, bw, db_dev ? p->g_db.dev : nullptr, p->P_fo, (int)p->max_fo, bf16, st_);

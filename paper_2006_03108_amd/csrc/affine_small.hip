@@ -398,8 +398,7 @@ __global__ __launch_bounds__(512, 2) void affine_small_bwd_kernel(SmallGrid gx, 
 
 // ---- host side ------------------------------------------------------------------
 
-// bf16 operands whose rows or lines are whole 4-byte words
-static bool words(const std::vector<GemmBlock>& blocks) {
+bool affine_small_words(const std::vector<GemmBlock>& blocks) {
   for (const GemmBlock& b : blocks)
     for (int s = 0; s < b.nseg; ++s) {
       const GemmSeg& g = b.seg[s];
@@ -475,7 +474,7 @@ double affine_small_fwd_us(const std::vector<GemmBlock>& blocks, bool bf16) {
   const SmallShape s = best_fwd(nullptr, blocks, bf16);
   const size_t arrays = blocks.size() * (blocks[0].nseg + 1) + blocks[0].nseg;
   const double us = std::max(1.0, s.wgs / 512.0) * product_us(s, 2.1, 0.12, bf16 ? 0.48 : 0.60, 0.78);
-  return joined(6.8 + 0.13 * arrays, us * (bf16 && !words(blocks) ? 1.5 : 1.0));  // (rows of odd bf16 come value by value)
+  return joined(6.8 + 0.13 * arrays, us * (bf16 && !affine_small_words(blocks) ? 1.5 : 1.0));  // (rows of odd bf16 come value by value)
 }
 double affine_small_bwd_us(const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16) {
   const SmallShape x = best_dx(nullptr, bx, bf16), w = best_dw(nullptr, bw, bf16);
@@ -508,7 +507,7 @@ int launch_affine_small_fwd(const GemmBlock* d_blocks, const std::vector<GemmBlo
   ProfScope prof("affine_fwd_small", st);
   const SmallShape s = best_fwd(d_blocks, blocks, bf16);
   if (!bf16) return fwd_pick<false, true>(s, st);
-  return words(blocks) ? fwd_pick<true, true>(s, st) : fwd_pick<true, false>(s, st);
+  return affine_small_words(blocks) ? fwd_pick<true, true>(s, st) : fwd_pick<true, false>(s, st);
 }
 
 template <bool BF16, bool V4, int MTX, bool SPLITX, bool SPLITW>
@@ -535,7 +534,7 @@ int launch_affine_small_bwd(const GemmBlock* d_bx, const std::vector<GemmBlock>&
   const int chunks = d_cs ? (max_f + 15) / 16 : 0;
   if (!d_cs) n_cs = 0;
   if (!bf16) return bwd_pick<false, true>(x, w, d_cs, n_cs, chunks, st);
-  return words(bx) && words(bw) ? bwd_pick<true, true>(x, w, d_cs, n_cs, chunks, st) : bwd_pick<true, false>(x, w, d_cs, n_cs, chunks, st);
+  return affine_small_words(bx) && affine_small_words(bw) ? bwd_pick<true, true>(x, w, d_cs, n_cs, chunks, st) : bwd_pick<true, false>(x, w, d_cs, n_cs, chunks, st);
 }
 
 }  // namespace distdl

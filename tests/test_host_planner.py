@@ -395,3 +395,15 @@ def test_choice_of_the_fused_kernels_is_that_of_the_call():
     answers = {aligned: dd.distdl_debug_conv_fused(first, aligned) for aligned in (1, 2)}
     assert answers[1] != answers[2]
     assert {aligned: dd.distdl_debug_conv_fused(second, aligned) for aligned in (2, 1)} == answers
+
+
+@pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi,by_alignment", [
+    (35, 1172, 1743, 1, 2, {2: False, 4: True, 16: True}),   # rows of whole words, none of whole 16-byte pieces
+    (115, 552, 1485, 1, 3, {2: False, 4: True, 16: False}),  # whole pieces: the bf16 tiles
+])
+def test_choice_of_the_small_affine_kernels_is_that_of_the_call(n_b, n_fi, n_fo, P_fo, P_fi, by_alignment):
+    """bf16 rows that do not start on a word move value by value, which the forward estimate knows: a plan answers for either
+    whatever it was asked before."""
+    for order in (list(by_alignment), list(by_alignment)[::-1]):
+        plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, torch.bfloat16)
+        assert {align: dd.distdl_debug_affine_small(plan, align)[0] for align in order} == by_alignment
