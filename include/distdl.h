@@ -465,6 +465,12 @@ int distdl_debug_affine_small(distdl_affine_plan* plan, int align, int32_t out[2
  * gradient, whether or not it is what runs: 64 or 256, 0 where it does not take
  * the layer. */
 int distdl_debug_conv_wgrad_rows(const distdl_plan* plan, int32_t* rows);
+/* 1 where an output array overlaps an input or another output, else 0: what
+ * the calls that write outputs while inputs are still being read ask of their
+ * arrays, which come in n_groups (up to 8) groups of count[g], output[g] != 0
+ * for outputs; arrays of no bytes or at address 0 count for nothing. */
+int distdl_debug_overlap(const uint64_t first[], const uint64_t bytes[], const int32_t count[], const int32_t output[],
+                         int n_groups);
 /* Runs the replacement policy of the cached device tables (see Conventions)
  * on a sequence of n calls without touching a device: call i arrives on
  * stream stream_id[i] with table contents table_id[i], during stream capture

@@ -67,6 +67,7 @@ _SIGS = {
     "distdl_conv_local_bwd": [_vp, _pp, _vp, _pp, _pp, _vp, _vp, _vp, C.c_size_t, _vp],
     "distdl_layout_convert": [_vp, _i, _i, _pp, _pp, _vp],
     "distdl_copy_ref": [_vp, _vp, C.c_size_t, _vp],
+    "distdl_debug_overlap": [C.POINTER(C.c_uint64), C.POINTER(C.c_uint64), _p32, _p32, _i],
     "distdl_debug_slot_policy": [_p32, _p32, _p32, _i, _p32],
     "distdl_debug_conv_path": [_vp, _p32],
     "distdl_debug_conv_kernels": [_vp, _i, _p32],
@@ -352,6 +353,14 @@ def distdl_layout_convert(plan, what, to_channels_last, src, dst):
 
 def distdl_copy_ref(src, dst):
     _check(lib.distdl_copy_ref(src.data_ptr(), dst.data_ptr(), src.numel() * src.element_size(), _stream()))
+
+
+def distdl_debug_overlap(groups):
+    """Whether an output overlaps an input or another output; groups: (output or not, [(first byte, bytes), ...])."""
+    arrays = [a for _, g in groups for a in g]
+    return bool(_check(lib.distdl_debug_overlap(
+        _arr(C.c_uint64, [a for a, _ in arrays]), _arr(C.c_uint64, [n for _, n in arrays]), _arr(C.c_int32, [len(g) for _, g in groups]),
+        _arr(C.c_int32, [o for o, _ in groups]), len(groups))))
 
 
 def distdl_debug_slot_policy(stream_ids, table_ids, capturing):

@@ -23,6 +23,7 @@
 #include "conv_split.h"
 #include "conv_wsplit.h"
 #include "profile.h"
+#include "ranges.h"
 #include "weight_job.h"
 
 namespace distdl {
@@ -426,41 +427,41 @@ static int weight_job(distdl_plan* p, Corr kernel, bool backward, const void* w,
   return kernel == Corr::kAny ? any_weight_job(p, backward, w, aligned, st, job) : DISTDL_OK;
 }
 
-// Whether no output of an adjoint lies on one of its inputs, or on another output: the fused adjoint writes dx, dw and db while
-// the others are still being read.
-static bool separate(const distdl_plan* p, const void* const x[], const void* w, const void* const dy[], void* const dx[], const void* dw,
-                     const void* db, const void* ws, size_t ws_bytes) {
-  struct Range {
-    uintptr_t lo, hi;
-    bool meets(const Range& r) const { return lo < r.hi && r.lo < hi; }
-  };
-  auto range = [](const void* at, size_t bytes) { return Range{(uintptr_t)at, (uintptr_t)at + bytes}; };
-  const size_t esz = dtype_size(p->dtype), wb = (size_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci * p->n_co * esz;
-  const Range one[4] = {range(w, wb), range(ws, ws_bytes), range(dw, wb), range(db, db ? p->n_co * esz : 0)};
-  auto buf = [&](const void* at, int i) {
-    const WorkerDev& wd = p->workers[i];
-    return range(at, (size_t)p->n_b * wd.buf[0] * wd.buf[1] * wd.buf[2] * p->n_ci * esz);
-  };
-  auto out = [&](const void* at, int i) {
-    const WorkerDev& wd = p->workers[i];
-    return range(at, (size_t)p->n_b * wd.out[0] * wd.out[1] * wd.out[2] * p->n_co * esz);
-  };
-  for (int i = 0; i < 4; ++i)
-    for (int j = i + 1; j < 4; ++j)
-      if (one[i].meets(one[j])) return false;
-  Range in_all{UINTPTR_MAX, 0}, dx_all{UINTPTR_MAX, 0};
-  auto widen = [](Range& r, const Range& by) { r.lo = std::min(r.lo, by.lo), r.hi = std::max(r.hi, by.hi); };
-  for (int i = 0; i < p->n_workers; ++i) {
-    const Range rx = buf(x[i], i), ry = out(dy[i], i), rd = buf(dx[i], i);
-    for (int j = 0; j < 4; ++j)
-      if (rd.meets(one[j]) || (j > 0 && (rx.meets(one[j]) || ry.meets(one[j])))) return false;
-    widen(in_all, rx), widen(in_all, ry), widen(dx_all, rd);
-  }
-  if (!in_all.meets(dx_all)) return true;
-  for (int i = 0; i < p->n_workers; ++i)
-    for (int j = 0; j < p->n_workers; ++j)
-      if (buf(dx[i], i).meets(buf(x[j], j)) || buf(dx[i], i).meets(out(dy[j], j))) return false;
-  return true;
+// Whether an output of a call lies on one of its inputs, or on another output: the fused kernels write y, and dx, dw and db, while
+// the inputs are still being read.
+static size_t x_bytes(const distdl_plan* p, int w) {
+  const WorkerDev& wd = p->workers[w];
+  return (size_t)p->n_b * wd.buf[0] * wd.buf[1] * wd.buf[2] * p->n_ci * dtype_size(p->dtype);
+}
+static size_t y_bytes(const distdl_plan* p, int w) {
+  const WorkerDev& wd = p->workers[w];
+  return (size_t)p->n_b * wd.out[0] * wd.out[1] * wd.out[2] * p->n_co * dtype_size(p->dtype);
+}
+static size_t w_bytes(const distdl_plan* p) { return (size_t)p->ksize[0] * p->ksize[1] * p->ksize[2] * p->n_ci * p->n_co * dtype_size(p->dtype); }
+static bool fwd_overlaps(const distdl_plan* p, const void* const x[], const void* w, const void* bias, void* const y[]) {
+  Ranges r((size_t)2 * p->n_workers + 2);
+  r.one(w, w_bytes(p), false);
+  r.one(bias, p->n_co * dtype_size(p->dtype), false);
+  r.begin(false);
+  for (int i = 0; i < p->n_workers; ++i) r.add(x[i], x_bytes(p, i));
+  r.begin(true);
+  for (int i = 0; i < p->n_workers; ++i) r.add(y[i], y_bytes(p, i));
+  return r.clash();
+}
+static bool bwd_overlaps(const distdl_plan* p, const void* const x[], const void* w, const void* const dy[], void* const dx[], const void* dw,
+                         const void* db, const void* ws, size_t ws_bytes) {
+  Ranges r((size_t)3 * p->n_workers + 4);
+  r.one(w, w_bytes(p), false);
+  r.one(ws, ws_bytes, true);
+  r.one(dw, w_bytes(p), true);
+  r.one(db, p->n_co * dtype_size(p->dtype), true);
+  r.begin(false);
+  for (int i = 0; i < p->n_workers; ++i) r.add(x[i], x_bytes(p, i));
+  r.begin(false);
+  for (int i = 0; i < p->n_workers; ++i) r.add(dy[i], y_bytes(p, i));
+  r.begin(true);
+  for (int i = 0; i < p->n_workers; ++i) r.add(dx[i], x_bytes(p, i));
+  return r.clash();
 }
 
 static int prepare_weights(distdl_plan* p, const void* w, hipStream_t st) {
@@ -581,7 +582,8 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
   for (int w = 0; w < plan->n_workers; ++w) xvec &= (uintptr_t)x_bufs_dev[w] % 16 == 0 && (uintptr_t)y_dev[w] % 16 == 0;
   const bool vec = xvec && plan->n_ci % 4 == 0 && plan->n_co % 4 == 0;
   const bool w_aligned = (uintptr_t)w_dev % 16 == 0;
-  const bool fused = halo && choose_fused(plan, false, vec, xvec, w_aligned) && conv_fused_ready(plan, false, st);
+  const bool fused = halo && choose_fused(plan, false, vec, xvec, w_aligned) && conv_fused_ready(plan, false, st) &&
+                     !fwd_overlaps(plan, x_bufs_dev, w_dev, bias_dev, y_dev);
   if (fused && !plan->d_workers) (void)conv_fused_us(plan, true, vec);  // (the adjoint's tables, on the way with the others)
   const Corr kernel = fused ? Corr::kDirect : choose_fwd(plan, xvec, w_aligned);
   if ((rc = plan_prepare_device(plan))) return rc;
@@ -679,7 +681,7 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
     nw <= 8192 ? by_type(std::integral_constant<int, 16>{}) : by_type(std::integral_constant<int, 64>{});
   };
   if (halo && choose_fused(plan, true, vec16, aligned, true) && conv_fused_ready(plan, true, st) &&
-      separate(plan, x_bufs_dev, w_dev, dy_dev, dx_bufs_dev, dw_dev, dbias_dev, workspace_dev, workspace_bytes)) {
+      !bwd_overlaps(plan, x_bufs_dev, w_dev, dy_dev, dx_bufs_dev, dw_dev, dbias_dev, workspace_dev, workspace_bytes)) {
     int partials = 0;
     if ((rc = conv_bwd_fused(plan, w_dev, dw_dev, dbias_dev, (float*)workspace_dev, vec16, st, &partials))) return rc;
     if (partials > 0) reduce_dw(partials);
@@ -721,13 +723,10 @@ int conv_bwd_core(distdl_plan* plan, const void* const x_bufs_dev[], const void*
   auto on = [](const void* a, size_t na, const void* b, size_t nb) {
     return a && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
   };
-  const size_t w_bytes = (size_t)c.taps * c.ci * c.co * esz, b_bytes = (size_t)c.co * esz;
-  bool in_place = on(dw_dev, w_bytes, w_dev, w_bytes) || on(dbias_dev, b_bytes, w_dev, w_bytes);
-  for (int w = 0; w < plan->n_workers; ++w) {
-    const WorkerDev& wd = plan->workers[w];
-    const size_t y_bytes = (size_t)plan->n_b * wd.out[0] * wd.out[1] * wd.out[2] * b_bytes;
-    in_place |= on(dw_dev, w_bytes, dy_dev[w], y_bytes) || on(dbias_dev, b_bytes, dy_dev[w], y_bytes);
-  }
+  const size_t wb = w_bytes(plan), bb = (size_t)c.co * esz;
+  bool in_place = on(dw_dev, wb, w_dev, wb) || on(dbias_dev, bb, w_dev, wb);
+  for (int w = 0; w < plan->n_workers; ++w)
+    in_place |= on(dw_dev, wb, dy_dev[w], y_bytes(plan, w)) || on(dbias_dev, bb, dy_dev[w], y_bytes(plan, w));
   const bool data_last = job.kind != 0 && !in_place && !write_back_hides(plan, kernel, wgrad);
   if (!data_last) {
     if ((rc = launch_weight_job(job, st))) return rc;

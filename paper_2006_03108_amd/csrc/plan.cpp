@@ -6,6 +6,7 @@
 
 #include "common.h"
 #include "conv_fused.h"
+#include "ranges.h"
 
 namespace distdl {
 
@@ -623,6 +624,17 @@ int distdl_plan_query(const distdl_plan* plan, int worker, distdl_worker_geom* o
     out->conv_origin[d] = g.origin;
   }
   return DISTDL_OK;
+}
+
+int distdl_debug_overlap(const uint64_t first[], const uint64_t bytes[], const int32_t count[], const int32_t output[], int n_groups) {
+  if (!first || !bytes || !count || !output) return set_error(DISTDL_ERR_NULL, "overlap: null argument");
+  if (n_groups < 0 || n_groups > Ranges::kGroups) return set_error(DISTDL_ERR_INVALID_ARG, "overlap: %d groups", n_groups);
+  Ranges r(0);
+  for (int g = 0, at = 0; g < n_groups; ++g) {
+    r.begin(output[g] != 0);
+    for (int i = 0; i < count[g]; ++i, ++at) r.add((const void*)(uintptr_t)first[at], bytes[at]);
+  }
+  return r.clash();
 }
 
 int distdl_debug_slot_policy(const int32_t stream_id[], const int32_t table_id[], const int32_t capturing[], int n,

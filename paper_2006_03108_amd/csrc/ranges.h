@@ -1,0 +1,94 @@
+// Whether the arrays of a call overlap in a way that one launch in the place of several must not meet.
+#pragma once
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+#include <utility>
+#include <vector>
+
+namespace distdl {
+
+// The arrays of a call, group by group (all x, all dx, ...).  Inputs may lie on inputs.
+//
+// A plan has up to a thousand workers, and each call asks.  Groups that lie apart, their arrays one behind the other, are compared as
+// wholes; else the arrays are sorted by address, by merging the runs in which they come (allocated worker by worker, each group is
+// one), and swept over once.  us, 256 workers whose x, dy and dx alternate: each with each 263, this way 6.5; in any order 15, a
+// block to each group 3.4; 1024 workers 5300, and 27, 222, 15.
+class Ranges {
+ public:
+  static constexpr int kGroups = 8;
+  explicit Ranges(size_t n) { all_.reserve(n); }
+  void begin(bool output) { groups_[n_groups_++] = Group{output, true, UINT64_MAX, 0}; }  // of up to kGroups
+  void add(const void* at, size_t bytes) {
+    if (!at || bytes == 0) return;
+    Group& g = groups_[n_groups_ - 1];
+    const uint64_t lo = (uint64_t)at, hi = lo + bytes;
+    g.apart &= lo >= g.hi;  // behind the last
+    g.lo = std::min(g.lo, lo), g.hi = std::max(g.hi, hi);
+    all_.push_back(Range{lo, hi | (g.output ? kOutput : 0)});
+  }
+  void one(const void* at, size_t bytes, bool output) { begin(output), add(at, bytes); }
+
+  // Whether an output lies on an input or on another output
+  bool clash() {
+    bool apart = true;
+    for (int i = 0; i < n_groups_ && apart; ++i) {
+      apart = groups_[i].apart || !groups_[i].output;
+      for (int j = 0; j < i; ++j)
+        if (groups_[i].output || groups_[j].output) apart &= groups_[i].hi <= groups_[j].lo || groups_[j].hi <= groups_[i].lo;
+    }
+    if (apart) return false;
+    sort();
+    uint64_t end = 0, end_out = 0;  // of all arrays so far, of the outputs
+    for (const Range& r : all_) {
+      const uint64_t hi = r.hi & ~kOutput;
+      if (r.lo < end_out || ((r.hi & kOutput) && r.lo < end)) return true;
+      end = std::max(end, hi);
+      if (r.hi & kOutput) end_out = hi;
+    }
+    return false;
+  }
+
+ private:
+  static constexpr uint64_t kOutput = uint64_t(1) << 63;  // (addresses have fewer bits)
+  struct Range {
+    uint64_t lo, hi;
+  };
+  struct Group {
+    bool output, apart;
+    uint64_t lo, hi;
+  };
+
+  void sort() {
+    auto before = [](const Range& a, const Range& b) { return a.lo < b.lo; };
+    std::vector<uint32_t> ends;  // of the runs
+    for (size_t i = 0, j; i < all_.size(); i = j) {
+      j = i + 1;
+      if (j < all_.size() && all_[j].lo < all_[i].lo) {
+        while (j < all_.size() && all_[j].lo < all_[j - 1].lo) ++j;
+        std::reverse(all_.begin() + i, all_.begin() + j);
+      } else {
+        while (j < all_.size() && all_[j].lo >= all_[j - 1].lo) ++j;
+      }
+      ends.push_back((uint32_t)j);
+    }
+    std::vector<Range> other(all_.size());
+    while (ends.size() > 1) {
+      size_t kept = 0;
+      for (size_t r = 0, from = 0; r < ends.size(); r += 2) {
+        const size_t mid = ends[r], to = r + 1 < ends.size() ? ends[r + 1] : mid;
+        std::merge(all_.begin() + from, all_.begin() + mid, all_.begin() + mid, all_.begin() + to, other.begin() + from, before);
+        ends[kept++] = (uint32_t)to;
+        from = to;
+      }
+      ends.resize(kept);
+      all_.swap(other);
+    }
+  }
+
+  std::vector<Range> all_;
+  Group groups_[kGroups];
+  int n_groups_ = 0;
+};
+
+}  // namespace distdl

@@ -203,6 +203,27 @@ def test_outputs_on_inputs_run_the_general_kernels(onto):
         assert torch.equal(first, adjoint(dd.distdl_conv_local_bwd))
 
 
+@pytest.mark.parametrize("onto", ["w", "bias", "nothing"])
+def test_forward_onto_its_weights_runs_the_general_kernels(onto):
+    require_gpu()
+    L = _Layer(_cfg(1, 8, 8, (16, 16), 1, 3, 1, 1), F32)
+    room = torch.empty(8 + L.y[0].numel(), device="cuda")
+    y = room[:L.y[0].numel()].view(L.y[0].shape)
+    w, b = L.w, L.b
+    if onto == "w":
+        w = room[-L.w.numel():].view(L.w.shape)   # (its last 8 values lie behind y)
+        w.copy_(L.w)
+    elif onto == "bias":
+        b = room[:8]
+        b.copy_(L.b)
+    dd.distdl_profile_enable(True)
+    dd.distdl_profile_report()
+    dd.distdl_conv_fwd(L.plan, L.x, w, b, [y])
+    names = set(dd.distdl_profile_report())
+    dd.distdl_profile_enable(False)
+    assert ("conv_fwd_fused" in names) == (onto == "nothing")
+
+
 # the layers by which the general kernels are tested elsewhere and that now run in one launch there
 SMALL = [(c[1:], dt) for c in CHOICE + FEW_ROWS for dt in (F32,)] + [(c[1:], BF16) for c in CHOICE_BF16 + FEW_ROWS] + \
         [(c, F32) for c in SIXTEEN + LAYERS + FEW]

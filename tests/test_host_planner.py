@@ -407,3 +407,58 @@ def test_choice_of_the_small_affine_kernels_is_that_of_the_call(n_b, n_fi, n_fo,
     for order in (list(by_alignment), list(by_alignment)[::-1]):
         plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, torch.bfloat16)
         assert {align: dd.distdl_debug_affine_small(plan, align)[0] for align in order} == by_alignment
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_overlap_of_a_calls_arrays(seed):
+    """Against every pair, for arrays in order, in reverse, interleaved, at random, with and without one that touches another."""
+    rng = random.Random(seed)
+    for _ in range(40):
+        n_groups, n = rng.randint(1, 8), rng.choice([1, 1, 2, 5, 17])
+        kinds = [rng.random() < 0.5 for _ in range(n_groups)]
+        slots = [(g, i) for g in range(n_groups) for i in range(n)]
+        order = rng.choice(["blocks", "interleaved", "random"])
+        if order == "interleaved":
+            slots.sort(key=lambda s: (s[1], s[0]))
+        elif order == "random":
+            rng.shuffle(slots)
+        at, place = 4096, {}
+        for s in slots:
+            size = rng.choice([0, 2, 64, 1000])
+            place[s] = (at, size)
+            at += size + rng.choice([0, 0, 2, 512])
+        for _ in range(rng.choice([0, 0, 1, 2])):                     # an array moved onto another one's place
+            a, b = rng.choice(slots), rng.choice(slots)
+            place[a] = (place[b][0] + rng.choice([-3, 0, 1, place[b][1]]), place[a][1])
+        if rng.random() < 0.2:
+            place[rng.choice(slots)] = (0, 64)                        # no array
+        groups = [(kinds[g], [place[g, i] for i in range(n)]) for g in range(n_groups)]
+        for k in range(n_groups):
+            if rng.random() < 0.3:
+                groups[k][1].reverse()
+        arrays = [(a, a + b, out) for out, g in groups for a, b in g if a and b]
+        want = any(p[0] < q[1] and q[0] < p[1] and (p[2] or q[2]) for i, p in enumerate(arrays) for q in arrays[:i])
+        assert dd.distdl_debug_overlap(groups) == want
+
+
+def test_overlap_of_many_workers_arrays():
+    """A thousand workers' arrays, allocated worker by worker or in any order: sixteen times as many take some sixteen times as long
+    (sorted: 16 * 12 / 8 = 24), where comparing each with each took 256 times as long."""
+    import ctypes as C
+    import time
+
+    def least(n, shuffled):
+        places = list(range(3 * n))
+        if shuffled:
+            random.Random(1).shuffle(places)
+        first = [4096 * (1 + places[3 * i + g]) for g in range(3) for i in range(n)]
+        args = ((C.c_uint64 * (3 * n))(*first), (C.c_uint64 * (3 * n))(*[4096] * (3 * n)), (C.c_int32 * 3)(n, n, n), (C.c_int32 * 3)(0, 0, 1), 3)
+        best = float("inf")
+        for _ in range(50):
+            t = time.perf_counter()
+            assert dd.lib.distdl_debug_overlap(*args) == 0
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    for shuffled in (False, True):
+        assert least(1024, shuffled) < 80 * least(64, shuffled)
