@@ -234,6 +234,10 @@ int distdl_layout_convert(const distdl_plan* plan, int what, int to_channels_las
  *   dy_i W_ij (i ascending).  db_dev may be NULL.
  * fp32: fp32 operands and accumulation.  bf16: bf16 operands, fp32
  * accumulation, outputs rounded to bf16 (nearest even); b and db are bf16.
+ * Outputs must not overlap inputs or one another, with one exception: dW and
+ * db may lie on W in a bf16 layer of at most 8 x 8 workers whose blocks have
+ * multiples of 8 features and whose arrays are 16-byte aligned (dx is made
+ * before them then).
  * ---------------------------------------------------------------------- */
 typedef struct distdl_affine_plan distdl_affine_plan;
 int distdl_affine_plan_create(distdl_affine_plan** out, int64_t n_b, int64_t n_fi, int64_t n_fo, int P_fo,

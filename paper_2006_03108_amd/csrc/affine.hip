@@ -14,6 +14,7 @@
 #include "common.h"
 #include "gemm_mfma.h"
 #include "profile.h"
+#include "ranges.h"
 
 struct distdl_affine_plan {
   int64_t n_b = 0, n_fi = 0, n_fo = 0;
@@ -257,15 +258,33 @@ static bool small_bwd(distdl_affine_plan* p, const std::vector<GemmBlock>& bx, c
   }
   return known || p->route > 0;
 }
-// Whether a dW lies on weights, which dx is made of in the same launch.
-static bool on_weights(const distdl_affine_plan* p, const void* const W[], void* const dW[]) {
-  const size_t esz = dtype_size(p->dtype);
-  const int n = p->P_fo * p->P_fi;
-  auto bytes = [&](int i) { return (uintptr_t)(p->fo_size[i / p->P_fi] * p->fi_size[i % p->P_fi]) * esz; };
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j)
-      if ((uintptr_t)dW[i] < (uintptr_t)W[j] + bytes(j) && (uintptr_t)W[j] < (uintptr_t)dW[i] + bytes(i)) return true;
-  return false;
+// Whether an output of a call lies on one of its inputs, or on another output: the small kernels write y, or dx, dW and db, while the
+// inputs are still being read, where the tiled ones may write behind them (the bf16 tiles dW and db behind dx, a reduction of a
+// split K behind everything).
+static void add_rows(Ranges& r, const distdl_affine_plan* p, const void* const at[], const std::vector<int64_t>& features, bool output) {
+  r.begin(output);
+  for (size_t i = 0; i < features.size(); ++i) r.add(at[i], (size_t)(p->n_b * features[i]) * dtype_size(p->dtype));
+}
+static void add_weights(Ranges& r, const distdl_affine_plan* p, const void* const at[], bool output) {
+  r.begin(output);
+  for (int i = 0; i < p->P_fo; ++i)
+    for (int j = 0; j < p->P_fi; ++j) r.add(at[i * p->P_fi + j], (size_t)(p->fo_size[i] * p->fi_size[j]) * dtype_size(p->dtype));
+}
+static void add_bias(Ranges& r, const distdl_affine_plan* p, const void* const at[], bool output) {
+  r.begin(output);
+  for (int i = 0; at && i < p->P_fo; ++i) r.add(at[i], (size_t)p->fo_size[i] * dtype_size(p->dtype));
+}
+static bool fwd_overlaps(const distdl_affine_plan* p, const void* const x[], const void* const W[], const void* const b[], void* const y[]) {
+  Ranges r((size_t)p->P_fo * p->P_fi + p->P_fi + 2 * p->P_fo);
+  add_rows(r, p, x, p->fi_size, false), add_weights(r, p, W, false), add_bias(r, p, b, false), add_rows(r, p, y, p->fo_size, true);
+  return r.clash();
+}
+static bool bwd_overlaps(const distdl_affine_plan* p, const void* const x[], const void* const W[], const void* const dy[], void* const dx[],
+                         void* const dW[], void* const db[]) {
+  Ranges r((size_t)2 * (p->P_fo * p->P_fi + p->P_fi + p->P_fo));
+  add_rows(r, p, x, p->fi_size, false), add_weights(r, p, W, false), add_rows(r, p, dy, p->fo_size, false);
+  add_rows(r, p, dx, p->fi_size, true), add_weights(r, p, dW, true), add_bias(r, p, db, true);
+  return r.clash();
 }
 
 }  // namespace distdl
@@ -356,7 +375,7 @@ int distdl_affine_fwd(distdl_affine_plan* p, const void* const x_dev[], const vo
   const bool bf16 = p->dtype == DISTDL_BF16;
   {  // matrix-core path
     const std::vector<GemmBlock> blocks = blocks_y(p, x_dev, W_dev, b_dev, y_dev);
-    if (small_fwd(p, blocks, bf16)) {
+    if (small_fwd(p, blocks, bf16) && !fwd_overlaps(p, x_dev, W_dev, b_dev, y_dev)) {
       if ((rc = p->g_fwd.upload(blocks, st_)) || (rc = launch_affine_small_fwd(p->g_fwd.dev, blocks, bf16, st_))) return rc;
       DISTDL_HIP_TRY(hipGetLastError());
       return DISTDL_OK;
@@ -405,7 +424,7 @@ int distdl_affine_bwd(distdl_affine_plan* p, const void* const x_dev[], const vo
     std::vector<ColsumBlock> bb(p->P_fo);
     for (int i = 0; i < p->P_fo; ++i)
       bb[i] = ColsumBlock{dy_dev[i], db_dev ? db_dev[i] : nullptr, (int32_t)p->n_b, (int32_t)p->fo_size[i]};
-    if (small_bwd(p, bx, bw, bf16) && !on_weights(p, W_dev, dW_dev)) {
+    if (small_bwd(p, bx, bw, bf16) && !bwd_overlaps(p, x_dev, W_dev, dy_dev, dx_dev, dW_dev, db_dev)) {
       if ((rc = p->g_dx.upload(bx, st_)) || (rc = p->g_dw.upload(bw, st_)) || (db_dev && (rc = p->g_db.upload(bb, st_)))) return rc;
       rc = launch_affine_small_bwd(p->g_dx.dev, bx, p->g_dw.dev, bw, db_dev ? p->g_db.dev : nullptr, p->P_fo, (int)p->max_fo, bf16, st_);
       if (rc) return rc;

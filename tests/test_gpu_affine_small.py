@@ -113,3 +113,41 @@ def test_more_workers_than_a_block_has_segments(P_fo, P_fi, dtype, route):
     want = (xd @ Wd.t() + torch.cat(b).double(), dyd @ Wd, dyd.t() @ xd, dyd.sum(0))
     for name, u, v in zip(("y", "dx", "dW", "db"), got, want):
         assert float((u.double() - v).norm()) <= (72 * 2.0 ** -24 if dtype == torch.float32 else 2.0 ** -8 + 1e-5) * float(v.norm()), name
+
+
+@pytest.mark.parametrize("dtype,onto", [(torch.bfloat16, "dW on W"), (torch.bfloat16, "db on W"), (torch.float32, "dW on W"),
+                                        (torch.float32, "dx on x"), (torch.float32, "y on x"), (torch.float32, "nothing")],
+                         ids=lambda v: v.replace(" ", "_") if isinstance(v, str) else str(v)[6:])
+def test_outputs_on_inputs_run_the_tiled_kernels(dtype, onto):
+    """The tiled kernels may write behind the last read of what lies below.  bf16: dW and db come after dx, so that either may lie on
+    the weights, and the numbers are those of arrays apart."""
+    require_gpu()
+    n_b, n_f, P = 73, 176, 2
+    g = torch.Generator(device="cuda").manual_seed(12)
+    new = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(dtype)
+    x, dy = [new(n_b, n_f // P) for _ in range(P)], [new(n_b, n_f // P) for _ in range(P)]
+    W, b = [new(n_f // P, n_f // P) for _ in range(P * P)], [new(n_f // P) for _ in range(P)]
+    y, dx, dW, db = ([torch.full_like(t, 7.0) for t in ts] for ts in (dy, x, W, b))
+    plan = dd.distdl_affine_plan_create(n_b, n_f, n_f, P, P, dtype)
+    assert dd.distdl_debug_affine_small(plan)[1] and (dtype == torch.bfloat16 or dd.distdl_debug_affine_small(plan)[0])
+    dd.distdl_debug_affine_route(plan, 0)
+    dd.distdl_affine_bwd(plan, x, W, dy, dx, dW, db)
+    want = [t.clone() for t in dx + dW + db]
+    dd.distdl_debug_affine_route(plan, -1)
+    if onto == "dW on W":
+        dW = W
+    elif onto == "db on W":
+        db = [W[3].view(-1)[i * n_f // P:(i + 1) * n_f // P] for i in range(P)]
+    elif onto == "dx on x":
+        dx = x
+    dd.distdl_profile_enable(True)
+    dd.distdl_profile_report()
+    dd.distdl_affine_bwd(plan, x, W, dy, dx, dW, db)
+    back = set(dd.distdl_profile_report())
+    dd.distdl_affine_fwd(plan, x, W, b, x if onto == "y on x" else y)
+    ahead = set(dd.distdl_profile_report())
+    dd.distdl_profile_enable(False)
+    assert ("affine_bwd_small" in back) == (onto in ("nothing", "y on x"))
+    assert dtype == torch.bfloat16 or ("affine_fwd_small" in ahead) == (onto != "y on x")
+    if dtype == torch.bfloat16:
+        assert all(map(torch.equal, dx + dW + db, want))
