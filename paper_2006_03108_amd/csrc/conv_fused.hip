@@ -837,8 +837,9 @@ void add_wgrad(const distdl_plan* p, Shape& sh) {
 
 // Estimated time of a direction's call, launches and all (us); infinite where it is not taken.  A workgroup's time is that of its
 // set-up, its weights, the positions and taps of its tiles and their steps of 16 k; compute units with several of them take longer
-// for each.  Two terms joined by a fourth power: what the host takes to launch, and what the device does.  Fitted to 600 layers of 1
-// to 64 channels, one to three dimensions, up to 600 000 positions and 0.4 GFLOP; four fifths are within 16 % (forward) and 22 %.
+// for each; y leaves at 5 TB/s, or value by value at a million in 1.1 us.  Two terms joined by a fourth power: what the host takes to launch, more
+// for each worker's arrays, and what the device does.  Fitted to 600 layers of 1 to 64 channels, one to three dimensions, up to
+// 600 000 positions and 0.4 GFLOP; four fifths are within 12 % (forward) and 14 %.
 static double joined(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
 double conv_fused_us(const distdl_plan* p, bool backward, bool vec) {
   if (!small_tensors(p)) return INFINITY;
@@ -846,20 +847,23 @@ double conv_fused_us(const distdl_plan* p, bool backward, bool vec) {
   if (!sh.fits) return INFINITY;
   if (backward && sh.a.dw_blocks == 0) add_wgrad(p, sh);
   const FusedArgs& a = sh.a;
+  const bool bf16 = p->dtype == DISTDL_BF16;
   const double stage = (double)std::min(16 * sh.NT, a.nc) * a.taps * a.kc / 2048, entries = (a.most_taps + 2) / (4.0 * a.wk),
                steps = std::max(1.0, std::ceil((double)a.most_taps * a.kc / 16)) / a.wk, load = a.blocks / 256.0;
+  const double written = 1e-6 * p->n_workers * p->n_b * (backward ? p->max_buf_cells : p->max_out_cells) * a.nc * dtype_size(p->dtype);  // of y or dx, MB
   const int resident = std::min(160 * 1024 / sh.lds, sh.NT == 4 ? 2 : 3);
   if (!backward) {
-    const double t = 0.87 + 0.94 * stage + a.tpw * (0.75 + 0.145 * entries + steps * ((vec ? 0.0 : 0.16) + 0.30 * sh.NT));
-    return joined(6.4, 4.6 + t * std::max(1.0, load / resident) * (1 + 0.26 * std::min(load, 3.0)));
+    const double t = 1.2 + stage + a.tpw * (0.58 + 0.17 * entries + steps * ((vec ? 0.0 : 0.21) + 0.32 * sh.NT));
+    const double store = vec && !bf16 ? 0.2 * written : 1.1 * written / (bf16 ? 2 : 4);
+    return joined(6.2 + 0.2 * p->n_workers, 3.2 + t * std::max(1.0, load / resident) * (1 + 0.22 * std::min(load, 3.0)) + store);
   }
-  const double t = 0.8 + 0.56 * stage + a.tpw * (0.79 + 0.02 * entries + steps * ((vec ? 0.03 : 0.12) + 0.145 * sh.NT));
+  const double t = 1.1 + 0.77 * stage + a.tpw * (0.69 + 0.077 * entries + steps * ((vec ? 0.08 : 0.2) + 0.11 * sh.NT));
   const bool whole = a.dw_chunks == 0;
   const double batches = std::max(1.0, whole ? wave_positions(p) / 16 : (double)p->n_b * p->max_out_cells / (a.dw_chunks * 64.0));
-  const double tw = 2.0 + batches * (vec ? 0.46 : 0.91), loadw = a.dw_blocks / 256.0;
-  const double longest = std::max(t, tw), all = (t * load + tw * loadw) / resident * (1 + 0.4 * std::min(load + loadw, 3.0));
-  const double reduce = whole ? 0 : 2.0 + 6.4e-6 * a.slot * p->n_workers * a.dw_chunks;
-  return joined(7.8, 5.0 + std::max(longest, all) + 0.8 * std::min(longest, all) + reduce);
+  const double tw = 1.6 + batches * (vec ? 0.91 : 1.5) * (bf16 ? 1.2 : 1.0), loadw = a.dw_blocks / 256.0;
+  const double longest = std::max(t, tw), all = (t * load + tw * loadw) / resident * (1 + 0.27 * std::min(load + loadw, 3.0));
+  const double reduce = whole ? 0 : 2.0 + 13e-6 * a.slot * p->n_workers * a.dw_chunks;
+  return joined(7.8 + 0.25 * p->n_workers, 3.5 + std::max(longest, all) + 0.58 * std::min(longest, all) + reduce + 0.092 * written);
 }
 
 // (a call that is recorded cannot bring the tables to the device: where it is the plan's first, the general kernels take it)

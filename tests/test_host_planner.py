@@ -390,7 +390,7 @@ def test_choice_of_the_fused_kernels_is_that_of_the_call():
     """What the launches apart are estimated at depends on the alignment of the weights, too (bf16: tiles or the gather kernel): a
     plan answers for either whatever it was asked before."""
     def plan():
-        return dd.distdl_plan_create(3, 7, 32, 24, [5, 4, 4], [3, 2, 2], [3] * 3, [1] * 3, [1] * 3, [1] * 3, torch.bfloat16)
+        return dd.distdl_plan_create(3, 1, 20, 4, [7, 7, 5], [2, 2, 1], [5] * 3, [2] * 3, [2] * 3, [1] * 3, torch.bfloat16)
     first, second = plan(), plan()
     answers = {aligned: dd.distdl_debug_conv_fused(first, aligned) for aligned in (1, 2)}
     assert answers[1] != answers[2]
