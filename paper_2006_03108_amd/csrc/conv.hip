@@ -385,12 +385,15 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
 // beside calls of 7 to 9 us either way, whose times vary by a tenth.
 // What the margins leave out: estimates are off by an eighth, and at 0.9 and 0.8, without what is written and the workers in
 // them, nineteen of 650 layers were slower, up to 1.45 times (back, bf16, 4 -> 37, 3 x 3, stride 2, 2 x 38 x 40 23.5 / 33.9).
+static double launches_us(const distdl_plan* p, bool backward) {  // what the host takes for them
+  return backward ? 12.0 + 0.25 * p->n_workers : 9.5 + 0.2 * p->n_workers;
+}
 static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool aligned, bool w_aligned) {
   int8_t& known = p->fused_kernel[backward][vec][aligned][w_aligned];
   if (known >= 0) return known != 0;
   const double us = conv_fused_us(p, backward, vec);
   const bool boxes = !p->fwd1.blocks.empty() || !p->fwd16.blocks.empty();
-  double apart = backward ? 12.0 + 0.25 * p->n_workers : 9.5 + 0.2 * p->n_workers;  // (what the host takes for the launches)
+  double apart = launches_us(p, backward);
   const double room = us < 20 ? 0.8 : 0.7;
   if (us >= room * apart && std::isfinite(us) && (backward || boxes)) {
     const Corr k = choose_corr(p, backward, aligned, w_aligned);
@@ -427,6 +430,14 @@ static bool write_back_hides(const distdl_plan* p, Corr kernel, Wgrad wgrad) {
 static int weight_job(distdl_plan* p, Corr kernel, bool backward, const void* w, bool aligned, hipStream_t st, WeightJob& job) {
   if (kernel == Corr::kSplit) return split_weight_job(p, backward, (const float*)w, st, job);
   return kernel == Corr::kAny ? any_weight_job(p, backward, w, aligned, st, job) : DISTDL_OK;
+}
+
+// The tables that go to the device with those of a plan whose first call is a fused forward pass: its own, and the adjoint's where they
+// are few and it is likely to want them.  (A copy of their own takes 15 to 20 us of the first adjoint; 64 records take 3 us of a
+// forward pass that may be all that the plan ever makes.)
+static void fused_first_tables(const distdl_plan* p, bool vec) {
+  conv_fused_make_tables(p, false);
+  if (conv_fused_records(p, true) <= 64 && conv_fused_us(p, true, vec) < 1.25 * launches_us(p, true)) conv_fused_make_tables(p, true);
 }
 
 // Whether an output of a call lies on one of its inputs, or on another output: the fused kernels write y, and dx, dw and db, while
@@ -586,7 +597,7 @@ int conv_fwd_core(distdl_plan* plan, void* const x_bufs_dev[], const void* w_dev
   const bool w_aligned = (uintptr_t)w_dev % 16 == 0;
   const bool fused = halo && choose_fused(plan, false, vec, xvec, w_aligned) && conv_fused_ready(plan, false, st) &&
                      !fwd_overlaps(plan, x_bufs_dev, w_dev, bias_dev, y_dev);
-  if (fused && !plan->d_workers) (void)conv_fused_us(plan, true, vec);  // (the adjoint's tables, on the way with the others)
+  if (fused && !plan->d_workers) fused_first_tables(plan, vec);
   const Corr kernel = fused ? Corr::kDirect : choose_fwd(plan, xvec, w_aligned);
   if ((rc = plan_prepare_device(plan))) return rc;
   for (int w = 0; w < plan->n_workers; ++w) {

@@ -582,7 +582,7 @@ struct Shape {
   int NT = 1, lds = 0;
   bool fits = false;
 };
-// What a plan keeps of one direction: the shapes of its launch without and with 16-byte accesses, its tables
+// What a plan keeps of one direction: the shapes of its launch without and with 16-byte accesses, and, once it is to run, its tables
 struct FusedPlan {
   Shape shape[2];
   std::vector<FusedRec> recs;
@@ -621,30 +621,56 @@ FusedDim dim_of(const distdl_plan* p, int mode, int w, int d, int par, int nt, i
   return g;
 }
 
-// The tables of a direction; false: a class has too many positions
-bool make_tables(const distdl_plan* p, int mode, FusedPlan& f, int& most_taps, int64_t& most_positions) {
-  int ncls = 1, taps = 1;
-  for (int d = 0; d < 3; ++d) {
-    taps *= p->ksize[d];
-    if (mode == 1) ncls *= p->stride[d];
+// The classes of a direction: a stride's in the adjoint, one forward
+struct Classes {
+  int n = 1, taps = 1, most_taps = 1;
+  std::vector<int> nt, tf, ts;  // [class][dimension]: taps, the first and the step between them
+  int par(const distdl_plan* p, int mode, int cls, int d) const {
+    if (mode == 0) return 0;
+    return d == 0 ? cls / (p->stride[1] * p->stride[2]) : d == 1 ? cls / p->stride[2] % p->stride[1] : cls % p->stride[2];
   }
-  most_taps = 1, most_positions = 1;
-  std::vector<int> nt(ncls * 3), tf(ncls * 3), ts(ncls * 3);
-  for (int cls = 0; cls < ncls; ++cls) {
-    int par[3] = {0, 0, 0}, all = 1;
-    if (mode == 1) par[0] = cls / (p->stride[1] * p->stride[2]), par[1] = cls / p->stride[2] % p->stride[1], par[2] = cls % p->stride[2];
+};
+Classes classes_of(const distdl_plan* p, int mode) {
+  Classes c;
+  for (int d = 0; d < 3; ++d) {
+    c.taps *= p->ksize[d];
+    if (mode == 1) c.n *= p->stride[d];
+  }
+  c.nt.resize(c.n * 3), c.tf.resize(c.n * 3), c.ts.resize(c.n * 3);
+  for (int cls = 0; cls < c.n; ++cls) {
+    int all = 1;
     for (int d = 0; d < 3; ++d) {
-      int &n = nt[cls * 3 + d] = p->ksize[d], &f = tf[cls * 3 + d] = 0, &s = ts[cls * 3 + d] = 1;
-      if (mode == 1) class_taps(p->ksize[d], p->stride[d], p->dilation[d], par[d], n, f, s);
+      int &n = c.nt[cls * 3 + d] = p->ksize[d], &f = c.tf[cls * 3 + d] = 0, &s = c.ts[cls * 3 + d] = 1;
+      if (mode == 1) class_taps(p->ksize[d], p->stride[d], p->dilation[d], c.par(p, mode, cls, d), n, f, s);
       all *= n;
     }
-    most_taps = std::max(most_taps, all);
+    c.most_taps = std::max(c.most_taps, all);
   }
+  return c;
+}
+
+// The most positions of a worker and class: extents of a dimension depend on a worker's place in it and on the class's parity there
+int64_t most_positions(const distdl_plan* p, int mode) {
+  int64_t most = p->n_b;
+  for (int d = 0; d < 3; ++d) {
+    int32_t n = 0;
+    const int step = d == 0 ? p->P[1] * p->P[2] : d == 1 ? p->P[2] : 1;  // from worker to worker along d
+    for (int at = 0; at < p->P[d]; ++at)
+      for (int par = 0; par < (mode == 0 ? 1 : p->stride[d]); ++par) n = std::max(n, dim_of(p, mode, at * step, d, par, 0, 0).nq);
+    most *= n;
+  }
+  return std::max<int64_t>(most, 1);
+}
+
+// The tables of a direction
+void make_tables(const distdl_plan* p, int mode, FusedPlan& f) {
+  const Classes c = classes_of(p, mode);
+  const int ncls = c.n, taps = c.taps, most_taps = c.most_taps;
   f.recs.resize((size_t)p->n_workers * ncls);
   f.tap_steps.assign((size_t)ncls * most_taps, int4{0, 0, 0, 0});
   f.tap_index.assign((size_t)ncls * taps, -1);
   for (int cls = 0; cls < ncls; ++cls) {
-    const int *n = &nt[cls * 3], *first = &tf[cls * 3], *s = &ts[cls * 3];
+    const int *n = &c.nt[cls * 3], *first = &c.tf[cls * 3], *s = &c.ts[cls * 3];
     int at = 0;
     for (int i0 = 0; i0 < n[0]; ++i0)
       for (int i1 = 0; i1 < n[1]; ++i1)
@@ -663,15 +689,11 @@ bool make_tables(const distdl_plan* p, int mode, FusedPlan& f, int& most_taps, i
       r = FusedRec{};
       int64_t total = p->n_b;
       for (int d = 0; d < 3; ++d) {
-        int par = 0;
-        if (mode == 1) par = d == 0 ? cls / (p->stride[1] * p->stride[2]) : d == 1 ? cls / p->stride[2] % p->stride[1] : cls % p->stride[2];
-        r.d[d] = dim_of(p, mode, w, d, par, n[0] * n[1] * n[2], first[d]);
+        r.d[d] = dim_of(p, mode, w, d, c.par(p, mode, cls, d), n[0] * n[1] * n[2], first[d]);
         total *= r.d[d].nq;
       }
-      if (total >= (1 << 20)) return false;  // (they are divided through a float)
       r.total = (int32_t)total;
       r.ntaps = n[0] * n[1] * n[2];
-      most_positions = std::max(most_positions, total);
     }
   }
   f.nears.resize((size_t)p->n_workers * 27);
@@ -701,7 +723,6 @@ bool make_tables(const distdl_plan* p, int mode, FusedPlan& f, int& most_taps, i
         near.shift += (f3[d] < 0 ? below : above) * stride[d];
       }
     }
-  return true;
 }
 
 Shape shape_of(const distdl_plan* p, int mode, bool vec, int taps, int64_t positions) {
@@ -756,20 +777,29 @@ FusedPlan* plan_of(const distdl_plan* p, int mode) {
   std::shared_ptr<void>& kept = p->fused_plan[mode];
   if (!kept) {
     auto f = std::make_shared<FusedPlan>();
-    int taps;
-    int64_t positions;
-    if (make_tables(p, mode, *f, taps, positions))
-      for (int vec = 0; vec < 2; ++vec) f->shape[vec] = shape_of(p, mode, vec != 0, taps, positions);
+    if (const int64_t positions = most_positions(p, mode); positions < (1 << 20))  // (they are divided through a float)
+      for (int vec = 0; vec < 2; ++vec) f->shape[vec] = shape_of(p, mode, vec != 0, classes_of(p, mode).most_taps, positions);
     kept = f;
   }
   return (FusedPlan*)kept.get();
 }
+
+}  // namespace
+
+// (what an estimate asks for is in the shapes: tables are made for the directions that run)
+void conv_fused_make_tables(const distdl_plan* p, bool backward) {
+  if (FusedPlan* const f = plan_of(p, backward); f->recs.empty()) make_tables(p, backward, *f);
+}
+int conv_fused_records(const distdl_plan* p, bool backward) { return p->n_workers * (backward ? p->stride[0] * p->stride[1] * p->stride[2] : 1); }
+
+namespace {
 
 // the launch of a direction, its tables on the device
 int shape_on_device(const distdl_plan* p, int mode, bool vec, Shape& sh) {
   FusedPlan* const f = plan_of(p, mode);
   if (!f->d_recs) {
     HostTables t;
+    conv_fused_make_tables(p, mode != 0);
     f->add_to(t);
     if (int rc = t.to_device(&f->own)) return rc;
   }
@@ -875,7 +905,7 @@ bool conv_fused_ready(const distdl_plan* p, bool backward, hipStream_t st) {
 
 void conv_fused_add_tables(const distdl_plan* p, HostTables& t) {
   for (const auto& kept : p->fused_plan)
-    if (FusedPlan* const f = (FusedPlan*)kept.get(); f && !f->d_recs && (f->shape[0].fits || f->shape[1].fits)) f->add_to(t);
+    if (FusedPlan* const f = (FusedPlan*)kept.get(); f && !f->d_recs && !f->recs.empty()) f->add_to(t);
 }
 
 int conv_fwd_fused(distdl_plan* p, const void* w, const void* bias, bool vec, bool wide, hipStream_t st) {

@@ -462,3 +462,17 @@ def test_overlap_of_many_workers_arrays():
 
     for shuffled in (False, True):
         assert least(1024, shuffled) < 80 * least(64, shuffled)
+
+
+def test_choice_of_the_fused_kernels_makes_no_tables():
+    """A thousand workers, a stride of 4 x 4 x 4: 65536 records of 176 bytes and more, 11.5 MB a plan, which a layer that goes another
+    way has no use for."""
+    def resident():
+        with open("/proc/self/statm") as f:
+            return int(f.read().split()[1]) * os.sysconf("SC_PAGE_SIZE")
+    new = lambda: dd.distdl_plan_create(3, 1, 8, 8, [64, 64, 128], [8, 8, 16], [4] * 3, [4] * 3, [0] * 3, [1] * 3)
+    assert dd.distdl_debug_conv_fused(new()) == (False, False)  # (what the first use of anything takes)
+    plans = [new() for _ in range(6)]
+    before = resident()
+    assert all(dd.distdl_debug_conv_fused(p) == (False, False) for p in plans)
+    assert resident() - before < 6 * 5e6
