@@ -373,29 +373,27 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
   }
 }
 
-// Small layers: everything of a direction in one launch (conv_fused.hip) where that is estimated at less than 0.8 of the launches
-// it replaces, from 20 us at less than 0.7; theirs are H and its kernel, or both contractions, the reduction and H*, each estimated
-// as above, and what the host takes for them.  Without a halo exchange there is one launch less to save in the forward pass, which
-// then goes that way only where it would take little more than a launch.  us, launches apart / together, forward and
-// back: 1 -> 1, 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 20 -> 4, 3^3, 4 x 13 x 12 x 17 on 3 x 2 x 2 26.8 / 14.1 and
-// 38.5 / 22.4; but 5 -> 32, 5^3, stride 2, bf16, 13 x 14 x 11 x 15 22 / 45 and 58 / 400.  Up to 100 us forward and 40 us back, where
-// the fp64 matrix instructions and the second reading of x weigh more than the launches (27 -> 11, 3 x 3, 10 x 244 x 329 258 / 283;
-// 24 -> 4, 3^3, bf16, 11 x 62 x 54 x 61 1026 / 2498).  Of 1475 layers, up to 0.4 GFLOP, 1003 go forward that way and 847 back: 1.57 and 1.75
-// times as fast in the mean; six and one of them 1.06 to 1.24 times slower (bf16, 4 -> 60, 2 x 2, 2 x 142 x 123 13.7 / 16.9),
-// beside calls of 7 to 9 us either way, whose times vary by a tenth.
-// What the margins leave out: estimates are off by an eighth, and at 0.9 and 0.8, without what is written and the workers in
-// them, nineteen of 650 layers were slower, up to 1.45 times (back, bf16, 4 -> 37, 3 x 3, stride 2, 2 x 38 x 40 23.5 / 33.9).
-static double launches_us(const distdl_plan* p, bool backward) {  // what the host takes for them
-  return backward ? 12.0 + 0.25 * p->n_workers : 9.5 + 0.2 * p->n_workers;
-}
+// Small layers: everything of a direction in one launch (conv_fused.hip) where that is estimated at less than 0.8 (0.75 from 20 us; back
+// 0.85 and 0.8) of the launches it replaces; theirs are H and its kernel, or both contractions, the reduction and H*, each estimated
+// as above, and what the host takes for them; its time for the workers' arrays is on neither side.  Without a halo exchange there is
+// one launch less to save in the forward pass, which then goes that way only where it would take little more than a launch.  us,
+// launches apart / together, forward and back: 1 -> 1, 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 20 -> 4, 3^3, 4 x 13 x
+// 12 x 17 on 3 x 2 x 2 26.8 / 14.1 and 38.5 / 22.4; but 5 -> 32, 5^3, stride 2, bf16, 13 x 14 x 11 x 15 22 / 45 and 58 / 400.  Up to
+// 100 us forward and 40 us back, where the fp64 matrix instructions and the second reading of x weigh more than the launches
+// (27 -> 11, 3 x 3, 10 x 244 x 329 258 / 283; 24 -> 4, 3^3, bf16, 11 x 62 x 54 x 61 1026 / 2498).  Of 1209 layers, up to 0.4 GFLOP, 834 go
+// forward that way and 739 back, 1.63 and 1.79 times as fast in the mean, eight by more than 0.05 slower, up to 1.12 times.
+// What the margins leave out: estimates are off by an eighth, and at 0.9 and 0.8 each way, without what is written and the workers
+// in them, nineteen of 650 layers were slower, up to 1.45 times (back, bf16, 4 -> 37, 3 x 3, stride 2, 2 x 38 x 40 23.5 / 33.9).
+static double arrays_us(const distdl_plan* p, bool backward) { return (backward ? 0.25 : 0.2) * p->n_workers; }  // the host's time for them, either way
+static double launches_us(const distdl_plan* p, bool backward) { return (backward ? 12.0 : 9.5) + arrays_us(p, backward); }  // and for the launches apart
 static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool aligned, bool w_aligned) {
   int8_t& known = p->fused_kernel[backward][vec][aligned][w_aligned];
   if (known >= 0) return known != 0;
   const double us = conv_fused_us(p, backward, vec);
   const bool boxes = !p->fwd1.blocks.empty() || !p->fwd16.blocks.empty();
   double apart = launches_us(p, backward);
-  const double room = us < 20 ? 0.8 : 0.7;
-  if (us >= room * apart && std::isfinite(us) && (backward || boxes)) {
+  const double room = backward ? (us < 20 ? 0.85 : 0.8) : us < 20 ? 0.8 : 0.75, arrays = arrays_us(p, backward);
+  if (us - arrays >= room * (apart - arrays) && std::isfinite(us) && (backward || boxes)) {
     const Corr k = choose_corr(p, backward, aligned, w_aligned);
     double corr = 0, wgrad = 0;
     if (k == Corr::k16) corr = corr16_us(p, backward);
@@ -408,7 +406,7 @@ static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool ali
     const double device = backward ? 6.1 + 1.1 * corr + wgrad : 2.2 + 1.2 * corr;
     apart = corr <= 0 || (backward && wgrad <= 0) ? 0.0 : std::sqrt(std::sqrt(std::pow(apart, 4) + std::pow(device, 4)));
   }
-  known = us < room * apart && us < (backward ? 40 : 100);
+  known = us - arrays < room * (apart - arrays) && us < (backward ? 40 : 100);
   return known != 0;
 }
 
