@@ -7,7 +7,6 @@
 //   adjoint   dW_ij = dy_i^T x_j,  db_i = sum_n dy_i,  dx_j = sum_i dy_i W_ij
 #include <algorithm>
 #include <atomic>
-#include <cmath>
 #include <cstring>
 
 #include "affine_small.h"
@@ -221,13 +220,15 @@ static std::vector<GemmBlock> blocks_dw(const distdl_affine_plan* p, const void*
   return blocks;
 }
 
-// Small layers (affine_small.hip): where their launch is estimated at less than 0.95 of the calls on the tiled kernels.  What
-// decides is that those start a tile at a time, and split a long K over two launches; with many tiles, or matrix instructions in
-// earnest, they are the faster ones.  us, tiled / small, forward and back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 295 x 624 -> 28,
-// 2 x 1 10.2 / 6.4 and 12.9 / 7.7; 37 x 2000 -> 1001, 2 x 3 12.9 / 10.3 and 18.1 / 20.5; 327 x 84 -> 7210, 2 x 2 18.9 / 25.1 and 25.5 / 46.9; bf16 of
-// odd rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4 and 16.6 / 12.0.  Over 120 layers of 1 to 100 rows the choice is 1.26 and 1.13
-// times as fast as the tiled kernels in the mean, and up to 1.12 times slower in three calls of 240.
-static double joined(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
+// Small layers (affine_small.hip): where their launch is estimated at less than 0.95 of the calls on the tiled kernels (from 12 us 0.85;
+// bf16 forward 0.88, back 0.9), the host's time for the arrays on neither side.  What decides is that the tiled ones start a tile at a
+// time, and split a long K over two launches; with many tiles, or matrix instructions in earnest, they are the faster ones.  us,
+// tiled / small, forward and back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 295 x 624 -> 28, 2 x 1 10.2 / 6.4 and
+// 12.9 / 7.7; 37 x 2000 -> 1001, 2 x 3 12.9 / 10.3 and 18.1 / 20.5; 327 x 84 -> 7210, 2 x 2 18.9 / 25.1 and 25.5 / 46.9; bf16 of odd
+// rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4 and 16.6 / 12.0.  Of 1500 layers of 1 to 1024 rows the choice is 1.20 and 1.11 times as fast
+// as the tiled kernels in the mean (bf16 1.05 and 1.17; the better one each time 1.21, 1.13, 1.10, 1.19), 30 directions of 3000 more
+// than 0.05 slower, up to 1.2 times.  The tiled kernels' times are fitted to half of them; nine tenths are within 16 % (bf16 forward
+// 30 %).
 static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& blocks, bool bf16) {
   if (p->route == 0 || !gemm_split_usable(blocks, bf16, true, true)) return false;  // (their range is the same)
   // (bf16 rows of whole 16-byte pieces take 7 to 9 us either way)
@@ -235,8 +236,10 @@ static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& block
   const bool vec = gemm_split_vec(blocks, bf16, true, true), wide = bf16 ? affine_small_words(blocks) : vec;
   int known = p->small_fwd[wide].load(std::memory_order_relaxed);
   if (known < 0) {
-    const double us = affine_small_fwd_us(blocks, bf16);
-    known = us < 0.95 * joined(9.2, 1.6 + 1.1 * gemm_split_plan(blocks, vec).us);
+    const double arrays = 0.13 * (blocks.size() * (blocks[0].nseg + 1) + blocks[0].nseg), us = affine_small_fwd_us(blocks, bf16, arrays);
+    const GemmSplitPlan y = gemm_split_plan(blocks, vec);
+    const double tiled = bf16 ? joined(7.7 + arrays, 1.6 * y.stages_us + 0.84 * y.split_us) : joined(7.4 + arrays, 3.3 + 1.2 * y.stages_us + 0.66 * y.split_us);
+    known = us - arrays < (bf16 ? 0.88 : us - arrays < 12 ? 0.95 : 0.85) * (tiled - arrays);
     p->small_fwd[wide].store(known, std::memory_order_relaxed);
   }
   return known || p->route > 0;
@@ -245,16 +248,20 @@ static bool small_bwd(distdl_affine_plan* p, const std::vector<GemmBlock>& bx, c
   if (p->route == 0 || !gemm_split_usable(bx, bf16, true, false) || !gemm_split_usable(bw, bf16, false, false)) return false;
   const bool vec = gemm_split_vec(bx, bf16, true, false) && gemm_split_vec(bw, bf16, false, false);
   const bool tiles = bf16 && gemm_mfma_usable(bx, bf16, true, false) && gemm_mfma_usable(bw, bf16, false, false);
-  int known = p->small_bwd[vec][tiles].load(std::memory_order_relaxed);
+  const bool wide = bf16 ? affine_small_words(bx) && affine_small_words(bw) : vec;
+  int known = p->small_bwd[wide][tiles].load(std::memory_order_relaxed);
   if (known < 0) {
-    const double us = affine_small_bwd_us(bx, bw, bf16), x = gemm_split_plan(bx, vec).us, w = gemm_split_plan(bw, vec).us;
-    // (bf16 tiles: two launches and more, 12 to 20 us; 29 x 32 -> 816 on 1 x 2 15.1 / 9.0, 73 x 176 -> 192 on 2 x 2 13.6 / 9.7,
-    // 299 x 3440 -> 96 16.6 / 14.7)
-    const double tiled = tiles ? 12.6 : joined(10.4, 1.28 * std::max(x, w) + 1.37 * std::min(x, w));
+    const double arrays = 0.13 * (2 * bw.size() + 2 * bx.size() + bx[0].nseg), us = affine_small_bwd_us(bx, bw, bf16, arrays);
+    const GemmSplitPlan x = gemm_split_plan(bx, vec), w = gemm_split_plan(bw, vec);
+    const double most = std::max(x.stages_us, w.stages_us), least = std::min(x.stages_us, w.stages_us), split = std::max(x.split_us, w.split_us),
+                 other = std::min(x.split_us, w.split_us), out = 1e-6 * ((double)p->n_b * p->n_fi + (double)p->n_fi * p->n_fo);
+    const double tiled = tiles  ? joined(13.0 + arrays, 6.3 + 1.1 * w.stages_us)  // (two launches and more)
+                         : bf16 ? joined(7.6 + arrays, 0.6 * most + 1.7 * least + 1.3 * split + 0.3 * other + 1.1 * out)
+                                : joined(7.5 + arrays, 2.1 + 0.95 * most + 1.4 * least + 0.8 * split + 0.52 * other + 1.6 * out);
     // (a bf16 dW leaves value by value: above 20 us, 20 x 4901 -> 1974 42 / 49, 9 x 2836 -> 3673 on 1 x 2 45 / 48, that is what
     // a call takes)
-    known = us < 0.95 * tiled && (!bf16 || us < 20);
-    p->small_bwd[vec][tiles].store(known, std::memory_order_relaxed);
+    known = us - arrays < 0.9 * (tiled - arrays) && (!bf16 || us < 20);
+    p->small_bwd[wide][tiles].store(known, std::memory_order_relaxed);
   }
   return known || p->route > 0;
 }

@@ -463,25 +463,30 @@ static SmallShape best_dw(const GemmBlock* d, const std::vector<GemmBlock>& b, b
   return shape_us(shared, bf16) < shape_us(own, bf16) ? shared : own;
 }
 
-// Estimated times of the calls, fitted to 160 layers of 1 to 1024 rows and 10 to 8192 features; four fifths are within 13 %.  A product:
-// a start, and a wave's chunks with their loads and matrix instructions, which take longer with two workgroups on a compute unit.
-// With it, by a fourth power: what the host takes, more for each array of the call.
-static double joined(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
-static double product_us(const SmallShape& s, double start, double chunk, double tile, double shared) {
-  return start + s.chunks * (chunk + tile * s.mt * s.nt) * (1 + shared * std::min(s.wgs / 256.0, 2.0));
+// Estimated times of the calls, fitted to 750 layers of 1 to 1024 rows and 10 to 8192 features; nine tenths are within 14 %.  A product:
+// a start, and a wave's chunks with their loads and matrix instructions, which take longer with two workgroups on a compute unit
+// (of four M-tiles forward, whose operands take 92 KB, there is one); what is written, value by value in bf16.  With it, by a
+// fourth power: what the host takes.
+static double shared_cu(const SmallShape& s, double more) { return 1 + more * std::min(s.wgs / 256.0, 2.0); }
+static double written(const std::vector<GemmBlock>& blocks) {  // 10^6 elements
+  double n = 0;
+  for (const GemmBlock& b : blocks) n += 1e-6 * b.M * b.N;
+  return n;
 }
-double affine_small_fwd_us(const std::vector<GemmBlock>& blocks, bool bf16) {
+double affine_small_fwd_us(const std::vector<GemmBlock>& blocks, bool bf16, double arrays) {
   const SmallShape s = best_fwd(nullptr, blocks, bf16);
-  const size_t arrays = blocks.size() * (blocks[0].nseg + 1) + blocks[0].nseg;
-  const double us = std::max(1.0, s.wgs / 512.0) * product_us(s, 2.1, 0.12, bf16 ? 0.48 : 0.60, 0.78);
-  return joined(6.8 + 0.13 * arrays, us * (bf16 && !affine_small_words(blocks) ? 1.5 : 1.0));  // (rows of odd bf16 come value by value)
+  const double rounds = std::ceil(s.wgs / (s.mt == 4 ? 256.0 : 512.0)), chunk = bf16 ? 0.28 + 0.36 * s.mt * s.nt : 0.23 + 0.65 * s.mt * s.nt;
+  const double us = rounds * (1.1 + s.chunks * chunk * (s.mt == 4 ? 1 : shared_cu(s, bf16 ? 0.29 : 0.2))) + (bf16 ? 2.1 : 2.6) * written(blocks);
+  return joined(6.9 + arrays, us * (bf16 && !affine_small_words(blocks) ? 1.7 : 1.0));  // (rows of odd bf16 come value by value)
 }
-double affine_small_bwd_us(const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16) {
+double affine_small_bwd_us(const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16, double arrays) {
   const SmallShape x = best_dx(nullptr, bx, bf16), w = best_dw(nullptr, bw, bf16);
-  const double tx = product_us(x, 2.05, 0.64, bf16 ? 0.32 : 0.29, 0.54), tw = product_us(w, 1.46, 0.78, bf16 ? 0.17 : 0.48, 0.46);
+  const double odd = bf16 && !(affine_small_words(bx) && affine_small_words(bw)) ? 1.4 : 1.0, dw = written(bw), out = written(bx) + dw;
+  const double tx = odd * (bf16 ? 1.0 + x.chunks * (0.46 + 0.22 * x.mt * x.nt) * shared_cu(x, 0.48) : 2.0 + x.chunks * (0.1 + 0.62 * x.mt * x.nt) * shared_cu(x, 0.66));
+  const double tw = odd * (bf16 ? 0.5 + w.chunks * (0.1 + 0.4 * w.mt * w.nt) : 0.5 + w.chunks * (1.6 + 0.43 * w.mt * w.nt) * shared_cu(w, 0.72));
+  const double store = bf16 ? 1.7 * out + 0.36 * dw / std::min(1.0, std::max(0.05, w.wgs / 256.0)) : 0.15 * out;
   const double longest = std::max(tx, tw), all = tx * x.wgs / 512.0 + tw * w.wgs / 512.0;
-  const size_t arrays = 2 * bw.size() + 2 * bx.size() + bx[0].nseg;
-  return joined(7.7 + 0.13 * arrays, std::max(longest, all) + 0.72 * std::min(longest, all));
+  return joined(bf16 ? 7.7 + arrays : 7.4 + arrays, std::max(longest, all) + (bf16 ? 0.64 : 0.22) * std::min(longest, all) + store);
 }
 
 template <bool BF16, bool A_KC, bool B_KC, int MT, int NT, bool SPLIT>

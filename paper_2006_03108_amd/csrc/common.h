@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cmath>
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
@@ -26,6 +27,9 @@ int set_error(int code, const char* fmt, ...);
   } while (0)
 
 inline size_t dtype_size(distdl_dtype t) { return t == DISTDL_F32 ? 4 : 2; }
+
+// Estimated times (us) of what the host and the device take for the same call: the longer one, and more where they are alike.
+inline double joined(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
 
 // Lets kernel `Kernel` be launched with more than 64 KB of dynamic LDS (up to the 160 KB of a compute unit).
 // The attribute is set once per kernel and device: the call is not cheap, and a launch path that made it every

@@ -404,7 +404,7 @@ static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool ali
     const Wgrad wk = backward ? choose_wgrad(p, vec) : Wgrad::kAny;
     if (backward && (wk == Wgrad::kAny || wk == Wgrad::k16)) wgrad = wgrad_us(p, wk);
     const double device = backward ? 6.1 + 1.1 * corr + wgrad : 2.2 + 1.2 * corr;
-    apart = corr <= 0 || (backward && wgrad <= 0) ? 0.0 : std::sqrt(std::sqrt(std::pow(apart, 4) + std::pow(device, 4)));
+    apart = corr <= 0 || (backward && wgrad <= 0) ? 0.0 : joined(apart, device);
   }
   known = us - arrays < room * (apart - arrays) && us < (backward ? 40 : 100);
   return known != 0;

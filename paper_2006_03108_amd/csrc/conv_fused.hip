@@ -870,7 +870,6 @@ void add_wgrad(const distdl_plan* p, Shape& sh) {
 // for each; y leaves at 5 TB/s, or value by value at a million in 1.1 us.  Two terms joined by a fourth power: what the host takes to launch, more
 // for each worker's arrays, and what the device does.  Fitted to 600 layers of 1 to 64 channels, one to three dimensions, up to
 // 600 000 positions and 0.4 GFLOP; four fifths are within 12 % (forward) and 14 %.
-static double joined(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
 double conv_fused_us(const distdl_plan* p, bool backward, bool vec) {
   if (!small_tensors(p)) return INFINITY;
   Shape& sh = plan_of(p, backward)->shape[vec];

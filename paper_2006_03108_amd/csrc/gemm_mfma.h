@@ -62,7 +62,7 @@ struct GemmSplitPlan {
   int tiles = 0, nsplit = 1, wgs = 0;
   int64_t max_mn = 0;
   size_t partial_floats = 0;  // of the fp32 partial tiles
-  double us = 0;              // estimated time, of the stages and of what the split costs
+  double stages_us = 0, split_us = 0;  // estimated times of the stages and of what the split of K costs
 };
 bool gemm_split_usable(const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc);
 bool gemm_split_vec(const std::vector<GemmBlock>& blocks, bool bf16, bool a_kc, bool b_kc);

@@ -581,9 +581,8 @@ GemmSplitPlan gemm_split_plan(const std::vector<GemmBlock>& blocks, bool vec) {
   double best = 1e30;
   for (int ns = 1; ns <= 16 && ns <= std::max(1, stages / 2); ++ns) {
     const double res = (double)all * ns / 256, tau = res <= 1 ? 1.4 : 1.4 + 0.8 * (std::min(res, 2.0) - 1);
-    const double cost = (stages + ns - 1) / ns * tau * std::max(1.0, res / 2) +
-                        (ns > 1 ? 5 + ns * (double)p.max_mn * blocks.size() * 8 / 5e6 : 0);
-    if (cost < best * 0.98) best = p.us = cost, p.nsplit = ns;
+    const double work = (stages + ns - 1) / ns * tau * std::max(1.0, res / 2), split = ns > 1 ? 5 + ns * (double)p.max_mn * blocks.size() * 8 / 5e6 : 0;
+    if (work + split < best * 0.98) best = work + split, p.stages_us = work, p.split_us = split, p.nsplit = ns;
   }
   p.wgs = p.tiles * p.nsplit * (int)blocks.size();
   p.partial_floats = p.nsplit > 1 ? (size_t)p.max_mn * p.nsplit * blocks.size() : 0;
