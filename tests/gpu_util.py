@@ -64,7 +64,7 @@ class ConvLayer:
         g = torch.Generator(device="cuda").manual_seed(seed)
         D = len(shape)
         each = lambda v: list(v) if isinstance(v, (list, tuple)) else [v] * D
-        self.k, self.s, self.D = each(k), each(s), D
+        self.k, self.s, self.D, self.aligned = each(k), each(s), D, offset == 0
         self.dil = each(1 if dil is None else dil)
         p = [v // 2 for v in self.k] if p is None else each(p)
 
@@ -89,6 +89,18 @@ class ConvLayer:
         dd.distdl_conv_fwd(self.plan, [self.x], self.w, None, [self.y])
         dd.distdl_conv_bwd(self.plan, [self.x], self.w, [self.dy], [self.dx], self.dw, self.db, self.ws)
         return self.y, self.dx[self.bulk], self.dw
+
+    def run_apart(self):
+        """The same with the halo exchange in calls of its own: on the kernels that distdl_debug_conv_kernels names, whatever the size."""
+        dd.distdl_halo_fwd(self.plan, [self.x])
+        dd.distdl_conv_local_fwd(self.plan, [self.x], self.w, None, [self.y])
+        dd.distdl_conv_local_bwd(self.plan, [self.x], self.w, [self.dy], [self.dx], self.dw, self.db, self.ws)
+        dd.distdl_halo_adj(self.plan, [self.dx])
+        return self.y, self.dx[self.bulk], self.dw
+
+    def ways(self):
+        """run, and run_apart where run takes a direction in one launch"""
+        return [self.run] + [self.run_apart] * any(dd.distdl_debug_conv_fused(self.plan, self.aligned))
 
     def exact(self):
         x, w, dy = self.x.double(), self.w.double(), self.dy.double()

@@ -123,24 +123,39 @@ def test_fused_layer(cfg, dtype, offset):
 @pytest.mark.parametrize("cfg", [FUSED[i] for i in (4, 5, 7, 8, 9, 10, 11)], ids=_ids)
 def test_fused_layer_with_values_that_are_not_finite(cfg):
     """An infinity in a cell next to a neighbour, and weights that are not finite, which a cell of dx that they do not reach has
-    nothing to do with: the same numbers, infinities and NaNs as from the general kernels (but the 16 x 16 tiles, which make NaNs of
-    such weights' products with cells that do not exist)."""
+    nothing to do with: the numbers, infinities and NaNs of fp64 sums, and of the general kernels (but the 16 x 16 tiles, which make
+    NaNs of such weights' products with cells that do not exist)."""
     require_gpu()
     L = _Layer(cfg, F32)
-    assert dd.distdl_debug_conv_kernels(L.plan)[1] != 2
-    L.w[(0, 0, *[0] * cfg["D"])], L.w[(cfg["c_out"] - 1, 1, *[-1] * cfg["D"])] = float("inf"), float("nan")
+    assert dd.distdl_debug_conv_fused(L.plan) == (True, True) and dd.distdl_debug_conv_kernels(L.plan)[1] != 2
+    first, last = (0, 0, *[0] * cfg["D"]), (cfg["c_out"] - 1, 1, *[-1] * cfg["D"])
+    L.w[first], L.w[last] = float("inf"), float("nan")
     g = L.plan.query(0)
     L.x[0][(0, *[a + n - 1 for a, n in zip(g["bulk_off"], g["in_size"])], 0)] = float("inf")
     L.dy[-1][(0, *[0] * cfg["D"], 0)] = float("-inf")
+    case, part = L.case, L.part
+    with np.errstate(invalid="ignore"):
+        w = case["w"].astype(np.float64)
+        w[first], w[last] = np.inf, np.nan
+        whole = case["x"].astype(np.float64)
+        whole[(0, 0, *[n - 1 for n in g["in_size"]])] = np.inf
+        bufs = prim.scatter_bulk(whole, part, fill=np.nan)
+        dy = [t.astype(np.float64) for t in prim.scatter_out(case["dy"], part)]
+        dy[-1][(0, 0, *[0] * cfg["D"])] = -np.inf
+        y = layers.dist_conv_forward(bufs, w, case["bias"], part, cfg["stride"], cfg["dilation"])
+        dx, dw, db = layers.dist_conv_adjoint(bufs, w, dy, part, cfg["stride"], cfg["dilation"], True)
+    cl = lambda ts: [torch.from_numpy(np.ascontiguousarray(np.moveaxis(t, 1, -1))).cuda() for t in ts]
+    want = [*cl(bufs), *cl(y), *cl(dx), torch.from_numpy(dw).cuda(), torch.from_numpy(db).cuda()]
     L.run()
     together = [t.clone() for t in L.outputs()]
     L.run_apart()
     assert any(bool(torch.isfinite(t).any()) for t in together[-3:]) and not all(bool(torch.isfinite(t).all()) for t in together)
-    for a, b in zip(together, L.outputs()):
+    for a, b, e in zip(together, L.outputs(), want):
         for of in (torch.isnan, torch.isposinf, torch.isneginf):
-            assert torch.equal(of(a), of(b))
+            assert torch.equal(of(a), of(b)) and torch.equal(of(a), of(e))
         sure = torch.isfinite(b)
         assert float((a[sure].double() - b[sure].double()).norm()) <= 2e-6 * float(b[sure].double().norm())
+        assert float((a[sure].double() - e[sure]).norm()) <= 5e-7 * float(e[sure].norm())
 
 
 def test_fused_calls_from_a_graph_and_on_two_streams():

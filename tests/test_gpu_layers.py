@@ -428,26 +428,28 @@ def test_affine_fwd_bwd(n_b, n_fi, n_fo, P_fo, P_fi, dtype, use_bias):
     g_W = [dev(W_parts[i][j]) for i in range(P_fo) for j in range(P_fi)]
     g_b = [dev(t) for t in b_parts] if use_bias else None
     g_dy = [dev(t) for t in dy_parts]
-    g_y = [torch.full(t.shape, 3.0, dtype=dtype, device="cuda") for t in y_want]
-    g_dx = [torch.full(t.shape, 3.0, dtype=dtype, device="cuda") for t in dx_want]
-    g_dW = [torch.full(dW_want[i][j].shape, 3.0, dtype=dtype, device="cuda") for i in range(P_fo) for j in range(P_fi)]
-    g_db = [torch.full(t.shape, 3.0, dtype=dtype, device="cuda") for t in db_want] if use_bias else None
     plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, dtype)
-    dd.distdl_affine_fwd(plan, g_x, g_W, g_b, g_y)
-    dd.distdl_affine_bwd(plan, g_x, g_W, g_dy, g_dx, g_dW, g_db)
-    torch.cuda.synchronize()
     host = lambda t: t.float().cpu().numpy()
-    for i in range(P_fo):
-        assert_close(host(g_y[i]), y_want[i], tol, f"y_{i}")
-        if use_bias:
-            assert_close(host(g_db[i]), db_want[i], tol, f"db_{i}")
+    for route in (-1, 0):  # what the plan chooses, which takes the small ones to kernels of their own, and the tiled kernels
+        dd.distdl_debug_affine_route(plan, route)
+        g_y = [torch.full(t.shape, 3.0, dtype=dtype, device="cuda") for t in y_want]
+        g_dx = [torch.full(t.shape, 3.0, dtype=dtype, device="cuda") for t in dx_want]
+        g_dW = [torch.full(dW_want[i][j].shape, 3.0, dtype=dtype, device="cuda") for i in range(P_fo) for j in range(P_fi)]
+        g_db = [torch.full(t.shape, 3.0, dtype=dtype, device="cuda") for t in db_want] if use_bias else None
+        dd.distdl_affine_fwd(plan, g_x, g_W, g_b, g_y)
+        dd.distdl_affine_bwd(plan, g_x, g_W, g_dy, g_dx, g_dW, g_db)
+        torch.cuda.synchronize()
+        for i in range(P_fo):
+            assert_close(host(g_y[i]), y_want[i], tol, f"y_{i}")
+            if use_bias:
+                assert_close(host(g_db[i]), db_want[i], tol, f"db_{i}")
+            for j in range(P_fi):
+                assert_close(host(g_dW[i * P_fi + j]), dW_want[i][j], tol, f"dW_{i}{j}")
         for j in range(P_fi):
-            assert_close(host(g_dW[i * P_fi + j]), dW_want[i][j], tol, f"dW_{i}{j}")
-    for j in range(P_fi):
-        assert_close(host(g_dx[j]), dx_want[j], tol, f"dx_{j}")
-    # whole-layer check against the sequential definition
-    assert_close(np.concatenate([host(t) for t in g_y], axis=1), layers.affine_forward(x, W, b if use_bias else None),
-                 tol, "y vs sequential")
+            assert_close(host(g_dx[j]), dx_want[j], tol, f"dx_{j}")
+        # whole-layer check against the sequential definition
+        assert_close(np.concatenate([host(t) for t in g_y], axis=1), layers.affine_forward(x, W, b if use_bias else None),
+                     tol, "y vs sequential")
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
@@ -475,6 +477,7 @@ def test_affine_step_replayed_from_a_graph_matches_eager(n_b, n_fi, n_fo, P_fo, 
     g_dW = [torch.zeros_like(t) for t in g_W]
     g_db = [torch.zeros_like(t) for t in g_b]
     plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, dtype)
+    dd.distdl_debug_affine_route(plan, 0)
 
     def step():
         dd.distdl_affine_fwd(plan, g_x, g_W, g_b, g_y)
@@ -861,6 +864,7 @@ def test_affine_split_against_fp64(n_b, n_fi, n_fo, P_fo, P_fi, offset):
     W, b = [new(size(r), size(c)) for r in rows for c in cols], [new(size(r)) for r in rows]
     y, dx, dW, db = ([new(*t.shape) for t in ts] for ts in (dy, x, W, b))
     plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi)
+    dd.distdl_debug_affine_route(plan, 0)  # (the small ones among them are summed in fp64 elsewhere)
     dd.distdl_affine_fwd(plan, x, W, b, y)
     dd.distdl_affine_bwd(plan, x, W, dy, dx, dW, db)
     err = lambda got, want: float((got.double() - want).norm() / want.norm().clamp_min(1e-300))
@@ -920,14 +924,16 @@ def test_affine_infinities_and_nans_stay_what_fp32_makes_of_them(n_b, n_fi, n_fo
     W[4, :] = 0.0                                # 0 * inf
     plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, 1, 1)
     y, dx, dW = torch.empty(n_b, n_fo, device="cuda"), torch.empty_like(x), torch.empty_like(W)
-    dd.distdl_affine_fwd(plan, [x], [W], None, [y])
-    dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], None)
-    for got, want in ((y, x.double() @ W.double().t()), (dx, dy.double() @ W.double()), (dW, dy.double().t() @ x.double())):
-        finite = want.abs() < 3e38
-        assert torch.equal(torch.isnan(got), torch.isnan(want))
-        assert torch.equal(got == float("inf"), want > 3.5e38) and torch.equal(got == float("-inf"), want < -3.5e38)
-        scale = want[finite].abs().clamp_min(1.0)
-        assert float(((got[finite].double() - want[finite]).abs() / scale).max()) < 1e-4
+    for route in (-1, 0):
+        dd.distdl_debug_affine_route(plan, route)
+        dd.distdl_affine_fwd(plan, [x], [W], None, [y])
+        dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], None)
+        for got, want in ((y, x.double() @ W.double().t()), (dx, dy.double() @ W.double()), (dW, dy.double().t() @ x.double())):
+            finite = want.abs() < 3e38
+            assert torch.equal(torch.isnan(got), torch.isnan(want))
+            assert torch.equal(got == float("inf"), want > 3.5e38) and torch.equal(got == float("-inf"), want < -3.5e38)
+            scale = want[finite].abs().clamp_min(1.0)
+            assert float(((got[finite].double() - want[finite]).abs() / scale).max()) < 1e-4
 
 
 # layers for the gather kernels: remainders of 64 and 256 rows and of 32 and 64 columns, one and several stages of k,

@@ -33,17 +33,18 @@ def test_conv_with_infinities_and_nans(shape):
     L.w[:, c_in - 1] *= 1e-3
     out = L.dy.shape[1:-1]
     L.dy[(last, *(v // 3 for v in out), c_out - 1)], L.dy[(0, *(v // 2 for v in out), 2)] = float("-inf"), float("nan")
-    for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
-        if name == "dw":                                             # (3e38 times dy overflows in one order and not in another)
-            got, want = got[:, :-1], want[:, :-1]
-        sure = (want.abs() < 1e38) | ~torch.isfinite(want)           # (those next to the largest number may go either way)
-        assert torch.equal(torch.isnan(got)[sure], torch.isnan(want)[sure]), name
-        assert torch.equal((got == float("inf"))[sure], (want == float("inf"))[sure]), name
-        assert torch.equal((got == float("-inf"))[sure], (want == float("-inf"))[sure]), name
-        plain = want.abs() < 1e30
-        assert bool(plain.any()) or name == "dw"
-        if bool(plain.any()):
-            assert _rel(got[plain], want[plain]) < 5e-6, name
+    for run in L.ways():
+        for name, got, want in zip(("y", "dx", "dw"), run(), L.exact()):
+            if name == "dw":                                             # (3e38 times dy overflows in one order and not in another)
+                got, want = got[:, :-1], want[:, :-1]
+            sure = (want.abs() < 1e38) | ~torch.isfinite(want)           # (those next to the largest number may go either way)
+            assert torch.equal(torch.isnan(got)[sure], torch.isnan(want)[sure]), name
+            assert torch.equal((got == float("inf"))[sure], (want == float("inf"))[sure]), name
+            assert torch.equal((got == float("-inf"))[sure], (want == float("-inf"))[sure]), name
+            plain = want.abs() < 1e30
+            assert bool(plain.any()) or name == "dw"
+            if bool(plain.any()):
+                assert _rel(got[plain], want[plain]) < 5e-6, name
 
 
 @pytest.mark.parametrize("shape", LAYERS[:-1], ids=IDS[:-1])
@@ -55,11 +56,12 @@ def test_conv_with_a_weight_that_is_not_finite(shape):
     L = ConvLayer(*shape)
     L.w[(1, 2, *[0] * len(n))], L.w[(c_out - 1, 0, *[k - 1] * len(n))] = float("inf"), float("nan")
     L.w[(c_out // 2, 1, *[k // 2] * len(n))] = float("-inf")
-    for name, got, want in zip(("y", "dx"), L.run(), L.exact()):
-        assert torch.equal(torch.isnan(got), torch.isnan(want)), name
-        assert torch.equal(got == float("inf"), want == float("inf")) and torch.equal(got == float("-inf"), want == float("-inf")), name
-        plain = torch.isfinite(want)
-        assert bool(plain.any()) and _rel(got[plain], want[plain]) < 5e-6, name
+    for run in L.ways():
+        for name, got, want in zip(("y", "dx"), run(), L.exact()):
+            assert torch.equal(torch.isnan(got), torch.isnan(want)), name
+            assert torch.equal(got == float("inf"), want == float("inf")) and torch.equal(got == float("-inf"), want == float("-inf")), name
+            plain = torch.isfinite(want)
+            assert bool(plain.any()) and _rel(got[plain], want[plain]) < 5e-6, name
 
 
 # few channels: several cells to a position (two, three; rows that end within one; strides; classes that are launches of
@@ -80,10 +82,11 @@ def test_layers_of_few_channels(shape, dilation):
     require_gpu()
     L = ConvLayer(*shape, dil=dilation)
     assert split_forms(L.plan) == FEW_FORMS[dilation][FEW.index(shape)]
-    L.y.fill_(7.0), L.dx.fill_(5.0)
-    for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
-        assert _rel(got, want) < 5e-6, name
-        assert float((got.double() - want).abs().max() / want.abs().max()) < 1e-5, name
+    for run in L.ways():
+        L.y.fill_(7.0), L.dx.fill_(5.0)
+        for name, got, want in zip(("y", "dx", "dw"), run(), L.exact()):
+            assert _rel(got, want) < 5e-6, name
+            assert float((got.double() - want).abs().max() / want.abs().max()) < 1e-5, name
 
 
 @pytest.mark.parametrize("shape", FEW, ids=FEW_IDS)
@@ -127,8 +130,9 @@ def test_conv_of_very_small_numbers(shape, small):
     require_gpu()
     L = ConvLayer(*shape)
     getattr(L, small).mul_(1e-36)
-    for name, got, want in zip(("y", "dx", "dw"), L.run(), L.exact()):
-        assert _rel(got, want) < 5e-6, name
+    for run in L.ways():
+        for name, got, want in zip(("y", "dx", "dw"), run(), L.exact()):
+            assert _rel(got, want) < 5e-6, name
 
 
 @pytest.mark.parametrize("small", ["x", "W", "dy"])
@@ -142,10 +146,12 @@ def test_affine_of_very_small_numbers(n_b, n_fi, n_fo, small):
     x, W, dy = t["x"], t["W"], t["dy"]
     y, dx, dW = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(W)
     plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, 1, 1)
-    dd.distdl_affine_fwd(plan, [x], [W], None, [y])
-    dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], None)
-    for got, want in ((y, x.double() @ W.double().t()), (dx, dy.double() @ W.double()), (dW, dy.double().t() @ x.double())):
-        assert _rel(got, want) < 1e-6
+    for route in (-1, 0):
+        dd.distdl_debug_affine_route(plan, route)
+        dd.distdl_affine_fwd(plan, [x], [W], None, [y])
+        dd.distdl_affine_bwd(plan, [x], [W], [dy], [dx], [dW], None)
+        for got, want in ((y, x.double() @ W.double().t()), (dx, dy.double() @ W.double()), (dW, dy.double().t() @ x.double())):
+            assert _rel(got, want) < 1e-6
 
 
 @pytest.mark.parametrize("shape", [(1, 64, 64, (18, 18, 18), 7, 1), (1, 36, 40, (60, 61), 15, 1)], ids=["7^3", "15^2"])
