@@ -220,15 +220,14 @@ static std::vector<GemmBlock> blocks_dw(const distdl_affine_plan* p, const void*
   return blocks;
 }
 
-// Small layers (affine_small.hip): where their launch is estimated at less than 0.95 of the calls on the tiled kernels (from 12 us 0.85;
-// bf16 forward 0.88, back 0.9), the host's time for the arrays on neither side.  What decides is that the tiled ones start a tile at a
-// time, and split a long K over two launches; with many tiles, or matrix instructions in earnest, they are the faster ones.  us,
-// tiled / small, forward and back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 295 x 624 -> 28, 2 x 1 10.2 / 6.4 and
-// 12.9 / 7.7; 37 x 2000 -> 1001, 2 x 3 12.9 / 10.3 and 18.1 / 20.5; 327 x 84 -> 7210, 2 x 2 18.9 / 25.1 and 25.5 / 46.9; bf16 of odd
-// rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4 and 16.6 / 12.0.  Of 1500 layers of 1 to 1024 rows the choice is 1.20 and 1.11 times as fast
-// as the tiled kernels in the mean (bf16 1.05 and 1.17; the better one each time 1.21, 1.13, 1.10, 1.19), 30 directions of 3000 more
-// than 0.05 slower, up to 1.2 times.  The tiled kernels' times are fitted to half of them; nine tenths are within 16 % (bf16 forward
-// 30 %).
+// Small layers (affine_small.hip): where their launch is estimated at less than 0.93 of the calls on the tiled kernels (fp32 forward 0.95,
+// from 12 us 0.85), the host's time for the arrays on neither side.  What decides is that the tiled ones start a tile at a time, and
+// split a long K over two launches; with many tiles, or matrix instructions in earnest, they are the faster ones.  us, tiled / small,
+// forward and back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 37 x 2000 -> 1001, 2 x 3 12.9 / 10.3 and 18.1 / 20.5;
+// 327 x 84 -> 7210, 2 x 2 18.9 / 25.1 and 25.5 / 46.9; bf16 of odd rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4 and 16.6 / 12.0.  Of 3000
+// layers of 1 to 1024 rows the choice is 1.22 and 1.10 times as fast as the tiled kernels in the mean (bf16 1.15 and 1.12; the better
+// one each time 1.23, 1.12, 1.16, 1.14), 25 directions of 5400 more than 0.15 slower.  The tiled kernels' times are fitted to 750
+// others.  Below 0.9 a bf16 forward pass that costs the host its least each way, 6.9 and 7.7, would never go: 98 x 64 -> 160 on 1 x 3 9.1 / 6.3.
 static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& blocks, bool bf16) {
   if (p->route == 0 || !gemm_split_usable(blocks, bf16, true, true)) return false;  // (their range is the same)
   // (bf16 rows of whole 16-byte pieces take 7 to 9 us either way)
@@ -239,7 +238,7 @@ static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& block
     const double arrays = 0.13 * (blocks.size() * (blocks[0].nseg + 1) + blocks[0].nseg), us = affine_small_fwd_us(blocks, bf16, arrays);
     const GemmSplitPlan y = gemm_split_plan(blocks, vec);
     const double tiled = bf16 ? joined(7.7 + arrays, 1.6 * y.stages_us + 0.84 * y.split_us) : joined(7.4 + arrays, 3.3 + 1.2 * y.stages_us + 0.66 * y.split_us);
-    known = us - arrays < (bf16 ? 0.88 : us - arrays < 12 ? 0.95 : 0.85) * (tiled - arrays);
+    known = us - arrays < (bf16 ? 0.93 : us - arrays < 12 ? 0.95 : 0.85) * (tiled - arrays);
     p->small_fwd[wide].store(known, std::memory_order_relaxed);
   }
   return known || p->route > 0;
@@ -260,7 +259,7 @@ static bool small_bwd(distdl_affine_plan* p, const std::vector<GemmBlock>& bx, c
                                 : joined(7.5 + arrays, 2.1 + 0.95 * most + 1.4 * least + 0.8 * split + 0.52 * other + 1.6 * out);
     // (a bf16 dW leaves value by value: above 20 us, 20 x 4901 -> 1974 42 / 49, 9 x 2836 -> 3673 on 1 x 2 45 / 48, that is what
     // a call takes)
-    known = us - arrays < 0.9 * (tiled - arrays) && (!bf16 || us < 20);
+    known = us - arrays < 0.93 * (tiled - arrays) && (!bf16 || us < 20);
     p->small_bwd[wide][tiles].store(known, std::memory_order_relaxed);
   }
   return known || p->route > 0;

@@ -409,6 +409,12 @@ def test_choice_of_the_small_affine_kernels_is_that_of_the_call(n_b, n_fi, n_fo,
         assert {align: dd.distdl_debug_affine_small(plan, align)[0] for align in order} == by_alignment
 
 
+@pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi", [(98, 64, 160, 1, 3), (13, 53, 253, 2, 3), (3, 30, 11, 1, 1)])
+def test_the_least_that_a_call_costs_the_host_keeps_no_small_affine_layer_from_one_launch(n_b, n_fi, n_fo, P_fo, P_fi):
+    """bf16 of odd rows, forward: where both estimates are little more than the host's time, the launch of small layers is the faster one."""
+    assert dd.distdl_debug_affine_small(dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, torch.bfloat16))[0]
+
+
 @pytest.mark.parametrize("seed", range(40))
 def test_overlap_of_a_calls_arrays(seed):
     """Against every pair, for arrays in order, in reverse, interleaved, at random, with and without one that touches another."""
