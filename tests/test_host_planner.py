@@ -397,6 +397,16 @@ def test_choice_of_the_fused_kernels_is_that_of_the_call():
     assert {aligned: dd.distdl_debug_conv_fused(second, aligned) for aligned in (2, 1)} == answers
 
 
+@pytest.mark.parametrize("n_b,c_in,c_out,n,P,k,p,dil,dtype", [
+    (13, 5, 1, (7, 9, 6), (1, 3, 2), 3, 0, 2, torch.float32), (10, 16, 36, (14, 12, 15), (2, 3, 2), 2, 0, 1, torch.float32),
+    (4, 4, 4, (156, 120), (1, 2), 2, 1, 1, torch.bfloat16), (10, 8, 4, (7710,), (2,), 5, 2, 2, torch.bfloat16)])
+def test_no_margin_leaves_an_adjoint_to_launches_that_take_half_as_long_again(n_b, c_in, c_out, n, P, k, p, dil, dtype):
+    """Measured at 30.8 us apart and 17.1 together, 48.5 / 32.6, 26.3 / 16.5, 27.1 / 18.2."""
+    D = len(n)
+    plan = dd.distdl_plan_create(D, n_b, c_in, c_out, n, P, (k,) * D, (1,) * D, (p,) * D, (dil,) * D, dtype)
+    assert dd.distdl_debug_conv_fused(plan)[1]
+
+
 @pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi,by_alignment", [
     (35, 1172, 1743, 1, 2, {2: False, 4: True, 16: True}),   # rows of whole words, none of whole 16-byte pieces
     (115, 552, 1485, 1, 3, {2: False, 4: True, 16: False}),  # whole pieces: the bf16 tiles
