@@ -19,14 +19,12 @@
 //     (tap of the other dimensions, place in the run), each run in octets of its own, what lies behind its end made zero.  Data
 //     gradient, or taps that are dilated: a run is the channels of one tap.  Neighbouring lanes load neighbouring octets, 16 bytes
 //     at a time whatever the alignment (bf16: the five words that hold them), where every element was a load that touched a line
-//     for each row.  us, element by element / by runs: forward of 3 -> 32, 7 x 7, stride 2, 8 x 224 x 224 32.7 / 27.6; 43 -> 1,
-//     5^3, 5 x 22 x 20 x 34 325 / 193; bf16 61 -> 2, 5^3, stride 2, 4 x 64 x 89 x 63 1705 / 602, 9 -> 2, 7 x 7, 2 x 252 x 325
-//     63 / 29; back with 29 channels of dy, 5^3, 2 x 31 x 29 x 35 741 / 524; bf16 22 channels, 5 x 5, 9 x 73 x 93 96 / 63.  Not
-//     for runs of less than 8, nor where their ends make more than 1.3 times the stages (2 -> 24, 5^3 67 / 81; 3 -> 22, 3 x 3,
-//     dilated 62 / 84), nor for less than half a stage (1 -> 45, 5 taps 27 / 30), or a whole one back (30 channels of dy, one tap,
-//     bf16 91 / 101).  bf16 quads are 8 bytes: runs of 16 and more, of whole quads, go by octets too, by quads / by octets
-//     forward of 60 -> 8, 5^3, 4 x 39 x 49 x 30 578 / 402, back with 60 channels, 5 x 5, 4 x 425 x 661 650 / 514, but 4 -> 44, 3^3,
-//     72 x 85 x 77, whose runs of 12 end in half an octet, 21 / 24.
+//     for each row.  us of the kernel, element by element / by runs: forward 3 -> 32, 7 x 7, stride 2, 8 x 224 x 224 25.5 / 23.5;
+//     43 -> 1, 5^3, 5 x 22 x 20 x 34 499 / 284; bf16 9 -> 2, 7 x 7, 2 x 252 x 325 54 / 23; back with 29 channels, 5^3, 2 x 31 x 29 x
+//     35 437 / 247.  Not for runs of less than 8, nor where their ends make more than 1.3 times the stages (2 -> 24, 5^3 67 / 81),
+//     nor for less than half a stage (1 -> 45, 5 taps 27 / 30), or a whole one back (30 channels, one tap, bf16 91 / 101).  bf16 quads
+//     are 8 bytes: runs of 16 and more, of whole quads, go by octets too (60 -> 8, 5^3, 4 x 39 x 49 x 30 499 / 362), but not 4 -> 44,
+//     3^3, 72 x 85 x 77, whose runs of 12 end in half an octet, 21 / 24.
 //     In those a lane per row, and the offset of a k, the same for all lanes, goes into the scalar offset of the load.
 //   wgrad_any_kernel: rows are k, columns output channels, the sum runs over output positions; the offset that all
 //     lanes share is that of the position.  Every (worker, chunk of positions) writes a partial, which also holds the

@@ -13,9 +13,11 @@
 // 16 x 16 tiles, 4 k an instruction: a wave's lane holds one position (one row of x^) and 4 consecutive k, fetched from memory
 // straight into registers; there is no staging to wait for but that of the weights, which are taken in the caller's order and
 // kept in LDS by output channel.  fp32 tensors are multiplied and summed in fp64: twice the matrix time, which is a small part
-// here (a pass takes 4 to 8 % longer than with fp32 matrix instructions in chains of 16 products), and every sum is exact but
-// for its last rounding, 2.5e-8, where the split products of the general kernels leave 4e-8 to 1e-7, and 16 x 16 tiles of fp32
-// 2e-7.  bf16 tensors are widened and multiplied in fp32.
+// here (a pass takes 4 to 8 % longer than with fp32 matrix instructions in chains of 16 products).  y, dx, and dw and db where one
+// workgroup sums over all positions, are rounded once, 2.5e-8, where the split products of the general kernels leave 4e-8 to 1e-7,
+// and 16 x 16 tiles of fp32 2e-7; dw and db of chunks are rounded for each chunk, and those parts are added in fp32, as the general
+// kernels' are.  A sum goes over taps and channels in their order, whichever worker a cell lies with: the order is fixed, but
+// in dx it is not that of the workers.  bf16 tensors are widened and multiplied in fp32.
 //
 // What bounds it is the number of instructions that one wave issues one after the other, at 4 clocks each: of 8900 clocks of a
 // workgroup for 1 -> 1 channels, 3 taps, 64 cells on four workers, the loads take a third.  So geometry and taps come from tables
@@ -133,9 +135,9 @@ __device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t rs, int i, bool ok
 }
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ float rcp(int v) { return __builtin_amdgcn_rcpf((float)v); }
-// n / d for n < 2^20, through the reciprocal: (n + 1/2) / d is at least 1 / 2d off any integer, and the product is off by less than
+// n / d for n < 2^20 (and no further), through the reciprocal: (n + 1/2) / d is at least 1 / 2d off any integer, and the product is off by less than
 // 2^-22 of itself
-__device__ __forceinline__ int div_by(int n, float rcp_d) { return (int)fmaf((float)n, rcp_d, 0.5f * rcp_d); }
+__device__ __forceinline__ int div_below20(int n, float rcp_d) { return (int)fmaf((float)n, rcp_d, 0.5f * rcp_d); }
 
 // The sums of 16 x 16 products, 4 k at a time.  Register e of lane (kk, i): row kk + 4 e (fp64) or 4 kk + e, column i.
 template <bool BF16>
@@ -156,8 +158,7 @@ constexpr int kZeros = 2048;
 __device__ __attribute__((aligned(16))) float fused_zeros[kZeros];
 
 template <bool BF16, int MODE, bool VEC, int NT>
-__device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers, void* const* in_bufs, void* const* out_bufs,
-                                           const FusedArgs& a, int b, char* smem) {
+__device__ __forceinline__ void fused_corr(void* const* in_bufs, void* const* out_bufs, const FusedArgs& a, int b, char* smem) {
   typedef std::conditional_t<BF16, uint16_t, float> T;
   const int group = b % a.groups;
   int r = b / a.groups;
@@ -190,7 +191,7 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
   auto run_of = [&](int cb) { return MODE == 0 ? cb * a.taps : real * a.taps; };
   auto all_of = [&](int cb) { return MODE == 0 ? real * cb * a.taps : cb * real * a.taps; };
   auto stage_one = [&](int c0, int run, float rrun, int all, int idx) {
-    const int q = div_by(idx, rrun), e = idx - q * run;
+    const int q = div_below20(idx, rrun), e = idx - q * run;
     const int from = MODE == 0 ? ((ch0 + q) * a.ci + c0) * a.taps + e : ((c0 + q) * a.ci + ch0) * a.taps + e;
     return load1<BF16>(rw, from, idx < all);
   };
@@ -229,7 +230,7 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
       for (int u = 0; u < WU; ++u) {
         const int idx = at + 256 * u;
         if (uniform(idx) >= all) break;
-        const int q = div_by(idx, rrun), e = idx - q * run, c = div_by(e, rt), t = e - c * a.taps;
+        const int q = div_below20(idx, rrun), e = idx - q * run, c = div_below20(e, rt), t = e - c * a.taps;
         const int m = strided ? map[min(t, a.taps - 1)] : t;
         if (idx < all && m >= 0) {
           wl[(MODE == 0 ? q : c) * a.pitch + m * cb + (MODE == 0 ? c : q)] = wv[u];
@@ -242,7 +243,7 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
     if (tail > 0) {
       const float rtail = rcp(tail);
       for (int e = tid; e < real * tail; e += 256) {
-        const int row = div_by(e, rtail);
+        const int row = div_below20(e, rtail);
         wl[row * a.pitch + K + e - row * tail] = 0.f;
       }
     }
@@ -260,7 +261,7 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
     {
       const FusedDim g0 = rec->d[0], g1 = rec->d[1], g2 = rec->d[2];
       const int q = min(pos, total - 1);  // (a lane beyond the last does the last's work and keeps it to itself)
-      const int q012 = div_by(q, g2.rq), q01 = div_by(q012, g1.rq), n = div_by(q01, g0.rq);
+      const int q012 = div_below20(q, g2.rq), q01 = div_below20(q012, g1.rq), n = div_below20(q01, g0.rq);
       const int q2 = q - q012 * g2.nq, q1 = q012 - q01 * g1.nq, q0 = q01 - n * g0.nq;
       const int w0 = g0.out0 + q0 * g0.ostep, w1 = g1.out0 + q1 * g1.ostep, w2 = g2.out0 + q2 * g2.ostep;
       auto in = [](int v, int lo, int len) { return (uint32_t)(v - lo) < (uint32_t)len; };
@@ -270,7 +271,7 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
       const int p0 = g0.in0 + q0 * g0.step, p1 = g1.in0 + q1 * g1.step, p2 = g2.in0 + q2 * g2.step;
       if (it > 0) __syncthreads();
       // (the last step may go beyond the taps)
-      const int entries = a.nch > 1 ? ntaps + 16 : ntaps + div_by((-(ntaps * a.cb) & 15) + a.cb - 1, rcp(a.cb));
+      const int entries = a.nch > 1 ? ntaps + 16 : ntaps + div_below20((-(ntaps * a.cb) & 15) + a.cb - 1, rcp(a.cb));
 #pragma unroll 2
       for (int t = kg * 4 + kq; t < entries; t += 4 * a.wk) {
         const int4 d = steps_of[min(t, a.most_taps - 1)];
@@ -300,13 +301,13 @@ __device__ __forceinline__ void fused_corr(const WorkerDev* __restrict__ workers
       auto load = [&](int st) -> f32x4 {
         const int qd = st * 4 + kq;
         if constexpr (VEC) {
-          const int t = div_by(qd, rcb);
+          const int t = div_below20(qd, rcb);
           return load4<BF16>(cells[t * 16 + i], c0 + (qd - t * (cb / 4)) * 4);
         } else {
           f32x4 v;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const int k = qd * 4 + j, t = div_by(k, rcb);
+            const int k = qd * 4 + j, t = div_below20(k, rcb);
             v[j] = load1<BF16>(cells[t * 16 + i], c0 + k - t * cb);
           }
           return v;
@@ -426,10 +427,10 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
   const float rci = rcp(a.ci), rk2 = rcp(a.k[2]), rk1 = rcp(a.k[1]);
 #pragma unroll
   for (int j = 0; j < NR; ++j) {
-    const int k = min(mt * 64 + (VEC ? 4 * i : 16 * j + i), rows - 1), tap = div_by(k, rci), t01 = div_by(tap, rk2);
+    const int k = min(mt * 64 + (VEC ? 4 * i : 16 * j + i), rows - 1), tap = div_below20(k, rci), t01 = div_below20(tap, rk2);
     cc[j] = VEC ? (k - tap * a.ci) / 4 * 4 : k - tap * a.ci;
     t2[j] = tap - t01 * a.k[2];
-    t0[j] = div_by(t01, rk1);
+    t0[j] = div_below20(t01, rk1);
     t1[j] = t01 - t0[j] * a.k[1];
   }
   int col[NT];
@@ -470,7 +471,7 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
     auto fetch = [&](f32x4 (&x)[U], float (&y)[U][NT], int at, int s) {
       if (s == 0) {
         const int q = min(at + lane, npos - 1);
-        const int q012 = div_by(q, rq2), q01 = div_by(q012, rq1), n = div_by(q01, rq0);
+        const int q012 = div_below20(q, rq2), q01 = div_below20(q012, rq1), n = div_below20(q01, rq0);
         const int o2 = q - q012 * wd.out[2], o1 = q012 - q01 * wd.out[1], o0 = q01 - n * wd.out[0];
         cell = n * sn + o0 * a.s[0] * s0 + o1 * a.s[1] * s1 + o2 * a.s[2] * a.ci;
       }
@@ -539,7 +540,7 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
     const float s = (float)((red[e] + red[64 * NB + e]) + red[2 * 64 * NB + e] + red[3 * 64 * NB + e]);
     if (k >= rows || ch >= a.co) continue;
     if (whole) {
-      const int tap = div_by(k, rci);
+      const int tap = div_below20(k, rci);
       st((T*)a.dw, ((size_t)ch * a.ci + (k - tap * a.ci)) * a.taps + tap, s);
     } else {
       slot[(size_t)k * a.co + ch] = s;
@@ -553,10 +554,10 @@ __device__ __forceinline__ void fused_wgrad(const WorkerDev* __restrict__ worker
 }
 
 template <bool BF16, bool VEC, int NT>
-__global__ __launch_bounds__(256, NT == 4 ? 2 : 3) void fused_fwd_kernel(const WorkerDev* __restrict__ workers, void* const* x_bufs, void* const* y_bufs, FusedArgs a) {
+__global__ __launch_bounds__(256, NT == 4 ? 2 : 3) void fused_fwd_kernel(void* const* x_bufs, void* const* y_bufs, FusedArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int b = (int)blockIdx.x;
-  if (b < a.blocks) return fused_corr<BF16, 0, VEC, NT>(workers, x_bufs, y_bufs, a, b, smem);
+  if (b < a.blocks) return fused_corr<BF16, 0, VEC, NT>(x_bufs, y_bufs, a, b, smem);
   if constexpr (BF16) {
     if (a.wide) halo_fwd_box<BF16x8>(a.hblocks, a.htasks, x_bufs, b - a.blocks);
     else halo_fwd_box<BF16x1>(a.hblocks, a.htasks, x_bufs, b - a.blocks);
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(256, NT == 4 ? 2 : 3) void fused_bwd_kernel(const W
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int b = (int)blockIdx.x;
   if (b < a.dw_blocks) fused_wgrad<BF16, VEC, 1>(workers, n_workers, x_bufs, dy_bufs, a, b, smem);
-  else fused_corr<BF16, 1, VEC, NT>(workers, dy_bufs, dx_bufs, a, b - a.dw_blocks, smem);
+  else fused_corr<BF16, 1, VEC, NT>(dy_bufs, dx_bufs, a, b - a.dw_blocks, smem);
 }
 
 // ---- host side ------------------------------------------------------------------
@@ -812,8 +813,8 @@ template <bool BF16, bool VEC, int NT>
 int launch_fwd(distdl_plan* p, const Shape& sh, int halo_blocks, hipStream_t st) {
   if (sh.lds > 64 * 1024)
     if (int rc = allow_large_lds<fused_fwd_kernel<BF16, VEC, NT>>()) return rc;
-  hipLaunchKernelGGL((fused_fwd_kernel<BF16, VEC, NT>), dim3((unsigned)(sh.a.blocks + halo_blocks)), dim3(256), sh.lds, st, p->d_workers, p->tab_x.dev,
-                     p->tab_y.dev, sh.a);
+  hipLaunchKernelGGL((fused_fwd_kernel<BF16, VEC, NT>), dim3((unsigned)(sh.a.blocks + halo_blocks)), dim3(256), sh.lds, st, p->tab_x.dev, p->tab_y.dev,
+                     sh.a);
   return DISTDL_OK;
 }
 template <bool BF16, bool VEC, int NT>
