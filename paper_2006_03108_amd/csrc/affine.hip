@@ -220,14 +220,16 @@ static std::vector<GemmBlock> blocks_dw(const distdl_affine_plan* p, const void*
   return blocks;
 }
 
-// Small layers (affine_small.hip): where their launch is estimated at less than 0.93 of the calls on the tiled kernels (fp32 forward 0.95,
-// from 12 us 0.85), the host's time for the arrays on neither side.  What decides is that the tiled ones start a tile at a time, and
-// split a long K over two launches; with many tiles, or matrix instructions in earnest, they are the faster ones.  us, tiled / small,
-// forward and back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 37 x 2000 -> 1001, 2 x 3 12.9 / 10.3 and 18.1 / 20.5;
-// 327 x 84 -> 7210, 2 x 2 18.9 / 25.1 and 25.5 / 46.9; bf16 of odd rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4 and 16.6 / 12.0.  Of 3000
-// layers of 1 to 1024 rows the choice is 1.22 and 1.10 times as fast as the tiled kernels in the mean (bf16 1.15 and 1.12; the better
-// one each time 1.23, 1.12, 1.16, 1.14), 25 directions of 5400 more than 0.15 slower.  The tiled kernels' times are fitted to 750
-// others.  Below 0.9 a bf16 forward pass that costs the host its least each way, 6.9 and 7.7, would never go: 98 x 64 -> 160 on 1 x 3 9.1 / 6.3.
+// Small layers (affine_small.hip): where their launch is estimated at less than 0.97 of the calls on the tiled kernels (back 0.96, bf16
+// 0.93), the host's time for the arrays on neither side.  What decides is that the tiled ones start a tile at a time, and split a long K
+// over two launches; with many tiles, or matrix instructions in earnest, they are the faster ones.  us, tiled / small, forward and
+// back: 256 x 400 -> 120 on 2 x 2 11.9 / 7.8 and 11.6 / 9.4; 37 x 2000 -> 1001, 2 x 3 12.9 / 10.3 and 18.1 / 20.5; 138 x 1488 -> 2512,
+// 3 x 3 20.9 / 29.1 forward; 327 x 84 -> 7210, 2 x 2 18.9 / 25.1 and 25.5 / 46.9; bf16 of odd rows 351 x 314 -> 498, 2 x 1 13.7 / 6.4
+// and 16.6 / 12.0.  Of 3000 layers of 1 to 1024 rows the choice is 1.22 and 1.11 times as fast as the tiled kernels in the mean (bf16
+// 1.15 and 1.12; the better one each time 1.23, 1.12, 1.16, 1.14), 10 directions of 5400 more than 0.15 slower, all of them back.  The
+// tiled kernels' times are fitted to the same layers; four fifths are within 20 % (rows that are not read in 16-byte pieces take longer).
+// Margins below 0.9 would keep every layer that costs the host its least either way on the tiled kernels: bf16 98 x 64 -> 160 on 1 x 3
+// 9.1 / 6.3 forward.
 static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& blocks, bool bf16) {
   if (p->route == 0 || !gemm_split_usable(blocks, bf16, true, true)) return false;  // (their range is the same)
   // (bf16 rows of whole 16-byte pieces take 7 to 9 us either way)
@@ -237,8 +239,9 @@ static bool small_fwd(distdl_affine_plan* p, const std::vector<GemmBlock>& block
   if (known < 0) {
     const double arrays = 0.13 * (blocks.size() * (blocks[0].nseg + 1) + blocks[0].nseg), us = affine_small_fwd_us(blocks, bf16, arrays);
     const GemmSplitPlan y = gemm_split_plan(blocks, vec);
-    const double tiled = bf16 ? joined(7.7 + arrays, 1.6 * y.stages_us + 0.84 * y.split_us) : joined(7.4 + arrays, 3.3 + 1.2 * y.stages_us + 0.66 * y.split_us);
-    known = us - arrays < (bf16 ? 0.93 : us - arrays < 12 ? 0.95 : 0.85) * (tiled - arrays);
+    const double tiled = bf16 ? joined(6.2 + arrays, 1.5 * y.stages_us + 0.83 * y.split_us)
+                              : joined(5.7 + arrays, 3.5 + (vec ? 1.15 : 1.38) * y.stages_us + 0.5 * y.split_us);
+    known = us - arrays < 0.97 * (tiled - arrays);
     p->small_fwd[wide].store(known, std::memory_order_relaxed);
   }
   return known || p->route > 0;
@@ -256,10 +259,10 @@ static bool small_bwd(distdl_affine_plan* p, const std::vector<GemmBlock>& bx, c
                  other = std::min(x.split_us, w.split_us), out = 1e-6 * ((double)p->n_b * p->n_fi + (double)p->n_fi * p->n_fo);
     const double tiled = tiles  ? joined(13.0 + arrays, 6.3 + 1.1 * w.stages_us)  // (two launches and more)
                          : bf16 ? joined(7.6 + arrays, 0.6 * most + 1.7 * least + 1.3 * split + 0.3 * other + 1.1 * out)
-                                : joined(7.5 + arrays, 2.1 + 0.95 * most + 1.4 * least + 0.8 * split + 0.52 * other + 1.6 * out);
+                                : joined(6.4 + arrays, 2.1 + (vec ? 0.95 : 1.2) * (most + least) + 0.65 * split + 0.18 * other + 1.4 * out);
     // (a bf16 dW leaves value by value: above 20 us, 20 x 4901 -> 1974 42 / 49, 9 x 2836 -> 3673 on 1 x 2 45 / 48, that is what
     // a call takes)
-    known = us - arrays < 0.93 * (tiled - arrays) && (!bf16 || us < 20);
+    known = us - arrays < (bf16 ? 0.93 : 0.96) * (tiled - arrays) && (!bf16 || us < 20);
     p->small_bwd[wide][tiles].store(known, std::memory_order_relaxed);
   }
   return known || p->route > 0;

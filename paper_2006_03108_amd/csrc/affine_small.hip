@@ -463,10 +463,10 @@ static SmallShape best_dw(const GemmBlock* d, const std::vector<GemmBlock>& b, b
   return shape_us(shared, bf16) < shape_us(own, bf16) ? shared : own;
 }
 
-// Estimated times of the calls, fitted to 750 layers of 1 to 1024 rows and 10 to 8192 features; nine tenths are within 14 %.  A product:
-// a start, and a wave's chunks with their loads and matrix instructions, which take longer with two workgroups on a compute unit
-// (of four M-tiles forward, whose operands take 92 KB, there is one); what is written, value by value in bf16.  With it, by a
-// fourth power: what the host takes.
+// Estimated times of the calls, fitted to 3000 layers of 1 to 1024 rows and 10 to 8192 features; four fifths are within 10 % (bf16
+// 13 %).  A product: a start, and a wave's chunks with their loads and matrix instructions, which take longer with two workgroups on
+// a compute unit; what is written, value by value in bf16.  With it, by a fourth power: what the host takes.  Forward a second
+// workgroup on a compute unit is all but a second round (0.75, bf16 0.83; of four M-tiles, whose operands take 92 KB, it is one).
 static double shared_cu(const SmallShape& s, double more) { return 1 + more * std::min(s.wgs / 256.0, 2.0); }
 static double written(const std::vector<GemmBlock>& blocks) {  // 10^6 elements
   double n = 0;
@@ -475,18 +475,24 @@ static double written(const std::vector<GemmBlock>& blocks) {  // 10^6 elements
 }
 double affine_small_fwd_us(const std::vector<GemmBlock>& blocks, bool bf16, double arrays) {
   const SmallShape s = best_fwd(nullptr, blocks, bf16);
-  const double rounds = std::ceil(s.wgs / (s.mt == 4 ? 256.0 : 512.0)), chunk = bf16 ? 0.28 + 0.36 * s.mt * s.nt : 0.23 + 0.65 * s.mt * s.nt;
-  const double us = rounds * (1.1 + s.chunks * chunk * (s.mt == 4 ? 1 : shared_cu(s, bf16 ? 0.29 : 0.2))) + (bf16 ? 2.1 : 2.6) * written(blocks);
-  return joined(6.9 + arrays, us * (bf16 && !affine_small_words(blocks) ? 1.7 : 1.0));  // (rows of odd bf16 come value by value)
+  const double rounds = std::ceil(s.wgs / 256.0), chunks = s.chunks * (1 + (s.mt == 4 ? 1.0 : bf16 ? 0.83 : 0.75) * (rounds - 1));
+  const double us = bf16 ? 0.25 * rounds + chunks * (0.24 + 0.46 * s.mt * s.nt) + 0.22 * written(blocks)
+                         : 0.7 * rounds + chunks * (0.21 + 0.7 * s.mt * s.nt) + 0.7 * written(blocks);
+  return joined(5.7 + arrays, us * (bf16 && !affine_small_words(blocks) ? 1.75 : 1.0));  // (rows of odd bf16 come value by value)
 }
 double affine_small_bwd_us(const std::vector<GemmBlock>& bx, const std::vector<GemmBlock>& bw, bool bf16, double arrays) {
   const SmallShape x = best_dx(nullptr, bx, bf16), w = best_dw(nullptr, bw, bf16);
-  const double odd = bf16 && !(affine_small_words(bx) && affine_small_words(bw)) ? 1.4 : 1.0, dw = written(bw), out = written(bx) + dw;
-  const double tx = odd * (bf16 ? 1.0 + x.chunks * (0.46 + 0.22 * x.mt * x.nt) * shared_cu(x, 0.48) : 2.0 + x.chunks * (0.1 + 0.62 * x.mt * x.nt) * shared_cu(x, 0.66));
-  const double tw = odd * (bf16 ? 0.5 + w.chunks * (0.1 + 0.4 * w.mt * w.nt) : 0.5 + w.chunks * (1.6 + 0.43 * w.mt * w.nt) * shared_cu(w, 0.72));
-  const double store = bf16 ? 1.7 * out + 0.36 * dw / std::min(1.0, std::max(0.05, w.wgs / 256.0)) : 0.15 * out;
-  const double longest = std::max(tx, tw), all = tx * x.wgs / 512.0 + tw * w.wgs / 512.0;
-  return joined(bf16 ? 7.7 + arrays : 7.4 + arrays, std::max(longest, all) + (bf16 ? 0.64 : 0.22) * std::min(longest, all) + store);
+  auto both = [&](double tx, double tw, double least) {
+    const double longest = std::max(tx, tw), all = tx * x.wgs / 512.0 + tw * w.wgs / 512.0;
+    return std::max(longest, all) + least * std::min(longest, all);
+  };
+  if (!bf16) {
+    const double us = both(2.7 + 0.64 * x.chunks * x.mt * x.nt * shared_cu(x, 0.5), 0.66 * w.chunks * (1 + w.mt * w.nt) * shared_cu(w, 0.5), 0.32);
+    return joined(6.5 + arrays, us + 1.2 * (std::ceil(std::max(x.wgs + w.wgs, 1) / 512.0) - 1));
+  }
+  const double odd = affine_small_words(bx) && affine_small_words(bw) ? 1.0 : 1.4, dw = written(bw);
+  const double store = 1.7 * (written(bx) + dw) + 0.36 * dw / std::min(1.0, std::max(0.05, w.wgs / 256.0));
+  return joined(7.7 + arrays, both(odd * (1.0 + x.chunks * (0.46 + 0.22 * x.mt * x.nt) * shared_cu(x, 0.48)), odd * (0.5 + w.chunks * (0.1 + 0.4 * w.mt * w.nt)), 0.64) + store);
 }
 
 template <bool BF16, bool A_KC, bool B_KC, int MT, int NT, bool SPLIT>

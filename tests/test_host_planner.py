@@ -408,15 +408,21 @@ def test_no_margin_leaves_an_adjoint_to_launches_that_take_half_as_long_again(n_
 
 
 @pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi,by_alignment", [
-    (35, 1172, 1743, 1, 2, {2: False, 4: True, 16: True}),   # rows of whole words, none of whole 16-byte pieces
+    (144, 2500, 1384, 3, 1, {2: False, 4: True, 16: True}),  # rows of whole words, none of whole 16-byte pieces
     (115, 552, 1485, 1, 3, {2: False, 4: True, 16: False}),  # whole pieces: the bf16 tiles
 ])
 def test_choice_of_the_small_affine_kernels_is_that_of_the_call(n_b, n_fi, n_fo, P_fo, P_fi, by_alignment):
     """bf16 rows that do not start on a word move value by value, which the forward estimate knows: a plan answers for either
-    whatever it was asked before."""
+    whatever it was asked before.  (Layers near the line, where the answers differ.)"""
     for order in (list(by_alignment), list(by_alignment)[::-1]):
         plan = dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, torch.bfloat16)
         assert {align: dd.distdl_debug_affine_small(plan, align)[0] for align in order} == by_alignment
+
+
+@pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi", [(38, 2656, 1776, 4, 3), (138, 1488, 2512, 3, 3), (30, 3248, 7040, 2, 2), (22, 1744, 6352, 2, 1)])
+def test_small_affine_layers_of_two_workgroups_a_compute_unit(n_b, n_fi, n_fo, P_fo, P_fi):
+    """256 to 512 workgroups forward are two rounds but for a quarter: tiled 20.9 us against 29.1 (138 x 1488 -> 2512), 29.9 / 38.8, 19.4 / 22.6."""
+    assert not dd.distdl_debug_affine_small(dd.distdl_affine_plan_create(n_b, n_fi, n_fo, P_fo, P_fi, torch.float32))[0]
 
 
 @pytest.mark.parametrize("n_b,n_fi,n_fo,P_fo,P_fi", [(98, 64, 160, 1, 3), (13, 53, 253, 2, 3), (3, 30, 11, 1, 1)])
