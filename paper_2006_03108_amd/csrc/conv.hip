@@ -374,26 +374,29 @@ static int wgrad_partials(const distdl_plan* p, Wgrad w, bool vec16) {  // per w
 }
 
 // Small layers: everything of a direction in one launch (conv_fused.hip) where that is estimated at less than 0.8 (0.75 from 20 us; back
-// 0.9) of the launches it replaces; theirs are H and its kernel, or both contractions, the reduction and H*, each estimated as above,
+// 0.95) of the launches it replaces; theirs are H and its kernel, or both contractions, the reduction and H*, each estimated as above,
 // and what the host takes for them; its time for the workers' arrays is on neither side.  Without a halo exchange there is one launch
-// less to save in the forward pass, which then goes that way only where it would take little more than a launch.  us, launches
-// apart / together, forward and back: 1 -> 1, 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 20 -> 4, 3^3, 4 x 13 x 12 x 17 on
+// less to save; the forward pass then goes that way only where it would take little more than a launch.  us, launches apart /
+// together, forward and back: 1 -> 1, 3 taps, 64 on four workers 11.7 / 6.8 and 18.0 / 8.6; 20 -> 4, 3^3, 4 x 13 x 12 x 17 on
 // 3 x 2 x 2 26.8 / 14.1 and 38.5 / 22.4; but 5 -> 32, 5^3, stride 2, bf16, 13 x 14 x 11 x 15 22 / 45 and 58 / 400.  Up to 100 us
 // forward and 40 us back, where the fp64 matrix instructions and the second reading of x weigh more than the launches (27 -> 11,
 // 3 x 3, 10 x 244 x 329 258 / 283; 24 -> 4, 3^3, bf16, 11 x 62 x 54 x 61 1026 / 2498).
 // Estimates are off by an eighth either way.  Of 4200 directions forward 2482 go together, 1.60 times as fast in the mean, 12 of them
-// more than 0.15 slower than apart; at 0.9 and 0.85 45, for 1.325 instead of 1.318 over all.  Back 2368 of 3900, 1.69 times, 13 more
-// than 0.15 slower; at 0.85 and 0.8 9, but 1.365 instead of 1.374 over all, and 81 left apart that take a fifth longer so, and up to 0.8 (5 -> 1,
+// more than 0.15 slower than apart; at 0.9 and 0.85 45, for 1.325 instead of 1.318 over all.  Back 2401 of 3900, 1.68 times, 9 more
+// than 0.15 slower; at 0.85 and 0.8 3, but 1.365 instead of 1.378 over all, and a hundred left apart that take a fifth longer so (5 -> 1,
 // 3^3, dilated, 13 x 7 x 9 x 6 on 1 x 3 x 2 30.8 / 17.1).
 static double arrays_us(const distdl_plan* p, bool backward) { return (backward ? 0.25 : 0.2) * p->n_workers; }  // the host's time for them, either way
-static double launches_us(const distdl_plan* p, bool backward) { return (backward ? 12.0 : 9.5) + arrays_us(p, backward); }  // and for the launches apart
+static bool has_boxes(const distdl_plan* p) { return !p->fwd1.blocks.empty() || !p->fwd16.blocks.empty(); }
+static double launches_us(const distdl_plan* p, bool backward) {  // and for the launches apart
+  return (!backward ? 9.5 : has_boxes(p) ? 12.0 : 9.0) + arrays_us(p, backward);
+}
 static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool aligned, bool w_aligned) {
   int8_t& known = p->fused_kernel[backward][vec][aligned][w_aligned];
   if (known >= 0) return known != 0;
   const double us = conv_fused_us(p, backward, vec);
-  const bool boxes = !p->fwd1.blocks.empty() || !p->fwd16.blocks.empty();
+  const bool boxes = has_boxes(p);
   double apart = launches_us(p, backward);
-  const double room = backward ? 0.9 : us < 20 ? 0.8 : 0.75, arrays = arrays_us(p, backward);
+  const double room = backward ? 0.95 : us < 20 ? 0.8 : 0.75, arrays = arrays_us(p, backward);
   if (us - arrays >= room * (apart - arrays) && std::isfinite(us) && (backward || boxes)) {
     const Corr k = choose_corr(p, backward, aligned, w_aligned);
     double corr = 0, wgrad = 0;
@@ -404,7 +407,7 @@ static bool choose_fused(const distdl_plan* p, bool backward, bool vec, bool ali
     // (a weight gradient on the split kernel or the bf16 planes is one of a layer that fills the chip)
     const Wgrad wk = backward ? choose_wgrad(p, vec) : Wgrad::kAny;
     if (backward && (wk == Wgrad::kAny || wk == Wgrad::k16)) wgrad = wgrad_us(p, wk);
-    const double device = backward ? 6.1 + 1.1 * corr + wgrad : 2.2 + 1.2 * corr;
+    const double device = backward ? (boxes ? 6.1 : 3.0) + 1.1 * corr + wgrad : 2.2 + 1.2 * corr;
     apart = corr <= 0 || (backward && wgrad <= 0) ? 0.0 : joined(apart, device);
   }
   known = us - arrays < room * (apart - arrays) && us < (backward ? 40 : 100);
