@@ -61,6 +61,15 @@ class Ranges {
 
   void sort() {
     auto before = [](const Range& a, const Range& b) { return a.lo < b.lo; };
+    if (all_.size() <= 32) {  // (without allocating: 12 arrays in any order 0.25 us, merged 0.35; 24 0.41 and 0.55)
+      for (size_t i = 1; i < all_.size(); ++i) {
+        const Range r = all_[i];
+        size_t j = i;
+        for (; j > 0 && r.lo < all_[j - 1].lo; --j) all_[j] = all_[j - 1];
+        all_[j] = r;
+      }
+      return;
+    }
     std::vector<uint32_t> ends;  // of the runs
     for (size_t i = 0, j; i < all_.size(); i = j) {
       j = i + 1;
