@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "affine_small.h"
+#include "buffer.h"
 #include "common.h"
 #include "gemm_mfma.h"
 #include "profile.h"
@@ -30,12 +31,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef const __attribute__((address_space(4))) GemmBlock* BlockPtr;  // (scalar loads: nothing writes the descriptors while a kernel runs)
 
-constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (operands are < 2 GiB)
 constexpr int kWaves = 8;
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
 // N neighbouring elements at byte offset `off`.  V4: bf16 elements in pairs of 4 bytes (fp32 buffer loads ask for no more alignment).
 template <bool BF16, bool V4, int N>
 __device__ __forceinline__ void load_n(float (&v)[N], __amdgpu_buffer_rsrc_t rs, uint32_t off) {

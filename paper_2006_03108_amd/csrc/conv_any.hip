@@ -37,6 +37,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "buffer.h"
 #include "common.h"
 #include "conv_any.h"
 #include "conv_mfma.h"
@@ -53,7 +54,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GiB)
 
 struct WgradAnyArgs {
   int32_t n_b, ci, co;
@@ -63,9 +63,6 @@ struct WgradAnyArgs {
   int64_t slot;
 };
 
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
 template <bool BF16>
 __device__ inline float load1(__amdgpu_buffer_rsrc_t rs, uint32_t vo, uint32_t so) {
   if constexpr (BF16) return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, vo, so, 0) << 16);

@@ -30,6 +30,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "buffer.h"
 #include "common.h"
 #include "conv_fused.h"
 #include "halo_box.h"
@@ -44,7 +45,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GB)
 
 // Tables of a plan and direction, made once on the host and copied to the device with its first pass.
 // A correlation over one worker and class of a stride: dimension by dimension
@@ -111,9 +111,6 @@ __device__ __forceinline__ f32x4 load4(uint64_t base, int i) {
   } else {
     return at_address<f32x4>(base + (int64_t)i * 4);
   }
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 // element i of a buffer; zero if !ok
 template <bool BF16>

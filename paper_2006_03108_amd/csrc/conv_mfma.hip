@@ -23,6 +23,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "buffer.h"
 #include "common.h"
 #include "conv_mfma.h"
 #include "lds_direct.h"
@@ -41,13 +42,8 @@ __host__ __device__ inline int64_t tiles_of(const PerWorker& g, const CorrArgs& 
 
 constexpr int kMaxPieces = 14;
 constexpr int kMaxBPieces = 8;  // weight pieces per thread held in registers (32 taps per plane)
-constexpr uint32_t kOob = 0x7ffffff0u;  // buffer offset that always fails the range check (buffers are < 2 GiB)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
 
 // Four consecutive channels as fp32 bit patterns: a 16-byte piece of an fp32 tensor, or an 8-byte piece of a
 // bf16 tensor widened on the way (bf16 tensors are multiplied in fp32 on the matrix cores).
@@ -145,12 +141,12 @@ __global__ __launch_bounds__(256, (PA <= 4 && MT == 2 && MODE == 0 && NT > 0) ? 
   const int si2 = a.kc, si1 = g.in_ext[2] * si2, si0 = g.in_ext[1] * si1;
   const uint32_t sin = (uint32_t)g.in_ext[0] * si0;
   const uint32_t so2 = a.nc, so1 = g.out_ext[2] * so2, so0 = g.out_ext[1] * so1, son = g.out_ext[0] * so0;
-  const __amdgpu_buffer_rsrc_t rin = make_rsrc(in_bufs[worker], (uint32_t)a.n_b * sin * ES);
-  const __amdgpu_buffer_rsrc_t rout = make_rsrc(out_bufs[worker], (uint32_t)a.n_b * son * ES);
+  const __amdgpu_buffer_rsrc_t rin = rsrc_of(in_bufs[worker], (uint32_t)a.n_b * sin * ES);
+  const __amdgpu_buffer_rsrc_t rout = rsrc_of(out_bufs[worker], (uint32_t)a.n_b * son * ES);
   const int ncc = (a.kc + CK - 1) / CK;
   const int nt0 = a.nt[0];
   const __amdgpu_buffer_rsrc_t rw =
-      make_rsrc(a.wt + (size_t)ntile * nt0 * ncc * nb_vec4 * 4, (uint32_t)(nt0 * ncc * nb_vec4) * 16u);
+      rsrc_of(a.wt + (size_t)ntile * nt0 * ncc * nb_vec4 * 4, (uint32_t)(nt0 * ncc * nb_vec4) * 16u);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, m = lane & 31;
 
@@ -873,8 +869,8 @@ __global__ __launch_bounds__(256, 2) void wgrad_taps_kernel(const WorkerDev* __r
 
   const uint32_t sx2 = a.ci, sx1 = wd.buf[2] * sx2, sx0 = wd.buf[1] * sx1, sxn = wd.buf[0] * sx0;
   const uint32_t sy2 = a.co, sy1 = wd.out[2] * sy2, sy0 = wd.out[1] * sy1, syn = wd.out[0] * sy0;
-  const __amdgpu_buffer_rsrc_t rx = make_rsrc(x_bufs[worker], (uint32_t)a.n_b * sxn * ES);
-  const __amdgpu_buffer_rsrc_t ry = make_rsrc(dy_bufs[worker], (uint32_t)a.n_b * syn * ES);
+  const __amdgpu_buffer_rsrc_t rx = rsrc_of(x_bufs[worker], (uint32_t)a.n_b * sxn * ES);
+  const __amdgpu_buffer_rsrc_t ry = rsrc_of(dy_bufs[worker], (uint32_t)a.n_b * syn * ES);
 
   floatx16 acc[TW];
 #pragma unroll

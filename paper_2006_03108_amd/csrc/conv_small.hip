@@ -19,6 +19,7 @@
 #include <memory>
 #include <vector>
 
+#include "buffer.h"
 #include "common.h"
 #include "conv_mfma.h"
 #include "profile.h"
@@ -42,10 +43,6 @@ struct Wgrad16Args {
   int32_t xcells, dcells;    // LDS cells of the input / dy staging areas
   int64_t slot;              // floats per partial: taps * ci * co + co
 };
-
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
 
 // n / d for n < 2^20 through the reciprocal (set-up code: a few divisions per thread)
 __device__ inline uint32_t div_small(uint32_t n, uint32_t d, float rcp) {

@@ -32,6 +32,7 @@
 #include <mutex>
 #include <memory>
 
+#include "buffer.h"
 #include "common.h"
 #include "conv_mfma.h"
 #include "conv_split.h"
@@ -47,7 +48,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (tensors are < 2 GiB)
 constexpr int kGroupTaps = 10, kFewTaps = 8, kMaxFewColumns = 0xffff;
 
 template <class ArgsPtr>
@@ -65,10 +65,6 @@ __host__ __device__ inline PerWorker derive_of(const WorkerDev& wd, ArgsPtr a) {
     g.os[2] = a->fold;
   }
   return g;
-}
-
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 
 // Bytes of half an LDS plane of the patch (8 channels of PA * 128 cells), of a plane.  The halves lie a multiple of 256

@@ -37,6 +37,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "buffer.h"
 #include "conv_wsplit.h"
 #include "profile.h"
 #include "split_bf16.h"
@@ -45,7 +46,6 @@ namespace distdl {
 
 namespace {
 
-constexpr uint32_t kOob = 0x7ffffff0u;  // buffer offset that always fails the range check (tensors are < 2 GiB)
 constexpr int kNx = 4;                  // input pieces per thread and step
 // Row tiles of a workgroup: seven for each of eight waves, five with three columns and three with four (more sums than
 // that leave a lane's 256 registers).
@@ -70,10 +70,6 @@ struct Args {
   int32_t tiles;               // of 16 rows
   int64_t slot;                // floats of a partial
 };
-
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
 
 __device__ inline bf16x8 operand(const char* first, const char* second) {
   union {

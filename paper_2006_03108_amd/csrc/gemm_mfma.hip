@@ -19,6 +19,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "buffer.h"
 #include "common.h"
 #include "gemm_mfma.h"
 #include "profile.h"
@@ -29,11 +30,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr uint32_t kGemmOob = 0x7ffffff0u;
-
-__device__ inline __amdgpu_buffer_rsrc_t gemm_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
 
 __device__ inline uint32_t f32_to_bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
@@ -140,7 +136,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
   // load cursor: segment, stage within it, and what depends on the segment
   int ls = 0, lin = g_first, l_nst = 0, l_K = 0;
   uint32_t l_lda = 0, l_ldb = 0;
-  __amdgpu_buffer_rsrc_t ra_rs = gemm_rsrc(nullptr, 0), rb_rs = gemm_rsrc(nullptr, 0);
+  __amdgpu_buffer_rsrc_t ra_rs = rsrc_of(nullptr, 0), rb_rs = rsrc_of(nullptr, 0);
   auto enter_segment = [&]() __attribute__((always_inline)) {
     const GemmSeg& sg = gb.seg[ls];
     l_K = sg.K;
@@ -148,8 +144,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
     l_lda = (uint32_t)sg.lda;
     l_ldb = (uint32_t)sg.ldb;
     // resources cover exactly the operand: rows beyond M / N (or k lines beyond K) read as zero
-    ra_rs = gemm_rsrc(sg.a, (uint32_t)(A_KC ? gb.M : sg.K) * sg.lda * ES);
-    rb_rs = gemm_rsrc(sg.b, (uint32_t)(B_KC ? gb.N : sg.K) * sg.ldb * ES);
+    ra_rs = rsrc_of(sg.a, (uint32_t)(A_KC ? gb.M : sg.K) * sg.lda * ES);
+    rb_rs = rsrc_of(sg.b, (uint32_t)(B_KC ? gb.N : sg.K) * sg.ldb * ES);
 #pragma unroll
     for (int i = 0; i < PA; ++i) {
       const int piece = tid + i * 256;
@@ -158,7 +154,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
       } else {
         const int mq = piece % (TILE_M / VE);
         a_goff[i] = ((uint32_t)a_k[i] * l_lda + m0 + mq * VE) * ES;
-        if (m0 + mq * VE >= gb.M) a_goff[i] = kGemmOob;  // columns beyond M (whole pieces: M % VE == 0)
+        if (m0 + mq * VE >= gb.M) a_goff[i] = kOob;  // columns beyond M (whole pieces: M % VE == 0)
       }
     }
 #pragma unroll
@@ -169,7 +165,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
       } else {
         const int nq = piece % (TILE_N / VE);
         b_goff[i] = ((uint32_t)b_k[i] * l_ldb + n0 + nq * VE) * ES;
-        if (n0 + nq * VE >= gb.N) b_goff[i] = kGemmOob;
+        if (n0 + nq * VE >= gb.N) b_goff[i] = kOob;
       }
     }
   };
@@ -194,11 +190,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmBlock* __restr
 #pragma unroll
     for (int i = 0; i < PA; ++i)
       ra[slot][i] = __builtin_amdgcn_raw_buffer_load_b128(
-          ra_rs, (!valid || (A_KC && k0 + a_k[i] >= l_K)) ? kGemmOob : a_goff[i], a_base, 0);
+          ra_rs, (!valid || (A_KC && k0 + a_k[i] >= l_K)) ? kOob : a_goff[i], a_base, 0);
 #pragma unroll
     for (int i = 0; i < PB; ++i)
       rb[slot][i] = __builtin_amdgcn_raw_buffer_load_b128(
-          rb_rs, (!valid || (B_KC && k0 + b_k[i] >= l_K)) ? kGemmOob : b_goff[i], b_base, 0);
+          rb_rs, (!valid || (B_KC && k0 + b_k[i] >= l_K)) ? kOob : b_goff[i], b_base, 0);
   };
   auto stash = [&](int buf, auto slot_c) __attribute__((always_inline)) {
     constexpr int slot = decltype(slot_c)::value;

@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "buffer.h"
 #include "common.h"
 #include "gemm_mfma.h"
 #include "profile.h"
@@ -34,16 +35,11 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr uint32_t kOob = 0x7ffffff0u;  // fails the range check of every buffer (operands are < 2 GiB)
 
 union Frag {
   u32x4 u;
   bf16x8 v;
 };
-
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
 
 template <bool BF16>
 __device__ inline float load_one(const void* p, size_t i) {
